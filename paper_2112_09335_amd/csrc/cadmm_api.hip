@@ -50,9 +50,9 @@ struct cadmm_ctx {
     int32_t* d_perm = nullptr;
     int32_t* d_seg1_pos = nullptr; int32_t* d_seg1_col = nullptr; float* d_seg1_val = nullptr;
     int32_t* d_segc_row = nullptr;
-    // reduction chunk tables of the Z search: [0] many segments per chunk (narrow next layer), [1] few (wide)
-    struct DevChunks { int32_t *unit = nullptr, *kind = nullptr, *begin = nullptr, *end = nullptr, *unit_ptr = nullptr; int32_t n = 0; };
-    DevChunks d_chunks[2];
+    // reduction chunk tables: layer l = 1..L-1 for its Z search, l = L (rows only) for the last-layer solve with backtracking
+    struct DevChunks { int4* tab = nullptr; int32_t* unit_ptr = nullptr; int32_t n = 0; };
+    std::vector<DevChunks> d_chunks;
     int32_t* d_labels = nullptr;
     int32_t* d_pred = nullptr;
     int64_t* d_row_seg_ptr = nullptr;
@@ -78,7 +78,7 @@ struct cadmm_ctx {
     float* P = nullptr;         // n_seg x max next width, the buffer of the layer being searched
     float* Pbuf[2] = {nullptr, nullptr};   // layers alternate: P of layer l stays until layer l+1 is done
     float* gradW = nullptr;
-    float* Wt = nullptr;
+    std::vector<float*> Wt;     // transposes of W_2 .. W_L, kept by the W steps
     float* Bcat = nullptr;      // [W_{l+1}; W_{l+1}^T W_{l+1}] for the low-rank form of the Z gradient
     float* tn_partial = nullptr;
     size_t tn_partial_floats = 0;
@@ -90,8 +90,10 @@ struct cadmm_ctx {
     float* fistaY = nullptr;
     LayerScalars* scalars = nullptr;   // [L+1]
     int32_t* status = nullptr;
-    bool base_valid = false, have_prev = false, dual_valid = false;
-    bool phi_valid = false;      // the penalties of the hidden layers whose gradient is not stored are evaluated too
+    // What the buffers hold at the moment.  base_valid: every H_l and T_l belongs to the current iterate.  gl_valid /
+    // gh_valid: so does G_L / do the G_l of the hidden layers that need one.  scal_valid: so do the readout scalars.
+    // stepped: an iteration has been run since the state was set from outside (there is a dual residual).
+    bool base_valid = false, gl_valid = false, gh_valid = false, scal_valid = false, stepped = false;
     int iter = 0;
     // The pre-activations T_l = A~ Z_{l-1} W_l are carried from one iteration to the next instead of being
     // formed anew: the W step leaves T_l - Q/tau = A~ Z_{l-1}^k W_l^{k+1}, and the Z step of layer l-1 changes
@@ -100,14 +102,14 @@ struct cadmm_ctx {
     // everything is formed again, which bounds the rounding drift.
     int t1_age = -1;
     int t1_refresh = 16;
-    // One iteration captured as a HIP graph, per variant of the launch sequence (base evaluation already
-    // done or not; previous T_L available or not).  Replayed by cadmm_run when the stream is not the
+    // One iteration captured as a HIP graph, per variant of the launch sequence (what of the base evaluation is
+    // already at hand).  Replayed by cadmm_run when the stream is not the
     // default stream; launch-bound problem sizes gain most.
     bool use_graph = true;
     bool use_lowrank = true;
     bool use_speculative = true;
-    struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false; };
-    GraphSlot graphs[2][2][2][2];
+    struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false; };
+    GraphSlot graphs[32];
     // optional per-kernel-class timing with HIP events on the context's stream
     bool prof_on = false;
     struct ProfRec { int cls; hipEvent_t a, b; };
@@ -154,6 +156,24 @@ int max_of(const std::vector<int>& v, int lo, int hi) {
     return m;
 }
 
+// Rows / segments per reduction chunk of layer l: a chunk is one workgroup's share of a pass over N x C_l (its rows) or
+// n_seg x C_{l+1} (its segments).  16384 elements give a workgroup sixteen 16-byte loads per lane and array, enough to
+// drown its fixed costs (three barriers, block sums); smaller problems get smaller chunks down to 2048 elements, so that
+// about a thousand workgroups share the pass and the chip is full.
+struct ChunkShape { int64_t rows, segs; };
+ChunkShape chunk_shape(const cadmm_ctx* c, int l) {
+    auto share = [](int64_t count, int width) {
+        int64_t e = count * width / 1024;
+        e = e < 2048 ? 2048 : e > 16384 ? 16384 : e;
+        e /= width;
+        return e < 1 ? (int64_t)1 : e;
+    };
+    ChunkShape cs;
+    cs.rows = share(c->hg.N, c->C[l]);
+    cs.segs = l < c->L ? share(c->hg.n_seg, c->C[l + 1]) : 0;
+    return cs;
+}
+
 // Assign every device buffer inside the workspace; with base == nullptr only the size is computed.
 size_t layout(cadmm_ctx* c, char* base) {
     const HostGraph& g = c->hg;
@@ -178,15 +198,14 @@ size_t layout(cadmm_ctx* c, char* base) {
     c->d_seg1_col = b.take<int32_t>(g.seg1_pos.size());
     c->d_seg1_val = b.take<float>(g.seg1_pos.size());
     c->d_segc_row = b.take<int32_t>(g.n_seg);
-    const size_t nch = g.chunks.size() > g.chunks_wide.size() ? g.chunks.size() : g.chunks_wide.size();
-    for (int t = 0; t < 2; ++t) {
-        const size_t nt = t == 0 ? g.chunks.size() : g.chunks_wide.size();
-        c->d_chunks[t].unit = b.take<int32_t>(nt);
-        c->d_chunks[t].kind = b.take<int32_t>(nt);
-        c->d_chunks[t].begin = b.take<int32_t>(nt);
-        c->d_chunks[t].end = b.take<int32_t>(nt);
-        c->d_chunks[t].unit_ptr = b.take<int32_t>(g.M + 1);
-        c->d_chunks[t].n = (int32_t)nt;
+    size_t nch = 0;
+    c->d_chunks.assign(L + 1, cadmm_ctx::DevChunks());
+    for (int l = 1; l <= L; ++l) {
+        const ChunkShape cs = chunk_shape(c, l);
+        c->d_chunks[l].n = (int32_t)count_chunks(g, cs.rows, cs.segs);
+        c->d_chunks[l].tab = b.take<int4>(c->d_chunks[l].n);
+        c->d_chunks[l].unit_ptr = b.take<int32_t>(g.M + 1);
+        nch = nch > (size_t)c->d_chunks[l].n ? nch : (size_t)c->d_chunks[l].n;
     }
     c->d_labels = b.take<int32_t>(N);
     c->d_pred = b.take<int32_t>(N);
@@ -225,15 +244,16 @@ size_t layout(cadmm_ctx* c, char* base) {
         tnmax = t > tnmax ? t : tnmax;
     }
     c->gradW = b.take<float>(wmax);
-    c->Wt = b.take<float>(wmax);
+    c->Wt.assign(L + 1, nullptr);
+    for (int l = 2; l <= L; ++l) c->Wt[l] = b.take<float>((size_t)c->C[l - 1] * c->C[l]);
     c->Bcat = b.take<float>((size_t)(max_of(c->C, 0, L) + kLowRankMax) * kLowRankMax);
     c->tn_partial = b.take<float>(tnmax);
     c->tn_partial_floats = tnmax;
-    size_t np = (size_t)kReduceBlocks * kMaxCand;
-    const size_t np2 = nch * (kMaxCand + 3);
+    size_t np = (size_t)kReduceBlocks * kRestCand;
+    const size_t np2 = nch * kRestCand;
     np = np > np2 ? np : np2;
     for (int l = 1; l <= L; ++l) {               // block results of the products that also evaluate a candidate
-        const size_t np3 = (size_t)gemm_nn_blocks(N, c->C[l]) * kMaxCand;
+        const size_t np3 = (size_t)gemm_nn_blocks(N, c->C[l]);
         np = np > np3 ? np : np3;
     }
     c->partials = b.take<double>(np);
@@ -371,46 +391,91 @@ void compute_T(cadmm_ctx* c, int l, bool force = false) {
 // it is formed on the fly from T_l and Z_l; a sweep therefore skips phi_G for it (phi_l is a readout).
 bool gradient_on_the_fly(const cadmm_ctx* c, int l) { return l < c->L && !c->agg_first[l]; }
 
-// H_l, T_l = H_l W_l, phi_l and G_l at the current iterate.  This is both the start of a sweep and the readout of
-// the previous one, so it is computed once per iterate (need_phi: also the penalties a sweep does not need).
-void base_eval(cadmm_ctx* c, bool need_phi) {
+// H_l and T_l = H_l W_l at the current iterate.
+void form_T(cadmm_ctx* c) {
+    if (c->base_valid) return;
+    const bool reuse = t1_reusable(c);
+    for (int l = 1; l <= c->L; ++l) compute_T(c, l);
+    if (!reuse) {                                // every T_l was just formed exactly
+        c->t1_age = 0;
+        c->gl_valid = false;
+    }
+    c->base_valid = true;
+}
+
+// What a sweep starts from: H_l, T_l, the dual step if one is pending, and the gradients G_l that are not formed on the fly.
+void base_eval(cadmm_ctx* c) {
     const int L = c->L;
     const int64_t N = c->hg.N;
-    auto run_phi_G = [&](int l) {
-        const double cnt = (double)N * c->C[l];
-        timed(c, P_PHI_G, 4.0 * cnt * (l == L ? 6 : 3), 0.0, [&] {
-            launch_phi_G(c->stream, c->T[l], c->Z[l], c->U, c->G[l], l == L ? c->TLprev : nullptr,
-                         c->have_prev ? 1 : 0, (l == L && c->u_pending) ? 1 : 0, N * c->C[l], l == L, c->nu, c->rho,
-                         c->partials, c->scalars + l);
+    form_T(c);
+    if (c->u_pending) c->gl_valid = false;
+    if (!c->gl_valid) {
+        timed(c, P_G_ONLY, 4.0 * (double)N * c->C[L] * 4, 0.0, [&] {
+            launch_G_only(c->stream, c->T[L], c->Z[L], c->U, c->G[L], c->u_pending ? 1 : 0, N * c->C[L], 1, c->nu, c->rho);
         });
-    };
-    if (!c->base_valid) {
-        for (int l = 1; l <= L; ++l) {
-            compute_T(c, l);
-            if (!gradient_on_the_fly(c, l) || need_phi) run_phi_G(l);
-        }
-        if (!t1_reusable(c)) c->t1_age = 0;                // every T_l was just formed exactly
         c->u_pending = false;
-        c->dual_valid = c->have_prev;
-        c->have_prev = true;
-        c->base_valid = true;
-        c->phi_valid = need_phi;
-    } else if (need_phi && !c->phi_valid) {
-        for (int l = 1; l <= L; ++l)
-            if (gradient_on_the_fly(c, l)) run_phi_G(l);
-        c->phi_valid = true;
+        c->gl_valid = true;
     }
+    if (!c->gh_valid) {
+        for (int l = 1; l < L; ++l)
+            if (!gradient_on_the_fly(c, l))
+                timed(c, P_G_ONLY, 4.0 * (double)N * c->C[l] * 3, 0.0, [&] {
+                    launch_G_only(c->stream, c->T[l], c->Z[l], nullptr, c->G[l], 0, N * c->C[l], 0, c->nu, c->rho);
+                });
+        c->gh_valid = true;
+    }
+}
+
+// The readout scalars of the current iterate: every phi_l, ||Z_L - T_L||, ||T_L - T_L(previous)||, R.
+void eval_scalars(cadmm_ctx* c) {
+    const int L = c->L;
+    const int64_t N = c->hg.N;
+    form_T(c);
+    if (c->scal_valid) return;
+    for (int l = 1; l <= L; ++l) {
+        const double cnt = (double)N * c->C[l];
+        const bool fly = gradient_on_the_fly(c, l);
+        timed(c, P_PHI_G, 4.0 * cnt * (l == L ? 6 : fly ? 2 : 3), 0.0, [&] {
+            launch_phi_G(c->stream, c->T[l], c->Z[l], c->U, fly ? nullptr : c->G[l], c->TLprev, c->stepped ? 1 : 0,
+                         (l == L && c->u_pending) ? 1 : 0, N * c->C[l], l == L, c->nu, c->rho, c->partials, c->scalars + l);
+        });
+    }
+    c->u_pending = false;
+    c->gl_valid = c->gh_valid = true;
+    launch_risk(c->stream, c->Z[L], c->d_labels, N, c->C[L], c->risk, c->partials, c->scalars + L);
+    c->scal_valid = true;
+}
+
+CarryArgs carry_args(const cadmm_ctx* c, int l) {
+    CarryArgs k;
+    k.P = c->Pbuf[(l - 1) & 1];
+    k.row_seg_ptr = c->d_row_seg_ptr; k.seg_comm = c->d_seg_comm; k.seg_pos = c->d_seg_pos;
+    k.units = c->unitsZ + (size_t)(l - 2) * c->hg.M; k.M = c->hg.M;
+    return k;
+}
+
+double carry_bytes(const cadmm_ctx* c, int l) {
+    return 4.0 * ((double)c->hg.n_seg * c->C[l] + 2.0 * (double)c->hg.N * c->C[l]) + 8.0 * (double)c->hg.n_seg;
 }
 
 // T_l <- A~ Z_{l-1}^{k+1} W_l^{k+1}, from the segment products P of layer l-1 and its accepted theta.
 void carry_T(cadmm_ctx* c, int l) {
     if (c->t1_refresh <= 0) return;
-    const int64_t N = c->hg.N;
-    const int Cl = c->C[l];
-    timed(c, P_T_CARRY, 4.0 * ((double)c->hg.n_seg * Cl + 2.0 * (double)N * Cl) + 8.0 * (double)c->hg.n_seg, 0.0, [&] {
-        launch_t_carry(c->stream, c->T[l], c->Pbuf[(l - 1) & 1], c->d_row_seg_ptr, c->d_seg_comm, c->d_seg_pos, N, Cl,
-                       c->unitsZ + (size_t)(l - 2) * c->hg.M, c->hg.M);
-    });
+    timed(c, P_T_CARRY, carry_bytes(c, l), 0.0,
+          [&] { launch_t_carry(c->stream, c->T[l], carry_args(c, l), c->hg.N, c->C[l]); });
+}
+
+// The searches of later candidates: four (what a search that has moved usually needs), then sixteen, then the rest up to
+// max_backtrack + 1 in all; where a pass over the data is cheap against a launch, all of them at once.
+template <class F>
+void later_candidates(const cadmm_ctx* c, double elements, int tried, F pass) {
+    int left = c->max_bt + 1 - tried;
+    if (left > 0 && elements <= 524288.0) { pass(left); return; }
+    for (int n : {4, kMaxCand, kRestCand}) {
+        if (left <= 0) return;
+        pass(n);
+        left -= n;
+    }
 }
 
 // W_l <- W_l - grad phi_l / tau_l with backtracking on tau_l (Section 3.1), from the T_l, H_l (or Z_{l-1}) and G_l
@@ -420,62 +485,70 @@ void w_update(cadmm_ctx* c, int l) {
     const int64_t N = c->hg.N;
     hipStream_t s = c->stream;
     const SearchParams sp = search_params(c);
-    const int more_passes = (c->max_bt + kMaxCand - 1) / kMaxCand;
-    {
-        const int K = c->C[l - 1], Cl = c->C[l];
-        const int64_t count = N * Cl;
-        const int last = (l == L);
-        Unit* unit = c->unitsW + (l - 1);
-        // grad phi = (A~ Z_{l-1})^T G_l = Z_{l-1}^T (A~ G_l)   (A~ is symmetric)
-        const float* left = c->H[l];
-        const float* right = c->G[l];
-        if (c->agg_first[l]) {
-            aggregate(c, c->G[l], c->H[l], Cl, SpmmEpilogue());
-            left = c->Z[l - 1];
-            right = c->H[l];
-        }
-        const bool fly = gradient_on_the_fly(c, l);    // G_l = nu (relu(T_l) - Z_l) 1[T_l > 0] formed inside the product
-        timed(c, Cl > 32 ? P_GEMM_TN : P_GEMM_TN_32,
-              4.0 * ((double)N * K + (double)N * Cl * (fly ? 2 : 1) + (double)K * Cl), 2.0 * (double)N * K * Cl,
-              [&] {
-                  if (fly) launch_gemm_tn(s, left, c->T[l], c->gradW, N, K, Cl, c->tn_partial, c->Z[l], c->nu);
-                  else launch_gemm_tn(s, left, right, c->gradW, N, K, Cl, c->tn_partial);
-              });
-        timed(c, P_OTHER, 8.0 * K * Cl, 0.0, [&] { launch_w_norms(s, c->gradW, c->W[l], K * Cl, unit, c->partials, sp); });
-        float* Q = c->G[l];                                                          // G_l is no longer needed
-        // T(W - g/tau) = T - Q/tau with Q = A~ Z_{l-1} gradW
-        // In a wide hidden layer the product that forms Q also evaluates the first candidate of the search and
-        // takes the step on T_l speculatively (tau rarely changes once found); later kernels repair it if needed.
-        const bool spec = c->use_speculative && !c->agg_first[l] && !last && Cl > 32;
-        if (c->agg_first[l]) {
-            gemm_nn(c, c->Z[l - 1], c->gradW, c->tmpV, N, K, Cl);
-            aggregate(c, c->tmpV, Q, Cl, SpmmEpilogue());
-        } else if (spec) {
-            GemmEpilogue ge;
-            ge.kind = 2; ge.Zl = c->Z[l]; ge.nu = c->nu; ge.Tio = c->T[l]; ge.unit = unit; ge.partials = c->partials;
-            timed(c, P_GEMM_NN_128_TRIAL, 4.0 * ((double)N * K + (double)K * Cl + 3.0 * (double)count), 2.0 * (double)N * K * Cl,
-                  [&] {
-                      launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, ge);
-                      launch_w_trial_finish(s, c->partials, (int)gemm_nn_blocks(N, Cl), sp, unit, c->status);
-                      GemmEpilogue again;          // Q itself, only if the step was taken ahead and then rejected
-                      again.unit = unit;
-                      launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, again);
-                  });
-        } else {
-            gemm_nn(c, c->H[l], c->gradW, Q, N, K, Cl);
-        }
-        // one pass reads T0, Q, Z_l (and U for the last layer); passes after an accepted one return at once
-        timed(c, P_W_TRIAL, spec ? 0.0 : 4.0 * (double)count * (last ? 4 : 3), 0.0, [&] {
-            if (!spec) launch_w_trial(s, c->T[l], Q, c->Z[l], c->U, count, last, 1, sp, unit, c->partials, c->status);
-            for (int p = 0; p < more_passes; ++p)
-                launch_w_trial(s, c->T[l], Q, c->Z[l], c->U, count, last, kMaxCand, sp, unit, c->partials, c->status,
-                               spec ? 1 : 0);
-        });
-        timed(c, P_W_STEP, 4.0 * ((spec ? 0.0 : 3.0) * (double)count + 3.0 * K * Cl), 0.0, [&] {
-            // W^{k+1}; T_l = A~ Z^k W^{k+1}
-            launch_w_step(s, c->W[l], c->gradW, K * Cl, c->T[l], Q, count, unit, spec ? 1 : 0);
-        });
+    const int K = c->C[l - 1], Cl = c->C[l];
+    const int64_t count = N * Cl;
+    const int last = (l == L);
+    Unit* unit = c->unitsW + (l - 1);
+    // grad phi = (A~ Z_{l-1})^T G_l = Z_{l-1}^T (A~ G_l)   (A~ is symmetric)
+    const float* left = c->H[l];
+    const float* right = c->G[l];
+    if (c->agg_first[l]) {
+        aggregate(c, c->G[l], c->H[l], Cl, SpmmEpilogue());
+        left = c->Z[l - 1];
+        right = c->H[l];
     }
+    const bool fly = gradient_on_the_fly(c, l);    // G_l = nu (relu(T_l) - Z_l) 1[T_l > 0] formed inside the product
+    int n_norms = 0;
+    timed(c, Cl > 32 ? P_GEMM_TN : P_GEMM_TN_32,
+          4.0 * ((double)N * K + (double)N * Cl * (fly ? 2 : 1) + (double)K * Cl), 2.0 * (double)N * K * Cl,
+          [&] {
+              n_norms = launch_gemm_tn(s, left, fly ? c->T[l] : right, c->gradW, N, K, Cl, c->tn_partial,
+                                       fly ? c->Z[l] : nullptr, c->nu, c->W[l], c->partials);
+          });
+    timed(c, P_OTHER, 16.0 * n_norms, 0.0, [&] { launch_w_begin(s, c->partials, n_norms, unit, sp); });
+    float* Q = c->G[l];                                                          // G_l is no longer needed
+    // T(W - g/tau) = T - Q/tau with Q = A~ Z_{l-1} gradW
+    // In a wide hidden layer the product that forms Q also evaluates the first candidate of the search and
+    // takes the step on T_l speculatively (tau rarely changes once found); later kernels repair it if needed.
+    const bool spec = c->use_speculative && !c->agg_first[l] && !last && Cl > 32;
+    if (c->agg_first[l]) {
+        gemm_nn(c, c->Z[l - 1], c->gradW, c->tmpV, N, K, Cl);
+        aggregate(c, c->tmpV, Q, Cl, SpmmEpilogue());
+    } else if (spec) {
+        GemmEpilogue ge;
+        ge.kind = 2; ge.Zl = c->Z[l]; ge.nu = c->nu; ge.Tio = c->T[l]; ge.unit = unit; ge.partials = c->partials;
+        timed(c, P_GEMM_NN_128_TRIAL, 4.0 * ((double)N * K + (double)K * Cl + 3.0 * (double)count), 2.0 * (double)N * K * Cl,
+              [&] {
+                  launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, ge);
+                  launch_w_trial_finish(s, c->partials, (int)gemm_nn_blocks(N, Cl), sp, unit, c->status);
+                  GemmEpilogue again;          // Q itself, only if the step was taken ahead and then rejected
+                  again.unit = unit;
+                  launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, again);
+              });
+    } else {
+        gemm_nn(c, c->H[l], c->gradW, Q, N, K, Cl);
+    }
+    // one pass reads T0, Q, Z_l (and U for the last layer); passes after an accepted one return at once
+    timed(c, P_W_TRIAL, spec ? 0.0 : 4.0 * (double)count * (last ? 4 : 3), 0.0, [&] {
+        if (last) {
+            launch_w_last_search(s, c->T[l], Q, c->Z[l], c->U, count, sp, unit, c->partials, c->status);
+            return;
+        }
+        if (!spec) launch_w_trial(s, c->T[l], Q, c->Z[l], count, 1, sp, unit, c->partials, c->status);
+        later_candidates(c, (double)count, 1, [&](int n) {
+            launch_w_trial(s, c->T[l], Q, c->Z[l], count, n, sp, unit, c->partials, c->status, spec ? 1 : 0);
+        });
+    });
+    timed(c, P_W_STEP, 4.0 * ((spec ? 0.0 : last ? 7.0 : 3.0) * (double)count + 3.0 * K * Cl), 0.0, [&] {
+        // W^{k+1}; T_l = A~ Z^k W^{k+1}; last layer: G_L of that T_L for the Z step of layer L-1
+        if (last)
+            launch_w_step_last(s, c->W[l], c->Wt[l], c->gradW, K, Cl, c->T[l], Q, count, unit, c->Z[l], c->U, c->G[l],
+                               c->schedule == 1 ? nullptr : c->TLprev, c->rho);
+        else
+            launch_w_step(s, c->W[l], c->Wt[l], c->gradW, K, Cl, c->T[l], Q, count, unit, spec ? 1 : 0);
+    });
+    if (last) c->gl_valid = true;
+    else c->gh_valid = false;
 }
 
 // Z_{l,m} <- Z_{l,m} - grad psi_{l,m} / theta_{l,m} for every community of hidden layer l (Appendix A, Eqs. 3, 4, 6-8),
@@ -486,93 +559,85 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     const int M = c->hg.M;
     hipStream_t s = c->stream;
     const SearchParams sp = search_params(c);
-    const int more_passes = (c->max_bt + kMaxCand - 1) / kMaxCand;
-    {
-        const int Cl = c->C[l], Cn = c->C[l + 1];
-        const int next_last = (l + 1 == L);
-        Unit* units = c->unitsZ + (size_t)(l - 1) * M;
-        c->P = c->Pbuf[l & 1];
+    const int Cl = c->C[l], Cn = c->C[l + 1];
+    const int next_last = (l + 1 == L);
+    Unit* units = c->unitsZ + (size_t)(l - 1) * M;
+    const float* Wt = c->Wt[l + 1];
+    c->P = c->Pbuf[l & 1];
+    if (!next_last || !c->gl_valid)                // (the W step of the last layer leaves G_L)
         timed(c, P_G_ONLY, 4.0 * (double)N * Cn * (next_last ? 4 : 3), 0.0, [&] {
-            launch_G_only(s, c->T[l + 1], c->Z[l + 1], c->U, c->G[l + 1], N * Cn, next_last, c->nu, c->rho);
+            launch_G_only(s, c->T[l + 1], c->Z[l + 1], c->U, c->G[l + 1], 0, N * Cn, next_last, c->nu, c->rho);
         });
-        timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] { launch_transpose(s, c->W[l + 1], c->Wt, Cl, Cn); });
-        // grad psi (all communities at once) = nu (Z_l - relu(T_l)) + A~ G_{l+1} W_{l+1}^T; aggregate on the
-        // narrower of the two widths, the penalty term rides in the epilogue of whichever kernel comes last.
-        // With a very narrow next layer the gradient is never stored: its consumers (the product with
-        // W_{l+1}, the search, the step) rebuild it per element from Z_l, T_l and the N x C_{l+1} factor
-        // A~ G_{l+1}, which removes a full write and two full reads of an N x C_l matrix.
-        const bool lowrank = c->use_lowrank && Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
-        if (lowrank) {
-            aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
-            timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] {
-                launch_relu(s, c->W[l + 1], c->Bcat, (int64_t)Cl * Cn, 0);             // rows 0..Cl: W_{l+1}
-                launch_gemm_nn(s, c->Wt, c->W[l + 1], c->Bcat + (size_t)Cl * Cn, Cn, Cl, Cn);   // then W^T W
-            });
-        } else if (Cn < Cl) {
-            aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
-            GemmEpilogue ge;
-            ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu;
-            gemm_nn(c, c->tmpA, c->Wt, c->tmpB, N, Cn, Cl, ge);
-        } else {
-            gemm_nn(c, c->G[l + 1], c->Wt, c->tmpA, N, Cn, Cl);                      // G_{l+1} W_{l+1}^T
-            SpmmEpilogue epi;
-            epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu;
-            aggregate(c, c->tmpA, c->tmpB, Cl, epi);
-        }
-        if (lowrank)
-            timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * (Cl + Cn) * Cn, [&] {
-                launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->Bcat, c->tmpV, N, Cl, Cn, Cn, c->nu);
-            });
-        else
-            gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn);                    // grad W_{l+1}
-        aggregate_segments(c, c->tmpV, c->P, Cn);                                    // A~_{r,m} (grad W) per segment
-        launch_reset_units(s, units, M, sp);
-        ZTrialArgs a;
-        const cadmm_ctx::DevChunks& ct = c->d_chunks[Cn > 32 ? 1 : 0];        // a segment's row of P and T_{l+1} has Cn columns
-        a.chunk_unit = ct.unit; a.chunk_kind = ct.kind;
-        a.chunk_begin = ct.begin; a.chunk_end = ct.end;
-        a.n_chunks = ct.n;
-        a.unit_chunk_ptr = ct.unit_ptr; a.M = M;
-        a.segc_row = c->d_segc_row;
-        a.Zl = c->Z[l]; a.gradZ = lowrank ? nullptr : c->tmpB; a.Tl = c->T[l]; a.Cl = Cl;
-        a.SG = c->tmpA; a.Wt = c->Wt;
-        a.Tn = c->T[l + 1]; a.Zn = c->Z[l + 1]; a.U = c->U; a.P = c->P; a.Cn = Cn;
-        a.Gn = c->G[l + 1];
-        a.next_is_last = next_last;
-        a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
-        // one pass reads Z_l, grad, T_l over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
-        const double zt_bytes = 4.0 * ((lowrank ? 2.0 : 3.0) * (double)N * Cl + (lowrank ? (double)N * Cn : 0.0) +
-                                       (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;
-        timed(c, P_Z_TRIAL, zt_bytes, 0.0, [&] {
-            a.first_pass = 1; a.ncand = 1;
-            launch_z_trial(s, a);
-            a.first_pass = 0; a.ncand = kMaxCand;
-            for (int p = 0; p < more_passes; ++p) launch_z_trial(s, a);
-        });
-        timed(c, P_Z_STEP, 4.0 * (3.0 * (double)N * Cl + (double)N + (lowrank ? (double)N * Cn : 0.0)), 0.0, [&] {
-            if (lowrank)
-                launch_z_step_lowrank(s, c->Z[l], c->T[l], c->tmpA, c->Wt, c->nu, c->d_row_comm, N, Cl, Cn, units, c->hg.M);
-            else
-                launch_z_step(s, c->Z[l], c->tmpB, c->d_row_comm, N, Cl, units, c->hg.M);
-        });
+    // grad psi (all communities at once) = nu (Z_l - relu(T_l)) + A~ G_{l+1} W_{l+1}^T; aggregate on the
+    // narrower of the two widths, the penalty term rides in the epilogue of whichever kernel comes last.
+    // With a very narrow next layer the gradient is never stored: its consumers (the product with
+    // W_{l+1}, the search, the step) rebuild it per element from Z_l, T_l and the N x C_{l+1} factor
+    // A~ G_{l+1}, which removes a full write and two full reads of an N x C_l matrix.
+    const bool lowrank = c->use_lowrank && Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
+    if (lowrank) {
+        aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
+        timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] { launch_lowrank_operand(s, c->W[l + 1], c->Bcat, Cl, Cn); });
+    } else if (Cn < Cl) {
+        aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
+        GemmEpilogue ge;
+        ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu;
+        gemm_nn(c, c->tmpA, Wt, c->tmpB, N, Cn, Cl, ge);
+    } else {
+        gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl);                         // G_{l+1} W_{l+1}^T
+        SpmmEpilogue epi;
+        epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu;
+        aggregate(c, c->tmpA, c->tmpB, Cl, epi);
     }
+    if (lowrank)
+        timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * (Cl + Cn) * Cn, [&] {
+            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->Bcat, c->tmpV, N, Cl, Cn, Cn, c->nu);
+        });
+    else
+        gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn);                    // grad W_{l+1}
+    aggregate_segments(c, c->tmpV, c->P, Cn);                                    // A~_{r,m} (grad W) per segment
+    ZTrialArgs a;
+    const cadmm_ctx::DevChunks& ct = c->d_chunks[l];
+    a.chunks = ct.tab;
+    a.n_chunks = ct.n;
+    a.unit_chunk_ptr = ct.unit_ptr; a.M = M;
+    a.segc_row = c->d_segc_row;
+    a.Zl = c->Z[l]; a.gradZ = lowrank ? nullptr : c->tmpB; a.Tl = c->T[l]; a.Cl = Cl;
+    a.SG = c->tmpA; a.Wt = Wt;
+    a.Tn = c->T[l + 1]; a.Zn = c->Z[l + 1]; a.P = c->P; a.Cn = Cn;
+    a.Gn = c->G[l + 1];
+    a.next_is_last = next_last;
+    a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
+    // one pass reads Z_l, grad, T_l over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
+    const double zt_bytes = 4.0 * ((lowrank ? 2.0 : 3.0) * (double)N * Cl + (lowrank ? (double)N * Cn : 0.0) +
+                                   (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;
+    timed(c, P_Z_TRIAL, zt_bytes, 0.0, [&] {
+        launch_z_first(s, a);
+        if (!next_last) later_candidates(c, (double)c->hg.n_seg * Cn, 1, [&](int n) { launch_z_more(s, a, n); });
+    });
+    timed(c, P_Z_STEP, 4.0 * (3.0 * (double)N * Cl + (double)N + (lowrank ? (double)N * Cn : 0.0)), 0.0, [&] {
+        if (lowrank) launch_z_step_lowrank(s, c->Z[l], c->T[l], c->tmpA, Wt, c->nu, c->d_row_comm, N, Cl, Cn, units, M);
+        else launch_z_step(s, c->Z[l], c->tmpB, c->d_row_comm, N, Cl, units, M);
+    });
 }
 
 // last layer Z_L (Eq. 5) and, for dual_form 0, the dual step (Eq. 2), both from Z_L^k, U^k and the T_L in memory
-void last_layer_update(cadmm_ctx* c) {
+// carry: T_L is also brought to the new Z_{L-1} and, with dual_form 0, the G_L of the next iteration is left.
+void last_layer_update(cadmm_ctx* c, bool carry) {
     const int L = c->L;
     const int64_t N = c->hg.N;
     if (c->fista_mode == 1 && c->J > 0) {
         // FISTA with backtracking on the blocks Z_{L,m}: J + 1 passes over the rows, a device-side search per step
         FistaArgs a;
         a.ZL = c->Z[L]; a.U = c->U; a.TL = c->T[L]; a.Xb = c->fistaX; a.Yb = c->fistaY; a.labels = c->d_labels;
-        const cadmm_ctx::DevChunks& ct = c->d_chunks[0];                      // only the chunks of rows are used here
-        a.chunk_unit = ct.unit; a.chunk_kind = ct.kind; a.chunk_begin = ct.begin; a.chunk_end = ct.end;
+        const cadmm_ctx::DevChunks& ct = c->d_chunks[L];                      // chunks of rows
+        a.chunks = ct.tab;
         a.n_chunks = ct.n; a.unit_chunk_ptr = ct.unit_ptr; a.M = c->hg.M;
         a.CL = c->C[L]; a.risk = c->risk; a.J = c->J; a.update_u = c->dual_form == 0 ? 1 : 0; a.rho = c->rho;
         a.sp = search_params(c); a.units = c->unitsF; a.partials = c->partials; a.status = c->status;
-        // candidates per step: 1 (16 in stage 0), then a pass of 4, then passes of 16 until max_backtrack + 1 are covered
-        const int wide_passes = (c->max_bt + kMaxCand - 1) / kMaxCand;
+        // Candidates per step: sixteen in stage 0, where L climbs from rho; then the current L, a pass of four, a pass
+        // of the rest.  Where the rows are few the pass of four costs its launch and not its arithmetic: its candidates
+        // are then evaluated with the first.
+        const int first = (double)N * c->C[L] <= 2.0e6 ? 4 : 1;
         timed(c, P_LAST_LAYER, 4.0 * (double)N * c->C[L] * (3.0 + 7.0 * (c->J - 1) + 6.0) + 4.0 * (double)N * (c->J + 1), 0.0, [&] {
             double t = 1.0;
             for (int stage = 0; stage <= c->J; ++stage) {
@@ -582,19 +647,26 @@ void last_layer_update(cadmm_ctx* c) {
                     mom = (float)((t - 1.0) / tn);
                     t = tn;
                 }
-                launch_fista_stage(c->stream, a, stage, 0, mom);
+                const int n0 = stage == 0 ? kMaxCand : stage < c->J ? first : 1;
+                launch_fista_stage(c->stream, a, stage, 0, n0, mom);
                 if (stage < c->J) {
-                    if (stage > 0) launch_fista_stage(c->stream, a, stage, 1, 0.f);
-                    for (int p = stage == 0 ? 1 : 0; p < wide_passes; ++p) launch_fista_stage(c->stream, a, stage, 2, 0.f);
+                    int left = c->max_bt + 1 - n0;
+                    if (n0 == 1 && left > 0) { launch_fista_stage(c->stream, a, stage, 1, 4, 0.f); left -= 4; }
+                    if (left > 0) launch_fista_stage(c->stream, a, stage, 1, left > 4 ? left : 5, 0.f);
                 }
             }
         });
+        if (carry) carry_T(c, L);
         return;
     }
-    timed(c, P_LAST_LAYER, 4.0 * (5.0 * (double)N * c->C[L] + (double)N), 0.0, [&] {
+    const bool with_carry = carry && c->t1_refresh > 0;
+    const CarryArgs k = with_carry ? carry_args(c, L) : CarryArgs();
+    timed(c, P_LAST_LAYER, 4.0 * (5.0 * (double)N * c->C[L] + (double)N) + (with_carry ? carry_bytes(c, L) : 0.0), 0.0, [&] {
         launch_last_layer(c->stream, c->Z[L], c->U, c->T[L], c->d_labels, N, c->C[L], c->risk, c->rho, c->J,
-                          c->dual_form == 0 ? 1 : 0);
+                          c->dual_form == 0 ? 1 : 0, with_carry ? &k : nullptr,
+                          c->dual_form == 0 ? c->G[L] : nullptr);
     });
+    if (with_carry && c->dual_form == 0) c->gl_valid = true;
 }
 
 // Serial baseline of Section 4.1 read as a Gauss-Seidel pass: for l = 1..L first W_l, then Z_l, each from the newest
@@ -602,44 +674,46 @@ void last_layer_update(cadmm_ctx* c) {
 void sweep_layer_by_layer(cadmm_ctx* c) {
     const int L = c->L;
     const int64_t N = c->hg.N;
-    base_eval(c, false);
+    base_eval(c);
+    launch_relu(c->stream, c->T[L], c->TLprev, N * c->C[L], 0);       // T_L is formed anew below: keep the old one
     for (int l = 1; l <= L; ++l) {
         if (l >= 2) {
             compute_T(c, l, true);
             if (!gradient_on_the_fly(c, l))
                 timed(c, P_G_ONLY, 4.0 * (double)N * c->C[l] * (l == L ? 4 : 3), 0.0, [&] {
-                    launch_G_only(c->stream, c->T[l], c->Z[l], c->U, c->G[l], N * c->C[l], l == L, c->nu, c->rho);
+                    launch_G_only(c->stream, c->T[l], c->Z[l], c->U, c->G[l], 0, N * c->C[l], l == L, c->nu, c->rho);
                 });
         }
         w_update(c, l);
         if (l < L) z_update_hidden(c, l);
-        else last_layer_update(c);
+        else last_layer_update(c, false);
     }
-    if (c->t1_age >= 0) c->t1_age++;
-    if (c->dual_form == 1) c->u_pending = true;
-    c->iter++;
-    c->base_valid = false;
+    c->gl_valid = false;
 }
 
 // Algorithm 1: every W_l from (W^k, Z^k, U^k), then every Z_{l,m} from (W^{k+1}, Z^k, U^k), then U.
 void sweep(cadmm_ctx* c) {
-    if (c->schedule == 1) { sweep_layer_by_layer(c); return; }
-    const int L = c->L;
-    base_eval(c, false);
-    for (int l = 1; l <= L; ++l) w_update(c, l);
-    // Ascending l keeps the Z update Jacobi although Z_l is overwritten in place: layer l reads Z_{l+1}^k
-    // (not yet touched) and T_l, T_{l+1}, which were formed from Z^k before any Z changed.
-    for (int l = 1; l <= L - 1; ++l) {
-        z_update_hidden(c, l);
-        // T_l is not read again in this sweep: bring it to the new Z_{l-1} (P and theta of layer l-1)
-        if (l >= 2) carry_T(c, l);
+    if (c->schedule == 1) {
+        sweep_layer_by_layer(c);
+    } else {
+        const int L = c->L;
+        base_eval(c);
+        for (int l = 1; l <= L; ++l) w_update(c, l);
+        // Ascending l keeps the Z update Jacobi although Z_l is overwritten in place: layer l reads Z_{l+1}^k
+        // (not yet touched) and T_l, T_{l+1}, which were formed from Z^k before any Z changed.
+        for (int l = 1; l <= L - 1; ++l) {
+            z_update_hidden(c, l);
+            // T_l is not read again in this sweep: bring it to the new Z_{l-1} (P and theta of layer l-1)
+            if (l >= 2) carry_T(c, l);
+        }
+        c->gl_valid = false;                         // G_L belongs to the old Z_L and U now
+        last_layer_update(c, true);
     }
-    last_layer_update(c);
-    carry_T(c, L);
-    if (c->t1_age >= 0) c->t1_age++;
     if (c->dual_form == 1) c->u_pending = true;      // applied by the next base evaluation, on the new iterates
+    c->gh_valid = c->base_valid = c->scal_valid = false;
+    c->stepped = true;
+    if (c->t1_age >= 0) c->t1_age++;
     c->iter++;
-    c->base_valid = false;
 }
 
 int check_launch(cadmm_ctx* c, const char* where) {
@@ -667,14 +741,11 @@ int upload_rows(cadmm_ctx* c, const float* src, int on_device, int C, float* dst
 }
 
 void drop_graphs(cadmm_ctx* c) {
-    for (auto& cube : c->graphs)
-        for (auto& plane : cube)
-            for (auto& row : plane)
-                for (auto& slot : row) {
-                    if (slot.exec) (void)hipGraphExecDestroy(slot.exec);
-                    slot.exec = nullptr;
-                    slot.tried = false;
-                }
+    for (auto& slot : c->graphs) {
+        if (slot.exec) (void)hipGraphExecDestroy(slot.exec);
+        slot.exec = nullptr;
+        slot.tried = false;
+    }
 }
 
 }  // namespace
@@ -722,7 +793,7 @@ int cadmm_build_graph(cadmm_ctx* c, int64_t N, int64_t n_edges, const int32_t* s
                       const int32_t* comm) {
     if (!c) return CADMM_EINVAL;
     if (c->has_ws) return fail(c, CADMM_EORDER, "graph cannot change after the workspace is set");
-    std::string e = build_host_graph(c->hg, N, n_edges, src, dst, M, comm, kChunkRows);
+    std::string e = build_host_graph(c->hg, N, n_edges, src, dst, M, comm);
     if (!e.empty()) { c->has_graph = false; return fail(c, CADMM_EINVAL, e); }
     c->has_graph = true;
     return CADMM_OK;
@@ -839,14 +910,16 @@ int cadmm_set_workspace(cadmm_ctx* c, void* dev_ptr, size_t bytes) {
     HIP_TRY(c, upload(s, c->d_seg1_col, g.seg1_col));
     HIP_TRY(c, upload(s, c->d_seg1_val, g.seg1_val));
     HIP_TRY(c, upload(s, c->d_segc_row, g.segc_row));
-    for (int t = 0; t < 2; ++t) {
-        std::vector<int32_t> cu, ck, cb, ce;
-        for (const Chunk& ch : (t == 0 ? g.chunks : g.chunks_wide)) { cu.push_back(ch.unit); ck.push_back(ch.kind); cb.push_back(ch.begin); ce.push_back(ch.end); }
-        HIP_TRY(c, upload(s, c->d_chunks[t].unit, cu));
-        HIP_TRY(c, upload(s, c->d_chunks[t].kind, ck));
-        HIP_TRY(c, upload(s, c->d_chunks[t].begin, cb));
-        HIP_TRY(c, upload(s, c->d_chunks[t].end, ce));
-        HIP_TRY(c, upload(s, c->d_chunks[t].unit_ptr, t == 0 ? g.unit_chunk_ptr : g.unit_chunk_ptr_wide));
+    std::vector<std::vector<Chunk>> tabs(c->L + 1);                 // alive until the stream has been waited for below
+    std::vector<std::vector<int32_t>> ptrs(c->L + 1);
+    for (int l = 1; l <= c->L; ++l) {
+        static_assert(sizeof(Chunk) == sizeof(int4), "chunks are read as int4");
+        const ChunkShape cs = chunk_shape(c, l);
+        build_chunks(g, cs.rows, cs.segs, tabs[l], ptrs[l]);
+        if ((int32_t)tabs[l].size() != c->d_chunks[l].n) return fail(c, CADMM_EINVAL, "internal error: reduction chunks");
+        if (!tabs[l].empty())
+            HIP_TRY(c, hipMemcpyAsync(c->d_chunks[l].tab, tabs[l].data(), tabs[l].size() * sizeof(Chunk), hipMemcpyHostToDevice, s));
+        HIP_TRY(c, upload(s, c->d_chunks[l].unit_ptr, ptrs[l]));
     }
     HIP_TRY(c, upload(s, c->d_row_seg_ptr, g.row_seg_ptr));
     HIP_TRY(c, upload(s, c->d_seg_comm, g.seg_comm));
@@ -888,6 +961,7 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
                                   hipMemcpyHostToDevice, s));
     }
     c->t1_age = -1;
+    for (int l = 2; l <= L; ++l) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
     aggregate(c, c->Z[0], c->H[1], c->C[0], SpmmEpilogue());      // A~ Z_0 never changes
     for (int l = 1; l <= L; ++l) {
         compute_T(c, l);
@@ -900,9 +974,9 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
     launch_fill_units(s, c->unitsF, c->hg.M, (double)c->rho);
     HIP_TRY(c, hipStreamSynchronize(s));                           // W0 host buffers may be freed by the caller
     c->iter = 0;
-    c->base_valid = false;
-    c->have_prev = false;
-    c->dual_valid = false;
+    c->base_valid = true;                                          // the forward pass left every H_l and T_l
+    c->t1_age = 0;
+    c->gl_valid = c->gh_valid = c->scal_valid = c->stepped = false;
     c->u_pending = false;
     c->has_init = true;
     return check_launch(c, "init");
@@ -914,36 +988,37 @@ int cadmm_run(cadmm_ctx* c, int32_t k) {
     for (int i = 0; i < k; ++i) {
         const bool graphable = c->use_graph && c->stream != nullptr && !c->prof_on;
         if (!graphable) { sweep(c); continue; }
-        const bool t1_skip = !c->base_valid && t1_reusable(c);
-        cadmm_ctx::GraphSlot& slot =
-            c->graphs[c->base_valid ? 1 : 0][c->have_prev ? 1 : 0][c->u_pending ? 1 : 0][t1_skip ? 1 : 0];
+        // what the launch sequence of an iteration depends on
+        const bool reuse = !c->base_valid && t1_reusable(c);
+        const bool gl = c->gl_valid && (c->base_valid || reuse);
+        cadmm_ctx::GraphSlot& slot = c->graphs[(c->base_valid ? 1 : 0) | (reuse ? 2 : 0) | (gl ? 4 : 0) | (c->gh_valid ? 8 : 0) |
+                                               (c->u_pending ? 16 : 0)];
         if (!slot.tried) {
             // capture this variant once; the capture enqueues nothing, sweep() only advances the host flags
             slot.tried = true;
-            const bool bv = c->base_valid, hp = c->have_prev, dv = c->dual_valid, up = c->u_pending;
+            const bool bv = c->base_valid, glv = c->gl_valid, ghv = c->gh_valid, scv = c->scal_valid, st = c->stepped, up = c->u_pending;
             const int it = c->iter, age = c->t1_age;
             if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
                 sweep(c);
+                slot.gl_after = c->gl_valid;
                 hipGraph_t graph = nullptr;
                 hipError_t e = hipStreamEndCapture(c->stream, &graph);
                 if (e == hipSuccess && graph) {
                     if (hipGraphInstantiate(&slot.exec, graph, nullptr, nullptr, 0) != hipSuccess) slot.exec = nullptr;
                     (void)hipGraphDestroy(graph);
                 }
-                c->base_valid = bv; c->have_prev = hp; c->dual_valid = dv; c->u_pending = up; c->iter = it;
-                c->t1_age = age;
+                c->base_valid = bv; c->gl_valid = glv; c->gh_valid = ghv; c->scal_valid = scv; c->stepped = st; c->u_pending = up;
+                c->iter = it; c->t1_age = age;
             }
             (void)hipGetLastError();
         }
         if (slot.exec && hipGraphLaunch(slot.exec, c->stream) == hipSuccess) {
             // the host-side bookkeeping sweep() would have done
-            if (!c->base_valid) {
-                c->dual_valid = c->have_prev;
-                c->have_prev = true;
-                if (!t1_skip) c->t1_age = 0;
-            }
+            if (!c->base_valid && !reuse) c->t1_age = 0;
             if (c->t1_age >= 0) c->t1_age++;
-            c->base_valid = false;
+            c->gl_valid = slot.gl_after;
+            c->base_valid = c->gh_valid = c->scal_valid = false;
+            c->stepped = true;
             c->u_pending = c->dual_form == 1;
             c->iter++;
         } else {
@@ -957,8 +1032,7 @@ int cadmm_eval(cadmm_ctx* c, cadmm_stats* out, double* layer_penalty) {
     if (!c || !out) return CADMM_EINVAL;
     if (!c->has_init) return fail(c, CADMM_EORDER, "init first");
     const int L = c->L;
-    base_eval(c, true);
-    launch_risk(c->stream, c->Z[L], c->d_labels, c->hg.N, c->C[L], c->risk, c->partials, c->scalars + L);
+    eval_scalars(c);
     std::vector<LayerScalars> sc(L + 1);
     int32_t st[4] = {0, 0, 0, 0};
     HIP_TRY(c, hipMemcpyAsync(sc.data(), c->scalars, (L + 1) * sizeof(LayerScalars), hipMemcpyDeviceToHost, c->stream));
@@ -973,7 +1047,7 @@ int cadmm_eval(cadmm_ctx* c, cadmm_stats* out, double* layer_penalty) {
     out->objective = sc[L].risk + pen;
     out->lagrangian = out->objective + sc[L].phi;
     out->primal_res = std::sqrt(sc[L].res2);
-    out->dual_res = c->dual_valid ? (double)c->rho * std::sqrt(sc[L].dT2) : 0.0;
+    out->dual_res = c->stepped ? (double)c->rho * std::sqrt(sc[L].dT2) : 0.0;
     out->iter = c->iter;
     out->status = st[0];
     if (!std::isfinite(out->lagrangian)) out->status |= CADMM_STATUS_NONFINITE;
@@ -1002,8 +1076,9 @@ int cadmm_predict(cadmm_ctx* c, int32_t* pred, float* logits, double* accuracy) 
             in = c->G[l];
         }
     }
-    c->base_valid = false;
-    c->t1_age = -1;                 // the T buffers now hold the forward pass, not images of the state
+    // the T and G buffers now hold the forward pass, not images of the state
+    c->base_valid = c->gl_valid = c->gh_valid = c->scal_valid = false;
+    c->t1_age = -1;
     launch_argmax_rows(s, c->T[L], c->d_pred, N, c->C[L]);
     std::vector<int32_t> p((size_t)N);
     HIP_TRY(c, hipMemcpyAsync(p.data(), c->d_pred, N * sizeof(int32_t), hipMemcpyDeviceToHost, s));
@@ -1041,7 +1116,7 @@ int cadmm_get_Z(cadmm_ctx* c, int32_t l, float* dst) {
 int cadmm_get_U(cadmm_ctx* c, float* dst) {
     if (!c || !dst) return CADMM_EINVAL;
     if (!c->has_init) return fail(c, CADMM_EORDER, "init first");
-    if (c->u_pending) base_eval(c, false);   // dual_form 1: the step of the last sweep rides on the base evaluation
+    if (c->u_pending) base_eval(c);          // dual_form 1: the step of the last sweep rides on the base evaluation
     return download_rows(c, c->U, c->C[c->L], dst);
 }
 
@@ -1087,12 +1162,15 @@ int cadmm_set_state(cadmm_ctx* c, const float* const* W, const float* const* Z, 
     if (!c->has_init) return fail(c, CADMM_EORDER, "init first");
     const int L = c->L, M = c->hg.M;
     hipStream_t s = c->stream;
-    if (c->u_pending) base_eval(c, false);   // finish the pending dual step before anything is overwritten
+    if (c->u_pending) base_eval(c);          // finish the pending dual step before anything is overwritten
     c->t1_age = -1;
     if (W)
         for (int l = 1; l <= L; ++l)
             if (W[l - 1])
                 HIP_TRY(c, hipMemcpyAsync(c->W[l], W[l - 1], (size_t)c->C[l - 1] * c->C[l] * sizeof(float), hipMemcpyHostToDevice, s));
+    if (W)
+        for (int l = 2; l <= L; ++l)
+            if (W[l - 1]) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
     if (Z)
         for (int l = 1; l <= L; ++l)
             if (Z[l - 1]) {
@@ -1115,9 +1193,7 @@ int cadmm_set_state(cadmm_ctx* c, const float* const* W, const float* const* Z, 
         if (nz) HIP_TRY(c, hipMemcpyAsync(c->unitsZ, uz.data(), nz * sizeof(Unit), hipMemcpyHostToDevice, s));
     }
     HIP_TRY(c, hipStreamSynchronize(s));
-    c->base_valid = false;
-    c->have_prev = false;
-    c->dual_valid = false;
+    c->base_valid = c->gl_valid = c->gh_valid = c->scal_valid = c->stepped = false;
     return CADMM_OK;
 }
 

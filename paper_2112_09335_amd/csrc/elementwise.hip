@@ -19,20 +19,38 @@ namespace {
 
 constexpr double kStepFloor = 1e-12;   // a step that moves the block by less than this fraction is not taken
 
-// VEC consecutive floats per lane: 16-byte accesses when the element count allows (VEC = 4), else scalar
-template <int VEC>
-__device__ __forceinline__ void ldv(float (&d)[VEC], const float* p) {
-    if constexpr (VEC == 4) {
-        const float4 v = *reinterpret_cast<const float4*>(p);
+// Four consecutive floats per lane from an address that need only be aligned to four bytes (a row of a matrix whose
+// width is no multiple of four starts anywhere): the chip takes 16-byte global accesses at any dword.  valid: how many of
+// the four exist (1..4); the others read as zero, which adds nothing to any of the sums below.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void ldq(float (&d)[4], const float* p, int valid) {
+    if (valid >= 4) {
+        const float4u v = *reinterpret_cast<const float4u*>(p);
         d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
     } else {
-        d[0] = *p;
+        d[0] = p[0];
+        d[1] = valid > 1 ? p[1] : 0.f;
+        d[2] = valid > 2 ? p[2] : 0.f;
+        d[3] = 0.f;
     }
 }
-template <int VEC>
-__device__ __forceinline__ void stv(float* p, const float (&d)[VEC]) {
-    if constexpr (VEC == 4) *reinterpret_cast<float4*>(p) = make_float4(d[0], d[1], d[2], d[3]);
-    else *p = d[0];
+__device__ __forceinline__ void stq(float* p, const float (&d)[4], int valid) {
+    if (valid >= 4) {
+        float4u v = {d[0], d[1], d[2], d[3]};
+        *reinterpret_cast<float4u*>(p) = v;
+    } else {
+        p[0] = d[0];
+        if (valid > 1) p[1] = d[1];
+        if (valid > 2) p[2] = d[2];
+    }
+}
+__device__ __forceinline__ int quad_valid(int64_t count, int64_t i) { return count - i < 4 ? (int)(count - i) : 4; }
+__device__ __forceinline__ void ldv4(float (&d)[4], const float* p) {
+    const float4 v = *reinterpret_cast<const float4*>(p);
+    d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+}
+__device__ __forceinline__ void stv4(float* p, const float (&d)[4]) {
+    *reinterpret_cast<float4*>(p) = make_float4(d[0], d[1], d[2], d[3]);
 }
 
 __device__ __forceinline__ double block_sum(double v, double* sm) {
@@ -47,15 +65,38 @@ __device__ __forceinline__ double block_sum(double v, double* sm) {
     return t;
 }
 
-// slack: the test accepts up to this much above the bound (0 for the tau and theta searches)
+// Sums of NV values over a workgroup of 256 threads, written to out[0..NV) by its first NV threads: one pass through LDS
+// for all of them (sm: NV * 4 doubles).
+template <int NV>
+__device__ __forceinline__ void block_sums_to(const double (&v)[NV], double* sm, double* out) {
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        double t = v[j];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) t += __shfl_down(t, o, 64);
+        if ((threadIdx.x & 63) == 0) sm[j * 4 + (threadIdx.x >> 6)] = t;
+    }
+    __syncthreads();
+    if (threadIdx.x < NV) {
+        const double* s = sm + threadIdx.x * 4;
+        out[threadIdx.x] = (s[0] + s[1]) + (s[2] + s[3]);
+    }
+}
+
+// Judges up to ncand candidates of a search, step, step eta, ...  The change of the objective under candidate j is
+// D[j] + c1 / step_j + c2 / step_j^2: the part that is exactly quadratic in 1/step is carried by its two coefficients,
+// summed once per search (u->c1, u->c2); D (null: nothing) is what has to be evaluated candidate by candidate.
+// slack: the test accepts up to this much above the bound (0 for the tau and theta searches).
 __device__ __forceinline__ void decide(Unit* u, const double* D, int ncand, SearchParams sp, int32_t* status,
                                        double slack = 0.0) {
     double step = u->step;
-    const double g = u->g;
+    const double g = u->g, c1 = u->c1, c2 = u->c2;
     int nt = u->ntrials;
     for (int j = 0; j < ncand; ++j) {
         ++nt;
-        const double d = D[j];
+        const double inv = 1.0 / step;
+        const double d = (D ? D[j] : 0.0) + inv * (c1 + c2 * inv);
         if (!(d == d) || fabs(d) > 1.7e308) atomicOr(status, 2);
         if (d <= -g / (2.0 * step) + slack) { u->step = step; u->ntrials = nt; u->done = 1; return; }
         if (nt > sp.max_backtrack) {
@@ -69,16 +110,22 @@ __device__ __forceinline__ void decide(Unit* u, const double* D, int ncand, Sear
     u->ntrials = nt;
 }
 
-// Start of a search, before its first trial: the first candidate is the last accepted value, or that divided by
-// eta if the parameters may shrink again.
+// First candidate of the next search: the last accepted value, or that divided by eta if the parameters may shrink again.
+__device__ __forceinline__ double first_candidate(const Unit* u, SearchParams sp) {
+    return sp.relax ? u->step / (double)sp.eta : u->step;
+}
+
+// Start of a search, before its first decision.
 __device__ __forceinline__ void begin_search(Unit* u, SearchParams sp) {
     u->spec = (u->ntrials == 1) ? 1 : 0;     // last search: first candidate accepted
     u->ntrials = 0;
     u->keep = u->step;
-    if (sp.relax) u->step = u->step / (double)sp.eta;
+    u->step = first_candidate(u, sp);
     u->step0 = u->step;
     u->done = 0;
     u->skip = 0;
+    u->c1 = 0.0;
+    u->c2 = 0.0;
 }
 
 // A step below resolution is not taken: the block and its step parameter stay as they were.
@@ -94,54 +141,50 @@ __device__ __forceinline__ void floor_test(Unit* u, double g, double bnorm) {
 // last layer:    r = z - t,        phi += u r + rho/2 r^2,               G = -(u + rho r)
 // apply_dual (last layer only): first take the dual ascent step U += rho (Z_L - T) on the iterate just
 // reached, then evaluate phi and G with the new U.
-template <int LAST, int VEC>
+// The flat kernels walk a matrix as one array, four floats per lane and trip; the last quad may be partial.
+template <int LAST>
 __global__ __launch_bounds__(256) void phi_G_kernel(const float* __restrict__ T, const float* __restrict__ Z,
                                                     float* __restrict__ U, float* __restrict__ G,
                                                     float* __restrict__ Tprev, int have_prev, int apply_dual,
                                                     int64_t count, float nu, float rho,
                                                     double* __restrict__ partials) {
-    __shared__ double sm[4];
-    double s_phi = 0.0, s_res = 0.0, s_dt = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * VEC;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC; i < count; i += stride) {
-        float t[VEC], z[VEC], g[VEC];
-        ldv<VEC>(t, T + i);
-        ldv<VEC>(z, Z + i);
+    __shared__ double sm[3 * 4];
+    double s[3] = {0.0, 0.0, 0.0};          // phi, ||Z - T||^2, ||T - Tprev||^2
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
+        const int nv = quad_valid(count, i);
+        float t[4], z[4], g[4];
+        ldq(t, T + i, nv);
+        ldq(z, Z + i, nv);
         if (LAST) {
-            float u[VEC], tp[VEC];
-            ldv<VEC>(u, U + i);
-            if (Tprev && have_prev) ldv<VEC>(tp, Tprev + i);
+            float u[4], tp[4] = {0.f, 0.f, 0.f, 0.f};
+            ldq(u, U + i, nv);
+            if (have_prev) ldq(tp, Tprev + i, nv);
             if (apply_dual) {
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) u[v] = u[v] + rho * (z[v] - t[v]);
-                stv<VEC>(U + i, u);
+                for (int v = 0; v < 4; ++v) u[v] = u[v] + rho * (z[v] - t[v]);
+                stq(U + i, u, nv);
             }
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
+            for (int v = 0; v < 4; ++v) {
                 const double r = (double)z[v] - (double)t[v];
-                s_phi += (double)u[v] * r + 0.5 * (double)rho * r * r;
-                s_res += r * r;
+                s[0] += (double)u[v] * r + 0.5 * (double)rho * r * r;
+                s[1] += r * r;
                 g[v] = -(u[v] + rho * (z[v] - t[v]));
-                if (Tprev && have_prev) { const double d = (double)t[v] - (double)tp[v]; s_dt += d * d; }
+                if (have_prev) { const double d = (double)t[v] - (double)tp[v]; s[2] += d * d; }
             }
-            if (Tprev) stv<VEC>(Tprev + i, t);
+            stq(Tprev + i, t, nv);
         } else {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
+            for (int v = 0; v < 4; ++v) {
                 const double e = (double)fmaxf(t[v], 0.f) - (double)z[v];
-                s_phi += e * e;
+                s[0] += e * e;
                 g[v] = (t[v] > 0.f) ? nu * (float)e : 0.f;
             }
         }
-        if (G) stv<VEC>(G + i, g);
+        if (G) stq(G + i, g, nv);
     }
-    s_phi = block_sum(s_phi, sm);
-    if (LAST) { s_res = block_sum(s_res, sm); s_dt = block_sum(s_dt, sm); }
-    if (threadIdx.x == 0) {
-        partials[blockIdx.x * 3 + 0] = s_phi;
-        partials[blockIdx.x * 3 + 1] = s_res;
-        partials[blockIdx.x * 3 + 2] = s_dt;
-    }
+    block_sums_to<3>(s, sm, partials + (int64_t)blockIdx.x * 3);
 }
 
 __global__ __launch_bounds__(256) void phi_G_finish_kernel(const double* __restrict__ partials, int nblocks, int last,
@@ -163,25 +206,32 @@ __global__ __launch_bounds__(256) void phi_G_finish_kernel(const double* __restr
     }
 }
 
-template <int LAST, int VEC>
+// G without the sums; last layer: the dual step first if asked for (apply_dual).
+template <int LAST>
 __global__ __launch_bounds__(256) void G_only_kernel(const float* __restrict__ T, const float* __restrict__ Z,
-                                                     const float* __restrict__ U, float* __restrict__ G,
+                                                     float* __restrict__ U, float* __restrict__ G, int apply_dual,
                                                      int64_t count, float nu, float rho) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * VEC;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC; i < count; i += stride) {
-        float t[VEC], z[VEC], g[VEC];
-        ldv<VEC>(t, T + i);
-        ldv<VEC>(z, Z + i);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
+        const int nv = quad_valid(count, i);
+        float t[4], z[4], g[4];
+        ldq(t, T + i, nv);
+        ldq(z, Z + i, nv);
         if (LAST) {
-            float u[VEC];
-            ldv<VEC>(u, U + i);
+            float u[4];
+            ldq(u, U + i, nv);
+            if (apply_dual) {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) g[v] = -(u[v] + rho * (z[v] - t[v]));
+                for (int v = 0; v < 4; ++v) u[v] = u[v] + rho * (z[v] - t[v]);
+                stq(U + i, u, nv);
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) g[v] = -(u[v] + rho * (z[v] - t[v]));
         } else {
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) g[v] = (t[v] > 0.f) ? nu * (float)((double)t[v] - (double)z[v]) : 0.f;
+            for (int v = 0; v < 4; ++v) g[v] = (t[v] > 0.f) ? nu * (float)((double)t[v] - (double)z[v]) : 0.f;
         }
-        stv<VEC>(G + i, g);
+        stq(G + i, g, nv);
     }
 }
 
@@ -222,67 +272,90 @@ __global__ __launch_bounds__(256) void risk_finish_kernel(const double* __restri
 }
 
 // ------------------------------------------------------------------------------------------ W search
-// ||gradW||^2 and ||W||^2: per-block partial sums, then one block adds them in order and starts the search.
-__global__ __launch_bounds__(256) void w_norms_kernel(const float* __restrict__ gradW, const float* __restrict__ W,
-                                                      int count, double* __restrict__ partials) {
+// Adds the block sums of ||gradW||^2 and ||W||^2 (left by the reduction of the W-gradient product) in order and starts
+// the search.
+__global__ __launch_bounds__(256) void w_begin_kernel(const double* __restrict__ partials, int nblocks, Unit* unit,
+                                                      SearchParams sp) {
     __shared__ double sm[4];
     double g = 0.0, b = 0.0;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < count; i += gridDim.x * blockDim.x) {
-        const double x = (double)gradW[i], w = (double)W[i];
-        g += x * x;
-        b += w * w;
-    }
+    for (int i = threadIdx.x; i < nblocks; i += 256) { g += partials[2 * i]; b += partials[2 * i + 1]; }
     g = block_sum(g, sm);
     b = block_sum(b, sm);
-    if (threadIdx.x == 0) { partials[2 * blockIdx.x] = g; partials[2 * blockIdx.x + 1] = b; }
+    if (threadIdx.x == 0) {
+        begin_search(unit, sp);
+        floor_test(unit, g, b);
+    }
 }
 
-__global__ __launch_bounds__(64) void w_norms_finish_kernel(const double* __restrict__ partials, int nblocks,
-                                                            Unit* unit, SearchParams sp) {
-    if (threadIdx.x != 0) return;
-    double g = 0.0, b = 0.0;
-    for (int i = 0; i < nblocks; ++i) { g += partials[2 * i]; b += partials[2 * i + 1]; }
-    begin_search(unit, sp);
-    floor_test(unit, g, b);
+// Last layer: under T -> T - Q/tau the penalty <U, Z - T> + rho/2 ||Z - T||^2 changes by
+// S1/tau + rho/2 S2/tau^2 with S1 = sum q (u + rho (z - t)), S2 = sum q^2, whatever tau is: one pass over memory decides
+// the whole search.
+__global__ __launch_bounds__(256) void w_last_sums_kernel(const float* __restrict__ T0, const float* __restrict__ Q,
+                                                          const float* __restrict__ Z, const float* __restrict__ U,
+                                                          int64_t count, float rho, const Unit* unit,
+                                                          double* __restrict__ partials) {
+    __shared__ double sm[2 * 4];
+    if (unit->done) return;
+    double s[2] = {0.0, 0.0};
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
+        const int nv = quad_valid(count, i);
+        float t[4], q[4], z[4], u[4];
+        ldq(t, T0 + i, nv);
+        ldq(q, Q + i, nv);
+        ldq(z, Z + i, nv);
+        ldq(u, U + i, nv);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const double qd = (double)q[v];
+            s[0] += qd * ((double)u[v] + (double)rho * ((double)z[v] - (double)t[v]));
+            s[1] += qd * qd;
+        }
+    }
+    block_sums_to<2>(s, sm, partials + (int64_t)blockIdx.x * 2);
 }
 
-template <int LAST, int NC, int VEC>
-__global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ T0, const float* __restrict__ Q,
-                                                      const float* __restrict__ Z, const float* __restrict__ U,
-                                                      int64_t count, SearchParams sp, const Unit* unit,
-                                                      double* __restrict__ partials, int speculated) {
+__global__ __launch_bounds__(256) void w_last_finish_kernel(const double* __restrict__ partials, int nblocks,
+                                                            SearchParams sp, Unit* unit, int32_t* status) {
     __shared__ double sm[4];
     if (unit->done) return;
-    const double spec_inv = (speculated && unit->spec) ? 1.0 / unit->step0 : 0.0;      // T0 holds T0 - Q/step0: undo
-    double inv[NC];
-    {
-        double step = unit->step;
-#pragma unroll
-        for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; }
+    double a = 0.0, b = 0.0;
+    for (int i = threadIdx.x; i < nblocks; i += 256) { a += partials[2 * i]; b += partials[2 * i + 1]; }
+    a = block_sum(a, sm);
+    b = block_sum(b, sm);
+    if (threadIdx.x == 0) {
+        unit->c1 = a;
+        unit->c2 = 0.5 * (double)sp.rho * b;
+        decide(unit, nullptr, sp.max_backtrack + 1, sp, status);
     }
-    double D[NC];
+}
+
+// Hidden layer: the ReLU makes the change of phi_l piecewise quadratic, so the candidates are evaluated one by one,
+// NC at a time and `rounds` times NC per launch (partials: NC * rounds per block).
+template <int NC>
+__global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ T0, const float* __restrict__ Q,
+                                                      const float* __restrict__ Z, int64_t count, SearchParams sp,
+                                                      int rounds, const Unit* unit, double* __restrict__ partials,
+                                                      int speculated) {
+    __shared__ double sm[NC * 4];
+    if (unit->done) return;
+    const double spec_inv = (speculated && unit->spec) ? 1.0 / unit->step0 : 0.0;      // T0 holds T0 - Q/step0: undo
+    double step = unit->step;
+    for (int r = 0; r < rounds; ++r) {
+        double inv[NC], D[NC];
 #pragma unroll
-    for (int j = 0; j < NC; ++j) D[j] = 0.0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * VEC;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC; i < count; i += stride) {
-        float t0v[VEC], qv[VEC], zv[VEC], uv[VEC];
-        ldv<VEC>(t0v, T0 + i);
-        ldv<VEC>(qv, Q + i);
-        ldv<VEC>(zv, Z + i);
-        if (LAST) ldv<VEC>(uv, U + i);
+        for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; D[j] = 0.0; }
+        const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+        for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
+            const int nv = quad_valid(count, i);
+            float t0v[4], qv[4], zv[4];
+            ldq(t0v, T0 + i, nv);
+            ldq(qv, Q + i, nv);
+            ldq(zv, Z + i, nv);
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            const double q = (double)qv[v], z = (double)zv[v];
-            const double t0 = (double)t0v[v] + q * spec_inv;
-            if (LAST) {
-                const double u = (double)uv[v];
-                const double r0 = z - t0;
-#pragma unroll
-                for (int j = 0; j < NC; ++j) {
-                    const double dq = q * inv[j];          // r_new - r_old
-                    D[j] += dq * (u + 0.5 * (double)sp.rho * (2.0 * r0 + dq));
-                }
-            } else {
+            for (int v = 0; v < 4; ++v) {
+                const double q = (double)qv[v], z = (double)zv[v];
+                const double t0 = (double)t0v[v] + q * spec_inv;
                 const double e0 = fmax(t0, 0.0) - z;
 #pragma unroll
                 for (int j = 0; j < NC; ++j) {
@@ -291,43 +364,56 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
                 }
             }
         }
-    }
+        const double hnu = 0.5 * (double)sp.nu;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-        const double s = block_sum(D[j], sm);
-        if (threadIdx.x == 0) partials[blockIdx.x * kMaxCand + j] = LAST ? s : 0.5 * (double)sp.nu * s;
+        for (int j = 0; j < NC; ++j) D[j] *= hnu;
+        block_sums_to<NC>(D, sm, partials + ((int64_t)blockIdx.x * rounds + r) * NC);
     }
 }
 
-__global__ __launch_bounds__(256) void w_trial_finish_kernel(const double* __restrict__ partials, int nblocks,
-                                                             int stride, int ncand, SearchParams sp, Unit* unit,
-                                                             int32_t* status) {
+// Sums the ncand block results (stride per block) of a pass and takes the decision.  Wavefront w takes the candidates w, w + 4, ...
+__global__ __launch_bounds__(256) void w_trial_finish_kernel(const double* __restrict__ partials, int nblocks, int ncand,
+                                                             SearchParams sp, Unit* unit, int32_t* status) {
     __shared__ double sm[4];
-    __shared__ double D[kMaxCand];
+    __shared__ double D[kRestCand];
     if (unit->done) return;
-    for (int j = 0; j < ncand; ++j) {
+    if (ncand == 1) {                                  // many blocks (a product's workgroups), one candidate
         double a = 0.0, b = 0.0, c = 0.0, d = 0.0;     // four independent loads in flight per thread
         int i = threadIdx.x;
         for (; i + 768 < nblocks; i += 1024) {
-            a += partials[(int64_t)i * stride + j];
-            b += partials[(int64_t)(i + 256) * stride + j];
-            c += partials[(int64_t)(i + 512) * stride + j];
-            d += partials[(int64_t)(i + 768) * stride + j];
+            a += partials[i];
+            b += partials[i + 256];
+            c += partials[i + 512];
+            d += partials[i + 768];
         }
-        for (; i < nblocks; i += 256) a += partials[(int64_t)i * stride + j];
-        a = (a + b) + (c + d);
-        a = block_sum(a, sm);
-        if (threadIdx.x == 0) D[j] = a;
+        for (; i < nblocks; i += 256) a += partials[i];
+        a = block_sum((a + b) + (c + d), sm);
+        if (threadIdx.x == 0) D[0] = a;
+    } else {
+        const int lane = threadIdx.x & 63;
+        for (int j = threadIdx.x >> 6; j < ncand; j += 4) {
+            double a = 0.0;
+            for (int i = lane; i < nblocks; i += 64) a += partials[(int64_t)i * ncand + j];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
+            if (lane == 0) D[j] = a;
+        }
     }
     __syncthreads();
     if (threadIdx.x == 0) decide(unit, D, ncand, sp, status);
 }
 
-template <int VEC>
-__global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, const float* __restrict__ gradW,
-                                                     int count_w, float* __restrict__ T, const float* __restrict__ Q,
-                                                     int64_t count_t, const Unit* unit, int speculated) {
-    if (unit->skip) return;
+// W <- W - gradW/tau with its transpose beside it, T <- T - Q/tau.  LAST: also keeps the old T (Tprev) and leaves
+// G = -(U + rho (Z - T)) of the new T for the Z step of the layer before (G may be the same array as Q).
+template <int LAST>
+__global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, float* __restrict__ Wt,
+                                                     const float* __restrict__ gradW, int K, int C,
+                                                     float* __restrict__ T, const float* Q, int64_t count_t,
+                                                     const Unit* unit, int speculated, const float* __restrict__ Z,
+                                                     const float* __restrict__ U, float* G, float* __restrict__ Tprev,
+                                                     float rho) {
+    const bool skip = unit->skip != 0;
+    if (LAST == 0 && skip) return;
     const double inv = 1.0 / unit->step;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
@@ -336,22 +422,45 @@ __global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, cons
     const bool spec = speculated && unit->spec;
     const double tinv = spec ? inv - 1.0 / unit->step0 : inv;
     const bool t_done = spec && unit->step == unit->step0;
-    for (int64_t i = gtid * VEC; !t_done && i < count_t; i += nthreads * VEC) {
-        float t[VEC], q[VEC];
-        ldv<VEC>(t, T + i);
-        ldv<VEC>(q, Q + i);
+    if (LAST || !t_done) {
+        for (int64_t i = gtid * 4; i < count_t; i += nthreads * 4) {
+            const int nv = quad_valid(count_t, i);
+            float t[4], q[4];
+            ldq(t, T + i, nv);
+            ldq(q, Q + i, nv);
+            if (LAST) {
+                float z[4], u[4], g[4];
+                ldq(z, Z + i, nv);
+                ldq(u, U + i, nv);
+                if (Tprev) stq(Tprev + i, t, nv);
+                if (!skip) {
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
-        stv<VEC>(T + i, t);
+                    for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
+                    stq(T + i, t, nv);
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) g[v] = -(u[v] + rho * (z[v] - t[v]));
+                stq(G + i, g, nv);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
+                stq(T + i, t, nv);
+            }
+        }
     }
-    for (int64_t i = gtid; i < count_w; i += nthreads) W[i] = (float)((double)W[i] - (double)gradW[i] * inv);
+    if (skip) return;
+    const int64_t count_w = (int64_t)K * C;
+    for (int64_t i = gtid; i < count_w; i += nthreads) {
+        const float w = (float)((double)W[i] - (double)gradW[i] * inv);
+        W[i] = w;
+        if (Wt) {
+            const int k = (int)(i / C), cc = (int)(i - (int64_t)k * C);
+            Wt[(int64_t)cc * K + k] = w;
+        }
+    }
 }
 
 // ------------------------------------------------------------------------------------------ Z search
-// One block per chunk.  kind 0: rows [begin,end) of community `unit`, own term
-//     nu/2 ||Z - relu(T_l)||^2  under  Z -> Z - gradZ/theta;
-// kind 1: segments [begin,end) (community,row order) of the next layer's term, whose pre-activation
-//     row T_{l+1,i} moves by -P_s/theta as seen from this community.
 // grad[v] = nu (z[v] - relu(t[v])) + sum_k sg[k] wt[k][v], always in this order (the step kernel must
 // reproduce the very same values the search saw).  The rows of W_{l+1}^T are read from LDS (wcol: this lane's four
 // columns of row 0, wv float4 per row): the kernels that rebuild the gradient stream N x C_l matrices and need the
@@ -370,196 +479,235 @@ __device__ __forceinline__ void lowrank_grad_lds(float (&g)[4], const float (&z)
     }
 }
 
-// s_wt: LDS room for W_{l+1}^T (LR only); wt_loaded: whether this workgroup has filled it already.
-template <int NC, int VEC, int LR>
-__device__ __forceinline__ void z_trial_chunk(const ZTrialArgs& a, int ch, double* sm, float* s_wt, bool& wt_loaded) {
-    const int unit = a.chunk_unit[ch];
-    const Unit* u = a.units + unit;
-    if (u->done) return;
-    const int kind = a.chunk_kind[ch];
-    if (LR == 1 && kind == 0 && !wt_loaded) {           // (uniform over the workgroup)
-        for (int i = threadIdx.x; i < a.Cn * a.Cl; i += 256) s_wt[i] = a.Wt[i];
-        __syncthreads();
-        wt_loaded = true;
+// How a workgroup walks rows of `width` floats: 2^shift lanes per row, four columns per lane and trip.
+struct RowWalk {
+    int wv, shift, c_first, r_first, r_step;
+    __device__ __forceinline__ explicit RowWalk(int width) {
+        wv = (width + 3) >> 2;
+        shift = 0;
+        while ((1 << shift) < wv && shift < 8) ++shift;
+        c_first = threadIdx.x & ((1 << shift) - 1);
+        r_first = threadIdx.x >> shift;
+        r_step = 256 >> shift;
     }
-    const int begin = a.chunk_begin[ch], end = a.chunk_end[ch];
-    double inv[NC];
-    {
-        double step = u->step;
-#pragma unroll
-        for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)a.sp.eta; }
-    }
-    double D[NC];
-#pragma unroll
-    for (int j = 0; j < NC; ++j) D[j] = 0.0;
-    double sg = 0.0, sb = 0.0;
-    const int width = kind == 0 ? a.Cl : a.Cn;
-    const int wv = (width + VEC - 1) / VEC;       // lane slots per row
-    int cshift = 0;
-    while ((1 << cshift) < wv && cshift < 8) ++cshift;
-    const int cp = 1 << cshift;
-    const int c_first = threadIdx.x & (cp - 1);
-    const int r_first = threadIdx.x >> cshift;
-    const int r_step = 256 >> cshift;
-    const double hnu = 0.5 * (double)a.sp.nu, hrho = 0.5 * (double)a.sp.rho;
-    if (kind == 0) {
-        // low-rank gradient: this thread's four columns of W_{l+1}^T, read from LDS (one column slot per thread)
-        const float4* const wcol = reinterpret_cast<const float4*>(s_wt) + (c_first < wv ? c_first : 0);
-        for (int r = begin + r_first; r < end; r += r_step) {
-            const int64_t base = (int64_t)r * width;
-            float srow[LR ? kLowRankMax : 1];      // this row of the N x Cn factor
+};
+
+// First pass of the search for theta_{l,m}, all communities of layer l at once, one workgroup per chunk (a chunk belongs
+// to one community).  What is summed decides every candidate of what is quadratic in 1/theta:
+//   rows (kind 0): nu/2 ||Z - relu(T_l)||^2 under Z -> Z - g/theta changes by nu/2 (-2 A/theta + B/theta^2) with
+//     A = sum e g, e = Z - relu(T_l), and B = ||g||^2; ||Z||^2 for the step floor.
+//   segments (kind 1), next layer the last one: <U, Z_L - T> + rho/2 ||Z_L - T||^2 under T -> T - P/theta changes by
+//     -S1/theta + rho/2 S2/theta^2 with S1 = sum p G_L (G_L = -(u + rho (z - t)) is at hand) and S2 = sum p^2.
+//   segments, next layer hidden (HID): its ReLU makes the term piecewise quadratic; the first candidate is evaluated.
+// So with a last next layer this one pass over memory is the whole search, and with a hidden one the later passes read
+// the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidate's change, S2.  Bound by HBM traffic.
+constexpr int kFirstVals = 5;
+template <int HID, int LR>
+__global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
+    __shared__ double sm[kFirstVals * 4];
+    extern __shared__ __align__(16) float s_wt[];       // [Cn][Cl] with the low-rank gradient, else nothing
+    const int4 ck = a.chunks[blockIdx.x];               // community, kind, first row / segment, one past the last
+    double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    if (ck.y == 0) {
+        const RowWalk w(a.Cl);
+        if constexpr (LR == 1) {
+            for (int i = threadIdx.x; i < a.Cn * a.Cl; i += 256) s_wt[i] = a.Wt[i];
+            __syncthreads();
+        }
+        const float4* const wcol = reinterpret_cast<const float4*>(s_wt) + (w.c_first < w.wv ? w.c_first : 0);
+        for (int r = ck.z + w.r_first; r < ck.w; r += w.r_step) {
+            const int64_t base = (int64_t)r * a.Cl;
+            float srow[LR ? kLowRankMax : 1];           // this row of the N x Cn factor
             if constexpr (LR == 1) {
 #pragma unroll
                 for (int k4 = 0; k4 < kLowRankMax / 4; ++k4) {
                     float q[4] = {0.f, 0.f, 0.f, 0.f};
-                    if (4 * k4 < a.Cn) ldv<4>(q, a.SG + (int64_t)r * a.Cn + 4 * k4);
+                    if (4 * k4 < a.Cn) ldv4(q, a.SG + (int64_t)r * a.Cn + 4 * k4);
                     srow[4 * k4] = q[0]; srow[4 * k4 + 1] = q[1]; srow[4 * k4 + 2] = q[2]; srow[4 * k4 + 3] = q[3];
                 }
             }
-            for (int cv = c_first; cv < wv; cv += cp) {
-                float zv[VEC], gv[VEC], tv[VEC];
-                ldv<VEC>(zv, a.Zl + base + cv * VEC);
-                ldv<VEC>(tv, a.Tl + base + cv * VEC);
-                if constexpr (LR == 1) lowrank_grad_lds(gv, zv, tv, srow, wcol, wv, a.Cn, a.sp.nu);
-                else ldv<VEC>(gv, a.gradZ + base + cv * VEC);
+            for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+                float zv[4], gv[4], tv[4];
+                const int nv = a.Cl - 4 * cv;
+                ldq(zv, a.Zl + base + 4 * cv, nv);
+                ldq(tv, a.Tl + base + 4 * cv, nv);
+                if constexpr (LR == 1) lowrank_grad_lds(gv, zv, tv, srow, wcol, w.wv, a.Cn, a.sp.nu);
+                else ldq(gv, a.gradZ + base + 4 * cv, nv);
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const double z = (double)zv[v], gz = (double)gv[v], t = (double)tv[v];
-                    const double e0 = z - fmax(t, 0.0);
-                    if (a.first_pass) { sg += gz * gz; sb += z * z; }
-#pragma unroll
-                    for (int j = 0; j < NC; ++j) {
-                        const double dz = -gz * inv[j];
-                        D[j] += hnu * dz * (2.0 * e0 + dz);
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const double z = (double)zv[v], gz = (double)gv[v];
+                    s[0] += (z - fmax((double)tv[v], 0.0)) * gz;
+                    s[1] += gz * gz;
+                    s[2] += z * z;
                 }
             }
         }
     } else {
-        for (int s = begin + r_first; s < end; s += r_step) {
-            const int64_t row = a.segc_row[s];
-            const int64_t base = row * width, pbase = (int64_t)s * width;
-            for (int cv = c_first; cv < wv; cv += cp) {
-                float tv[VEC], zv[VEC], pv[VEC];
-                ldv<VEC>(pv, a.P + pbase + cv * VEC);
-                if (a.next_is_last) {
-                    // the change of <U, Z_L - T> + rho/2 |Z_L - T|^2 under T -> T - p/theta is
-                    // (p/theta) (u + rho (z - t)) + rho/2 (p/theta)^2, and u + rho (z - t) = -G_L is at hand
-                    ldv<VEC>(tv, a.Gn + base + cv * VEC);
+        const RowWalk w(a.Cn);
+        const double inv = HID ? 1.0 / first_candidate(a.units + ck.x, a.sp) : 0.0;
+        for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
+            const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
+            for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+                const int nv = a.Cn - 4 * cv;
+                float pv[4], tv[4], zv[4];
+                ldq(pv, a.P + pbase + 4 * cv, nv);
+                if constexpr (HID) {
+                    ldq(tv, a.Tn + base + 4 * cv, nv);
+                    ldq(zv, a.Zn + base + 4 * cv, nv);
                 } else {
-                    ldv<VEC>(tv, a.Tn + base + cv * VEC);
-                    ldv<VEC>(zv, a.Zn + base + cv * VEC);
+                    ldq(tv, a.Gn + base + 4 * cv, nv);
                 }
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) {
-                    const double t0 = (double)tv[v], z = (double)zv[v], p = (double)pv[v];
-                    if (a.next_is_last) {
-#pragma unroll
-                        for (int j = 0; j < NC; ++j) {
-                            const double dq = p * inv[j];
-                            D[j] += dq * (hrho * dq - t0);
-                        }
+                for (int v = 0; v < 4; ++v) {
+                    const double t = (double)tv[v], p = (double)pv[v];
+                    if constexpr (HID) {
+                        const double z = (double)zv[v];
+                        const double e0 = fmax(t, 0.0) - z, e1 = fmax(t - p * inv, 0.0) - z;
+                        s[3] += (e1 - e0) * (e1 + e0);
                     } else {
-                        const double e0 = fmax(t0, 0.0) - z;
-#pragma unroll
-                        for (int j = 0; j < NC; ++j) {
-                            const double e1 = fmax(t0 - p * inv[j], 0.0) - z;
-                            D[j] += hnu * (e1 - e0) * (e1 + e0);
-                        }
+                        s[3] += p * t;
+                        s[4] += p * p;
                     }
                 }
             }
         }
     }
-    double* out = a.partials + (int64_t)ch * (kMaxCand + 2);
+    block_sums_to<kFirstVals>(s, sm, a.partials + (int64_t)blockIdx.x * kFirstVals);
+}
+
+// One workgroup per community: adds its chunks' sums in order, applies the step floor and takes the decision (all of
+// them if the whole change is quadratic).
+template <int HID>
+__global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
+    __shared__ double sm[kFirstVals * 4];
+    __shared__ double S[kFirstVals];
+    const int unit = blockIdx.x;
+    const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
+    double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    for (int i = c0 + threadIdx.x; i < c1; i += 256)
 #pragma unroll
-    for (int j = 0; j < NC; ++j) {
-        const double s = block_sum(D[j], sm);
-        if (threadIdx.x == 0) out[j] = s;
-    }
-    if (a.first_pass) {
-        sg = block_sum(sg, sm);
-        sb = block_sum(sb, sm);
-        if (threadIdx.x == 0) { out[kMaxCand] = sg; out[kMaxCand + 1] = sb; }
-    }
-}
-
-// The first pass (one candidate) runs one block per chunk.  A later pass (NC candidates) usually finds every
-// community done: each block first looks at all the done flags at once and leaves if nothing is pending,
-// otherwise a small grid strides over the chunks.
-template <int NC, int VEC, int LR>
-__global__ __launch_bounds__(256) void z_trial_kernel(ZTrialArgs a) {
-    __shared__ double sm[4];
-    extern __shared__ __align__(16) float s_wt[];       // [Cn][Cl] with the low-rank gradient, else nothing
-    bool wt_loaded = false;
-    if constexpr (NC == 1) {
-        z_trial_chunk<NC, VEC, LR>(a, blockIdx.x, sm, s_wt, wt_loaded);
-    } else {
-        int pending = 0;
-        for (int i = threadIdx.x; i < a.M; i += 256) pending |= (a.units[i].done == 0);
-        if (!__syncthreads_or(pending)) return;
-        for (int ch = blockIdx.x; ch < a.n_chunks; ch += gridDim.x) z_trial_chunk<NC, VEC, LR>(a, ch, sm, s_wt, wt_loaded);
+        for (int q = 0; q < kFirstVals; ++q) s[q] += a.partials[(int64_t)i * kFirstVals + q];
+    block_sums_to<kFirstVals>(s, sm, S);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        Unit* u = a.units + unit;
+        const double hnu = 0.5 * (double)a.sp.nu;
+        begin_search(u, a.sp);
+        floor_test(u, S[1], S[2]);
+        if (u->done) return;
+        u->c1 = -2.0 * hnu * S[0];
+        u->c2 = hnu * S[1];
+        if (HID) {
+            const double d = hnu * S[3];
+            decide(u, &d, 1, a.sp, a.status);
+        } else {
+            u->c1 -= S[3];
+            u->c2 += 0.5 * (double)a.sp.rho * S[4];
+            decide(u, nullptr, a.sp.max_backtrack + 1, a.sp, a.status);
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void z_trial_finish_kernel(ZTrialArgs a) {
-    __shared__ double sm[4];
-    __shared__ double D[kMaxCand + 2];
+// Later passes over the segments (hidden next layer): `rounds` times NC further candidates for the communities still
+// searching.  Usually every community is done: a workgroup looks at all the flags at once and leaves if nothing is pending.
+template <int NC>
+__global__ __launch_bounds__(256) void z_more_kernel(ZTrialArgs a, int rounds) {
+    __shared__ double sm[NC * 4];
+    int pending = 0;
+    for (int i = threadIdx.x; i < a.M; i += 256) pending |= (a.units[i].done == 0);
+    if (!__syncthreads_or(pending)) return;
+    const RowWalk w(a.Cn);
+    const double hnu = 0.5 * (double)a.sp.nu;
+    for (int ch = blockIdx.x; ch < a.n_chunks; ch += gridDim.x) {
+        const int4 ck = a.chunks[ch];
+        if (ck.y == 0) continue;
+        const Unit* u = a.units + ck.x;
+        if (u->done) continue;
+        double step = u->step;
+        for (int rd = 0; rd < rounds; ++rd) {
+            double inv[NC], D[NC];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)a.sp.eta; D[j] = 0.0; }
+            for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
+                const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
+                for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+                    const int nv = a.Cn - 4 * cv;
+                    float pv[4], tv[4], zv[4];
+                    ldq(pv, a.P + pbase + 4 * cv, nv);
+                    ldq(tv, a.Tn + base + 4 * cv, nv);
+                    ldq(zv, a.Zn + base + 4 * cv, nv);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const double t = (double)tv[v], z = (double)zv[v], p = (double)pv[v];
+                        const double e0 = fmax(t, 0.0) - z;
+#pragma unroll
+                        for (int j = 0; j < NC; ++j) {
+                            const double e1 = fmax(t - p * inv[j], 0.0) - z;
+                            D[j] += (e1 - e0) * (e1 + e0);
+                        }
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < NC; ++j) D[j] *= hnu;
+            block_sums_to<NC>(D, sm, a.partials + ((int64_t)ch * rounds + rd) * NC);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void z_more_finish_kernel(ZTrialArgs a, int ncand) {
+    __shared__ double D[kRestCand];
     const int unit = blockIdx.x;
     Unit* u = a.units + unit;
     if (u->done) return;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
-    const int nq = a.first_pass ? kMaxCand + 2 : a.ncand;
-    for (int q = 0; q < nq; ++q) {
-        if (q >= a.ncand && q < kMaxCand) continue;
+    const int lane = threadIdx.x & 63;
+    for (int j = threadIdx.x >> 6; j < ncand; j += 4) {
         double s = 0.0;
-        for (int i = c0 + threadIdx.x; i < c1; i += blockDim.x) s += a.partials[(int64_t)i * (kMaxCand + 2) + q];
-        s = block_sum(s, sm);
-        if (threadIdx.x == 0) D[q] = s;
+        for (int i = c0 + lane; i < c1; i += 64)
+            if (a.chunks[i].y != 0) s += a.partials[(int64_t)i * ncand + j];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (lane == 0) D[j] = s;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        if (a.first_pass) {
-            floor_test(u, D[kMaxCand], D[kMaxCand + 1]);      // the search began in reset_units_kernel
-            if (u->done) return;
-        }
-        decide(u, D, a.ncand, a.sp, a.status);
+    if (threadIdx.x == 0) decide(u, D, ncand, a.sp, a.status);
+}
+
+// 1/theta of every community in LDS (0 where no step is taken): kernels that need the step parameter of a row's or a
+// segment's community then do not wait for it in a chain of dependent loads (row -> community -> unit).
+constexpr int kStepUnits = 1024;
+__device__ __forceinline__ double unit_inv(const Unit* u) { return u->skip ? 0.0 : 1.0 / u->step; }
+template <bool LDSU>
+__device__ __forceinline__ void load_inv(double* s_inv, const Unit* __restrict__ units, int M) {
+    if constexpr (LDSU) {
+        for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = unit_inv(units + i);
+        __syncthreads();
     }
 }
 
-constexpr int kStepUnits = 1024;       // communities whose 1/theta a workgroup keeps in LDS
-// Z_{l,m} <- Z_{l,m} - grad / theta_{l,m}.  LDSU: 1/theta of every community (0 where no step is taken) is copied
-// to LDS first and the loads of a row are issued before its community is known: the row's community, then its step
-// parameter, then the data used to be three dependent round trips per row.
-template <int VEC, bool LDSU>
+// Z_{l,m} <- Z_{l,m} - grad / theta_{l,m}; the loads of a row are issued before its community is known.
+template <bool LDSU>
 __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, const float* __restrict__ gradZ,
                                                      const int32_t* __restrict__ row_comm, int64_t N, int Cl,
                                                      const Unit* __restrict__ units, int M) {
     __shared__ double s_inv[LDSU ? kStepUnits : 1];
-    if constexpr (LDSU) {
-        for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = units[i].skip ? 0.0 : 1.0 / units[i].step;
-        __syncthreads();
-    }
-    const int wv = (Cl + VEC - 1) / VEC;
-    int cshift = 0;
-    while ((1 << cshift) < wv && cshift < 8) ++cshift;
-    const int cp = 1 << cshift;
-    const int c_first = threadIdx.x & (cp - 1);
-    const int64_t r_step = (int64_t)gridDim.x * (256 >> cshift);
-    for (int64_t r = (int64_t)blockIdx.x * (256 >> cshift) + (threadIdx.x >> cshift); r < N; r += r_step) {
+    load_inv<LDSU>(s_inv, units, M);
+    const RowWalk w(Cl);
+    const int64_t r_step = (int64_t)gridDim.x * w.r_step;
+    for (int64_t r = (int64_t)blockIdx.x * w.r_step + w.r_first; r < N; r += r_step) {
         const int cm = row_comm[r];
         const int64_t base = r * Cl;
-        for (int cv = c_first; cv < wv; cv += cp) {
-            float z[VEC], g[VEC];
-            ldv<VEC>(z, Zl + base + cv * VEC);
-            ldv<VEC>(g, gradZ + base + cv * VEC);
-            double inv;
-            if constexpr (LDSU) inv = s_inv[cm];
-            else inv = units[cm].skip ? 0.0 : 1.0 / units[cm].step;
+        for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+            const int nv = Cl - 4 * cv;
+            float z[4], g[4];
+            ldq(z, Zl + base + 4 * cv, nv);
+            ldq(g, gradZ + base + 4 * cv, nv);
+            const double inv = LDSU ? s_inv[cm] : unit_inv(units + cm);
             if (inv == 0.0) break;                   // no step for this row's community
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) z[v] = (float)((double)z[v] - (double)g[v] * inv);
-            stv<VEC>(Zl + base + cv * VEC, z);
+            for (int v = 0; v < 4; ++v) z[v] = (float)((double)z[v] - (double)g[v] * inv);
+            stq(Zl + base + 4 * cv, z, nv);
         }
     }
 }
@@ -576,7 +724,7 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
     __shared__ double s_inv[LDSU ? kStepUnits : 1];
     extern __shared__ __align__(16) float s_wt[];        // [Cn][Cl]
     if constexpr (LDSU) {
-        for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = units[i].skip ? 0.0 : 1.0 / units[i].step;
+        for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = unit_inv(units + i);
     }
     for (int i = threadIdx.x; i < Cn * Cl; i += 256) s_wt[i] = Wt[i];
     __syncthreads();
@@ -598,12 +746,12 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
             const int64_t rr = r < N ? r : N - 1;    // a row past the end repeats the last one and is not stored
             cm[q] = row_comm[rr];
             const int64_t o = rr * Cl + c_first * 4;
-            ldv<4>(z[q], Zl + o);
-            ldv<4>(t[q], Tl + o);
+            ldv4(z[q], Zl + o);
+            ldv4(t[q], Tl + o);
 #pragma unroll
             for (int k4 = 0; k4 < kLowRankMax / 4; ++k4) {
                 float v[4] = {0.f, 0.f, 0.f, 0.f};
-                if (4 * k4 < Cn) ldv<4>(v, SG + rr * Cn + 4 * k4);
+                if (4 * k4 < Cn) ldv4(v, SG + rr * Cn + 4 * k4);
                 sg[q][4 * k4] = v[0]; sg[q][4 * k4 + 1] = v[1]; sg[q][4 * k4 + 2] = v[2]; sg[q][4 * k4 + 3] = v[3];
             }
         }
@@ -628,11 +776,11 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
             const int64_t r = r0 + q * rows_per_block;
             double inv;
             if constexpr (LDSU) inv = s_inv[cm[q]];
-            else inv = units[cm[q]].skip ? 0.0 : 1.0 / units[cm[q]].step;
+            else inv = unit_inv(units + cm[q]);
             if (r >= N || inv == 0.0) continue;
 #pragma unroll
             for (int v = 0; v < 4; ++v) z[q][v] = (float)((double)z[q][v] - (double)g[q][v] * inv);
-            stv<4>(Zl + r * Cl + c_first * 4, z[q]);
+            stv4(Zl + r * Cl + c_first * 4, z[q]);
         }
     }
 }
@@ -641,70 +789,58 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
 // - sum over the segments (i, c) of P_{(i,c)} / theta_{l,c}  (P = A~_{., c} grad W_{l+1}, already formed for the
 // search).  Applying that keeps T_{l+1} valid for the next iteration without a new aggregation and product.
 constexpr int kCarryBatch = 4;
-constexpr int kCarryUnits = 1024;      // communities whose 1/theta a workgroup keeps in LDS
-// LDSU: the workgroup first copies 1/theta of every community (0 for a skipped step) into LDS, which takes the
-// lookup of a segment's step parameter out of the chain of dependent global loads (row -> segment -> unit).
-template <int VEC, bool LDSU>
-__global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, const float* __restrict__ P,
-                                                      const int64_t* __restrict__ row_seg_ptr,
-                                                      const int32_t* __restrict__ seg_comm,
-                                                      const int32_t* __restrict__ seg_pos, int64_t N, int Cn,
-                                                      const Unit* __restrict__ units, int M) {
-    __shared__ double s_inv[LDSU ? kCarryUnits : 1];
-    if constexpr (LDSU) {
-        for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = units[i].skip ? 0.0 : 1.0 / units[i].step;
-        __syncthreads();
+// acc += that sum for columns 4 cv .. of row r; returns whether any of the row's communities took a step.
+// kCarryBatch segments at a time: their index, unit and row loads do not depend on each other, so they are in flight
+// together; the sums are still taken in segment order.
+template <bool LDSU>
+__device__ __forceinline__ bool carry_sum(double (&acc)[4], const CarryArgs& k, const double* s_inv, int64_t r, int Cn,
+                                          int cv) {
+    const int64_t s0 = k.row_seg_ptr[r], s1 = k.row_seg_ptr[r + 1];
+    const int nv = Cn - 4 * cv;
+    bool any = false;
+    for (int64_t sgm = s0; sgm < s1; sgm += kCarryBatch) {
+        int cm[kCarryBatch], ps[kCarryBatch];
+#pragma unroll
+        for (int j = 0; j < kCarryBatch; ++j) {
+            const int64_t sj = sgm + j < s1 ? sgm + j : s1 - 1;
+            cm[j] = k.seg_comm[sj];
+            ps[j] = k.seg_pos[sj];
+        }
+        double inv[kCarryBatch];
+        float p[kCarryBatch][4];
+#pragma unroll
+        for (int j = 0; j < kCarryBatch; ++j) {
+            inv[j] = LDSU ? s_inv[cm[j]] : unit_inv(k.units + cm[j]);
+            if (sgm + j >= s1) inv[j] = 0.0;
+            ldq(p[j], k.P + (int64_t)ps[j] * Cn + 4 * cv, nv);
+        }
+#pragma unroll
+        for (int j = 0; j < kCarryBatch; ++j) {
+            if (inv[j] == 0.0) continue;          // past the row's end, or a step that was not taken
+            any = true;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[v] += (double)p[j][v] * inv[j];
+        }
     }
-    const int wv = (Cn + VEC - 1) / VEC;
-    int cshift = 0;
-    while ((1 << cshift) < wv && cshift < 8) ++cshift;
-    const int cp = 1 << cshift;
-    const int c_first = threadIdx.x & (cp - 1);
-    const int64_t r_step = (int64_t)gridDim.x * (256 >> cshift);
-    for (int64_t r = (int64_t)blockIdx.x * (256 >> cshift) + (threadIdx.x >> cshift); r < N; r += r_step) {
-        const int64_t s0 = row_seg_ptr[r], s1 = row_seg_ptr[r + 1];
-        for (int cv = c_first; cv < wv; cv += cp) {
-            double acc[VEC];
+    return any;
+}
+
+template <bool LDSU>
+__global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, CarryArgs k, int64_t N, int Cn) {
+    __shared__ double s_inv[LDSU ? kStepUnits : 1];
+    load_inv<LDSU>(s_inv, k.units, k.M);
+    const RowWalk w(Cn);
+    const int64_t r_step = (int64_t)gridDim.x * w.r_step;
+    for (int64_t r = (int64_t)blockIdx.x * w.r_step + w.r_first; r < N; r += r_step) {
+        for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+            double acc[4] = {0.0, 0.0, 0.0, 0.0};
+            if (!carry_sum<LDSU>(acc, k, s_inv, r, Cn, cv)) continue;
+            const int nv = Cn - 4 * cv;
+            float t[4];
+            ldq(t, Tn + r * Cn + 4 * cv, nv);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[v] = 0.0;
-            bool any = false;
-            // kCarryBatch segments at a time: their index, unit and row loads do not depend on each other, so they
-            // are in flight together; the sums are still taken in segment order.
-            for (int64_t sgm = s0; sgm < s1; sgm += kCarryBatch) {
-                int cm[kCarryBatch], ps[kCarryBatch];
-#pragma unroll
-                for (int j = 0; j < kCarryBatch; ++j) {
-                    const int64_t sj = sgm + j < s1 ? sgm + j : s1 - 1;
-                    cm[j] = seg_comm[sj];
-                    ps[j] = seg_pos[sj];
-                }
-                double inv[kCarryBatch];
-                float p[kCarryBatch][VEC];
-#pragma unroll
-                for (int j = 0; j < kCarryBatch; ++j) {
-                    if constexpr (LDSU) {
-                        inv[j] = s_inv[cm[j]];
-                    } else {
-                        const Unit* u = units + cm[j];
-                        inv[j] = u->skip ? 0.0 : 1.0 / u->step;
-                    }
-                    if (sgm + j >= s1) inv[j] = 0.0;
-                    ldv<VEC>(p[j], P + (int64_t)ps[j] * Cn + cv * VEC);
-                }
-#pragma unroll
-                for (int j = 0; j < kCarryBatch; ++j) {
-                    if (inv[j] == 0.0) continue;          // past the row's end, or a step that was not taken
-                    any = true;
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[v] += (double)p[j][v] * inv[j];
-                }
-            }
-            if (!any) continue;
-            float t[VEC];
-            ldv<VEC>(t, Tn + r * Cn + cv * VEC);
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) t[v] = (float)((double)t[v] - acc[v]);
-            stv<VEC>(Tn + r * Cn + cv * VEC, t);
+            for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - acc[v]);
+            stq(Tn + r * Cn + 4 * cv, t, nv);
         }
     }
 }
@@ -715,36 +851,30 @@ __global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, co
 // formed by xor-shuffles inside the lane group.  FISTA on
 //   R(z, y_i) + <u, z - c> + rho/2 ||z - c||^2,   c = row of A~ Z_{L-1}^k W_L^{k+1},
 // whose smooth part is the whole objective: x_j = y_j - grad(y_j)/Lip, Lip = rho + (1/2 | 1).
-template <int LPLOG>
-__global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL, float* __restrict__ U,
-                                                         const float* __restrict__ TL,
+// CARRY: T_L is then brought to the new Z_{L-1} (carry_sum) and, with G, the gradient G_L = -(U + rho (Z_L - T_L)) of the
+// next iteration is left, all while the row is in registers: one launch and no second pass over Z_L, U and T_L.
+template <int LPLOG, int CARRY, bool LDSU>
+__global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL, float* __restrict__ U, float* __restrict__ TL,
                                                          const int32_t* __restrict__ labels, int64_t N, int CL,
-                                                         int risk, float rho, int J, int update_u) {
+                                                         int risk, float rho, int J, int update_u, CarryArgs k,
+                                                         float* __restrict__ G) {
+    __shared__ double s_inv[CARRY && LDSU ? kStepUnits : 1];
+    if constexpr (CARRY) load_inv<LDSU>(s_inv, k.units, k.M);
     constexpr int LP = 1 << LPLOG;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t row = t >> LPLOG;
     const int j0 = (int)(t & (LP - 1)) * 4;
     const bool act = row < N;                       // uniform over the lane group of a row
     const int64_t base = (act ? row : 0) * CL + j0;
-    const bool vec = (CL % 4) == 0;
+    const int nv = act ? CL - j0 : 0;               // columns of this lane (none, or one to four)
     bool ok[4];
-    float c[4], u[4], xp[4], y[4], x[4];
+    float c[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f}, xp[4] = {0.f, 0.f, 0.f, 0.f}, y[4], x[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) ok[v] = act && (j0 + v < CL);
-    if (vec && ok[0]) {
-        const float4 a = *reinterpret_cast<const float4*>(TL + base);
-        const float4 b = *reinterpret_cast<const float4*>(U + base);
-        const float4 d = *reinterpret_cast<const float4*>(ZL + base);
-        c[0] = a.x; c[1] = a.y; c[2] = a.z; c[3] = a.w;
-        u[0] = b.x; u[1] = b.y; u[2] = b.z; u[3] = b.w;
-        xp[0] = d.x; xp[1] = d.y; xp[2] = d.z; xp[3] = d.w;
-    } else {
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            c[v] = ok[v] ? TL[base + v] : 0.f;
-            u[v] = ok[v] ? U[base + v] : 0.f;
-            xp[v] = ok[v] ? ZL[base + v] : 0.f;
-        }
+    for (int v = 0; v < 4; ++v) ok[v] = v < nv;
+    if (nv > 0) {
+        ldq(c, TL + base, nv);
+        ldq(u, U + base, nv);
+        ldq(xp, ZL + base, nv);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) { y[v] = xp[v]; x[v] = xp[v]; }
@@ -791,24 +921,62 @@ __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL,
             tk = tn;
         }
     }
-    if (vec && ok[0]) {
-        if (update_u) *reinterpret_cast<float4*>(U + base) = make_float4(un[0], un[1], un[2], un[3]);
-        *reinterpret_cast<float4*>(ZL + base) = make_float4(x[0], x[1], x[2], x[3]);
-    } else {
+    if (nv <= 0) return;
+    if (update_u) stq(U + base, un, nv);
+    stq(ZL + base, x, nv);
+    if constexpr (CARRY) {
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        if (carry_sum<LDSU>(acc, k, s_inv, row, CL, j0 >> 2)) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (ok[v]) {
-                if (update_u) U[base + v] = un[v];
-                ZL[base + v] = x[v];
-            }
+            for (int v = 0; v < 4; ++v) c[v] = (float)((double)c[v] - acc[v]);
+            stq(TL + base, c, nv);
+        }
+        if (G) {
+            float g[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) g[v] = -(un[v] + rho * (x[v] - c[v]));
+            stq(G + base, g, nv);
+        }
     }
 }
 
+// relu (or a plain copy) of a matrix
 __global__ __launch_bounds__(256) void relu_kernel(const float* __restrict__ T, float* __restrict__ Z, int64_t count,
                                                    int apply_relu) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += stride)
-        Z[i] = apply_relu ? fmaxf(T[i], 0.f) : T[i];
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
+        const int nv = quad_valid(count, i);
+        float t[4];
+        ldq(t, T + i, nv);
+        if (apply_relu) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) t[v] = fmaxf(t[v], 0.f);
+        }
+        stq(Z + i, t, nv);
+    }
+}
+
+// What the low-rank form of the Z gradient needs of W_{l+1} (Cl x Cn, Cn <= kLowRankMax): Bcat = [W; W^T W].
+// One workgroup: W goes through LDS (64 KB at most), thread (i, j) forms its entry of W^T W in fp64.
+__global__ __launch_bounds__(256) void lowrank_operand_kernel(const float* __restrict__ W, float* __restrict__ Bcat, int Cl,
+                                                              int Cn) {
+    extern __shared__ __align__(16) float s_w[];
+    const int n = Cl * Cn;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const float w = W[i];
+        s_w[i] = w;
+        Bcat[i] = w;
+    }
+    __syncthreads();
+    const int i = threadIdx.x / Cn, j = threadIdx.x % Cn;
+    if (i >= Cn) return;
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};            // four chains: the loop is bound by the latency of one
+    int k = 0;
+    for (; k + 3 < Cl; k += 4)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[q] += (double)s_w[(k + q) * Cn + i] * (double)s_w[(k + q) * Cn + j];
+    for (; k < Cl; ++k) acc[0] += (double)s_w[k * Cn + i] * (double)s_w[k * Cn + j];
+    Bcat[n + threadIdx.x] = (float)((acc[0] + acc[1]) + (acc[2] + acc[3]));
 }
 
 // class of every node: index of the largest entry of its row (the first one on equal values)
@@ -861,8 +1029,8 @@ __device__ __forceinline__ double row_lse(const double (&z)[4], const bool (&ok)
 }
 
 template <int LPLOG, int NC>
-__global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage, int more, float mom) {
-    __shared__ double sm[4];
+__global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage, int more, int rounds, float mom) {
+    __shared__ double sm[NC * 4];
     constexpr int LP = 1 << LPLOG;
     if (more) {                                        // a pass of further candidates: only if some search is pending
         int pending = 0;
@@ -870,12 +1038,15 @@ __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage
         if (!__syncthreads_or(pending)) return;
     }
     for (int ch = blockIdx.x; ch < a.n_chunks; ch += gridDim.x) {
-        if (a.chunk_kind[ch] != 0) continue;           // only the chunks of rows
-        const Unit* u = a.units + a.chunk_unit[ch];
+        const int4 ck = a.chunks[ch];
+        if (ck.y != 0) continue;                       // only the chunks of rows
+        const Unit* u = a.units + ck.x;
         if (more && u->done) continue;
         const double Lcur = (stage == 0 && !more) ? (double)a.rho : u->step;       // every solve starts from L = rho
         const bool skipped = stage > 0 && !more && u->skip;
-        const int r0 = a.chunk_begin[ch], r1 = a.chunk_end[ch];
+        const int r0 = ck.z, r1 = ck.w;
+        double L_round = more ? u->step : Lcur;        // first candidate of this round
+        for (int rd = 0; rd < rounds; ++rd) {
         double D[NC], sgg = 0.0, syy = 0.0, sF = 0.0;
 #pragma unroll
         for (int q = 0; q < NC; ++q) D[q] = 0.0;
@@ -962,7 +1133,7 @@ __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage
             const double glab = group_sum<LPLOG>(gl);
             const double gg_row = group_sum<LPLOG>(gg), ug_row = group_sum<LPLOG>(ug), gd_row = group_sum<LPLOG>(gd);
             sgg += gg; syy += yy; sF += Fy;
-            double Lq = more ? u->step : Lcur;
+            double Lq = L_round;
 #pragma unroll
             for (int q = 0; q < NC; ++q) {
                 const double inv = 1.0 / Lq;
@@ -986,15 +1157,15 @@ __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage
             }
         }
         if (stage == a.J && !more) continue;
-        double* out = a.partials + (int64_t)ch * kFistaStride;
-#pragma unroll
-        for (int q = 0; q < NC; ++q) {
-            const double t = block_sum(D[q], sm);
-            if (threadIdx.x == 0) out[q] = t;
-        }
-        if (!more) {
+        if (more) {
+            block_sums_to<NC>(D, sm, a.partials + ((int64_t)ch * rounds + rd) * NC);
+            for (int q = 0; q < NC; ++q) L_round *= (double)a.sp.eta;
+        } else {
+            double* out = a.partials + (int64_t)ch * kFistaStride;
+            block_sums_to<NC>(D, sm, out);
             const double t0 = block_sum(sgg, sm), t1 = block_sum(syy, sm), t2 = block_sum(sF, sm);
             if (threadIdx.x == 0) { out[kMaxCand] = t0; out[kMaxCand + 1] = t1; out[kMaxCand + 2] = t2; }
+        }
         }
     }
 }
@@ -1002,19 +1173,21 @@ __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage
 // Takes the decisions of a pass.  first_pass: the searches of stage `stage` begin here (the counters of the finished
 // stage are added up, every solve starts from L = rho), the step floor is applied, then the first candidates are judged.
 __global__ __launch_bounds__(256) void fista_finish_kernel(FistaArgs a, int ncand, int first_pass, int stage) {
-    __shared__ double sm[4];
-    __shared__ double D[kFistaStride];
+    __shared__ double D[kRestCand];
     const int unit = blockIdx.x;
     Unit* u = a.units + unit;
     if (!first_pass && u->done) return;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
-    for (int q = 0; q < kFistaStride; ++q) {
-        if ((q < kMaxCand && q >= ncand) || (q >= kMaxCand && !first_pass)) continue;
+    const int lane = threadIdx.x & 63;
+    const int n_val = first_pass ? kFistaStride : ncand;
+    for (int q = threadIdx.x >> 6; q < n_val; q += 4) {       // a wavefront per value
+        if (first_pass && q >= ncand && q < kMaxCand) continue;
         double s = 0.0;
-        for (int i = c0 + threadIdx.x; i < c1; i += blockDim.x)
-            if (a.chunk_kind[i] == 0) s += a.partials[(int64_t)i * kFistaStride + q];
-        s = block_sum(s, sm);
-        if (threadIdx.x == 0) D[q] = s;
+        for (int i = c0 + lane; i < c1; i += 64)
+            if (a.chunks[i].y == 0) s += a.partials[(int64_t)i * n_val + q];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
+        if (lane == 0) D[q] = s;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -1035,14 +1208,8 @@ __global__ void fill_units_kernel(Unit* units, int n, double step) {
     if (i >= n) return;
     Unit u;
     u.step = step; u.step0 = step; u.keep = step; u.g = 0.0; u.bnorm = 0.0; u.done = 0; u.skip = 0; u.ntrials = 0;
-    u.spec = 0; u.total = 0; u.pad = 0;
+    u.spec = 0; u.total = 0; u.pad = 0; u.c1 = 0.0; u.c2 = 0.0;
     units[i] = u;
-}
-
-__global__ void reset_units_kernel(Unit* units, int n, SearchParams sp) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    begin_search(units + i, sp);
 }
 
 __global__ __launch_bounds__(256) void permute_rows_kernel(const float* __restrict__ src, float* __restrict__ dst,
@@ -1072,22 +1239,16 @@ void launch_phi_G(hipStream_t s, const float* T, const float* Z, float* U, float
                   int have_prev, int apply_dual, int64_t count, int last, float nu, float rho, double* partials,
                   LayerScalars* out) {
     const int nb = flat_grid(count);
-    const bool v4 = (count % 4) == 0;
-#define CADMM_PHI_G(L_, V_) hipLaunchKernelGGL((phi_G_kernel<L_, V_>), dim3(nb), dim3(256), 0, s, T, Z, U, G, Tprev, have_prev, apply_dual, count, nu, rho, partials)
-    if (last) { if (v4) CADMM_PHI_G(1, 4); else CADMM_PHI_G(1, 1); }
-    else { if (v4) CADMM_PHI_G(0, 4); else CADMM_PHI_G(0, 1); }
-#undef CADMM_PHI_G
+    if (last) hipLaunchKernelGGL((phi_G_kernel<1>), dim3(nb), dim3(256), 0, s, T, Z, U, G, Tprev, have_prev, apply_dual, count, nu, rho, partials);
+    else hipLaunchKernelGGL((phi_G_kernel<0>), dim3(nb), dim3(256), 0, s, T, Z, U, G, Tprev, have_prev, apply_dual, count, nu, rho, partials);
     hipLaunchKernelGGL(phi_G_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, last, nu, out);
 }
 
-void launch_G_only(hipStream_t s, const float* T, const float* Z, const float* U, float* G, int64_t count,
+void launch_G_only(hipStream_t s, const float* T, const float* Z, float* U, float* G, int apply_dual, int64_t count,
                    int last, float nu, float rho) {
     const int nb = flat_grid(count);
-    const bool v4 = (count % 4) == 0;
-#define CADMM_G_ONLY(L_, V_) hipLaunchKernelGGL((G_only_kernel<L_, V_>), dim3(nb), dim3(256), 0, s, T, Z, U, G, count, nu, rho)
-    if (last) { if (v4) CADMM_G_ONLY(1, 4); else CADMM_G_ONLY(1, 1); }
-    else { if (v4) CADMM_G_ONLY(0, 4); else CADMM_G_ONLY(0, 1); }
-#undef CADMM_G_ONLY
+    if (last) hipLaunchKernelGGL((G_only_kernel<1>), dim3(nb), dim3(256), 0, s, T, Z, U, G, apply_dual, count, nu, rho);
+    else hipLaunchKernelGGL((G_only_kernel<0>), dim3(nb), dim3(256), 0, s, T, Z, U, G, apply_dual, count, nu, rho);
 }
 
 void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t N, int CL, int risk,
@@ -1097,74 +1258,86 @@ void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t 
     hipLaunchKernelGGL(risk_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
 }
 
-void launch_w_norms(hipStream_t s, const float* gradW, const float* W, int count, Unit* unit, double* partials,
-                    SearchParams sp) {
-    int nb = (count + 2047) / 2048;
-    if (nb > 64) nb = 64;
-    if (nb < 1) nb = 1;
-    hipLaunchKernelGGL(w_norms_kernel, dim3(nb), dim3(256), 0, s, gradW, W, count, partials);
-    hipLaunchKernelGGL(w_norms_finish_kernel, dim3(1), dim3(64), 0, s, partials, nb, unit, sp);
+void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp) {
+    hipLaunchKernelGGL(w_begin_kernel, dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp);
 }
 
 void launch_w_trial_finish(hipStream_t s, double* partials, int n_partials, SearchParams sp, Unit* unit,
                            int32_t* status) {
-    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, n_partials, 1, 1, sp, unit, status);
+    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, n_partials, 1, sp, unit, status);
 }
 
-void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U,
-                    int64_t count, int last, int ncand, SearchParams sp, Unit* unit, double* partials,
-                    int32_t* status, int speculated) {
+void launch_w_last_search(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U, int64_t count,
+                          SearchParams sp, Unit* unit, double* partials, int32_t* status) {
     const int nb = flat_grid(count);
-    const bool v4 = (count % 4) == 0;
-#define CADMM_W_TRIAL(L_, N_, V_) hipLaunchKernelGGL((w_trial_kernel<L_, N_, V_>), dim3(nb), dim3(256), 0, s, T0, Q, Z, U, count, sp, unit, partials, speculated)
-    if (ncand == 1) {
-        if (last) { if (v4) CADMM_W_TRIAL(1, 1, 4); else CADMM_W_TRIAL(1, 1, 1); }
-        else { if (v4) CADMM_W_TRIAL(0, 1, 4); else CADMM_W_TRIAL(0, 1, 1); }
-    } else {
-        ncand = kMaxCand;
-        if (last) { if (v4) CADMM_W_TRIAL(1, kMaxCand, 4); else CADMM_W_TRIAL(1, kMaxCand, 1); }
-        else { if (v4) CADMM_W_TRIAL(0, kMaxCand, 4); else CADMM_W_TRIAL(0, kMaxCand, 1); }
-    }
-#undef CADMM_W_TRIAL
-    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, kMaxCand, ncand, sp, unit, status);
+    hipLaunchKernelGGL(w_last_sums_kernel, dim3(nb), dim3(256), 0, s, T0, Q, Z, U, count, sp.rho, unit, partials);
+    hipLaunchKernelGGL(w_last_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, sp, unit, status);
 }
 
-void launch_w_step(hipStream_t s, float* W, const float* gradW, int count_w, float* T, const float* Q,
+void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float* Z, int64_t count, int ncand,
+                    SearchParams sp, Unit* unit, double* partials, int32_t* status, int speculated) {
+    int nb = flat_grid(count);
+    if (ncand == 1)
+        hipLaunchKernelGGL((w_trial_kernel<1>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
+    else if (ncand <= 4)
+        hipLaunchKernelGGL((w_trial_kernel<4>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
+    else
+        hipLaunchKernelGGL((w_trial_kernel<kMaxCand>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp,
+                           (ncand + kMaxCand - 1) / kMaxCand, unit, partials, speculated);
+    const int nc = ncand == 1 ? 1 : ncand <= 4 ? 4 : (ncand + kMaxCand - 1) / kMaxCand * kMaxCand;
+    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, nc, sp, unit, status);
+}
+
+void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
                    int64_t count_t, const Unit* unit, int speculated) {
-    const int nb = flat_grid(count_t > count_w ? count_t : count_w);
-    if (count_t % 4 == 0) hipLaunchKernelGGL((w_step_kernel<4>), dim3(nb), dim3(256), 0, s, W, gradW, count_w, T, Q, count_t, unit, speculated);
-    else hipLaunchKernelGGL((w_step_kernel<1>), dim3(nb), dim3(256), 0, s, W, gradW, count_w, T, Q, count_t, unit, speculated);
+    const int64_t cw = (int64_t)K * C;
+    const int nb = flat_grid(count_t > cw ? count_t : cw);
+    hipLaunchKernelGGL((w_step_kernel<0>), dim3(nb), dim3(256), 0, s, W, Wt, gradW, K, C, T, Q, count_t, unit, speculated,
+                       nullptr, nullptr, nullptr, nullptr, 0.f);
 }
 
-void launch_z_trial(hipStream_t s, const ZTrialArgs& a0) {
-    ZTrialArgs a = a0;
+void launch_w_step_last(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
+                        int64_t count_t, const Unit* unit, const float* Z, const float* U, float* G, float* Tprev, float rho) {
+    const int64_t cw = (int64_t)K * C;
+    const int nb = flat_grid(count_t > cw ? count_t : cw);
+    hipLaunchKernelGGL((w_step_kernel<1>), dim3(nb), dim3(256), 0, s, W, Wt, gradW, K, C, T, Q, count_t, unit, 0, Z, U, G,
+                       Tprev, rho);
+}
+
+void launch_z_first(hipStream_t s, const ZTrialArgs& a) {
+    const bool lr = a.gradZ == nullptr;               // low-rank gradient (the caller checked the shape limits)
+    const size_t lds = lr ? (size_t)a.Cn * a.Cl * sizeof(float) : 0;          // W_{l+1}^T: at most 16 x 1024 floats
+    const dim3 grid(a.n_chunks), block(256);
     if (a.n_chunks > 0) {
-        const bool v4 = (a.Cl % 4) == 0 && (a.Cn % 4) == 0;
-        const bool lr = a.gradZ == nullptr;           // low-rank gradient (the caller checked the shape limits)
-        const size_t lds = lr ? (size_t)a.Cn * a.Cl * sizeof(float) : 0;      // W_{l+1}^T: at most 16 x 1024 floats
-        if (a.ncand == 1) {
-            if (lr) hipLaunchKernelGGL((z_trial_kernel<1, 4, 1>), dim3(a.n_chunks), dim3(256), lds, s, a);
-            else if (v4) hipLaunchKernelGGL((z_trial_kernel<1, 4, 0>), dim3(a.n_chunks), dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((z_trial_kernel<1, 1, 0>), dim3(a.n_chunks), dim3(256), 0, s, a);
+        if (a.next_is_last) {
+            if (lr) hipLaunchKernelGGL((z_first_kernel<0, 1>), grid, block, lds, s, a);
+            else hipLaunchKernelGGL((z_first_kernel<0, 0>), grid, block, 0, s, a);
         } else {
-            a.ncand = kMaxCand;
-            // a small grid: such a pass nearly always finds every community done and only has to notice it
-            const int nb = a.n_chunks < kReduceBlocks / 4 ? a.n_chunks : kReduceBlocks / 4;
-            if (lr) hipLaunchKernelGGL((z_trial_kernel<kMaxCand, 4, 1>), dim3(nb), dim3(256), lds, s, a);
-            else if (v4) hipLaunchKernelGGL((z_trial_kernel<kMaxCand, 4, 0>), dim3(nb), dim3(256), 0, s, a);
-            else hipLaunchKernelGGL((z_trial_kernel<kMaxCand, 1, 0>), dim3(nb), dim3(256), 0, s, a);
+            if (lr) hipLaunchKernelGGL((z_first_kernel<1, 1>), grid, block, lds, s, a);
+            else hipLaunchKernelGGL((z_first_kernel<1, 0>), grid, block, 0, s, a);
         }
     }
-    hipLaunchKernelGGL(z_trial_finish_kernel, dim3(a.M), dim3(256), 0, s, a);
+    if (a.next_is_last) hipLaunchKernelGGL((z_first_finish_kernel<0>), dim3(a.M), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((z_first_finish_kernel<1>), dim3(a.M), dim3(256), 0, s, a);
+}
+
+void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand) {
+    // the pass of four is often needed and takes a grid that fills the chip, the others hardly ever
+    const int cap = ncand <= 4 ? kReduceBlocks : kReduceBlocks / 4;
+    const dim3 grid(a.n_chunks < cap ? a.n_chunks : cap), block(256);
+    const int rounds = (ncand + kMaxCand - 1) / kMaxCand;
+    if (a.n_chunks > 0) {
+        if (ncand <= 4) hipLaunchKernelGGL((z_more_kernel<4>), grid, block, 0, s, a, 1);
+        else hipLaunchKernelGGL((z_more_kernel<kMaxCand>), grid, block, 0, s, a, rounds);
+    }
+    hipLaunchKernelGGL(z_more_finish_kernel, dim3(a.M), dim3(256), 0, s, a, ncand <= 4 ? 4 : rounds * kMaxCand);
 }
 
 void launch_z_step(hipStream_t s, float* Zl, const float* gradZ, const int32_t* row_comm, int64_t N, int Cl,
                    const Unit* units, int M) {
     const int nb = flat_grid(N * (int64_t)Cl);
-#define CADMM_ZSTEP(V_, L_) hipLaunchKernelGGL((z_step_kernel<V_, L_>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M)
-    if (M <= kStepUnits) { if (Cl % 4 == 0) CADMM_ZSTEP(4, true); else CADMM_ZSTEP(1, true); }
-    else { if (Cl % 4 == 0) CADMM_ZSTEP(4, false); else CADMM_ZSTEP(1, false); }
-#undef CADMM_ZSTEP
+    if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
+    else hipLaunchKernelGGL((z_step_kernel<false>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
 }
 
 void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const float* SG, const float* Wt, float nu,
@@ -1179,24 +1352,30 @@ void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const floa
         hipLaunchKernelGGL((z_step_lowrank_kernel<false>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M);
 }
 
-void launch_t_carry(hipStream_t s, float* Tn, const float* P, const int64_t* row_seg_ptr, const int32_t* seg_comm,
-                    const int32_t* seg_pos, int64_t N, int Cn, const Unit* units, int M) {
+void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int Cn) {
     const int nb = flat_grid(N * (int64_t)Cn * 4);
-#define CADMM_CARRY(V_, L_) hipLaunchKernelGGL((t_carry_kernel<V_, L_>), dim3(nb), dim3(256), 0, s, Tn, P, row_seg_ptr, seg_comm, seg_pos, N, Cn, units, M)
-    if (M <= kCarryUnits) { if (Cn % 4 == 0) CADMM_CARRY(4, true); else CADMM_CARRY(1, true); }
-    else { if (Cn % 4 == 0) CADMM_CARRY(4, false); else CADMM_CARRY(1, false); }
-#undef CADMM_CARRY
+    if (k.M <= kStepUnits) hipLaunchKernelGGL((t_carry_kernel<true>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
+    else hipLaunchKernelGGL((t_carry_kernel<false>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
 }
 
-void launch_last_layer(hipStream_t s, float* ZL, float* U, const float* TL, const int32_t* labels, int64_t N,
-                       int CL, int risk, float rho, int J, int update_u) {
-#define CADMM_LAST(LG_) hipLaunchKernelGGL((last_layer_kernel<LG_>), dim3((unsigned)(((N << LG_) + 255) / 256)), dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u)
+void launch_last_layer(hipStream_t s, float* ZL, float* U, float* TL, const int32_t* labels, int64_t N,
+                       int CL, int risk, float rho, int J, int update_u, const CarryArgs* carry, float* G) {
+    const CarryArgs k = carry ? *carry : CarryArgs();
+#define CADMM_LAST(LG_) do { \
+        const dim3 grid((unsigned)(((N << LG_) + 255) / 256)); \
+        if (!carry) hipLaunchKernelGGL((last_layer_kernel<LG_, 0, true>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, nullptr); \
+        else if (k.M <= kStepUnits) hipLaunchKernelGGL((last_layer_kernel<LG_, 1, true>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G); \
+        else hipLaunchKernelGGL((last_layer_kernel<LG_, 1, false>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G); } while (0)
     if (CL <= 4) CADMM_LAST(0);
     else if (CL <= 8) CADMM_LAST(1);
     else if (CL <= 16) CADMM_LAST(2);
     else if (CL <= 32) CADMM_LAST(3);
     else CADMM_LAST(4);
 #undef CADMM_LAST
+}
+
+void launch_lowrank_operand(hipStream_t s, const float* W, float* Bcat, int Cl, int Cn) {
+    hipLaunchKernelGGL(lowrank_operand_kernel, dim3(1), dim3(256), (size_t)Cl * Cn * sizeof(float), s, W, Bcat, Cl, Cn);
 }
 
 void launch_relu(hipStream_t s, const float* T, float* Z, int64_t count, int apply_relu) {
@@ -1207,33 +1386,30 @@ void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, int64_t N,
     hipLaunchKernelGGL(argmax_rows_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, T, pred, N, C);
 }
 
-void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, float mom) {
+void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, int ncand, float mom) {
     if (a.n_chunks <= 0) return;
-    // more = 0: the pass that takes the step and tries the first candidate (sixteen at once in stage 0, where L climbs
-    // from rho); more = 1: four further candidates on a full grid (a step usually needs one or two doublings, in many
-    // communities at once); more = 2: sixteen further candidates on a small grid, which usually finds nothing pending
-    const int nc = more == 0 ? (stage == 0 ? kMaxCand : 1) : (more == 1 ? 4 : kMaxCand);
-    const int cap = more == 0 ? a.n_chunks : (more == 1 ? kReduceBlocks : kReduceBlocks / 4);
+    // more = 0: the pass that takes the step and tries the first candidates; more = 1: ncand further candidates, four on a
+    // grid that fills the chip (a step usually needs one or two doublings, in many communities at once), more of them on a
+    // small grid, which usually finds nothing pending
+    const int nc = ncand <= 1 ? 1 : ncand <= 4 ? 4 : kMaxCand;
+    const int rounds = (ncand + nc - 1) / nc;
+    const int cap = more == 0 ? a.n_chunks : (nc == 4 ? kReduceBlocks : kReduceBlocks / 4);
     const int nb = a.n_chunks < cap ? a.n_chunks : cap;
 #define CADMM_FISTA(LG_) do { \
-        if (nc == kMaxCand) hipLaunchKernelGGL((fista_stage_kernel<LG_, kMaxCand>), dim3(nb), dim3(256), 0, s, a, stage, more, mom); \
-        else if (nc == 4) hipLaunchKernelGGL((fista_stage_kernel<LG_, 4>), dim3(nb), dim3(256), 0, s, a, stage, more, mom); \
-        else hipLaunchKernelGGL((fista_stage_kernel<LG_, 1>), dim3(nb), dim3(256), 0, s, a, stage, more, mom); } while (0)
+        if (nc == kMaxCand) hipLaunchKernelGGL((fista_stage_kernel<LG_, kMaxCand>), dim3(nb), dim3(256), 0, s, a, stage, more, rounds, mom); \
+        else if (nc == 4) hipLaunchKernelGGL((fista_stage_kernel<LG_, 4>), dim3(nb), dim3(256), 0, s, a, stage, more, rounds, mom); \
+        else hipLaunchKernelGGL((fista_stage_kernel<LG_, 1>), dim3(nb), dim3(256), 0, s, a, stage, more, rounds, mom); } while (0)
     if (a.CL <= 4) CADMM_FISTA(0);
     else if (a.CL <= 8) CADMM_FISTA(1);
     else if (a.CL <= 16) CADMM_FISTA(2);
     else if (a.CL <= 32) CADMM_FISTA(3);
     else CADMM_FISTA(4);
 #undef CADMM_FISTA
-    if (stage < a.J) hipLaunchKernelGGL(fista_finish_kernel, dim3(a.M), dim3(256), 0, s, a, nc, more ? 0 : 1, stage);
+    if (stage < a.J) hipLaunchKernelGGL(fista_finish_kernel, dim3(a.M), dim3(256), 0, s, a, nc * rounds, more ? 0 : 1, stage);
 }
 
 void launch_fill_units(hipStream_t s, Unit* units, int n, double step) {
     hipLaunchKernelGGL(fill_units_kernel, dim3((n + 255) / 256), dim3(256), 0, s, units, n, step);
-}
-
-void launch_reset_units(hipStream_t s, Unit* units, int n, SearchParams sp) {
-    hipLaunchKernelGGL(reset_units_kernel, dim3((n + 255) / 256), dim3(256), 0, s, units, n, sp);
 }
 
 void launch_permute_rows(hipStream_t s, const float* src, float* dst, const int32_t* idx, int64_t N, int C,

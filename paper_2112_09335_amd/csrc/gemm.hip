@@ -25,16 +25,36 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int BM = 128;
 constexpr int BK = 16;
 
-__device__ __forceinline__ float4 ld4_guard(const float* base, int64_t off, bool ok, bool aligned, int valid) {
-    // valid: number of in-range elements (0..4) starting at off
+// Up to four consecutive floats at any four-byte alignment (the chip takes 16-byte global accesses at any dword; a
+// matrix whose width is no multiple of four has rows that start anywhere); entries past `valid` read as zero.
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ void ld4u(float (&d)[4], const float* p, int valid) {
+    if (valid >= 4) {
+        const float4u v = *reinterpret_cast<const float4u*>(p);
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    } else {
+        d[0] = valid > 0 ? p[0] : 0.f;
+        d[1] = valid > 1 ? p[1] : 0.f;
+        d[2] = valid > 2 ? p[2] : 0.f;
+        d[3] = 0.f;
+    }
+}
+__device__ __forceinline__ void st4u(float* p, const float (&d)[4], int valid) {
+    if (valid >= 4) {
+        float4u v = {d[0], d[1], d[2], d[3]};
+        *reinterpret_cast<float4u*>(p) = v;
+    } else {
+        p[0] = d[0];
+        if (valid > 1) p[1] = d[1];
+        if (valid > 2) p[2] = d[2];
+    }
+}
+__device__ __forceinline__ float4 ld4_guard(const float* base, int64_t off, bool ok, int valid) {
+    // valid: number of in-range elements starting at off (none if <= 0)
     if (!ok || valid <= 0) return make_float4(0.f, 0.f, 0.f, 0.f);
-    if (aligned && valid >= 4) return *reinterpret_cast<const float4*>(base + off);
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    v.x = base[off];
-    if (valid > 1) v.y = base[off + 1];
-    if (valid > 2) v.z = base[off + 2];
-    if (valid > 3) v.w = base[off + 3];
-    return v;
+    float v[4];
+    ld4u(v, base + off, valid);
+    return make_float4(v[0], v[1], v[2], v[3]);
 }
 
 // Consecutive workgroups go round-robin to the eight XCDs, each with an L2 of its own.  Workgroups that read the
@@ -70,7 +90,6 @@ __device__ __forceinline__ void tile128_epilogue(floatx16 (&acc)[2][2], float* C
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lk = lane >> 5;
-    const bool c_al = (C % 4) == 0;
     double inv0 = 0.0, dsum = 0.0;
     bool take = false;
     if constexpr (EPI == 2) {
@@ -109,36 +128,20 @@ __device__ __forceinline__ void tile128_epilogue(floatx16 (&acc)[2][2], float* C
             const int c = c0 + 4 * cq;
             if (row >= n || c >= C) continue;
             const float4 v4 = *reinterpret_cast<const float4*>(Cs + rl * LDC + 4 * cq);
-            float v[4] = {v4.x, v4.y, v4.z, v4.w};
+            float v[4] = {v4.x, v4.y, v4.z, v4.w}, z[4] = {0.f, 0.f, 0.f, 0.f}, t[4] = {0.f, 0.f, 0.f, 0.f};
             const int64_t o = row * C + c;
-            if (c_al) {
-                float4 z4 = make_float4(0.f, 0.f, 0.f, 0.f), t4 = z4;
-                if constexpr (EPI != 0) {
-                    z4 = *reinterpret_cast<const float4*>(Zl + o);
-                    t4 = *reinterpret_cast<const float4*>(tin + o);
-                }
-                v[0] = finish(v[0], z4.x, t4.x);
-                v[1] = finish(v[1], z4.y, t4.y);
-                v[2] = finish(v[2], z4.z, t4.z);
-                v[3] = finish(v[3], z4.w, t4.w);
-                if constexpr (EPI == 2) {
-                    if (take) *reinterpret_cast<float4*>(Tio + o) = t4;
-                    else *reinterpret_cast<float4*>(out + o) = make_float4(v[0], v[1], v[2], v[3]);
-                } else {
-                    *reinterpret_cast<float4*>(out + o) = make_float4(v[0], v[1], v[2], v[3]);
-                }
+            const int nv = C - c;                       // columns of this lane (four, or the row's last few)
+            if constexpr (EPI != 0) {
+                ld4u(z, Zl + o, nv);
+                ld4u(t, tin + o, nv);
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = finish(v[e], z[e], t[e]);     // (zeros past the row's end add nothing)
+            if constexpr (EPI == 2) {
+                if (take) st4u(Tio + o, t, nv);
+                else st4u(out + o, v, nv);
             } else {
-                for (int e = 0; e < 4 && c + e < C; ++e) {
-                    float z = 0.f, t = 0.f;
-                    if constexpr (EPI != 0) { z = Zl[o + e]; t = tin[o + e]; }
-                    const float w = finish(v[e], z, t);
-                    if constexpr (EPI == 2) {
-                        if (take) Tio[o + e] = t;
-                        else out[o + e] = w;
-                    } else {
-                        out[o + e] = w;
-                    }
-                }
+                st4u(out + o, v, nv);
             }
         }
     }
@@ -194,8 +197,6 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
     xcd_group(blockIdx.x, gridDim.x, (unsigned)ctiles, mtile, ctile);
     const int64_t m0 = mtile * BM;
     const int c0 = ctile * BN;
-    const bool a_al = (K % 4) == 0;
-    const bool b_al = (C % 4) == 0;
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
             const int row = f / A_Q, kq = f % A_Q;
             const int64_t gr = m0 + row;
             const int k = k0 + 4 * kq;
-            ra[i] = ld4_guard(A, gr * K + k, gr < n, a_al, K - k);
+            ra[i] = ld4_guard(A, gr * K + k, gr < n, K - k);
         }
 #pragma unroll
         for (int i = 0; i < B_PER_T; ++i) {
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
             if (f < B_F4) {
                 const int kr = f / (BN / 4), cq = f % (BN / 4);
                 const int k = k0 + kr, c = c0 + 4 * cq;
-                rb[i] = ld4_guard(B, (int64_t)k * C + c, k < K, b_al, C - c);
+                rb[i] = ld4_guard(B, (int64_t)k * C + c, k < K, C - c);
             }
         }
     };
@@ -340,8 +341,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     xcd_group(blockIdx.x, gridDim.x, (unsigned)ctiles, mtile, ctile);
     const int64_t m0 = mtile * BM;
     const int c0 = ctile * BN;
-    const bool a_al = (K % 4) == 0;
-    const bool b_al = (C % 4) == 0;
 
     floatx16 acc[2][2];
 #pragma unroll
@@ -362,7 +361,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
             const int row = f >> 2, kq = f & 3;
             const int64_t gr = m0 + row;
             const int k = k0 + 4 * kq;
-            ra[i] = ld4_guard(A, gr * K + k, gr < n, a_al, K - k);
+            ra[i] = ld4_guard(A, gr * K + k, gr < n, K - k);
         }
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -454,7 +453,6 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     const int wm = tid >> 6;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     const int K = K1 + K2;
-    const bool b_al = (C % 4) == 0;
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -484,7 +482,7 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
         {
             const int kr = tid / (BN / 4), cq = tid % (BN / 4);      // 32 x 8 float4, one per thread
             const int k = k0 + kr, c = 4 * cq;
-            rb = ld4_guard(Bcat, (int64_t)k * C + c, k < K, b_al, C - c);
+            rb = ld4_guard(Bcat, (int64_t)k * C + c, k < K, C - c);
         }
     };
     auto stash = [&]() {
@@ -558,8 +556,6 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
     const int c0 = (tile % ctiles) * BN;
     const int64_t r_begin = chunk * rows_per_chunk;
     const int64_t r_end = (r_begin + rows_per_chunk < n) ? (r_begin + rows_per_chunk) : n;
-    const bool a_al = (K % 4) == 0;
-    const bool g_al = (C % 4) == 0;
 
     floatx16 acc[TM][TN];
 #pragma unroll
@@ -577,7 +573,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
             const int rr = f >> 5, kq = f & 31;
             const int64_t gr = r0 + rr;
             const int k = k0 + 4 * kq;
-            ra[i] = ld4_guard(A, gr * K + k, gr < r_end, a_al, K - k);
+            ra[i] = ld4_guard(A, gr * K + k, gr < r_end, K - k);
         }
 #pragma unroll
         for (int i = 0; i < G_PER_T; ++i) {
@@ -586,10 +582,10 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
                 const int rr = f / (BN / 4), cq = f % (BN / 4);
                 const int64_t gr = r0 + rr;
                 const int c = c0 + 4 * cq;
-                rg[i] = ld4_guard(G, gr * C + c, gr < r_end, g_al, C - c);
+                rg[i] = ld4_guard(G, gr * C + c, gr < r_end, C - c);
                 if constexpr (PRO == 1) {
                     const float4 t = rg[i];
-                    const float4 z = ld4_guard(Zl, gr * C + c, gr < r_end, g_al, C - c);
+                    const float4 z = ld4_guard(Zl, gr * C + c, gr < r_end, C - c);
                     rg[i].x = (t.x > 0.f) ? nu * (t.x - z.x) : 0.f;
                     rg[i].y = (t.y > 0.f) ? nu * (t.y - z.y) : 0.f;
                     rg[i].z = (t.z > 0.f) ? nu * (t.z - z.z) : 0.f;
@@ -769,20 +765,47 @@ __global__ __launch_bounds__(256) void gemm_tn_split_kernel(const float* __restr
         }
 }
 
-// Eight lanes share one output entry: lane j adds chunks j, j+8, ... in order, then the eight partial
-// sums are added in lane order by a shuffle tree (fixed order, so the result is reproducible).
-__global__ __launch_bounds__(256) void gemm_tn_reduce_kernel(const float* __restrict__ partial,
-                                                             float* __restrict__ out, int64_t count, int nchunks) {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t i = t >> 3;
-    const int j = (int)(t & 7);
-    double acc = 0.0;
-    if (i < count)
-        for (int c = j; c < nchunks; c += 8) acc += (double)partial[(int64_t)c * count + i];
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    acc += __shfl_xor(acc, 4, 64);
-    if (i < count && j == 0) out[i] = (float)acc;
+// out = sum of the chunks' partial matrices, in fp64 and in a fixed order.  A workgroup takes 64 entries: sixteen lanes of
+// four consecutive entries, sixteen groups of lanes that take the chunks round-robin and are added up in LDS.
+// With W, the workgroup also leaves its share of ||out||^2 and ||W||^2 in norms (two doubles per workgroup).
+__global__ __launch_bounds__(256) void gemm_tn_reduce_kernel(const float* __restrict__ partial, float* __restrict__ out,
+                                                             int64_t count, int nchunks, const float* __restrict__ W,
+                                                             double* __restrict__ norms) {
+    __shared__ double sm[16][64];
+    const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+    double ng = 0.0, nw = 0.0;
+    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < count; i0 += (int64_t)gridDim.x * 64) {
+        const int64_t i = i0 + 4 * x;
+        double acc[4] = {0.0, 0.0, 0.0, 0.0};
+        if (i < count)
+            for (int c = y; c < nchunks; c += 16) {
+                float v[4];
+                ld4u(v, partial + (int64_t)c * count + i, count - i < 4 ? (int)(count - i) : 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += (double)v[e];
+            }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sm[y][4 * x + e] = acc[e];
+        __syncthreads();
+        if (threadIdx.x < 64 && i0 + threadIdx.x < count) {
+            double t = 0.0;
+#pragma unroll
+            for (int q = 0; q < 16; ++q) t += sm[q][threadIdx.x];
+            const float g = (float)t;
+            out[i0 + threadIdx.x] = g;
+            if (W) {
+                const double w = (double)W[i0 + threadIdx.x];
+                ng += (double)g * (double)g;
+                nw += w * w;
+            }
+        }
+    }
+    if (W && threadIdx.x < 64) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { ng += __shfl_down(ng, o, 64); nw += __shfl_down(nw, o, 64); }
+        if (threadIdx.x == 0) { norms[2 * blockIdx.x] = ng; norms[2 * blockIdx.x + 1] = nw; }
+    }
 }
 
 __global__ __launch_bounds__(256) void transpose_kernel(const float* __restrict__ in, float* __restrict__ out,
@@ -956,9 +979,9 @@ size_t gemm_tn_scratch_floats(int64_t n, int K, int C) {
     return (size_t)p.nchunks * K * C;
 }
 
-void launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
-                    float* partial, const float* Zl, float nu) {
-    if (K <= 0 || C <= 0) return;
+int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
+                   float* partial, const float* Zl, float nu, const float* W, double* norms) {
+    if (K <= 0 || C <= 0) return 0;
     TnPlan p = tn_plan(n, K, C);
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.tiles)), block(256);
     if (g_split && p.bn == 128) {
@@ -976,8 +999,10 @@ void launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, i
             hipLaunchKernelGGL((gemm_tn_kernel<32, 0>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
     }
     const int64_t count = (int64_t)K * C;
-    hipLaunchKernelGGL(gemm_tn_reduce_kernel, dim3((unsigned)((count * 8 + 255) / 256)), dim3(256), 0, s, partial, out,
-                       count, p.nchunks);
+    const int64_t tiles = (count + 63) / 64;
+    const int nb = (int)(tiles < kReduceBlocks ? tiles : kReduceBlocks);
+    hipLaunchKernelGGL(gemm_tn_reduce_kernel, dim3(nb), dim3(256), 0, s, partial, out, count, p.nchunks, W, norms);
+    return nb;
 }
 
 double launch_mfma_chain(hipStream_t s, float* out, int blocks, int iters) {

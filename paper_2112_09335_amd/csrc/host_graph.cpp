@@ -233,8 +233,31 @@ bool block_table_ok(const RowSchedule& rs, int lpr_log2, const BlockTable& bt) {
     return true;
 }
 
+void build_chunks(const HostGraph& g, int64_t rows, int64_t segs, std::vector<Chunk>& chunks, std::vector<int32_t>& unit_ptr) {
+    chunks.clear();
+    chunks.reserve((size_t)count_chunks(g, rows, segs));
+    unit_ptr.assign(g.M + 1, 0);
+    auto cut = [&](int32_t m, int32_t kind, int64_t begin, int64_t end, int64_t per) {
+        for (int64_t b = begin; b < end; b += per) chunks.push_back({m, kind, (int32_t)b, (int32_t)std::min(b + per, end)});
+    };
+    for (int32_t m = 0; m < g.M; ++m) {
+        cut(m, 0, g.comm_row_ptr[m], g.comm_row_ptr[m + 1], rows);
+        if (segs > 0) cut(m, 1, g.segc_comm_ptr[m], g.segc_comm_ptr[m + 1], segs);
+        unit_ptr[m + 1] = (int32_t)chunks.size();
+    }
+}
+
+int64_t count_chunks(const HostGraph& g, int64_t rows, int64_t segs) {
+    int64_t n = 0;
+    for (int32_t m = 0; m < g.M; ++m) {
+        n += (g.comm_row_ptr[m + 1] - g.comm_row_ptr[m] + rows - 1) / rows;
+        if (segs > 0) n += (g.segc_comm_ptr[m + 1] - g.segc_comm_ptr[m] + segs - 1) / segs;
+    }
+    return n;
+}
+
 std::string build_host_graph(HostGraph& g, int64_t N, int64_t n_edges, const int32_t* src,
-                             const int32_t* dst, int32_t M, const int32_t* comm, int chunk_rows) {
+                             const int32_t* dst, int32_t M, const int32_t* comm) {
     if (N < 1 || N > INT32_MAX) return "N must be in [1, 2^31)";
     if (M < 1) return "M must be positive";
     if (n_edges < 0) return "n_edges must be non-negative";
@@ -419,23 +442,6 @@ std::string build_host_graph(HostGraph& g, int64_t N, int64_t n_edges, const int
         }
     }
 
-    // reduction chunks: for every community its own rows, then its segments.  A segment carries a row of the next
-    // layer: where that layer is narrow, eight times as many segments as rows go into a chunk, so that a chunk's fixed
-    // costs (unit state, block reductions) do not outweigh its pass over memory; where it is wide, as many as rows, or
-    // the few heavy chunks of a community are what the launch waits for.
-    auto build_chunks = [&](int64_t chunk_segs, std::vector<Chunk>& chunks, std::vector<int32_t>& ptr) {
-        chunks.clear();
-        ptr.assign(M + 1, 0);
-        for (int32_t m = 0; m < M; ++m) {
-            for (int64_t b = g.comm_row_ptr[m]; b < g.comm_row_ptr[m + 1]; b += chunk_rows)
-                chunks.push_back({m, 0, (int32_t)b, (int32_t)std::min<int64_t>(b + chunk_rows, g.comm_row_ptr[m + 1])});
-            for (int64_t b = g.segc_comm_ptr[m]; b < g.segc_comm_ptr[m + 1]; b += chunk_segs)
-                chunks.push_back({m, 1, (int32_t)b, (int32_t)std::min<int64_t>(b + chunk_segs, g.segc_comm_ptr[m + 1])});
-            ptr[m + 1] = (int32_t)chunks.size();
-        }
-    };
-    build_chunks((int64_t)chunk_rows * 8, g.chunks, g.unit_chunk_ptr);
-    build_chunks((int64_t)chunk_rows, g.chunks_wide, g.unit_chunk_ptr_wide);
     return "";
 }
 

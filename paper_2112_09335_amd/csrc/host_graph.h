@@ -101,16 +101,15 @@ struct HostGraph {
     RowSchedule row_sched;              // the CSR rows; output row = the row, group = its community
     RowSchedule seg_sched;              // the segments with several entries; output row = position in the (community, row) order,
                                         // group = the segment's community
-    // reduction chunks for the Z search, grouped by community: many segments per chunk for a narrow next layer ...
-    std::vector<Chunk>   chunks;
-    std::vector<int32_t> unit_chunk_ptr; // [M+1]
-    // ... and the same with as many segments as rows per chunk, for a wide one
-    std::vector<Chunk>   chunks_wide;
-    std::vector<int32_t> unit_chunk_ptr_wide;
 };
+
+// Reduction chunks: for every community its rows, `rows` at a time, then its segments in the (community, row) order, `segs`
+// at a time (0: none); unit_ptr [M+1] = first chunk of every community.
+void build_chunks(const HostGraph& g, int64_t rows, int64_t segs, std::vector<Chunk>& chunks, std::vector<int32_t>& unit_ptr);
+int64_t count_chunks(const HostGraph& g, int64_t rows, int64_t segs);
 
 // Returns an empty string on success, an error text otherwise.
 std::string build_host_graph(HostGraph& g, int64_t N, int64_t n_edges, const int32_t* src,
-                             const int32_t* dst, int32_t M, const int32_t* comm, int chunk_rows);
+                             const int32_t* dst, int32_t M, const int32_t* comm);
 
 }  // namespace cadmm

@@ -90,17 +90,19 @@ void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const
 // out[K x C] = A[n x K]^T * G[n x C]; partial: scratch of gemm_tn_scratch_floats(n,K,C) floats.
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C);
 // With Zl != nullptr, G holds the pre-activation T of a hidden layer and the right operand is
-// nu (relu(T) - Zl) 1[T > 0], formed on the fly.
-void launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
-                    float* partial, const float* Zl = nullptr, float nu = 0.f);
+// nu (relu(T) - Zl) 1[T > 0], formed on the fly.  With W (K x C), norms gets block sums of ||out||^2 and ||W||^2 (pairs);
+// returns how many (at most kReduceBlocks).
+int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
+                   float* partial, const float* Zl = nullptr, float nu = 0.f, const float* W = nullptr,
+                   double* norms = nullptr);
 // out[C x K] = in[K x C]^T (small)
 void launch_transpose(hipStream_t s, const float* in, float* out, int K, int C);
 
 // ---------------------------------------------------------------- fused elementwise + reductions (elementwise.hip)
 constexpr int kReduceBlocks = 2048;      // grid of the flat reducing kernels
-constexpr int kMaxCand = 16;             // step-size candidates evaluated per pass
+constexpr int kMaxCand = 16;             // step-size candidates evaluated at once in a later pass
+constexpr int kRestCand = 64;            // most candidates a pass evaluates (in rounds of kMaxCand)
 constexpr int kLowRankMax = 16;          // widest next layer for which the Z gradient is kept in low-rank form
-constexpr int kChunkRows = 128;          // rows / segments per reduction chunk of the Z search
 
 // One step-size search ("unit"): a layer's tau, or a (layer, community)'s theta.
 struct Unit {
@@ -115,6 +117,7 @@ struct Unit {
     int32_t spec;      // the previous search accepted its first candidate: a speculative step with step0 is safe
     int32_t total;     // candidates tested since the counter was cleared (the last-layer solve adds up its steps)
     int32_t pad;
+    double c1, c2;     // the part of the objective's change that is quadratic in 1/step: c1 / step + c2 / step^2
 };
 
 // Readout scalars of one layer's base evaluation.
@@ -137,31 +140,38 @@ struct SearchParams {
 void launch_phi_G(hipStream_t s, const float* T, const float* Z, float* U, float* G, float* Tprev,
                   int have_prev, int apply_dual, int64_t count, int last, float nu, float rho, double* partials,
                   LayerScalars* out);
-// G only (no reduction), same formulas.
-void launch_G_only(hipStream_t s, const float* T, const float* Z, const float* U, float* G, int64_t count,
+// G only (no reduction), same formulas; last layer: the dual step first if apply_dual.
+void launch_G_only(hipStream_t s, const float* T, const float* Z, float* U, float* G, int apply_dual, int64_t count,
                    int last, float nu, float rho);
 // R(Z_L, Y) summed over labelled rows -> out->risk
 void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t N, int CL, int risk,
                  double* partials, LayerScalars* out);
-// unit.g = ||gradW||^2, unit.bnorm = ||W||^2, applies the step floor, resets the search state.
-void launch_w_norms(hipStream_t s, const float* gradW, const float* W, int count, Unit* unit, double* partials,
-                    SearchParams sp);
-// One pass of the W search: candidates step*eta^j, j < ncand, on phi_l(T0 - Q/step).
-// speculated != 0: T0 already holds the speculative step T0 - Q/step0; the pass rebuilds T0 = T0 + Q/step0.
-void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U,
-                    int64_t count, int last, int ncand, SearchParams sp, Unit* unit, double* partials,
-                    int32_t* status, int speculated = 0);
+// unit.g = ||gradW||^2, unit.bnorm = ||W||^2 from block sums (pairs), applies the step floor, starts the search.
+void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp);
+// The whole W search of the last layer (its objective is quadratic in T): one pass over memory and the decision.
+void launch_w_last_search(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U, int64_t count,
+                          SearchParams sp, Unit* unit, double* partials, int32_t* status);
+// One pass of the W search of a hidden layer: the next ncand candidates step*eta^j (1, 4, or rounds of kMaxCand) on
+// phi_l(T0 - Q/step).  speculated != 0: T0 already holds the speculative step T0 - Q/step0; the pass rebuilds
+// T0 = T0 + Q/step0.
+void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float* Z, int64_t count, int ncand,
+                    SearchParams sp, Unit* unit, double* partials, int32_t* status, int speculated = 0);
 // Sums n_partials block results of an epilogue-2 product (candidate 0 only) and takes the search decision.
 void launch_w_trial_finish(hipStream_t s, double* partials, int n_partials, SearchParams sp, Unit* unit,
                            int32_t* status);
-// W -= gradW/step (count_w entries), T = T0 - Q/step (count_t entries); no-op if unit.skip.
+// W -= gradW/step, Wt (C x K, may be null) its transpose, T = T0 - Q/step (count_t entries); no-op if unit.skip.
 // speculated != 0: T already holds T0 - Q/step0 and is only repaired if the accepted step differs.
-void launch_w_step(hipStream_t s, float* W, const float* gradW, int count_w, float* T, const float* Q,
-                   int64_t count_t, const Unit* unit, int speculated = 0);
+void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
+                   int64_t count_t, const Unit* unit, int speculated);
+// The same for the last layer; it also keeps the old T in Tprev (if not null) and leaves G = -(U + rho (Z - T)) of the new
+// T (also if the step is skipped).  G may be Q.
+void launch_w_step_last(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
+                        int64_t count_t, const Unit* unit, const float* Z, const float* U, float* G, float* Tprev, float rho);
 
-// Z search, layer l (widths Cl, Cn = C_{l+1}).  Device arrays of the graph:
+// Z search, layer l (widths Cl, Cn = C_{l+1}).  chunks: (community, kind, begin, end); kind 0 = rows [begin, end) of the
+// community, kind 1 = segments [begin, end) of the (community, row) order, grouped by community.
 struct ZTrialArgs {
-    const int32_t* chunk_unit; const int32_t* chunk_kind; const int32_t* chunk_begin; const int32_t* chunk_end;
+    const int4* chunks;
     int32_t n_chunks;
     const int32_t* unit_chunk_ptr; int32_t M;
     const int32_t* segc_row;
@@ -169,17 +179,18 @@ struct ZTrialArgs {
     // low-rank form of the gradient (gradZ == nullptr): grad = nu (Zl - relu(Tl)) + SG Wt, SG is N x Cn with
     // Cn <= kLowRankMax, Wt is Cn x Cl; it is recomputed per element instead of being read
     const float* SG = nullptr; const float* Wt = nullptr;
-    const float* Tn; const float* Zn; const float* U; const float* P; int Cn;   // next layer, per segment
-    const float* Gn = nullptr;   // last next layer: G_L = -(U + rho (Z_L - T_L)), read in place of Tn, Zn and U
+    const float* Tn; const float* Zn; const float* P; int Cn;   // next layer, per segment
+    const float* Gn = nullptr;   // last next layer: G_L = -(U + rho (Z_L - T_L)), read in place of Tn and Zn
     int next_is_last;
-    int first_pass;        // also accumulate ||gradZ_m||^2 and ||Z_m||^2, apply the step floor
-    int ncand;
     SearchParams sp;
     Unit* units;           // [M]
-    double* partials;      // [n_chunks * (kMaxCand + 2)]
+    double* partials;      // [n_chunks * kRestCand]
     int32_t* status;
 };
-void launch_z_trial(hipStream_t s, const ZTrialArgs& a);
+// Starts the searches of all communities and judges the first candidate; with a last next layer, all of them.
+void launch_z_first(hipStream_t s, const ZTrialArgs& a);
+// The next ncand candidates (4, or rounds of kMaxCand) where the next layer is hidden.
+void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand);
 // Z_l[i,:] -= gradZ[i,:] / theta[comm(i)]
 void launch_z_step(hipStream_t s, float* Zl, const float* gradZ, const int32_t* row_comm, int64_t N, int Cl,
                    const Unit* units, int M);
@@ -188,37 +199,42 @@ void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const floa
                            const int32_t* row_comm, int64_t N, int Cl, int Cn, const Unit* units, int M);
 // Tn[i,:] -= sum over the segments (i,c) of row i of P[(i,c),:] / theta_c  (communities whose step was skipped
 // contribute nothing): the pre-activation of the next layer after the Z step, without a new aggregation.
-void launch_t_carry(hipStream_t s, float* Tn, const float* P, const int64_t* row_seg_ptr, const int32_t* seg_comm,
-                    const int32_t* seg_pos, int64_t N, int Cn, const Unit* units, int M);
+struct CarryArgs {
+    const float* P = nullptr;
+    const int64_t* row_seg_ptr = nullptr; const int32_t* seg_comm = nullptr; const int32_t* seg_pos = nullptr;
+    const Unit* units = nullptr; int M = 0;
+};
+void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int Cn);
 // Last layer (Appendix A, Eq. 5) by J FISTA steps per row, fused with the dual step (Eq. 2):
 //   U_new = U + rho (Z_L - T_L),  Z_L_new = FISTA(start Z_L; c = T_L, U, rho)
-// update_u = 0 leaves U alone (the dual step is then taken on the new iterates by the next phi_G)
-void launch_last_layer(hipStream_t s, float* ZL, float* U, const float* TL, const int32_t* labels, int64_t N,
-                       int CL, int risk, float rho, int J, int update_u);
+// update_u = 0 leaves U alone (the dual step is then taken on the new iterates by the next base evaluation).
+// carry: T_L is then brought to the new Z_{L-1}, and G (if not null; needs update_u) gets -(U_new + rho (Z_L_new - T_L_new)).
+void launch_last_layer(hipStream_t s, float* ZL, float* U, float* TL, const int32_t* labels, int64_t N,
+                       int CL, int risk, float rho, int J, int update_u, const CarryArgs* carry, float* G);
+// Bcat = [W; W^T W] for the low-rank form of the Z gradient (W is Cl x Cn)
+void launch_lowrank_operand(hipStream_t s, const float* W, float* Bcat, int Cl, int Cn);
 // Last layer by FISTA with backtracking on the block subproblem of Z_{L,m} (Appendix A, Eq. 5): one L per community
 // and step, found by the device-side search over the rows of the community (chunk tables of the graph, kind 0).
 // Stage `stage` of `J` steps: stage 0 evaluates 16 candidates L = rho eta^q at y_0 = Z_L; stage j = 1..J-1 takes step
 // j-1 with the L found (x_j = y_{j-1} - grad / L, y_j = x_j + mom (x_j - x_{j-1})) and evaluates the current L at
 // y_j; stage J takes the last step, writes Z_L (rows without label: their exact minimiser) and, with update_u, the dual
-// step of Eq. 2 with the old Z_L.  more = 1 launches a pass of 16 further candidates for the searches not yet done
+// step of Eq. 2 with the old Z_L.  more = 1 launches a pass of ncand further candidates for the searches not yet done
 // (it returns at once otherwise).  Every stage is followed by the finishing kernel that takes the decisions.
 struct FistaArgs {
     float* ZL; float* U; const float* TL; float* Xb; float* Yb;      // Xb, Yb: N x CL scratch (x_j and y_j)
     const int32_t* labels;
-    const int32_t* chunk_unit; const int32_t* chunk_kind; const int32_t* chunk_begin; const int32_t* chunk_end;
-    int32_t n_chunks; const int32_t* unit_chunk_ptr; int32_t M;
+    const int4* chunks; int32_t n_chunks; const int32_t* unit_chunk_ptr; int32_t M;      // as in ZTrialArgs
     int CL, risk, J, update_u;
     float rho;
     SearchParams sp;
     Unit* units;           // [M]
-    double* partials;      // [n_chunks * (kMaxCand + 3)]
+    double* partials;      // [n_chunks * kRestCand]
     int32_t* status;
 };
-void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, float mom);
+void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, int ncand, float mom);
 void launch_relu(hipStream_t s, const float* T, float* Z, int64_t count, int apply_relu);
 void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, int64_t N, int C);
 void launch_fill_units(hipStream_t s, Unit* units, int n, double step);
-void launch_reset_units(hipStream_t s, Unit* units, int n, SearchParams sp);
 // gather / scatter rows between caller order and internal order: dst[r,:] = src[idx[r],:] or dst[idx[r],:] = src[r,:]
 void launch_permute_rows(hipStream_t s, const float* src, float* dst, const int32_t* idx, int64_t N, int C,
                          int scatter);
