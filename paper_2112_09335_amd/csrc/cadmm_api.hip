@@ -23,6 +23,7 @@ using namespace cadmm;
 constexpr size_t kStaticScratchFloats = (size_t)18 << 20;          // 72 MiB
 static __device__ __align__(256) float scratch[kStaticScratchFloats];
 constexpr int kMaxDevices = 64;
+constexpr size_t kReadoutBytes = 16384;                            // pinned page for small readouts
 static float* g_scratch_ptr[kMaxDevices] = {};                     // device address of `scratch` on GPU d, once looked up
 static std::mutex g_scratch_mutex;
 
@@ -58,7 +59,7 @@ struct cadmm_ctx {
     int64_t* d_row_seg_ptr = nullptr;
     int32_t* d_seg_comm = nullptr;
     int32_t* d_seg_pos = nullptr;
-    std::vector<int32_t> h_labels;     // internal row order
+    int64_t n_labelled = 0;
     // split rows of the CSR row list and of the segment list; side buffer for their parts
     struct DevSchedule {               // device copy of a RowSchedule
         int4* rec = nullptr; int2* ent = nullptr; int32_t* long_row = nullptr; int32_t* long_ptr = nullptr;
@@ -110,6 +111,12 @@ struct cadmm_ctx {
     bool use_speculative = true;
     struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false; };
     GraphSlot graphs[32];
+    // pinned host memory, allocated when first needed and freed with the context: two pieces through which large transfers
+    // are pipelined, and a page for readouts of a few values
+    char* stage[2] = {nullptr, nullptr};
+    hipEvent_t stage_free[2] = {nullptr, nullptr};
+    char* readout = nullptr;
+    int64_t large_readouts = 0;
     // optional per-kernel-class timing with HIP events on the context's stream
     bool prof_on = false;
     struct ProfRec { int cls; hipEvent_t a, b; };
@@ -269,8 +276,9 @@ size_t layout(cadmm_ctx* c, char* base) {
     return (b.off + 255) & ~(size_t)255;
 }
 
-template <class T>
-hipError_t upload(hipStream_t s, T* dst, const std::vector<T>& src) {
+template <class T, class V>
+hipError_t upload(hipStream_t s, T* dst, const V& src) {
+    static_assert(sizeof(T) == sizeof(src[0]), "the device reads the host's records as they are");
     if (src.empty()) return hipSuccess;
     return hipMemcpyAsync(dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice, s);
 }
@@ -722,19 +730,82 @@ int check_launch(cadmm_ctx* c, const char* where) {
     return CADMM_OK;
 }
 
+// Large readouts into pageable memory go through two pinned pieces: the DMA of one runs while host threads copy the other
+// out.  The runtime's own path is one thread, which also takes the page faults of a fresh destination: 128 MB came out in
+// 12 ms, now in 4.  From kStageMin on the pieces pay once they are there (8 MB: 0.2 ms less), and getting them pays from
+// kStageGet on or with the second such readout; a program that reads 8 MB once does not wait for pinned memory.  For
+// uploads, whose source is there already, the runtime's path is the faster one at any size (27 GB/s).
+constexpr size_t kStageBytes = (size_t)8 << 20;
+constexpr size_t kStageMin = (size_t)4 << 20;
+constexpr size_t kStageGet = (size_t)16 << 20;
+constexpr int64_t kStageWork = 8 * 16384;        // HostPool work that asks for eight threads
+
+bool have_stage(cadmm_ctx* c, size_t bytes) {
+    if (bytes < kStageMin || (++c->large_readouts < 2 && bytes < kStageGet)) return false;
+    for (int k = 0; k < 2; ++k) {
+        if (!c->stage[k] && hipHostMalloc(reinterpret_cast<void**>(&c->stage[k]), kStageBytes, hipHostMallocDefault) != hipSuccess) {
+            c->stage[k] = nullptr;
+            (void)hipGetLastError();
+            return false;
+        }
+        if (!c->stage_free[k] && hipEventCreateWithFlags(&c->stage_free[k], hipEventDisableTiming) != hipSuccess) {
+            c->stage_free[k] = nullptr;
+            (void)hipGetLastError();
+            return false;
+        }
+    }
+    return true;
+}
+
+void copy_with(HostPool& pool, char* dst, const char* src, size_t bytes) {
+    pool.run((int64_t)bytes, 512 << 10, [&](int64_t lo, int64_t hi, int) { std::memcpy(dst + lo, src + lo, (size_t)(hi - lo)); });
+}
+
+// device -> host, waits for the stream
+int copy_out(cadmm_ctx* c, void* dst, const void* src, size_t bytes) {
+    if (!have_stage(c, bytes)) {
+        HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+        return CADMM_OK;
+    }
+    const size_t n = (bytes + kStageBytes - 1) / kStageBytes;
+    auto size_of = [&](size_t k) { return k + 1 < n ? kStageBytes : bytes - k * kStageBytes; };
+    auto issue = [&](size_t k) {
+        hipError_t e = hipMemcpyAsync(c->stage[k & 1], static_cast<const char*>(src) + k * kStageBytes, size_of(k), hipMemcpyDeviceToHost, c->stream);
+        return e != hipSuccess ? e : hipEventRecord(c->stage_free[k & 1], c->stream);
+    };
+    HostPool pool(kStageWork);
+    for (size_t k = 0; k < n && k < 2; ++k) HIP_TRY(c, issue(k));
+    for (size_t k = 0; k < n; ++k) {
+        HIP_TRY(c, hipEventSynchronize(c->stage_free[k & 1]));
+        copy_with(pool, static_cast<char*>(dst) + k * kStageBytes, c->stage[k & 1], size_of(k));
+        if (k + 2 < n) HIP_TRY(c, issue(k + 2));
+    }
+    return CADMM_OK;
+}
+
+// A page of pinned memory for small readouts (null if there is none to be had: the caller's pageable memory then serves).
+char* readout_page(cadmm_ctx* c) {
+    if (!c->readout && hipHostMalloc(reinterpret_cast<void**>(&c->readout), kReadoutBytes, hipHostMallocDefault) != hipSuccess) {
+        c->readout = nullptr;
+        (void)hipGetLastError();
+    }
+    return c->readout;
+}
+
 // copy an N x C matrix out in the caller's node order
 int download_rows(cadmm_ctx* c, const float* src_internal, int C, float* dst_host) {
     const int64_t N = c->hg.N;
     launch_permute_rows(c->stream, src_internal, c->tmpA, c->d_perm, N, C, 1);   // tmpA[perm[r]] = src[r]
-    HIP_TRY(c, hipMemcpyAsync(dst_host, c->tmpA, (size_t)N * C * sizeof(float), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const int rc = copy_out(c, dst_host, c->tmpA, (size_t)N * C * sizeof(float));
+    if (rc != CADMM_OK) return rc;
     return check_launch(c, "download_rows");
 }
 
 int upload_rows(cadmm_ctx* c, const float* src, int on_device, int C, float* dst_internal) {
     const int64_t N = c->hg.N;
-    HIP_TRY(c, hipMemcpyAsync(c->tmpA, src, (size_t)N * C * sizeof(float),
-                              on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
+    const size_t bytes = (size_t)N * C * sizeof(float);
+    HIP_TRY(c, hipMemcpyAsync(c->tmpA, src, bytes, on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
     launch_permute_rows(c->stream, c->tmpA, dst_internal, c->d_perm, N, C, 0);   // dst[r] = tmpA[perm[r]]
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     return check_launch(c, "upload_rows");
@@ -775,6 +846,11 @@ void cadmm_destroy(cadmm_ctx* ctx) {
         for (auto& r : ctx->prof_recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
         for (auto e : ctx->prof_pool) (void)hipEventDestroy(e);
         drop_graphs(ctx);
+        for (int k = 0; k < 2; ++k) {
+            if (ctx->stage[k]) (void)hipHostFree(ctx->stage[k]);
+            if (ctx->stage_free[k]) (void)hipEventDestroy(ctx->stage_free[k]);
+        }
+        if (ctx->readout) (void)hipHostFree(ctx->readout);
     }
     delete ctx;
 }
@@ -883,29 +959,21 @@ int cadmm_set_workspace(cadmm_ctx* c, void* dev_ptr, size_t bytes) {
     hipStream_t s = c->stream;
     HIP_TRY(c, upload(s, c->d_row_comm, g.row_comm));
     HIP_TRY(c, upload(s, c->d_perm, g.perm));
-    auto upload_schedule = [&](cadmm_ctx::DevSchedule& d, const RowSchedule& rs) -> hipError_t {
+    auto upload_schedule = [&](cadmm_ctx::DevSchedule& d, const RowSchedule& rs, const BlockTable* tables) -> hipError_t {
         hipError_t e;
         for (int l = 0; l < 7; ++l) {
-            BlockTable bt;
-            build_block_table(rs, l, bt);
-            static_assert(sizeof(BlockRows) == sizeof(int4), "table entries are read as int4");
-            if ((int64_t)bt.blocks.size() != d.n_blocks[l] || !block_table_ok(rs, l, bt)) return hipErrorInvalidValue;
+            const BlockTable& bt = tables[l];            // built and checked with the graph
+            if ((int64_t)bt.blocks.size() != d.n_blocks[l]) return hipErrorInvalidValue;
             for (int k = 0; k <= 8; ++k) d.xcd_start[l][k] = bt.xcd_start[k];
-            if (!bt.blocks.empty()) {
-                // synchronous with respect to the host buffer: the table is a temporary
-                if ((e = hipMemcpyAsync(d.blocks[l], bt.blocks.data(), bt.blocks.size() * sizeof(BlockRows),
-                                        hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-                if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-            }
+            if ((e = upload(s, d.blocks[l], bt.blocks)) != hipSuccess) return e;
         }
-        static_assert(sizeof(RowRecord) == sizeof(int4) && sizeof(EntryPair) == sizeof(int2), "records are read as int4, pairs as int2");
-        if (!rs.rec.empty() && (e = hipMemcpyAsync(d.rec, rs.rec.data(), rs.rec.size() * sizeof(RowRecord), hipMemcpyHostToDevice, s)) != hipSuccess) return e;
-        if ((e = hipMemcpyAsync(d.ent, rs.ent.data(), rs.ent.size() * sizeof(EntryPair), hipMemcpyHostToDevice, s)) != hipSuccess) return e;
+        if ((e = upload(s, d.rec, rs.rec)) != hipSuccess) return e;
+        if ((e = upload(s, d.ent, rs.ent)) != hipSuccess) return e;
         if ((e = upload(s, d.long_row, rs.long_row)) != hipSuccess) return e;
         return upload(s, d.long_ptr, rs.long_part_ptr);
     };
-    HIP_TRY(c, upload_schedule(c->d_rows, g.row_sched));
-    HIP_TRY(c, upload_schedule(c->d_segs, g.seg_sched));
+    HIP_TRY(c, upload_schedule(c->d_rows, g.row_sched, g.row_tables));
+    HIP_TRY(c, upload_schedule(c->d_segs, g.seg_sched, g.seg_tables));
     HIP_TRY(c, upload(s, c->d_seg1_pos, g.seg1_pos));
     HIP_TRY(c, upload(s, c->d_seg1_col, g.seg1_col));
     HIP_TRY(c, upload(s, c->d_seg1_val, g.seg1_val));
@@ -913,12 +981,10 @@ int cadmm_set_workspace(cadmm_ctx* c, void* dev_ptr, size_t bytes) {
     std::vector<std::vector<Chunk>> tabs(c->L + 1);                 // alive until the stream has been waited for below
     std::vector<std::vector<int32_t>> ptrs(c->L + 1);
     for (int l = 1; l <= c->L; ++l) {
-        static_assert(sizeof(Chunk) == sizeof(int4), "chunks are read as int4");
         const ChunkShape cs = chunk_shape(c, l);
         build_chunks(g, cs.rows, cs.segs, tabs[l], ptrs[l]);
         if ((int32_t)tabs[l].size() != c->d_chunks[l].n) return fail(c, CADMM_EINVAL, "internal error: reduction chunks");
-        if (!tabs[l].empty())
-            HIP_TRY(c, hipMemcpyAsync(c->d_chunks[l].tab, tabs[l].data(), tabs[l].size() * sizeof(Chunk), hipMemcpyHostToDevice, s));
+        HIP_TRY(c, upload(s, c->d_chunks[l].tab, tabs[l]));
         HIP_TRY(c, upload(s, c->d_chunks[l].unit_ptr, ptrs[l]));
     }
     HIP_TRY(c, upload(s, c->d_row_seg_ptr, g.row_seg_ptr));
@@ -926,6 +992,7 @@ int cadmm_set_workspace(cadmm_ctx* c, void* dev_ptr, size_t bytes) {
     HIP_TRY(c, upload(s, c->d_seg_pos, g.seg_pos));
     HIP_TRY(c, hipMemsetAsync(c->status, 0, 4 * sizeof(int32_t), s));
     HIP_TRY(c, hipStreamSynchronize(s));     // the host vectors above must outlive the copies
+    for (int l = 0; l < 7; ++l) c->hg.row_tables[l] = c->hg.seg_tables[l] = BlockTable();
     c->has_ws = true;
     return CADMM_OK;
 }
@@ -934,16 +1001,20 @@ int cadmm_set_data(cadmm_ctx* c, const float* X, const int32_t* labels, int x_on
     if (!c || !X || !labels) return CADMM_EINVAL;
     if (!c->has_ws) return fail(c, CADMM_EORDER, "set_workspace first");
     const int64_t N = c->hg.N;
-    std::vector<int32_t> lab(N);
-    for (int64_t r = 0; r < N; ++r) {
-        int32_t y = labels[c->hg.perm[r]];
-        if (y < -1 || y >= c->C[c->L]) return fail(c, CADMM_EINVAL, "label out of range");
-        lab[r] = y;
+    int64_t labelled = 0;
+    bool bad = false;
+    const int32_t n_classes = c->C[c->L];
+    for (int64_t i = 0; i < N; ++i) {
+        bad |= labels[i] < -1 || labels[i] >= n_classes;
+        labelled += labels[i] >= 0;
     }
-    HIP_TRY(c, hipMemcpyAsync(c->d_labels, lab.data(), N * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
-    int rc = upload_rows(c, X, x_on_device, c->C[0], c->Z[0]);     // synchronises
+    if (bad) return fail(c, CADMM_EINVAL, "label out of range");
+    c->n_labelled = labelled;
+    HIP_TRY(c, hipMemcpyAsync(c->d_pred, labels, (size_t)N * sizeof(int32_t), hipMemcpyHostToDevice, c->stream));
+    // class ids are moved as 32-bit words
+    launch_permute_rows(c->stream, reinterpret_cast<const float*>(c->d_pred), reinterpret_cast<float*>(c->d_labels), c->d_perm, N, 1, 0);
+    const int rc = upload_rows(c, X, x_on_device, c->C[0], c->Z[0]);         // synchronises
     if (rc != CADMM_OK) return rc;
-    c->h_labels.swap(lab);
     c->has_data = true;
     c->has_init = false;
     return CADMM_OK;
@@ -1033,11 +1104,16 @@ int cadmm_eval(cadmm_ctx* c, cadmm_stats* out, double* layer_penalty) {
     if (!c->has_init) return fail(c, CADMM_EORDER, "init first");
     const int L = c->L;
     eval_scalars(c);
-    std::vector<LayerScalars> sc(L + 1);
-    int32_t st[4] = {0, 0, 0, 0};
-    HIP_TRY(c, hipMemcpyAsync(sc.data(), c->scalars, (L + 1) * sizeof(LayerScalars), hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(st, c->status, sizeof(st), hipMemcpyDeviceToHost, c->stream));
+    // the scalars and, behind them, the status word in one copy
+    const size_t bytes = (size_t)(reinterpret_cast<char*>(c->status) - reinterpret_cast<char*>(c->scalars)) + 4 * sizeof(int32_t);
+    std::vector<char> pageable;
+    char* page = bytes <= kReadoutBytes ? readout_page(c) : nullptr;
+    if (!page) { pageable.resize(bytes); page = pageable.data(); }
+    HIP_TRY(c, hipMemcpyAsync(page, c->scalars, bytes, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const LayerScalars* sc = reinterpret_cast<const LayerScalars*>(page);
+    int32_t st[4];
+    std::memcpy(st, page + bytes - sizeof(st), sizeof(st));
     double pen = 0.0;
     for (int l = 1; l < L; ++l) {
         pen += sc[l].phi;
@@ -1079,16 +1155,25 @@ int cadmm_predict(cadmm_ctx* c, int32_t* pred, float* logits, double* accuracy) 
     // the T and G buffers now hold the forward pass, not images of the state
     c->base_valid = c->gl_valid = c->gh_valid = c->scal_valid = false;
     c->t1_age = -1;
-    launch_argmax_rows(s, c->T[L], c->d_pred, N, c->C[L]);
-    std::vector<int32_t> p((size_t)N);
-    HIP_TRY(c, hipMemcpyAsync(p.data(), c->d_pred, N * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIP_TRY(c, hipStreamSynchronize(s));
-    int64_t labelled = 0, hit = 0;
-    for (int64_t r = 0; r < N; ++r) {
-        if (pred) pred[c->hg.perm[r]] = p[r];
-        if (c->h_labels[r] >= 0) { ++labelled; hit += (p[r] == c->h_labels[r]); }
+    // classes in the caller's node order, and per workgroup how many labelled nodes have their label
+    static_assert(kArgmaxBlocks * sizeof(int32_t) <= kReadoutBytes, "the counts fit the readout page");
+    int32_t* const hits_dev = reinterpret_cast<int32_t*>(c->partials);
+    launch_argmax_rows(s, c->T[L], c->d_pred, c->d_perm, c->d_labels, hits_dev, N, c->C[L]);
+    std::vector<int32_t> hits_host;
+    int32_t* hits = reinterpret_cast<int32_t*>(readout_page(c));
+    if (!hits) { hits_host.resize(kArgmaxBlocks); hits = hits_host.data(); }
+    HIP_TRY(c, hipMemcpyAsync(hits, hits_dev, kArgmaxBlocks * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    if (pred) {
+        const int rc = copy_out(c, pred, c->d_pred, (size_t)N * sizeof(int32_t));
+        if (rc != CADMM_OK) return rc;
+    } else {
+        HIP_TRY(c, hipStreamSynchronize(s));
     }
-    if (accuracy) *accuracy = labelled ? (double)hit / (double)labelled : 0.0;
+    if (accuracy) {
+        int64_t hit = 0;
+        for (int b = 0; b < kArgmaxBlocks; ++b) hit += hits[b];
+        *accuracy = c->n_labelled ? (double)hit / (double)c->n_labelled : 0.0;
+    }
     if (logits) {
         int rc = download_rows(c, c->T[L], c->C[L], logits);
         if (rc != CADMM_OK) return rc;
@@ -1125,10 +1210,15 @@ int cadmm_get_steps(cadmm_ctx* c, double* tau, double* theta, int32_t* n_trials,
     if (!c->has_init) return fail(c, CADMM_EORDER, "init first");
     const int L = c->L, M = c->hg.M;
     const int nz = (L - 1) * M;
-    std::vector<Unit> uw(L), uz(nz);
-    HIP_TRY(c, hipMemcpyAsync(uw.data(), c->unitsW, L * sizeof(Unit), hipMemcpyDeviceToHost, c->stream));
-    if (nz) HIP_TRY(c, hipMemcpyAsync(uz.data(), c->unitsZ, nz * sizeof(Unit), hipMemcpyDeviceToHost, c->stream));
+    // unitsW and, behind it, unitsZ in one copy
+    const size_t bytes = (size_t)(reinterpret_cast<char*>(c->unitsZ + nz) - reinterpret_cast<char*>(c->unitsW));
+    std::vector<char> pageable;
+    char* page = bytes <= kReadoutBytes ? readout_page(c) : nullptr;
+    if (!page) { pageable.resize(bytes); page = pageable.data(); }
+    HIP_TRY(c, hipMemcpyAsync(page, c->unitsW, bytes, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    const Unit* uw = reinterpret_cast<const Unit*>(page);
+    const Unit* uz = reinterpret_cast<const Unit*>(page + bytes - nz * sizeof(Unit));
     for (int l = 0; l < L; ++l) {
         if (tau) tau[l] = uw[l].step;
         if (n_trials) n_trials[l] = uw[l].ntrials;

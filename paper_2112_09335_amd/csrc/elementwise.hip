@@ -979,17 +979,26 @@ __global__ __launch_bounds__(256) void lowrank_operand_kernel(const float* __res
     Bcat[n + threadIdx.x] = (float)((acc[0] + acc[1]) + (acc[2] + acc[3]));
 }
 
-// class of every node: index of the largest entry of its row (the first one on equal values)
+// class of every node, see launch_argmax_rows
 __global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restrict__ T, int32_t* __restrict__ pred,
-                                                          int64_t N, int C) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const float* t = T + i * C;
-    int best = 0;
-    float bv = t[0];
-    for (int c = 1; c < C; ++c)
-        if (t[c] > bv) { bv = t[c]; best = c; }
-    pred[i] = best;
+                                                          const int32_t* __restrict__ perm, const int32_t* __restrict__ labels,
+                                                          int32_t* __restrict__ hits, int64_t N, int C) {
+    __shared__ int sm[4];
+    int hit = 0;
+    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < N; i += (int64_t)kArgmaxBlocks * 256) {
+        const float* t = T + i * C;
+        int best = 0;
+        float bv = t[0];
+        for (int c = 1; c < C; ++c)
+            if (t[c] > bv) { bv = t[c]; best = c; }
+        pred[perm[i]] = best;
+        hit += best == labels[i];                       // (no class is -1)
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) hit += __shfl_down(hit, o, 64);
+    if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = hit;
+    __syncthreads();
+    if (threadIdx.x == 0) hits[blockIdx.x] = sm[0] + sm[1] + sm[2] + sm[3];
 }
 
 // ------------------------------------------------------------------------------------------ last layer, FISTA with backtracking
@@ -1382,8 +1391,9 @@ void launch_relu(hipStream_t s, const float* T, float* Z, int64_t count, int app
     hipLaunchKernelGGL(relu_kernel, dim3(flat_grid(count)), dim3(256), 0, s, T, Z, count, apply_relu);
 }
 
-void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, int64_t N, int C) {
-    hipLaunchKernelGGL(argmax_rows_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, s, T, pred, N, C);
+void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, const int32_t* perm, const int32_t* labels, int32_t* hits,
+                        int64_t N, int C) {
+    hipLaunchKernelGGL(argmax_rows_kernel, dim3(kArgmaxBlocks), dim3(256), 0, s, T, pred, perm, labels, hits, N, C);
 }
 
 void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, int ncand, float mom) {

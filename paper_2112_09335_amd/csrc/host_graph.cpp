@@ -4,26 +4,10 @@
 
 #include <algorithm>
 #include <cmath>
-#include <thread>
 
 namespace cadmm {
 
 namespace {
-
-template <class F>
-void parallel_rows(int64_t n, F f) {
-    unsigned hw = std::thread::hardware_concurrency();
-    int nt = (int)std::min<int64_t>(std::max(1u, std::min(hw, 16u)), std::max<int64_t>(1, n / 4096));
-    if (nt <= 1) { f(0, n); return; }
-    std::vector<std::thread> th;
-    int64_t per = (n + nt - 1) / nt;
-    for (int t = 0; t < nt; ++t) {
-        int64_t lo = t * per, hi = std::min(n, lo + per);
-        if (lo >= hi) break;
-        th.emplace_back([=] { f(lo, hi); });
-    }
-    for (auto& x : th) x.join();
-}
 
 // Stored class of a row with len entries (see RowSchedule): -1 = split.
 int stored_class(int64_t len) {
@@ -33,101 +17,121 @@ int stored_class(int64_t len) {
     return kLengthClasses - 1 - k;
 }
 
-// Row r of the list has the entries [lo[r], hi[r]) of col / val, belongs to group grp[r] (n_groups groups) and goes
-// to output row out[r] (r if out is null).
-void make_schedule(RowSchedule& rs, int64_t nrows, const int64_t* lo, const int64_t* hi, const int32_t* out,
-                   const int32_t* grp, int32_t n_groups, const int32_t* col, const float* val) {
+// Row r of the list has the entries [lo(r), hi(r)) of col / val, belongs to group grp(r) (n_groups groups) and goes
+// to output row out(r).
+template <class Lo, class Hi, class Out, class Grp>
+void make_schedule(HostPool& pool, RowSchedule& rs, int64_t nrows, Lo lo, Hi hi, Out out, Grp grp, int32_t n_groups,
+                   const int32_t* col, const float* val) {
     rs = RowSchedule();
-    // counting sort on (group, class)
-    const size_t nkeys = (size_t)n_groups * kLengthClasses;
-    std::vector<int64_t> count(nkeys + 1, 0);
-    int64_t n_long = 0;
-    for (int64_t r = 0; r < nrows; ++r) {
-        const int j = stored_class(hi[r] - lo[r]);
-        if (j < 0) ++n_long; else ++count[(size_t)grp[r] * kLengthClasses + j + 1];
-    }
-    for (size_t k = 0; k < nkeys; ++k) count[k + 1] += count[k];
-    for (size_t k = 0; k < nkeys; ++k)
-        if (count[k + 1] > count[k])
-            rs.runs.push_back({count[k], count[k + 1], (int32_t)(k % kLengthClasses), (int32_t)(k / kLengthClasses)});
-    const int64_t n_sched = nrows - n_long;
+    // counting sort on (group, class); the rows to be split are picked out in order
+    const int64_t nkeys = (int64_t)n_groups * kLengthClasses;
+    HVec<int32_t> src((size_t)nrows);                          // list row of scheduled row i
+    HVec<int64_t> start;
+    stable_counting_sort(
+        pool, nrows, nkeys, start,
+        [&](int64_t r) {
+            const int j = stored_class(hi(r) - lo(r));
+            return j < 0 ? (int64_t)-1 : (int64_t)grp(r) * kLengthClasses + j;
+        },
+        [&](int64_t r, int64_t at) { src[(size_t)at] = (int32_t)r; });
+    const int64_t n_sched = start[(size_t)nkeys];
+    for (int64_t k = 0; k < nkeys; ++k)
+        if (start[(size_t)k + 1] > start[(size_t)k])
+            rs.runs.push_back({start[(size_t)k], start[(size_t)k + 1], (int32_t)(k % kLengthClasses), (int32_t)(k / kLengthClasses)});
     rs.n_sched = n_sched;
-    std::vector<int64_t> src((size_t)n_sched);                 // list row of scheduled row i
     std::vector<int64_t> long_src;
-    {
-        std::vector<int64_t> cur(count.begin(), count.end() - 1);
-        for (int64_t r = 0; r < nrows; ++r) {
-            const int j = stored_class(hi[r] - lo[r]);
-            if (j < 0) long_src.push_back(r); else src[(size_t)cur[(size_t)grp[r] * kLengthClasses + j]++] = r;
-        }
-    }
+    if (n_sched < nrows)
+        for (int64_t r = 0; r < nrows; ++r)
+            if (stored_class(hi(r) - lo(r)) < 0) long_src.push_back(r);
     // records and chunk ranges: chunk 0 is the padding chunk, then the scheduled rows, then the parts of split rows
     auto chunks_of = [](int64_t len) { return (len + kChunkEntries - 1) / kChunkEntries; };
-    int64_t n_parts = 0;
-    for (int64_t r : long_src) n_parts += (hi[r] - lo[r] + kSplitPart - 1) / kSplitPart;
-    rs.rec.resize((size_t)(n_sched + n_parts));
-    int64_t at = 1;
-    for (int64_t i = 0; i < n_sched; ++i) {
+    HVec<int64_t> chunk0;
+    prefix_sum(pool, n_sched, 1, chunk0, [&](int64_t i) {
         const int64_t r = src[(size_t)i];
-        const int64_t nc = chunks_of(hi[r] - lo[r]);
-        rs.rec[(size_t)i] = {(int32_t)at, (int32_t)(at + nc), out ? out[r] : (int32_t)r, 0};
-        at += nc;
-    }
+        return chunks_of(hi(r) - lo(r));
+    });
     std::vector<int64_t> part_lo, part_hi;                     // entry ranges of the parts in col / val
+    std::vector<RowRecord> part_rec;
+    int64_t at = chunk0[(size_t)n_sched];
     rs.long_part_ptr.push_back(0);
     for (int64_t r : long_src) {
-        for (int64_t p = lo[r]; p < hi[r]; p += kSplitPart) {
-            const int64_t p1 = p + kSplitPart < hi[r] ? p + kSplitPart : hi[r];
+        for (int64_t p = lo(r); p < hi(r); p += kSplitPart) {
+            const int64_t p1 = p + kSplitPart < hi(r) ? p + kSplitPart : hi(r);
             const int64_t nc = chunks_of(p1 - p);
-            const int64_t k = (int64_t)part_lo.size();
-            rs.rec[(size_t)(n_sched + k)] = {(int32_t)at, (int32_t)(at + nc), (int32_t)k, 0};
+            part_rec.push_back({(int32_t)at, (int32_t)(at + nc), (int32_t)part_lo.size(), 0});
             part_lo.push_back(p);
             part_hi.push_back(p1);
             at += nc;
         }
-        rs.long_row.push_back(out ? out[r] : (int32_t)r);
+        rs.long_row.push_back(out(r));
         rs.long_part_ptr.push_back((int32_t)part_lo.size());
     }
-    rs.ent.assign((size_t)at * kChunkEntries, EntryPair{0, 0.f});
+    const int64_t n_parts = (int64_t)part_lo.size();
+    rs.rec.resize((size_t)(n_sched + n_parts));
+    rs.ent.resize((size_t)at * kChunkEntries);
+    for (int k = 0; k < kChunkEntries; ++k) rs.ent[(size_t)k] = EntryPair{0, 0.f};
     auto fill = [&](const RowRecord& rec, int64_t p0, int64_t p1) {
         EntryPair* e = rs.ent.data() + (size_t)rec.chunk0 * kChunkEntries;
         const int64_t n = p1 - p0, padded = (int64_t)(rec.chunk1 - rec.chunk0) * kChunkEntries;
         for (int64_t k = 0; k < n; ++k) e[k] = {col[p0 + k], val[p0 + k]};
         for (int64_t k = n; k < padded; ++k) e[k] = {n > 0 ? col[p0] : 0, 0.f};
     };
-    parallel_rows(n_sched, [&](int64_t i0, int64_t i1) {
-        for (int64_t i = i0; i < i1; ++i) fill(rs.rec[(size_t)i], lo[src[(size_t)i]], hi[src[(size_t)i]]);
+    pool.run(n_sched, 1024, [&](int64_t i0, int64_t i1, int) {
+        for (int64_t i = i0; i < i1; ++i) {
+            const int64_t r = src[(size_t)i];
+            RowRecord& rec = rs.rec[(size_t)i];
+            rec = {(int32_t)chunk0[(size_t)i], (int32_t)chunk0[(size_t)i + 1], out(r), 0};
+            fill(rec, lo(r), hi(r));
+        }
     });
-    for (int64_t k = 0; k < n_parts; ++k) fill(rs.rec[(size_t)(n_sched + k)], part_lo[(size_t)k], part_hi[(size_t)k]);
+    pool.run(n_parts, 64, [&](int64_t k0, int64_t k1, int) {
+        for (int64_t k = k0; k < k1; ++k) {
+            rs.rec[(size_t)(n_sched + k)] = part_rec[(size_t)k];
+            fill(part_rec[(size_t)k], part_lo[(size_t)k], part_hi[(size_t)k]);
+        }
+    });
 }
 
 // What the aggregation kernels rely on: every record names an in-range, non-empty chunk range past the padding chunk,
 // the chunk ranges tile the entry array in order, the runs tile the scheduled rows and a row sits in a run whose
 // class bounds its length, a part is no longer than kSplitPart, output rows are in range, every column is in range.
-bool schedule_ok(const RowSchedule& rs, int64_t n_out, int64_t n_cols) {
+bool schedule_ok(HostPool& pool, const RowSchedule& rs, int64_t n_out, int64_t n_cols) {
     const int64_t n = rs.n_rows(), np = rs.n_parts(), nchunks = rs.n_chunks();
     if (n < 0 || np < 0 || nchunks < 1 || nchunks > INT32_MAX || rs.ent.size() % kChunkEntries != 0) return false;
-    int64_t at = 1;
-    for (int64_t i = 0; i < n + np; ++i) {
-        const RowRecord& r = rs.rec[(size_t)i];
-        if (r.chunk0 != at || r.chunk1 <= r.chunk0 || r.chunk1 > nchunks) return false;
-        if (r.out < 0 || r.out >= (i < n ? n_out : np)) return false;
-        if (i >= n && (int64_t)(r.chunk1 - r.chunk0) * kChunkEntries > kSplitPart) return false;
-        at = r.chunk1;
-    }
-    if (at != nchunks) return false;
-    for (const EntryPair& e : rs.ent)
-        if (e.col < 0 || e.col >= n_cols) return false;
+    std::atomic<bool> bad{false};
+    pool.run(n + np, 16384, [&](int64_t i0, int64_t i1, int) {
+        bool b = false;
+        for (int64_t i = i0; i < i1; ++i) {
+            const RowRecord& r = rs.rec[(size_t)i];
+            b |= r.chunk0 != (i ? rs.rec[(size_t)i - 1].chunk1 : 1) || r.chunk1 <= r.chunk0 || r.chunk1 > nchunks;
+            b |= r.out < 0 || r.out >= (i < n ? n_out : np);
+            b |= i >= n && (int64_t)(r.chunk1 - r.chunk0) * kChunkEntries > kSplitPart;
+        }
+        if (b) bad = true;
+    });
+    if ((n + np ? rs.rec[(size_t)(n + np) - 1].chunk1 : 1) != nchunks) return false;
+    pool.run((int64_t)rs.ent.size(), 65536, [&](int64_t i0, int64_t i1, int) {
+        bool b = false;
+        for (int64_t i = i0; i < i1; ++i) b |= rs.ent[(size_t)i].col < 0 || rs.ent[(size_t)i].col >= n_cols;
+        if (b) bad = true;
+    });
     int64_t row = 0;
     for (const ScheduleRun& run : rs.runs) {
         if (run.row0 != row || run.row1 <= run.row0 || run.cls < 0 || run.cls >= kLengthClasses) return false;
-        const int64_t cap = run.cls == 0 ? kSplitThreshold : (int64_t)(4 << (kLengthClasses - 1 - run.cls));
-        const int64_t cap_chunks = (cap + kChunkEntries - 1) / kChunkEntries;
-        for (int64_t i = run.row0; i < run.row1; ++i)
-            if (rs.rec[(size_t)i].chunk1 - rs.rec[(size_t)i].chunk0 > cap_chunks) return false;
         row = run.row1;
     }
     if (row != n) return false;
+    pool.run((int64_t)rs.runs.size(), 8, [&](int64_t k0, int64_t k1, int) {
+        bool b = false;
+        for (int64_t k = k0; k < k1; ++k) {
+            const ScheduleRun& run = rs.runs[(size_t)k];
+            const int64_t cap = run.cls == 0 ? kSplitThreshold : (int64_t)(4 << (kLengthClasses - 1 - run.cls));
+            const int64_t cap_chunks = (cap + kChunkEntries - 1) / kChunkEntries;
+            for (int64_t i = run.row0; i < run.row1; ++i) b |= rs.rec[(size_t)i].chunk1 - rs.rec[(size_t)i].chunk0 > cap_chunks;
+        }
+        if (b) bad = true;
+    });
+    if (bad) return false;
     if (rs.long_part_ptr.size() != rs.long_row.size() + 1) return false;
     for (size_t i = 0; i < rs.long_row.size(); ++i)
         if (rs.long_row[i] < 0 || rs.long_row[i] >= n_out || rs.long_part_ptr[i] >= rs.long_part_ptr[i + 1] ||
@@ -215,18 +219,26 @@ void build_block_table(const RowSchedule& rs, int lpr_log2, BlockTable& out) {
 bool block_table_ok(const RowSchedule& rs, int lpr_log2, const BlockTable& bt) {
     const int64_t n_rows = rs.n_rows(), n_parts = rs.n_parts();
     if (n_rows + n_parts > INT32_MAX) return false;
-    std::vector<BlockRows> sorted(bt.blocks);
-    std::sort(sorted.begin(), sorted.end(), [](const BlockRows& a, const BlockRows& b) { return a.row0 < b.row0; });
-    int64_t at = 0;
-    for (const BlockRows& b : sorted) {
-        if (b.row0 != at || b.row1 <= b.row0 || b.g < 0 || lpr_log2 + b.g > 6 || b.trips < 1) return false;
+    int64_t next = 0;                              // the workgroups of scheduled rows come in row order
+    std::vector<char> part_seen((size_t)n_parts, 0);
+    int64_t parts_listed = 0;
+    for (const BlockRows& b : bt.blocks) {
+        if (b.row1 <= b.row0 || b.row0 < 0 || b.row1 > n_rows + n_parts || b.g < 0 || lpr_log2 + b.g > 6 || b.trips < 1) return false;
         if ((int64_t)b.row1 - b.row0 > (4LL << (6 - lpr_log2 - b.g))) return false;
-        if (b.row0 < n_rows && b.row1 > n_rows) return false;
+        if (b.row0 < n_rows) {
+            if (b.row0 != next || b.row1 > n_rows) return false;
+            next = b.row1;
+        } else {
+            for (int64_t i = b.row0; i < b.row1; ++i) {
+                if (part_seen[(size_t)(i - n_rows)]) return false;
+                part_seen[(size_t)(i - n_rows)] = 1;
+                ++parts_listed;
+            }
+        }
         for (int64_t i = b.row0; i < b.row1; ++i)
             if ((int64_t)(rs.rec[(size_t)i].chunk1 - rs.rec[(size_t)i].chunk0) > ((int64_t)b.trips << b.g)) return false;
-        at = b.row1;
     }
-    if (at != n_rows + n_parts) return false;
+    if (next != n_rows || parts_listed != n_parts) return false;
     if (bt.xcd_start[0] != 0 || bt.xcd_start[8] != (int64_t)bt.blocks.size()) return false;
     for (int k = 0; k < 8; ++k)
         if (bt.xcd_start[k] > bt.xcd_start[k + 1]) return false;
@@ -262,186 +274,165 @@ std::string build_host_graph(HostGraph& g, int64_t N, int64_t n_edges, const int
     if (M < 1) return "M must be positive";
     if (n_edges < 0) return "n_edges must be non-negative";
     if (n_edges > 0 && (!src || !dst)) return "src/dst are null";
-    for (int64_t e = 0; e < n_edges; ++e)
-        if (src[e] < 0 || src[e] >= N || dst[e] < 0 || dst[e] >= N) return "edge endpoint out of range";
     g = HostGraph();
     g.N = N;
     g.M = M;
-
-    // community of every caller node
-    std::vector<int32_t> cm(N);
-    if (comm) {
-        for (int64_t i = 0; i < N; ++i) {
-            if (comm[i] < 0 || comm[i] >= M) return "community id out of range";
-            cm[i] = comm[i];
-        }
-    } else {
-        int64_t chunk = (N + M - 1) / M;
-        for (int64_t i = 0; i < N; ++i) cm[i] = (int32_t)(i / chunk);
-    }
+    HostPool pool(4 * n_edges + 8 * N);
+    std::atomic<bool> bad{false};
+    pool.run(n_edges, 65536, [&](int64_t lo, int64_t hi, int) {
+        bool b = false;
+        for (int64_t e = lo; e < hi; ++e) b |= src[e] < 0 || src[e] >= N || dst[e] < 0 || dst[e] >= N;
+        if (b) bad = true;
+    });
+    if (bad) return "edge endpoint out of range";
+    const int64_t chunk = (N + M - 1) / M;
+    if (comm)
+        pool.run(N, 65536, [&](int64_t lo, int64_t hi, int) {
+            bool b = false;
+            for (int64_t i = lo; i < hi; ++i) b |= comm[i] < 0 || comm[i] >= M;
+            if (b) bad = true;
+        });
+    if (bad) return "community id out of range";
 
     // stable counting sort by community: internal numbering
-    g.comm_row_ptr.assign(M + 1, 0);
-    for (int64_t i = 0; i < N; ++i) g.comm_row_ptr[cm[i] + 1]++;
-    for (int32_t m = 0; m < M; ++m) g.comm_row_ptr[m + 1] += g.comm_row_ptr[m];
-    g.perm.resize(N);
-    g.inv_perm.resize(N);
-    {
-        std::vector<int64_t> cur(g.comm_row_ptr.begin(), g.comm_row_ptr.end() - 1);
-        for (int64_t i = 0; i < N; ++i) {
-            int64_t r = cur[cm[i]]++;
-            g.perm[r] = (int32_t)i;
-            g.inv_perm[i] = (int32_t)r;
-        }
-    }
-    g.row_comm.resize(N);
-    for (int64_t r = 0; r < N; ++r) g.row_comm[r] = cm[g.perm[r]];
+    g.perm.resize((size_t)N);
+    g.inv_perm.resize((size_t)N);
+    g.row_comm.resize((size_t)N);
+    auto comm_of = [&](int64_t i) { return comm ? comm[i] : (int32_t)(i / chunk); };
+    stable_counting_sort(pool, N, M, g.comm_row_ptr, [&](int64_t i) { return (int64_t)comm_of(i); },
+                         [&](int64_t i, int64_t r) {
+                             g.perm[(size_t)r] = (int32_t)i;
+                             g.inv_perm[(size_t)i] = (int32_t)r;
+                             g.row_comm[(size_t)r] = comm_of(i);
+                         });
 
-    // bucket both orientations by row (with repeats), then sort + unique inside every row
-    std::vector<int64_t> cnt(N + 1, 0);
-    for (int64_t e = 0; e < n_edges; ++e) {
-        if (src[e] == dst[e]) continue;
-        cnt[g.inv_perm[src[e]] + 1]++;
-        cnt[g.inv_perm[dst[e]] + 1]++;
-    }
-    for (int64_t i = 0; i < N; ++i) cnt[i + 1] += cnt[i];
-    std::vector<int32_t> raw((size_t)cnt[N]);
-    {
-        std::vector<int64_t> cur(cnt.begin(), cnt.end() - 1);
-        for (int64_t e = 0; e < n_edges; ++e) {
-            if (src[e] == dst[e]) continue;
-            int32_t a = g.inv_perm[src[e]], b = g.inv_perm[dst[e]];
-            raw[(size_t)cur[a]++] = b;
-            raw[(size_t)cur[b]++] = a;
-        }
-    }
-    std::vector<int32_t> deg(N);   // distinct neighbours
-    parallel_rows(N, [&](int64_t lo, int64_t hi) {
-        for (int64_t i = lo; i < hi; ++i) {
-            int32_t* b = raw.data() + cnt[i];
-            int32_t* e = raw.data() + cnt[i + 1];
-            std::sort(b, e);
-            deg[i] = (int32_t)(std::unique(b, e) - b);
-        }
-    });
-    g.row_ptr.assign(N + 1, 0);
-    for (int64_t i = 0; i < N; ++i) g.row_ptr[i + 1] = g.row_ptr[i] + deg[i] + 1;   // + self loop
-    g.nnz = g.row_ptr[N];
+    // both orientations of every edge by row, sorted, repeats dropped
+    HVec<int64_t> raw_ptr;
+    HVec<int32_t> raw, deg;
+    distinct_neighbours(pool, N, n_edges, src, dst, [&](int32_t x) { return g.inv_perm[(size_t)x]; }, raw_ptr, raw, deg);
+    prefix_sum(pool, N, 0, g.row_ptr, [&](int64_t i) { return (int64_t)deg[(size_t)i] + 1; });      // + self loop
+    g.nnz = g.row_ptr[(size_t)N];
     g.E = (g.nnz - N) / 2;
     g.col.resize((size_t)g.nnz);
     g.val.resize((size_t)g.nnz);
-    parallel_rows(N, [&](int64_t lo, int64_t hi) {
+    HVec<int32_t> seg_cnt((size_t)N);
+    std::atomic<int64_t> n_halo{0};
+    pool.run(N, 1024, [&](int64_t lo, int64_t hi, int) {
+        int64_t n_h = 0;
         for (int64_t i = lo; i < hi; ++i) {
-            const int32_t* b = raw.data() + cnt[i];
-            int64_t o = g.row_ptr[i];
-            bool self_done = false;
-            for (int32_t k = 0; k < deg[i]; ++k) {
-                if (!self_done && b[k] > i) { g.col[(size_t)o++] = (int32_t)i; self_done = true; }
-                g.col[(size_t)o++] = b[k];
+            const int32_t* b = raw.data() + raw_ptr[(size_t)i];
+            const int32_t own = g.row_comm[(size_t)i], d = deg[(size_t)i];
+            int64_t o = g.row_ptr[(size_t)i];
+            const double di = (double)(d + 1);
+            int32_t prev = -1, segs = 0;
+            bool halo = false, self_done = false;
+            auto put = [&](int32_t j) {
+                const double dj = (double)(deg[(size_t)j] + 1);
+                g.col[(size_t)o] = j;
+                g.val[(size_t)o++] = (float)(1.0 / std::sqrt(di * dj));
+                const int32_t cc = g.row_comm[(size_t)j];
+                if (cc != prev) { ++segs; prev = cc; }
+                halo |= cc != own;
+            };
+            for (int32_t k = 0; k < d; ++k) {
+                if (!self_done && b[k] > i) { put((int32_t)i); self_done = true; }
+                put(b[k]);
             }
-            if (!self_done) g.col[(size_t)o++] = (int32_t)i;
-            double di = (double)(deg[i] + 1);
-            for (int64_t p = g.row_ptr[i]; p < g.row_ptr[i + 1]; ++p) {
-                double dj = (double)(deg[g.col[(size_t)p]] + 1);
-                g.val[(size_t)p] = (float)(1.0 / std::sqrt(di * dj));
-            }
+            if (!self_done) put((int32_t)i);
+            seg_cnt[(size_t)i] = segs;
+            n_h += halo;
         }
+        n_halo += n_h;
     });
-    std::vector<int32_t>().swap(raw);
+    g.n_halo_rows = n_halo;
+    HVec<int32_t>().swap(raw);
+    HVec<int64_t>().swap(raw_ptr);
 
     // segments in (row, community) order
     g.neighbour.assign((size_t)M * M, 0);
-    std::vector<int64_t> seg_cnt(N + 1, 0);
-    std::vector<uint8_t> halo(N, 0);
-    parallel_rows(N, [&](int64_t lo, int64_t hi) {
-        for (int64_t i = lo; i < hi; ++i) {
-            int32_t prev = -1;
-            int64_t c = 0;
-            for (int64_t p = g.row_ptr[i]; p < g.row_ptr[i + 1]; ++p) {
-                int32_t cc = g.row_comm[g.col[(size_t)p]];
-                if (cc != prev) { ++c; prev = cc; }
-                if (cc != g.row_comm[i]) halo[i] = 1;
-            }
-            seg_cnt[i + 1] = c;
-        }
-    });
-    for (int64_t i = 0; i < N; ++i) {
-        seg_cnt[i + 1] += seg_cnt[i];
-        g.n_halo_rows += halo[i];
-    }
-    g.n_seg = seg_cnt[N];
+    prefix_sum(pool, N, 0, g.row_seg_ptr, [&](int64_t i) { return (int64_t)seg_cnt[(size_t)i]; });
+    g.n_seg = g.row_seg_ptr[(size_t)N];
     if (g.n_seg > INT32_MAX) return "too many (row, community) segments";
     g.seg_ptr.resize((size_t)g.n_seg + 1);
     g.seg_row.resize((size_t)g.n_seg);
     g.seg_comm.resize((size_t)g.n_seg);
-    for (int64_t i = 0; i < N; ++i) {
-        int32_t prev = -1;
-        int64_t s = seg_cnt[i] - 1;
-        for (int64_t p = g.row_ptr[i]; p < g.row_ptr[i + 1]; ++p) {
-            int32_t cc = g.row_comm[g.col[(size_t)p]];
-            if (cc != prev) {
+    pool.run(N, 1024, [&](int64_t lo, int64_t hi, int) {
+        for (int64_t i = lo; i < hi; ++i) {
+            const int32_t own = g.row_comm[(size_t)i];
+            int32_t prev = -1;
+            int64_t s = g.row_seg_ptr[(size_t)i] - 1;
+            for (int64_t p = g.row_ptr[(size_t)i]; p < g.row_ptr[(size_t)i + 1]; ++p) {
+                const int32_t cc = g.row_comm[(size_t)g.col[(size_t)p]];
+                if (cc == prev) continue;
                 ++s;
                 g.seg_ptr[(size_t)s] = p;
                 g.seg_row[(size_t)s] = (int32_t)i;
                 g.seg_comm[(size_t)s] = cc;
                 prev = cc;
-                if (cc != g.row_comm[i]) g.neighbour[(size_t)g.row_comm[i] * M + cc] = 1;
+                if (cc != own) {
+                    uint8_t* nb = &g.neighbour[(size_t)own * M + cc];        // several threads may set it, all to 1
+                    if (!__atomic_load_n(nb, __ATOMIC_RELAXED)) __atomic_store_n(nb, (uint8_t)1, __ATOMIC_RELAXED);
+                }
             }
         }
-    }
+    });
     g.seg_ptr[(size_t)g.n_seg] = g.nnz;
 
     // segments in (community, row) order: stable counting sort on the community
-    g.segc_comm_ptr.assign(M + 1, 0);
-    for (int64_t s = 0; s < g.n_seg; ++s) g.segc_comm_ptr[g.seg_comm[(size_t)s] + 1]++;
-    for (int32_t m = 0; m < M; ++m) g.segc_comm_ptr[m + 1] += g.segc_comm_ptr[m];
     g.segc_order.resize((size_t)g.n_seg);
     g.segc_row.resize((size_t)g.n_seg);
-    {
-        std::vector<int64_t> cur(g.segc_comm_ptr.begin(), g.segc_comm_ptr.end() - 1);
-        for (int64_t s = 0; s < g.n_seg; ++s) {
-            int64_t j = cur[g.seg_comm[(size_t)s]]++;
-            g.segc_order[(size_t)j] = s;
-            g.segc_row[(size_t)j] = g.seg_row[(size_t)s];
-        }
-    }
-    g.row_seg_ptr.assign(seg_cnt.begin(), seg_cnt.end());
     g.seg_pos.resize((size_t)g.n_seg);
-    for (int64_t j = 0; j < g.n_seg; ++j) g.seg_pos[(size_t)g.segc_order[(size_t)j]] = (int32_t)j;
+    stable_counting_sort(pool, g.n_seg, M, g.segc_comm_ptr, [&](int64_t s) { return (int64_t)g.seg_comm[(size_t)s]; },
+                         [&](int64_t s, int64_t j) {
+                             g.segc_order[(size_t)j] = s;
+                             g.segc_row[(size_t)j] = g.seg_row[(size_t)s];
+                             g.seg_pos[(size_t)s] = (int32_t)j;
+                         });
 
-    make_schedule(g.row_sched, N, g.row_ptr.data(), g.row_ptr.data() + 1, nullptr, g.row_comm.data(), M, g.col.data(),
-                  g.val.data());
+    make_schedule(pool, g.row_sched, N, [&](int64_t r) { return g.row_ptr[(size_t)r]; }, [&](int64_t r) { return g.row_ptr[(size_t)r + 1]; },
+                  [](int64_t r) { return (int32_t)r; }, [&](int64_t r) { return g.row_comm[(size_t)r]; }, M, g.col.data(), g.val.data());
     {
-        std::vector<int64_t> mlo, mhi;
-        std::vector<int32_t> mpos, mgrp;
-        for (int64_t j = 0; j < g.n_seg; ++j) {
+        // by length: key 0 = one entry (scaled copies of a row), key 1 = several (aggregated like rows), both in the
+        // (community, row) order
+        HVec<int64_t> start;
+        auto len_of = [&](int64_t j) {
             const int64_t s = g.segc_order[(size_t)j];
-            const int64_t lo = g.seg_ptr[(size_t)s], hi = g.seg_ptr[(size_t)s + 1];
-            if (hi - lo == 1) {
-                g.seg1_pos.push_back((int32_t)j);
-                g.seg1_col.push_back(g.col[(size_t)lo]);
-                g.seg1_val.push_back(g.val[(size_t)lo]);
-            } else {
-                mlo.push_back(lo);
-                mhi.push_back(hi);
-                mpos.push_back((int32_t)j);
-                mgrp.push_back(g.seg_comm[(size_t)s]);
+            return g.seg_ptr[(size_t)s + 1] - g.seg_ptr[(size_t)s];
+        };
+        HVec<int32_t> by_len((size_t)g.n_seg);
+        stable_counting_sort(pool, g.n_seg, 2, start, [&](int64_t j) { return (int64_t)(len_of(j) > 1); },
+                             [&](int64_t j, int64_t at) { by_len[(size_t)at] = (int32_t)j; });
+        const int64_t n1 = start[1];
+        g.seg1_pos.resize((size_t)n1);
+        g.seg1_col.resize((size_t)n1);
+        g.seg1_val.resize((size_t)n1);
+        pool.run(n1, 16384, [&](int64_t lo, int64_t hi, int) {
+            for (int64_t k = lo; k < hi; ++k) {
+                const int32_t j = by_len[(size_t)k];
+                const int64_t p = g.seg_ptr[(size_t)g.segc_order[(size_t)j]];
+                g.seg1_pos[(size_t)k] = j;
+                g.seg1_col[(size_t)k] = g.col[(size_t)p];
+                g.seg1_val[(size_t)k] = g.val[(size_t)p];
             }
-        }
-        make_schedule(g.seg_sched, (int64_t)mpos.size(), mlo.data(), mhi.data(), mpos.data(), mgrp.data(), M, g.col.data(),
-                      g.val.data());
+        });
+        const int32_t* m = by_len.data() + n1;
+        auto seg_of = [&](int64_t r) { return (size_t)g.segc_order[(size_t)m[r]]; };
+        make_schedule(pool, g.seg_sched, g.n_seg - n1, [&](int64_t r) { return g.seg_ptr[seg_of(r)]; },
+                      [&](int64_t r) { return g.seg_ptr[seg_of(r) + 1]; }, [&](int64_t r) { return m[r]; },
+                      [&](int64_t r) { return g.seg_comm[seg_of(r)]; }, M, g.col.data(), g.val.data());
     }
 
-    if (!schedule_ok(g.row_sched, N, N) || !schedule_ok(g.seg_sched, g.n_seg, N)) return "internal error: row schedule";
-    for (int l = 0; l < 7; ++l) {
-        BlockTable bt;
-        for (const RowSchedule* rs : {&g.row_sched, &g.seg_sched}) {
-            build_block_table(*rs, l, bt);
-            if (!block_table_ok(*rs, l, bt) || (int64_t)bt.blocks.size() != count_blocks(*rs, l))
-                return "internal error: workgroup table of the aggregation";
+    if (!schedule_ok(pool, g.row_sched, N, N) || !schedule_ok(pool, g.seg_sched, g.n_seg, N)) return "internal error: row schedule";
+    pool.run(14, 1, [&](int64_t t0, int64_t t1, int) {
+        for (int64_t t = t0; t < t1; ++t) {
+            const RowSchedule& rs = t < 7 ? g.row_sched : g.seg_sched;
+            const int l = (int)(t % 7);
+            BlockTable& bt = t < 7 ? g.row_tables[l] : g.seg_tables[l];
+            build_block_table(rs, l, bt);
+            if (!block_table_ok(rs, l, bt)) bad = true;
         }
-    }
-
+    });
+    if (bad) return "internal error: workgroup table of the aggregation";
     return "";
 }
 

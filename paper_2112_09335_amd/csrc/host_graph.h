@@ -4,6 +4,8 @@
 #include <string>
 #include <vector>
 
+#include "host_pool.h"
+
 namespace cadmm {
 
 // Work unit of the per-community reductions of the Z step-size search: a run of rows of one
@@ -43,8 +45,8 @@ struct ScheduleRun {
 struct RowRecord { int32_t chunk0, chunk1, out, pad; };     // 16 bytes: one load per row
 struct EntryPair { int32_t col; float val; };
 struct RowSchedule {
-    std::vector<RowRecord> rec;                  // [n_rows + n_parts]
-    std::vector<EntryPair> ent;                  // [n_chunks * kChunkEntries]
+    HVec<RowRecord> rec;                  // [n_rows + n_parts]
+    HVec<EntryPair> ent;                  // [n_chunks * kChunkEntries]
     std::vector<ScheduleRun> runs;               // in order; they tile [0, n_rows)
     int64_t n_sched = 0;                         // scheduled (unsplit) rows
     std::vector<int32_t> long_row;               // [n_long] output row of a split row
@@ -75,32 +77,34 @@ bool block_table_ok(const RowSchedule& rs, int lpr_log2, const BlockTable& bt);
 struct HostGraph {
     int64_t N = 0, E = 0, nnz = 0, n_seg = 0, n_halo_rows = 0;
     int32_t M = 0;
-    std::vector<int32_t> perm;          // [N] internal row -> caller id
-    std::vector<int32_t> inv_perm;      // [N] caller id -> internal row
-    std::vector<int64_t> comm_row_ptr;  // [M+1]
-    std::vector<int32_t> row_comm;      // [N] community of an internal row
-    std::vector<int64_t> row_ptr;       // [N+1]
-    std::vector<int32_t> col;           // [nnz]
-    std::vector<float>   val;           // [nnz]
+    HVec<int32_t> perm;          // [N] internal row -> caller id
+    HVec<int32_t> inv_perm;      // [N] caller id -> internal row
+    HVec<int64_t> comm_row_ptr;  // [M+1]
+    HVec<int32_t> row_comm;      // [N] community of an internal row
+    HVec<int64_t> row_ptr;       // [N+1]
+    HVec<int32_t> col;           // [nnz]
+    HVec<float>   val;           // [nnz]
     // segments, (row, community) order
-    std::vector<int64_t> seg_ptr;       // [n_seg+1]
-    std::vector<int32_t> seg_row;       // [n_seg]
-    std::vector<int32_t> seg_comm;      // [n_seg]
+    HVec<int64_t> seg_ptr;       // [n_seg+1]
+    HVec<int32_t> seg_row;       // [n_seg]
+    HVec<int32_t> seg_comm;      // [n_seg]
     std::vector<uint8_t> neighbour;     // [M*M]
     // segments, (community, row) order
-    std::vector<int64_t> segc_order;    // [n_seg] index into the (row, community) order
-    std::vector<int32_t> segc_row;      // [n_seg]
-    std::vector<int64_t> segc_comm_ptr; // [M+1]
-    std::vector<int64_t> row_seg_ptr;   // [N+1] segments of a row in the (row, community) order
-    std::vector<int32_t> seg_pos;       // [n_seg] position of that segment in the (community, row) order
+    HVec<int64_t> segc_order;    // [n_seg] index into the (row, community) order
+    HVec<int32_t> segc_row;      // [n_seg]
+    HVec<int64_t> segc_comm_ptr; // [M+1]
+    HVec<int64_t> row_seg_ptr;   // [N+1] segments of a row in the (row, community) order
+    HVec<int32_t> seg_pos;       // [n_seg] position of that segment in the (community, row) order
     // the same segments by length: one with a single entry is a scaled copy of one gathered row (listed in the
     // (community, row) order); the others are aggregated like rows (seg_sched)
-    std::vector<int32_t> seg1_pos;      // [n_seg1] position of the segment in the (community, row) order
-    std::vector<int32_t> seg1_col;      // [n_seg1] its entry
-    std::vector<float>   seg1_val;      // [n_seg1]
+    HVec<int32_t> seg1_pos;      // [n_seg1] position of the segment in the (community, row) order
+    HVec<int32_t> seg1_col;      // [n_seg1] its entry
+    HVec<float>   seg1_val;      // [n_seg1]
     RowSchedule row_sched;              // the CSR rows; output row = the row, group = its community
     RowSchedule seg_sched;              // the segments with several entries; output row = position in the (community, row) order,
                                         // group = the segment's community
+    // workgroup tables of the two schedules per lane count, until they have been uploaded
+    BlockTable row_tables[7], seg_tables[7];
 };
 
 // Reduction chunks: for every community its rows, `rows` at a time, then its segments in the (community, row) order, `segs`

@@ -233,7 +233,11 @@ struct FistaArgs {
 };
 void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, int ncand, float mom);
 void launch_relu(hipStream_t s, const float* T, float* Z, int64_t count, int apply_relu);
-void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, int64_t N, int C);
+// pred[perm[r]] = class of internal row r (its largest entry, the first one on equal values); hits[b], b < kArgmaxBlocks:
+// labelled rows of workgroup b whose class is their label
+constexpr int kArgmaxBlocks = 512;
+void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, const int32_t* perm, const int32_t* labels, int32_t* hits,
+                        int64_t N, int C);
 void launch_fill_units(hipStream_t s, Unit* units, int n, double step);
 // gather / scatter rows between caller order and internal order: dst[r,:] = src[idx[r],:] or dst[idx[r],:] = src[r,:]
 void launch_permute_rows(hipStream_t s, const float* src, float* dst, const int32_t* idx, int64_t N, int C,
