@@ -306,6 +306,11 @@ std::string build_host_graph(HostGraph& g, int64_t N, int64_t n_edges, const int
                              g.row_comm[(size_t)r] = comm_of(i);
                          });
 
+    for (int32_t m = 0; m < M; ++m) {
+        const double n = (double)(g.comm_row_ptr[(size_t)m + 1] - g.comm_row_ptr[(size_t)m]);
+        g.group_rows += n * n / (double)N;
+    }
+
     // both orientations of every edge by row, sorted, repeats dropped
     HVec<int64_t> raw_ptr;
     HVec<int32_t> raw, deg;

@@ -80,6 +80,7 @@ struct HostGraph {
     HVec<int32_t> perm;          // [N] internal row -> caller id
     HVec<int32_t> inv_perm;      // [N] caller id -> internal row
     HVec<int64_t> comm_row_ptr;  // [M+1]
+    double group_rows = 0.0;            // average size of a row's own community
     HVec<int32_t> row_comm;      // [N] community of an internal row
     HVec<int64_t> row_ptr;       // [N+1]
     HVec<int32_t> col;           // [nnz]

@@ -31,6 +31,7 @@ struct SpmmSchedule {
     const int32_t* long_row = nullptr;
     const int32_t* long_part_ptr = nullptr;
     float* side = nullptr;
+    double group_rows = 0.0;       // rows of the community an average gather goes to
     const int4* blocks[7] = {};
     int64_t n_blocks[7] = {};
     int64_t xcd_start[7][9] = {};
@@ -43,8 +44,8 @@ double launch_gather_calibration(hipStream_t s, const SpmmSchedule& sc, int64_t 
                                  float* out);
 void launch_spmm_single(hipStream_t s, const int32_t* pos, const int32_t* col, const float* val, const float* X,
                         float* Y, int64_t n, int width);
-// columns of the feature matrix handled per launch (0 = all); smaller tiles keep a community's share of
-// the gathered matrix inside one XCD's L2 at the price of re-reading the entries once per tile
+// columns of the feature matrix handled at a time, if fewer than the launch's own choice (0 = that choice); smaller tiles
+// keep a community's share of the gathered matrix inside one XCD's L2 at the price of re-reading the entries once per tile
 void set_spmm_tile_cols(int cols);
 // 1: every XCD walks one contiguous slice of the workgroup table, whole communities one after the other (default);
 // 0: workgroups in plain table order, which deals consecutive row blocks round-robin to the XCDs

@@ -8,7 +8,7 @@
 // names the rows of every workgroup.  Features are row-major fp32.
 //
 // Mapping: a group of LPR lanes (a power of two, up to the 64-lane wavefront) reads one gathered
-// neighbour row with one fully coalesced VEC*4-byte load per lane and keeps VEC*R accumulators per lane.
+// neighbour row with one fully coalesced VEC*4-byte load per lane and keeps VEC accumulators per lane.
 // GPR such groups share one output row and take its chunks round-robin, one chunk = eight gathers in flight per
 // group and trip; their partial sums are added by a wavefront-level xor-shuffle reduction.  GPR is chosen per run
 // of one length class so that one trip covers the class's longest row: short rows pack many rows into a
@@ -30,21 +30,20 @@ namespace cadmm {
 
 namespace {
 
-template <int VEC> struct VecT;
-template <> struct VecT<4> { using type = float4; };
-template <> struct VecT<1> { using type = float; };
-
+// Rows of a width that is no multiple of four start at any dword; the chip takes 16-byte global accesses there.  VEC = 4
+// therefore serves every width of four and more: the last quad of a row is moved back to end with the row, and the columns
+// it shares with the quad before come out the same from both.  VEC = 1 is for widths of one to three.
+typedef float float_x4 __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC>
 __device__ __forceinline__ void load_vec(float (&dst)[VEC], const float* p) {
     if constexpr (VEC == 4) {
-        float4 v = *reinterpret_cast<const float4*>(p);
+        const float_x4 v = *reinterpret_cast<const float_x4*>(p);
         dst[0] = v.x; dst[1] = v.y; dst[2] = v.z; dst[3] = v.w;
     } else {
         dst[0] = *p;
     }
 }
 
-typedef float float_x4 __attribute__((ext_vector_type(4)));
 
 // results are written once and read by a later kernel: streamed past the L2's resident lines
 template <int VEC>
@@ -110,13 +109,14 @@ __device__ __forceinline__ void load_chunk(const int2* __restrict__ ent, int64_t
     }
 }
 
-// LPRL: lanes per gathered row as a power of two (3 stands for 8 and more, lpr_log2_arg then says how many); R column
-// repeats per lane (more than one only for more than 256 columns, a whole wavefront per gathered row).
-template <int VEC, int R, int EPI, int LPRL>
+// LPRL: lanes per gathered row as a power of two (3 stands for 8 and more, lpr_log2_arg then says how many).
+// blockIdx.y: tile of tile_cols columns.  The gathered matrix is walked one column tile after the other where a
+// community's rows of it do not fit an XCD's L2 at full width (see launch_vec).
+template <int VEC, int EPI, int LPRL>
 __global__ __launch_bounds__(256) void spmm_rows_kernel(
     const int4* __restrict__ rec, int64_t nrows, const int2* __restrict__ ent, const float* __restrict__ X,
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
-    XcdMap xm, int col0, int col1, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu) {
+    XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu) {
     // Workgroup b belongs to XCD b mod 8 and takes the (b / 8)-th entry of that XCD's slice of the table (or, without
     // the XCD-aware numbering, simply entry b).  Records from nrows on are the parts of split rows.
     const int lpr_log2 = LPRL < 3 ? LPRL : lpr_log2_arg;
@@ -143,77 +143,52 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(
     const int gpr = 1 << gpr_log2;
     const int grp = (lane >> lpr_log2) & (gpr - 1);
     const int sub = lane & (lpr - 1);
-    const int cbase = col0 + sub * VEC;                 // first column of repeat 0
-    const int cstride = lpr * VEC;                      // columns between repeats
-
-    float acc[R][VEC];
-#pragma unroll
-    for (int q = 0; q < R; ++q)
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[q][v] = 0.f;
+    const int col0 = (int)blockIdx.y * tile_cols;
+    const int col1 = width - col0 < tile_cols ? width : col0 + tile_cols;
+    const bool on = col0 + sub * VEC < col1;
     // a lane past the last column reads the last columns again without storing them
-    int ccl[R];
+    const int cc = on && col0 + sub * VEC + VEC <= width ? col0 + sub * VEC : (on ? width : col1) - VEC;
+
+    float acc[VEC];
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int cc = cbase + q * cstride;
-        ccl[q] = cc < col1 ? cc : col1 - VEC;
-    }
+    for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
     // the epilogue's operands (rows of Z_l and T_l at the output row) are asked for before the gathers, so that their
     // latency is not added at the end of every row
-    float ez[R][VEC], et[R][VEC];
+    float ez[VEC], et[VEC];
     if constexpr (EPI == 1) {
         if (!is_part && grp == 0) {
-#pragma unroll
-            for (int q = 0; q < R; ++q) {
-                const int64_t o = (int64_t)r.z * (int64_t)width + ccl[q];
-                load_vec<VEC>(ez[q], Zl + o);
-                load_vec<VEC>(et[q], Tl + o);
-            }
+            const int64_t o = (int64_t)r.z * (int64_t)width + cc;
+            load_vec<VEC>(ez, Zl + o);
+            load_vec<VEC>(et, Tl + o);
         }
     }
-    // the groups of a row take its chunks grp, grp + gpr, ...: eight gathers in flight per group (four per column
-    // repeat for the wide shapes); the padding of a chunk carries weight zero, so no entry is masked
-    constexpr int UH = (R == 1) ? 8 : 4;
+    // the groups of a row take its chunks grp, grp + gpr, ...: eight gathers in flight per group; the padding of a chunk
+    // carries weight zero, so no entry is masked
     for (int ch = r.x + grp; ch < r.y; ch += gpr) {
         int32_t c[8];
         float a[8];
         load_chunk<LPRL>(ent, ch, lpr_log2, lane, c, a);
+        float x[8][VEC];
 #pragma unroll
-        for (int h = 0; h < 8 / UH; ++h) {
-            float x[UH][R][VEC];
+        for (int u = 0; u < 8; ++u) load_vec<VEC>(x[u], X + (int64_t)c[u] * width + cc);
 #pragma unroll
-            for (int u = 0; u < UH; ++u)
+        for (int u = 0; u < 8; ++u)
 #pragma unroll
-                for (int q = 0; q < R; ++q) load_vec<VEC>(x[u][q], X + (int64_t)c[UH * h + u] * width + ccl[q]);
-#pragma unroll
-            for (int u = 0; u < UH; ++u)
-#pragma unroll
-                for (int q = 0; q < R; ++q)
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[q][v] = fmaf(a[UH * h + u], x[u][q][v], acc[q][v]);
-        }
+            for (int v = 0; v < VEC; ++v) acc[v] = fmaf(a[u], x[u][v], acc[v]);
     }
     // wavefront-level reduction across the groups of the row
     for (int off = lpr; off < (lpr << gpr_log2); off <<= 1) {
 #pragma unroll
-        for (int q = 0; q < R; ++q)
-#pragma unroll
-            for (int v = 0; v < VEC; ++v) acc[q][v] += __shfl_xor(acc[q][v], off, 64);
+        for (int v = 0; v < VEC; ++v) acc[v] += __shfl_xor(acc[v], off, 64);
     }
-    if (grp != 0) return;
+    if (grp != 0 || !on) return;
+    if constexpr (EPI == 1) {
+        if (!is_part) {
 #pragma unroll
-    for (int q = 0; q < R; ++q) {
-        const int cc = cbase + q * cstride;
-        if (cc < col1) {
-            if constexpr (EPI == 1) {
-                if (!is_part) {
-#pragma unroll
-                    for (int v = 0; v < VEC; ++v) acc[q][v] = nu * (ez[q][v] - fmaxf(et[q][v], 0.f)) + acc[q][v];
-                }
-            }
-            store_vec<VEC>(dst + cc, acc[q]);
+            for (int v = 0; v < VEC; ++v) acc[v] = nu * (ez[v] - fmaxf(et[v], 0.f)) + acc[v];
         }
     }
+    store_vec<VEC>(dst + cc, acc);
 }
 
 // Output rows with a single entry (most (row, neighbour community) segments of a sparse graph): row pos[k] of Y is
@@ -239,7 +214,8 @@ __global__ __launch_bounds__(256) void spmm_single_kernel(const int32_t* __restr
         c[j] = col[k];
         a[j] = val[k];
     }
-    for (int cc = sub * VEC; cc < width; cc += lpr * VEC) {
+    for (int c0 = sub * VEC; c0 < width; c0 += lpr * VEC) {
+        const int cc = c0 + VEC <= width ? c0 : width - VEC;
         float x[kSingleBatch][VEC];
 #pragma unroll
         for (int j = 0; j < kSingleBatch; ++j) load_vec<VEC>(x[j], X + (int64_t)c[j] * width + cc);
@@ -299,7 +275,7 @@ template <int VEC, int EPI>
 __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restrict__ side,
                                                           const int32_t* __restrict__ long_row,
                                                           const int32_t* __restrict__ long_part_ptr, int64_t n_long,
-                                                          float* __restrict__ Y, int width, int col0, int col1,
+                                                          float* __restrict__ Y, int width,
                                                           const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                           float nu, int lpr_log2) {
     const int64_t i = blockIdx.x;
@@ -308,9 +284,9 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
     const int p0 = long_part_ptr[i], p1 = long_part_ptr[i + 1];
     const int lpr = 1 << lpr_log2, groups = 64 >> lpr_log2;
     const int sub = threadIdx.x & (lpr - 1), grp = threadIdx.x >> lpr_log2;
-    for (int cb = col0; cb < col1; cb += lpr * VEC) {           // same trip count in every lane
-        const int c = cb + sub * VEC;
-        const bool ok = c < col1;
+    for (int cb = 0; cb < width; cb += lpr * VEC) {             // same trip count in every lane
+        const bool ok = cb + sub * VEC < width;
+        const int c = cb + sub * VEC + VEC <= width ? cb + sub * VEC : width - VEC;
         float acc[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -339,55 +315,53 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
     }
 }
 
-template <int VEC, int R>
-void launch_cfg(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y, int width, int lpr_log2, int col0,
-                int col1, const SpmmEpilogue& epi) {
-    XcdMap xm;
-    int64_t longest = 0;
-    for (int k = 0; k <= 8; ++k) xm.start[k] = sc.xcd_start[lpr_log2][k];
-    for (int k = 0; k < 8; ++k) longest = xm.start[k + 1] - xm.start[k] > longest ? xm.start[k + 1] - xm.start[k] : longest;
-    const int64_t nb = g_xcd_remap ? 8 * longest : (sc.n_blocks[lpr_log2] + 7) / 8 * 8;
-    if (nb <= 0) return;
-    dim3 grid((unsigned)nb), block(256);
-#define CADMM_ROWS(L_) do { \
-        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, R, 1, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
-                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, col0, col1, g_xcd_remap, epi.Zl, epi.Tl, epi.nu); \
-        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, R, 0, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
-                                lpr_log2, sc.blocks[lpr_log2], xm, col0, col1, g_xcd_remap, nullptr, nullptr, 0.f); } while (0)
-    if constexpr (R == 1) {
-        if (lpr_log2 == 0) CADMM_ROWS(0);
-        else if (lpr_log2 == 1) CADMM_ROWS(1);
-        else if (lpr_log2 == 2) CADMM_ROWS(2);
-        else CADMM_ROWS(3);
-    } else {
-        CADMM_ROWS(3);                                   // column repeats only occur with a whole wavefront per row
-    }
-#undef CADMM_ROWS
+// Columns per tile.  The rows of a community gather mostly rows of that community: 4 * columns * rows-of-a-community bytes
+// are what an XCD's 4 MB L2 would have to hold for those gathers to hit.  Columns are halved from 256 (a whole wavefront
+// of 16-byte loads per gathered row, which is also the most the kernel takes) until that fits, down to 32: the
+// requests of narrower rows cost the L2 as much as those of 128 bytes, and the entries are read once more per tile.
+// Measured per pass over the rows, tiled against untiled: 200000 nodes in 32 communities, width 512: 563 against 766 us
+// (128 columns); 500000 in 16, width 512: 1459 against 1980 us (32 columns); 13752 in 3, width 1000: 180 against 222 us (256).
+int tile_of(const SpmmSchedule& sc, int width, int vec) {
+    int tile = 64 * vec;
+    while (tile > 32 && 4.0 * tile * sc.group_rows > 4.5e6) tile >>= 1;
+    if (g_tile_cols > 0 && g_tile_cols < tile) tile = (g_tile_cols + vec - 1) / vec * vec;
+    return tile < width ? tile : width;
 }
 
 template <int VEC>
 void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y, int width, const SpmmEpilogue& epi) {
-    // column tiles of at most 64 lanes * VEC * 4 repeats; a smaller tile can be requested
-    int tile = 64 * VEC * 4;
-    if (g_tile_cols > 0 && g_tile_cols < tile) tile = (g_tile_cols + VEC - 1) / VEC * VEC;
-    for (int col0 = 0; col0 < width; col0 += tile) {
-        const int col1 = (width - col0 < tile) ? width : col0 + tile;
-        const int lanes_needed = (col1 - col0 + VEC - 1) / VEC;
-        int lpr_log2 = 0;
-        while ((1 << lpr_log2) < lanes_needed && lpr_log2 < 6) ++lpr_log2;
-        const int reps = (lanes_needed + (1 << lpr_log2) - 1) >> lpr_log2;
-        if (reps <= 1) launch_cfg<VEC, 1>(s, sc, X, Y, width, lpr_log2, col0, col1, epi);
-        else if (reps <= 2) launch_cfg<VEC, 2>(s, sc, X, Y, width, lpr_log2, col0, col1, epi);
-        else launch_cfg<VEC, 4>(s, sc, X, Y, width, lpr_log2, col0, col1, epi);
-        if (sc.n_long > 0) {
-            dim3 grid((unsigned)sc.n_long), block(64);
-            if (epi.kind == 1)
-                hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
-                                   sc.long_part_ptr, sc.n_long, Y, width, col0, col1, epi.Zl, epi.Tl, epi.nu, lpr_log2);
-            else
-                hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
-                                   sc.long_part_ptr, sc.n_long, Y, width, col0, col1, nullptr, nullptr, 0.f, lpr_log2);
-        }
+    const int tile = tile_of(sc, width, VEC);
+    const int lanes_needed = (tile + VEC - 1) / VEC;
+    int lpr_log2 = 0;
+    while ((1 << lpr_log2) < lanes_needed) ++lpr_log2;
+    XcdMap xm;
+    int64_t longest = 0;
+    for (int k = 0; k <= 8; ++k) xm.start[k] = sc.xcd_start[lpr_log2][k];
+    for (int k = 0; k < 8; ++k) longest = xm.start[k + 1] - xm.start[k] > longest ? xm.start[k + 1] - xm.start[k] : longest;
+    const int64_t nb = g_xcd_remap ? 8 * longest : (sc.n_blocks[lpr_log2] + 7) / 8 * 8;       // (a multiple of 8 either way)
+    if (nb > 0) {
+        const dim3 grid((unsigned)nb, (unsigned)((width + tile - 1) / tile)), block(256);
+#define CADMM_ROWS(L_) do { \
+        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
+                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu); \
+        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
+                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f); } while (0)
+        if (lpr_log2 == 0) CADMM_ROWS(0);
+        else if (lpr_log2 == 1) CADMM_ROWS(1);
+        else if (lpr_log2 == 2) CADMM_ROWS(2);
+        else CADMM_ROWS(3);
+#undef CADMM_ROWS
+    }
+    if (sc.n_long > 0) {
+        const dim3 grid((unsigned)sc.n_long), block(64);
+        int clog2 = 0;                                       // lanes that cover the columns of a combined row
+        while (clog2 < 6 && (VEC << clog2) < width) ++clog2;
+        if (epi.kind == 1)
+            hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
+                               sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2);
+        else
+            hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
+                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2);
     }
 }
 
@@ -411,14 +385,14 @@ double launch_gather_calibration(hipStream_t s, const SpmmSchedule& sc, int64_t 
 
 void launch_spmm(hipStream_t s, const SpmmSchedule& sched, const float* X, float* Y, int width, const SpmmEpilogue& epi) {
     if ((sched.n_rows <= 0 && sched.n_parts <= 0) || width <= 0) return;
-    if (width % 4 == 0) launch_vec<4>(s, sched, X, Y, width, epi);
+    if (width >= 4) launch_vec<4>(s, sched, X, Y, width, epi);
     else launch_vec<1>(s, sched, X, Y, width, epi);
 }
 
 void launch_spmm_single(hipStream_t s, const int32_t* pos, const int32_t* col, const float* val, const float* X,
                         float* Y, int64_t n, int width) {
     if (n <= 0 || width <= 0) return;
-    const int vec = (width % 4 == 0) ? 4 : 1;
+    const int vec = width >= 4 ? 4 : 1;
     const int lanes_needed = (width + vec - 1) / vec;
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < lanes_needed && lpr_log2 < 6) ++lpr_log2;
