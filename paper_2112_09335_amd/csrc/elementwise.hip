@@ -11,6 +11,8 @@
 // evaluates up to kMaxCand candidates step*eta^j in one sweep over memory, the finishing kernel picks the
 // first that passes the test  value(step) - value(0) <= -||grad||^2 / (2 step)  and marks the search
 // done; later passes see the flag and return at once.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace cadmm {
@@ -19,38 +21,81 @@ namespace {
 
 constexpr double kStepFloor = 1e-12;   // a step that moves the block by less than this fraction is not taken
 
-// Four consecutive floats per lane from an address that need only be aligned to four bytes (a row of a matrix whose
-// width is no multiple of four starts anywhere): the chip takes 16-byte global accesses at any dword.  valid: how many of
-// the four exist (1..4); the others read as zero, which adds nothing to any of the sums below.
+// Four consecutive floats per lane at any dword (the chip takes 16-byte global accesses there).
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ void ldq(float (&d)[4], const float* p, int valid) {
-    if (valid >= 4) {
-        const float4u v = *reinterpret_cast<const float4u*>(p);
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    } else {
-        d[0] = p[0];
-        d[1] = valid > 1 ? p[1] : 0.f;
-        d[2] = valid > 2 ? p[2] : 0.f;
-        d[3] = 0.f;
-    }
-}
-__device__ __forceinline__ void stq(float* p, const float (&d)[4], int valid) {
-    if (valid >= 4) {
-        float4u v = {d[0], d[1], d[2], d[3]};
-        *reinterpret_cast<float4u*>(p) = v;
-    } else {
-        p[0] = d[0];
-        if (valid > 1) p[1] = d[1];
-        if (valid > 2) p[2] = d[2];
-    }
-}
-__device__ __forceinline__ int quad_valid(int64_t count, int64_t i) { return count - i < 4 ? (int)(count - i) : 4; }
 __device__ __forceinline__ void ldv4(float (&d)[4], const float* p) {
-    const float4 v = *reinterpret_cast<const float4*>(p);
+    const float4u v = *reinterpret_cast<const float4u*>(p);
     d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
 }
 __device__ __forceinline__ void stv4(float* p, const float (&d)[4]) {
-    *reinterpret_cast<float4*>(p) = make_float4(d[0], d[1], d[2], d[3]);
+    float4u v = {d[0], d[1], d[2], d[3]};
+    *reinterpret_cast<float4u*>(p) = v;
+}
+
+// Flat kernels: a matrix as one array, f(i, WHOLE) for every four consecutive entries from i on; WHOLE = std::false_type for
+// the last one to three, which one lane handles apart (ldq reads zeros for what is missing, which adds nothing to any sum).
+template <class F>
+__device__ __forceinline__ void for_quads(int64_t count, F f) {
+    const int64_t whole = count & ~(int64_t)3;
+    const int64_t first = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
+    for (int64_t i = first; i < whole; i += stride) f(i, std::true_type{});
+    if (first == 0 && whole < count) f(whole, std::false_type{});
+}
+template <class WHOLE>
+__device__ __forceinline__ void ldq(float (&d)[4], const float* p, int64_t left, WHOLE) {
+    if constexpr (WHOLE::value) ldv4(d, p);
+    else {
+        d[0] = p[0];
+        d[1] = left > 1 ? p[1] : 0.f;
+        d[2] = left > 2 ? p[2] : 0.f;
+        d[3] = 0.f;
+    }
+}
+template <class WHOLE>
+__device__ __forceinline__ void stq(float* p, const float (&d)[4], int64_t left, WHOLE) {
+    if constexpr (WHOLE::value) stv4(p, d);
+    else {
+        p[0] = d[0];
+        if (left > 1) p[1] = d[1];
+        if (left > 2) p[2] = d[2];
+    }
+}
+
+// Row kernels: columns c .. c+3 (c < width) of a row of `width` floats, zeros past its end, by the width's kind:
+// kFull: a multiple of four; kTail: another width of four and more, the last quad is read so that it ends with the row and
+// moved into place; kNarrow: one to three.  No branches: a load under a condition that differs between lanes makes the
+// compiler wait for one load before it issues the next.
+enum RowMode { kFull = 0, kTail = 1, kNarrow = 2 };
+template <int MODE>
+__device__ __forceinline__ void ldr(float (&d)[4], const float* row, int c, int width) {
+    if constexpr (MODE == kFull) {
+        ldv4(d, row + c);
+    } else if constexpr (MODE == kTail) {
+        const int off = c + 4 <= width ? 0 : c + 4 - width;
+        float q[4];
+        ldv4(q, row + c - off);
+        const bool o2 = (off & 2) != 0, o1 = (off & 1) != 0;
+        const float a0 = o2 ? q[2] : q[0], a1 = o2 ? q[3] : q[1], a2 = o2 ? 0.f : q[2], a3 = o2 ? 0.f : q[3];
+        d[0] = o1 ? a1 : a0;
+        d[1] = o1 ? a2 : a1;
+        d[2] = o1 ? a3 : a2;
+        d[3] = o1 ? 0.f : a3;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = row[c + e < width ? c + e : width - 1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) d[e] = c + e < width ? d[e] : 0.f;
+    }
+}
+template <int MODE>
+__device__ __forceinline__ void str(float* row, int c, int width, const float (&d)[4]) {
+    if (MODE == kFull || c + 4 <= width) stv4(row + c, d);
+    else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (c + e < width) row[c + e] = d[e];
+    }
 }
 
 __device__ __forceinline__ double block_sum(double v, double* sm) {
@@ -150,20 +195,19 @@ __global__ __launch_bounds__(256) void phi_G_kernel(const float* __restrict__ T,
                                                     double* __restrict__ partials) {
     __shared__ double sm[3 * 4];
     double s[3] = {0.0, 0.0, 0.0};          // phi, ||Z - T||^2, ||T - Tprev||^2
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
-        const int nv = quad_valid(count, i);
+    for_quads(count, [&](int64_t i, auto w) {
+        const int64_t nv = count - i;
         float t[4], z[4], g[4];
-        ldq(t, T + i, nv);
-        ldq(z, Z + i, nv);
+        ldq(t, T + i, nv, w);
+        ldq(z, Z + i, nv, w);
         if (LAST) {
             float u[4], tp[4] = {0.f, 0.f, 0.f, 0.f};
-            ldq(u, U + i, nv);
-            if (have_prev) ldq(tp, Tprev + i, nv);
+            ldq(u, U + i, nv, w);
+            if (have_prev) ldq(tp, Tprev + i, nv, w);
             if (apply_dual) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) u[v] = u[v] + rho * (z[v] - t[v]);
-                stq(U + i, u, nv);
+                stq(U + i, u, nv, w);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -173,7 +217,7 @@ __global__ __launch_bounds__(256) void phi_G_kernel(const float* __restrict__ T,
                 g[v] = -(u[v] + rho * (z[v] - t[v]));
                 if (have_prev) { const double d = (double)t[v] - (double)tp[v]; s[2] += d * d; }
             }
-            stq(Tprev + i, t, nv);
+            stq(Tprev + i, t, nv, w);
         } else {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -182,8 +226,8 @@ __global__ __launch_bounds__(256) void phi_G_kernel(const float* __restrict__ T,
                 g[v] = (t[v] > 0.f) ? nu * (float)e : 0.f;
             }
         }
-        if (G) stq(G + i, g, nv);
-    }
+        if (G) stq(G + i, g, nv, w);
+    });
     block_sums_to<3>(s, sm, partials + (int64_t)blockIdx.x * 3);
 }
 
@@ -211,19 +255,18 @@ template <int LAST>
 __global__ __launch_bounds__(256) void G_only_kernel(const float* __restrict__ T, const float* __restrict__ Z,
                                                      float* __restrict__ U, float* __restrict__ G, int apply_dual,
                                                      int64_t count, float nu, float rho) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
-        const int nv = quad_valid(count, i);
+    for_quads(count, [&](int64_t i, auto w) {
+        const int64_t nv = count - i;
         float t[4], z[4], g[4];
-        ldq(t, T + i, nv);
-        ldq(z, Z + i, nv);
+        ldq(t, T + i, nv, w);
+        ldq(z, Z + i, nv, w);
         if (LAST) {
             float u[4];
-            ldq(u, U + i, nv);
+            ldq(u, U + i, nv, w);
             if (apply_dual) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) u[v] = u[v] + rho * (z[v] - t[v]);
-                stq(U + i, u, nv);
+                stq(U + i, u, nv, w);
             }
 #pragma unroll
             for (int v = 0; v < 4; ++v) g[v] = -(u[v] + rho * (z[v] - t[v]));
@@ -231,8 +274,8 @@ __global__ __launch_bounds__(256) void G_only_kernel(const float* __restrict__ T
 #pragma unroll
             for (int v = 0; v < 4; ++v) g[v] = (t[v] > 0.f) ? nu * (float)((double)t[v] - (double)z[v]) : 0.f;
         }
-        stq(G + i, g, nv);
-    }
+        stq(G + i, g, nv, w);
+    });
 }
 
 // ------------------------------------------------------------------------------------------ risk
@@ -297,21 +340,20 @@ __global__ __launch_bounds__(256) void w_last_sums_kernel(const float* __restric
     __shared__ double sm[2 * 4];
     if (unit->done) return;
     double s[2] = {0.0, 0.0};
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
-        const int nv = quad_valid(count, i);
+    for_quads(count, [&](int64_t i, auto w) {
+        const int64_t nv = count - i;
         float t[4], q[4], z[4], u[4];
-        ldq(t, T0 + i, nv);
-        ldq(q, Q + i, nv);
-        ldq(z, Z + i, nv);
-        ldq(u, U + i, nv);
+        ldq(t, T0 + i, nv, w);
+        ldq(q, Q + i, nv, w);
+        ldq(z, Z + i, nv, w);
+        ldq(u, U + i, nv, w);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const double qd = (double)q[v];
             s[0] += qd * ((double)u[v] + (double)rho * ((double)z[v] - (double)t[v]));
             s[1] += qd * qd;
         }
-    }
+    });
     block_sums_to<2>(s, sm, partials + (int64_t)blockIdx.x * 2);
 }
 
@@ -345,13 +387,12 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
         double inv[NC], D[NC];
 #pragma unroll
         for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; D[j] = 0.0; }
-        const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-        for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
-            const int nv = quad_valid(count, i);
+        for_quads(count, [&](int64_t i, auto w) {
+            const int64_t nv = count - i;
             float t0v[4], qv[4], zv[4];
-            ldq(t0v, T0 + i, nv);
-            ldq(qv, Q + i, nv);
-            ldq(zv, Z + i, nv);
+            ldq(t0v, T0 + i, nv, w);
+            ldq(qv, Q + i, nv, w);
+            ldq(zv, Z + i, nv, w);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const double q = (double)qv[v], z = (double)zv[v];
@@ -363,7 +404,7 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
                     D[j] += (e1 - e0) * (e1 + e0);
                 }
             }
-        }
+        });
         const double hnu = 0.5 * (double)sp.nu;
 #pragma unroll
         for (int j = 0; j < NC; ++j) D[j] *= hnu;
@@ -423,30 +464,30 @@ __global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, floa
     const double tinv = spec ? inv - 1.0 / unit->step0 : inv;
     const bool t_done = spec && unit->step == unit->step0;
     if (LAST || !t_done) {
-        for (int64_t i = gtid * 4; i < count_t; i += nthreads * 4) {
-            const int nv = quad_valid(count_t, i);
+        for_quads(count_t, [&](int64_t i, auto w) {
+            const int64_t nv = count_t - i;
             float t[4], q[4];
-            ldq(t, T + i, nv);
-            ldq(q, Q + i, nv);
+            ldq(t, T + i, nv, w);
+            ldq(q, Q + i, nv, w);
             if (LAST) {
                 float z[4], u[4], g[4];
-                ldq(z, Z + i, nv);
-                ldq(u, U + i, nv);
-                if (Tprev) stq(Tprev + i, t, nv);
+                ldq(z, Z + i, nv, w);
+                ldq(u, U + i, nv, w);
+                if (Tprev) stq(Tprev + i, t, nv, w);
                 if (!skip) {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
-                    stq(T + i, t, nv);
+                    stq(T + i, t, nv, w);
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) g[v] = -(u[v] + rho * (z[v] - t[v]));
-                stq(G + i, g, nv);
+                stq(G + i, g, nv, w);
             } else {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
-                stq(T + i, t, nv);
+                stq(T + i, t, nv, w);
             }
-        }
+        });
     }
     if (skip) return;
     const int64_t count_w = (int64_t)K * C;
@@ -501,8 +542,9 @@ struct RowWalk {
 //   segments, next layer hidden (HID): its ReLU makes the term piecewise quadratic; the first candidate is evaluated.
 // So with a last next layer this one pass over memory is the whole search, and with a hidden one the later passes read
 // the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidate's change, S2.  Bound by HBM traffic.
+// RM, SM: kinds of the widths Cl and Cn.
 constexpr int kFirstVals = 5;
-template <int HID, int LR>
+template <int HID, int LR, int RM, int SM>
 __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
     __shared__ double sm[kFirstVals * 4];
     extern __shared__ __align__(16) float s_wt[];       // [Cn][Cl] with the low-rank gradient, else nothing
@@ -528,11 +570,10 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
             }
             for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
                 float zv[4], gv[4], tv[4];
-                const int nv = a.Cl - 4 * cv;
-                ldq(zv, a.Zl + base + 4 * cv, nv);
-                ldq(tv, a.Tl + base + 4 * cv, nv);
+                ldr<RM>(zv, a.Zl + base, 4 * cv, a.Cl);
+                ldr<RM>(tv, a.Tl + base, 4 * cv, a.Cl);
                 if constexpr (LR == 1) lowrank_grad_lds(gv, zv, tv, srow, wcol, w.wv, a.Cn, a.sp.nu);
-                else ldq(gv, a.gradZ + base + 4 * cv, nv);
+                else ldr<RM>(gv, a.gradZ + base, 4 * cv, a.Cl);
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const double z = (double)zv[v], gz = (double)gv[v];
@@ -548,14 +589,13 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
         for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
             const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
             for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
-                const int nv = a.Cn - 4 * cv;
                 float pv[4], tv[4], zv[4];
-                ldq(pv, a.P + pbase + 4 * cv, nv);
+                ldr<SM>(pv, a.P + pbase, 4 * cv, a.Cn);
                 if constexpr (HID) {
-                    ldq(tv, a.Tn + base + 4 * cv, nv);
-                    ldq(zv, a.Zn + base + 4 * cv, nv);
+                    ldr<SM>(tv, a.Tn + base, 4 * cv, a.Cn);
+                    ldr<SM>(zv, a.Zn + base, 4 * cv, a.Cn);
                 } else {
-                    ldq(tv, a.Gn + base + 4 * cv, nv);
+                    ldr<SM>(tv, a.Gn + base, 4 * cv, a.Cn);
                 }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
@@ -610,7 +650,7 @@ __global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
 
 // Later passes over the segments (hidden next layer): `rounds` times NC further candidates for the communities still
 // searching.  Usually every community is done: a workgroup looks at all the flags at once and leaves if nothing is pending.
-template <int NC>
+template <int NC, int SM>
 __global__ __launch_bounds__(256) void z_more_kernel(ZTrialArgs a, int rounds) {
     __shared__ double sm[NC * 4];
     int pending = 0;
@@ -631,11 +671,10 @@ __global__ __launch_bounds__(256) void z_more_kernel(ZTrialArgs a, int rounds) {
             for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
                 const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
                 for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
-                    const int nv = a.Cn - 4 * cv;
                     float pv[4], tv[4], zv[4];
-                    ldq(pv, a.P + pbase + 4 * cv, nv);
-                    ldq(tv, a.Tn + base + 4 * cv, nv);
-                    ldq(zv, a.Zn + base + 4 * cv, nv);
+                    ldr<SM>(pv, a.P + pbase, 4 * cv, a.Cn);
+                    ldr<SM>(tv, a.Tn + base, 4 * cv, a.Cn);
+                    ldr<SM>(zv, a.Zn + base, 4 * cv, a.Cn);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const double t = (double)tv[v], z = (double)zv[v], p = (double)pv[v];
@@ -687,7 +726,7 @@ __device__ __forceinline__ void load_inv(double* s_inv, const Unit* __restrict__
 }
 
 // Z_{l,m} <- Z_{l,m} - grad / theta_{l,m}; the loads of a row are issued before its community is known.
-template <bool LDSU>
+template <bool LDSU, int RM>
 __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, const float* __restrict__ gradZ,
                                                      const int32_t* __restrict__ row_comm, int64_t N, int Cl,
                                                      const Unit* __restrict__ units, int M) {
@@ -699,15 +738,14 @@ __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, con
         const int cm = row_comm[r];
         const int64_t base = r * Cl;
         for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
-            const int nv = Cl - 4 * cv;
             float z[4], g[4];
-            ldq(z, Zl + base + 4 * cv, nv);
-            ldq(g, gradZ + base + 4 * cv, nv);
+            ldr<RM>(z, Zl + base, 4 * cv, Cl);
+            ldr<RM>(g, gradZ + base, 4 * cv, Cl);
             const double inv = LDSU ? s_inv[cm] : unit_inv(units + cm);
             if (inv == 0.0) break;                   // no step for this row's community
 #pragma unroll
             for (int v = 0; v < 4; ++v) z[v] = (float)((double)z[v] - (double)g[v] * inv);
-            stq(Zl + base + 4 * cv, z, nv);
+            str<RM>(Zl + base, 4 * cv, Cl, z);
         }
     }
 }
@@ -791,12 +829,11 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
 constexpr int kCarryBatch = 4;
 // acc += that sum for columns 4 cv .. of row r; returns whether any of the row's communities took a step.
 // kCarryBatch segments at a time: their index, unit and row loads do not depend on each other, so they are in flight
-// together; the sums are still taken in segment order.
-template <bool LDSU>
+// together; the sums are still taken in segment order.  s_inv: 1/theta of the communities in LDS, or null if there are too many.
+template <int SM>
 __device__ __forceinline__ bool carry_sum(double (&acc)[4], const CarryArgs& k, const double* s_inv, int64_t r, int Cn,
                                           int cv) {
     const int64_t s0 = k.row_seg_ptr[r], s1 = k.row_seg_ptr[r + 1];
-    const int nv = Cn - 4 * cv;
     bool any = false;
     for (int64_t sgm = s0; sgm < s1; sgm += kCarryBatch) {
         int cm[kCarryBatch], ps[kCarryBatch];
@@ -809,14 +846,17 @@ __device__ __forceinline__ bool carry_sum(double (&acc)[4], const CarryArgs& k, 
         double inv[kCarryBatch];
         float p[kCarryBatch][4];
 #pragma unroll
-        for (int j = 0; j < kCarryBatch; ++j) {
-            inv[j] = LDSU ? s_inv[cm[j]] : unit_inv(k.units + cm[j]);
-            if (sgm + j >= s1) inv[j] = 0.0;
-            ldq(p[j], k.P + (int64_t)ps[j] * Cn + 4 * cv, nv);
+        for (int j = 0; j < kCarryBatch; ++j) ldr<SM>(p[j], k.P + (int64_t)ps[j] * Cn, 4 * cv, Cn);
+        if (s_inv) {
+#pragma unroll
+            for (int j = 0; j < kCarryBatch; ++j) inv[j] = s_inv[cm[j]];
+        } else {
+#pragma unroll
+            for (int j = 0; j < kCarryBatch; ++j) inv[j] = unit_inv(k.units + cm[j]);
         }
 #pragma unroll
         for (int j = 0; j < kCarryBatch; ++j) {
-            if (inv[j] == 0.0) continue;          // past the row's end, or a step that was not taken
+            if (sgm + j >= s1 || inv[j] == 0.0) continue;          // past the row's end, or a step that was not taken
             any = true;
 #pragma unroll
             for (int v = 0; v < 4; ++v) acc[v] += (double)p[j][v] * inv[j];
@@ -824,23 +864,27 @@ __device__ __forceinline__ bool carry_sum(double (&acc)[4], const CarryArgs& k, 
     }
     return any;
 }
+__device__ __forceinline__ const double* carry_inv(double* s_inv, const CarryArgs& k) {
+    if (k.M > kStepUnits) return nullptr;
+    load_inv<true>(s_inv, k.units, k.M);
+    return s_inv;
+}
 
-template <bool LDSU>
+template <int SM>
 __global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, CarryArgs k, int64_t N, int Cn) {
-    __shared__ double s_inv[LDSU ? kStepUnits : 1];
-    load_inv<LDSU>(s_inv, k.units, k.M);
+    __shared__ double s_buf[kStepUnits];
+    const double* const s_inv = carry_inv(s_buf, k);
     const RowWalk w(Cn);
     const int64_t r_step = (int64_t)gridDim.x * w.r_step;
     for (int64_t r = (int64_t)blockIdx.x * w.r_step + w.r_first; r < N; r += r_step) {
         for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
             double acc[4] = {0.0, 0.0, 0.0, 0.0};
-            if (!carry_sum<LDSU>(acc, k, s_inv, r, Cn, cv)) continue;
-            const int nv = Cn - 4 * cv;
+            if (!carry_sum<SM>(acc, k, s_inv, r, Cn, cv)) continue;
             float t[4];
-            ldq(t, Tn + r * Cn + 4 * cv, nv);
+            ldr<SM>(t, Tn + r * Cn, 4 * cv, Cn);
 #pragma unroll
             for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - acc[v]);
-            stq(Tn + r * Cn + 4 * cv, t, nv);
+            str<SM>(Tn + r * Cn, 4 * cv, Cn, t);
         }
     }
 }
@@ -853,28 +897,29 @@ __global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, Ca
 // whose smooth part is the whole objective: x_j = y_j - grad(y_j)/Lip, Lip = rho + (1/2 | 1).
 // CARRY: T_L is then brought to the new Z_{L-1} (carry_sum) and, with G, the gradient G_L = -(U + rho (Z_L - T_L)) of the
 // next iteration is left, all while the row is in registers: one launch and no second pass over Z_L, U and T_L.
-template <int LPLOG, int CARRY, bool LDSU>
+template <int LPLOG, int CARRY, int SM>
 __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL, float* __restrict__ U, float* __restrict__ TL,
                                                          const int32_t* __restrict__ labels, int64_t N, int CL,
                                                          int risk, float rho, int J, int update_u, CarryArgs k,
                                                          float* __restrict__ G) {
-    __shared__ double s_inv[CARRY && LDSU ? kStepUnits : 1];
-    if constexpr (CARRY) load_inv<LDSU>(s_inv, k.units, k.M);
+    __shared__ double s_buf[CARRY ? kStepUnits : 1];
+    const double* s_inv = nullptr;
+    if constexpr (CARRY) s_inv = carry_inv(s_buf, k);
     constexpr int LP = 1 << LPLOG;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t row = t >> LPLOG;
     const int j0 = (int)(t & (LP - 1)) * 4;
     const bool act = row < N;                       // uniform over the lane group of a row
-    const int64_t base = (act ? row : 0) * CL + j0;
+    const int64_t base = (act ? row : 0) * CL;
     const int nv = act ? CL - j0 : 0;               // columns of this lane (none, or one to four)
     bool ok[4];
     float c[4] = {0.f, 0.f, 0.f, 0.f}, u[4] = {0.f, 0.f, 0.f, 0.f}, xp[4] = {0.f, 0.f, 0.f, 0.f}, y[4], x[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) ok[v] = v < nv;
     if (nv > 0) {
-        ldq(c, TL + base, nv);
-        ldq(u, U + base, nv);
-        ldq(xp, ZL + base, nv);
+        ldr<SM>(c, TL + base, j0, CL);
+        ldr<SM>(u, U + base, j0, CL);
+        ldr<SM>(xp, ZL + base, j0, CL);
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) { y[v] = xp[v]; x[v] = xp[v]; }
@@ -922,20 +967,20 @@ __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL,
         }
     }
     if (nv <= 0) return;
-    if (update_u) stq(U + base, un, nv);
-    stq(ZL + base, x, nv);
+    if (update_u) str<SM>(U + base, j0, CL, un);
+    str<SM>(ZL + base, j0, CL, x);
     if constexpr (CARRY) {
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (carry_sum<LDSU>(acc, k, s_inv, row, CL, j0 >> 2)) {
+        if (carry_sum<SM>(acc, k, s_inv, row, CL, j0 >> 2)) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) c[v] = (float)((double)c[v] - acc[v]);
-            stq(TL + base, c, nv);
+            str<SM>(TL + base, j0, CL, c);
         }
         if (G) {
             float g[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) g[v] = -(un[v] + rho * (x[v] - c[v]));
-            stq(G + base, g, nv);
+            str<SM>(G + base, j0, CL, g);
         }
     }
 }
@@ -943,17 +988,16 @@ __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL,
 // relu (or a plain copy) of a matrix
 __global__ __launch_bounds__(256) void relu_kernel(const float* __restrict__ T, float* __restrict__ Z, int64_t count,
                                                    int apply_relu) {
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x * 4;
-    for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4; i < count; i += stride) {
-        const int nv = quad_valid(count, i);
+    for_quads(count, [&](int64_t i, auto w) {
+        const int64_t nv = count - i;
         float t[4];
-        ldq(t, T + i, nv);
+        ldq(t, T + i, nv, w);
         if (apply_relu) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) t[v] = fmaxf(t[v], 0.f);
         }
-        stq(Z + i, t, nv);
-    }
+        stq(Z + i, t, nv, w);
+    });
 }
 
 // What the low-rank form of the Z gradient needs of W_{l+1} (Cl x Cn, Cn <= kLowRankMax): Bcat = [W; W^T W].
@@ -1221,17 +1265,22 @@ __global__ void fill_units_kernel(Unit* units, int n, double step) {
     units[i] = u;
 }
 
+// rows between the caller's and the internal order, 16 bytes per lane
+template <int RM>
 __global__ __launch_bounds__(256) void permute_rows_kernel(const float* __restrict__ src, float* __restrict__ dst,
                                                            const int32_t* __restrict__ idx, int64_t N, int C,
                                                            int scatter) {
-    const int64_t total = N * (int64_t)C;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-        const int64_t r = e / C;
-        const int c = (int)(e - r * C);
-        const int64_t o = (int64_t)idx[r] * C + c;
-        if (scatter) dst[o] = src[e];
-        else dst[e] = src[o];
+    const RowWalk w(C);
+    const int64_t r_step = (int64_t)gridDim.x * w.r_step;
+    for (int64_t r = (int64_t)blockIdx.x * w.r_step + w.r_first; r < N; r += r_step) {
+        const int64_t o = idx[r];
+        const float* const from = src + (scatter ? r : o) * C;
+        float* const to = dst + (scatter ? o : r) * C;
+        for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+            float v[4];
+            ldr<RM>(v, from, 4 * cv, C);
+            str<RM>(to, 4 * cv, C, v);
+        }
     }
 }
 
@@ -1313,19 +1362,34 @@ void launch_w_step_last(hipStream_t s, float* W, float* Wt, const float* gradW, 
                        Tprev, rho);
 }
 
+// calls f with the width's kind as an integral constant
+template <class F>
+static void with_mode(int width, F f) {
+    if (width % 4 == 0) f(std::integral_constant<int, kFull>{});
+    else if (width >= 4) f(std::integral_constant<int, kTail>{});
+    else f(std::integral_constant<int, kNarrow>{});
+}
+
 void launch_z_first(hipStream_t s, const ZTrialArgs& a) {
     const bool lr = a.gradZ == nullptr;               // low-rank gradient (the caller checked the shape limits)
     const size_t lds = lr ? (size_t)a.Cn * a.Cl * sizeof(float) : 0;          // W_{l+1}^T: at most 16 x 1024 floats
     const dim3 grid(a.n_chunks), block(256);
-    if (a.n_chunks > 0) {
-        if (a.next_is_last) {
-            if (lr) hipLaunchKernelGGL((z_first_kernel<0, 1>), grid, block, lds, s, a);
-            else hipLaunchKernelGGL((z_first_kernel<0, 0>), grid, block, 0, s, a);
-        } else {
-            if (lr) hipLaunchKernelGGL((z_first_kernel<1, 1>), grid, block, lds, s, a);
-            else hipLaunchKernelGGL((z_first_kernel<1, 0>), grid, block, 0, s, a);
-        }
-    }
+    if (a.n_chunks > 0)
+        with_mode(a.Cn, [&](auto sm) {
+            constexpr int SM = decltype(sm)::value;
+            if (lr) {
+                if constexpr (SM == kFull) {          // (both widths are multiples of four)
+                    if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, 1, kFull, kFull>), grid, block, lds, s, a);
+                    else hipLaunchKernelGGL((z_first_kernel<1, 1, kFull, kFull>), grid, block, lds, s, a);
+                }
+                return;
+            }
+            with_mode(a.Cl, [&](auto rm) {
+                constexpr int RM = decltype(rm)::value;
+                if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, 0, RM, SM>), grid, block, 0, s, a);
+                else hipLaunchKernelGGL((z_first_kernel<1, 0, RM, SM>), grid, block, 0, s, a);
+            });
+        });
     if (a.next_is_last) hipLaunchKernelGGL((z_first_finish_kernel<0>), dim3(a.M), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((z_first_finish_kernel<1>), dim3(a.M), dim3(256), 0, s, a);
 }
@@ -1335,18 +1399,23 @@ void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand) {
     const int cap = ncand <= 4 ? kReduceBlocks : kReduceBlocks / 4;
     const dim3 grid(a.n_chunks < cap ? a.n_chunks : cap), block(256);
     const int rounds = (ncand + kMaxCand - 1) / kMaxCand;
-    if (a.n_chunks > 0) {
-        if (ncand <= 4) hipLaunchKernelGGL((z_more_kernel<4>), grid, block, 0, s, a, 1);
-        else hipLaunchKernelGGL((z_more_kernel<kMaxCand>), grid, block, 0, s, a, rounds);
-    }
+    if (a.n_chunks > 0)
+        with_mode(a.Cn, [&](auto sm) {
+            constexpr int SM = decltype(sm)::value;
+            if (ncand <= 4) hipLaunchKernelGGL((z_more_kernel<4, SM>), grid, block, 0, s, a, 1);
+            else hipLaunchKernelGGL((z_more_kernel<kMaxCand, SM>), grid, block, 0, s, a, rounds);
+        });
     hipLaunchKernelGGL(z_more_finish_kernel, dim3(a.M), dim3(256), 0, s, a, ncand <= 4 ? 4 : rounds * kMaxCand);
 }
 
 void launch_z_step(hipStream_t s, float* Zl, const float* gradZ, const int32_t* row_comm, int64_t N, int Cl,
                    const Unit* units, int M) {
     const int nb = flat_grid(N * (int64_t)Cl);
-    if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
-    else hipLaunchKernelGGL((z_step_kernel<false>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
+    with_mode(Cl, [&](auto rm) {
+        constexpr int RM = decltype(rm)::value;
+        if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
+        else hipLaunchKernelGGL((z_step_kernel<false, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
+    });
 }
 
 void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const float* SG, const float* Wt, float nu,
@@ -1363,24 +1432,32 @@ void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const floa
 
 void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int Cn) {
     const int nb = flat_grid(N * (int64_t)Cn * 4);
-    if (k.M <= kStepUnits) hipLaunchKernelGGL((t_carry_kernel<true>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
-    else hipLaunchKernelGGL((t_carry_kernel<false>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
+    with_mode(Cn, [&](auto sm) {
+        hipLaunchKernelGGL((t_carry_kernel<decltype(sm)::value>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
+    });
 }
 
 void launch_last_layer(hipStream_t s, float* ZL, float* U, float* TL, const int32_t* labels, int64_t N,
                        int CL, int risk, float rho, int J, int update_u, const CarryArgs* carry, float* G) {
     const CarryArgs k = carry ? *carry : CarryArgs();
-#define CADMM_LAST(LG_) do { \
-        const dim3 grid((unsigned)(((N << LG_) + 255) / 256)); \
-        if (!carry) hipLaunchKernelGGL((last_layer_kernel<LG_, 0, true>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, nullptr); \
-        else if (k.M <= kStepUnits) hipLaunchKernelGGL((last_layer_kernel<LG_, 1, true>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G); \
-        else hipLaunchKernelGGL((last_layer_kernel<LG_, 1, false>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G); } while (0)
-    if (CL <= 4) CADMM_LAST(0);
-    else if (CL <= 8) CADMM_LAST(1);
-    else if (CL <= 16) CADMM_LAST(2);
-    else if (CL <= 32) CADMM_LAST(3);
-    else CADMM_LAST(4);
-#undef CADMM_LAST
+    with_mode(CL, [&](auto sm) {
+        constexpr int SM = decltype(sm)::value;
+        auto go = [&](auto lg) {
+            constexpr int LG = decltype(lg)::value;
+            const dim3 grid((unsigned)(((N << LG) + 255) / 256));
+            if (carry) hipLaunchKernelGGL((last_layer_kernel<LG, 1, SM>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G);
+            else hipLaunchKernelGGL((last_layer_kernel<LG, 0, SM>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, nullptr);
+        };
+        if constexpr (SM == kNarrow) {
+            go(std::integral_constant<int, 0>{});
+        } else {
+            if (CL <= 4) go(std::integral_constant<int, 0>{});
+            else if (CL <= 8) go(std::integral_constant<int, 1>{});
+            else if (CL <= 16) go(std::integral_constant<int, 2>{});
+            else if (CL <= 32) go(std::integral_constant<int, 3>{});
+            else go(std::integral_constant<int, 4>{});
+        }
+    });
 }
 
 void launch_lowrank_operand(hipStream_t s, const float* W, float* Bcat, int Cl, int Cn) {
@@ -1424,7 +1501,10 @@ void launch_fill_units(hipStream_t s, Unit* units, int n, double step) {
 
 void launch_permute_rows(hipStream_t s, const float* src, float* dst, const int32_t* idx, int64_t N, int C,
                          int scatter) {
-    hipLaunchKernelGGL(permute_rows_kernel, dim3(flat_grid(N * (int64_t)C)), dim3(256), 0, s, src, dst, idx, N, C, scatter);
+    with_mode(C, [&](auto rm) {
+        hipLaunchKernelGGL((permute_rows_kernel<decltype(rm)::value>), dim3(flat_grid(N * (int64_t)((C + 3) & ~3))), dim3(256), 0, s, src,
+                           dst, idx, N, C, scatter);
+    });
 }
 
 }  // namespace cadmm

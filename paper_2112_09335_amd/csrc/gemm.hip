@@ -14,6 +14,9 @@
 // C[8*(r/4) + 4*(lane/32) + r%4][lane%32].
 // gemm_tn splits n into chunks, each block reduces one chunk for one 128 x BN output tile into a
 // partial matrix; a second kernel adds the partials in chunk order in fp64 (deterministic).
+#include <algorithm>
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace cadmm {
@@ -25,9 +28,60 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 constexpr int BM = 128;
 constexpr int BK = 16;
 
-// Up to four consecutive floats at any four-byte alignment (the chip takes 16-byte global accesses at any dword; a
-// matrix whose width is no multiple of four has rows that start anywhere); entries past `valid` read as zero.
+// Four consecutive columns c .. c+3 of a row of `width` floats; entries past the row's end read as zero.  Every variant is
+// free of branches: a load under a condition that differs between lanes makes the compiler wait for one load before it
+// issues the next.  The chip takes 16-byte global accesses at any dword, so rows of any width are read in quads:
+//   width a multiple of four (kFull): the quad is there or not at all;
+//   other widths of four and more (kTail): the last quad is moved back to end with the row, and its entries into place;
+//   one to three columns (kNarrow): dwords.
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+enum RowMode { kFull = 0, kTail = 1, kNarrow = 2 };
+__device__ __forceinline__ int row_mode(int width) { return width % 4 == 0 ? kFull : width >= 4 ? kTail : kNarrow; }
+// Loading and putting the quad right are two steps, so that a kernel that fetches ahead does the second where it uses the
+// quad: anything done to a loaded value right away makes the fetch wait for it.
+template <int MODE>
+__device__ __forceinline__ float4 ld_quad_raw(const float* row, int c, int width) {
+    if constexpr (MODE == kNarrow) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = row[c + e < width ? c + e : width - 1];
+        return make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+        const int cc = MODE == kFull ? (c < width ? c : 0) : (c + 4 <= width ? c : width - 4);
+        const float4u q = *reinterpret_cast<const float4u*>(row + cc);
+        return make_float4(q.x, q.y, q.z, q.w);
+    }
+}
+template <int MODE>
+__device__ __forceinline__ float4 fix_quad(float4 q, int c, int width) {
+    if constexpr (MODE == kFull) {
+        const bool in = c < width;
+        return make_float4(in ? q.x : 0.f, in ? q.y : 0.f, in ? q.z : 0.f, in ? q.w : 0.f);
+    } else if constexpr (MODE == kTail) {
+        const int off = c + 4 <= width ? 0 : c + 4 - width;     // how many entries of the quad come before column c
+        const bool o2 = (off & 2) != 0, o1 = (off & 1) != 0, none = off >= 4;
+        const float a0 = o2 ? q.z : q.x, a1 = o2 ? q.w : q.y, a2 = o2 ? 0.f : q.z, a3 = o2 ? 0.f : q.w;
+        const float b0 = o1 ? a1 : a0, b1 = o1 ? a2 : a1, b2 = o1 ? a3 : a2, b3 = o1 ? 0.f : a3;
+        return make_float4(none ? 0.f : b0, none ? 0.f : b1, none ? 0.f : b2, none ? 0.f : b3);
+    } else {
+        return make_float4(c < width ? q.x : 0.f, c + 1 < width ? q.y : 0.f, c + 2 < width ? q.z : 0.f, c + 3 < width ? q.w : 0.f);
+    }
+}
+template <int MODE>
+__device__ __forceinline__ float4 ld_quad(const float* row, int c, int width) {
+    return fix_quad<MODE>(ld_quad_raw<MODE>(row, c, width), c, width);
+}
+__device__ __forceinline__ float4 ld_quad_raw(int mode, const float* row, int c, int width) {        // mode: uniform
+    if (mode == kFull) return ld_quad_raw<kFull>(row, c, width);
+    if (mode == kTail) return ld_quad_raw<kTail>(row, c, width);
+    return ld_quad_raw<kNarrow>(row, c, width);
+}
+__device__ __forceinline__ float4 fix_quad(int mode, float4 q, int c, int width) {
+    if (mode == kFull) return fix_quad<kFull>(q, c, width);
+    if (mode == kTail) return fix_quad<kTail>(q, c, width);
+    return fix_quad<kNarrow>(q, c, width);
+}
+// up to four entries of a flat array of which `valid` (one to four) exist
 __device__ __forceinline__ void ld4u(float (&d)[4], const float* p, int valid) {
     if (valid >= 4) {
         const float4u v = *reinterpret_cast<const float4u*>(p);
@@ -49,14 +103,6 @@ __device__ __forceinline__ void st4u(float* p, const float (&d)[4], int valid) {
         if (valid > 2) p[2] = d[2];
     }
 }
-__device__ __forceinline__ float4 ld4_guard(const float* base, int64_t off, bool ok, int valid) {
-    // valid: number of in-range elements starting at off (none if <= 0)
-    if (!ok || valid <= 0) return make_float4(0.f, 0.f, 0.f, 0.f);
-    float v[4];
-    ld4u(v, base + off, valid);
-    return make_float4(v[0], v[1], v[2], v[3]);
-}
-
 // Consecutive workgroups go round-robin to the eight XCDs, each with an L2 of its own.  Workgroups that read the
 // same operand tile (the `inner` column tiles of one row tile, the tiles of one row chunk) are therefore given
 // indices 8 apart, so that they run at about the same time on ONE XCD and the shared tile comes from its L2.
@@ -73,29 +119,26 @@ __device__ __forceinline__ void xcd_group(unsigned b, unsigned nb, unsigned inne
     }
 }
 
-// Epilogue of a 128 x 128 result tile held as 2 x 2 accumulators per wavefront (2 x 2 wavefronts).
+// Epilogue of a result tile of 64 T x 64 T held as T x T accumulators per wavefront (2 x 2 wavefronts).
 // The accumulators hold 32 consecutive columns per row and lane group; passing each 32-row slab of the tile
-// through LDS (Cs: 32 x 132 floats, the operand buffer reused) turns every global access of the epilogue into
-// float4 pieces of a 512-byte row.
+// through LDS (Cs: 32 x (64 T + 4) floats, the operand buffer reused) turns every global access of the epilogue into
+// 16-byte pieces of a row of 256 T bytes.
 // EPI 0: out = acc.  EPI 1: out = nu (Zl - relu(Tl)) + acc.  EPI 2: first candidate of the W search and the step
 // on Tio ahead of the decision, see GemmEpilogue.
-template <int EPI>
-__device__ __forceinline__ void tile128_epilogue(floatx16 (&acc)[2][2], float* Cs, int64_t m0, int c0, int64_t n, int C,
-                                                 float* __restrict__ out, const float* __restrict__ Zl,
-                                                 const float* __restrict__ Tl, float nu, float* __restrict__ Tio,
-                                                 const Unit* unit, double* __restrict__ partials) {
-    constexpr int LDC = 128 + 4;
+template <int EPI, int T, int MODE>
+__device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
+                                                   float* __restrict__ out, const float* __restrict__ Zl,
+                                                   const float* tin, float nu, float* __restrict__ Tio, double inv0,
+                                                   bool take, double& dsum) {
+    constexpr int BN = 64 * T;
+    constexpr int LDC = BN + 4;
+    constexpr int Q = BN / 4;                            // quads per row
+    constexpr int PER_T = 32 * Q / 256;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lk = lane >> 5;
-    double inv0 = 0.0, dsum = 0.0;
-    bool take = false;
-    if constexpr (EPI == 2) {
-        inv0 = unit->skip ? 0.0 : 1.0 / unit->step0;
-        take = unit->spec != 0 && !unit->skip;
-    }
     // one result element: returns what goes to out, updates t (EPI 2) and the candidate's sum
     auto finish = [&](float v, float z, float& t) -> float {
         if constexpr (EPI == 1) v = nu * (z - fmaxf(t, 0.f)) + v;
@@ -108,85 +151,105 @@ __device__ __forceinline__ void tile128_epilogue(floatx16 (&acc)[2][2], float* C
         }
         return v;
     };
-    const float* tin = (EPI == 2) ? Tio : Tl;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 2 * T; ++q) {
         __syncthreads();
-        if (wm == q / 2) {
+        if (wm == q / T) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j)
+            for (int j = 0; j < T; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    Cs[(8 * (r >> 2) + 4 * lk + (r & 3)) * LDC + wn * 64 + j * 32 + li] = acc[q % 2][j][r];
+                    Cs[(8 * (r >> 2) + 4 * lk + (r & 3)) * LDC + wn * 32 * T + j * 32 + li] = acc[q % T][j][r];
         }
         __syncthreads();
+        // two 16-byte pieces of a lane at a time, their loads before either is used (more would cost the product registers)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int f = tid + 256 * u;
-            const int rl = f >> 5, cq = f & 31;
-            const int64_t row = m0 + 32 * q + rl;
-            const int c = c0 + 4 * cq;
-            if (row >= n || c >= C) continue;
-            const float4 v4 = *reinterpret_cast<const float4*>(Cs + rl * LDC + 4 * cq);
-            float v[4] = {v4.x, v4.y, v4.z, v4.w}, z[4] = {0.f, 0.f, 0.f, 0.f}, t[4] = {0.f, 0.f, 0.f, 0.f};
-            const int64_t o = row * C + c;
-            const int nv = C - c;                       // columns of this lane (four, or the row's last few)
+        for (int u0 = 0; u0 < PER_T; u0 += 2) {
+            float4 z4[2], t4[2];
             if constexpr (EPI != 0) {
-                ld4u(z, Zl + o, nv);
-                ld4u(t, tin + o, nv);
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int f = tid + 256 * (u0 + u);
+                    const int64_t row = m0 + 32 * q + f / Q;
+                    const int64_t ro = (row < n ? row : n - 1) * (int64_t)C;
+                    z4[u] = ld_quad<MODE>(Zl + ro, c0 + 4 * (f % Q), C);
+                    t4[u] = ld_quad<MODE>(tin + ro, c0 + 4 * (f % Q), C);
+                }
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = finish(v[e], z[e], t[e]);     // (zeros past the row's end add nothing)
-            if constexpr (EPI == 2) {
-                if (take) st4u(Tio + o, t, nv);
-                else st4u(out + o, v, nv);
-            } else {
-                st4u(out + o, v, nv);
+            for (int u = 0; u < 2; ++u) {
+                const int f = tid + 256 * (u0 + u);
+                const int rl = f / Q, cq = f % Q;
+                const int64_t row = m0 + 32 * q + rl;
+                const int c = c0 + 4 * cq;
+                if (row >= n || c >= C) continue;
+                const float4 v4 = *reinterpret_cast<const float4*>(Cs + rl * LDC + 4 * cq);
+                float v[4] = {v4.x, v4.y, v4.z, v4.w}, t[4] = {0.f, 0.f, 0.f, 0.f};
+                const int64_t o = row * C + c;
+                const int nv = MODE == kFull ? 4 : C - c;       // columns of this lane (four, or the row's last few)
+                if constexpr (EPI != 0) {
+                    const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
+                    t[0] = t4[u].x; t[1] = t4[u].y; t[2] = t4[u].z; t[3] = t4[u].w;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = finish(v[e], z[e], t[e]);     // (zeros past the row's end add nothing)
+                }
+                if constexpr (EPI == 2) {
+                    if (take) st4u(Tio + o, t, nv);
+                    else st4u(out + o, v, nv);
+                } else {
+                    st4u(out + o, v, nv);
+                }
             }
         }
     }
+}
+
+template <int EPI, int T>
+__device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
+                                              float* __restrict__ out, const float* __restrict__ Zl,
+                                              const float* __restrict__ Tl, float nu, float* __restrict__ Tio,
+                                              const Unit* unit, double* __restrict__ partials) {
+    double inv0 = 0.0, dsum = 0.0;
+    bool take = false;
+    if constexpr (EPI == 2) {
+        inv0 = unit->skip ? 0.0 : 1.0 / unit->step0;
+        take = unit->spec != 0 && !unit->skip;
+    }
+    const float* tin = (EPI == 2) ? Tio : Tl;
+    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum);
+    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum);   // (C > 32)
     if constexpr (EPI == 2) {
         __shared__ double red[4];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
-        if (lane == 0) red[wave] = dsum;
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = dsum;
         __syncthreads();
-        if (tid == 0) partials[blockIdx.x] = 0.5 * (double)nu * (red[0] + red[1] + red[2] + red[3]);
+        if (threadIdx.x == 0) partials[blockIdx.x] = 0.5 * (double)nu * (red[0] + red[1] + red[2] + red[3]);
     }
 }
 
 // ------------------------------------------------------------------------------------------------ NN
 // EPI 1: out = nu * (Zl - relu(Tl)) + A B   (gradient of the Z subproblem, Appendix A)
 // EPI 2: out = Q = A B; first candidate of the W search and speculative step on Tio (Section 3.1), see kernels.h
-template <int BN, int EPI>
+template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                       float* __restrict__ out, int64_t n, int K, int C,
                                                       const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                       float nu, float* __restrict__ Tio, const Unit* unit,
                                                       double* __restrict__ partials) {
-    constexpr int WN = (BN == 128) ? 2 : 1;       // waves along columns
-    constexpr int WM = 4 / WN;                    // waves along rows
-    constexpr int TM = BM / (WM * 32);            // 32x32 tiles per wave along rows
-    constexpr int TN = BN / (WN * 32);
-    // columns of A per step: the narrow variant is bound by reading A, and takes a whole 128-byte line of a
-    // row per step so that no half line has to survive in the L2 until the next step
-    constexpr int BKK = (BN == 32) ? 32 : BK;
-    constexpr int LDA = BKK + 1;
+    constexpr int BN = 128;
+    constexpr int LDA = BK + 1;
     constexpr int LDB = BN + 4;
-    constexpr int A_Q = BKK / 4;                  // float4 per row of the A tile
-    constexpr int A_PER_T = BM * A_Q / 256;
-    constexpr int B_F4 = BKK * BN / 4;            // float4 loads for the B tile
-    constexpr int B_PER_T = (B_F4 + 255) / 256;
 
     // one buffer: the operand tiles during the product, a 32-row slab of the result tile afterwards
-    __shared__ __align__(16) float smem[BM * LDA + BKK * LDB];
+    __shared__ __align__(16) float smem[BM * LDA + BK * LDB];
     float* const As = smem;
     float* const Bs = smem + BM * LDA;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
-    const int wm = wave / WN, wn = wave % WN;
+    const int wm = wave >> 1, wn = wave & 1;
     const int ctiles = (C + BN - 1) / BN;
     if constexpr (EPI == 0) {
         // gated plain product: Q again for a W search whose speculative step (epilogue 2, Q not stored) was rejected
@@ -198,96 +261,184 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
     const int64_t m0 = mtile * BM;
     const int c0 = ctile * BN;
 
-    floatx16 acc[TM][TN];
+    floatx16 acc[2][2];
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < TN; ++j)
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    float4 ra[A_PER_T], rb[B_PER_T];
+    float4 ra[2], rb[2];
     auto fetch = [&](int k0) {
 #pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) {
+        for (int i = 0; i < 2; ++i) {
             const int f = tid + 256 * i;
-            const int row = f / A_Q, kq = f % A_Q;
-            const int64_t gr = m0 + row;
-            const int k = k0 + 4 * kq;
-            ra[i] = ld4_guard(A, gr * K + k, gr < n, K - k);
-        }
-#pragma unroll
-        for (int i = 0; i < B_PER_T; ++i) {
-            const int f = tid + 256 * i;
-            if (f < B_F4) {
-                const int kr = f / (BN / 4), cq = f % (BN / 4);
-                const int k = k0 + kr, c = c0 + 4 * cq;
-                rb[i] = ld4_guard(B, (int64_t)k * C + c, k < K, C - c);
-            }
+            const int64_t gr = m0 + (f >> 2) < n ? m0 + (f >> 2) : n - 1;
+            const int k = k0 + (f >> 5) < K ? k0 + (f >> 5) : K - 1;
+            const float* ar = A + gr * K;
+            const float* br = B + (int64_t)k * C;
+            if (K % 4 == 0) ra[i] = ld_quad<kFull>(ar, k0 + 4 * (f & 3), K);
+            else if (K >= 4) ra[i] = ld_quad<kTail>(ar, k0 + 4 * (f & 3), K);
+            else ra[i] = ld_quad<kNarrow>(ar, k0 + 4 * (f & 3), K);
+            rb[i] = C % 4 == 0 ? ld_quad<kFull>(br, c0 + 4 * (f & 31), C) : ld_quad<kTail>(br, c0 + 4 * (f & 31), C);
         }
     };
     auto stash = [&]() {
 #pragma unroll
-        for (int i = 0; i < A_PER_T; ++i) {
+        for (int i = 0; i < 2; ++i) {
             const int f = tid + 256 * i;
-            const int row = f / A_Q, kq = f % A_Q;
-            float* d = As + row * LDA + 4 * kq;
+            float* d = As + (f >> 2) * LDA + 4 * (f & 3);
             d[0] = ra[i].x; d[1] = ra[i].y; d[2] = ra[i].z; d[3] = ra[i].w;
-        }
-#pragma unroll
-        for (int i = 0; i < B_PER_T; ++i) {
-            const int f = tid + 256 * i;
-            if (f < B_F4) {
-                const int kr = f / (BN / 4), cq = f % (BN / 4);
-                *reinterpret_cast<float4*>(Bs + kr * LDB + 4 * cq) = rb[i];
-            }
+            *reinterpret_cast<float4*>(Bs + (f >> 5) * LDB + 4 * (f & 31)) = rb[i];
         }
     };
 
-    const int nk = (K + BKK - 1) / BKK;
+    const int nk = (K + BK - 1) / BK;
     fetch(0);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();            // previous tile fully consumed
         stash();
         __syncthreads();
-        if (kt + 1 < nk) fetch((kt + 1) * BKK);
+        if (kt + 1 < nk) fetch((kt + 1) * BK);
         const int li = lane & 31, lk = lane >> 5;
 #pragma unroll
-        for (int kk = 0; kk < BKK; kk += 2) {
-            float a[TM], b[TN];
+        for (int kk = 0; kk < BK; kk += 2) {
+            float a[2], b[2];
 #pragma unroll
-            for (int i = 0; i < TM; ++i) a[i] = As[(wm * TM * 32 + i * 32 + li) * LDA + kk + lk];
+            for (int i = 0; i < 2; ++i) a[i] = As[(wm * 64 + i * 32 + li) * LDA + kk + lk];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) b[j] = Bs[(kk + lk) * LDB + wn * TN * 32 + j * 32 + li];
+            for (int j = 0; j < 2; ++j) b[j] = Bs[(kk + lk) * LDB + wn * 64 + j * 32 + li];
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
+                for (int j = 0; j < 2; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
         }
     }
-    if constexpr (BN == 128) {
-        static_assert(32 * (BN + 4) <= BM * LDA + BKK * LDB, "result slab must fit the operand buffer");
-        tile128_epilogue<EPI>(acc, smem, m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
+    static_assert(32 * (BN + 4) <= BM * LDA + BK * LDB, "result slab must fit the operand buffer");
+    tile_epilogue<EPI, 2>(acc, smem, m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
+}
+
+// Results of at most 32 columns: bound by reading A, so a step takes 32 columns of it (a whole 128-byte line of every
+// row; no half line has to survive in the L2 until the next step).  A wavefront forms 32 rows.
+//   SPLIT 0: four wavefronts share a workgroup's 128 rows and its tile of B.
+//   SPLIT 1: they share 32 rows and take a quarter of the K steps each, added up in LDS at the end.  For few rows: a
+//   workgroup per 128 rows leaves most of the chip idle and its K steps are one chain of memory latencies
+//   (13752 x 1000 by 10 columns: 77 us in 108 workgroups, 17 us in 430).
+template <int EPI, int SPLIT>
+__global__ __launch_bounds__(256) void gemm_nn_narrow_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                             float* __restrict__ out, int64_t n, int K, int C,
+                                                             const float* __restrict__ Zl, const float* __restrict__ Tl,
+                                                             float nu) {
+    constexpr int KS = 32;
+    constexpr int LDA = KS + 1;
+    constexpr int LDB = 32 + 4;
+    constexpr int A_TILE = 32 * LDA, B_TILE = KS * LDB;
+    constexpr int B_PER_T = SPLIT ? 4 : 1;
+    __shared__ __align__(16) float As[4 * A_TILE];                       // 32 rows per wavefront
+    __shared__ __align__(16) float Bs[(SPLIT ? 4 : 1) * B_TILE];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t m0 = (int64_t)blockIdx.x * (SPLIT ? 32 : 128) + (SPLIT ? 0 : 32 * wave);   // this wavefront's rows
+    const int li = lane & 31, lk = lane >> 5;
+    float* const Aw = As + wave * A_TILE;
+    float* const Bw = Bs + (SPLIT ? wave * B_TILE : 0);
+    floatx16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    // A: lane takes quad lane % 8 of rows lane / 8 + 8 i; B: rows of the K step, columns past C are never stored
+    int64_t arow[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t r = m0 + (lane >> 3) + 8 * i;
+        arow[i] = (r < n ? r : n - 1) * K;
+    }
+    float4 ra[4], rb[B_PER_T];
+    auto fetch_mode = [&](int k0, auto am, auto bm) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) ra[i] = ld_quad_raw<decltype(am)::value>(A + arow[i], k0 + 4 * (lane & 7), K);
+#pragma unroll
+        for (int i = 0; i < B_PER_T; ++i) {
+            const int f = SPLIT ? lane + 64 * i : tid;
+            const int k = k0 + (f >> 3);
+            rb[i] = ld_quad_raw<decltype(bm)::value>(B + (int64_t)(k < K ? k : K - 1) * C, 4 * (f & 7), C);
+        }
+    };
+    auto fetch = [&](int k0) {
+        using full = std::integral_constant<int, kFull>;
+        using tail = std::integral_constant<int, kTail>;
+        using narrow = std::integral_constant<int, kNarrow>;
+        if (K % 4 == 0) {
+            if (C % 4 == 0) fetch_mode(k0, full{}, full{});
+            else if (C >= 4) fetch_mode(k0, full{}, tail{});
+            else fetch_mode(k0, full{}, narrow{});
+        } else if (K >= 4) {
+            if (C >= 4) fetch_mode(k0, tail{}, tail{});
+            else fetch_mode(k0, tail{}, narrow{});
+        } else {
+            if (C >= 4) fetch_mode(k0, narrow{}, tail{});
+            else fetch_mode(k0, narrow{}, narrow{});
+        }
+    };
+    const int amode = row_mode(K), bmode = row_mode(C);
+    auto stash = [&](int k0) {
+        if (amode != kFull || k0 + KS > K)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ra[i] = fix_quad(amode, ra[i], k0 + 4 * (lane & 7), K);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float* d = Aw + ((lane >> 3) + 8 * i) * LDA + 4 * (lane & 7);
+            d[0] = ra[i].x; d[1] = ra[i].y; d[2] = ra[i].z; d[3] = ra[i].w;
+        }
+#pragma unroll
+        for (int i = 0; i < B_PER_T; ++i) {
+            const int f = SPLIT ? lane + 64 * i : tid;
+            *reinterpret_cast<float4*>(Bw + (f >> 3) * LDB + 4 * (f & 7)) = fix_quad(bmode, rb[i], 4 * (f & 7), C);
+        }
+    };
+    // SPLIT: wavefront w takes the K steps w, w + 4, ...; a step past the end is all zeros in A
+    const int nk = (K + KS - 1) / KS;
+    const int stride = SPLIT ? 4 : 1, trips = SPLIT ? (nk + 3) / 4 : nk;
+    int ks = SPLIT ? wave : 0;
+    fetch(ks * KS);
+    for (int kt = 0; kt < trips; ++kt) {
+        __syncthreads();
+        stash(ks * KS);
+        __syncthreads();
+        ks += stride;
+        if (kt + 1 < trips) fetch(ks * KS);
+#pragma unroll
+        for (int kk = 0; kk < KS; kk += 2) {
+            const float a = Aw[li * LDA + kk + lk];
+            const float b = Bw[(kk + lk) * LDB + li];
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+        }
+    }
+    auto store = [&](int row_in_tile, float v) {
+        const int64_t row = m0 + row_in_tile;
+        if (row < n && li < C) {
+            if constexpr (EPI == 1) v = nu * (Zl[row * C + li] - fmaxf(Tl[row * C + li], 0.f)) + v;
+            out[row * C + li] = v;
+        }
+    };
+    if constexpr (SPLIT == 0) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) store(8 * (r >> 2) + 4 * lk + (r & 3), acc[r]);
     } else {
-        static_assert(BN == 128 || EPI != 2, "the search epilogue exists for the wide tile only");
-        const int li = lane & 31, lk = lane >> 5;
+        static_assert(4 * 16 * 64 <= 4 * A_TILE, "the four partial tiles must fit the operand buffer");
+        __syncthreads();
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+        for (int r = 0; r < 16; ++r) As[(wave * 16 + r) * 64 + lane] = acc[r];
+        __syncthreads();
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int c = c0 + wn * TN * 32 + j * 32 + li;
-                if (c >= C) continue;
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t row = m0 + wm * TM * 32 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-                    if (row < n) {
-                        float v = acc[i][j][r];
-                        if constexpr (EPI == 1) v = nu * (Zl[row * C + c] - fmaxf(Tl[row * C + c], 0.f)) + v;
-                        out[row * C + c] = v;
-                    }
-                }
-            }
+        for (int q = 0; q < 4; ++q) {                        // wavefront w finishes accumulator registers 4 w .. 4 w + 3
+            const int r = 4 * wave + q;
+            float v = As[r * 64 + lane];
+            for (int w = 1; w < 4; ++w) v += As[(w * 16 + r) * 64 + lane];
+            store(8 * (r >> 2) + 4 * lk + (r & 3), v);
+        }
     }
 }
 
@@ -313,124 +464,157 @@ __device__ __forceinline__ void split3_pair(float x0, float x1, unsigned& h, uns
     l = __builtin_amdgcn_perm(__float_as_uint(s1), __float_as_uint(s0), 0x07060302u);
 }
 
-// (four wavefronts per SIMD asked for: the few registers that spill cost less than the fourth wavefront gains)
-template <int EPI>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) void gemm_nn_split_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                            float* __restrict__ out, int64_t n, int K, int C,
-                                                            const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                            float nu, float* __restrict__ Tio, const Unit* unit,
-                                                            double* __restrict__ partials) {
-    constexpr int BN = 128;
+// The six products of one K step, smallest terms first, for T x T accumulators per wavefront; As / Bs: three planes of
+// 64 T rows (columns of B) by 16 k.
+template <int T, int LDH>
+__device__ __forceinline__ void multiply_split(floatx16 (&acc)[T][T], const unsigned short* As, const unsigned short* Bs,
+                                               int a_row, int b_row, int lk) {
+    constexpr int PLANE = 64 * T * LDH;
+    bf16x8 a[3][T];
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int i = 0; i < T; ++i)
+            a[p][i] = *reinterpret_cast<const bf16x8*>(As + p * PLANE + (a_row + i * 32) * LDH + 8 * lk);
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+        bf16x8 b[3];                             // one column tile's parts at a time keeps the register count down
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            b[p] = *reinterpret_cast<const bf16x8*>(Bs + p * PLANE + (b_row + j * 32) * LDH + 8 * lk);
+#pragma unroll
+        for (int i = 0; i < T; ++i) {
+            floatx16 c = acc[i][j];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2][i], b[0], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[2], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[1], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[0], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[1], c, 0, 0, 0);
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[0], c, 0, 0, 0);
+            acc[i][j] = c;
+        }
+    }
+}
+// NE consecutive k of one tile row, split and stored into the three planes at element o (NE = 4 or 8)
+template <int NE>
+__device__ __forceinline__ void stash_split(unsigned short* S, int plane, int o, const float (&x)[NE]) {
+    unsigned h[NE / 2], m[NE / 2], l[NE / 2];
+#pragma unroll
+    for (int e = 0; e < NE / 2; ++e) split3_pair(x[2 * e], x[2 * e + 1], h[e], m[e], l[e]);
+    if constexpr (NE == 8) {
+        *reinterpret_cast<uint4*>(S + o) = make_uint4(h[0], h[1], h[2], h[3]);
+        *reinterpret_cast<uint4*>(S + plane + o) = make_uint4(m[0], m[1], m[2], m[3]);
+        *reinterpret_cast<uint4*>(S + 2 * plane + o) = make_uint4(l[0], l[1], l[2], l[3]);
+    } else {
+        *reinterpret_cast<uint2*>(S + o) = make_uint2(h[0], h[1]);
+        *reinterpret_cast<uint2*>(S + plane + o) = make_uint2(m[0], m[1]);
+        *reinterpret_cast<uint2*>(S + 2 * plane + o) = make_uint2(l[0], l[1]);
+    }
+}
+
+// T: 32 x 32 accumulators per wavefront and direction; the workgroup's tile is 64 T x 64 T.  PF: K steps fetched ahead.
+// T = 2, PF = 1 for many tiles (four wavefronts per SIMD are asked for: the few registers that spill cost less than the
+// fourth wavefront gains, and a second step in flight costs more occupancy than the latency it hides).  T = 1, PF = 4
+// where 128 x 128 tiles would not give every compute unit two: a workgroup is then alone on its compute unit and waits
+// for memory once per step.
+// The vector ALU is the scarce unit here (the split of both operands): every address is a uniform base, advanced by
+// scalar instructions, plus an offset that a thread computes once.
+template <int EPI, int T, int PF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 : 1, T == 2 ? 4 : 8))) void gemm_nn_split_kernel(
+    const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ out, int64_t n, int K, int C,
+    const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
+    double* __restrict__ partials) {
     if constexpr (EPI == 0) {
         // gated plain product, as in gemm_nn_kernel
         if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
     }
+    constexpr int BT = 64 * T;                    // rows and columns of the tile
     constexpr int LDH = BK + 8;                   // bf16 per tile row: rows start 16-byte aligned
-    constexpr int PLANE = BM * LDH;               // BM == BN
-    __shared__ __align__(16) unsigned short smem[6 * PLANE];
-    unsigned short* const As = smem;              // [3][BM][LDH]: A tile, k contiguous per row
-    unsigned short* const Bs = smem + 3 * PLANE;  // [3][BN][LDH]: B tile transposed, k contiguous per column
+    constexpr int PLANE = BT * LDH;
+    constexpr int NB = 4 * T;                     // k per thread of the B tile
+    constexpr int kSlab = 32 * (BT + 4) * 4;      // bytes of the result slab, which reuses the operand buffer
+    constexpr int kBytes = 6 * PLANE * 2 > kSlab ? 6 * PLANE * 2 : kSlab;
+    __shared__ __align__(16) unsigned short smem[kBytes / 2];
+    unsigned short* const As = smem;              // [3][BT][LDH]: A tile, k contiguous per row
+    unsigned short* const Bs = smem + 3 * PLANE;  // [3][BT][LDH]: B tile transposed, k contiguous per column
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lk = lane >> 5;
-    const int ctiles = (C + BN - 1) / BN;
+    const int ctiles = (C + BT - 1) / BT;
     int64_t mtile;
     int ctile;
     xcd_group(blockIdx.x, gridDim.x, (unsigned)ctiles, mtile, ctile);
-    const int64_t m0 = mtile * BM;
-    const int c0 = ctile * BN;
+    const int64_t m0 = mtile * BT;
+    const int c0 = ctile * BT;
 
-    floatx16 acc[2][2];
+    floatx16 acc[T][T];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < T; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // A: thread takes 4 consecutive k of two rows; B: 8 consecutive k of one column (coalesced across the columns)
-    float4 ra[2];
-    float rb[8];
-    const int bc = tid & 127, bkg = tid >> 7;
-    auto fetch = [&](int k0) {
+    // A: thread takes 4 consecutive k of T rows; B: NB consecutive k of one column (coalesced across the columns).  Rows
+    // past n and columns past C repeat the last one: their results are never stored.
+    const float* const At = A + m0 * K;
+    const int rows = (int)(n - m0 < BT ? n - m0 : BT);
+    int aoff[T];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int f = tid + 256 * i;
-            const int row = f >> 2, kq = f & 3;
-            const int64_t gr = m0 + row;
-            const int k = k0 + 4 * kq;
-            ra[i] = ld4_guard(A, gr * K + k, gr < n, K - k);
-        }
+    for (int i = 0; i < T; ++i) {
+        const int r = (tid >> 2) + 64 * i;
+        aoff[i] = (r < rows ? r : rows - 1) * K + 4 * (tid & 3);
+    }
+    const int bc = tid & (BT - 1);
+    const int bkg = __builtin_amdgcn_readfirstlane(tid / BT);
+    const int boff = c0 + bc < C ? c0 + bc : C - 1;
+    float ra[PF][T][4], rb[PF][NB];
+    auto fetch = [&](int s, int k0) {
+        if (k0 + BK <= K) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int k = k0 + 8 * bkg + e;
-            rb[e] = (k < K && c0 + bc < C) ? B[(int64_t)k * C + c0 + bc] : 0.f;
-        }
-    };
-    auto stash = [&]() {
+            for (int i = 0; i < T; ++i) {
+                const float4u q = *reinterpret_cast<const float4u*>(At + k0 + aoff[i]);
+                ra[s][i][0] = q.x; ra[s][i][1] = q.y; ra[s][i][2] = q.z; ra[s][i][3] = q.w;
+            }
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int f = tid + 256 * i;
-            const int row = f >> 2, kq = f & 3;
-            unsigned h0, m0_, l0, h1, m1, l1;
-            split3_pair(ra[i].x, ra[i].y, h0, m0_, l0);
-            split3_pair(ra[i].z, ra[i].w, h1, m1, l1);
-            const int o = row * LDH + 4 * kq;
-            *reinterpret_cast<uint2*>(As + o) = make_uint2(h0, h1);
-            *reinterpret_cast<uint2*>(As + PLANE + o) = make_uint2(m0_, m1);
-            *reinterpret_cast<uint2*>(As + 2 * PLANE + o) = make_uint2(l0, l1);
-        }
-        {
-            unsigned h[4], m[4], l[4];
+            for (int e = 0; e < NB; ++e) rb[s][e] = (B + (int64_t)(k0 + NB * bkg + e) * C)[boff];
+        } else {                                  // the last, partial step: A is zero past K, B repeats its last row
 #pragma unroll
-            for (int e = 0; e < 4; ++e) split3_pair(rb[2 * e], rb[2 * e + 1], h[e], m[e], l[e]);
-            const int o = bc * LDH + 8 * bkg;
-            *reinterpret_cast<uint4*>(Bs + o) = make_uint4(h[0], h[1], h[2], h[3]);
-            *reinterpret_cast<uint4*>(Bs + PLANE + o) = make_uint4(m[0], m[1], m[2], m[3]);
-            *reinterpret_cast<uint4*>(Bs + 2 * PLANE + o) = make_uint4(l[0], l[1], l[2], l[3]);
-        }
-    };
-
-    auto multiply = [&]() {
-        bf16x8 a[3][2];
+            for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+                for (int e = 0; e < 4; ++e) {
+                    const int k = k0 + 4 * (tid & 3) + e;
+                    const float v = At[aoff[i] - 4 * (tid & 3) + (k < K ? k : K - 1)];
+                    ra[s][i][e] = k < K ? v : 0.f;
+                }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                a[p][i] = *reinterpret_cast<const bf16x8*>(As + p * PLANE + (wm * 64 + i * 32 + li) * LDH + 8 * lk);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            bf16x8 b[3];                             // one column tile's parts at a time keeps the register count down
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                b[p] = *reinterpret_cast<const bf16x8*>(Bs + p * PLANE + (wn * 64 + j * 32 + li) * LDH + 8 * lk);
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                floatx16 c = acc[i][j];
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2][i], b[0], c, 0, 0, 0);   // small terms first
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[2], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[1], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[0], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[1], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[0], c, 0, 0, 0);
-                acc[i][j] = c;
+            for (int e = 0; e < NB; ++e) {
+                const int k = k0 + NB * bkg + e;
+                rb[s][e] = (B + (int64_t)(k < K ? k : K - 1) * C)[boff];
             }
         }
     };
-    // (fetching two steps ahead was tried: the second register set costs more occupancy than the latency it hides)
     const int nk = (K + BK - 1) / BK;
-    fetch(0);
-    for (int kt = 0; kt < nk; ++kt) {
-        __syncthreads();
-        stash();
-        __syncthreads();
-        if (kt + 1 < nk) fetch((kt + 1) * BK);
-        multiply();
+#pragma unroll
+    for (int s = 0; s < PF; ++s)
+        if (s < nk) fetch(s, s * BK);
+    for (int kt0 = 0; kt0 < nk; kt0 += PF) {
+#pragma unroll
+        for (int s = 0; s < PF; ++s) {
+            const int kt = kt0 + s;
+            if (PF > 1 && kt >= nk) break;
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < T; ++i) stash_split<4>(As, PLANE, ((tid >> 2) + 64 * i) * LDH + 4 * (tid & 3), ra[s][i]);
+            stash_split<NB>(Bs, PLANE, bc * LDH + NB * bkg, rb[s]);
+            __syncthreads();
+            if (kt + PF < nk) fetch(s, (kt + PF) * BK);
+            multiply_split<T, LDH>(acc, As, Bs, wm * 32 * T + li, wn * 32 * T + li, lk);
+        }
     }
-    static_assert(32 * (BN + 4) * 4 <= 6 * PLANE * 2, "result slab must fit the operand buffer");
-    tile128_epilogue<EPI>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
+    tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
 }
 
 // out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 32.
@@ -482,7 +666,7 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
         {
             const int kr = tid / (BN / 4), cq = tid % (BN / 4);      // 32 x 8 float4, one per thread
             const int k = k0 + kr, c = 4 * cq;
-            rb = ld4_guard(Bcat, (int64_t)k * C + c, k < K, C - c);
+            rb = ld_quad<kFull>(Bcat + (int64_t)(k < K ? k : K - 1) * C, c, C);       // (C is a multiple of four)
         }
     };
     auto stash = [&]() {
@@ -526,7 +710,8 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
 // Block (chunk, ktile, ctile): partial[chunk][k][c] = sum_{rows of chunk} A[row][k] G[row][c].
 // PRO 1: the right operand is the hidden-layer pre-activation gradient nu (relu(T) - Z) 1[T > 0], formed from
 // T (passed as G) and Z while the tile is loaded, so that it is never stored.
-template <int BN, int PRO>
+// FULL: both widths are multiples of four.
+template <int BN, int PRO, int FULL>
 __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                       const float* __restrict__ Zl, float nu,
                                                       float* __restrict__ partial, int64_t n, int K, int C,
@@ -565,48 +750,48 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    float4 ra[2], rg[G_PER_T];
+    float4 ra[2], rg[G_PER_T], rz[PRO ? G_PER_T : 1];
+    const int amode = FULL ? kFull : row_mode(K), gmode = FULL ? kFull : row_mode(C);
     auto fetch = [&](int64_t r0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {              // A tile: 16 rows x 128 k = 512 float4
+        for (int i = 0; i < 2; ++i) {              // A tile: 16 rows x 128 k = 512 quads; columns past K are never stored
             const int f = tid + 256 * i;
-            const int rr = f >> 5, kq = f & 31;
-            const int64_t gr = r0 + rr;
-            const int k = k0 + 4 * kq;
-            ra[i] = ld4_guard(A, gr * K + k, gr < r_end, K - k);
+            const int64_t gr = r0 + (f >> 5);
+            ra[i] = ld_quad_raw(amode, A + (gr < r_end ? gr : r_end - 1) * K, k0 + 4 * (f & 31), K);     // rows past the chunk: G is zero
         }
 #pragma unroll
         for (int i = 0; i < G_PER_T; ++i) {
             const int f = tid + 256 * i;
             if (f < G_F4) {
-                const int rr = f / (BN / 4), cq = f % (BN / 4);
-                const int64_t gr = r0 + rr;
-                const int c = c0 + 4 * cq;
-                rg[i] = ld4_guard(G, gr * C + c, gr < r_end, C - c);
-                if constexpr (PRO == 1) {
-                    const float4 t = rg[i];
-                    const float4 z = ld4_guard(Zl, gr * C + c, gr < r_end, C - c);
-                    rg[i].x = (t.x > 0.f) ? nu * (t.x - z.x) : 0.f;
-                    rg[i].y = (t.y > 0.f) ? nu * (t.y - z.y) : 0.f;
-                    rg[i].z = (t.z > 0.f) ? nu * (t.z - z.z) : 0.f;
-                    rg[i].w = (t.w > 0.f) ? nu * (t.w - z.w) : 0.f;
-                }
+                const int64_t gr = r0 + f / (BN / 4);
+                const int64_t go = (gr < r_end ? gr : r_end - 1) * C;
+                const int c = c0 + 4 * (f % (BN / 4));
+                rg[i] = ld_quad_raw(gmode, G + go, c, C);
+                if constexpr (PRO == 1) rz[i] = ld_quad_raw(gmode, Zl + go, c, C);
             }
         }
     };
-    auto stash = [&]() {
+    auto stash = [&](int64_t r0) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int f = tid + 256 * i;
-            const int rr = f >> 5, kq = f & 31;
-            *reinterpret_cast<float4*>(As + rr * LDA + 4 * kq) = ra[i];
+            *reinterpret_cast<float4*>(As + (f >> 5) * LDA + 4 * (f & 31)) = fix_quad(amode, ra[i], k0 + 4 * (f & 31), K);
         }
 #pragma unroll
         for (int i = 0; i < G_PER_T; ++i) {
             const int f = tid + 256 * i;
             if (f < G_F4) {
                 const int rr = f / (BN / 4), cq = f % (BN / 4);
-                *reinterpret_cast<float4*>(Gs + rr * LDG + 4 * cq) = rg[i];
+                float4 g = fix_quad(gmode, rg[i], c0 + 4 * cq, C);
+                if constexpr (PRO == 1) {
+                    const float4 z = fix_quad(gmode, rz[i], c0 + 4 * cq, C);
+                    g.x = (g.x > 0.f) ? nu * (g.x - z.x) : 0.f;
+                    g.y = (g.y > 0.f) ? nu * (g.y - z.y) : 0.f;
+                    g.z = (g.z > 0.f) ? nu * (g.z - z.z) : 0.f;
+                    g.w = (g.w > 0.f) ? nu * (g.w - z.w) : 0.f;
+                }
+                const bool in = r0 + rr < r_end;
+                *reinterpret_cast<float4*>(Gs + rr * LDG + 4 * cq) = make_float4(in ? g.x : 0.f, in ? g.y : 0.f, in ? g.z : 0.f, in ? g.w : 0.f);
             }
         }
     };
@@ -615,7 +800,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
     if (r_begin < r_end) fetch(r_begin);
     for (int64_t r0 = r_begin; r0 < r_end; r0 += BK) {
         __syncthreads();
-        stash();
+        stash(r0);
         __syncthreads();
         if (r0 + BK < r_end) fetch(r0 + BK);
 #pragma unroll
@@ -649,149 +834,146 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
 
 // gemm_tn on the bf16 matrix cores, same three-way split as gemm_nn_split_kernel.  Both operands are contracted
 // over the rows, so both tiles are stored transposed (8 consecutive rows of one column per lane and MFMA): a thread
-// loads 8 rows of one column, which is coalesced across the threads of a wavefront (consecutive columns).
-// PRO 1 forms G = nu (relu(T) - Z) 1[T > 0] from T (passed as G) and Zl while loading.  128 x 128 result tile.
-template <int PRO>
+// loads 4 T rows of one column, which is coalesced across the threads of a wavefront (consecutive columns).
+// PRO 1 forms G = nu (relu(T) - Z) 1[T > 0] from T (passed as G) and Zl while loading.  Tile 64 T x 64 T; T, PF as there.
+// A row's address is uniform over a wavefront: scalar instructions form it, a thread adds its column.
+template <int PRO, int T, int PF>
 __global__ __launch_bounds__(256) void gemm_tn_split_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                             const float* __restrict__ Zl, float nu,
                                                             float* __restrict__ partial, int64_t n, int K, int C,
                                                             int64_t rows_per_chunk) {
+    constexpr int BT = 64 * T;
     constexpr int LDH = BK + 8;
-    constexpr int PLANE = 128 * LDH;
+    constexpr int PLANE = BT * LDH;
+    constexpr int NR = 4 * T;                     // rows per thread
     __shared__ __align__(16) unsigned short smem[6 * PLANE];
-    unsigned short* const As = smem;              // [3][128 columns of A][LDH rows]
-    unsigned short* const Gs = smem + 3 * PLANE;  // [3][128 columns of G][LDH rows]
+    unsigned short* const As = smem;              // [3][BT columns of A][LDH rows]
+    unsigned short* const Gs = smem + 3 * PLANE;  // [3][BT columns of G][LDH rows]
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lk = lane >> 5;
-    const int ktiles = (K + 127) / 128;
-    const int ctiles = (C + 127) / 128;
+    const int ktiles = (K + BT - 1) / BT;
+    const int ctiles = (C + BT - 1) / BT;
     int tile;
     int64_t chunk;
     xcd_group(blockIdx.x, gridDim.x, (unsigned)(ktiles * ctiles), chunk, tile);
-    const int k0 = (tile / ctiles) * 128;
-    const int c0 = (tile % ctiles) * 128;
+    const int k0 = (tile / ctiles) * BT;
+    const int c0 = (tile % ctiles) * BT;
     const int64_t r_begin = chunk * rows_per_chunk;
     const int64_t r_end = (r_begin + rows_per_chunk < n) ? (r_begin + rows_per_chunk) : n;
 
-    floatx16 acc[2][2];
+    floatx16 acc[T][T];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < T; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    const int col = tid & 127, rg = tid >> 7;     // this thread: column `col` of both tiles, rows 8 rg .. 8 rg + 7
-    const bool a_on = k0 + col < K, g_on = c0 + col < C;
-    float ra[8], rgv[8];
-    auto fetch = [&](int64_t r0) {
+    // this thread: column `col` of both tiles (one past the edge repeats the last: never stored), rows NR rg .. NR rg + NR - 1
+    const int col = tid & (BT - 1);
+    const int rg = __builtin_amdgcn_readfirstlane(tid / BT);
+    const int acol = k0 + col < K ? k0 + col : K - 1, gcol = c0 + col < C ? c0 + col : C - 1;
+    float ra[PF][NR], rgv[PF][NR], rz[PRO ? PF : 1][NR];
+    auto fetch = [&](int s, int64_t r0) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int64_t r = r0 + 8 * rg + e;
-            const bool on = r < r_end;
-            ra[e] = (on && a_on) ? A[r * K + k0 + col] : 0.f;
-            float g = (on && g_on) ? G[r * C + c0 + col] : 0.f;
-            if constexpr (PRO == 1) {
-                const float z = (on && g_on) ? Zl[r * C + c0 + col] : 0.f;
-                g = (g > 0.f) ? nu * (g - z) : 0.f;
-            }
-            rgv[e] = g;
+        for (int e = 0; e < NR; ++e) {
+            const int64_t r = r0 + NR * rg + e;
+            const int64_t rr = r < r_end ? r : r_end - 1;      // rows past the chunk: G is set to zero there
+            ra[s][e] = (A + rr * K)[acol];
+            rgv[s][e] = (G + rr * C)[gcol];
+            if constexpr (PRO == 1) rz[s][e] = (Zl + rr * C)[gcol];
         }
     };
-    auto stash = [&]() {
-        unsigned h[4], m[4], l[4];
+    auto stash = [&](int s, int64_t r0) {
+        stash_split<NR>(As, PLANE, col * LDH + NR * rg, ra[s]);
+        if constexpr (PRO == 1)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) split3_pair(ra[2 * e], ra[2 * e + 1], h[e], m[e], l[e]);
-        const int o = col * LDH + 8 * rg;
-        *reinterpret_cast<uint4*>(As + o) = make_uint4(h[0], h[1], h[2], h[3]);
-        *reinterpret_cast<uint4*>(As + PLANE + o) = make_uint4(m[0], m[1], m[2], m[3]);
-        *reinterpret_cast<uint4*>(As + 2 * PLANE + o) = make_uint4(l[0], l[1], l[2], l[3]);
+            for (int e = 0; e < NR; ++e) rgv[s][e] = rgv[s][e] > 0.f ? nu * (rgv[s][e] - rz[s][e]) : 0.f;
+        if (r0 + BK > r_end)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) split3_pair(rgv[2 * e], rgv[2 * e + 1], h[e], m[e], l[e]);
-        *reinterpret_cast<uint4*>(Gs + o) = make_uint4(h[0], h[1], h[2], h[3]);
-        *reinterpret_cast<uint4*>(Gs + PLANE + o) = make_uint4(m[0], m[1], m[2], m[3]);
-        *reinterpret_cast<uint4*>(Gs + 2 * PLANE + o) = make_uint4(l[0], l[1], l[2], l[3]);
+            for (int e = 0; e < NR; ++e) rgv[s][e] = r0 + NR * rg + e < r_end ? rgv[s][e] : 0.f;
+        stash_split<NR>(Gs, PLANE, col * LDH + NR * rg, rgv[s]);
     };
-
-    auto multiply = [&]() {
-        bf16x8 a[3][2];
+    const int steps = r_begin < r_end ? (int)((r_end - r_begin + BK - 1) / BK) : 0;
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+    for (int s = 0; s < PF; ++s)
+        if (s < steps) fetch(s, r_begin + s * BK);
+    for (int t0 = 0; t0 < steps; t0 += PF) {
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
-                a[p][i] = *reinterpret_cast<const bf16x8*>(As + p * PLANE + (wm * 64 + i * 32 + li) * LDH + 8 * lk);
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            bf16x8 b[3];                             // one column tile's parts at a time keeps the register count down
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                b[p] = *reinterpret_cast<const bf16x8*>(Gs + p * PLANE + (wn * 64 + j * 32 + li) * LDH + 8 * lk);
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                floatx16 c = acc[i][j];
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[2][i], b[0], c, 0, 0, 0);   // small terms first
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[2], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[1], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[1][i], b[0], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[1], c, 0, 0, 0);
-                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[0][i], b[0], c, 0, 0, 0);
-                acc[i][j] = c;
-            }
+        for (int s = 0; s < PF; ++s) {
+            const int t = t0 + s;
+            if (PF > 1 && t >= steps) break;
+            __syncthreads();
+            stash(s, r_begin + (int64_t)t * BK);
+            __syncthreads();
+            if (t + PF < steps) fetch(s, r_begin + (int64_t)(t + PF) * BK);
+            multiply_split<T, LDH>(acc, As, Gs, wm * 32 * T + li, wn * 32 * T + li, lk);
         }
-    };
-    if (r_begin < r_end) fetch(r_begin);
-    for (int64_t r0 = r_begin; r0 < r_end; r0 += BK) {
-        __syncthreads();
-        stash();
-        __syncthreads();
-        if (r0 + BK < r_end) fetch(r0 + BK);
-        multiply();
     }
     float* dst = partial + chunk * (int64_t)K * C;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < T; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int c = c0 + wn * 64 + j * 32 + li;
+        for (int j = 0; j < T; ++j) {
+            const int c = c0 + wn * 32 * T + j * 32 + li;
             if (c >= C) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int k = k0 + wm * 64 + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+                const int k = k0 + wm * 32 * T + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
                 if (k < K) dst[(int64_t)k * C + c] = acc[i][j][r];
             }
         }
 }
 
-// out = sum of the chunks' partial matrices, in fp64 and in a fixed order.  A workgroup takes 64 entries: sixteen lanes of
-// four consecutive entries, sixteen groups of lanes that take the chunks round-robin and are added up in LDS.
+// out = sum of the chunks' partial matrices, in fp64 and in a fixed order.  A workgroup takes 4 X entries: X lanes of four
+// consecutive entries, 256 / X groups of lanes that take the chunks round-robin, four loads in flight each, and are
+// added up in LDS.  X = 16 for large results, 4 for small ones, whose few workgroups would walk many chunks one by one.
 // With W, the workgroup also leaves its share of ||out||^2 and ||W||^2 in norms (two doubles per workgroup).
+template <int X>
 __global__ __launch_bounds__(256) void gemm_tn_reduce_kernel(const float* __restrict__ partial, float* __restrict__ out,
                                                              int64_t count, int nchunks, const float* __restrict__ W,
                                                              double* __restrict__ norms) {
-    __shared__ double sm[16][64];
-    const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+    constexpr int G = 256 / X;
+    __shared__ double sm[G][4 * X];
+    const int x = threadIdx.x & (X - 1), y = threadIdx.x / X;
     double ng = 0.0, nw = 0.0;
-    for (int64_t i0 = (int64_t)blockIdx.x * 64; i0 < count; i0 += (int64_t)gridDim.x * 64) {
+    for (int64_t i0 = (int64_t)blockIdx.x * (4 * X); i0 < count; i0 += (int64_t)gridDim.x * (4 * X)) {
         const int64_t i = i0 + 4 * x;
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (i < count)
-            for (int c = y; c < nchunks; c += 16) {
-                float v[4];
-                ld4u(v, partial + (int64_t)c * count + i, count - i < 4 ? (int)(count - i) : 4);
+        auto sum = [&](auto whole) {
+            for (int c0 = y; c0 < nchunks; c0 += 4 * G) {
+                float v[4][4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[e] += (double)v[e];
+                for (int u = 0; u < 4; ++u) {
+                    const int c = c0 + u * G < nchunks ? c0 + u * G : c0;
+                    if constexpr (decltype(whole)::value) {
+                        const float4u q = *reinterpret_cast<const float4u*>(partial + (int64_t)c * count + i);
+                        v[u][0] = q.x; v[u][1] = q.y; v[u][2] = q.z; v[u][3] = q.w;
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[u][e] = partial[(int64_t)c * count + (i + e < count ? i + e : count - 1)];
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (c0 + u * G < nchunks)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[e] += (double)v[u][e];
             }
+        };
+        if (i + 4 <= count) sum(std::true_type{});
+        else sum(std::false_type{});                     // (entries past the end are not written)
         __syncthreads();
 #pragma unroll
         for (int e = 0; e < 4; ++e) sm[y][4 * x + e] = acc[e];
         __syncthreads();
-        if (threadIdx.x < 64 && i0 + threadIdx.x < count) {
+        if (threadIdx.x < 4 * X && i0 + threadIdx.x < count) {
             double t = 0.0;
-#pragma unroll
-            for (int q = 0; q < 16; ++q) t += sm[q][threadIdx.x];
+#pragma unroll 8
+            for (int q = 0; q < G; ++q) t += sm[q][threadIdx.x];
             const float g = (float)t;
             out[i0 + threadIdx.x] = g;
             if (W) {
@@ -898,28 +1080,40 @@ __global__ __launch_bounds__(256) void stream_update_kernel(const float4* __rest
 
 int g_split = 1;      // 1: wide products run on the bf16 matrix cores with three-way split operands, 0: fp32 MFMA
 
+// Tiles per wavefront direction of the split product out[n x C]: 128 x 128 tiles where they give every compute unit two, else
+// 64 x 64 (see gemm_nn_split_kernel).
+constexpr int64_t kFewTiles = 512;
+int nn_tile(int64_t n, int C) {
+    if (!g_split) return 2;
+    return ((n + 127) / 128) * ((C + 127) / 128) < kFewTiles ? 1 : 2;
+}
+
 struct TnPlan {
     int nchunks;
     int64_t rows_per_chunk;
-    int bn;
+    int bn;              // columns per tile: 128, 64 (split product with few workgroups) or 32
     int tiles;
 };
 
+// The rows are cut into chunks so that about 1024 workgroups, four per compute unit, share the product; a chunk has at
+// least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.
 TnPlan tn_plan(int64_t n, int K, int C) {
     TnPlan p;
-    p.bn = (C > 32) ? 128 : 32;
-    const int ktiles = (K + BM - 1) / BM;
-    const int ctiles = (C + p.bn - 1) / p.bn;
-    p.tiles = ktiles * ctiles;
-    int64_t want = (1024 + p.tiles - 1) / p.tiles;          // about 1024 blocks, four per compute unit
-    int64_t max_chunks = (n + 255) / 256;                   // at least 256 rows per chunk
-    int64_t nch = want < max_chunks ? want : max_chunks;
-    if (nch < 1) nch = 1;
-    int64_t rpc = (n + nch - 1) / nch;
-    rpc = (rpc + BK - 1) / BK * BK;
-    p.rows_per_chunk = rpc;
-    p.nchunks = (int)((n + rpc - 1) / rpc);
-    if (p.nchunks < 1) p.nchunks = 1;
+    auto plan = [&](int bm, int bn) {
+        p.bn = bn;
+        p.tiles = ((K + bm - 1) / bm) * ((C + bn - 1) / bn);
+        int64_t nch = (1024 + p.tiles - 1) / p.tiles;
+        nch = std::min(nch, (n + 63) / 64);
+        nch = std::min(nch, std::max<int64_t>(32, n * (K + C) / (2 * (int64_t)K * C)));
+        if (nch < 1) nch = 1;
+        int64_t rpc = (n + nch - 1) / nch;
+        rpc = (rpc + BK - 1) / BK * BK;
+        p.rows_per_chunk = rpc;
+        p.nchunks = (int)std::max<int64_t>(1, (n + rpc - 1) / rpc);
+    };
+    if (C <= 32) { plan(BM, 32); return p; }
+    plan(BM, 128);
+    if (g_split && (int64_t)p.nchunks * p.tiles < kFewTiles) plan(64, 64);
     return p;
 }
 
@@ -931,34 +1125,39 @@ int get_gemm_split() { return g_split; }
 void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, int64_t n, int K, int C,
                     const GemmEpilogue& epi) {
     if (n <= 0 || C <= 0) return;
-    const int64_t mt = (n + BM - 1) / BM;
+    const dim3 block(256);
     if (C > 32) {
-        const int ct = (C + 127) / 128;
-        dim3 grid((unsigned)(mt * ct));
-#define CADMM_NN128(K2_, K1_, K0_) \
+        const int t = nn_tile(n, C);
+        const dim3 grid((unsigned)gemm_nn_blocks(n, C));
+#define CADMM_NN(K2_, K1_, K0_) \
         if (epi.kind == 2) \
-            hipLaunchKernelGGL(K2_, grid, dim3(256), 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
+            hipLaunchKernelGGL(K2_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
                                epi.partials); \
         else if (epi.kind == 1) \
-            hipLaunchKernelGGL(K1_, grid, dim3(256), 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
+            hipLaunchKernelGGL(K1_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
                                nullptr); \
         else \
-            hipLaunchKernelGGL(K0_, grid, dim3(256), 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
+            hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
                                nullptr)
-        if (g_split) {
-            CADMM_NN128((gemm_nn_split_kernel<2>), (gemm_nn_split_kernel<1>), (gemm_nn_split_kernel<0>));
+        if (!g_split) {
+            CADMM_NN((gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
+        } else if (t == 2) {
+            CADMM_NN((gemm_nn_split_kernel<2, 2, 1>), (gemm_nn_split_kernel<1, 2, 1>), (gemm_nn_split_kernel<0, 2, 1>));
         } else {
-            CADMM_NN128((gemm_nn_kernel<128, 2>), (gemm_nn_kernel<128, 1>), (gemm_nn_kernel<128, 0>));
+            CADMM_NN((gemm_nn_split_kernel<2, 1, 4>), (gemm_nn_split_kernel<1, 1, 4>), (gemm_nn_split_kernel<0, 1, 4>));
         }
-#undef CADMM_NN128
+#undef CADMM_NN
     } else {
-        dim3 grid((unsigned)mt);
-        if (epi.kind == 1)
-            hipLaunchKernelGGL((gemm_nn_kernel<32, 1>), grid, dim3(256), 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu,
-                               nullptr, nullptr, nullptr);
-        else
-            hipLaunchKernelGGL((gemm_nn_kernel<32, 0>), grid, dim3(256), 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f,
-                               nullptr, nullptr, nullptr);
+        // (two workgroups per compute unit, as for the wide products; the rows are the only tiles here)
+        const bool few = (n + 127) / 128 < kFewTiles;
+        const dim3 grid((unsigned)(few ? (n + 31) / 32 : (n + 127) / 128));
+        if (epi.kind == 1) {
+            if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<1, 1>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu);
+            else hipLaunchKernelGGL((gemm_nn_narrow_kernel<1, 0>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu);
+        } else {
+            if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<0, 1>), grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f);
+            else hipLaunchKernelGGL((gemm_nn_narrow_kernel<0, 0>), grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f);
+        }
     }
 }
 
@@ -970,8 +1169,8 @@ void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const
 }
 
 int64_t gemm_nn_blocks(int64_t n, int C) {
-    const int64_t mt = (n + BM - 1) / BM;
-    return C > 32 ? mt * ((C + 127) / 128) : mt;
+    const int b = 64 * nn_tile(n, C);
+    return ((n + b - 1) / b) * ((C + b - 1) / b);
 }
 
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C) {
@@ -984,24 +1183,29 @@ int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, in
     if (K <= 0 || C <= 0) return 0;
     TnPlan p = tn_plan(n, K, C);
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.tiles)), block(256);
-    if (g_split && p.bn == 128) {
-        if (Zl) hipLaunchKernelGGL((gemm_tn_split_kernel<1>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
-        else hipLaunchKernelGGL((gemm_tn_split_kernel<0>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
-    } else if (Zl) {
-        if (p.bn == 128)
-            hipLaunchKernelGGL((gemm_tn_kernel<128, 1>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
-        else
-            hipLaunchKernelGGL((gemm_tn_kernel<32, 1>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
+#define CADMM_TN(KERNEL_) hipLaunchKernelGGL(KERNEL_, grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk)
+    if (p.bn == 64) {
+        if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 1, 4>));
+        else CADMM_TN((gemm_tn_split_kernel<0, 1, 4>));
+    } else if (g_split && p.bn == 128) {
+        if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 2, 1>));
+        else CADMM_TN((gemm_tn_split_kernel<0, 2, 1>));
+    } else if (p.bn == 128) {
+        if (Zl) CADMM_TN((gemm_tn_kernel<128, 1, 0>));
+        else CADMM_TN((gemm_tn_kernel<128, 0, 0>));
     } else {
-        if (p.bn == 128)
-            hipLaunchKernelGGL((gemm_tn_kernel<128, 0>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
-        else
-            hipLaunchKernelGGL((gemm_tn_kernel<32, 0>), grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk);
+        const bool full = K % 4 == 0 && C % 4 == 0;
+        if (Zl) CADMM_TN((gemm_tn_kernel<32, 1, 0>));
+        else if (full) CADMM_TN((gemm_tn_kernel<32, 0, 1>));
+        else CADMM_TN((gemm_tn_kernel<32, 0, 0>));
     }
+#undef CADMM_TN
     const int64_t count = (int64_t)K * C;
-    const int64_t tiles = (count + 63) / 64;
+    const bool large = count >= 16384;               // a workgroup of 64 entries on every compute unit
+    const int64_t tiles = (count + (large ? 63 : 15)) / (large ? 64 : 16);
     const int nb = (int)(tiles < kReduceBlocks ? tiles : kReduceBlocks);
-    hipLaunchKernelGGL(gemm_tn_reduce_kernel, dim3(nb), dim3(256), 0, s, partial, out, count, p.nchunks, W, norms);
+    if (large) hipLaunchKernelGGL((gemm_tn_reduce_kernel<16>), dim3(nb), block, 0, s, partial, out, count, p.nchunks, W, norms);
+    else hipLaunchKernelGGL((gemm_tn_reduce_kernel<4>), dim3(nb), block, 0, s, partial, out, count, p.nchunks, W, norms);
     return nb;
 }
 
