@@ -200,7 +200,10 @@ int  cadmm_set_state(cadmm_ctx* ctx, const float* const* W, const float* const* 
  *                        a change of Z_{l,m}, for every r in N_m or r = m)
  *   transform:           out = A B        A device n x K, B device K x C, out n x C
  *   wgrad:               out = A^T G      A device n x K, G device n x C, out K x C
+ * They run on the context's stream, or on the one named by cadmm_op_stream (NULL = the default stream): there, in the order
+ * of the calls, after everything the context has enqueued before and before everything it enqueues later.
  */
+int  cadmm_op_stream(cadmm_ctx* ctx, void* hip_stream);
 int  cadmm_op_aggregate(cadmm_ctx* ctx, const float* X, int32_t width, float* Y);
 int  cadmm_op_aggregate_segments(cadmm_ctx* ctx, const float* V, int32_t width, float* P);
 int  cadmm_op_transform(cadmm_ctx* ctx, const float* A, int64_t n, int32_t K, const float* B,

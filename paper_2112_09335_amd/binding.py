@@ -23,7 +23,7 @@ EXPORTS = [
     "cadmm_get_Z", "cadmm_get_U", "cadmm_get_steps", "cadmm_set_state", "cadmm_op_aggregate",
     "cadmm_op_aggregate_segments", "cadmm_op_transform", "cadmm_op_wgrad",
     "cadmm_profile", "cadmm_get_profile", "cadmm_profile_class_name", "cadmm_tune", "cadmm_predict",
-    "cadmm_partition", "cadmm_op_calibrate", "cadmm_op_wgrad_noalloc", "cadmm_get_fista",
+    "cadmm_partition", "cadmm_op_calibrate", "cadmm_op_wgrad_noalloc", "cadmm_get_fista", "cadmm_op_stream",
 ]
 PROFILE_CLASSES = 19
 
@@ -90,6 +90,7 @@ def load_library():
     lib.cadmm_op_transform.argtypes = [vp, vp, i64, i32, vp, i32, vp]
     lib.cadmm_op_wgrad.argtypes = [vp, vp, vp, i64, i32, i32, vp]
     lib.cadmm_op_wgrad_noalloc.argtypes = [vp, vp, vp, i64, i32, i32, vp]
+    lib.cadmm_op_stream.argtypes = [vp, vp]
     lib.cadmm_op_calibrate.argtypes = [vp, i32, vp, vp, i64, i32, C.POINTER(C.c_double)]
     lib.cadmm_tune.argtypes = [vp, C.c_char_p, i32]
     lib.cadmm_predict.argtypes = [vp, vp, vp, C.POINTER(C.c_double)]
@@ -313,14 +314,16 @@ class Solver:
     def _leave(self):
         self._torch.cuda.current_stream(self.device).wait_stream(self.stream)
 
+    def _on_current_stream(self):
+        """Kernel-level calls are launched on torch's current stream, in order with the library's own."""
+        self.lib.cadmm_op_stream(self.h, self._torch.cuda.current_stream(self.device).cuda_stream)
+
     def op_aggregate(self, X):
         torch = self._torch
         assert X.is_cuda and X.dtype == torch.float32 and X.is_contiguous() and X.shape[0] == self.N
         Y = torch.empty_like(X)
-        self._enter()
-        self._check(self.lib.cadmm_op_aggregate(self.h, C.c_void_p(X.data_ptr()), X.shape[1],
-                                                C.c_void_p(Y.data_ptr())), "cadmm_op_aggregate")
-        self._leave()
+        self._on_current_stream()
+        self._check(self.lib.cadmm_op_aggregate(self.h, X.data_ptr(), X.shape[1], Y.data_ptr()), "cadmm_op_aggregate")
         return Y
 
     def op_aggregate_segments(self, V):
@@ -328,21 +331,18 @@ class Solver:
         assert V.is_cuda and V.dtype == torch.float32 and V.is_contiguous() and V.shape[0] == self.N
         nseg = self.graph_sizes()[1]
         P = torch.empty((nseg, V.shape[1]), dtype=torch.float32, device=V.device)
-        self._enter()
-        self._check(self.lib.cadmm_op_aggregate_segments(self.h, C.c_void_p(V.data_ptr()), V.shape[1],
-                                                         C.c_void_p(P.data_ptr())), "cadmm_op_aggregate_segments")
-        self._leave()
+        self._on_current_stream()
+        self._check(self.lib.cadmm_op_aggregate_segments(self.h, V.data_ptr(), V.shape[1], P.data_ptr()),
+                    "cadmm_op_aggregate_segments")
         return P
 
     def op_transform(self, A, B):
         torch = self._torch
         assert A.is_cuda and B.is_cuda and A.is_contiguous() and B.is_contiguous() and A.shape[1] == B.shape[0]
         out = torch.empty((A.shape[0], B.shape[1]), dtype=torch.float32, device=A.device)
-        self._enter()
-        self._check(self.lib.cadmm_op_transform(self.h, C.c_void_p(A.data_ptr()), A.shape[0], A.shape[1],
-                                                C.c_void_p(B.data_ptr()), B.shape[1], C.c_void_p(out.data_ptr())),
-                    "cadmm_op_transform")
-        self._leave()
+        self._on_current_stream()
+        self._check(self.lib.cadmm_op_transform(self.h, A.data_ptr(), A.shape[0], A.shape[1], B.data_ptr(), B.shape[1],
+                                                out.data_ptr()), "cadmm_op_transform")
         return out
 
     def op_calibrate(self, kind, count, reps=5):
@@ -381,10 +381,9 @@ class Solver:
         torch = self._torch
         assert A.is_cuda and G.is_cuda and A.is_contiguous() and G.is_contiguous() and A.shape[0] == G.shape[0]
         out = torch.empty((A.shape[1], G.shape[1]), dtype=torch.float32, device=A.device)
-        self._enter()
-        self._check(self.lib.cadmm_op_wgrad(self.h, C.c_void_p(A.data_ptr()), C.c_void_p(G.data_ptr()), A.shape[0],
-                                            A.shape[1], G.shape[1], C.c_void_p(out.data_ptr())), "cadmm_op_wgrad")
-        self._leave()
+        self._on_current_stream()
+        self._check(self.lib.cadmm_op_wgrad(self.h, A.data_ptr(), G.data_ptr(), A.shape[0], A.shape[1], G.shape[1],
+                                            out.data_ptr()), "cadmm_op_wgrad")
         return out
 
     def op_wgrad_noalloc(self, A, G, out=None):
@@ -393,11 +392,9 @@ class Solver:
         assert A.is_cuda and G.is_cuda and A.is_contiguous() and G.is_contiguous() and A.shape[0] == G.shape[0]
         if out is None:
             out = torch.empty((A.shape[1], G.shape[1]), dtype=torch.float32, device=A.device)
-        self._enter()
-        self._check(self.lib.cadmm_op_wgrad_noalloc(self.h, C.c_void_p(A.data_ptr()), C.c_void_p(G.data_ptr()),
-                                                    A.shape[0], A.shape[1], G.shape[1], C.c_void_p(out.data_ptr())),
-                    "cadmm_op_wgrad_noalloc")
-        self._leave()
+        self._on_current_stream()
+        self._check(self.lib.cadmm_op_wgrad_noalloc(self.h, A.data_ptr(), G.data_ptr(), A.shape[0], A.shape[1],
+                                                    G.shape[1], out.data_ptr()), "cadmm_op_wgrad_noalloc")
         return out
 
     def tune(self, key, value):

@@ -178,3 +178,45 @@ def test_calibration_kernels_report_a_rate(ctx):
     assert s.op_calibrate("mfma", 200, 3) > 1.0             # TFLOP/s
     assert s.op_calibrate("mfma_bf16", 200, 3) > 1.0
     assert s.op_calibrate("mfma_bf16_valu6", 200, 3) > 1.0
+
+
+def test_kernel_calls_are_ordered_with_the_sweep_and_can_be_captured():
+    """A kernel-level call runs on torch's current stream, after the iterations enqueued before it and before those enqueued
+    later (they share scratch memory), and inside a captured graph."""
+    import torch
+    from paper_2112_09335_amd import binding
+    w = synth.config(2, 0.1)
+    a, b = binding.Solver.from_workload(w, 0), binding.Solver.from_workload(w, 0)
+    try:
+        side = torch.cuda.Stream()
+        X = torch.randn(w.N, 128, device="cuda")
+        torch.cuda.synchronize()
+        want = b.op_aggregate(X * 2)
+        torch.cuda.synchronize()
+        for _ in range(3):
+            a.run(2)
+            with torch.cuda.stream(side):
+                got = a.op_aggregate(X * 2)
+            here = a.op_aggregate(X + X)
+            a.run(1)
+            b.run(3)
+            torch.cuda.synchronize()
+            assert torch.equal(got, want) and torch.equal(here, want)
+        for l in range(1, w.L + 1):
+            assert np.array_equal(a.get_W(l), b.get_W(l)) and np.array_equal(a.get_Z(l), b.get_Z(l))
+        G, out = torch.randn(w.N, 3, device="cuda"), torch.empty(128, 3, device="cuda")
+        graph = torch.cuda.CUDAGraph()
+        a.op_wgrad_noalloc(X, G, out)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            a.op_wgrad_noalloc(X, G, out)
+        for k in range(3):
+            X.mul_(1.5)
+            eager = b.op_wgrad_noalloc(X, G)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, eager), k
+            a.run(1)
+    finally:
+        a.close()
+        b.close()
