@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -184,6 +185,14 @@ ChunkShape chunk_shape(const cadmm_ctx* c, int l) {
     ChunkShape cs;
     cs.rows = share(c->hg.N, c->C[l]);
     cs.segs = l < c->L ? share(c->hg.n_seg, c->C[l + 1]) : 0;
+    if (l == c->L) {
+        // the last-layer solve is bound by its chains of fp64 exponentials: a workgroup gets the rows its lanes cover at once
+        // (four classes per lane, lanes per row a power of two), or as many such sets as give 2048 workgroups
+        int lanes = 1;
+        while (4 * lanes < c->C[l]) lanes *= 2;
+        const int64_t set = 256 / lanes;
+        cs.rows = set * std::max<int64_t>(1, c->hg.N / (set * 2048));
+    }
     return cs;
 }
 

@@ -191,7 +191,11 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                     const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
                     t[0] = t4[u].x; t[1] = t4[u].y; t[2] = t4[u].z; t[3] = t4[u].w;
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = finish(v[e], z[e], t[e]);     // (zeros past the row's end add nothing)
+                    for (int e = 0; e < 4; ++e) {
+                        // (columns past C hold a copy of the last one; with z and t zero there a zero adds nothing)
+                        if constexpr (MODE != kFull) v[e] = e < nv ? v[e] : 0.f;
+                        v[e] = finish(v[e], z[e], t[e]);
+                    }
                 }
                 if constexpr (EPI == 2) {
                     if (take) st4u(Tio + o, t, nv);
