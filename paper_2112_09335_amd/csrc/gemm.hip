@@ -1101,8 +1101,8 @@ struct TnPlan {
 
 // The rows are cut into chunks so that the workgroups that the chip holds at once share the product: three per compute unit for
 // the 128 x 128 tiles (their registers allow no more; 1024 workgroups ran as 768 and a second round a third full: 1.74 against
-// 1.60 ms for 500000 x 512 x 512), four for the others; two rounds of them where a chunk would be longer than 2048 rows,
-// which bounds the fp32 sums over the rows of one.  A chunk has at least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.
+// 1.58 ms for 500000 x 512 x 512), four for the others.  Where a chunk would be longer than 2048 rows there are 1024 all
+// the same: the sums over its rows are in fp32, and longer ones would be less accurate.  A chunk has at least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.
 constexpr int kTnBlocksWide = 768, kTnBlocks = 1024;
 TnPlan tn_plan(int64_t n, int K, int C) {
     TnPlan p;
@@ -1110,7 +1110,7 @@ TnPlan tn_plan(int64_t n, int K, int C) {
         p.bn = bn;
         p.tiles = ((K + bm - 1) / bm) * ((C + bn - 1) / bn);
         int want = bn == 128 ? kTnBlocksWide : kTnBlocks;
-        if (bn == 128 && n * p.tiles / want > 2048) want *= 2;
+        if (bn == 128 && n * p.tiles / want > 2048) want = kTnBlocks;
         int64_t nch = bn == 128 && p.tiles <= want ? want / p.tiles : (want + p.tiles - 1) / p.tiles;
         nch = std::min(nch, (n + 63) / 64);
         nch = std::min(nch, std::max<int64_t>(32, n * (K + C) / (2 * (int64_t)K * C)));
