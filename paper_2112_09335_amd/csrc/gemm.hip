@@ -841,8 +841,10 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
 // loads 4 T rows of one column, which is coalesced across the threads of a wavefront (consecutive columns).
 // PRO 1 forms G = nu (relu(T) - Z) 1[T > 0] from T (passed as G) and Zl while loading.  Tile 64 T x 64 T; T, PF as there.
 // A row's address is uniform over a wavefront: scalar instructions form it, a thread adds its column.
+// Four wavefronts per SIMD are asked for without the prologue (1.68 -> 1.49 ms for 500000 x 512 x 512); with it that spills
+// sixteen registers in the loop and loses more than the fourth wavefront gains.
 template <int PRO, int T, int PF>
-__global__ __launch_bounds__(256) void gemm_tn_split_kernel(const float* __restrict__ A, const float* __restrict__ G,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 && PRO == 0 ? 4 : 1, T == 2 && PRO == 0 ? 4 : 8))) void gemm_tn_split_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                             const float* __restrict__ Zl, float nu,
                                                             float* __restrict__ partial, int64_t n, int K, int C,
                                                             int64_t rows_per_chunk) {
@@ -1099,19 +1101,19 @@ struct TnPlan {
     int tiles;
 };
 
-// The rows are cut into chunks so that the workgroups that the chip holds at once share the product: three per compute unit for
-// the 128 x 128 tiles (their registers allow no more; 1024 workgroups ran as 768 and a second round a third full: 1.74 against
-// 1.58 ms for 500000 x 512 x 512), four for the others.  Where a chunk would be longer than 2048 rows there are 1024 all
-// the same: the sums over its rows are in fp32, and longer ones would be less accurate.  A chunk has at least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.
-constexpr int kTnBlocksWide = 768, kTnBlocks = 1024;
-TnPlan tn_plan(int64_t n, int K, int C) {
+// The rows are cut into chunks so that the workgroups that the chip holds at once share the product: four per compute unit,
+// three for the 128 x 128 tiles with the prologue (their registers allow no more: 1024 of them ran as 768 and a second round
+// a third full, 191 against 172 us for 13752 x 767 x 1000).  Where a chunk would then be longer than 2048 rows there are 1024
+// all the same: the sums over its rows are in fp32, and longer ones would be less accurate.  A chunk has at least 64 rows,
+// and beyond 32 chunks the partial matrices stay below half the size of the operands.
+constexpr int kTnBlocks = 1024, kTnBlocksPrologue = 768;
+TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
     TnPlan p;
     auto plan = [&](int bm, int bn) {
         p.bn = bn;
         p.tiles = ((K + bm - 1) / bm) * ((C + bn - 1) / bn);
-        int want = bn == 128 ? kTnBlocksWide : kTnBlocks;
-        if (bn == 128 && n * p.tiles / want > 2048) want = kTnBlocks;
-        int64_t nch = bn == 128 && p.tiles <= want ? want / p.tiles : (want + p.tiles - 1) / p.tiles;
+        const bool fewer = prologue && bn == 128 && n * p.tiles / kTnBlocksPrologue <= 2048;
+        int64_t nch = fewer ? std::max(1, kTnBlocksPrologue / p.tiles) : (kTnBlocks + p.tiles - 1) / p.tiles;
         nch = std::min(nch, (n + 63) / 64);
         nch = std::min(nch, std::max<int64_t>(32, n * (K + C) / (2 * (int64_t)K * C)));
         if (nch < 1) nch = 1;
@@ -1183,14 +1185,13 @@ int64_t gemm_nn_blocks(int64_t n, int C) {
 }
 
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C) {
-    TnPlan p = tn_plan(n, K, C);
-    return (size_t)p.nchunks * K * C;
+    return (size_t)std::max(tn_plan(n, K, C, false).nchunks, tn_plan(n, K, C, true).nchunks) * K * C;
 }
 
 int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
                    float* partial, const float* Zl, float nu, const float* W, double* norms) {
     if (K <= 0 || C <= 0) return 0;
-    TnPlan p = tn_plan(n, K, C);
+    TnPlan p = tn_plan(n, K, C, Zl != nullptr);
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.tiles)), block(256);
 #define CADMM_TN(KERNEL_) hipLaunchKernelGGL(KERNEL_, grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk)
     if (p.bn == 64) {
