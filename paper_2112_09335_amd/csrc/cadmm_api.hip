@@ -85,6 +85,8 @@ struct cadmm_ctx {
     float* tn_partial = nullptr;
     size_t tn_partial_floats = 0;
     double* partials = nullptr;
+    double* row_sums = nullptr; // RowSums of the Z gradient being searched, for up to row_sum_tiles tiles
+    int row_sum_tiles = 0;
     Unit* unitsW = nullptr;     // [L]
     Unit* unitsZ = nullptr;     // [(L-1) * M]
     Unit* unitsF = nullptr;     // [M]: the L of the last-layer solve with backtracking (fista_mode 1)
@@ -170,6 +172,30 @@ int max_of(const std::vector<int>& v, int lo, int hi) {
     return m;
 }
 
+SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, const RowSchedule& rs);
+
+// How the Z gradient of hidden layer l is formed (z_update_hidden).
+enum GradPath { kGradLowRank, kGradProduct, kGradAggregate };
+GradPath grad_path(const cadmm_ctx* c, int l) {
+    const int Cl = c->C[l], Cn = c->C[l + 1];
+    if (c->use_lowrank && Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024) return kGradLowRank;
+    return Cn < Cl ? kGradProduct : kGradAggregate;
+}
+// Column tiles in which the last kernel of that path leaves the rows' sums for the search; 0: it does not, the search reads the
+// gradient (narrow layers, where that is little, and so many tiles that their sums would not be).
+constexpr int kMaxSumTiles = 16;
+int sum_tiles_of(const cadmm_ctx* c, int l, GradPath path) {
+    const int Cl = c->C[l];
+    int tiles = 0;
+    if (path == kGradLowRank) tiles = 1;
+    else if (path == kGradProduct) tiles = Cl > 32 ? gemm_nn_tiles(c->hg.N, Cl) : 0;
+    else if (Cl >= 4) tiles = spmm_tiles(schedule_of(c, c->d_rows, c->hg.row_sched), Cl);
+    return tiles <= kMaxSumTiles ? tiles : 0;
+}
+int gradient_sum_tiles(const cadmm_ctx* c, int l) {          // most of any path that tuning can choose
+    return std::max(sum_tiles_of(c, l, grad_path(c, l)), c->C[l + 1] < c->C[l] ? std::max(1, sum_tiles_of(c, l, kGradProduct)) : 0);
+}
+
 // Rows / segments per reduction chunk of layer l: a chunk is one workgroup's share of a pass over N x C_l (its rows) or
 // n_seg x C_{l+1} (its segments).  16384 elements give a workgroup sixteen 16-byte loads per lane and array, enough to
 // drown its fixed costs (three barriers, block sums); smaller problems get smaller chunks down to 2048 elements, so that
@@ -183,7 +209,8 @@ ChunkShape chunk_shape(const cadmm_ctx* c, int l) {
         return e < 1 ? (int64_t)1 : e;
     };
     ChunkShape cs;
-    cs.rows = share(c->hg.N, c->C[l]);
+    const int sum_tiles = l < c->L ? sum_tiles_of(c, l, grad_path(c, l)) : 0;
+    cs.rows = share(c->hg.N, sum_tiles ? 6 * sum_tiles : c->C[l]);       // (three doubles per tile)
     cs.segs = l < c->L ? share(c->hg.n_seg, c->C[l + 1]) : 0;
     if (l == c->L) {
         // the last-layer solve is bound by its chains of fp64 exponentials: a workgroup gets the rows its lanes cover at once
@@ -279,6 +306,9 @@ size_t layout(cadmm_ctx* c, char* base) {
         np = np > np3 ? np : np3;
     }
     c->partials = b.take<double>(np);
+    c->row_sum_tiles = 0;
+    for (int l = 1; l < L; ++l) c->row_sum_tiles = std::max(c->row_sum_tiles, gradient_sum_tiles(c, l));
+    c->row_sums = b.take<double>((size_t)N * c->row_sum_tiles * 3);
     c->unitsW = b.take<Unit>(L);
     c->unitsZ = b.take<Unit>((size_t)(L - 1) * g.M);
     c->unitsF = b.take<Unit>((size_t)g.M);
@@ -344,6 +374,7 @@ SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, co
     sc.rec = d.rec; sc.ent = d.ent;
     sc.n_long = rs.n_long(); sc.long_row = d.long_row; sc.long_part_ptr = d.long_ptr;
     sc.side = c->side;
+    sc.n_out = c->hg.N;
     sc.group_rows = c->hg.group_rows;
     for (int l = 0; l < 7; ++l) {
         sc.blocks[l] = d.blocks[l];
@@ -597,27 +628,29 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     // With a very narrow next layer the gradient is never stored: its consumers (the product with
     // W_{l+1}, the search, the step) rebuild it per element from Z_l, T_l and the N x C_{l+1} factor
     // A~ G_{l+1}, which removes a full write and two full reads of an N x C_l matrix.
-    const bool lowrank = c->use_lowrank && Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
+    const GradPath path = grad_path(c, l);
+    const bool lowrank = path == kGradLowRank;
+    int sum_tiles = sum_tiles_of(c, l, path);
+    if (sum_tiles > c->row_sum_tiles) sum_tiles = 0;          // (the tiles' width was tuned since the workspace was laid out)
+    double* const row_sums = sum_tiles ? c->row_sums : nullptr;
     if (lowrank) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
         timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] { launch_lowrank_operand(s, c->W[l + 1], c->Bcat, Cl, Cn); });
-    } else if (Cn < Cl) {
+        timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * (Cl + Cn) * Cn, [&] {
+            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->Bcat, Wt, c->tmpV, N, Cl, Cn, Cn, c->nu, row_sums);
+        });
+    } else if (path == kGradProduct) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
         GemmEpilogue ge;
-        ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu;
+        ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu; ge.row_sums = row_sums;
         gemm_nn(c, c->tmpA, Wt, c->tmpB, N, Cn, Cl, ge);
     } else {
         gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl);                         // G_{l+1} W_{l+1}^T
         SpmmEpilogue epi;
-        epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu;
+        epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu; epi.row_sums = row_sums;
         aggregate(c, c->tmpA, c->tmpB, Cl, epi);
     }
-    if (lowrank)
-        timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * (Cl + Cn) * Cn, [&] {
-            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->Bcat, c->tmpV, N, Cl, Cn, Cn, c->nu);
-        });
-    else
-        gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn);                    // grad W_{l+1}
+    if (!lowrank) gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn);          // grad W_{l+1}
     aggregate_segments(c, c->tmpV, c->P, Cn);                                    // A~_{r,m} (grad W) per segment
     ZTrialArgs a;
     const cadmm_ctx::DevChunks& ct = c->d_chunks[l];
@@ -626,13 +659,13 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     a.unit_chunk_ptr = ct.unit_ptr; a.M = M;
     a.segc_row = c->d_segc_row;
     a.Zl = c->Z[l]; a.gradZ = lowrank ? nullptr : c->tmpB; a.Tl = c->T[l]; a.Cl = Cl;
-    a.SG = c->tmpA; a.Wt = Wt;
+    a.row_sums = row_sums; a.sum_tiles = sum_tiles; a.N = N;
     a.Tn = c->T[l + 1]; a.Zn = c->Z[l + 1]; a.P = c->P; a.Cn = Cn;
     a.Gn = c->G[l + 1];
     a.next_is_last = next_last;
     a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
-    // one pass reads Z_l, grad, T_l over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
-    const double zt_bytes = 4.0 * ((lowrank ? 2.0 : 3.0) * (double)N * Cl + (lowrank ? (double)N * Cn : 0.0) +
+    // one pass reads Z_l, grad, T_l (or their sums) over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
+    const double zt_bytes = 4.0 * ((sum_tiles ? 6.0 * sum_tiles * (double)N : 3.0 * (double)N * Cl) +
                                    (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;
     timed(c, P_Z_TRIAL, zt_bytes, 0.0, [&] {
         launch_z_first(s, a);

@@ -502,24 +502,6 @@ __global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, floa
 }
 
 // ------------------------------------------------------------------------------------------ Z search
-// grad[v] = nu (z[v] - relu(t[v])) + sum_k sg[k] wt[k][v], always in this order (the step kernel must
-// reproduce the very same values the search saw).  The rows of W_{l+1}^T are read from LDS (wcol: this lane's four
-// columns of row 0, wv float4 per row): the kernels that rebuild the gradient stream N x C_l matrices and need the
-// wavefronts in flight that 64 registers per lane for these rows would cost them.
-__device__ __forceinline__ void lowrank_grad_lds(float (&g)[4], const float (&z)[4], const float (&t)[4],
-                                                 const float (&sg)[kLowRankMax], const float4* wcol, int wv, int Cn, float nu) {
-#pragma unroll
-    for (int v = 0; v < 4; ++v) g[v] = nu * (z[v] - fmaxf(t[v], 0.f));
-#pragma unroll
-    for (int k = 0; k < kLowRankMax; ++k) {
-        if (k < Cn) {
-            const float4 w4 = wcol[k * wv];
-            g[0] = fmaf(sg[k], w4.x, g[0]); g[1] = fmaf(sg[k], w4.y, g[1]);
-            g[2] = fmaf(sg[k], w4.z, g[2]); g[3] = fmaf(sg[k], w4.w, g[3]);
-        }
-    }
-}
-
 // How a workgroup walks rows of `width` floats: 2^shift lanes per row, four columns per lane and trip.
 struct RowWalk {
     int wv, shift, c_first, r_first, r_step;
@@ -542,47 +524,44 @@ struct RowWalk {
 //   segments, next layer hidden (HID): its ReLU makes the term piecewise quadratic; the first candidate is evaluated.
 // So with a last next layer this one pass over memory is the whole search, and with a hidden one the later passes read
 // the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidate's change, S2.  Bound by HBM traffic.
-// RM, SM: kinds of the widths Cl and Cn.
+// SM: kind of the width Cn.
 constexpr int kFirstVals = 5;
-template <int HID, int LR, int RM, int SM>
+template <int RM>
+__device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int end, double (&s)[kFirstVals]) {
+    const RowWalk w(a.Cl);
+    for (int r = begin + w.r_first; r < end; r += w.r_step) {
+        const int64_t base = (int64_t)r * a.Cl;
+        for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+            float zv[4], gv[4], tv[4];
+            ldr<RM>(zv, a.Zl + base, 4 * cv, a.Cl);
+            ldr<RM>(tv, a.Tl + base, 4 * cv, a.Cl);
+            ldr<RM>(gv, a.gradZ + base, 4 * cv, a.Cl);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double z = (double)zv[v], gz = (double)gv[v];
+                s[0] += (z - fmax((double)tv[v], 0.0)) * gz;
+                s[1] += gz * gz;
+                s[2] += z * z;
+            }
+        }
+    }
+}
+
+template <int HID, int SM>
 __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
     __shared__ double sm[kFirstVals * 4];
-    extern __shared__ __align__(16) float s_wt[];       // [Cn][Cl] with the low-rank gradient, else nothing
     const int4 ck = a.chunks[blockIdx.x];               // community, kind, first row / segment, one past the last
     double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (ck.y == 0) {
-        const RowWalk w(a.Cl);
-        if constexpr (LR == 1) {
-            for (int i = threadIdx.x; i < a.Cn * a.Cl; i += 256) s_wt[i] = a.Wt[i];
-            __syncthreads();
-        }
-        const float4* const wcol = reinterpret_cast<const float4*>(s_wt) + (w.c_first < w.wv ? w.c_first : 0);
-        for (int r = ck.z + w.r_first; r < ck.w; r += w.r_step) {
-            const int64_t base = (int64_t)r * a.Cl;
-            float srow[LR ? kLowRankMax : 1];           // this row of the N x Cn factor
-            if constexpr (LR == 1) {
-#pragma unroll
-                for (int k4 = 0; k4 < kLowRankMax / 4; ++k4) {
-                    float q[4] = {0.f, 0.f, 0.f, 0.f};
-                    if (4 * k4 < a.Cn) ldv4(q, a.SG + (int64_t)r * a.Cn + 4 * k4);
-                    srow[4 * k4] = q[0]; srow[4 * k4 + 1] = q[1]; srow[4 * k4 + 2] = q[2]; srow[4 * k4 + 3] = q[3];
-                }
+        if (a.row_sums) {                               // the kernel that formed the gradient left the rows' sums
+            const int64_t n = 3 * (int64_t)(ck.w - ck.z);
+            for (int t = 0; t < a.sum_tiles; ++t) {
+                const double* const p = a.row_sums + 3 * ((int64_t)t * a.N + ck.z);
+                for (int64_t i = 3 * (int64_t)threadIdx.x; i < n; i += 3 * 256) { s[0] += p[i]; s[1] += p[i + 1]; s[2] += p[i + 2]; }
             }
-            for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
-                float zv[4], gv[4], tv[4];
-                ldr<RM>(zv, a.Zl + base, 4 * cv, a.Cl);
-                ldr<RM>(tv, a.Tl + base, 4 * cv, a.Cl);
-                if constexpr (LR == 1) lowrank_grad_lds(gv, zv, tv, srow, wcol, w.wv, a.Cn, a.sp.nu);
-                else ldr<RM>(gv, a.gradZ + base, 4 * cv, a.Cl);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const double z = (double)zv[v], gz = (double)gv[v];
-                    s[0] += (z - fmax((double)tv[v], 0.0)) * gz;
-                    s[1] += gz * gz;
-                    s[2] += z * z;
-                }
-            }
-        }
+        } else if (a.Cl % 4 == 0) z_first_rows<kFull>(a, ck.z, ck.w, s);
+        else if (a.Cl >= 4) z_first_rows<kTail>(a, ck.z, ck.w, s);
+        else z_first_rows<kNarrow>(a, ck.z, ck.w, s);
     } else {
         const RowWalk w(a.Cn);
         const double inv = HID ? 1.0 / first_candidate(a.units + ck.x, a.sp) : 0.0;
@@ -750,8 +729,8 @@ __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, con
     }
 }
 
-// The same step with the gradient rebuilt from its low-rank form (see lowrank_grad_lds: the same operations in the
-// same order); a lane group handles two rows per trip with every load issued before the first use.  The rows of W_{l+1}^T
+// The same step with the gradient rebuilt from its low-rank form, nu (z - relu(t)) + sum_k sg[k] wt[k] with the operations in
+// the order in which gemm_nn_gradz_kernel formed it for the search; a lane group handles two rows per trip with every load issued before the first use.  The rows of W_{l+1}^T
 // live in LDS, not in 64 registers per lane: the kernel is a plain in-place update of Z_l and needs the wavefronts in
 // flight that a small register footprint allows (5 TB/s against 4.4 with the rows in registers).
 template <bool LDSU>
@@ -1371,24 +1350,12 @@ static void with_mode(int width, F f) {
 }
 
 void launch_z_first(hipStream_t s, const ZTrialArgs& a) {
-    const bool lr = a.gradZ == nullptr;               // low-rank gradient (the caller checked the shape limits)
-    const size_t lds = lr ? (size_t)a.Cn * a.Cl * sizeof(float) : 0;          // W_{l+1}^T: at most 16 x 1024 floats
     const dim3 grid(a.n_chunks), block(256);
     if (a.n_chunks > 0)
         with_mode(a.Cn, [&](auto sm) {
             constexpr int SM = decltype(sm)::value;
-            if (lr) {
-                if constexpr (SM == kFull) {          // (both widths are multiples of four)
-                    if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, 1, kFull, kFull>), grid, block, lds, s, a);
-                    else hipLaunchKernelGGL((z_first_kernel<1, 1, kFull, kFull>), grid, block, lds, s, a);
-                }
-                return;
-            }
-            with_mode(a.Cl, [&](auto rm) {
-                constexpr int RM = decltype(rm)::value;
-                if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, 0, RM, SM>), grid, block, 0, s, a);
-                else hipLaunchKernelGGL((z_first_kernel<1, 0, RM, SM>), grid, block, 0, s, a);
-            });
+            if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, SM>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((z_first_kernel<1, SM>), grid, block, 0, s, a);
         });
     if (a.next_is_last) hipLaunchKernelGGL((z_first_finish_kernel<0>), dim3(a.M), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((z_first_finish_kernel<1>), dim3(a.M), dim3(256), 0, s, a);

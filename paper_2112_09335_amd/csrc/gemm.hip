@@ -129,7 +129,7 @@ template <int EPI, int T, int MODE>
 __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                                    float* __restrict__ out, const float* __restrict__ Zl,
                                                    const float* tin, float nu, float* __restrict__ Tio, double inv0,
-                                                   bool take, double& dsum) {
+                                                   bool take, double& dsum, double* __restrict__ row_sums) {
     constexpr int BN = 64 * T;
     constexpr int LDC = BN + 4;
     constexpr int Q = BN / 4;                            // quads per row
@@ -182,9 +182,29 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 const int rl = f / Q, cq = f % Q;
                 const int64_t row = m0 + 32 * q + rl;
                 const int c = c0 + 4 * cq;
-                if (row >= n || c >= C) continue;
                 const float4 v4 = *reinterpret_cast<const float4*>(Cs + rl * LDC + 4 * cq);
                 float v[4] = {v4.x, v4.y, v4.z, v4.w}, t[4] = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (EPI == 1) {
+                    if (row_sums) {                              // (uniform) the row's sums over this tile's columns
+                        const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w}, tt[4] = {t4[u].x, t4[u].y, t4[u].z, t4[u].w};
+                        double rs[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const bool in = c + e < C;
+                            const float g = nu * (z[e] - fmaxf(tt[e], 0.f)) + v[e];
+                            const double zd = in ? (double)z[e] : 0.0, gd = in ? (double)g : 0.0;
+                            rs[0] += (zd - fmax((double)tt[e], 0.0)) * gd;
+                            rs[1] += gd * gd;
+                            rs[2] += zd * zd;
+                        }
+#pragma unroll
+                        for (int o = 1; o < Q; o <<= 1)
+#pragma unroll
+                            for (int s = 0; s < 3; ++s) rs[s] += __shfl_xor(rs[s], o, 64);
+                        if (cq < 3 && row < n) row_sums[((int64_t)(c0 / BN) * n + row) * 3 + cq] = cq == 0 ? rs[0] : cq == 1 ? rs[1] : rs[2];
+                    }
+                }
+                if (row >= n || c >= C) continue;
                 const int64_t o = row * C + c;
                 const int nv = MODE == kFull ? 4 : C - c;       // columns of this lane (four, or the row's last few)
                 if constexpr (EPI != 0) {
@@ -213,6 +233,8 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, 
                                               float* __restrict__ out, const float* __restrict__ Zl,
                                               const float* __restrict__ Tl, float nu, float* __restrict__ Tio,
                                               const Unit* unit, double* __restrict__ partials) {
+    // (epilogue 1 has no partials: the argument then carries the row sums)
+    double* const row_sums = EPI == 1 ? partials : nullptr;
     double inv0 = 0.0, dsum = 0.0;
     bool take = false;
     if constexpr (EPI == 2) {
@@ -220,8 +242,8 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, 
         take = unit->spec != 0 && !unit->skip;
     }
     const float* tin = (EPI == 2) ? Tio : Tl;
-    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum);
-    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum);   // (C > 32)
+    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum, row_sums);
+    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum, row_sums);   // (C > 32)
     if constexpr (EPI == 2) {
         __shared__ double red[4];
 #pragma unroll
@@ -621,13 +643,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
     tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
 }
 
-// out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 32.
+// out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 16.
 // This is (grad_Z psi) W for grad = nu (Z - relu(T)) + SG W^T and S = W^T W, without ever storing the gradient:
-// the left operand is formed while its tile is loaded.  K1 and K2 are multiples of four.
+// the left operand is formed while its tile is loaded.  K1 and K2 are multiples of four, K2 = C.
+// The kernel is bound by reading Z and T; beside that it rebuilds the gradient of every element (C fused multiply-adds, the
+// rows of W^T and the block's rows of SG from LDS) for the row sums of the search, which then reads neither matrix:
+// 0.82 ms for the product and 0.75 for the search's pass over the rows of 2M x 256, 1.0 ms together.
+constexpr int kSgLd = kLowRankMax + 4;            // row stride of SG in LDS: the eight rows a wavefront reads at once hit different banks
 __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                             const float* __restrict__ SG, const float* __restrict__ Bcat,
-                                                            float* __restrict__ out, int64_t n, int K1, int K2, int C,
-                                                            float nu) {
+                                                            const float* __restrict__ Wt, float* __restrict__ out, int64_t n,
+                                                            int K1, int K2, int C, float nu, double* __restrict__ row_sums) {
     constexpr int BN = 32;
     // 32 columns of Z_l and T_l per step: every row then gives a whole 128-byte line of each matrix to one step.
     // With half lines the second half had left the L2 before its step came (twice the traffic, measured).
@@ -636,6 +662,8 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     constexpr int LDB = BN + 4;
     __shared__ __align__(16) float As[BM * LDA];
     __shared__ __align__(16) float Bs[GBK * LDB];
+    __shared__ __align__(16) float s_sg[BM * kSgLd];
+    extern __shared__ __align__(16) float s_wt[];        // [C][K1]
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wm = tid >> 6;
@@ -644,46 +672,94 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    float4 ra[4], rb;
+    for (int i = tid; i < C * K1 / 4; i += 256) reinterpret_cast<float4*>(s_wt)[i] = reinterpret_cast<const float4*>(Wt)[i];
+    for (int i = tid; i < BM * (K2 / 4); i += 256) {
+        const int r = i / (K2 / 4), q = i - r * (K2 / 4);
+        const int64_t gr = m0 + r < n ? m0 + r : n - 1;
+        *reinterpret_cast<float4*>(s_sg + r * kSgLd + 4 * q) = *reinterpret_cast<const float4*>(SG + gr * K2 + 4 * q);
+    }
+    // thread: quad tid % 8 of rows tid / 8 + 32 i
+    const int kq = tid & 7;
+    int64_t grow[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t gr = m0 + (tid >> 3) + 32 * i;
+        grow[i] = gr < n ? gr : n - 1;
+    }
+    double rs[4][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) rs[i][0] = rs[i][1] = rs[i][2] = 0.0;
+    float4 rz[4], rt[4], rb;
     auto fetch = [&](int k0) {
+        const int k = k0 + 4 * kq < K1 ? k0 + 4 * kq : 0;                // (quads past K1 are not used)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int f = tid + 256 * i;
-            const int row = f >> 3, kq = f & 7;
-            const int64_t gr = m0 + row;
-            const int k = k0 + 4 * kq;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (gr < n) {
-                if (k < K1) {
-                    const float4 z = *reinterpret_cast<const float4*>(Zl + gr * K1 + k);
-                    const float4 t = *reinterpret_cast<const float4*>(Tl + gr * K1 + k);
-                    v.x = nu * (z.x - fmaxf(t.x, 0.f));
-                    v.y = nu * (z.y - fmaxf(t.y, 0.f));
-                    v.z = nu * (z.z - fmaxf(t.z, 0.f));
-                    v.w = nu * (z.w - fmaxf(t.w, 0.f));
-                } else if (k < K) {
-                    v = *reinterpret_cast<const float4*>(SG + gr * K2 + (k - K1));
-                }
-            }
-            ra[i] = v;
+            rz[i] = *reinterpret_cast<const float4*>(Zl + grow[i] * K1 + k);
+            rt[i] = *reinterpret_cast<const float4*>(Tl + grow[i] * K1 + k);
         }
-        {
-            const int kr = tid / (BN / 4), cq = tid % (BN / 4);      // 32 x 8 float4, one per thread
-            const int k = k0 + kr, c = 4 * cq;
-            rb = ld_quad<kFull>(Bcat + (int64_t)(k < K ? k : K - 1) * C, c, C);       // (C is a multiple of four)
-        }
+        const int kr = tid / (BN / 4), cq = tid % (BN / 4);              // 32 x 8 quads, one per thread
+        rb = ld_quad_raw<kFull>(Bcat + (int64_t)(k0 + kr < K ? k0 + kr : K - 1) * C, 4 * cq, C);
     };
-    auto stash = [&]() {
+    auto stash = [&](int k0) {
+        const int k = k0 + 4 * kq;
+        const bool own = k < K1;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int f = tid + 256 * i;
-            const int row = f >> 3, kq = f & 7;
-            float* d = As + row * LDA + 4 * kq;
-            d[0] = ra[i].x; d[1] = ra[i].y; d[2] = ra[i].z; d[3] = ra[i].w;
+            const float z[4] = {rz[i].x, rz[i].y, rz[i].z, rz[i].w}, t[4] = {rt[i].x, rt[i].y, rt[i].z, rt[i].w};
+            float* const d = As + ((tid >> 3) + 32 * i) * LDA + 4 * kq;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = nu * (z[e] - fmaxf(t[e], 0.f));
+            if (!own) {                                                  // the columns of SG, then zeros
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = k < K ? s_sg[((tid >> 3) + 32 * i) * kSgLd + (k - K1) + e] : 0.f;
+            }
+            d[0] = v[0]; d[1] = v[1]; d[2] = v[2]; d[3] = v[3];
         }
         {
             const int kr = tid / (BN / 4), cq = tid % (BN / 4);
-            *reinterpret_cast<float4*>(Bs + kr * LDB + 4 * cq) = rb;
+            *reinterpret_cast<float4*>(Bs + kr * LDB + 4 * cq) = fix_quad<kFull>(rb, 4 * cq, C);
+        }
+    };
+    // the gradient of the quads just stashed, and what the search needs of it
+    auto sums = [&](int k0) {
+        const int k = k0 + 4 * kq;
+        if (k >= K1) return;
+        float g[4][4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            g[i][0] = nu * (rz[i].x - fmaxf(rt[i].x, 0.f));
+            g[i][1] = nu * (rz[i].y - fmaxf(rt[i].y, 0.f));
+            g[i][2] = nu * (rz[i].z - fmaxf(rt[i].z, 0.f));
+            g[i][3] = nu * (rz[i].w - fmaxf(rt[i].w, 0.f));
+        }
+        for (int q4 = 0; q4 < K2; q4 += 4) {
+            float4 sg[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sg[i] = *reinterpret_cast<const float4*>(s_sg + ((tid >> 3) + 32 * i) * kSgLd + q4);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 w = *reinterpret_cast<const float4*>(s_wt + (q4 + q) * K1 + k);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float f = q == 0 ? sg[i].x : q == 1 ? sg[i].y : q == 2 ? sg[i].z : sg[i].w;
+                    g[i][0] = fmaf(f, w.x, g[i][0]);
+                    g[i][1] = fmaf(f, w.y, g[i][1]);
+                    g[i][2] = fmaf(f, w.z, g[i][2]);
+                    g[i][3] = fmaf(f, w.w, g[i][3]);
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float z[4] = {rz[i].x, rz[i].y, rz[i].z, rz[i].w}, t[4] = {rt[i].x, rt[i].y, rt[i].z, rt[i].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const double zd = (double)z[e], gd = (double)g[i][e];
+                rs[i][0] += (zd - fmax((double)t[e], 0.0)) * gd;
+                rs[i][1] += gd * gd;
+                rs[i][2] += zd * zd;
+            }
         }
     };
     const int nk = (K + GBK - 1) / GBK;
@@ -691,7 +767,8 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     fetch(0);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();
-        stash();
+        stash(kt * GBK);
+        sums(kt * GBK);
         __syncthreads();
         if (kt + 1 < nk) fetch((kt + 1) * GBK);
 #pragma unroll
@@ -707,6 +784,15 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
             const int64_t row = m0 + wm * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
             if (row < n) out[row * C + li] = acc[r];
         }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) rs[i][q] += __shfl_xor(rs[i][q], o, 64);
+        const int64_t row = m0 + (tid >> 3) + 32 * i;
+        if (kq < 3 && row < n) row_sums[row * 3 + kq] = kq == 0 ? rs[i][0] : kq == 1 ? rs[i][1] : rs[i][2];
     }
 }
 
@@ -1146,7 +1232,7 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
                                epi.partials); \
         else if (epi.kind == 1) \
             hipLaunchKernelGGL(K1_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
-                               nullptr); \
+                               epi.row_sums); \
         else \
             hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
                                nullptr)
@@ -1173,10 +1259,15 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
 }
 
 void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Bcat,
-                          float* out, int64_t n, int K1, int K2, int C, float nu) {
+                          const float* Wt, float* out, int64_t n, int K1, int K2, int C, float nu, double* row_sums) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, Bcat, out,
-                       n, K1, K2, C, nu);
+    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), (size_t)C * K1 * sizeof(float), s, Zl, Tl,
+                       SG, Bcat, Wt, out, n, K1, K2, C, nu, row_sums);
+}
+
+int gemm_nn_tiles(int64_t n, int C) {
+    const int b = 64 * nn_tile(n, C);
+    return (C + b - 1) / b;
 }
 
 int64_t gemm_nn_blocks(int64_t n, int C) {

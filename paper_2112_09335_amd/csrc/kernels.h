@@ -10,11 +10,16 @@ namespace cadmm {
 // ---------------------------------------------------------------- sparse aggregation (spmm.hip)
 // Y[r,:] = sum_{p in [lo[r], hi[r])} val[p] * X[col[p],:]   for r < nrows.
 // epilogue 0: store;  1: Y = nu * (Zl - relu(Tl)) + sum  (gradient of the Z subproblem).
+// RowSums: with row_sums (epilogue 1, widths of four and more) the launch also leaves, per column tile and row, the three
+// sums over the tile's columns that the search for theta needs of the gradient g just formed: sum e g with
+// e = Zl - relu(Tl), sum g^2, sum Zl^2 (three doubles at row_sums + (tile * rows + row) * 3), so that the search does not
+// have to read the three N x C_l matrices again.
 struct SpmmEpilogue {
     int kind = 0;
     const float* Zl = nullptr;
     const float* Tl = nullptr;
     float nu = 0.f;
+    double* row_sums = nullptr;
 };
 // Device view of a row list laid out for the aggregation (RowSchedule on the host).  rec[i] = (first chunk, one past
 // the last chunk, output row, 0) of scheduled row i; a chunk is 8 (column, value) pairs of 8 bytes, padded with
@@ -31,11 +36,13 @@ struct SpmmSchedule {
     const int32_t* long_row = nullptr;
     const int32_t* long_part_ptr = nullptr;
     float* side = nullptr;
+    int64_t n_out = 0;             // output rows
     double group_rows = 0.0;       // rows of the community an average gather goes to
     const int4* blocks[7] = {};
     int64_t n_blocks[7] = {};
     int64_t xcd_start[7][9] = {};
 };
+int spmm_tiles(const SpmmSchedule& sched, int width);          // column tiles of such a launch (width >= 4)
 void launch_spmm(hipStream_t s, const SpmmSchedule& sched, const float* X, float* Y, int width, const SpmmEpilogue& epi);
 // Y[pos[k], :] = val[k] * X[col[k], :] for k < n: the output rows that have a single entry.
 // calibration: only the gathers of the row list's column stream, rows of `width` floats (4, 8, 16, ... 256) of X;
@@ -69,7 +76,9 @@ struct GemmEpilogue {
     float* Tio = nullptr;
     const Unit* unit = nullptr;
     double* partials = nullptr;
+    double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C) column tiles
 };
+int gemm_nn_tiles(int64_t n, int C);           // column tiles of that launch (C > 32)
 void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, int64_t n, int K, int C,
                     const GemmEpilogue& epi = GemmEpilogue());
 // 1: plain products wider than 32 columns use three-way bf16 splits of both operands on the bf16 matrix cores
@@ -86,8 +95,10 @@ void launch_stream_update(hipStream_t s, const float* src, float* dst, int64_t c
 int64_t gemm_nn_blocks(int64_t n, int C);      // grid size of that launch (= block results of epilogue 2)
 // out[n x C] = [nu (Zl - relu(Tl)) | SG] * Bcat, Bcat = [W (K1 x C); S (K2 x C)], C <= 32, K1 % 4 == K2 % 4 == 0:
 // the product (grad_Z psi) W with grad = nu (Zl - relu(Tl)) + SG W^T, S = W^T W, the gradient never stored.
+// The rows' RowSums (one tile) are left on the way: the gradient is rebuilt per element with Wt = W^T (C x K1), the
+// operations and their order as in launch_z_step_lowrank.
 void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Bcat,
-                          float* out, int64_t n, int K1, int K2, int C, float nu);
+                          const float* Wt, float* out, int64_t n, int K1, int K2, int C, float nu, double* row_sums);
 // out[K x C] = A[n x K]^T * G[n x C]; partial: scratch of gemm_tn_scratch_floats(n,K,C) floats.
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C);
 // With Zl != nullptr, G holds the pre-activation T of a hidden layer and the right operand is
@@ -176,10 +187,8 @@ struct ZTrialArgs {
     int32_t n_chunks;
     const int32_t* unit_chunk_ptr; int32_t M;
     const int32_t* segc_row;
-    const float* Zl; const float* gradZ; const float* Tl; int Cl;       // own term, rows of the community
-    // low-rank form of the gradient (gradZ == nullptr): grad = nu (Zl - relu(Tl)) + SG Wt, SG is N x Cn with
-    // Cn <= kLowRankMax, Wt is Cn x Cl; it is recomputed per element instead of being read
-    const float* SG = nullptr; const float* Wt = nullptr;
+    const float* Zl; const float* gradZ; const float* Tl; int Cl;       // own term, rows of the community ...
+    const double* row_sums = nullptr; int sum_tiles = 0; int64_t N = 0; // ... or what the gradient's kernel left of it (RowSums)
     const float* Tn; const float* Zn; const float* P; int Cn;   // next layer, per segment
     const float* Gn = nullptr;   // last next layer: G_L = -(U + rho (Z_L - T_L)), read in place of Tn and Zn
     int next_is_last;

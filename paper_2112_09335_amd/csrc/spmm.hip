@@ -56,6 +56,24 @@ __device__ __forceinline__ void store_vec(float* p, const float (&src)[VEC]) {
     }
 }
 
+// Row sums of a gradient g with its z and t, see RowSums: this lane's share of one quad whose first `skip` columns belong to
+// the quad before it.
+__device__ __forceinline__ void add_row_sums(double (&s)[3], const float* g, const float* z, const float* t, int skip) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const double zd = v >= skip ? (double)z[v] : 0.0, gd = v >= skip ? (double)g[v] : 0.0;
+        s[0] += (zd - fmax((double)t[v], 0.0)) * gd;
+        s[1] += gd * gd;
+        s[2] += zd * zd;
+    }
+}
+// adds the shares of 2^lpr_log2 neighbouring lanes; every one of them gets the sums
+__device__ __forceinline__ void reduce_row_sums(double (&s)[3], int lpr_log2) {
+    for (int o = 1; o < (1 << lpr_log2); o <<= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], o, 64);
+}
+
 // Slice k of the workgroup table (the workgroups of XCD k) is [start[k], start[k+1]).
 struct XcdMap {
     long long start[9];
@@ -116,7 +134,8 @@ template <int VEC, int EPI, int LPRL>
 __global__ __launch_bounds__(256) void spmm_rows_kernel(
     const int4* __restrict__ rec, int64_t nrows, const int2* __restrict__ ent, const float* __restrict__ X,
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
-    XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu) {
+    XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu,
+    double* __restrict__ row_sums, int64_t n_out) {
     // Workgroup b belongs to XCD b mod 8 and takes the (b / 8)-th entry of that XCD's slice of the table (or, without
     // the XCD-aware numbering, simply entry b).  Records from nrows on are the parts of split rows.
     const int lpr_log2 = LPRL < 3 ? LPRL : lpr_log2_arg;
@@ -181,13 +200,25 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[v] += __shfl_xor(acc[v], off, 64);
     }
-    if (grp != 0 || !on) return;
+    if (grp != 0) return;
     if constexpr (EPI == 1) {
         if (!is_part) {
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[v] = nu * (ez[v] - fmaxf(et[v], 0.f)) + acc[v];
+            if constexpr (VEC == 4) {
+                if (row_sums) {                          // (uniform; every lane of the row's first group is here)
+                    double rs[3] = {0.0, 0.0, 0.0};
+                    add_row_sums(rs, acc, ez, et, on ? col0 + sub * 4 - cc : 4);
+                    reduce_row_sums(rs, lpr_log2);
+                    double* const o = row_sums + ((int64_t)blockIdx.y * n_out + r.z) * 3;
+                    if (sub < 3) o[sub] = sub == 0 ? rs[0] : sub == 1 ? rs[1] : rs[2];
+                    if (lpr < 3 && sub == 0)
+                        for (int q = lpr; q < 3; ++q) o[q] = q == 1 ? rs[1] : rs[2];
+                }
+            }
         }
     }
+    if (!on) return;
     store_vec<VEC>(dst + cc, acc);
 }
 
@@ -277,13 +308,15 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
                                                           const int32_t* __restrict__ long_part_ptr, int64_t n_long,
                                                           float* __restrict__ Y, int width,
                                                           const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                          float nu, int lpr_log2) {
+                                                          float nu, int lpr_log2, double* __restrict__ row_sums,
+                                                          int n_tiles, int64_t n_out) {
     const int64_t i = blockIdx.x;
     if (i >= n_long) return;
     const int64_t row = long_row[i];
     const int p0 = long_part_ptr[i], p1 = long_part_ptr[i + 1];
     const int lpr = 1 << lpr_log2, groups = 64 >> lpr_log2;
     const int sub = threadIdx.x & (lpr - 1), grp = threadIdx.x >> lpr_log2;
+    double rs[3] = {0.0, 0.0, 0.0};
     for (int cb = 0; cb < width; cb += lpr * VEC) {             // same trip count in every lane
         const bool ok = cb + sub * VEC < width;
         const int c = cb + sub * VEC + VEC <= width ? cb + sub * VEC : width - VEC;
@@ -310,8 +343,17 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
             load_vec<VEC>(t, Tl + o);
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[v] = nu * (z[v] - fmaxf(t[v], 0.f)) + acc[v];
+            if constexpr (VEC == 4) add_row_sums(rs, acc, z, t, cb + sub * VEC - c);
         }
         store_vec<VEC>(Y + o, acc);
+    }
+    if constexpr (EPI == 1 && VEC == 4) {
+        if (row_sums && grp == 0) {                             // the whole row's sums in the first tile's place
+            reduce_row_sums(rs, lpr_log2);
+            for (int tile = sub; tile < n_tiles; tile += lpr)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) row_sums[((int64_t)tile * n_out + row) * 3 + q] = tile == 0 ? rs[q] : 0.0;
+        }
     }
 }
 
@@ -343,9 +385,9 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         const dim3 grid((unsigned)nb, (unsigned)((width + tile - 1) / tile)), block(256);
 #define CADMM_ROWS(L_) do { \
         if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
-                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu); \
+                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, sc.n_out); \
         else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
-                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f); } while (0)
+                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, 0); } while (0)
         if (lpr_log2 == 0) CADMM_ROWS(0);
         else if (lpr_log2 == 1) CADMM_ROWS(1);
         else if (lpr_log2 == 2) CADMM_ROWS(2);
@@ -358,14 +400,20 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         while (clog2 < 6 && (VEC << clog2) < width) ++clog2;
         if (epi.kind == 1)
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
-                               sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2);
+                               sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2, epi.row_sums,
+                               (width + tile - 1) / tile, sc.n_out);
         else
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
-                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2);
+                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, 0, 0);
     }
 }
 
 }  // namespace
+
+int spmm_tiles(const SpmmSchedule& sched, int width) {
+    const int tile = tile_of(sched, width, 4);
+    return (width + tile - 1) / tile;
+}
 
 void set_spmm_tile_cols(int cols) { g_tile_cols = cols > 0 ? cols : 0; }
 void set_spmm_xcd_remap(int on) { g_xcd_remap = on ? 1 : 0; }
