@@ -83,7 +83,7 @@ struct cadmm_ctx {
     std::vector<float*> Wt;     // transposes of W_2 .. W_L, kept by the W steps
     float* Bcat = nullptr;      // [W_{l+1}; W_{l+1}^T W_{l+1}] for the low-rank form of the Z gradient
     float* tn_partial = nullptr;
-    size_t tn_partial_floats = 0;
+    size_t tn_base_floats = 0;  // largest gemm_tn_base_floats that tn_partial serves
     double* partials = nullptr;
     double* row_sums = nullptr; // RowSums of the Z gradient being searched, for up to row_sum_tiles tiles
     int row_sum_tiles = 0;
@@ -176,10 +176,13 @@ SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, co
 
 // How the Z gradient of hidden layer l is formed (z_update_hidden).
 enum GradPath { kGradLowRank, kGradProduct, kGradAggregate };
-GradPath grad_path(const cadmm_ctx* c, int l) {
+bool low_rank_shape(const cadmm_ctx* c, int l) {
     const int Cl = c->C[l], Cn = c->C[l + 1];
-    if (c->use_lowrank && Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024) return kGradLowRank;
-    return Cn < Cl ? kGradProduct : kGradAggregate;
+    return Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
+}
+GradPath grad_path(const cadmm_ctx* c, int l) {
+    if (c->use_lowrank && low_rank_shape(c, l)) return kGradLowRank;
+    return c->C[l + 1] < c->C[l] ? kGradProduct : kGradAggregate;
 }
 // Column tiles in which the last kernel of that path leaves the rows' sums for the search; 0: it does not, the search reads the
 // gradient (narrow layers, where that is little, and so many tiles that their sums would not be).
@@ -192,8 +195,14 @@ int sum_tiles_of(const cadmm_ctx* c, int l, GradPath path) {
     else if (Cl >= 4) tiles = spmm_tiles(schedule_of(c, c->d_rows, c->hg.row_sched), Cl);
     return tiles <= kMaxSumTiles ? tiles : 0;
 }
-int gradient_sum_tiles(const cadmm_ctx* c, int l) {          // most of any path that tuning can choose
-    return std::max(sum_tiles_of(c, l, grad_path(c, l)), c->C[l + 1] < c->C[l] ? std::max(1, sum_tiles_of(c, l, kGradProduct)) : 0);
+// What the workspace is laid out for: a number of the shapes alone, so that its size does not change with the tuning knobs
+// (a knob that asks for more tiles later goes without the sums).
+int sum_tiles_reserved(const cadmm_ctx* c, int l) {
+    const int Cl = c->C[l], Cn = c->C[l + 1];
+    int tiles = 0;
+    if (Cn < Cl) tiles = std::max(1, Cl > 32 ? gemm_nn_most_tiles(c->hg.N, Cl) : 0);
+    else if (Cl >= 4) tiles = spmm_default_tiles(schedule_of(c, c->d_rows, c->hg.row_sched), Cl);
+    return tiles <= kMaxSumTiles ? tiles : low_rank_shape(c, l) ? 1 : 0;
 }
 
 // Rows / segments per reduction chunk of layer l: a chunk is one workgroup's share of a pass over N x C_l (its rows) or
@@ -209,7 +218,7 @@ ChunkShape chunk_shape(const cadmm_ctx* c, int l) {
         return e < 1 ? (int64_t)1 : e;
     };
     ChunkShape cs;
-    const int sum_tiles = l < c->L ? sum_tiles_of(c, l, grad_path(c, l)) : 0;
+    const int sum_tiles = l == c->L ? 0 : low_rank_shape(c, l) ? 1 : sum_tiles_reserved(c, l);
     cs.rows = share(c->hg.N, sum_tiles ? 6 * sum_tiles : c->C[l]);       // (three doubles per tile)
     cs.segs = l < c->L ? share(c->hg.n_seg, c->C[l + 1]) : 0;
     if (l == c->L) {
@@ -285,19 +294,19 @@ size_t layout(cadmm_ctx* c, char* base) {
     c->Pbuf[0] = b.take<float>(g.n_seg * max_of(c->C, 2, L));
     c->Pbuf[1] = L > 2 ? b.take<float>(g.n_seg * max_of(c->C, 2, L)) : c->Pbuf[0];
     c->P = c->Pbuf[0];
-    size_t wmax = 0, tnmax = 0;
+    size_t wmax = 0, tnbase = 0;
     for (int l = 1; l <= L; ++l) {
         size_t w = (size_t)c->C[l - 1] * c->C[l];
         wmax = w > wmax ? w : wmax;
-        size_t t = gemm_tn_scratch_floats(N, c->C[l - 1], c->C[l]);
-        tnmax = t > tnmax ? t : tnmax;
+        size_t t = gemm_tn_base_floats(N, c->C[l - 1], c->C[l]);
+        tnbase = t > tnbase ? t : tnbase;
     }
     c->gradW = b.take<float>(wmax);
     c->Wt.assign(L + 1, nullptr);
     for (int l = 2; l <= L; ++l) c->Wt[l] = b.take<float>((size_t)c->C[l - 1] * c->C[l]);
     c->Bcat = b.take<float>((size_t)(max_of(c->C, 0, L) + kLowRankMax) * kLowRankMax);
-    c->tn_partial = b.take<float>(tnmax);
-    c->tn_partial_floats = tnmax;
+    c->tn_partial = b.take<float>(gemm_tn_reserve(tnbase));
+    c->tn_base_floats = tnbase;
     size_t np = (size_t)kReduceBlocks * kRestCand;
     const size_t np2 = nch * kRestCand;
     np = np > np2 ? np : np2;
@@ -307,7 +316,7 @@ size_t layout(cadmm_ctx* c, char* base) {
     }
     c->partials = b.take<double>(np);
     c->row_sum_tiles = 0;
-    for (int l = 1; l < L; ++l) c->row_sum_tiles = std::max(c->row_sum_tiles, gradient_sum_tiles(c, l));
+    for (int l = 1; l < L; ++l) c->row_sum_tiles = std::max(c->row_sum_tiles, sum_tiles_reserved(c, l));
     c->row_sums = b.take<double>((size_t)N * c->row_sum_tiles * 3);
     c->unitsW = b.take<Unit>(L);
     c->unitsZ = b.take<Unit>((size_t)(L - 1) * g.M);
@@ -1500,7 +1509,7 @@ int cadmm_op_transform(cadmm_ctx* c, const float* A, int64_t n, int32_t K, const
 int cadmm_op_wgrad(cadmm_ctx* c, const float* A, const float* G, int64_t n, int32_t K, int32_t C, float* out) {
     if (!c || !A || !G || !out || n < 1 || K < 1 || C < 1) return CADMM_EINVAL;
     if (!c->has_ws) return fail(c, CADMM_EORDER, "set_workspace first");
-    if (gemm_tn_scratch_floats(n, K, C) > c->tn_partial_floats) return fail(c, CADMM_ENOMEM, "shape needs more scratch than the model reserved");
+    if (gemm_tn_base_floats(n, K, C) > c->tn_base_floats) return fail(c, CADMM_ENOMEM, "shape needs more scratch than the model reserved");
     return on_op_stream(c, "op_wgrad", [&] {
         timed(c, C > 32 ? P_GEMM_TN : P_GEMM_TN_32, 4.0 * ((double)n * K + (double)n * C + (double)K * C),
               2.0 * (double)n * K * C, [&] { launch_gemm_tn(c->stream, A, G, out, n, K, C, c->tn_partial); });
@@ -1511,7 +1520,7 @@ int cadmm_op_wgrad_noalloc(cadmm_ctx* c, const float* A, const float* G, int64_t
     if (!c || !A || !G || !out || n < 1 || K < 1 || C < 1) return CADMM_EINVAL;
     if (c->device < 0) return fail(c, CADMM_EUNSUPPORTED, "host-only context (device -1) has no device path");
     if (c->device >= kMaxDevices) return fail(c, CADMM_EUNSUPPORTED, "device index beyond the static scratch table");
-    const size_t need = gemm_tn_scratch_floats(n, K, C);
+    const size_t need = gemm_tn_base_floats(n, K, C);
     if (need > kStaticScratchFloats)
         return fail(c, CADMM_ENOMEM, "shape needs " + std::to_string(need) + " floats of scratch, the static scratch holds " +
                                          std::to_string(kStaticScratchFloats) + "; use cadmm_op_wgrad with a workspace");

@@ -1175,10 +1175,27 @@ int g_split = 1;      // 1: wide products run on the bf16 matrix cores with thre
 // Tiles per wavefront direction of the split product out[n x C]: 128 x 128 tiles where they give every compute unit two, else
 // 64 x 64 (see gemm_nn_split_kernel).
 constexpr int64_t kFewTiles = 512;
-int nn_tile(int64_t n, int C) {
-    if (!g_split) return 2;
+int nn_tile(int64_t n, int C, int split) {
+    if (!split) return 2;
     return ((n + 127) / 128) * ((C + 127) / 128) < kFewTiles ? 1 : 2;
 }
+
+}  // namespace
+
+// Scratch is asked for by shape alone, so that a workspace holds what its shapes need however the library is tuned later.
+// The base is that of chunks of at least 256 rows, about 1024 workgroups of 128-row tiles; callers are refused by it.  Small
+// shapes get up to five times that, so that they can be cut into chunks of 64 rows.
+constexpr size_t kTnSmallScratch = (size_t)8 << 20;
+size_t gemm_tn_base_floats(int64_t n, int K, int C) {
+    const int64_t bn = C > 32 ? 128 : 32, tiles = ((K + BM - 1) / BM) * ((C + bn - 1) / bn);
+    const int64_t nch = std::max<int64_t>(1, std::min<int64_t>((1024 + tiles - 1) / tiles, (n + 255) / 256));
+    const int64_t rpc = std::max<int64_t>(BK, ((n + nch - 1) / nch + BK - 1) / BK * BK);
+    return (size_t)std::max<int64_t>(1, (n + rpc - 1) / rpc) * K * C;
+}
+size_t gemm_tn_reserve(size_t base) { return std::max(base, std::min(kTnSmallScratch, 5 * base)); }
+size_t gemm_tn_scratch_floats(int64_t n, int K, int C) { return gemm_tn_reserve(gemm_tn_base_floats(n, K, C)); }
+
+namespace {
 
 struct TnPlan {
     int nchunks;
@@ -1191,7 +1208,8 @@ struct TnPlan {
 // three for the 128 x 128 tiles with the prologue (their registers allow no more: 1024 of them ran as 768 and a second round
 // a third full, 191 against 172 us for 13752 x 767 x 1000).  Where a chunk would then be longer than 2048 rows there are 1024
 // all the same: the sums over its rows are in fp32, and longer ones would be less accurate.  A chunk has at least 64 rows,
-// and beyond 32 chunks the partial matrices stay below half the size of the operands.
+// and beyond 32 chunks the partial matrices stay below half the size of the operands.  They fit the scratch of the shape
+// (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
 constexpr int kTnBlocks = 1024, kTnBlocksPrologue = 768;
 TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
     TnPlan p;
@@ -1202,6 +1220,7 @@ TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
         int64_t nch = fewer ? std::max(1, kTnBlocksPrologue / p.tiles) : (kTnBlocks + p.tiles - 1) / p.tiles;
         nch = std::min(nch, (n + 63) / 64);
         nch = std::min(nch, std::max<int64_t>(32, n * (K + C) / (2 * (int64_t)K * C)));
+        nch = std::min(nch, (int64_t)gemm_tn_scratch_floats(n, K, C) / ((int64_t)K * C));
         if (nch < 1) nch = 1;
         int64_t rpc = (n + nch - 1) / nch;
         rpc = (rpc + BK - 1) / BK * BK;
@@ -1224,7 +1243,7 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
     if (n <= 0 || C <= 0) return;
     const dim3 block(256);
     if (C > 32) {
-        const int t = nn_tile(n, C);
+        const int t = nn_tile(n, C, g_split);
         const dim3 grid((unsigned)gemm_nn_blocks(n, C));
 #define CADMM_NN(K2_, K1_, K0_) \
         if (epi.kind == 2) \
@@ -1266,17 +1285,17 @@ void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const
 }
 
 int gemm_nn_tiles(int64_t n, int C) {
-    const int b = 64 * nn_tile(n, C);
+    const int b = 64 * nn_tile(n, C, g_split);
+    return (C + b - 1) / b;
+}
+int gemm_nn_most_tiles(int64_t n, int C) {
+    const int b = 64 * nn_tile(n, C, 1);
     return (C + b - 1) / b;
 }
 
 int64_t gemm_nn_blocks(int64_t n, int C) {
-    const int b = 64 * nn_tile(n, C);
+    const int b = 64 * nn_tile(n, C, g_split);
     return ((n + b - 1) / b) * ((C + b - 1) / b);
-}
-
-size_t gemm_tn_scratch_floats(int64_t n, int K, int C) {
-    return (size_t)std::max(tn_plan(n, K, C, false).nchunks, tn_plan(n, K, C, true).nchunks) * K * C;
 }
 
 int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,

@@ -43,6 +43,7 @@ struct SpmmSchedule {
     int64_t xcd_start[7][9] = {};
 };
 int spmm_tiles(const SpmmSchedule& sched, int width);          // column tiles of such a launch (width >= 4)
+int spmm_default_tiles(const SpmmSchedule& sched, int width);  // the same without the tuned tile width
 void launch_spmm(hipStream_t s, const SpmmSchedule& sched, const float* X, float* Y, int width, const SpmmEpilogue& epi);
 // Y[pos[k], :] = val[k] * X[col[k], :] for k < n: the output rows that have a single entry.
 // calibration: only the gathers of the row list's column stream, rows of `width` floats (4, 8, 16, ... 256) of X;
@@ -79,6 +80,7 @@ struct GemmEpilogue {
     double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C) column tiles
 };
 int gemm_nn_tiles(int64_t n, int C);           // column tiles of that launch (C > 32)
+int gemm_nn_most_tiles(int64_t n, int C);      // most of them, whatever set_gemm_split says
 void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, int64_t n, int K, int C,
                     const GemmEpilogue& epi = GemmEpilogue());
 // 1: plain products wider than 32 columns use three-way bf16 splits of both operands on the bf16 matrix cores
@@ -101,6 +103,8 @@ void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const
                           const float* Wt, float* out, int64_t n, int K1, int K2, int C, float nu, double* row_sums);
 // out[K x C] = A[n x K]^T * G[n x C]; partial: scratch of gemm_tn_scratch_floats(n,K,C) floats.
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C);
+size_t gemm_tn_base_floats(int64_t n, int K, int C);            // what decides whether a caller's scratch will do ...
+size_t gemm_tn_reserve(size_t base);                            // ... and the scratch that serves every shape of that base
 // With Zl != nullptr, G holds the pre-activation T of a hidden layer and the right operand is
 // nu (relu(T) - Zl) 1[T > 0], formed on the fly.  With W (K x C), norms gets block sums of ||out||^2 and ||W||^2 (pairs);
 // returns how many (at most kReduceBlocks).

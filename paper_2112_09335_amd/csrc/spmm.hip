@@ -62,7 +62,7 @@ __device__ __forceinline__ void add_row_sums(double (&s)[3], const float* g, con
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const double zd = v >= skip ? (double)z[v] : 0.0, gd = v >= skip ? (double)g[v] : 0.0;
-        s[0] += (zd - fmax((double)t[v], 0.0)) * gd;
+        s[0] += (v >= skip ? zd - fmax((double)t[v], 0.0) : 0.0) * gd;
         s[1] += gd * gd;
         s[2] += zd * zd;
     }
@@ -363,16 +363,16 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
 // requests of narrower rows cost the L2 as much as those of 128 bytes, and the entries are read once more per tile.
 // Measured per pass over the rows, tiled against untiled: 200000 nodes in 32 communities, width 512: 563 against 766 us
 // (128 columns); 500000 in 16, width 512: 1459 against 1980 us (32 columns); 13752 in 3, width 1000: 180 against 222 us (256).
-int tile_of(const SpmmSchedule& sc, int width, int vec) {
+int tile_of(const SpmmSchedule& sc, int width, int vec, int most) {
     int tile = 64 * vec;
     while (tile > 32 && 4.0 * tile * sc.group_rows > 4.5e6) tile >>= 1;
-    if (g_tile_cols > 0 && g_tile_cols < tile) tile = (g_tile_cols + vec - 1) / vec * vec;
+    if (most > 0 && most < tile) tile = (most + vec - 1) / vec * vec;
     return tile < width ? tile : width;
 }
 
 template <int VEC>
 void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y, int width, const SpmmEpilogue& epi) {
-    const int tile = tile_of(sc, width, VEC);
+    const int tile = tile_of(sc, width, VEC, g_tile_cols);
     const int lanes_needed = (tile + VEC - 1) / VEC;
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < lanes_needed) ++lpr_log2;
@@ -411,7 +411,11 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
 }  // namespace
 
 int spmm_tiles(const SpmmSchedule& sched, int width) {
-    const int tile = tile_of(sched, width, 4);
+    const int tile = tile_of(sched, width, 4, g_tile_cols);
+    return (width + tile - 1) / tile;
+}
+int spmm_default_tiles(const SpmmSchedule& sched, int width) {
+    const int tile = tile_of(sched, width, 4, 0);
     return (width + tile - 1) / tile;
 }
 

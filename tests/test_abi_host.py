@@ -115,3 +115,24 @@ def test_workspace_size_is_plausible_for_the_large_configs():
     state = 4 * w.N * sum(w.dims)
     assert state < s.workspace_bytes() < 12 * state
     s.close()
+
+
+@pytest.mark.parametrize("dims", [[64, 256, 16], [128, 300, 250, 7], [32, 512, 512, 10], [500, 1000, 10], [700, 40, 300, 3]])
+def test_workspace_size_depends_on_the_shapes_alone(dims):
+    """The tuning knobs, some of them process-wide, may change between asking for the size, handing over the workspace and
+    running: what fits before must fit afterwards."""
+    w = synth.config(3, 0.02)
+    s = host_solver()
+    s.build_graph(w.N, w.src, w.dst, w.M, w.comm)
+    s.set_model(dims, **synth.DEFAULT_HYPER)
+    sizes = {s.workspace_bytes()}
+    try:
+        for key, values in (("gemm_split", (0, 1)), ("use_lowrank", (0, 1)), ("spmm_tile_cols", (4, 32, 0))):
+            for v in values:
+                s.tune(key, v)
+                sizes.add(s.workspace_bytes())
+    finally:
+        s.tune("gemm_split", 1)
+        s.tune("spmm_tile_cols", 0)
+    assert len(sizes) == 1
+    s.close()
