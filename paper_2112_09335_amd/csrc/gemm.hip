@@ -307,7 +307,9 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
             if (K % 4 == 0) ra[i] = ld_quad<kFull>(ar, k0 + 4 * (f & 3), K);
             else if (K >= 4) ra[i] = ld_quad<kTail>(ar, k0 + 4 * (f & 3), K);
             else ra[i] = ld_quad<kNarrow>(ar, k0 + 4 * (f & 3), K);
-            rb[i] = C % 4 == 0 ? ld_quad<kFull>(br, c0 + 4 * (f & 31), C) : ld_quad<kTail>(br, c0 + 4 * (f & 31), C);
+            // (both operands are zero past K: a zero times an infinity would not be)
+            const float4 b = C % 4 == 0 ? ld_quad<kFull>(br, c0 + 4 * (f & 31), C) : ld_quad<kTail>(br, c0 + 4 * (f & 31), C);
+            rb[i] = k0 + (f >> 5) < K ? b : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     };
     auto stash = [&]() {
@@ -421,10 +423,12 @@ __global__ __launch_bounds__(256) void gemm_nn_narrow_kernel(const float* __rest
 #pragma unroll
         for (int i = 0; i < B_PER_T; ++i) {
             const int f = SPLIT ? lane + 64 * i : tid;
-            *reinterpret_cast<float4*>(Bw + (f >> 3) * LDB + 4 * (f & 7)) = fix_quad(bmode, rb[i], 4 * (f & 7), C);
+            float4 b = fix_quad(bmode, rb[i], 4 * (f & 7), C);
+            if (k0 + (f >> 3) >= K) b = make_float4(0.f, 0.f, 0.f, 0.f);       // (as A: zero times infinity is no zero)
+            *reinterpret_cast<float4*>(Bw + (f >> 3) * LDB + 4 * (f & 7)) = b;
         }
     };
-    // SPLIT: wavefront w takes the K steps w, w + 4, ...; a step past the end is all zeros in A
+    // SPLIT: wavefront w takes the K steps w, w + 4, ...; a step past the end is all zeros
     const int nk = (K + KS - 1) / KS;
     const int stride = SPLIT ? 4 : 1, trips = SPLIT ? (nk + 3) / 4 : nk;
     int ks = SPLIT ? wave : 0;
@@ -650,7 +654,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
 // rows of W^T and the block's rows of SG from LDS) for the row sums of the search, which then reads neither matrix:
 // 0.82 ms for the product and 0.75 for the search's pass over the rows of 2M x 256, 1.0 ms together.
 constexpr int kSgLd = kLowRankMax + 4;            // row stride of SG in LDS: the eight rows a wavefront reads at once hit different banks
-__global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                             const float* __restrict__ SG, const float* __restrict__ Bcat,
                                                             const float* __restrict__ Wt, float* __restrict__ out, int64_t n,
                                                             int K1, int K2, int C, float nu, double* __restrict__ row_sums) {
@@ -663,7 +667,7 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     __shared__ __align__(16) float As[BM * LDA];
     __shared__ __align__(16) float Bs[GBK * LDB];
     __shared__ __align__(16) float s_sg[BM * kSgLd];
-    extern __shared__ __align__(16) float s_wt[];        // [C][K1]
+    __shared__ __align__(16) float s_wt[2][kLowRankMax * GBK];           // the step's 32 columns of W^T
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wm = tid >> 6;
@@ -672,7 +676,17 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    for (int i = tid; i < C * K1 / 4; i += 256) reinterpret_cast<float4*>(s_wt)[i] = reinterpret_cast<const float4*>(Wt)[i];
+    // threads of the first two wavefronts: quad tid % 8 of row tid / 8 of the tile that starts at column k0
+    const bool has_w = tid < 8 * kLowRankMax;
+    float4 rw = make_float4(0.f, 0.f, 0.f, 0.f);
+    auto fetch_w = [&](int k0) {
+        const int q = tid >> 3 < K2 ? tid >> 3 : K2 - 1, k = k0 + 4 * (tid & 7) < K1 ? k0 + 4 * (tid & 7) : 0;
+        rw = *reinterpret_cast<const float4*>(Wt + (int64_t)q * K1 + k);
+    };
+    if (has_w) {
+        fetch_w(0);
+        *reinterpret_cast<float4*>(s_wt[0] + 4 * tid) = rw;
+    }
     for (int i = tid; i < BM * (K2 / 4); i += 256) {
         const int r = i / (K2 / 4), q = i - r * (K2 / 4);
         const int64_t gr = m0 + r < n ? m0 + r : n - 1;
@@ -722,9 +736,8 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
         }
     };
     // the gradient of the quads just stashed, and what the search needs of it
-    auto sums = [&](int k0) {
-        const int k = k0 + 4 * kq;
-        if (k >= K1) return;
+    auto sums = [&](int k0, const float* wt) {
+        if (k0 + 4 * kq >= K1) return;
         float g[4][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -739,7 +752,7 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
             for (int i = 0; i < 4; ++i) sg[i] = *reinterpret_cast<const float4*>(s_sg + ((tid >> 3) + 32 * i) * kSgLd + q4);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 w = *reinterpret_cast<const float4*>(s_wt + (q4 + q) * K1 + k);
+                const float4 w = *reinterpret_cast<const float4*>(wt + (q4 + q) * GBK + 4 * kq);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float f = q == 0 ? sg[i].x : q == 1 ? sg[i].y : q == 2 ? sg[i].z : sg[i].w;
@@ -765,12 +778,18 @@ __global__ __launch_bounds__(256) void gemm_nn_gradz_kernel(const float* __restr
     const int nk = (K + GBK - 1) / GBK;
     const int li = lane & 31, lk = lane >> 5;
     fetch(0);
+    if (has_w) fetch_w(GBK);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();
+        // the tile of W^T is stored a step before it is read: no third barrier
+        if (has_w) *reinterpret_cast<float4*>(s_wt[(kt + 1) & 1] + 4 * tid) = rw;
         stash(kt * GBK);
-        sums(kt * GBK);
+        sums(kt * GBK, s_wt[kt & 1]);
         __syncthreads();
-        if (kt + 1 < nk) fetch((kt + 1) * GBK);
+        if (kt + 1 < nk) {
+            fetch((kt + 1) * GBK);
+            if (has_w) fetch_w((kt + 2) * GBK);
+        }
 #pragma unroll
         for (int kk = 0; kk < GBK; kk += 2) {
             const float a = As[(wm * 32 + li) * LDA + kk + lk];
@@ -847,7 +866,7 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
         for (int i = 0; i < 2; ++i) {              // A tile: 16 rows x 128 k = 512 quads; columns past K are never stored
             const int f = tid + 256 * i;
             const int64_t gr = r0 + (f >> 5);
-            ra[i] = ld_quad_raw(amode, A + (gr < r_end ? gr : r_end - 1) * K, k0 + 4 * (f & 31), K);     // rows past the chunk: G is zero
+            ra[i] = ld_quad_raw(amode, A + (gr < r_end ? gr : r_end - 1) * K, k0 + 4 * (f & 31), K);     // rows past the chunk: see stash
         }
 #pragma unroll
         for (int i = 0; i < G_PER_T; ++i) {
@@ -865,7 +884,9 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(const float* __restrict__ 
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int f = tid + 256 * i;
-            *reinterpret_cast<float4*>(As + (f >> 5) * LDA + 4 * (f & 31)) = fix_quad(amode, ra[i], k0 + 4 * (f & 31), K);
+            float4 a = fix_quad(amode, ra[i], k0 + 4 * (f & 31), K);
+            if (r0 + (f >> 5) >= r_end) a = make_float4(0.f, 0.f, 0.f, 0.f);   // both operands are zero there
+            *reinterpret_cast<float4*>(As + (f >> 5) * LDA + 4 * (f & 31)) = a;
         }
 #pragma unroll
         for (int i = 0; i < G_PER_T; ++i) {
@@ -1280,8 +1301,7 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
 void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Bcat,
                           const float* Wt, float* out, int64_t n, int K1, int K2, int C, float nu, double* row_sums) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), (size_t)C * K1 * sizeof(float), s, Zl, Tl,
-                       SG, Bcat, Wt, out, n, K1, K2, C, nu, row_sums);
+    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, Bcat, Wt, out, n, K1, K2, C, nu, row_sums);
 }
 
 int gemm_nn_tiles(int64_t n, int C) {

@@ -171,6 +171,22 @@ def test_products_agree_on_the_fp32_and_the_bf16_split_matrix_core_paths(ctx, n,
         s.tune("gemm_split", 1)
 
 
+@pytest.mark.parametrize("n,K,C", [(100, 37, 7), (70001, 37, 7), (50, 130, 16), (77, 5, 3)])
+def test_an_infinity_in_the_last_row_stays_an_infinity_in_narrow_products(ctx, n, K, C):
+    """Steps past the end of the contraction repeat the last row of an operand: it must not meet the zeros of the other."""
+    s, g, torch = ctx
+    say("infinity", n, K, C)
+    A, B = torch.ones(n, K, device="cuda"), torch.ones(K, C, device="cuda")
+    B[K - 1, 1] = float("inf")
+    want = torch.full((n, C), float(K), device="cuda")
+    want[:, 1] = float("inf")
+    assert torch.equal(s.op_transform(A, B), want)
+    A[n - 1, 2] = float("-inf")
+    G, want = torch.ones(n, C, device="cuda"), torch.full((K, C), float(n), device="cuda")
+    want[2] = float("-inf")
+    assert torch.equal(s.op_wgrad_noalloc(A, G), want)
+
+
 def test_calibration_kernels_report_a_rate(ctx):
     s, g, torch = ctx
     assert s.op_calibrate("copy", 1 << 22, 3) > 10.0        # GB/s
