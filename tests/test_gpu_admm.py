@@ -82,6 +82,17 @@ def test_unlabelled_nodes_least_squares_risk_one_community_and_ragged_sizes():
     run_case(w4, 3, "empty-graph")
 
 
+@pytest.mark.parametrize("dims,more", [([101, 301, 90, 6], {}), ([30, 90, 301, 70, 7], {"step_policy": 1}),
+                                       ([67, 49, 261, 3], {"schedule": 1, "fista_mode": 1})])
+def test_ragged_widths_across_column_tiles(dims, more):
+    """Widths that are no multiple of four on both sides of the narrow-side rule: the searches' row sums are left by the
+    aggregation, the product or the gradient kernel, with a partial last quad and a partial last tile."""
+    w = synth.make_workload("ragged-wide", 21 + len(more), 1501, 5, dims, dims[-1], 4, graph="sbm", features="gaussian",
+                            avg_degree=9, frac_intra=0.8, labelled_fraction=0.4)
+    w.hyper.update(more)
+    run_case(w, 4, "ragged-wide/" + "-".join(map(str, dims)))
+
+
 def test_backtracking_cap_status_and_resume_are_consistent():
     from paper_2112_09335_amd import binding
     w = synth.config(1, 0.5)

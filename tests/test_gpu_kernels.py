@@ -171,6 +171,25 @@ def test_products_agree_on_the_fp32_and_the_bf16_split_matrix_core_paths(ctx, n,
         s.tune("gemm_split", 1)
 
 
+@pytest.mark.parametrize("n,K,C", [(63, 17, 33), (65, 129, 65), (2047, 300, 200), (32640, 37, 200), (32641, 37, 200),
+                                   (65408, 37, 7), (65409, 37, 7), (32641, 300, 201), (3, 1, 1), (20011, 128, 32)])
+def test_products_on_both_sides_of_the_tile_rules(ctx, n, K, C):
+    """64-row tiles against 128-row ones (wide results), 32-row against 128-row workgroups (narrow ones), chunks from 64 rows:
+    the sizes where a rule changes sides, remainders of tiles, chunks and quads.  fp32 sums of at most 2048 terms: the same
+    2e-6 of |A||B| as above."""
+    s, g, torch = ctx
+    say("tile rules", n, K, C)
+    rng = np.random.default_rng(n + 3 * K + C)
+    A = rng.standard_normal((n, K)).astype(np.float32)
+    B = rng.standard_normal((K, C)).astype(np.float32)
+    G = rng.standard_normal((n, C)).astype(np.float32)
+    At, Bt, Gt = (torch.from_numpy(x).cuda() for x in (A, B, G))
+    for got, X, Y in ((s.op_transform(At, Bt), A, B), (s.op_wgrad(At, Gt), A.T, G)):
+        ref = X.astype(np.float64) @ Y.astype(np.float64)
+        mag = np.abs(X).astype(np.float64) @ np.abs(Y).astype(np.float64)
+        assert (np.abs(got.cpu().numpy() - ref) / mag).max() < 2e-6
+
+
 @pytest.mark.parametrize("n,K,C", [(100, 37, 7), (70001, 37, 7), (50, 130, 16), (77, 5, 3)])
 def test_an_infinity_in_the_last_row_stays_an_infinity_in_narrow_products(ctx, n, K, C):
     """Steps past the end of the contraction repeat the last row of an operand: it must not meet the zeros of the other."""
