@@ -4,6 +4,7 @@
 #include <atomic>
 #include <condition_variable>
 #include <cstdint>
+#include <exception>
 #include <memory>
 #include <mutex>
 #include <thread>
@@ -28,12 +29,17 @@ template <class T> using HVec = std::vector<T, NoInitAlloc<T>>;
 // Threads are started once per pool (a parallel region that starts its own costs more than most of the regions here) and
 // spin briefly between regions before they sleep.  `work`: number of elementary steps of the whole call; a pool takes one
 // thread per 16384 of them, at most 16 and at most what the machine has, so that a small call stays on its caller's thread.
+// Where the system gives no more threads the pool works with those it has: the calls here are C entries, nothing may throw.
 class HostPool {
 public:
     explicit HostPool(int64_t work) {
         const int64_t hw = std::max(1u, std::thread::hardware_concurrency());
         const int n = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(hw, 16), work / 16384));
-        for (int w = 1; w < n; ++w) threads_.emplace_back([this, w] { loop(w); });
+        try {
+            threads_.reserve((size_t)n - 1);
+            for (int w = 1; w < n; ++w) threads_.emplace_back([this, w] { loop(w); });
+        } catch (const std::exception&) {   // std::system_error, std::bad_alloc
+        }
     }
     ~HostPool() {
         {

@@ -2,6 +2,8 @@
 (graph construction, argument checking) agrees bit for bit with the oracle's graph part.  No GPU call."""
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -136,3 +138,40 @@ def test_workspace_size_depends_on_the_shapes_alone(dims):
         s.tune("spmm_tile_cols", 0)
     assert len(sizes) == 1
     s.close()
+
+
+NO_THREADS = """
+import resource
+import numpy as np
+from paper_2112_09335_amd import binding, synth
+w = synth.config(2)
+def graph(comm):
+    s = binding.Solver(device=-1)
+    comm = s.partition(w.N, w.src, w.dst, w.M) if comm is None else comm
+    s.build_graph(w.N, w.src, w.dst, w.M, comm)
+    g = s.get_graph()
+    s.close()
+    return [comm] + [g[k] for k in sorted(g)]
+before = graph(w.comm) + graph(None)
+resource.setrlimit(resource.RLIMIT_AS, (int(open("/proc/self/statm").read().split()[0]) * 4096 + (256 << 20),) * 2)
+import ctypes
+libc = ctypes.CDLL(None)
+attr = ctypes.create_string_buffer(64)
+assert libc.pthread_attr_init(attr) == 0 and libc.pthread_attr_setstacksize(attr, ctypes.c_size_t(1 << 30)) == 0
+assert libc.pthread_setattr_default_np(attr) == 0            # stacks that do not fit the limit: no thread can start
+import threading
+try:
+    threading.Thread(target=int).start()
+    raise SystemExit("a thread started")
+except RuntimeError:
+    pass
+after = graph(w.comm) + graph(None)
+assert all(np.array_equal(a, b) for a, b in zip(before, after))
+print("same graph")
+"""
+
+
+def test_host_work_without_threads():
+    """Where no thread can be started the calls do their work on the caller's thread, with the same result."""
+    r = subprocess.run([sys.executable, "-c", NO_THREADS], cwd=ROOT, capture_output=True, text=True, timeout=100)
+    assert r.returncode == 0 and "same graph" in r.stdout, (r.returncode, r.stdout, r.stderr)
