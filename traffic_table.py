@@ -27,19 +27,19 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 CLASSES = {
     "spmm_rows_kernel[rows]": [("spmm_rows_kernel", "rows"), ("spmm_combine_kernel", "rows")],
     "spmm_rows_kernel[segments]": [("spmm_rows_kernel", "segments"), ("spmm_combine_kernel", "segments"), ("spmm_single_kernel", None)],
-    "gemm_nn_split_kernel<2>+finish": [(r"gemm_nn_split_kernel<2>", None)],
-    "gemm_nn_split_kernel<0>": [(r"gemm_nn_split_kernel<0>", None)],
+    "gemm_nn_split_kernel<2>+finish": [(r"gemm_nn_split_kernel<2,", None)],
+    "gemm_nn_split_kernel<0>": [(r"gemm_nn_split_kernel<0,", None)],
     "gemm_tn_split_kernel+reduce": [(r"gemm_tn_split_kernel", None)],
-    "gemm_nn_kernel<32>": [(r"gemm_nn_kernel<32, 0>", None)],
+    "gemm_nn_kernel<32>": [(r"gemm_nn_narrow_kernel<0,", None)],
     "gemm_tn_kernel<32>+reduce": [(r"gemm_tn_kernel<32", None)],
     "gemm_nn_gradz_kernel": [(r"gemm_nn_gradz_kernel", None)],
-    "z_trial_kernel": [(r"z_trial_kernel<1,", None)],
+    "z_trial_kernel": [(r"z_first_kernel", None)],
     "z_step_kernel": [(r"z_step(_lowrank)?_kernel", None)],
     "t_carry_kernel": [(r"t_carry_kernel", None)],
     "last_layer_kernel": [(r"last_layer_kernel", None)],
     "phi_G_kernel": [(r"phi_G_kernel<1,", None)],
     "G_only_kernel": [(r"G_only_kernel", None)],
-    "w_trial_kernel": [(r"w_trial_kernel<1, 1,", None)],
+    "w_trial_kernel": [(r"w_last_sums_kernel", None)],
     "w_step_kernel": [(r"w_step_kernel", None)],
 }
 
