@@ -81,18 +81,7 @@ __device__ __forceinline__ float4 fix_quad(int mode, float4 q, int c, int width)
     if (mode == kTail) return fix_quad<kTail>(q, c, width);
     return fix_quad<kNarrow>(q, c, width);
 }
-// up to four entries of a flat array of which `valid` (one to four) exist
-__device__ __forceinline__ void ld4u(float (&d)[4], const float* p, int valid) {
-    if (valid >= 4) {
-        const float4u v = *reinterpret_cast<const float4u*>(p);
-        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
-    } else {
-        d[0] = valid > 0 ? p[0] : 0.f;
-        d[1] = valid > 1 ? p[1] : 0.f;
-        d[2] = valid > 2 ? p[2] : 0.f;
-        d[3] = 0.f;
-    }
-}
+// stores up to four entries of a flat array of which `valid` (one to four) exist
 __device__ __forceinline__ void st4u(float* p, const float (&d)[4], int valid) {
     if (valid >= 4) {
         float4u v = {d[0], d[1], d[2], d[3]};
