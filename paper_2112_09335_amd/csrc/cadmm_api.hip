@@ -128,7 +128,7 @@ struct cadmm_ctx {
     int64_t large_readouts = 0;
     // optional per-kernel-class timing with HIP events on the context's stream
     bool prof_on = false;
-    struct ProfRec { int cls; hipEvent_t a, b; };
+    struct ProfRec { int cls; hipEvent_t a, b; double bytes, flops; };
     std::vector<ProfRec> prof_recs;
     std::vector<hipEvent_t> prof_pool;
     double prof_ms[CADMM_PROFILE_CLASSES] = {0};
@@ -370,9 +370,7 @@ void timed(cadmm_ctx* c, int cls, double bytes, double flops, F body) {
     body();
     if (a && b) {
         (void)hipEventRecord(b, c->stream);
-        c->prof_recs.push_back({cls, a, b});
-        c->prof_bytes[cls] += bytes;
-        c->prof_flops[cls] += flops;
+        c->prof_recs.push_back({cls, a, b, bytes, flops});
     }
 }
 
@@ -1415,6 +1413,7 @@ int cadmm_profile(cadmm_ctx* c, int enable) {
     if (c->device < 0) return fail(c, CADMM_EUNSUPPORTED, "host-only context");
     c->prof_on = enable != 0;
     if (enable) {
+        HIP_TRY(c, own_stream(c));               // (records of kernel-level calls are on the caller's stream)
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         for (auto& r : c->prof_recs) { c->prof_pool.push_back(r.a); c->prof_pool.push_back(r.b); }
         c->prof_recs.clear();
@@ -1428,13 +1427,21 @@ int cadmm_profile(cadmm_ctx* c, int enable) {
 int cadmm_get_profile(cadmm_ctx* c, double* ms, int64_t* records, double* bytes, double* flops) {
     if (!c) return CADMM_EINVAL;
     if (c->device < 0) return fail(c, CADMM_EUNSUPPORTED, "host-only context");
+    HIP_TRY(c, own_stream(c));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     for (auto& r : c->prof_recs) {
         float t = 0.f;
-        if (hipEventElapsedTime(&t, r.a, r.b) == hipSuccess) {
-            c->prof_ms[r.cls] += (double)t;
-            c->prof_launches[r.cls] += 1;
+        if (hipEventElapsedTime(&t, r.a, r.b) != hipSuccess) {
+            // (recorded into a capture: there is no time)
+            (void)hipGetLastError();
+            (void)hipEventDestroy(r.a);
+            (void)hipEventDestroy(r.b);
+            continue;
         }
+        c->prof_ms[r.cls] += (double)t;
+        c->prof_launches[r.cls] += 1;
+        c->prof_bytes[r.cls] += r.bytes;
+        c->prof_flops[r.cls] += r.flops;
         c->prof_pool.push_back(r.a);
         c->prof_pool.push_back(r.b);
     }

@@ -215,6 +215,32 @@ def test_calibration_kernels_report_a_rate(ctx):
     assert s.op_calibrate("mfma_bf16_valu6", 200, 3) > 1.0
 
 
+def test_profile_counts_kernel_calls_that_still_run_on_another_stream():
+    """Eight products of more than a millisecond each on torch's stream: collecting the records waits for them."""
+    import torch
+    from paper_2112_09335_amd import binding
+    n, K, C = 400000, 512, 512
+    s = binding.Solver(0)
+    try:
+        A, B = torch.zeros(n, K, device="cuda"), torch.zeros(K, C, device="cuda")
+        s.op_transform(A, B)
+        torch.cuda.synchronize()
+        for reset in (False, True):
+            s.profile(True)
+            for _ in range(8):
+                s.op_transform(A, B)
+            if reset:
+                s.profile(True)                      # clears what was enqueued before
+            rec = [r for r in s.get_profile().values() if r["records"]]
+            torch.cuda.synchronize()
+            assert sum(r["records"] for r in rec) == (0 if reset else 8)
+            if not reset:
+                assert rec[0]["ms"] > 0 and rec[0]["flops"] == 8 * 2.0 * n * K * C
+        s.profile(False)
+    finally:
+        s.close()
+
+
 def test_kernel_calls_are_ordered_with_the_sweep_and_can_be_captured():
     """A kernel-level call runs on torch's current stream, after the iterations enqueued before it and before those enqueued
     later (they share scratch memory), and inside a captured graph."""
