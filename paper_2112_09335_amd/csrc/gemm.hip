@@ -1214,24 +1214,25 @@ struct TnPlan {
     int tiles;
 };
 
-// The rows are cut into chunks so that the workgroups that the chip holds at once share the product: four per compute unit,
-// three for the 128 x 128 tiles with the prologue (their registers allow no more: 1024 of them ran as 768 and a second round
-// a third full, 191 against 172 us for 13752 x 767 x 1000).  Where a chunk would then be longer than 2048 rows there are 1024
-// all the same: the sums over its rows are in fp32, and longer ones would be less accurate.  A chunk has at least 64 rows,
-// and beyond 32 chunks the partial matrices stay below half the size of the operands.  They fit the scratch of the shape
-// (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
-constexpr int kTnBlocks = 1024, kTnBlocksPrologue = 768;
-TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
+// The rows are cut into chunks so that about 1024 workgroups share the product, four per compute unit.  A chunk has at
+// least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.  The sums over a
+// chunk's rows are in fp32, their error grows with its length: whatever the tile and these limits ask for, there are no
+// fewer chunks than at the base (128-row tiles, 256 rows).  Longer chunks would be faster with the prologue, whose
+// registers let the chip hold 768 workgroups and not 1024, but not as accurate: 13752 x 767 x 1000 in 864 rows 157 us and
+// 4.6e-7 of the 64-bit product, in 640 rows 182 us and 3.9e-7; 16956 x 476 x 347 in 784 rows 83 us and 4.4e-7, in 256 rows
+// 76 us and 2.6e-7.  They fit the scratch of the shape (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
+constexpr int kTnBlocks = 1024;
+TnPlan tn_plan(int64_t n, int K, int C) {
     TnPlan p;
+    const int64_t base_chunks = (int64_t)gemm_tn_base_floats(n, K, C) / ((int64_t)K * C);
     auto plan = [&](int bm, int bn) {
         p.bn = bn;
         p.tiles = ((K + bm - 1) / bm) * ((C + bn - 1) / bn);
-        const bool fewer = prologue && bn == 128 && n * p.tiles / kTnBlocksPrologue <= 2048;
-        int64_t nch = fewer ? std::max(1, kTnBlocksPrologue / p.tiles) : (kTnBlocks + p.tiles - 1) / p.tiles;
+        int64_t nch = (kTnBlocks + p.tiles - 1) / p.tiles;
         nch = std::min(nch, (n + 63) / 64);
         nch = std::min(nch, std::max<int64_t>(32, n * (K + C) / (2 * (int64_t)K * C)));
         nch = std::min(nch, (int64_t)gemm_tn_scratch_floats(n, K, C) / ((int64_t)K * C));
-        if (nch < 1) nch = 1;
+        nch = std::max(nch, base_chunks);
         int64_t rpc = (n + nch - 1) / nch;
         rpc = (rpc + BK - 1) / BK * BK;
         p.rows_per_chunk = rpc;
@@ -1310,7 +1311,7 @@ int64_t gemm_nn_blocks(int64_t n, int C) {
 int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
                    float* partial, const float* Zl, float nu, const float* W, double* norms) {
     if (K <= 0 || C <= 0) return 0;
-    TnPlan p = tn_plan(n, K, C, Zl != nullptr);
+    TnPlan p = tn_plan(n, K, C);
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.tiles)), block(256);
 #define CADMM_TN(KERNEL_) hipLaunchKernelGGL(KERNEL_, grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk)
     if (p.bn == 64) {

@@ -206,6 +206,54 @@ def test_an_infinity_in_the_last_row_stays_an_infinity_in_narrow_products(ctx, n
     assert torch.equal(s.op_wgrad_noalloc(A, G), want)
 
 
+def base_chunk_rows(n, K, C):
+    """Rows per chunk of the W-gradient product at its base: about 1024 workgroups of 128-row tiles, at least 256 rows."""
+    tiles = -(-K // 128) * -(-C // (128 if C > 32 else 32))
+    chunks = max(1, min(-(-1024 // tiles), -(-n // 256)))
+    return -(-(-(-n // chunks)) // 16) * 16
+
+
+# 48 and 49 tiles, the limit on the partial matrices (512 x 512), 64-row tiles (476 x 347, 500 x 128), narrow results
+FP32_SUM_SHAPES = [(13752, 767, 1000), (32114, 896, 896), (20000, 512, 512), (16956, 476, 347), (20000, 500, 128), (5000, 100, 20)]
+
+
+@pytest.mark.parametrize("split", [1, 0])
+@pytest.mark.parametrize("n,K,C", FP32_SUM_SHAPES)
+def test_fp32_sums_of_the_wgrad_product_are_no_longer_than_a_base_chunk(n, K, C, split):
+    """Chunks are added in fp64, so how many rows are summed in fp32 can be counted: 2^29 in the first row swallows the ones
+    behind it (half a unit in its last place is 32, sixteen rows are added at a time) until the chunk ends.  -2^29 in the last row brings
+    the sum back to a small whole number; the chunk it closes is rounded once, by at most 32."""
+    import torch
+    from paper_2112_09335_amd import binding
+    say("fp32 sums", n, K, C, split)
+    s = binding.Solver(0)
+    s.tune("gemm_split", split)                      # process-wide
+    try:
+        A, G = torch.ones(n, K, device="cuda"), torch.ones(n, C, device="cuda")
+        G[0] = 2.0 ** 29
+        G[n - 1] = -2.0 ** 29
+        lost = n - 2 - s.op_wgrad_noalloc(A, G)
+        assert lost.abs().max().item() <= base_chunk_rows(n, K, C) + 32
+        # the same through the hidden-layer prologue: a graph without edges (A~ = 1), T_1 = 1 everywhere and nu = 1 make
+        # nu (T_1 - Z_1) those numbers, and the search reports the squared norm of their sums
+        s.build_graph(n, np.zeros(0, np.int32), np.zeros(0, np.int32), 1, None)
+        s.set_model([K, C, 3], **dict(HYPER, nu=1.0))
+        s.set_workspace()
+        s.set_data(np.ones((n, K), np.float32), np.zeros(n, np.int32))
+        W1 = np.zeros((K, C), np.float32)
+        W1[0] = 1.0
+        s.init([W1, np.zeros((C, 3), np.float32)])
+        Z1 = np.zeros((n, C), np.float32)
+        Z1[0], Z1[n - 1] = -2.0 ** 29, 2.0 ** 29
+        s.set_state(Z=[Z1, None])
+        s.run(1)
+        lost = n - 2 - (s.get_steps()[3][0] / (K * C)) ** 0.5
+        assert abs(lost) <= base_chunk_rows(n, K, C) + 32
+    finally:
+        s.tune("gemm_split", 1)
+        s.close()
+
+
 def test_calibration_kernels_report_a_rate(ctx):
     s, g, torch = ctx
     assert s.op_calibrate("copy", 1 << 22, 3) > 10.0        # GB/s
