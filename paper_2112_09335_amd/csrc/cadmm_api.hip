@@ -1480,7 +1480,8 @@ int cadmm_tune(cadmm_ctx* c, const char* key, int32_t value) {
         drop_graphs(c);
         return CADMM_OK;
     }
-    if (std::strcmp(key, "spmm_tile_cols") == 0) { set_spmm_tile_cols(value); return CADMM_OK; }
+    // process-wide, and part of a captured launch as well
+    if (std::strcmp(key, "spmm_tile_cols") == 0) { set_spmm_tile_cols(value); drop_graphs(c); return CADMM_OK; }
     if (std::strcmp(key, "spmm_xcd_remap") == 0) { set_spmm_xcd_remap(value); drop_graphs(c); return CADMM_OK; }
     return fail(c, CADMM_EINVAL, "unknown tuning key");
 }

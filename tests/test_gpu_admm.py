@@ -157,6 +157,30 @@ def test_graph_replay_equals_plain_launches_bit_for_bit():
     b.close()
 
 
+def test_the_column_tile_knob_reaches_captured_iterations():
+    """The tile width decides the order of an aggregation's sums and who leaves the row sums of the Z search: iterations
+    captured before the knob was turned must not be replayed after it."""
+    import torch
+    from paper_2112_09335_amd import binding
+    w = synth.config(3, 0.01)
+    a, b = binding.Solver.from_workload(w, 0), binding.Solver.from_workload(w, 0)
+    b.tune("use_graph", 0)
+    try:
+        X = torch.randn(w.N, 256, device="cuda")
+        whole = a.op_aggregate(X)
+        for tile in (0, 32, 0):
+            a.tune("spmm_tile_cols", tile)               # process-wide: b follows
+            assert torch.equal(a.op_aggregate(X), whole) == (tile == 0)
+            a.run(3)
+            b.run(3)
+            for l in range(1, w.L + 1):
+                assert np.array_equal(a.get_W(l), b.get_W(l)) and np.array_equal(a.get_Z(l), b.get_Z(l)), (tile, l)
+    finally:
+        a.tune("spmm_tile_cols", 0)
+        a.close()
+        b.close()
+
+
 def test_inference_matches_the_oracle_between_iterations():
     from paper_2112_09335_amd import binding
     w = synth.config(3, 0.01)
