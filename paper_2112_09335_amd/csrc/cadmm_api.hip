@@ -115,9 +115,9 @@ struct cadmm_ctx {
     struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false; };
     GraphSlot graphs[32];
     // Kernel-level calls on a stream of the caller's (cadmm_op_stream): such a call is launched there, after what the context's
-    // own stream holds (own_busy: something may still run on it) and after kernel-level calls on other streams; whatever uses
+    // own stream holds (own_busy: something may still run on it) and after the kernel-level call before it; whatever uses
     // the own stream next waits for it (op_busy).
-    hipStream_t op_stream = nullptr, op_last = nullptr;
+    hipStream_t op_stream = nullptr;
     bool op_stream_set = false, op_busy = false, own_busy = false;
     hipEvent_t ev_own = nullptr, ev_op = nullptr;
     // pinned host memory, allocated when first needed and freed with the context: two pieces through which large transfers
@@ -907,7 +907,8 @@ int on_op_stream(cadmm_ctx* c, const char* what, F body) {
         HIP_TRY(c, hipEventRecord(c->ev_own, c->stream));
         HIP_TRY(c, hipStreamWaitEvent(c->op_stream, c->ev_own, 0));
     }
-    if (c->op_busy && c->op_last != c->op_stream) HIP_TRY(c, hipStreamWaitEvent(c->op_stream, c->ev_op, 0));
+    // (also where the handles are equal: a stream may have got the address of one that was destroyed)
+    if (c->op_busy) HIP_TRY(c, hipStreamWaitEvent(c->op_stream, c->ev_op, 0));
     const hipStream_t own = c->stream;
     c->stream = c->op_stream;
     body();
@@ -915,7 +916,6 @@ int on_op_stream(cadmm_ctx* c, const char* what, F body) {
     HIP_TRY(c, hipEventRecord(c->ev_op, c->op_stream));
     c->own_busy = false;             // what the own stream held comes before what this stream holds now
     c->op_busy = true;
-    c->op_last = c->op_stream;
     return check_launch(c, what);
 }
 

@@ -70,6 +70,27 @@ def test_aggregate_with_hub_rows_and_column_tiles(hub_ctx, width, tile):
     assert rel_err(P, (S @ X.astype(np.float64))[s.get_segment_order()]) < 3e-6
 
 
+def test_kernel_calls_on_a_stream_that_takes_the_place_of_a_destroyed_one(hub_ctx):
+    """The runtime may give a new stream the handle of a destroyed one whose work still runs; the calls share the buffer of
+    split rows, so the second must wait for the first."""
+    import ctypes
+    s, g, torch = hub_ctx
+    X = [torch.randn(g.N, 300, device="cuda") for _ in range(4)]
+    want = [s.op_aggregate(x) for x in X]
+    Y = [torch.empty_like(x) for x in X]
+    torch.cuda.synchronize()
+    for x, y in zip(X, Y):
+        stream = ctypes.c_void_p()
+        assert s.lib.hipStreamCreate(ctypes.byref(stream)) == 0
+        assert s.lib.cadmm_op_stream(s.h, stream) == 0
+        for _ in range(20):
+            assert s.lib.cadmm_op_aggregate(s.h, x.data_ptr(), 300, y.data_ptr()) == 0
+        assert s.lib.hipStreamDestroy(stream) == 0
+    torch.cuda.synchronize()
+    for y, w in zip(Y, want):
+        assert torch.equal(y, w)
+
+
 def rel_err(got, ref):
     return float(np.abs(got - ref).max() / max(np.abs(ref).max(), 1e-300))
 
