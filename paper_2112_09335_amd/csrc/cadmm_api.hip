@@ -870,6 +870,13 @@ int upload_rows(cadmm_ctx* c, const float* src, int on_device, int C, float* dst
 // Called by everything that enqueues on the context's own stream.
 hipError_t own_stream(cadmm_ctx* c) {
     if (!c->op_busy) return hipSuccess;
+    // A capture cannot wait for work outside of it, and what runs next on the stream itself still has to.
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->stream) {
+        const hipError_t e = hipStreamIsCapturing(c->stream, &cap);
+        if (e != hipSuccess) return e;
+    }
+    if (cap != hipStreamCaptureStatusNone) return hipSuccess;
     c->op_busy = false;
     return hipStreamWaitEvent(c->stream, c->ev_op, 0);
 }

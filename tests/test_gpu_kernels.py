@@ -350,3 +350,41 @@ def test_kernel_calls_are_ordered_with_the_sweep_and_can_be_captured():
     finally:
         a.close()
         b.close()
+
+
+def test_a_capture_of_the_own_stream_leaves_the_order_of_the_calls_around_it():
+    """A call on torch's stream still runs while the context's own stream is captured; what the own stream does after the
+    capture waits for that call, and replays give the eager result."""
+    import torch
+    from paper_2112_09335_amd import binding
+    w = synth.config(2, 0.1)
+    a, b = binding.Solver.from_workload(w, 0), binding.Solver.from_workload(w, 0)
+    try:
+        X, G, out = torch.randn(w.N, 500, device="cuda"), torch.randn(w.N, 128, device="cuda"), torch.empty(500, 128, device="cuda")
+        want = b.op_wgrad(X, G)
+        torch.cuda.synchronize()
+        a.run(1)
+        for _ in range(50):
+            got = a.op_wgrad(X, G)                       # (shares the scratch of the partial matrices with the sweep)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(a.stream):
+            graph.capture_begin()
+            a.op_wgrad_noalloc(X, G, out)
+            graph.capture_end()
+        a.run(2)
+        b.run(3)
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+        for l in range(1, w.L + 1):
+            assert np.array_equal(a.get_W(l), b.get_W(l)) and np.array_equal(a.get_Z(l), b.get_Z(l))
+        for k in range(3):
+            X.mul_(1.5)
+            eager = b.op_wgrad_noalloc(X, G)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, eager), k
+            a.run(1)
+    finally:
+        a.close()
+        b.close()
