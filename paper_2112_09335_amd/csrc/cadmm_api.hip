@@ -877,8 +877,11 @@ hipError_t own_stream(cadmm_ctx* c) {
         if (e != hipSuccess) return e;
     }
     if (cap != hipStreamCaptureStatusNone) return hipSuccess;
+    const hipError_t e = hipStreamWaitEvent(c->stream, c->ev_op, 0);
+    if (e != hipSuccess) return e;
     c->op_busy = false;
-    return hipStreamWaitEvent(c->stream, c->ev_op, 0);
+    c->own_busy = true;              // (also where the caller is refused after this and enqueues nothing itself)
+    return hipSuccess;
 }
 
 // Runs a kernel-level call on the stream chosen by cadmm_op_stream.  Launching there, instead of on the context's stream with

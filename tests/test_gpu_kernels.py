@@ -388,3 +388,29 @@ def test_a_capture_of_the_own_stream_leaves_the_order_of_the_calls_around_it():
     finally:
         a.close()
         b.close()
+
+
+def test_a_refused_call_between_kernel_calls_on_two_streams_keeps_their_order():
+    """set_data makes the own stream wait for the call before it, then refuses the labels and enqueues nothing: a call on a
+    third stream still waits for the one on the first, with which it shares the scratch of the partial matrices."""
+    import torch
+    from paper_2112_09335_amd import binding
+    w = synth.config(2, 0.1)
+    s = binding.Solver.from_workload(w, 0)
+    try:
+        X = [torch.randn(w.N, 500, device="cuda") for _ in range(2)]
+        G = [torch.randn(w.N, 128, device="cuda") for _ in range(2)]
+        want = [s.op_wgrad(x, g) for x, g in zip(X, G)]
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        for _ in range(5):
+            for _ in range(50):
+                first = s.op_wgrad(X[0], G[0])
+            with pytest.raises(binding.CadmmError):
+                s.set_data(w.X, np.full(w.N, w.dims[-1], np.int32))
+            with torch.cuda.stream(side):
+                second = s.op_wgrad(X[1], G[1])
+            torch.cuda.synchronize()
+            assert torch.equal(first, want[0]) and torch.equal(second, want[1])
+    finally:
+        s.close()
