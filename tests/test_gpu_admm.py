@@ -93,6 +93,14 @@ def test_ragged_widths_across_column_tiles(dims, more):
     run_case(w, 4, "ragged-wide/" + "-".join(map(str, dims)))
 
 
+def copies(w, n):
+    """n disjoint copies of a workload: every copy goes through the same values, so a workload of any size has the ReLU ties
+    of a small one."""
+    at = np.repeat(np.arange(n, dtype=np.int64) * w.N, w.E)
+    return synth.Workload(w.name, w.N * n, w.M, (np.tile(w.src, n) + at).astype(np.int32), (np.tile(w.dst, n) + at).astype(np.int32),
+                          np.tile(w.comm, n), np.tile(w.X, (n, 1)), np.tile(w.labels, n), w.dims, w.W0, w.iters, dict(w.hyper))
+
+
 def test_backtracking_cap_status_and_resume_are_consistent():
     from paper_2112_09335_amd import binding
     w = synth.config(1, 0.5)
@@ -352,6 +360,11 @@ def test_last_layer_by_fista_with_backtracking():
     w.hyper["fista_mode"] = 1
     w.hyper["schedule"] = 1
     run_case(w, 4, "fista-backtracking/40-classes/layer-by-layer")
+    # from 300000 entries of Z_L on a step starts with one candidate, and four more follow where it fails
+    w = copies(synth.make_workload("many-rows", 42, 101, 3, [12, 16, 10], 10, 4, graph="sbm", features="gaussian", avg_degree=8,
+                                   frac_intra=0.7), 300)
+    w.hyper["fista_mode"] = 1
+    run_case(w, 4, "fista-backtracking/many-rows")
 
 
 def test_more_communities_than_a_workgroup_keeps_step_parameters_for():
