@@ -86,7 +86,7 @@ def test_unlabelled_nodes_least_squares_risk_one_community_and_ragged_sizes():
                                        ([67, 49, 261, 3], {"schedule": 1, "fista_mode": 1})])
 def test_ragged_widths_across_column_tiles(dims, more):
     """Widths that are no multiple of four on both sides of the narrow-side rule: the searches' row sums are left by the
-    aggregation, the product or the gradient kernel, with a partial last quad and a partial last tile."""
+    64-column product over several tiles or by the aggregation in one tile, with a partial last quad in either."""
     w = synth.make_workload("ragged-wide", 21 + len(more), 1501, 5, dims, dims[-1], 4, graph="sbm", features="gaussian",
                             avg_degree=9, frac_intra=0.8, labelled_fraction=0.4)
     w.hyper.update(more)
@@ -99,6 +99,16 @@ def copies(w, n):
     at = np.repeat(np.arange(n, dtype=np.int64) * w.N, w.E)
     return synth.Workload(w.name, w.N * n, w.M, (np.tile(w.src, n) + at).astype(np.int32), (np.tile(w.dst, n) + at).astype(np.int32),
                           np.tile(w.comm, n), np.tile(w.X, (n, 1)), np.tile(w.labels, n), w.dims, w.W0, w.iters, dict(w.hyper))
+
+
+@pytest.mark.parametrize("dims", [[24, 133, 46, 5], [24, 136, 48, 5]])
+def test_many_rows_reach_the_128_column_products(dims):
+    """From 512 tiles of 128 x 128 on: the first trial of tau_1 with its step, and the gradient of Z_1 with its row sums over
+    a whole and a partial column tile, at widths with and without a partial last quad."""
+    w = copies(synth.make_workload("many-rows", 41, 101, 3, dims, dims[-1], 4, graph="sbm", features="gaussian", avg_degree=8,
+                                   frac_intra=0.7), 325)
+    assert -(-w.N // 128) * -(-dims[1] // 128) >= 512
+    run_case(w, 6, "many-rows/" + "-".join(map(str, dims)))
 
 
 def test_backtracking_cap_status_and_resume_are_consistent():
@@ -231,6 +241,9 @@ def test_low_rank_gradient_path_and_its_stored_twin():
     w = synth.make_workload("lowrank", 21, 1500, 6, [36, 48, 12, 4], 4, 6, graph="sbm", features="gaussian",
                             avg_degree=9, frac_intra=0.8)
     run_case(w, 6, "low-rank")
+    # the gradient kernel takes 32 columns at a time: a last step of four own columns, the factor's and zeros
+    run_case(synth.make_workload("lowrank", 22, 1500, 6, [36, 100, 12, 4], 4, 5, graph="sbm", features="gaussian",
+                                 avg_degree=9, frac_intra=0.8), 5, "low-rank/partial-step")
     a = binding.Solver.from_workload(w, 0)
     b = binding.Solver.from_workload(w, 0)
     b.tune("use_lowrank", 0)
@@ -306,6 +319,11 @@ def test_hub_rows_and_hub_segments_are_split_inside_the_sweep():
     base = synth.make_workload("hub", 33, 2000, 4, [20, 30, 30, 5], 5, 6, graph="sbm", features="gaussian",
                                avg_degree=8, frac_intra=0.8)
     run_case(synth.add_hubs(base, 34, 2, 600, 0.7), 5, "hubs/odd-widths")
+    # an aggregated gradient of two column tiles, the second one of five columns: the row sums come tile by tile from the
+    # aggregation, and those of the split rows from the combine kernel, all in the first tile's place
+    base = synth.make_workload("hub", 37, 1500, 4, [20, 261, 300, 5], 5, 4, graph="sbm", features="gaussian",
+                               avg_degree=8, frac_intra=0.8)
+    run_case(synth.add_hubs(base, 38, 3, 600, 0.7), 3, "hubs/two-column-tiles")
     # two layers, narrow last layer: low-rank gradient and narrow-side association of layer 2 on hub rows
     base = synth.make_workload("hub", 35, 2400, 6, [24, 40, 8], 8, 6, graph="dcsbm", features="gaussian",
                                avg_degree=10, frac_intra=0.8, exponent=2.5)
