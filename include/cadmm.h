@@ -201,7 +201,9 @@ int  cadmm_set_state(cadmm_ctx* ctx, const float* const* W, const float* const* 
  *   transform:           out = A B        A device n x K, B device K x C, out n x C
  *   wgrad:               out = A^T G      A device n x K, G device n x C, out K x C
  * They run on the context's stream, or on the one named by cadmm_op_stream (NULL = the default stream): there, in the order
- * of the calls, after everything the context has enqueued before and before everything it enqueues later.
+ * of the calls, after everything the context has enqueued before and before everything it enqueues later.  A call on a
+ * stream that is being captured is ordered inside the captured graph; a replay of that graph is the caller's to order
+ * against the context (aggregate, aggregate_segments and wgrad use scratch of the workspace, as the iterations do).
  */
 int  cadmm_op_stream(cadmm_ctx* ctx, void* hip_stream);
 int  cadmm_op_aggregate(cadmm_ctx* ctx, const float* X, int32_t width, float* Y);
@@ -214,7 +216,7 @@ int  cadmm_op_wgrad(cadmm_ctx* ctx, const float* A, const float* G, int64_t n, i
 /*
  * cadmm_op_wgrad for callers that cannot allocate device memory or hand over a workspace: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels and the same result bit for bit as
- * cadmm_op_wgrad (out = A^T G, A device n x K, G device n x C, out device K x C, enqueued on the context's stream),
+ * cadmm_op_wgrad (out = A^T G, A device n x K, G device n x C, out device K x C, on the stream of the kernel-level calls),
  * but the per-chunk partial matrices of the product live in a static device array inside the library (72 MiB on every
  * GPU the library runs on, held until the process ends) instead of the workspace, so the call works on a context
  * that has no graph, model or workspace yet and calls no allocating routine.  Shapes whose partial matrices need more
@@ -251,7 +253,7 @@ int  cadmm_op_calibrate(cadmm_ctx* ctx, int32_t kind, const float* src, float* d
 /*
  * Per-kernel-class timing for benchmarks (no counterpart in the paper).  cadmm_profile(ctx, 1) clears
  * the counters and makes every later launch group be bracketed by a pair of HIP events on the
- * context's stream; cadmm_profile(ctx, 0) stops that.  cadmm_get_profile synchronises and returns,
+ * stream it runs on; cadmm_profile(ctx, 0) stops that.  cadmm_get_profile synchronises and returns,
  * per class (host arrays of CADMM_PROFILE_CLASSES entries, any may be NULL): elapsed milliseconds,
  * number of timed launch groups, and the algorithmic bytes and flops booked for them (what the
  * operation must move / compute: operands read once, results written once).

@@ -8,9 +8,10 @@
 // partial sums, a finishing kernel adds them in index order, so results are reproducible run to run.
 //
 // A step-size search is a sequence of passes enqueued by the host without reading anything back: a pass
-// evaluates up to kMaxCand candidates step*eta^j in one sweep over memory, the finishing kernel picks the
-// first that passes the test  value(step) - value(0) <= -||grad||^2 / (2 step)  and marks the search
-// done; later passes see the flag and return at once.
+// evaluates one, four or up to kRestCand candidates step*eta^j (kMaxCand of them per sweep over memory; all
+// of them by two sums where the change is quadratic in 1/step), the finishing kernel picks the first that
+// passes the test  value(step) - value(0) <= -||grad||^2 / (2 step)  and marks the search done; later passes
+// see the flag and return at once.
 #include <type_traits>
 
 #include "kernels.h"

@@ -45,11 +45,11 @@ struct SpmmSchedule {
 int spmm_tiles(const SpmmSchedule& sched, int width);          // column tiles of such a launch (width >= 4)
 int spmm_default_tiles(const SpmmSchedule& sched, int width);  // the same without the tuned tile width
 void launch_spmm(hipStream_t s, const SpmmSchedule& sched, const float* X, float* Y, int width, const SpmmEpilogue& epi);
-// Y[pos[k], :] = val[k] * X[col[k], :] for k < n: the output rows that have a single entry.
 // calibration: only the gathers of the row list's column stream, rows of `width` floats (4, 8, 16, ... 256) of X;
 // out: 256 floats (never written in practice); returns the bytes the launch asks the memory system for
 double launch_gather_calibration(hipStream_t s, const SpmmSchedule& sc, int64_t n_chunks, const float* X, int width,
                                  float* out);
+// Y[pos[k], :] = val[k] * X[col[k], :] for k < n: the output rows that have a single entry.
 void launch_spmm_single(hipStream_t s, const int32_t* pos, const int32_t* col, const float* val, const float* X,
                         float* Y, int64_t n, int width);
 // columns of the feature matrix handled at a time, if fewer than the launch's own choice (0 = that choice); smaller tiles

@@ -361,8 +361,10 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
 // are what an XCD's 4 MB L2 would have to hold for those gathers to hit.  Columns are halved from 256 (a whole wavefront
 // of 16-byte loads per gathered row, which is also the most the kernel takes) until that fits, down to 32: the
 // requests of narrower rows cost the L2 as much as those of 128 bytes, and the entries are read once more per tile.
-// Measured per pass over the rows, tiled against untiled: 200000 nodes in 32 communities, width 512: 563 against 766 us
-// (128 columns); 500000 in 16, width 512: 1459 against 1980 us (32 columns); 13752 in 3, width 1000: 180 against 222 us (256).
+// Measured per pass over the rows, chosen tile against 256 columns: 200000 nodes in 32 communities, width 512: 535 against
+// 575 us (128 columns); 500000 in 16, width 512: 1381 against 1787 us (32 columns); 13752 in 3, width 1000: 129 against 172 us
+// (128).  At 4.1e6 bytes for 256 columns, just below the line, 64000 nodes in 16, width 512, take 141 us so and 147 in tiles of
+// 128, but 12000 in 3, width 1000, 138 and 109.
 int tile_of(const SpmmSchedule& sc, int width, int vec, int most) {
     int tile = 64 * vec;
     while (tile > 32 && 4.0 * tile * sc.group_rows > 4.5e6) tile >>= 1;
