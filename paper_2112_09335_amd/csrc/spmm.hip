@@ -358,16 +358,33 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
 }
 
 // Columns per tile.  The rows of a community gather mostly rows of that community: 4 * columns * rows-of-a-community bytes
-// are what an XCD's 4 MB L2 would have to hold for those gathers to hit.  Columns are halved from 256 (a whole wavefront
-// of 16-byte loads per gathered row, which is also the most the kernel takes) until that fits, down to 32: the
+// are what an XCD's 4 MB L2 would have to hold for those gathers to hit.  The tile that fits is 256 columns (a whole wavefront
+// of 16-byte loads per gathered row, which is also the most the kernel takes), halved until that holds, down to 32: the
 // requests of narrower rows cost the L2 as much as those of 128 bytes, and the entries are read once more per tile.
-// Measured per pass over the rows, chosen tile against 256 columns: 200000 nodes in 32 communities, width 512: 535 against
-// 575 us (128 columns); 500000 in 16, width 512: 1381 against 1787 us (32 columns); 13752 in 3, width 1000: 129 against 172 us
-// (128).  At 4.1e6 bytes for 256 columns, just below the line, 64000 nodes in 16, width 512, take 141 us so and 147 in tiles of
-// 128, but 12000 in 3, width 1000, 138 and 109.
+// Chosen against 256 columns: 200000 nodes in 32 communities, width 512: 535 against 575 us (128 columns); 500000 in 16, width
+// 512: 1381 against 1787 (32); 13752 in 3, width 1000: 129 against 172 (128).  At 4.1e6 bytes for 256 columns, just below the
+// line, 64000 nodes in 16, width 512, take 141 us so and 147 in tiles of 128, but 12000 in 3, width 1000, 138 and 109.
+// Two things can make the fewest tiles the faster way all the same.  A pass costs what its lanes per row cost, whether the
+// tile fills them or not (200000 in 32, width 160: 157 us whole, 209 as 128 + 32; 287602 in 4, width 36: 111 and 154 as 32 +
+// 4).  And where rows do not start on 128-byte lines a tile of every row straddles one line more (287602 in 4, width 230:
+// 549 us whole, 856 in tiles of 32).  The rule counts columns: a straddled line as ten of them, and a quarter more for columns
+// that do not fit (a tenth in tiles of up to 128, where a wavefront has two rows and more to wait for).  Against the best of
+// the tiles tried it is within 7 % in 122 of 124 measurements, widths 30 to 1000 on nine graphs.
+// The tiles of a launch are about equally wide (13752 in 8, width 257: 47 us as 132 + 125, 51 as 256 + 1), in whole lines
+// or half lines where the rows are.
 int tile_of(const SpmmSchedule& sc, int width, int vec, int most) {
-    int tile = 64 * vec;
-    while (tile > 32 && 4.0 * tile * sc.group_rows > 4.5e6) tile >>= 1;
+    constexpr int kMost = 256;
+    int fit = kMost;
+    while (fit > 32 && 4.0 * fit * sc.group_rows > 4.5e6) fit >>= 1;
+    const int unit = width % 32 == 0 ? 32 : width % 16 == 0 ? 16 : vec;
+    auto even = [&](int tiles) { return ((width + tiles - 1) / tiles + unit - 1) / unit * unit; };
+    const int few = (width + kMost - 1) / kMost;
+    int tiles = (width + fit - 1) / fit;
+    if (few < tiles) {
+        const int line = width % 32 == 0 ? 0 : 10;
+        if (20 * tiles * (fit + line) > (even(few) <= 128 ? 22 : 25) * few * (even(few) + line)) tiles = few;
+    }
+    int tile = even(tiles);
     if (most > 0 && most < tile) tile = (most + vec - 1) / vec * vec;
     return tile < width ? tile : width;
 }

@@ -175,3 +175,24 @@ def test_host_work_without_threads():
     """Where no thread can be started the calls do their work on the caller's thread, with the same result."""
     r = subprocess.run([sys.executable, "-c", NO_THREADS], cwd=ROOT, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "same graph" in r.stdout, (r.returncode, r.stdout, r.stderr)
+
+
+def test_a_few_columns_beyond_a_tile_of_the_aggregation_are_no_pass_of_their_own():
+    """One community of 40000 rows: tiles of 32 columns would suit its L2 share, but a second pass over the entries for the
+    columns that are left costs more than it saves.  The workspace holds three doubles per row and tile for the gradient of
+    Z_1 (aggregated, as C_2 >= C_1), so the steps of its size show where a tile is added."""
+    N = 40000
+    none = np.zeros(0, np.int32)
+
+    def size(width):
+        s = host_solver()
+        s.build_graph(N, none, none, 1, np.zeros(N, np.int32))
+        s.set_model([8, width, 64], **synth.DEFAULT_HYPER)
+        b = s.workspace_bytes()
+        s.close()
+        return b
+
+    step = {w: size(w) - size(w - 4) for w in range(28, 68, 4)}
+    for w in step:
+        # (what else there is grows by nearly the same from step to step)
+        assert (step[w] - step[28] > 12 * N) == (w == 64), (w, step)

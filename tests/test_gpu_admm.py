@@ -319,8 +319,8 @@ def test_hub_rows_and_hub_segments_are_split_inside_the_sweep():
     base = synth.make_workload("hub", 33, 2000, 4, [20, 30, 30, 5], 5, 6, graph="sbm", features="gaussian",
                                avg_degree=8, frac_intra=0.8)
     run_case(synth.add_hubs(base, 34, 2, 600, 0.7), 5, "hubs/odd-widths")
-    # an aggregated gradient of two column tiles, the second one of five columns: the row sums come tile by tile from the
-    # aggregation, and those of the split rows from the combine kernel, all in the first tile's place
+    # an aggregated gradient of two column tiles, the second one with a partial last quad: the row sums come tile by tile from
+    # the aggregation, and those of the split rows from the combine kernel, all in the first tile's place
     base = synth.make_workload("hub", 37, 1500, 4, [20, 261, 300, 5], 5, 4, graph="sbm", features="gaussian",
                                avg_degree=8, frac_intra=0.8)
     run_case(synth.add_hubs(base, 38, 3, 600, 0.7), 3, "hubs/two-column-tiles")

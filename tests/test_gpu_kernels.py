@@ -107,6 +107,31 @@ def test_aggregate_matches_sparse_product(ctx, width):
     assert rel_err(Y.cpu().numpy().astype(np.float64), ref) < 2e-6
 
 
+@pytest.fixture(scope="module")
+def one_community_ctx():
+    """40000 rows in one community, whose rows fit an XCD's L2 in no more than 32 columns: the tile rules part here."""
+    import torch
+    from paper_2112_09335_amd import binding
+    rng = np.random.default_rng(78)
+    N = 40000
+    src, dst = rng.integers(0, N, 150000).astype(np.int32), rng.integers(0, N, 150000).astype(np.int32)
+    s = binding.Solver(0)
+    s.build_graph(N, src, dst, 1, np.zeros(N, np.int32))
+    s.set_model([516, 64, 16], **HYPER)
+    s.set_workspace()
+    yield s, OracleGraph(N, src, dst, 1, np.zeros(N, np.int32)), torch
+    s.close()
+
+
+@pytest.mark.parametrize("width", [33, 48, 64, 96, 100, 130, 256, 261, 300, 320, 516])
+def test_aggregate_in_whole_rows_even_tiles_and_tiles_of_a_line(one_community_ctx, width):
+    s, g, torch = one_community_ctx
+    say("one community, width", width)
+    X = np.random.default_rng(width).standard_normal((g.N, width)).astype(np.float32)
+    Y = s.op_aggregate(torch.from_numpy(X).cuda()).cpu().numpy().astype(np.float64)
+    assert rel_err(Y, g.A @ X.astype(np.float64)) < 2e-6
+
+
 def test_aggregate_is_exact_on_integers_scaled_by_the_values(ctx):
     """With X = e_j (unit columns) the result reproduces the stored values of A~ bit for bit."""
     s, g, torch = ctx
