@@ -791,6 +791,17 @@ int check_launch(cadmm_ctx* c, const char* where) {
     return CADMM_OK;
 }
 
+// An event for the context's streams: of the context's device, whichever is current for the calling thread.
+hipError_t make_event(cadmm_ctx* c, hipEvent_t* e) {
+    int current = c->device;
+    hipError_t r = hipGetDevice(&current);
+    if (r == hipSuccess && current != c->device) r = hipSetDevice(c->device);
+    if (r == hipSuccess) r = hipEventCreateWithFlags(e, hipEventDisableTiming);
+    if (r != hipSuccess) *e = nullptr;
+    if (current != c->device) (void)hipSetDevice(current);
+    return r;
+}
+
 // Large readouts into pageable memory go through two pinned pieces: the DMA of one runs while host threads copy the other
 // out.  The runtime's own path is one thread, which also takes the page faults of a fresh destination: 128 MB came out in
 // 12 ms, now in 4.  From kStageMin on the pieces pay once they are there (8 MB: 0.2 ms less), and getting them pays from
@@ -809,8 +820,7 @@ bool have_stage(cadmm_ctx* c, size_t bytes) {
             (void)hipGetLastError();
             return false;
         }
-        if (!c->stage_free[k] && hipEventCreateWithFlags(&c->stage_free[k], hipEventDisableTiming) != hipSuccess) {
-            c->stage_free[k] = nullptr;
+        if (!c->stage_free[k] && make_event(c, &c->stage_free[k]) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
@@ -902,13 +912,13 @@ int on_op_stream(cadmm_ctx* c, const char* what, F body) {
         return check_launch(c, what);
     }
     for (hipEvent_t* e : {&c->ev_own, &c->ev_op})
-        if (!*e) HIP_TRY(c, hipEventCreateWithFlags(e, hipEventDisableTiming));
+        if (!*e) HIP_TRY(c, make_event(c, e));
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (c->op_stream) HIP_TRY(c, hipStreamIsCapturing(c->op_stream, &cap));
     if (cap != hipStreamCaptureStatusNone) {
         hipEvent_t in = nullptr, out = nullptr;
-        HIP_TRY(c, hipEventCreateWithFlags(&in, hipEventDisableTiming));
-        HIP_TRY(c, hipEventCreateWithFlags(&out, hipEventDisableTiming));
+        HIP_TRY(c, make_event(c, &in));
+        HIP_TRY(c, make_event(c, &out));
         HIP_TRY(c, hipEventRecord(in, c->op_stream));
         HIP_TRY(c, hipStreamWaitEvent(c->stream, in, 0));
         body();

@@ -439,3 +439,31 @@ def test_a_refused_call_between_kernel_calls_on_two_streams_keeps_their_order():
             assert torch.equal(first, want[0]) and torch.equal(second, want[1])
     finally:
         s.close()
+
+
+def test_kernel_calls_and_readouts_while_another_device_is_current():
+    """The events of a context belong to its own device, whichever the calling thread has current."""
+    import torch
+    from paper_2112_09335_amd import binding
+    if torch.cuda.device_count() < 2:
+        pytest.skip("needs two GPUs")
+    w = synth.make_workload("two-devices", 5, 20000, 4, [256, 64, 4], 4, 2, graph="sbm", features="gaussian", avg_degree=6,
+                            frac_intra=0.8)
+    s = binding.Solver.from_workload(w, 0)
+    try:
+        X = torch.randn(w.N, 64, device="cuda:0")
+        with torch.cuda.device(0):
+            want = s.op_aggregate(X)
+            s.run(2)
+            Z = [s.get_Z(1) for _ in range(2)]
+        with torch.cuda.device(1):
+            t = binding.Solver.from_workload(w, 0)
+            torch.cuda.set_device(1)
+            got = t.op_aggregate(X)
+            t.run(2)
+            assert torch.equal(got, want)
+            for _ in range(2):                           # (the second large readout goes through the pinned pieces)
+                assert np.array_equal(t.get_Z(1), Z[0])
+            t.close()
+    finally:
+        s.close()
