@@ -399,8 +399,9 @@ double spmm_bytes(const cadmm_ctx* c, int64_t out_rows, int width, int extra_rea
 
 void gemm_nn(cadmm_ctx* c, const float* A, const float* B, float* out, int64_t n, int K, int C,
              const GemmEpilogue& epi = GemmEpilogue()) {
-    timed(c, C > 32 ? (epi.kind ? P_GEMM_NN_128_GRADZ : P_GEMM_NN_128) : P_GEMM_NN_32,
-          4.0 * ((double)n * K + (double)K * C + (double)n * C * (epi.kind ? 3 : 1)), 2.0 * (double)n * K * C,
+    const int passes = epi.kind == 3 ? (out ? 2 : 1) : epi.kind ? 3 : 1;        // matrices of the result's size that are read or written
+    timed(c, C > 32 ? (epi.kind == 1 ? P_GEMM_NN_128_GRADZ : P_GEMM_NN_128) : P_GEMM_NN_32,
+          4.0 * ((double)n * K + (double)K * C + (double)n * C * passes), 2.0 * (double)n * K * C,
           [&] { launch_gemm_nn(c->stream, A, B, out, n, K, C, epi); });
 }
 
@@ -433,19 +434,27 @@ void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width) {
 
 bool t1_reusable(const cadmm_ctx* c) { return c->t1_age >= 0 && c->t1_age < c->t1_refresh; }
 
+GemmEpilogue relu_epilogue(float* relu_out) {
+    GemmEpilogue e;
+    if (relu_out) { e.kind = 3; e.Tio = relu_out; }
+    return e;
+}
+
 // T_l = A~ Z_{l-1} W_l in the association chosen for the layer.  Used by the initial forward pass and
 // by every base evaluation, so that re-evaluating an unchanged point reproduces T_l bit for bit.
-void compute_T(cadmm_ctx* c, int l, bool force = false) {
+// relu_out (may be null): also gets relu(T_l).
+void compute_T(cadmm_ctx* c, int l, bool force = false, float* relu_out = nullptr) {
     const int64_t N = c->hg.N;
     const bool carried = !force && t1_reusable(c);     // T[l] already holds A~ Z_{l-1} W_l for the current state
     if (c->agg_first[l]) {
         if (carried) return;
         gemm_nn(c, c->Z[l - 1], c->W[l], c->tmpV, N, c->C[l - 1], c->C[l]);
         aggregate(c, c->tmpV, c->T[l], c->C[l], SpmmEpilogue());
+        if (relu_out) launch_relu(c->stream, c->T[l], relu_out, N * c->C[l], 1);
     } else {
         if (l >= 2) aggregate(c, c->Z[l - 1], c->H[l], c->C[l - 1], SpmmEpilogue());   // the W step needs H_l itself
         if (carried) return;
-        gemm_nn(c, c->H[l], c->W[l], c->T[l], N, c->C[l - 1], c->C[l]);
+        gemm_nn(c, c->H[l], c->W[l], c->T[l], N, c->C[l - 1], c->C[l], relu_epilogue(relu_out));
     }
 }
 
@@ -1173,8 +1182,8 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
     for (int l = 2; l <= L; ++l) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
     aggregate(c, c->Z[0], c->H[1], c->C[0], SpmmEpilogue());      // A~ Z_0 never changes
     for (int l = 1; l <= L; ++l) {
-        compute_T(c, l);
-        launch_relu(s, c->T[l], c->Z[l], N * c->C[l], l < L);
+        compute_T(c, l, false, l < L ? c->Z[l] : nullptr);
+        if (l == L) launch_relu(s, c->T[l], c->Z[l], N * c->C[l], 0);
     }
     HIP_TRY(c, hipMemsetAsync(c->U, 0, (size_t)N * c->C[L] * sizeof(float), s));
     HIP_TRY(c, hipMemsetAsync(c->status, 0, 4 * sizeof(int32_t), s));
@@ -1287,10 +1296,11 @@ int cadmm_predict(cadmm_ctx* c, int32_t* pred, float* logits, double* accuracy) 
             aggregate(c, c->tmpV, c->T[l], c->C[l], SpmmEpilogue());
         } else {
             if (l >= 2) aggregate(c, in, c->H[l], c->C[l - 1], SpmmEpilogue());
-            gemm_nn(c, c->H[l], c->W[l], c->T[l], N, c->C[l - 1], c->C[l]);
+            // (of a hidden layer only the activation is needed)
+            gemm_nn(c, c->H[l], c->W[l], l < L ? nullptr : c->T[l], N, c->C[l - 1], c->C[l], relu_epilogue(l < L ? c->G[l] : nullptr));
         }
         if (l < L) {
-            launch_relu(s, c->T[l], c->G[l], N * c->C[l], 1);
+            if (c->agg_first[l]) launch_relu(s, c->T[l], c->G[l], N * c->C[l], 1);
             in = c->G[l];
         }
     }

@@ -115,7 +115,7 @@ __device__ __forceinline__ void xcd_group(unsigned b, unsigned nb, unsigned inne
 // through LDS (Cs: 32 x (64 T + 4) floats, the operand buffer reused) turns every global access of the epilogue into
 // 16-byte pieces of a row of 256 T bytes.
 // EPI 0: out = acc.  EPI 1: out = nu (Zl - relu(Tl)) + acc.  EPI 2: first candidate of the W search and the step
-// on Tio ahead of the decision, see GemmEpilogue.
+// on Tio ahead of the decision, see GemmEpilogue.  EPI 3: out (if there is one) = acc, Tio = relu(acc).
 template <int EPI, int T, int MODE>
 __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                                    float* __restrict__ out, const float* __restrict__ Zl,
@@ -157,7 +157,7 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
 #pragma unroll
         for (int u0 = 0; u0 < PER_T; u0 += 2) {
             float4 z4[2], t4[2];
-            if constexpr (EPI != 0) {
+            if constexpr (EPI == 1 || EPI == 2) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int f = tid + 256 * (u0 + u);
@@ -198,7 +198,7 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 if (row >= n || c >= C) continue;
                 const int64_t o = row * C + c;
                 const int nv = MODE == kFull ? 4 : C - c;       // columns of this lane (four, or the row's last few)
-                if constexpr (EPI != 0) {
+                if constexpr (EPI == 1 || EPI == 2) {
                     const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
                     t[0] = t4[u].x; t[1] = t4[u].y; t[2] = t4[u].z; t[3] = t4[u].w;
 #pragma unroll
@@ -211,6 +211,11 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 if constexpr (EPI == 2) {
                     if (take) st4u(Tio + o, t, nv);
                     else st4u(out + o, v, nv);
+                } else if constexpr (EPI == 3) {
+                    if (out) st4u(out + o, v, nv);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+                    st4u(Tio + o, v, nv);
                 } else {
                     st4u(out + o, v, nv);
                 }
@@ -248,6 +253,7 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, 
 // ------------------------------------------------------------------------------------------------ NN
 // EPI 1: out = nu * (Zl - relu(Tl)) + A B   (gradient of the Z subproblem, Appendix A)
 // EPI 2: out = Q = A B; first candidate of the W search and speculative step on Tio (Section 3.1), see kernels.h
+// EPI 3: Tio = relu(A B), and out = A B if there is an out
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                       float* __restrict__ out, int64_t n, int K, int C,
@@ -349,7 +355,7 @@ template <int EPI, int SPLIT>
 __global__ __launch_bounds__(256) void gemm_nn_narrow_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                              float* __restrict__ out, int64_t n, int K, int C,
                                                              const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                             float nu) {
+                                                             float nu, float* __restrict__ relu_out) {
     constexpr int KS = 32;
     constexpr int LDA = KS + 1;
     constexpr int LDB = 32 + 4;
@@ -441,7 +447,8 @@ __global__ __launch_bounds__(256) void gemm_nn_narrow_kernel(const float* __rest
         const int64_t row = m0 + row_in_tile;
         if (row < n && li < C) {
             if constexpr (EPI == 1) v = nu * (Zl[row * C + li] - fmaxf(Tl[row * C + li], 0.f)) + v;
-            out[row * C + li] = v;
+            if constexpr (EPI == 3) relu_out[row * C + li] = fmaxf(v, 0.f);
+            if (EPI != 3 || out) out[row * C + li] = v;
         }
     };
     if constexpr (SPLIT == 0) {
@@ -1261,8 +1268,10 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
     if (C > 32) {
         const int t = nn_tile(n, C, g_split);
         const dim3 grid((unsigned)gemm_nn_blocks(n, C));
-#define CADMM_NN(K2_, K1_, K0_) \
-        if (epi.kind == 2) \
+#define CADMM_NN(K3_, K2_, K1_, K0_) \
+        if (epi.kind == 3) \
+            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, nullptr); \
+        else if (epi.kind == 2) \
             hipLaunchKernelGGL(K2_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
                                epi.partials); \
         else if (epi.kind == 1) \
@@ -1272,24 +1281,24 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
             hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
                                nullptr)
         if (!g_split) {
-            CADMM_NN((gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
+            CADMM_NN((gemm_nn_kernel<3>), (gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
         } else if (t == 2) {
-            CADMM_NN((gemm_nn_split_kernel<2, 2, 1>), (gemm_nn_split_kernel<1, 2, 1>), (gemm_nn_split_kernel<0, 2, 1>));
+            CADMM_NN((gemm_nn_split_kernel<3, 2, 1>), (gemm_nn_split_kernel<2, 2, 1>), (gemm_nn_split_kernel<1, 2, 1>), (gemm_nn_split_kernel<0, 2, 1>));
         } else {
-            CADMM_NN((gemm_nn_split_kernel<2, 1, 4>), (gemm_nn_split_kernel<1, 1, 4>), (gemm_nn_split_kernel<0, 1, 4>));
+            CADMM_NN((gemm_nn_split_kernel<3, 1, 4>), (gemm_nn_split_kernel<2, 1, 4>), (gemm_nn_split_kernel<1, 1, 4>), (gemm_nn_split_kernel<0, 1, 4>));
         }
 #undef CADMM_NN
     } else {
         // (two workgroups per compute unit, as for the wide products; the rows are the only tiles here)
         const bool few = (n + 127) / 128 < kFewTiles;
         const dim3 grid((unsigned)(few ? (n + 31) / 32 : (n + 127) / 128));
-        if (epi.kind == 1) {
-            if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<1, 1>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu);
-            else hipLaunchKernelGGL((gemm_nn_narrow_kernel<1, 0>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu);
-        } else {
-            if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<0, 1>), grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f);
-            else hipLaunchKernelGGL((gemm_nn_narrow_kernel<0, 0>), grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f);
-        }
+#define CADMM_NARROW(E_) \
+        if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<E_, 1>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, epi.Tio); \
+        else hipLaunchKernelGGL((gemm_nn_narrow_kernel<E_, 0>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, epi.Tio)
+        if (epi.kind == 3) { CADMM_NARROW(3); }
+        else if (epi.kind == 1) { CADMM_NARROW(1); }
+        else { CADMM_NARROW(0); }
+#undef CADMM_NARROW
     }
 }
 

@@ -225,6 +225,27 @@ def test_inference_matches_the_oracle_between_iterations():
     solver.close()
 
 
+@pytest.mark.parametrize("n,dims", [(700, [20, 33, 32, 5]), (701, [37, 3, 130, 4]), (40007, [16, 200, 129, 7]), (70001, [9, 5, 31, 3])])
+def test_forward_pass_of_init_and_inference_over_product_shapes(n, dims):
+    """The products leave relu(T_l) themselves: 64- and 128-column tiles, narrow ones for few and many rows, partial quads, and
+    a hidden layer that aggregates on its narrow side.  Three fp32 contractions of at most 200 terms: far below 1e-5."""
+    from oracle.graph import OracleGraph
+    from paper_2112_09335_amd import binding
+    w = synth.make_workload("forward", 61, n, 3, dims, dims[-1], 1, graph="sbm", features="gaussian", avg_degree=6, frac_intra=0.8)
+    A = OracleGraph(w.N, w.src, w.dst, w.M, w.comm)
+    solver = binding.Solver.from_workload(w, 0)
+    try:
+        X = w.X.astype(np.float64)
+        for l, W in enumerate(w.W0, 1):
+            X = (A.A @ (X[A.perm] @ W.astype(np.float64)))[A.inv_perm]
+            X = np.maximum(X, 0.0) if l < w.L else X
+            assert np.linalg.norm(solver.get_Z(l) - X) <= 1e-5 * np.linalg.norm(X), l
+        _, logits, _ = solver.predict()
+        assert np.linalg.norm(logits - X) <= 1e-5 * np.linalg.norm(X)
+    finally:
+        solver.close()
+
+
 def test_dual_ascent_on_new_iterates_variant():
     w = synth.config(1, 0.5)
     w.hyper["dual_form"] = 1
