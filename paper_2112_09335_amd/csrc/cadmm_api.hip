@@ -174,15 +174,21 @@ int max_of(const std::vector<int>& v, int lo, int hi) {
 
 SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, const RowSchedule& rs);
 
-// How the Z gradient of hidden layer l is formed (z_update_hidden).
+// How the Z gradient of hidden layer l is formed (z_update_hidden).  The penalty term and the row sums are cheaper in the
+// product's epilogue, which moves whole 512-byte pieces of rows, than in the aggregation's (a column tile at a time; 500000 x
+// 512: 2140 us with the epilogue, 1320 without), so the product comes last unless the aggregation would be the wider for it.
+// Product last against aggregation last, whole iterations: widths 256, 256 2 % less time (200000 nodes) and 1 % (20000),
+// 128, 128 1 and 0 %; 128, 144 2 and 1 % more, 128, 256 5 and 1 % more, 64, 80 3 and 2 % more; 20, 20 no difference (the
+// narrow product leaves no row sums).
 enum GradPath { kGradLowRank, kGradProduct, kGradAggregate };
 bool low_rank_shape(const cadmm_ctx* c, int l) {
     const int Cl = c->C[l], Cn = c->C[l + 1];
     return Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
 }
+bool product_last(int Cl, int Cn) { return Cn < Cl || (Cn == Cl && Cl > 32); }
 GradPath grad_path(const cadmm_ctx* c, int l) {
     if (c->use_lowrank && low_rank_shape(c, l)) return kGradLowRank;
-    return c->C[l + 1] < c->C[l] ? kGradProduct : kGradAggregate;
+    return product_last(c->C[l], c->C[l + 1]) ? kGradProduct : kGradAggregate;
 }
 // Column tiles in which the last kernel of that path leaves the rows' sums for the search; 0: it does not, the search reads the
 // gradient (narrow layers, where that is little, and so many tiles that their sums would not be).
@@ -200,7 +206,7 @@ int sum_tiles_of(const cadmm_ctx* c, int l, GradPath path) {
 int sum_tiles_reserved(const cadmm_ctx* c, int l) {
     const int Cl = c->C[l], Cn = c->C[l + 1];
     int tiles = 0;
-    if (Cn < Cl) tiles = std::max(1, Cl > 32 ? gemm_nn_most_tiles(c->hg.N, Cl) : 0);
+    if (product_last(Cl, Cn)) tiles = std::max(1, Cl > 32 ? gemm_nn_most_tiles(c->hg.N, Cl) : 0);
     else if (Cl >= 4) tiles = spmm_default_tiles(schedule_of(c, c->d_rows, c->hg.row_sched), Cl);
     return tiles <= kMaxSumTiles ? tiles : low_rank_shape(c, l) ? 1 : 0;
 }
@@ -643,7 +649,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
             launch_G_only(s, c->T[l + 1], c->Z[l + 1], c->U, c->G[l + 1], 0, N * Cn, next_last, c->nu, c->rho);
         });
     // grad psi (all communities at once) = nu (Z_l - relu(T_l)) + A~ G_{l+1} W_{l+1}^T; aggregate on the
-    // narrower of the two widths, the penalty term rides in the epilogue of whichever kernel comes last.
+    // narrower of the two widths (grad_path), the penalty term rides in the epilogue of whichever kernel comes last.
     // With a very narrow next layer the gradient is never stored: its consumers (the product with
     // W_{l+1}, the search, the step) rebuild it per element from Z_l, T_l and the N x C_{l+1} factor
     // A~ G_{l+1}, which removes a full write and two full reads of an N x C_l matrix.
