@@ -558,8 +558,12 @@ void later_candidates(const cadmm_ctx* c, double elements, int tried, F pass) {
     }
 }
 
+// Whether the W step of hidden layer l leaves G_l for the Z step of layer l - 1: where nothing that G_l is made of changes in
+// between.  (Layer by layer, W_l moves after Z_{l-1}.)
+bool leaves_gradient(const cadmm_ctx* c, int l) { return c->schedule == 0 && l >= 2; }
+
 // W_l <- W_l - grad phi_l / tau_l with backtracking on tau_l (Section 3.1), from the T_l, H_l (or Z_{l-1}) and G_l
-// in memory; leaves T_l = A~ Z_{l-1} W_l^{new}.
+// in memory; leaves T_l = A~ Z_{l-1} W_l^{new}, and where the Z step of layer l - 1 follows in the same sweep, its G_l.
 void w_update(cadmm_ctx* c, int l) {
     const int L = c->L;
     const int64_t N = c->hg.N;
@@ -587,6 +591,7 @@ void w_update(cadmm_ctx* c, int l) {
           });
     timed(c, P_OTHER, 16.0 * n_norms, 0.0, [&] { launch_w_begin(s, c->partials, n_norms, unit, sp); });
     float* Q = c->G[l];                                                          // G_l is no longer needed
+    const bool leave_g = !last && leaves_gradient(c, l);
     // T(W - g/tau) = T - Q/tau with Q = A~ Z_{l-1} gradW
     // In a wide hidden layer the product that forms Q also evaluates the first candidate of the search and
     // takes the step on T_l speculatively (tau rarely changes once found); later kernels repair it if needed.
@@ -596,8 +601,8 @@ void w_update(cadmm_ctx* c, int l) {
         aggregate(c, c->tmpV, Q, Cl, SpmmEpilogue());
     } else if (spec) {
         GemmEpilogue ge;
-        ge.kind = 2; ge.Zl = c->Z[l]; ge.nu = c->nu; ge.Tio = c->T[l]; ge.unit = unit; ge.partials = c->partials;
-        timed(c, P_GEMM_NN_128_TRIAL, 4.0 * ((double)N * K + (double)K * Cl + 3.0 * (double)count), 2.0 * (double)N * K * Cl,
+        ge.kind = 2; ge.Zl = c->Z[l]; ge.nu = c->nu; ge.Tio = c->T[l]; ge.unit = unit; ge.partials = c->partials; ge.leave_g = leave_g;
+        timed(c, P_GEMM_NN_128_TRIAL, 4.0 * ((double)N * K + (double)K * Cl + (leave_g ? 4.0 : 3.0) * (double)count), 2.0 * (double)N * K * Cl,
               [&] {
                   launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, ge);
                   launch_w_trial_finish(s, c->partials, (int)gemm_nn_blocks(N, Cl), sp, unit, c->status);
@@ -619,13 +624,13 @@ void w_update(cadmm_ctx* c, int l) {
             launch_w_trial(s, c->T[l], Q, c->Z[l], count, n, sp, unit, c->partials, c->status, spec ? 1 : 0);
         });
     });
-    timed(c, P_W_STEP, 4.0 * ((spec ? 0.0 : last ? 7.0 : 3.0) * (double)count + 3.0 * K * Cl), 0.0, [&] {
+    timed(c, P_W_STEP, 4.0 * ((spec ? 0.0 : last ? 7.0 : leave_g ? 5.0 : 3.0) * (double)count + 3.0 * K * Cl), 0.0, [&] {
         // W^{k+1}; T_l = A~ Z^k W^{k+1}; last layer: G_L of that T_L for the Z step of layer L-1
         if (last)
             launch_w_step_last(s, c->W[l], c->Wt[l], c->gradW, K, Cl, c->T[l], Q, count, unit, c->Z[l], c->U, c->G[l],
                                c->schedule == 1 ? nullptr : c->TLprev, c->rho);
         else
-            launch_w_step(s, c->W[l], c->Wt[l], c->gradW, K, Cl, c->T[l], Q, count, unit, spec ? 1 : 0);
+            launch_w_step(s, c->W[l], c->Wt[l], c->gradW, K, Cl, c->T[l], Q, count, unit, spec ? 1 : 0, leave_g ? c->Z[l] : nullptr, c->nu);
     });
     if (last) c->gl_valid = true;
     else c->gh_valid = false;
@@ -644,7 +649,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     Unit* units = c->unitsZ + (size_t)(l - 1) * M;
     const float* Wt = c->Wt[l + 1];
     c->P = c->Pbuf[l & 1];
-    if (!next_last || !c->gl_valid)                // (the W step of the last layer leaves G_L)
+    if (next_last ? !c->gl_valid : !leaves_gradient(c, l + 1))                 // (else the W step of layer l + 1 has left it)
         timed(c, P_G_ONLY, 4.0 * (double)N * Cn * (next_last ? 4 : 3), 0.0, [&] {
             launch_G_only(s, c->T[l + 1], c->Z[l + 1], c->U, c->G[l + 1], 0, N * Cn, next_last, c->nu, c->rho);
         });

@@ -445,17 +445,19 @@ __global__ __launch_bounds__(256) void w_trial_finish_kernel(const double* __res
     if (threadIdx.x == 0) decide(unit, D, ncand, sp, status);
 }
 
-// W <- W - gradW/tau with its transpose beside it, T <- T - Q/tau.  LAST: also keeps the old T (Tprev) and leaves
-// G = -(U + rho (Z - T)) of the new T for the Z step of the layer before (G may be the same array as Q).
+// W <- W - gradW/tau with its transpose beside it, T <- T - Q/tau.  LAST: also keeps the old T (Tprev).  The gradient
+// of the new T is left for the Z step of the layer before (G may be the same array as Q): LAST G = -(U + rho (Z - T)), else,
+// if there is a G, nu (relu(T) - Z) 1[T > 0].
 template <int LAST>
 __global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, float* __restrict__ Wt,
                                                      const float* __restrict__ gradW, int K, int C,
                                                      float* __restrict__ T, const float* Q, int64_t count_t,
                                                      const Unit* unit, int speculated, const float* __restrict__ Z,
                                                      const float* __restrict__ U, float* G, float* __restrict__ Tprev,
-                                                     float rho) {
+                                                     float nu, float rho) {
     const bool skip = unit->skip != 0;
-    if (LAST == 0 && skip) return;
+    const bool leave = LAST || G != nullptr;
+    if (skip && (!leave || speculated)) return;
     const double inv = 1.0 / unit->step;
     const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t nthreads = (int64_t)gridDim.x * blockDim.x;
@@ -463,30 +465,31 @@ __global__ __launch_bounds__(256) void w_step_kernel(float* __restrict__ W, floa
     // otherwise T0 - Q/step = T + Q (1/step0 - 1/step)
     const bool spec = speculated && unit->spec;
     const double tinv = spec ? inv - 1.0 / unit->step0 : inv;
-    const bool t_done = spec && unit->step == unit->step0;
+    const bool t_done = spec && !skip && unit->step == unit->step0;
     if (LAST || !t_done) {
         for_quads(count_t, [&](int64_t i, auto w) {
             const int64_t nv = count_t - i;
             float t[4], q[4];
             ldq(t, T + i, nv, w);
-            ldq(q, Q + i, nv, w);
+            if (!skip) ldq(q, Q + i, nv, w);
+            float z[4], u[4], g[4];
+            if (leave) ldq(z, Z + i, nv, w);
             if (LAST) {
-                float z[4], u[4], g[4];
-                ldq(z, Z + i, nv, w);
                 ldq(u, U + i, nv, w);
                 if (Tprev) stq(Tprev + i, t, nv, w);
-                if (!skip) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
-                    stq(T + i, t, nv, w);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) g[v] = -(u[v] + rho * (z[v] - t[v]));
-                stq(G + i, g, nv, w);
-            } else {
+            }
+            if (!skip) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) t[v] = (float)((double)t[v] - (double)q[v] * tinv);
                 stq(T + i, t, nv, w);
+            }
+            if (leave) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    if (LAST) g[v] = -(u[v] + rho * (z[v] - t[v]));
+                    else g[v] = t[v] > 0.f ? nu * (float)((double)t[v] - (double)z[v]) : 0.f;
+                }
+                stq(G + i, g, nv, w);
             }
         });
     }
@@ -1326,12 +1329,12 @@ void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float*
     hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, nc, sp, unit, status);
 }
 
-void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
-                   int64_t count_t, const Unit* unit, int speculated) {
+void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, float* Q,
+                   int64_t count_t, const Unit* unit, int speculated, const float* Z, float nu) {
     const int64_t cw = (int64_t)K * C;
     const int nb = flat_grid(count_t > cw ? count_t : cw);
     hipLaunchKernelGGL((w_step_kernel<0>), dim3(nb), dim3(256), 0, s, W, Wt, gradW, K, C, T, Q, count_t, unit, speculated,
-                       nullptr, nullptr, nullptr, nullptr, 0.f);
+                       Z, nullptr, Z ? Q : nullptr, nullptr, nu, 0.f);
 }
 
 void launch_w_step_last(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
@@ -1339,7 +1342,7 @@ void launch_w_step_last(hipStream_t s, float* W, float* Wt, const float* gradW, 
     const int64_t cw = (int64_t)K * C;
     const int nb = flat_grid(count_t > cw ? count_t : cw);
     hipLaunchKernelGGL((w_step_kernel<1>), dim3(nb), dim3(256), 0, s, W, Wt, gradW, K, C, T, Q, count_t, unit, 0, Z, U, G,
-                       Tprev, rho);
+                       Tprev, 0.f, rho);
 }
 
 // calls f with the width's kind as an integral constant

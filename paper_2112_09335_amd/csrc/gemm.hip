@@ -120,7 +120,7 @@ template <int EPI, int T, int MODE>
 __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                                    float* __restrict__ out, const float* __restrict__ Zl,
                                                    const float* tin, float nu, float* __restrict__ Tio, double inv0,
-                                                   bool take, double& dsum, double* __restrict__ row_sums) {
+                                                   bool take, bool hold, bool leave_g, double& dsum, double* __restrict__ row_sums) {
     constexpr int BN = 64 * T;
     constexpr int LDC = BN + 4;
     constexpr int Q = BN / 4;                            // quads per row
@@ -210,7 +210,16 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 }
                 if constexpr (EPI == 2) {
                     if (take) st4u(Tio + o, t, nv);
-                    else st4u(out + o, v, nv);
+                    if (take || hold) {
+                        if (leave_g) {                                   // (as launch_G_only forms it)
+                            const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) v[e] = t[e] > 0.f ? nu * (float)((double)t[e] - (double)z[e]) : 0.f;
+                            st4u(out + o, v, nv);
+                        }
+                    } else {
+                        st4u(out + o, v, nv);
+                    }
                 } else if constexpr (EPI == 3) {
                     if (out) st4u(out + o, v, nv);
 #pragma unroll
@@ -228,18 +237,19 @@ template <int EPI, int T>
 __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                               float* __restrict__ out, const float* __restrict__ Zl,
                                               const float* __restrict__ Tl, float nu, float* __restrict__ Tio,
-                                              const Unit* unit, double* __restrict__ partials) {
+                                              const Unit* unit, int leave_g, double* __restrict__ partials) {
     // (epilogue 1 has no partials: the argument then carries the row sums)
     double* const row_sums = EPI == 1 ? partials : nullptr;
     double inv0 = 0.0, dsum = 0.0;
-    bool take = false;
+    bool take = false, hold = false;
     if constexpr (EPI == 2) {
+        hold = unit->skip != 0;
         inv0 = unit->skip ? 0.0 : 1.0 / unit->step0;
         take = unit->spec != 0 && !unit->skip;
     }
     const float* tin = (EPI == 2) ? Tio : Tl;
-    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum, row_sums);
-    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, dsum, row_sums);   // (C > 32)
+    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, leave_g != 0, dsum, row_sums);
+    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, leave_g != 0, dsum, row_sums);   // (C > 32)
     if constexpr (EPI == 2) {
         __shared__ double red[4];
 #pragma unroll
@@ -258,7 +268,7 @@ template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                       float* __restrict__ out, int64_t n, int K, int C,
                                                       const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                      float nu, float* __restrict__ Tio, const Unit* unit,
+                                                      float nu, float* __restrict__ Tio, const Unit* unit, int leave_g,
                                                       double* __restrict__ partials) {
     constexpr int BN = 128;
     constexpr int LDA = BK + 1;
@@ -319,7 +329,13 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
         }
     };
 
-    const int nk = (K + BK - 1) / BK;
+    int nk = (K + BK - 1) / BK;
+    if constexpr (EPI == 2) {
+        if (unit->skip) {           // no step is taken: nothing reads Q, the epilogue leaves G of the T that stays
+            if (!leave_g) return;
+            nk = 0;
+        }
+    }
     fetch(0);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();            // previous tile fully consumed
@@ -342,7 +358,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
         }
     }
     static_assert(32 * (BN + 4) <= BM * LDA + BK * LDB, "result slab must fit the operand buffer");
-    tile_epilogue<EPI, 2>(acc, smem, m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
+    tile_epilogue<EPI, 2>(acc, smem, m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, leave_g, partials);
 }
 
 // Results of at most 32 columns: bound by reading A, so a step takes 32 columns of it (a whole 128-byte line of every
@@ -551,7 +567,7 @@ template <int EPI, int T, int PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 : 1, T == 2 ? 4 : 8))) void gemm_nn_split_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ out, int64_t n, int K, int C,
     const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
-    double* __restrict__ partials) {
+    int leave_g, double* __restrict__ partials) {
     if constexpr (EPI == 0) {
         // gated plain product, as in gemm_nn_kernel
         if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
@@ -624,7 +640,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
             }
         }
     };
-    const int nk = (K + BK - 1) / BK;
+    int nk = (K + BK - 1) / BK;
+    if constexpr (EPI == 2) {
+        if (unit->skip) {                         // as in gemm_nn_kernel
+            if (!leave_g) return;
+            nk = 0;
+        }
+    }
 #pragma unroll
     for (int s = 0; s < PF; ++s)
         if (s < nk) fetch(s, s * BK);
@@ -642,7 +664,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
             multiply_split<T, LDH>(acc, As, Bs, wm * 32 * T + li, wn * 32 * T + li, lk);
         }
     }
-    tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
+    tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, leave_g, partials);
 }
 
 // out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 16.
@@ -1270,16 +1292,16 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
         const dim3 grid((unsigned)gemm_nn_blocks(n, C));
 #define CADMM_NN(K3_, K2_, K1_, K0_) \
         if (epi.kind == 3) \
-            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, nullptr); \
+            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, 0, nullptr); \
         else if (epi.kind == 2) \
             hipLaunchKernelGGL(K2_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
-                               epi.partials); \
+                               epi.leave_g ? 1 : 0, epi.partials); \
         else if (epi.kind == 1) \
             hipLaunchKernelGGL(K1_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
-                               epi.row_sums); \
+                               0, epi.row_sums); \
         else \
             hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
-                               nullptr)
+                               0, nullptr)
         if (!g_split) {
             CADMM_NN((gemm_nn_kernel<3>), (gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
         } else if (t == 2) {

@@ -69,6 +69,9 @@ struct Unit;
 // (its workgroups leave at once otherwise) and w_step repairs Tio from it.  The step is only taken ahead of the
 // decision when the previous search accepted its first candidate: then Q/step0 is small against Tio and
 // undoing it costs one rounding; with a step0 far too small (first iterations) it would wipe out Tio.
+// leave_g: where the step is taken ahead, out gets the gradient G = nu (relu(t1) - Zl) 1[t1 > 0] for the Z step of the layer
+// before (launch_w_step leaves it otherwise): one more store here instead of a pass that reads two matrices again.
+// Where the search takes no step at all (unit->skip) nothing reads Q: the product is not formed, out gets G with leave_g.
 // epilogue 3 (forward pass): Tio = relu(A B), and out = A B unless out is null; a pass over the pre-activations of its own
 // would read them once more (200000 x 256: 76 us).
 struct GemmEpilogue {
@@ -78,6 +81,7 @@ struct GemmEpilogue {
     float nu = 0.f;
     float* Tio = nullptr;
     const Unit* unit = nullptr;
+    bool leave_g = false;
     double* partials = nullptr;
     double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C) column tiles
 };
@@ -179,8 +183,10 @@ void launch_w_trial_finish(hipStream_t s, double* partials, int n_partials, Sear
                            int32_t* status);
 // W -= gradW/step, Wt (C x K, may be null) its transpose, T = T0 - Q/step (count_t entries); no-op if unit.skip.
 // speculated != 0: T already holds T0 - Q/step0 and is only repaired if the accepted step differs.
-void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
-                   int64_t count_t, const Unit* unit, int speculated);
+// With Z, Q gets the gradient G = nu (relu(T) - Z) 1[T > 0] of the new T (also if the step is skipped), unless the
+// product has left it there (epilogue 2 with leave_g).
+void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, float* Q,
+                   int64_t count_t, const Unit* unit, int speculated, const float* Z, float nu);
 // The same for the last layer; it also keeps the old T in Tprev (if not null) and leaves G = -(U + rho (Z - T)) of the new
 // T (also if the step is skipped).  G may be Q.
 void launch_w_step_last(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, const float* Q,
