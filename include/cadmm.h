@@ -269,6 +269,8 @@ const char* cadmm_profile_class_name(int32_t cls);
  * nu (Z_l - relu(T_l)) + (A~ G_{l+1}) W_{l+1}^T and rebuilt per element by its consumers (default), 0 = stored.
  * "use_speculative" (per context): 1 = in a wide hidden layer the product Q = A~ Z_{l-1} grad W also evaluates the
  * first candidate of the tau search and takes the step on the pre-activation speculatively (default), 0 = separate passes.
+ * "use_floor_first" (per context): the Z search of a hidden layer tests the step floor before it forms what only a step
+ * needs: 1 = in large layers (default), 2 = wherever the sums for it are at hand, 0 = never.
  * "t1_refresh" (per context): the pre-activations A~ Z_{l-1} W_l are carried from one iteration to the
  * next (through the W step, and through the segment products of the Z step) and formed anew every
  * this many iterations (default 16; 0 = always form them anew).

@@ -92,6 +92,7 @@ struct cadmm_ctx {
     Unit* unitsF = nullptr;     // [M]: the L of the last-layer solve with backtracking (fista_mode 1)
     float* fistaX = nullptr;    // N x C_L each: x_j and y_j of that solve
     float* fistaY = nullptr;
+    int32_t* gates = nullptr;          // [L]: whether any community of layer l = 1..L-1 takes a Z step (floor_first)
     LayerScalars* scalars = nullptr;   // [L+1]
     int32_t* status = nullptr;
     // What the buffers hold at the moment.  base_valid: every H_l and T_l belongs to the current iterate.  gl_valid /
@@ -112,6 +113,7 @@ struct cadmm_ctx {
     bool use_graph = true;
     bool use_lowrank = true;
     bool use_speculative = true;
+    int use_floor_first = 1;     // 0: never, 1: by size, 2: wherever the row sums allow it
     struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false; };
     GraphSlot graphs[32];
     // Kernel-level calls on a stream of the caller's (cadmm_op_stream): such a call is launched there, after what the context's
@@ -331,6 +333,7 @@ size_t layout(cadmm_ctx* c, char* base) {
         c->fistaX = b.take<float>(N * c->C[L]);
         c->fistaY = b.take<float>(N * c->C[L]);
     }
+    c->gates = b.take<int32_t>(L);
     c->scalars = b.take<LayerScalars>(L + 1);
     c->status = b.take<int32_t>(4);
     return (b.off + 255) & ~(size_t)255;
@@ -430,11 +433,13 @@ void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpil
 
 // P_{(i,c)} = sum over the entries of row i in community c of A~_ij V_j, one output row per segment, in the
 // (community, row) order: the segments with several entries as a row list, those with one entry as scaled copies.
-void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width) {
+void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width, const int32_t* gate = nullptr) {
     timed(c, P_SPMM_SEG, spmm_bytes(c, c->hg.n_seg, width, 0), 2.0 * (double)c->hg.nnz * width, [&] {
-        launch_spmm(c->stream, schedule_of(c, c->d_segs, c->hg.seg_sched), V, P, width, SpmmEpilogue());
+        SpmmEpilogue e;
+        e.gate = gate;
+        launch_spmm(c->stream, schedule_of(c, c->d_segs, c->hg.seg_sched), V, P, width, e);
         launch_spmm_single(c->stream, c->d_seg1_pos, c->d_seg1_col, c->d_seg1_val, V, P, (int64_t)c->hg.seg1_pos.size(),
-                           width);
+                           width, gate);
     });
 }
 
@@ -523,11 +528,25 @@ void eval_scalars(cadmm_ctx* c) {
     c->scal_valid = true;
 }
 
+// Whether the Z search of layer l tests the step floor before grad W_{l+1} and the segment products are formed.  From the
+// forward pass on an iteration's steps reach one layer further back each time; until then a layer's gradient is below
+// resolution, and without a step in any community nothing of what only a step needs is formed.  That costs two launches
+// (9 us in every iteration): 1 % and less of an iteration from 2^24 entries on (65536 x 256: 0.9 ms).
+bool floor_first(const cadmm_ctx* c, int l, int sum_tiles) {
+    return sum_tiles > 0 && (c->use_floor_first == 2 || (c->use_floor_first == 1 && c->hg.N * (int64_t)c->C[l] >= (int64_t)1 << 24));
+}
+const int32_t* z_gate(const cadmm_ctx* c, int l) {
+    int tiles = sum_tiles_of(c, l, grad_path(c, l));
+    if (tiles > c->row_sum_tiles) tiles = 0;
+    return floor_first(c, l, tiles) ? c->gates + l : nullptr;
+}
+
 CarryArgs carry_args(const cadmm_ctx* c, int l) {
     CarryArgs k;
     k.P = c->Pbuf[(l - 1) & 1];
     k.row_seg_ptr = c->d_row_seg_ptr; k.seg_comm = c->d_seg_comm; k.seg_pos = c->d_seg_pos;
     k.units = c->unitsZ + (size_t)(l - 2) * c->hg.M; k.M = c->hg.M;
+    k.gate = z_gate(c, l - 1);
     return k;
 }
 
@@ -680,8 +699,6 @@ void z_update_hidden(cadmm_ctx* c, int l) {
         epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu; epi.row_sums = row_sums;
         aggregate(c, c->tmpA, c->tmpB, Cl, epi);
     }
-    if (!lowrank) gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn);          // grad W_{l+1}
-    aggregate_segments(c, c->tmpV, c->P, Cn);                                    // A~_{r,m} (grad W) per segment
     ZTrialArgs a;
     const cadmm_ctx::DevChunks& ct = c->d_chunks[l];
     a.chunks = ct.tab;
@@ -693,17 +710,25 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     a.Tn = c->T[l + 1]; a.Zn = c->Z[l + 1]; a.P = c->P; a.Cn = Cn;
     a.Gn = c->G[l + 1];
     a.next_is_last = next_last;
+    a.gate = floor_first(c, l, sum_tiles) ? c->gates + l : nullptr;
     a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
+    if (a.gate) timed(c, P_Z_TRIAL, 4.0 * 6.0 * sum_tiles * (double)N, 0.0, [&] { launch_z_floor(s, a); });
+    if (!lowrank) {
+        GemmEpilogue ge;
+        ge.gate = a.gate;
+        gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn, ge);                // grad W_{l+1}
+    }
+    aggregate_segments(c, c->tmpV, c->P, Cn, a.gate);                            // A~_{r,m} (grad W) per segment
     // one pass reads Z_l, grad, T_l (or their sums) over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
-    const double zt_bytes = 4.0 * ((sum_tiles ? 6.0 * sum_tiles * (double)N : 3.0 * (double)N * Cl) +
+    const double zt_bytes = 4.0 * ((a.gate ? 0.0 : sum_tiles ? 6.0 * sum_tiles * (double)N : 3.0 * (double)N * Cl) +
                                    (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;
     timed(c, P_Z_TRIAL, zt_bytes, 0.0, [&] {
         launch_z_first(s, a);
         if (!next_last) later_candidates(c, (double)c->hg.n_seg * Cn, 1, [&](int n) { launch_z_more(s, a, n); });
     });
     timed(c, P_Z_STEP, 4.0 * (3.0 * (double)N * Cl + (double)N + (lowrank ? (double)N * Cn : 0.0)), 0.0, [&] {
-        if (lowrank) launch_z_step_lowrank(s, c->Z[l], c->T[l], c->tmpA, Wt, c->nu, c->d_row_comm, N, Cl, Cn, units, M);
-        else launch_z_step(s, c->Z[l], c->tmpB, c->d_row_comm, N, Cl, units, M);
+        if (lowrank) launch_z_step_lowrank(s, c->Z[l], c->T[l], c->tmpA, Wt, c->nu, c->d_row_comm, N, Cl, Cn, units, M, a.gate);
+        else launch_z_step(s, c->Z[l], c->tmpB, c->d_row_comm, N, Cl, units, M, a.gate);
     });
 }
 
@@ -1517,10 +1542,12 @@ int cadmm_tune(cadmm_ctx* c, const char* key, int32_t value) {
     if (std::strcmp(key, "use_graph") == 0) { c->use_graph = value != 0; return CADMM_OK; }
     const bool k_lowrank = std::strcmp(key, "use_lowrank") == 0, k_spec = std::strcmp(key, "use_speculative") == 0;
     const bool k_split = std::strcmp(key, "gemm_split") == 0, k_refresh = std::strcmp(key, "t1_refresh") == 0;
-    if (k_lowrank || k_spec || k_split || k_refresh) {
+    const bool k_floor = std::strcmp(key, "use_floor_first") == 0;
+    if (k_lowrank || k_spec || k_split || k_refresh || k_floor) {
         // each of these changes the launch sequence of an iteration: captured iterations of this context are dropped
         if (k_lowrank) c->use_lowrank = value != 0;
         else if (k_spec) c->use_speculative = value != 0;
+        else if (k_floor) c->use_floor_first = value;
         else if (k_refresh) { c->t1_refresh = value; c->t1_age = -1; }
         else set_gemm_split(value);                  // process-wide
         drop_graphs(c);

@@ -529,7 +529,10 @@ struct RowWalk {
 // So with a last next layer this one pass over memory is the whole search, and with a hidden one the later passes read
 // the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidate's change, S2.  Bound by HBM traffic.
 // SM: kind of the width Cn.
+// With a gate the search comes in two parts, the rows (launch_z_floor) and, where any community takes a step, the segments:
+// for the rows alone two more launches, for the segments nothing that nobody needs.  `part` says which chunks a launch takes.
 constexpr int kFirstVals = 5;
+enum FirstPart { kBoth = 0, kRowsOnly = 1, kSegmentsOnly = 2 };
 template <int RM>
 __device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int end, double (&s)[kFirstVals]) {
     const RowWalk w(a.Cl);
@@ -552,9 +555,12 @@ __device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int
 }
 
 template <int HID, int SM>
-__global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
+__global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a, int part) {
     __shared__ double sm[kFirstVals * 4];
+    if (part == kRowsOnly && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
+    if (part == kSegmentsOnly && *a.gate == 0) return;
     const int4 ck = a.chunks[blockIdx.x];               // community, kind, first row / segment, one past the last
+    if ((part == kRowsOnly && ck.y != 0) || (part == kSegmentsOnly && ck.y == 0)) return;
     double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (ck.y == 0) {
         if (a.row_sums) {                               // the kernel that formed the gradient left the rows' sums
@@ -568,7 +574,9 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
         else z_first_rows<kNarrow>(a, ck.z, ck.w, s);
     } else {
         const RowWalk w(a.Cn);
-        const double inv = HID ? 1.0 / first_candidate(a.units + ck.x, a.sp) : 0.0;
+        const Unit* const u = a.units + ck.x;           // (launch_z_floor has started the search, or the finishing kernel will)
+        if (part == kSegmentsOnly && u->done) return;
+        const double inv = HID ? 1.0 / (part == kSegmentsOnly ? u->step0 : first_candidate(u, a.sp)) : 0.0;
         for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
             const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
             for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
@@ -601,26 +609,33 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
 // One workgroup per community: adds its chunks' sums in order, applies the step floor and takes the decision (all of
 // them if the whole change is quadratic).
 template <int HID>
-__global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
+__global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a, int part) {
     __shared__ double sm[kFirstVals * 4];
     __shared__ double S[kFirstVals];
     const int unit = blockIdx.x;
+    Unit* u = a.units + unit;
+    if (part == kSegmentsOnly && u->done) return;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
     double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
-    for (int i = c0 + threadIdx.x; i < c1; i += 256)
+    for (int i = c0 + threadIdx.x; i < c1; i += 256) {
+        if (part != kBoth && (a.chunks[i].y == 0) != (part == kRowsOnly)) continue;
 #pragma unroll
         for (int q = 0; q < kFirstVals; ++q) s[q] += a.partials[(int64_t)i * kFirstVals + q];
+    }
     block_sums_to<kFirstVals>(s, sm, S);
     __syncthreads();
     if (threadIdx.x == 0) {
-        Unit* u = a.units + unit;
         const double hnu = 0.5 * (double)a.sp.nu;
-        begin_search(u, a.sp);
-        floor_test(u, S[1], S[2]);
-        if (u->done) return;
-        u->c1 = -2.0 * hnu * S[0];
-        u->c2 = hnu * S[1];
-        if (HID) {
+        if (part != kSegmentsOnly) {
+            begin_search(u, a.sp);
+            floor_test(u, S[1], S[2]);
+            if (u->done) return;
+            u->c1 = -2.0 * hnu * S[0];
+            u->c2 = hnu * S[1];
+        }
+        if (part == kRowsOnly) {
+            atomicOr(a.gate, 1);
+        } else if (HID) {
             const double d = hnu * S[3];
             decide(u, &d, 1, a.sp, a.status);
         } else {
@@ -712,8 +727,9 @@ __device__ __forceinline__ void load_inv(double* s_inv, const Unit* __restrict__
 template <bool LDSU, int RM>
 __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, const float* __restrict__ gradZ,
                                                      const int32_t* __restrict__ row_comm, int64_t N, int Cl,
-                                                     const Unit* __restrict__ units, int M) {
+                                                     const Unit* __restrict__ units, int M, const int32_t* __restrict__ gate) {
     __shared__ double s_inv[LDSU ? kStepUnits : 1];
+    if (gate && *gate == 0) return;
     load_inv<LDSU>(s_inv, units, M);
     const RowWalk w(Cl);
     const int64_t r_step = (int64_t)gridDim.x * w.r_step;
@@ -741,9 +757,11 @@ template <bool LDSU>
 __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__ Zl, const float* __restrict__ Tl,
                                                              const float* __restrict__ SG, const float* __restrict__ Wt,
                                                              float nu, const int32_t* __restrict__ row_comm, int64_t N,
-                                                             int Cl, int Cn, const Unit* __restrict__ units, int M) {
+                                                             int Cl, int Cn, const Unit* __restrict__ units, int M,
+                                                             const int32_t* __restrict__ gate) {
     __shared__ double s_inv[LDSU ? kStepUnits : 1];
     extern __shared__ __align__(16) float s_wt[];        // [Cn][Cl]
+    if (gate && *gate == 0) return;
     if constexpr (LDSU) {
         for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = unit_inv(units + i);
     }
@@ -856,6 +874,7 @@ __device__ __forceinline__ const double* carry_inv(double* s_inv, const CarryArg
 template <int SM>
 __global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, CarryArgs k, int64_t N, int Cn) {
     __shared__ double s_buf[kStepUnits];
+    if (k.gate && *k.gate == 0) return;
     const double* const s_inv = carry_inv(s_buf, k);
     const RowWalk w(Cn);
     const int64_t r_step = (int64_t)gridDim.x * w.r_step;
@@ -887,7 +906,10 @@ __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL,
                                                          float* __restrict__ G) {
     __shared__ double s_buf[CARRY ? kStepUnits : 1];
     const double* s_inv = nullptr;
-    if constexpr (CARRY) s_inv = carry_inv(s_buf, k);
+    const bool carries = CARRY && !(k.gate && *k.gate == 0);
+    if constexpr (CARRY) {
+        if (carries) s_inv = carry_inv(s_buf, k);
+    }
     constexpr int LP = 1 << LPLOG;
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t row = t >> LPLOG;
@@ -954,7 +976,7 @@ __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL,
     str<SM>(ZL + base, j0, CL, x);
     if constexpr (CARRY) {
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
-        if (carry_sum<SM>(acc, k, s_inv, row, CL, j0 >> 2)) {
+        if (carries && carry_sum<SM>(acc, k, s_inv, row, CL, j0 >> 2)) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) c[v] = (float)((double)c[v] - acc[v]);
             str<SM>(TL + base, j0, CL, c);
@@ -1353,17 +1375,19 @@ static void with_mode(int width, F f) {
     else f(std::integral_constant<int, kNarrow>{});
 }
 
-void launch_z_first(hipStream_t s, const ZTrialArgs& a) {
+static void launch_first_part(hipStream_t s, const ZTrialArgs& a, int part) {
     const dim3 grid(a.n_chunks), block(256);
     if (a.n_chunks > 0)
         with_mode(a.Cn, [&](auto sm) {
             constexpr int SM = decltype(sm)::value;
-            if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, SM>), grid, block, 0, s, a);
-            else hipLaunchKernelGGL((z_first_kernel<1, SM>), grid, block, 0, s, a);
+            if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, SM>), grid, block, 0, s, a, part);
+            else hipLaunchKernelGGL((z_first_kernel<1, SM>), grid, block, 0, s, a, part);
         });
-    if (a.next_is_last) hipLaunchKernelGGL((z_first_finish_kernel<0>), dim3(a.M), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((z_first_finish_kernel<1>), dim3(a.M), dim3(256), 0, s, a);
+    if (a.next_is_last) hipLaunchKernelGGL((z_first_finish_kernel<0>), dim3(a.M), dim3(256), 0, s, a, part);
+    else hipLaunchKernelGGL((z_first_finish_kernel<1>), dim3(a.M), dim3(256), 0, s, a, part);
 }
+void launch_z_floor(hipStream_t s, const ZTrialArgs& a) { launch_first_part(s, a, kRowsOnly); }
+void launch_z_first(hipStream_t s, const ZTrialArgs& a) { launch_first_part(s, a, a.gate ? kSegmentsOnly : kBoth); }
 
 void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand) {
     // the pass of four is often needed and takes a grid that fills the chip, the others hardly ever
@@ -1380,25 +1404,25 @@ void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand) {
 }
 
 void launch_z_step(hipStream_t s, float* Zl, const float* gradZ, const int32_t* row_comm, int64_t N, int Cl,
-                   const Unit* units, int M) {
+                   const Unit* units, int M, const int32_t* gate) {
     const int nb = flat_grid(N * (int64_t)Cl);
     with_mode(Cl, [&](auto rm) {
         constexpr int RM = decltype(rm)::value;
-        if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
-        else hipLaunchKernelGGL((z_step_kernel<false, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M);
+        if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M, gate);
+        else hipLaunchKernelGGL((z_step_kernel<false, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M, gate);
     });
 }
 
 void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const float* SG, const float* Wt, float nu,
-                           const int32_t* row_comm, int64_t N, int Cl, int Cn, const Unit* units, int M) {
+                           const int32_t* row_comm, int64_t N, int Cl, int Cn, const Unit* units, int M, const int32_t* gate) {
     // more and smaller workgroups than the reducing kernels use: nothing is reduced here
     int64_t nb = (N * (int64_t)Cl + 2047) / 2048;
     nb = nb < 1 ? 1 : (nb > 4 * kReduceBlocks ? 4 * kReduceBlocks : nb);
     const size_t lds = (size_t)Cn * Cl * sizeof(float);                 // at most 16 x 1024 floats (the low-rank limit)
     if (M <= kStepUnits)
-        hipLaunchKernelGGL((z_step_lowrank_kernel<true>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M);
+        hipLaunchKernelGGL((z_step_lowrank_kernel<true>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
     else
-        hipLaunchKernelGGL((z_step_lowrank_kernel<false>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M);
+        hipLaunchKernelGGL((z_step_lowrank_kernel<false>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
 }
 
 void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int Cn) {

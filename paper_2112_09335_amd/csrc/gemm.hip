@@ -269,7 +269,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
                                                       float* __restrict__ out, int64_t n, int K, int C,
                                                       const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                       float nu, float* __restrict__ Tio, const Unit* unit, int leave_g,
-                                                      double* __restrict__ partials) {
+                                                      double* __restrict__ partials, const int32_t* __restrict__ gate) {
     constexpr int BN = 128;
     constexpr int LDA = BK + 1;
     constexpr int LDB = BN + 4;
@@ -285,6 +285,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
     const int wm = wave >> 1, wn = wave & 1;
     const int ctiles = (C + BN - 1) / BN;
     if constexpr (EPI == 0) {
+        if (gate && *gate == 0) return;
         // gated plain product: Q again for a W search whose speculative step (epilogue 2, Q not stored) was rejected
         if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
     }
@@ -371,7 +372,8 @@ template <int EPI, int SPLIT>
 __global__ __launch_bounds__(256) void gemm_nn_narrow_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                              float* __restrict__ out, int64_t n, int K, int C,
                                                              const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                             float nu, float* __restrict__ relu_out) {
+                                                             float nu, float* __restrict__ relu_out, const int32_t* __restrict__ gate) {
+    if (EPI == 0 && gate && *gate == 0) return;
     constexpr int KS = 32;
     constexpr int LDA = KS + 1;
     constexpr int LDB = 32 + 4;
@@ -567,8 +569,9 @@ template <int EPI, int T, int PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 : 1, T == 2 ? 4 : 8))) void gemm_nn_split_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ out, int64_t n, int K, int C,
     const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
-    int leave_g, double* __restrict__ partials) {
+    int leave_g, double* __restrict__ partials, const int32_t* __restrict__ gate) {
     if constexpr (EPI == 0) {
+        if (gate && *gate == 0) return;
         // gated plain product, as in gemm_nn_kernel
         if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
     }
@@ -1292,16 +1295,16 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
         const dim3 grid((unsigned)gemm_nn_blocks(n, C));
 #define CADMM_NN(K3_, K2_, K1_, K0_) \
         if (epi.kind == 3) \
-            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, 0, nullptr); \
+            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, 0, nullptr, nullptr); \
         else if (epi.kind == 2) \
             hipLaunchKernelGGL(K2_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
-                               epi.leave_g ? 1 : 0, epi.partials); \
+                               epi.leave_g ? 1 : 0, epi.partials, nullptr); \
         else if (epi.kind == 1) \
             hipLaunchKernelGGL(K1_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
-                               0, epi.row_sums); \
+                               0, epi.row_sums, nullptr); \
         else \
             hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
-                               0, nullptr)
+                               0, nullptr, epi.gate)
         if (!g_split) {
             CADMM_NN((gemm_nn_kernel<3>), (gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
         } else if (t == 2) {
@@ -1315,8 +1318,8 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
         const bool few = (n + 127) / 128 < kFewTiles;
         const dim3 grid((unsigned)(few ? (n + 31) / 32 : (n + 127) / 128));
 #define CADMM_NARROW(E_) \
-        if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<E_, 1>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, epi.Tio); \
-        else hipLaunchKernelGGL((gemm_nn_narrow_kernel<E_, 0>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, epi.Tio)
+        if (few) hipLaunchKernelGGL((gemm_nn_narrow_kernel<E_, 1>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, epi.Tio, epi.gate); \
+        else hipLaunchKernelGGL((gemm_nn_narrow_kernel<E_, 0>), grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, epi.Tio, epi.gate)
         if (epi.kind == 3) { CADMM_NARROW(3); }
         else if (epi.kind == 1) { CADMM_NARROW(1); }
         else { CADMM_NARROW(0); }

@@ -14,8 +14,10 @@ namespace cadmm {
 // sums over the tile's columns that the search for theta needs of the gradient g just formed: sum e g with
 // e = Zl - relu(Tl), sum g^2, sum Zl^2 (three doubles at row_sums + (tile * rows + row) * 3), so that the search does not
 // have to read the three N x C_l matrices again.
+// gate (epilogue 0; may be null): the launch does nothing where *gate is 0, see ZTrialArgs.
 struct SpmmEpilogue {
     int kind = 0;
+    const int32_t* gate = nullptr;
     const float* Zl = nullptr;
     const float* Tl = nullptr;
     float nu = 0.f;
@@ -51,7 +53,7 @@ double launch_gather_calibration(hipStream_t s, const SpmmSchedule& sc, int64_t 
                                  float* out);
 // Y[pos[k], :] = val[k] * X[col[k], :] for k < n: the output rows that have a single entry.
 void launch_spmm_single(hipStream_t s, const int32_t* pos, const int32_t* col, const float* val, const float* X,
-                        float* Y, int64_t n, int width);
+                        float* Y, int64_t n, int width, const int32_t* gate = nullptr);
 // columns of the feature matrix handled at a time, if fewer than the launch's own choice (0 = that choice); smaller tiles
 // keep a community's share of the gathered matrix inside one XCD's L2 at the price of re-reading the entries once per tile
 void set_spmm_tile_cols(int cols);
@@ -81,6 +83,7 @@ struct GemmEpilogue {
     float nu = 0.f;
     float* Tio = nullptr;
     const Unit* unit = nullptr;
+    const int32_t* gate = nullptr;   // epilogue 0: nothing is formed where *gate is 0, see ZTrialArgs
     bool leave_g = false;
     double* partials = nullptr;
     double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C) column tiles
@@ -205,26 +208,33 @@ struct ZTrialArgs {
     const float* Gn = nullptr;   // last next layer: G_L = -(U + rho (Z_L - T_L)), read in place of Tn and Zn
     int next_is_last;
     SearchParams sp;
+    // Floor first: the step floor is tested with the rows' sums alone, before anything that only a step needs is formed
+    // (grad W_{l+1}, the segment products), and *gate says whether any community takes one.
+    int32_t* gate = nullptr;
     Unit* units;           // [M]
     double* partials;      // [n_chunks * kRestCand]
     int32_t* status;
 };
-// Starts the searches of all communities and judges the first candidate; with a last next layer, all of them.
+// Starts the searches of all communities and applies the step floor (with row_sums and gate).
+void launch_z_floor(hipStream_t s, const ZTrialArgs& a);
+// Starts the searches of all communities (unless launch_z_floor has) and judges the first candidate; with a last next
+// layer, all of them.
 void launch_z_first(hipStream_t s, const ZTrialArgs& a);
 // The next ncand candidates (4, or rounds of kMaxCand) where the next layer is hidden.
 void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand);
 // Z_l[i,:] -= gradZ[i,:] / theta[comm(i)]
 void launch_z_step(hipStream_t s, float* Zl, const float* gradZ, const int32_t* row_comm, int64_t N, int Cl,
-                   const Unit* units, int M);
+                   const Unit* units, int M, const int32_t* gate);
 // the same step with the gradient in its low-rank form nu (Zl - relu(Tl)) + SG Wt (SG: N x Cn, Wt: Cn x Cl)
 void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const float* SG, const float* Wt, float nu,
-                           const int32_t* row_comm, int64_t N, int Cl, int Cn, const Unit* units, int M);
+                           const int32_t* row_comm, int64_t N, int Cl, int Cn, const Unit* units, int M, const int32_t* gate);
 // Tn[i,:] -= sum over the segments (i,c) of row i of P[(i,c),:] / theta_c  (communities whose step was skipped
 // contribute nothing): the pre-activation of the next layer after the Z step, without a new aggregation.
 struct CarryArgs {
     const float* P = nullptr;
     const int64_t* row_seg_ptr = nullptr; const int32_t* seg_comm = nullptr; const int32_t* seg_pos = nullptr;
     const Unit* units = nullptr; int M = 0;
+    const int32_t* gate = nullptr;       // may be null; where *gate is 0 no community took a step (ZTrialArgs)
 };
 void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int Cn);
 // Last layer (Appendix A, Eq. 5) by J FISTA steps per row, fused with the dual step (Eq. 2):

@@ -135,7 +135,8 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(
     const int4* __restrict__ rec, int64_t nrows, const int2* __restrict__ ent, const float* __restrict__ X,
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
     XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu,
-    double* __restrict__ row_sums, int64_t n_out) {
+    double* __restrict__ row_sums, int64_t n_out, const int32_t* __restrict__ gate) {
+    if (EPI == 0 && gate && *gate == 0) return;
     // Workgroup b belongs to XCD b mod 8 and takes the (b / 8)-th entry of that XCD's slice of the table (or, without
     // the XCD-aware numbering, simply entry b).  Records from nrows on are the parts of split rows.
     const int lpr_log2 = LPRL < 3 ? LPRL : lpr_log2_arg;
@@ -230,7 +231,9 @@ template <int VEC>
 __global__ __launch_bounds__(256) void spmm_single_kernel(const int32_t* __restrict__ pos,
                                                           const int32_t* __restrict__ col,
                                                           const float* __restrict__ val, const float* __restrict__ X,
-                                                          float* __restrict__ Y, int64_t n, int width, int lpr_log2) {
+                                                          float* __restrict__ Y, int64_t n, int width, int lpr_log2,
+                                                          const int32_t* __restrict__ gate) {
+    if (gate && *gate == 0) return;
     const int lpr = 1 << lpr_log2;
     const int sub = threadIdx.x & (lpr - 1);
     const int64_t group = (int64_t)blockIdx.x * (256 >> lpr_log2) + (threadIdx.x >> lpr_log2);
@@ -309,9 +312,9 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
                                                           float* __restrict__ Y, int width,
                                                           const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                           float nu, int lpr_log2, double* __restrict__ row_sums,
-                                                          int n_tiles, int64_t n_out) {
+                                                          int n_tiles, int64_t n_out, const int32_t* __restrict__ gate) {
     const int64_t i = blockIdx.x;
-    if (i >= n_long) return;
+    if (i >= n_long || (EPI == 0 && gate && *gate == 0)) return;
     const int64_t row = long_row[i];
     const int p0 = long_part_ptr[i], p1 = long_part_ptr[i + 1];
     const int lpr = 1 << lpr_log2, groups = 64 >> lpr_log2;
@@ -404,9 +407,9 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         const dim3 grid((unsigned)nb, (unsigned)((width + tile - 1) / tile)), block(256);
 #define CADMM_ROWS(L_) do { \
         if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
-                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, sc.n_out); \
+                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, sc.n_out, nullptr); \
         else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
-                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, 0); } while (0)
+                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, 0, epi.gate); } while (0)
         if (lpr_log2 == 0) CADMM_ROWS(0);
         else if (lpr_log2 == 1) CADMM_ROWS(1);
         else if (lpr_log2 == 2) CADMM_ROWS(2);
@@ -420,10 +423,10 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         if (epi.kind == 1)
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
                                sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2, epi.row_sums,
-                               (width + tile - 1) / tile, sc.n_out);
+                               (width + tile - 1) / tile, sc.n_out, nullptr);
         else
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
-                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, 0, 0);
+                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, 0, 0, epi.gate);
     }
 }
 
@@ -461,7 +464,7 @@ void launch_spmm(hipStream_t s, const SpmmSchedule& sched, const float* X, float
 }
 
 void launch_spmm_single(hipStream_t s, const int32_t* pos, const int32_t* col, const float* val, const float* X,
-                        float* Y, int64_t n, int width) {
+                        float* Y, int64_t n, int width, const int32_t* gate) {
     if (n <= 0 || width <= 0) return;
     const int vec = width >= 4 ? 4 : 1;
     const int lanes_needed = (width + vec - 1) / vec;
@@ -470,8 +473,8 @@ void launch_spmm_single(hipStream_t s, const int32_t* pos, const int32_t* col, c
     const int64_t groups = (n + kSingleBatch - 1) / kSingleBatch;
     const int64_t per_block = 256 >> lpr_log2;
     const int64_t nb = (groups + per_block - 1) / per_block;
-    if (vec == 4) hipLaunchKernelGGL((spmm_single_kernel<4>), dim3((unsigned)nb), dim3(256), 0, s, pos, col, val, X, Y, n, width, lpr_log2);
-    else hipLaunchKernelGGL((spmm_single_kernel<1>), dim3((unsigned)nb), dim3(256), 0, s, pos, col, val, X, Y, n, width, lpr_log2);
+    if (vec == 4) hipLaunchKernelGGL((spmm_single_kernel<4>), dim3((unsigned)nb), dim3(256), 0, s, pos, col, val, X, Y, n, width, lpr_log2, gate);
+    else hipLaunchKernelGGL((spmm_single_kernel<1>), dim3((unsigned)nb), dim3(256), 0, s, pos, col, val, X, Y, n, width, lpr_log2, gate);
 }
 
 }  // namespace cadmm

@@ -175,6 +175,30 @@ def test_graph_replay_equals_plain_launches_bit_for_bit():
     b.close()
 
 
+@pytest.mark.parametrize("name,more", [("three", {}), ("lowrank", {"step_policy": 1}), ("deep", {}), ("ragged", {"schedule": 1, "dual_form": 1})])
+def test_step_floor_tested_first_gives_the_same_iterates_bit_for_bit(name, more):
+    """From the forward pass on the layers far from the last one take no step at first: nothing of what only a step needs is
+    formed then.  One community is cut off from the labels, so that only some communities of a layer step later on."""
+    from paper_2112_09335_amd import binding
+    w = {"three": lambda: synth.config(3, 0.01), "lowrank": lambda: synth.config(4, 0.002), "deep": lambda: synth.config(5, 0.002, M=4),
+         "ragged": lambda: synth.make_workload("floor", 71, 1501, 5, [30, 90, 301, 90, 7], 7, 4, graph="sbm", features="gaussian",
+                                               avg_degree=9, frac_intra=0.8)}[name]()
+    w.hyper.update(more)
+    keep = (w.comm[w.src] != 1) == (w.comm[w.dst] != 1)
+    w.src, w.dst = w.src[keep].copy(), w.dst[keep].copy()
+    w.labels[w.comm == 1] = -1
+    got = []
+    for mode in (0, 2):
+        s = binding.Solver.from_workload(w, 0)
+        s.tune("use_floor_first", mode)
+        s.run(5)
+        tau, theta, trials, _ = s.get_steps()
+        got.append([s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [s.get_U(), tau, theta, trials])
+        s.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def test_the_column_tile_knob_reaches_captured_iterations():
     """The tile width decides the order of an aggregation's sums and who leaves the row sums of the Z search: iterations
     captured before the knob was turned must not be replayed after it."""
