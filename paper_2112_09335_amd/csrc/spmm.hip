@@ -130,8 +130,13 @@ __device__ __forceinline__ void load_chunk(const int2* __restrict__ ent, int64_t
 // LPRL: lanes per gathered row as a power of two (3 stands for 8 and more, lpr_log2_arg then says how many).
 // blockIdx.y: tile of tile_cols columns.  The gathered matrix is walked one column tile after the other where a
 // community's rows of it do not fit an XCD's L2 at full width (see launch_vec).
-template <int VEC, int EPI, int LPRL>
-__global__ __launch_bounds__(256) void spmm_rows_kernel(
+// OFF32: X has at most 2^24 rows and 4 GiB.  A gather is then a uniform base and a 32-bit offset of its lane, made by one
+// 24-bit multiply-add and held in one register, not by a 64-bit multiply-add in two; eight wavefronts per SIMD fit instead
+// of six (they are asked for where a row takes eight lanes and more: 63 registers, not 71).  Over the rows, us before and
+// after: 200000 x 256 249 and 233, x 128 120 and 109, x 33 69 and 60; 500000 x 512 1398 and 1268; 2M power law x 128 2715 and
+// 2465, x 16 456 and 446.
+template <int VEC, int EPI, int LPRL, int OFF32>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EPI == 0 && LPRL == 3 ? 8 : 1, 8))) void spmm_rows_kernel(
     const int4* __restrict__ rec, int64_t nrows, const int2* __restrict__ ent, const float* __restrict__ X,
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
     XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu,
@@ -169,6 +174,7 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(
     // a lane past the last column reads the last columns again without storing them
     const int cc = on && col0 + sub * VEC + VEC <= width ? col0 + sub * VEC : (on ? width : col1) - VEC;
 
+    const uint32_t pitch = 4u * (uint32_t)width, cc4 = 4u * (uint32_t)cc;
     float acc[VEC];
 #pragma unroll
     for (int v = 0; v < VEC; ++v) acc[v] = 0.f;
@@ -190,7 +196,12 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(
         load_chunk<LPRL>(ent, ch, lpr_log2, lane, c, a);
         float x[8][VEC];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) load_vec<VEC>(x[u], X + (int64_t)c[u] * width + cc);
+        for (int u = 0; u < 8; ++u) {
+            if constexpr (OFF32)
+                load_vec<VEC>(x[u], reinterpret_cast<const float*>(reinterpret_cast<const char*>(X) + (__umul24((uint32_t)c[u], pitch) + cc4)));
+            else
+                load_vec<VEC>(x[u], X + (int64_t)c[u] * width + cc);
+        }
 #pragma unroll
         for (int u = 0; u < 8; ++u)
 #pragma unroll
@@ -405,16 +416,19 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
     const int64_t nb = g_xcd_remap ? 8 * longest : (sc.n_blocks[lpr_log2] + 7) / 8 * 8;       // (a multiple of 8 either way)
     if (nb > 0) {
         const dim3 grid((unsigned)nb, (unsigned)((width + tile - 1) / tile)), block(256);
-#define CADMM_ROWS(L_) do { \
-        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
+        const bool off32 = sc.n_out <= (1 << 24) && 4 * sc.n_out * (int64_t)width <= ((int64_t)1 << 32);
+#define CADMM_ROWS(L_) do { if (off32) CADMM_ROWS_OFF(L_, 1); else CADMM_ROWS_OFF(L_, 0); } while (0)
+#define CADMM_ROWS_OFF(L_, O_) do { \
+        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
                                               sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, sc.n_out, nullptr); \
-        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
+        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
                                 lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, 0, epi.gate); } while (0)
         if (lpr_log2 == 0) CADMM_ROWS(0);
         else if (lpr_log2 == 1) CADMM_ROWS(1);
         else if (lpr_log2 == 2) CADMM_ROWS(2);
         else CADMM_ROWS(3);
 #undef CADMM_ROWS
+#undef CADMM_ROWS_OFF
     }
     if (sc.n_long > 0) {
         const dim3 grid((unsigned)sc.n_long), block(64);

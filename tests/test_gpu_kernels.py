@@ -132,6 +132,33 @@ def test_aggregate_in_whole_rows_even_tiles_and_tiles_of_a_line(one_community_ct
     assert rel_err(Y, g.A @ X.astype(np.float64)) < 2e-6
 
 
+@pytest.mark.parametrize("n", [1 << 24, (1 << 24) + 3])
+def test_aggregate_on_both_sides_of_the_32_bit_offsets(n):
+    """Up to 2^24 rows a gather's offset is formed in 32 bits, beyond in 64.  A few edges between far ends of the numbering;
+    a node without edges keeps its row.  Three terms at most per entry: within 1e-6 of their magnitudes."""
+    import torch
+    from paper_2112_09335_amd import binding
+    say("row offsets", n)
+    rng = np.random.default_rng(9)
+    nodes = np.unique(np.concatenate([[0, n - 1, n - 2], rng.integers(0, n, size=997)])).astype(np.int32)
+    src, dst = nodes[:-1], nodes[1:]                       # a path through them
+    src, dst = np.append(src, 0).astype(np.int32), np.append(dst, n - 1).astype(np.int32)
+    s = binding.Solver(0)
+    try:
+        s.build_graph(n, src, dst, 1, None)
+        s.set_model([5, 5, 3], **HYPER)
+        s.set_workspace()
+        for width in (4, 5):
+            X = torch.randn(n, width, device="cuda")
+            Y = s.op_aggregate(X)
+            want = X.clone()
+            x = X[torch.from_numpy(nodes).cuda().long()].double()          # every touched node has two neighbours: 1/3 each
+            want[torch.from_numpy(nodes).cuda().long()] = ((x + x.roll(1, 0) + x.roll(-1, 0)) / 3.0).float()
+            assert (Y - want).abs().max().item() <= 1e-6 * X.abs().max().item()
+    finally:
+        s.close()
+
+
 def test_aggregate_is_exact_on_integers_scaled_by_the_values(ctx):
     """With X = e_j (unit columns) the result reproduces the stored values of A~ bit for bit."""
     s, g, torch = ctx
