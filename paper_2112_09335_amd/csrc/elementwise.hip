@@ -383,37 +383,58 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
     __shared__ double sm[NC * 4];
     if (unit->done) return;
     const double spec_inv = (speculated && unit->spec) ? 1.0 / unit->step0 : 0.0;      // T0 holds T0 - Q/step0: undo
+    // round r's workgroups are their own: the rounds of a small matrix share the chip (2000 x 64, four rounds: 31 us in one
+    // after the other, 5 so), those of a large one follow each other
+    const int r = blockIdx.y;
     double step = unit->step;
-    for (int r = 0; r < rounds; ++r) {
-        double inv[NC], D[NC];
+    for (int j = 0; j < r * NC; ++j) step *= (double)sp.eta;
+    double inv[NC], D[NC];
 #pragma unroll
-        for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; D[j] = 0.0; }
-        for_quads(count, [&](int64_t i, auto w) {
-            const int64_t nv = count - i;
-            float t0v[4], qv[4], zv[4];
-            ldq(t0v, T0 + i, nv, w);
-            ldq(qv, Q + i, nv, w);
-            ldq(zv, Z + i, nv, w);
+    for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; D[j] = 0.0; }
+    for_quads(count, [&](int64_t i, auto w) {
+        const int64_t nv = count - i;
+        float t0v[4], qv[4], zv[4];
+        ldq(t0v, T0 + i, nv, w);
+        ldq(qv, Q + i, nv, w);
+        ldq(zv, Z + i, nv, w);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const double q = (double)qv[v], z = (double)zv[v];
-                const double t0 = (double)t0v[v] + q * spec_inv;
-                const double e0 = fmax(t0, 0.0) - z;
+        for (int v = 0; v < 4; ++v) {
+            const double q = (double)qv[v], z = (double)zv[v];
+            const double t0 = (double)t0v[v] + q * spec_inv;
+            const double e0 = fmax(t0, 0.0) - z;
 #pragma unroll
-                for (int j = 0; j < NC; ++j) {
-                    const double e1 = fmax(t0 - q * inv[j], 0.0) - z;
-                    D[j] += (e1 - e0) * (e1 + e0);
-                }
+            for (int j = 0; j < NC; ++j) {
+                const double e1 = fmax(t0 - q * inv[j], 0.0) - z;
+                D[j] += (e1 - e0) * (e1 + e0);
             }
-        });
-        const double hnu = 0.5 * (double)sp.nu;
+        }
+    });
+    const double hnu = 0.5 * (double)sp.nu;
 #pragma unroll
-        for (int j = 0; j < NC; ++j) D[j] *= hnu;
-        block_sums_to<NC>(D, sm, partials + ((int64_t)blockIdx.x * rounds + r) * NC);
+    for (int j = 0; j < NC; ++j) D[j] *= hnu;
+    block_sums_to<NC>(D, sm, partials + ((int64_t)blockIdx.x * rounds + r) * NC);
+}
+
+// D[q] = sum of partials[i * stride + q] over the blocks i0 <= i < i1 for q < count, by 256 threads (the caller synchronises).  A
+// wavefront takes four values at a time, their loads in flight together (five iterations on
+// 2000 nodes: 46 us in these kernels with one value at a time, 37 so).
+__device__ __forceinline__ void sum_candidates(const double* __restrict__ partials, int i0, int i1, int stride, int count, double* D) {
+    const int lane = threadIdx.x & 63;
+    for (int q0 = (threadIdx.x >> 6) * 4; q0 < count; q0 += 16) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        for (int i = i0 + lane; i < i1; i += 64)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) s[e] += partials[(int64_t)i * stride + (q0 + e < count ? q0 + e : q0)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) s[e] += __shfl_down(s[e], o, 64);
+            if (lane == 0 && q0 + e < count) D[q0 + e] = s[e];
+        }
     }
 }
 
-// Sums the ncand block results (stride per block) of a pass and takes the decision.  Wavefront w takes the candidates w, w + 4, ...
+// Sums the ncand block results (stride per block) of a pass and takes the decision.
 __global__ __launch_bounds__(256) void w_trial_finish_kernel(const double* __restrict__ partials, int nblocks, int ncand,
                                                              SearchParams sp, Unit* unit, int32_t* status) {
     __shared__ double sm[4];
@@ -432,14 +453,7 @@ __global__ __launch_bounds__(256) void w_trial_finish_kernel(const double* __res
         a = block_sum((a + b) + (c + d), sm);
         if (threadIdx.x == 0) D[0] = a;
     } else {
-        const int lane = threadIdx.x & 63;
-        for (int j = threadIdx.x >> 6; j < ncand; j += 4) {
-            double a = 0.0;
-            for (int i = lane; i < nblocks; i += 64) a += partials[(int64_t)i * ncand + j];
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) a += __shfl_down(a, o, 64);
-            if (lane == 0) D[j] = a;
-        }
+        sum_candidates(partials, 0, nblocks, ncand, ncand, D);
     }
     __syncthreads();
     if (threadIdx.x == 0) decide(unit, D, ncand, sp, status);
@@ -1056,19 +1070,34 @@ __global__ __launch_bounds__(256) void argmax_rows_kernel(const float* __restric
 // gradient g of F(z) = R(z, y) + <u, z - c> + rho/2 ||z - c||^2 at y, and for a candidate L the difference
 // F(y - g/L) - F(y), term by term (the log-sum-exp of both points, the linear and the quadratic terms through
 // x - y = -g/L), so that nothing is lost to the cancellation of two nearly equal values of F.
-constexpr int kFistaStride = kMaxCand + 3;        // per chunk: candidate differences, ||g||^2, ||y||^2, F(y)
+constexpr int kFistaSums = 3;                     // per chunk behind the candidates' differences: ||g||^2, ||y||^2, F(y)
 constexpr double kFistaSlack = 1e-12;             // the test accepts up to this relative rounding of F(y)
 
+// The value of the lane that is 2^S away, for the steps of a butterfly over up to sixteen neighbouring lanes: after the steps
+// below S the lanes of a group of 2^S hold the same value, so the mirror image of 8 or 16 lanes serves for 4 and 8.  A lane
+// exchange inside a row of sixteen is a modifier of a move; __shfl_xor goes through LDS, a hundred cycles per step of a chain of
+// dependent reductions.
+template <int S>
+__device__ __forceinline__ double across(double v) {
+    constexpr int ctrl = S == 0 ? 0xB1 : S == 1 ? 0x4E : S == 2 ? 0x141 : 0x140;      // quad 1 0 3 2, quad 2 3 0 1, half mirror, mirror
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), ctrl, 0xF, 0xF, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), ctrl, 0xF, 0xF, true);
+    return __hiloint2double(hi, lo);
+}
 template <int LPLOG>
 __device__ __forceinline__ double group_sum(double v) {
-#pragma unroll
-    for (int o = 1; o < (1 << LPLOG); o <<= 1) v += __shfl_xor(v, o, 64);
+    if constexpr (LPLOG > 0) v += across<0>(v);
+    if constexpr (LPLOG > 1) v += across<1>(v);
+    if constexpr (LPLOG > 2) v += across<2>(v);
+    if constexpr (LPLOG > 3) v += across<3>(v);
     return v;
 }
 template <int LPLOG>
 __device__ __forceinline__ double group_max(double v) {
-#pragma unroll
-    for (int o = 1; o < (1 << LPLOG); o <<= 1) v = fmax(v, __shfl_xor(v, o, 64));
+    if constexpr (LPLOG > 0) v = fmax(v, across<0>(v));
+    if constexpr (LPLOG > 1) v = fmax(v, across<1>(v));
+    if constexpr (LPLOG > 2) v = fmax(v, across<2>(v));
+    if constexpr (LPLOG > 3) v = fmax(v, across<3>(v));
     return v;
 }
 
@@ -1088,7 +1117,7 @@ __device__ __forceinline__ double row_lse(const double (&z)[4], const bool (&ok)
 
 template <int LPLOG, int NC>
 __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage, int more, int rounds, float mom) {
-    __shared__ double sm[NC * 4];
+    __shared__ double sm[(NC + kFistaSums) * 4];
     constexpr int LP = 1 << LPLOG;
     if (more) {                                        // a pass of further candidates: only if some search is pending
         int pending = 0;
@@ -1219,10 +1248,11 @@ __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage
             block_sums_to<NC>(D, sm, a.partials + ((int64_t)ch * rounds + rd) * NC);
             for (int q = 0; q < NC; ++q) L_round *= (double)a.sp.eta;
         } else {
-            double* out = a.partials + (int64_t)ch * kFistaStride;
-            block_sums_to<NC>(D, sm, out);
-            const double t0 = block_sum(sgg, sm), t1 = block_sum(syy, sm), t2 = block_sum(sF, sm);
-            if (threadIdx.x == 0) { out[kMaxCand] = t0; out[kMaxCand + 1] = t1; out[kMaxCand + 2] = t2; }
+            double all[NC + kFistaSums];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) all[q] = D[q];
+            all[NC] = sgg; all[NC + 1] = syy; all[NC + 2] = sF;
+            block_sums_to<NC + kFistaSums>(all, sm, a.partials + (int64_t)ch * (NC + kFistaSums));
         }
         }
     }
@@ -1231,30 +1261,21 @@ __global__ __launch_bounds__(256) void fista_stage_kernel(FistaArgs a, int stage
 // Takes the decisions of a pass.  first_pass: the searches of stage `stage` begin here (the counters of the finished
 // stage are added up, every solve starts from L = rho), the step floor is applied, then the first candidates are judged.
 __global__ __launch_bounds__(256) void fista_finish_kernel(FistaArgs a, int ncand, int first_pass, int stage) {
-    __shared__ double D[kRestCand];
+    __shared__ double D[kRestCand];               // (a first pass has sixteen candidates at most)
     const int unit = blockIdx.x;
     Unit* u = a.units + unit;
     if (!first_pass && u->done) return;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
-    const int lane = threadIdx.x & 63;
-    const int n_val = first_pass ? kFistaStride : ncand;
-    for (int q = threadIdx.x >> 6; q < n_val; q += 4) {       // a wavefront per value
-        if (first_pass && q >= ncand && q < kMaxCand) continue;
-        double s = 0.0;
-        for (int i = c0 + lane; i < c1; i += 64)
-            if (a.chunks[i].y == 0) s += a.partials[(int64_t)i * n_val + q];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) s += __shfl_down(s, o, 64);
-        if (lane == 0) D[q] = s;
-    }
+    const int n_val = first_pass ? ncand + kFistaSums : ncand;       // (the chunks are all of rows)
+    sum_candidates(a.partials, c0, c1, n_val, n_val, D);
     __syncthreads();
     if (threadIdx.x == 0) {
         if (first_pass) {
             if (stage == 0) { u->step = (double)a.rho; u->total = 0; }
             else u->total += u->ntrials;
             u->ntrials = 0; u->done = 0; u->skip = 0; u->keep = u->step;
-            floor_test(u, D[kMaxCand], D[kMaxCand + 1]);
-            u->step0 = kFistaSlack * fabs(D[kMaxCand + 2]);       // kept for the passes of further candidates
+            floor_test(u, D[ncand], D[ncand + 1]);
+            u->step0 = kFistaSlack * fabs(D[ncand + 2]);       // kept for the passes of further candidates
             if (u->done) return;
         }
         decide(u, D, ncand, a.sp, a.status, u->step0);
@@ -1345,7 +1366,7 @@ void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float*
     else if (ncand <= 4)
         hipLaunchKernelGGL((w_trial_kernel<4>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
     else
-        hipLaunchKernelGGL((w_trial_kernel<kMaxCand>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp,
+        hipLaunchKernelGGL((w_trial_kernel<kMaxCand>), dim3(nb, (ncand + kMaxCand - 1) / kMaxCand), dim3(256), 0, s, T0, Q, Z, count, sp,
                            (ncand + kMaxCand - 1) / kMaxCand, unit, partials, speculated);
     const int nc = ncand == 1 ? 1 : ncand <= 4 ? 4 : (ncand + kMaxCand - 1) / kMaxCand * kMaxCand;
     hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, nc, sp, unit, status);
