@@ -1064,6 +1064,145 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 && P
         }
 }
 
+// gemm_tn_split_kernel<1> in larger tiles, for matrices whose rows fill them.  With the prologue a thread holds three
+// operands' numbers in flight, which leaves the 128 x 128 kernel at three wavefronts per SIMD, two barriers per step and 2.3
+// elements to split per matrix instruction.  Here a workgroup forms 256 x 128, a wavefront 128 x 64 of it (128 accumulator
+// registers, two wavefronts per SIMD): half as much to split, three quarters as much to read from LDS, two buffers and one
+// barrier per step, and the next step's numbers are formed and split between the matrix instructions of this one.
+// 500000 x 512 x 512 1657 -> 1332 us, 200000 x 256 x 256 198 -> 162, 20000 x 700 x 512 128 -> 100, 30000 x 480 x 200 71 -> 58,
+// 13752 x 767 x 1000 174 -> 159.  The same tile without the prologue gains 0 to 6 % (the 128 x 128 kernel then fits four
+// wavefronts), and in out = A B it loses to its longer epilogue what it gains: not used there.
+constexpr int kWideM = 4, kWideN = 2;                        // 32 x 32 accumulators of a wavefront
+constexpr int kWideRows = 64 * kWideM, kWideCols = 64 * kWideN;
+constexpr int kWideA = kWideRows * BK, kWideB = kWideCols * BK;        // bf16 of one plane: the tile of A, then that of B
+constexpr int kWideBuf = 3 * (kWideA + kWideB);
+// A tile row's 16 k are two 16-byte halves, swapped in every other group of four rows: the eight lanes that read or write at
+// once hit different banks without padding.  Element of the half that holds k (0 or 8) of row r:
+__device__ __forceinline__ int wide_at(int r, int half) { return r * BK + ((half ^ ((r >> 2) & 1)) << 3); }
+// One step: the products of the tiles in S; after those of accumulator row i, between(i).
+template <class F>
+__device__ __forceinline__ void wide_step(floatx16 (&acc)[kWideM][kWideN], const unsigned short* S, int ao, int bo, F between) {
+    bf16x8 b[kWideN][3], a[2][3];
+    auto load_a = [&](bf16x8 (&x)[3], int i) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) x[p] = *reinterpret_cast<const bf16x8*>(S + ao + p * kWideA + i * 32 * BK);
+    };
+#pragma unroll
+    for (int j = 0; j < kWideN; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) b[j][p] = *reinterpret_cast<const bf16x8*>(S + bo + p * kWideB + j * 32 * BK);
+    load_a(a[0], 0);
+#pragma unroll
+    for (int i = 0; i < kWideM; ++i) {
+        if (i + 1 < kWideM) load_a(a[(i + 1) & 1], i + 1);
+        constexpr int P[6] = {2, 0, 1, 1, 0, 0}, Q[6] = {0, 2, 1, 0, 1, 0};          // smallest terms first
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int j = 0; j < kWideN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i & 1][P[t]], b[j][Q[t]], acc[i][j], 0, 0, 0);
+        between(i);
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void gemm_tn_wide_kernel(const float* __restrict__ A, const float* __restrict__ G,
+                                                              const float* __restrict__ Zl, float nu,
+                                                              float* __restrict__ partial, int64_t n, int K, int C,
+                                                              int64_t rows_per_chunk) {
+    __shared__ __align__(16) unsigned short smem[2 * kWideBuf];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int li = lane & 31, lk = lane >> 5;
+    const int ktiles = (K + kWideRows - 1) / kWideRows;
+    const int ctiles = (C + kWideCols - 1) / kWideCols;
+    int tile;
+    int64_t chunk;
+    xcd_group(blockIdx.x, gridDim.x, (unsigned)(ktiles * ctiles), chunk, tile);
+    const int k0 = (tile / ctiles) * kWideRows;
+    const int c0 = (tile % ctiles) * kWideCols;
+    const int64_t r_begin = chunk * rows_per_chunk;
+    const int64_t r_end = (r_begin + rows_per_chunk < n) ? (r_begin + rows_per_chunk) : n;
+
+    floatx16 acc[kWideM][kWideN];
+#pragma unroll
+    for (int i = 0; i < kWideM; ++i)
+#pragma unroll
+        for (int j = 0; j < kWideN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // columns past the edge repeat the last one: never stored; rows past the chunk: G is set to zero there
+    const int col = tid & (kWideCols - 1);
+    const int rg = __builtin_amdgcn_readfirstlane(tid / kWideCols);
+    const int acol = k0 + tid < K ? k0 + tid : K - 1, gcol = c0 + col < C ? c0 + col : C - 1;
+    float ra[2][8], rgv[8], rz[8];
+    auto fetch_a = [&](int64_t r0, int h) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int64_t r = r0 + 8 * h + e;
+            ra[h][e] = (A + (r < r_end ? r : r_end - 1) * K)[acol];
+        }
+    };
+    auto fetch_g = [&](int64_t r0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int64_t r = r0 + 8 * rg + e, rr = r < r_end ? r : r_end - 1;
+            rgv[e] = (G + rr * C)[gcol];
+            rz[e] = (Zl + rr * C)[gcol];
+        }
+    };
+    const int aw = wide_at(tid, 0), aw8 = wide_at(tid, 1), gw = 3 * kWideA + wide_at(col, rg);
+    auto stash_a = [&](unsigned short* D, int h) { stash_split<8>(D, kWideA, h ? aw8 : aw, ra[h]); };
+    auto stash_g = [&](unsigned short* D, int64_t r0) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) rgv[e] = rgv[e] > 0.f ? nu * (rgv[e] - rz[e]) : 0.f;
+        if (r0 + BK > r_end)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rgv[e] = r0 + 8 * rg + e < r_end ? rgv[e] : 0.f;
+        stash_split<8>(D, kWideB, gw, rgv);
+    };
+    const int ao = wide_at(wm * 32 * kWideM + li, lk), bo = 3 * kWideA + wide_at(wn * 32 * kWideN + li, lk);
+    const int steps = r_begin < r_end ? (int)((r_end - r_begin + BK - 1) / BK) : 0;
+    if (steps > 0) {
+        fetch_a(r_begin, 0);
+        fetch_a(r_begin, 1);
+        fetch_g(r_begin);
+        stash_a(smem, 0);
+        stash_a(smem, 1);
+        stash_g(smem, r_begin);
+        const int64_t r1 = r_begin + BK;
+        fetch_a(r1, 0);                           // (past the chunk's end: its last row again, stored nowhere)
+        fetch_a(r1, 1);
+        fetch_g(r1);
+    }
+    for (int t = 0; t < steps; ++t) {
+        unsigned short* const D = smem + ((t + 1) & 1) * kWideBuf;
+        const int64_t r1 = r_begin + (int64_t)(t + 1) * BK, r2 = r1 + BK;
+        __syncthreads();
+        // (behind the last step the buffer that nobody reads any more is filled once more)
+        wide_step(acc, smem + (t & 1) * kWideBuf, ao, bo, [&](int i) {
+            if (i == 0) { stash_a(D, 0); fetch_a(r2, 0); }
+            if (i == 1) { stash_a(D, 1); fetch_a(r2, 1); }
+            if (i == 2) { stash_g(D, r1); fetch_g(r2); }
+        });
+    }
+    float* dst = partial + chunk * (int64_t)K * C;
+#pragma unroll
+    for (int i = 0; i < kWideM; ++i)
+#pragma unroll
+        for (int j = 0; j < kWideN; ++j) {
+            const int c = c0 + wn * 32 * kWideN + j * 32 + li;
+            if (c >= C) continue;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int k = k0 + wm * 32 * kWideM + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+                if (k < K) dst[(int64_t)k * C + c] = acc[i][j][r];
+            }
+        }
+}
+
 // out = sum of the chunks' partial matrices, in fp64 and in a fixed order.  A workgroup takes 4 X entries: X lanes of four
 // consecutive entries, 256 / X groups of lanes that take the chunks round-robin, four loads in flight each, and are
 // added up in LDS.  X = 16 for large results, 4 for small ones, whose few workgroups would walk many chunks one by one.
@@ -1249,6 +1388,7 @@ struct TnPlan {
     int64_t rows_per_chunk;
     int bn;              // columns per tile: 128, 64 (split product with few workgroups) or 32
     int tiles;
+    bool wide;           // 256 rows of K per tile: gemm_tn_wide_kernel
 };
 
 // The rows are cut into chunks so that about 1024 workgroups share the product, four per compute unit.  A chunk has at
@@ -1259,13 +1399,15 @@ struct TnPlan {
 // 4.6e-7 of the 64-bit product, in 640 rows 182 us and 3.9e-7; 16956 x 476 x 347 in 784 rows 83 us and 4.4e-7, in 256 rows
 // 76 us and 2.6e-7.  They fit the scratch of the shape (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
 constexpr int kTnBlocks = 1024;
-TnPlan tn_plan(int64_t n, int K, int C) {
+// prologue: the right operand is formed on the way.
+TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
     TnPlan p;
     const int64_t base_chunks = (int64_t)gemm_tn_base_floats(n, K, C) / ((int64_t)K * C);
-    auto plan = [&](int bm, int bn) {
+    auto plan = [&](int bm, int bn, int blocks = kTnBlocks) {
         p.bn = bn;
+        p.wide = bm == kWideRows;
         p.tiles = ((K + bm - 1) / bm) * ((C + bn - 1) / bn);
-        int64_t nch = (kTnBlocks + p.tiles - 1) / p.tiles;
+        int64_t nch = (blocks + p.tiles - 1) / p.tiles;
         nch = std::min(nch, (n + 63) / 64);
         nch = std::min(nch, std::max<int64_t>(32, n * (K + C) / (2 * (int64_t)K * C)));
         nch = std::min(nch, (int64_t)gemm_tn_scratch_floats(n, K, C) / ((int64_t)K * C));
@@ -1278,6 +1420,8 @@ TnPlan tn_plan(int64_t n, int K, int C) {
     if (C <= 32) { plan(BM, 32); return p; }
     plan(BM, 128);
     if (g_split && (int64_t)p.nchunks * p.tiles < kFewTiles) plan(64, 64);
+    // (where the last 256 rows would be half empty the tiles cost more than they gain: 384 x 256 138 -> 188 us)
+    else if (g_split && prologue && (K + kWideRows - 1) / kWideRows * 2 == (K + 127) / 128) plan(kWideRows, 128, kTnBlocks / 2);
     return p;
 }
 
@@ -1350,12 +1494,14 @@ int64_t gemm_nn_blocks(int64_t n, int C) {
 int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
                    float* partial, const float* Zl, float nu, const float* W, double* norms) {
     if (K <= 0 || C <= 0) return 0;
-    TnPlan p = tn_plan(n, K, C);
+    TnPlan p = tn_plan(n, K, C, Zl != nullptr);
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.tiles)), block(256);
 #define CADMM_TN(KERNEL_) hipLaunchKernelGGL(KERNEL_, grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk)
     if (p.bn == 64) {
         if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 1, 4>));
         else CADMM_TN((gemm_tn_split_kernel<0, 1, 4>));
+    } else if (p.wide) {
+        CADMM_TN(gemm_tn_wide_kernel);
     } else if (g_split && p.bn == 128) {
         if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 2, 1>));
         else CADMM_TN((gemm_tn_split_kernel<0, 2, 1>));

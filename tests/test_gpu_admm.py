@@ -101,10 +101,11 @@ def copies(w, n):
                           np.tile(w.comm, n), np.tile(w.X, (n, 1)), np.tile(w.labels, n), w.dims, w.W0, w.iters, dict(w.hyper))
 
 
-@pytest.mark.parametrize("dims", [[24, 133, 46, 5], [24, 136, 48, 5]])
+@pytest.mark.parametrize("dims", [[24, 133, 46, 5], [24, 136, 48, 5], [201, 133, 46, 5]])
 def test_many_rows_reach_the_128_column_products(dims):
     """From 512 tiles of 128 x 128 on: the first trial of tau_1 with its step, and the gradient of Z_1 with its row sums over
-    a whole and a partial column tile, at widths with and without a partial last quad."""
+    a whole and a partial column tile, at widths with and without a partial last quad.  201 x 133: the gradient of W_1 in
+    tiles of 256 x 128, chunks that end within a step."""
     w = copies(synth.make_workload("many-rows", 41, 101, 3, dims, dims[-1], 4, graph="sbm", features="gaussian", avg_degree=8,
                                    frac_intra=0.7), 325)
     assert -(-w.N // 128) * -(-dims[1] // 128) >= 512
