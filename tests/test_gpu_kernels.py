@@ -442,6 +442,37 @@ def test_a_capture_of_the_own_stream_leaves_the_order_of_the_calls_around_it():
         b.close()
 
 
+@pytest.mark.parametrize("own", [False, True])
+def test_calls_on_the_null_stream_and_on_another_one_in_turn(own):
+    """The calls share their scratch: one on another stream (a side stream, the context's own) waits for those on the null
+    stream before it, and they for it, although a call on the null stream leaves no event behind."""
+    import torch
+    from paper_2112_09335_amd import binding
+    s = binding.Solver(0)
+    try:
+        side = s.stream if own else torch.cuda.Stream()
+        gen = torch.Generator(device="cuda").manual_seed(3)
+        A = [torch.randn(20000, 256, generator=gen, device="cuda") for _ in range(2)]
+        G = [torch.randn(20000, 200, generator=gen, device="cuda") for _ in range(2)]
+        want = []
+        for a, g in zip(A, G):
+            want.append(s.op_wgrad_noalloc(a, g))
+            torch.cuda.synchronize()
+        out = [torch.empty_like(want[0]) for _ in range(12)]
+        torch.cuda.synchronize()
+        for i, o in enumerate(out):
+            if i % 3 == 2:
+                with torch.cuda.stream(side):
+                    s.op_wgrad_noalloc(A[i % 2], G[i % 2], o)
+            else:
+                s.op_wgrad_noalloc(A[i % 2], G[i % 2], o)
+        torch.cuda.synchronize()
+        for i, o in enumerate(out):
+            assert torch.equal(o, want[i % 2]), i
+    finally:
+        s.close()
+
+
 def test_a_refused_call_between_kernel_calls_on_two_streams_keeps_their_order():
     """set_data makes the own stream wait for the call before it, then refuses the labels and enqueues nothing: a call on a
     third stream still waits for the one on the first, with which it shares the scratch of the partial matrices."""
