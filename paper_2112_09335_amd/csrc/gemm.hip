@@ -116,11 +116,13 @@ __device__ __forceinline__ void xcd_group(unsigned b, unsigned nb, unsigned inne
 // 16-byte pieces of a row of 256 T bytes.
 // EPI 0: out = acc.  EPI 1: out = nu (Zl - relu(Tl)) + acc.  EPI 2: first candidate of the W search and the step
 // on Tio ahead of the decision, see GemmEpilogue.  EPI 3: out (if there is one) = acc, Tio = relu(acc).
+// EPI 4: 2 that leaves G (GemmEpilogue::leave_g); an epilogue of its own, since its registers made the product of 2 spill
+// (2M x 128 x 256: 1444 us without it, 1681 with).
 template <int EPI, int T, int MODE>
 __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                                    float* __restrict__ out, const float* __restrict__ Zl,
                                                    const float* tin, float nu, float* __restrict__ Tio, double inv0,
-                                                   bool take, bool hold, bool leave_g, double& dsum, double* __restrict__ row_sums) {
+                                                   bool take, bool hold, double& dsum, double* __restrict__ row_sums) {
     constexpr int BN = 64 * T;
     constexpr int LDC = BN + 4;
     constexpr int Q = BN / 4;                            // quads per row
@@ -133,7 +135,7 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
     // one result element: returns what goes to out, updates t (EPI 2) and the candidate's sum
     auto finish = [&](float v, float z, float& t) -> float {
         if constexpr (EPI == 1) v = nu * (z - fmaxf(t, 0.f)) + v;
-        if constexpr (EPI == 2) {
+        if constexpr (EPI == 2 || EPI == 4) {
             const double t0 = (double)t, zd = (double)z;
             const double t1 = t0 - (double)v * inv0;
             const double e0 = fmax(t0, 0.0) - zd, e1 = fmax(t1, 0.0) - zd;
@@ -157,7 +159,7 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
 #pragma unroll
         for (int u0 = 0; u0 < PER_T; u0 += 2) {
             float4 z4[2], t4[2];
-            if constexpr (EPI == 1 || EPI == 2) {
+            if constexpr (EPI == 1 || EPI == 2 || EPI == 4) {
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int f = tid + 256 * (u0 + u);
@@ -198,7 +200,7 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 if (row >= n || c >= C) continue;
                 const int64_t o = row * C + c;
                 const int nv = MODE == kFull ? 4 : C - c;       // columns of this lane (four, or the row's last few)
-                if constexpr (EPI == 1 || EPI == 2) {
+                if constexpr (EPI == 1 || EPI == 2 || EPI == 4) {
                     const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
                     t[0] = t4[u].x; t[1] = t4[u].y; t[2] = t4[u].z; t[3] = t4[u].w;
 #pragma unroll
@@ -210,16 +212,15 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 }
                 if constexpr (EPI == 2) {
                     if (take) st4u(Tio + o, t, nv);
-                    if (take || hold) {
-                        if (leave_g) {                                   // (as launch_G_only forms it)
-                            const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
+                    else st4u(out + o, v, nv);
+                } else if constexpr (EPI == 4) {
+                    if (take) st4u(Tio + o, t, nv);
+                    if (take || hold) {                                  // (as launch_G_only forms it)
+                        const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) v[e] = t[e] > 0.f ? nu * (float)((double)t[e] - (double)z[e]) : 0.f;
-                            st4u(out + o, v, nv);
-                        }
-                    } else {
-                        st4u(out + o, v, nv);
+                        for (int e = 0; e < 4; ++e) v[e] = t[e] > 0.f ? nu * (float)((double)t[e] - (double)z[e]) : 0.f;
                     }
+                    st4u(out + o, v, nv);
                 } else if constexpr (EPI == 3) {
                     if (out) st4u(out + o, v, nv);
 #pragma unroll
@@ -237,20 +238,20 @@ template <int EPI, int T>
 __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                               float* __restrict__ out, const float* __restrict__ Zl,
                                               const float* __restrict__ Tl, float nu, float* __restrict__ Tio,
-                                              const Unit* unit, int leave_g, double* __restrict__ partials) {
+                                              const Unit* unit, double* __restrict__ partials) {
     // (epilogue 1 has no partials: the argument then carries the row sums)
     double* const row_sums = EPI == 1 ? partials : nullptr;
     double inv0 = 0.0, dsum = 0.0;
     bool take = false, hold = false;
-    if constexpr (EPI == 2) {
-        hold = unit->skip != 0;
+    if constexpr (EPI == 2 || EPI == 4) {
+        hold = EPI == 4 && unit->skip != 0;
         inv0 = unit->skip ? 0.0 : 1.0 / unit->step0;
         take = unit->spec != 0 && !unit->skip;
     }
-    const float* tin = (EPI == 2) ? Tio : Tl;
-    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, leave_g != 0, dsum, row_sums);
-    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, leave_g != 0, dsum, row_sums);   // (C > 32)
-    if constexpr (EPI == 2) {
+    const float* tin = (EPI == 2 || EPI == 4) ? Tio : Tl;
+    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, dsum, row_sums);
+    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, dsum, row_sums);   // (C > 32)
+    if constexpr (EPI == 2 || EPI == 4) {
         __shared__ double red[4];
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
@@ -263,12 +264,12 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, 
 // ------------------------------------------------------------------------------------------------ NN
 // EPI 1: out = nu * (Zl - relu(Tl)) + A B   (gradient of the Z subproblem, Appendix A)
 // EPI 2: out = Q = A B; first candidate of the W search and speculative step on Tio (Section 3.1), see kernels.h
-// EPI 3: Tio = relu(A B), and out = A B if there is an out
+// EPI 3: Tio = relu(A B), and out = A B if there is an out;  EPI 4: 2, and G where the step is taken ahead or not at all
 template <int EPI>
 __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ A, const float* __restrict__ B,
                                                       float* __restrict__ out, int64_t n, int K, int C,
                                                       const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                      float nu, float* __restrict__ Tio, const Unit* unit, int leave_g,
+                                                      float nu, float* __restrict__ Tio, const Unit* unit,
                                                       double* __restrict__ partials, const int32_t* __restrict__ gate) {
     constexpr int BN = 128;
     constexpr int LDA = BK + 1;
@@ -331,9 +332,9 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
     };
 
     int nk = (K + BK - 1) / BK;
-    if constexpr (EPI == 2) {
-        if (unit->skip) {           // no step is taken: nothing reads Q, the epilogue leaves G of the T that stays
-            if (!leave_g) return;
+    if constexpr (EPI == 2 || EPI == 4) {
+        if (unit->skip) {           // no step is taken: nothing reads Q; epilogue 4 leaves G of the T that stays
+            if (EPI == 2) return;
             nk = 0;
         }
     }
@@ -359,7 +360,7 @@ __global__ __launch_bounds__(256) void gemm_nn_kernel(const float* __restrict__ 
         }
     }
     static_assert(32 * (BN + 4) <= BM * LDA + BK * LDB, "result slab must fit the operand buffer");
-    tile_epilogue<EPI, 2>(acc, smem, m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, leave_g, partials);
+    tile_epilogue<EPI, 2>(acc, smem, m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
 }
 
 // Results of at most 32 columns: bound by reading A, so a step takes 32 columns of it (a whole 128-byte line of every
@@ -569,7 +570,7 @@ template <int EPI, int T, int PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 : 1, T == 2 ? 4 : 8))) void gemm_nn_split_kernel(
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ out, int64_t n, int K, int C,
     const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
-    int leave_g, double* __restrict__ partials, const int32_t* __restrict__ gate) {
+    double* __restrict__ partials, const int32_t* __restrict__ gate) {
     if constexpr (EPI == 0) {
         if (gate && *gate == 0) return;
         // gated plain product, as in gemm_nn_kernel
@@ -644,9 +645,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
         }
     };
     int nk = (K + BK - 1) / BK;
-    if constexpr (EPI == 2) {
+    if constexpr (EPI == 2 || EPI == 4) {
         if (unit->skip) {                         // as in gemm_nn_kernel
-            if (!leave_g) return;
+            if (EPI == 2) return;
             nk = 0;
         }
     }
@@ -667,7 +668,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
             multiply_split<T, LDH>(acc, As, Bs, wm * 32 * T + li, wn * 32 * T + li, lk);
         }
     }
-    tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, leave_g, partials);
+    tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
 }
 
 // out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 16.
@@ -1437,24 +1438,27 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
     if (C > 32) {
         const int t = nn_tile(n, C, g_split);
         const dim3 grid((unsigned)gemm_nn_blocks(n, C));
-#define CADMM_NN(K3_, K2_, K1_, K0_) \
+#define CADMM_NN(K4_, K3_, K2_, K1_, K0_) \
         if (epi.kind == 3) \
-            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, 0, nullptr, nullptr); \
+            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, nullptr, nullptr); \
+        else if (epi.kind == 2 && epi.leave_g) \
+            hipLaunchKernelGGL(K4_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
+                               epi.partials, nullptr); \
         else if (epi.kind == 2) \
             hipLaunchKernelGGL(K2_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
-                               epi.leave_g ? 1 : 0, epi.partials, nullptr); \
+                               epi.partials, nullptr); \
         else if (epi.kind == 1) \
             hipLaunchKernelGGL(K1_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
-                               0, epi.row_sums, nullptr); \
+                               epi.row_sums, nullptr); \
         else \
             hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
-                               0, nullptr, epi.gate)
+                               nullptr, epi.gate)
         if (!g_split) {
-            CADMM_NN((gemm_nn_kernel<3>), (gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
+            CADMM_NN((gemm_nn_kernel<4>), (gemm_nn_kernel<3>), (gemm_nn_kernel<2>), (gemm_nn_kernel<1>), (gemm_nn_kernel<0>));
         } else if (t == 2) {
-            CADMM_NN((gemm_nn_split_kernel<3, 2, 1>), (gemm_nn_split_kernel<2, 2, 1>), (gemm_nn_split_kernel<1, 2, 1>), (gemm_nn_split_kernel<0, 2, 1>));
+            CADMM_NN((gemm_nn_split_kernel<4, 2, 1>), (gemm_nn_split_kernel<3, 2, 1>), (gemm_nn_split_kernel<2, 2, 1>), (gemm_nn_split_kernel<1, 2, 1>), (gemm_nn_split_kernel<0, 2, 1>));
         } else {
-            CADMM_NN((gemm_nn_split_kernel<3, 1, 4>), (gemm_nn_split_kernel<2, 1, 4>), (gemm_nn_split_kernel<1, 1, 4>), (gemm_nn_split_kernel<0, 1, 4>));
+            CADMM_NN((gemm_nn_split_kernel<4, 1, 4>), (gemm_nn_split_kernel<3, 1, 4>), (gemm_nn_split_kernel<2, 1, 4>), (gemm_nn_split_kernel<1, 1, 4>), (gemm_nn_split_kernel<0, 1, 4>));
         }
 #undef CADMM_NN
     } else {

@@ -29,7 +29,7 @@ CLASSES = {
     "spmm_rows_kernel[segments]": [("spmm_rows_kernel", "segments"), ("spmm_combine_kernel", "segments"), ("spmm_single_kernel", None)],
     "gemm_nn_split_kernel<2>+finish": [(r"gemm_nn_split_kernel<2,", None)],
     "gemm_nn_split_kernel<0>": [(r"gemm_nn_split_kernel<0,", None)],
-    "gemm_tn_split_kernel+reduce": [(r"gemm_tn_split_kernel", None)],
+    "gemm_tn_split_kernel+reduce": [(r"gemm_tn_(split|wide)_kernel", None)],
     "gemm_nn_kernel<32>": [(r"gemm_nn_narrow_kernel<0,", None)],
     "gemm_tn_kernel<32>+reduce": [(r"gemm_tn_kernel<32", None)],
     "gemm_nn_gradz_kernel": [(r"gemm_nn_gradz_kernel", None)],
