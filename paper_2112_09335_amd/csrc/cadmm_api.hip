@@ -181,14 +181,15 @@ SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, co
 // product's epilogue, which moves whole 512-byte pieces of rows, than in the aggregation's (a column tile at a time; 500000 x
 // 512: 2140 us with the epilogue, 1320 without), so the product comes last unless the aggregation would be the wider for it.
 // Product last against aggregation last, whole iterations: widths 256, 256 2 % less time (200000 nodes) and 1 % (20000),
-// 128, 128 1 and 0 %; 128, 144 2 and 1 % more, 128, 256 5 and 1 % more, 64, 80 3 and 2 % more; 20, 20 no difference (the
-// narrow product leaves no row sums).
+// 128, 128 1 and 0 %; 128, 144 2 and 1 % more, 128, 256 5 and 1 % more, 64, 80 3 and 2 % more.  Up to 64 equal columns, a tile
+// or two of the aggregation, there is no difference to be seen (five iterations, 200000 nodes: 64, 64 7.86 and 7.83 ms, 48, 48
+// 7.37 and 7.46; 20000 nodes 1.84 and 1.84, 1.78 and 1.79), and the aggregation stays last.
 enum GradPath { kGradLowRank, kGradProduct, kGradAggregate };
 bool low_rank_shape(const cadmm_ctx* c, int l) {
     const int Cl = c->C[l], Cn = c->C[l + 1];
     return Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
 }
-bool product_last(int Cl, int Cn) { return Cn < Cl || (Cn == Cl && Cl > 32); }
+bool product_last(int Cl, int Cn) { return Cn < Cl || (Cn == Cl && Cl > 64); }
 GradPath grad_path(const cadmm_ctx* c, int l) {
     if (c->use_lowrank && low_rank_shape(c, l)) return kGradLowRank;
     return product_last(c->C[l], c->C[l + 1]) ? kGradProduct : kGradAggregate;
