@@ -56,11 +56,11 @@ def load(path):
     return d
 
 
-def steady(v):
+def steady(v, every=False):
     """Mean counter value, mean duration and count of the typical dispatches: those within a factor of two of the median
-    duration (the first iterations and the periodic exact re-evaluations run longer forms of some kernels)."""
+    duration (the first iterations and the periodic exact re-evaluations run longer forms of some kernels).  every: of all dispatches."""
     med = sorted(x[1] for x in v)[len(v) // 2]
-    sel = [x for x in v if 0.5 * med <= x[1] <= 2.0 * med] or v
+    sel = [x for x in v if every or 0.5 * med <= x[1] <= 2.0 * med] or v
     return sum(x[0] for x in sel) / len(sel), sum(x[1] for x in sel) / len(sel), len(sel)
 
 
@@ -81,8 +81,9 @@ def main():
     write_scale = gib / (steady(w[copy[0]])[0] * 1024.0)
     rows = {}
     for k in f:
-        fv, us, n = steady(f[k])
-        wv = steady(w[k])[0] if k in w else 0.0
+        every = k[0].startswith("z_first_kernel")      # its rows and its segments are a launch and a group each
+        fv, us, n = steady(f[k], every)
+        wv = steady(w[k], every)[0] if k in w else 0.0
         rows[k] = dict(fetch=fetch_scale * fv * 1024.0, write=write_scale * wv * 1024.0, us=us, n=n, total_us=us * n)
     # the aggregation over the rows runs several times per iteration, the one over the segments once: of the two most
     # frequent grids of the narrow aggregation kernel the one with more dispatches is the rows
@@ -127,7 +128,7 @@ def main():
         fo.write(f"  python3 traffic_table.py --dir {args.dir} --workload \"{args.workload}\" --out {args.out}\n")
         fo.write(f"measured at commit {commit} (kernel sources {meta['kernel_source_hash']}), {meta['date']}\n")
         fo.write("Counter values are KiB per dispatch between the L2 and the fabric; a row is the mean over the dispatches of that\n"
-                 "kernel and grid within a factor of two of its median duration.  GB = 1e9 bytes.  Calibration: the library's\n"
+                 "kernel and grid within a factor of two of its median duration (z_first_kernel: over all).  GB = 1e9 bytes.  Calibration: the library's\n"
                  f"plain copy of 1 GiB in the same run shows 1/{fetch_scale:.3f} of its size in FETCH_SIZE and 1/{write_scale:.3f} in WRITE_SIZE,\n"
                  "so the counters are multiplied by these factors.\n\n")
         fo.write(f"{'kernel':46s} {'grid':>11s} {'n':>4s} {'fetch GB':>9s} {'write GB':>9s} {'avg us':>9s}\n")
