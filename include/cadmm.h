@@ -256,7 +256,9 @@ int  cadmm_op_calibrate(cadmm_ctx* ctx, int32_t kind, const float* src, float* d
  * stream it runs on; cadmm_profile(ctx, 0) stops that.  cadmm_get_profile synchronises and returns,
  * per class (host arrays of CADMM_PROFILE_CLASSES entries, any may be NULL): elapsed milliseconds,
  * number of timed launch groups, and the algorithmic bytes and flops booked for them (what the
- * operation must move / compute: operands read once, results written once).
+ * operation must move / compute: operands read once, results written once).  Where the step floor finds no step to take
+ * the groups that only a step needs return at once: each is then booked without flops and with the bytes of what it still
+ * does, under the last class ("other") unless that is what its own kernel is for.
  */
 #define CADMM_PROFILE_CLASSES 19
 int  cadmm_profile(cadmm_ctx* ctx, int enable);

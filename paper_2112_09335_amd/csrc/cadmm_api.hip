@@ -25,6 +25,7 @@ constexpr size_t kStaticScratchFloats = (size_t)18 << 20;          // 72 MiB
 static __device__ __align__(256) float scratch[kStaticScratchFloats];
 constexpr int kMaxDevices = 64;
 constexpr size_t kReadoutBytes = 16384;                            // pinned page for small readouts
+constexpr int kProfFlags = 4096;
 static float* g_scratch_ptr[kMaxDevices] = {};                     // device address of `scratch` on GPU d, once looked up
 static std::mutex g_scratch_mutex;
 
@@ -131,8 +132,14 @@ struct cadmm_ctx {
     int64_t large_readouts = 0;
     // optional per-kernel-class timing with HIP events on the context's stream
     bool prof_on = false;
-    struct ProfRec { int cls; hipEvent_t a, b; double bytes, flops; };
+    // Whether a launch does its work may be decided on the device (a step floor): the flag is noted when it is written, and a
+    // record whose launch did not is booked as what remains of it.  flag < 0: the launch always does its work.
+    struct Unless { int flag = -1; int32_t idle_value = 0; int cls = 0; double bytes = 0.0; };
+    struct ProfRec { int cls; hipEvent_t a, b; double bytes, flops; Unless unless; };
     std::vector<ProfRec> prof_recs;
+    std::vector<int32_t*> prof_flags;      // pinned pieces of kProfFlags noted flags each
+    int prof_flags_used = 0;
+    std::vector<int> gate_notes;           // [L]: the note of gates[l] in the present iteration
     std::vector<hipEvent_t> prof_pool;
     double prof_ms[CADMM_PROFILE_CLASSES] = {0};
     int64_t prof_launches[CADMM_PROFILE_CLASSES] = {0};
@@ -372,16 +379,36 @@ hipEvent_t prof_event(cadmm_ctx* c) {
     return e;
 }
 
-// Times the launches enqueued by `body` as one record of class `cls` and books its algorithmic work.
+// Notes a flag of the device at this point of the stream; returns the note's number, -1 where nothing is recorded (or there is no
+// memory for it: the launches then count as done).
+int note_flag(cadmm_ctx* c, const int32_t* flag) {
+    if (!c->prof_on || !flag) return -1;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (c->stream && (hipStreamIsCapturing(c->stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone)) return -1;
+    if ((size_t)c->prof_flags_used == c->prof_flags.size() * kProfFlags) {
+        int32_t* piece = nullptr;
+        if (hipHostMalloc(reinterpret_cast<void**>(&piece), kProfFlags * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            return -1;
+        }
+        c->prof_flags.push_back(piece);
+    }
+    const int note = c->prof_flags_used++;
+    launch_note_flag(c->stream, flag, c->prof_flags[note / kProfFlags] + note % kProfFlags);
+    return note;
+}
+
+// Times the launches enqueued by `body` as one record of class `cls` and books its algorithmic work, or what `unless` says.
+using Unless = cadmm_ctx::Unless;
 template <class F>
-void timed(cadmm_ctx* c, int cls, double bytes, double flops, F body) {
+void timed(cadmm_ctx* c, int cls, double bytes, double flops, F body, const Unless& unless = Unless()) {
     if (!c->prof_on) { body(); return; }
     hipEvent_t a = prof_event(c), b = prof_event(c);
     if (a && b) (void)hipEventRecord(a, c->stream);
     body();
     if (a && b) {
         (void)hipEventRecord(b, c->stream);
-        c->prof_recs.push_back({cls, a, b, bytes, flops});
+        c->prof_recs.push_back({cls, a, b, bytes, flops, unless});
     }
 }
 
@@ -409,11 +436,11 @@ double spmm_bytes(const cadmm_ctx* c, int64_t out_rows, int width, int extra_rea
 }
 
 void gemm_nn(cadmm_ctx* c, const float* A, const float* B, float* out, int64_t n, int K, int C,
-             const GemmEpilogue& epi = GemmEpilogue()) {
+             const GemmEpilogue& epi = GemmEpilogue(), const Unless& unless = Unless()) {
     const int passes = epi.kind == 3 ? (out ? 2 : 1) : epi.kind ? 3 : 1;        // matrices of the result's size that are read or written
     timed(c, C > 32 ? (epi.kind == 1 ? P_GEMM_NN_128_GRADZ : P_GEMM_NN_128) : P_GEMM_NN_32,
           4.0 * ((double)n * K + (double)K * C + (double)n * C * passes), 2.0 * (double)n * K * C,
-          [&] { launch_gemm_nn(c->stream, A, B, out, n, K, C, epi); });
+          [&] { launch_gemm_nn(c->stream, A, B, out, n, K, C, epi); }, unless);
 }
 
 SearchParams search_params(const cadmm_ctx* c) {
@@ -435,14 +462,15 @@ void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpil
 
 // P_{(i,c)} = sum over the entries of row i in community c of A~_ij V_j, one output row per segment, in the
 // (community, row) order: the segments with several entries as a row list, those with one entry as scaled copies.
-void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width, const int32_t* gate = nullptr) {
+void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width, const int32_t* gate = nullptr,
+                        const Unless& unless = Unless()) {
     timed(c, P_SPMM_SEG, spmm_bytes(c, c->hg.n_seg, width, 0), 2.0 * (double)c->hg.nnz * width, [&] {
         SpmmEpilogue e;
         e.gate = gate;
         launch_spmm(c->stream, schedule_of(c, c->d_segs, c->hg.seg_sched), V, P, width, e);
         launch_spmm_single(c->stream, c->d_seg1_pos, c->d_seg1_col, c->d_seg1_val, V, P, (int64_t)c->hg.seg1_pos.size(),
                            width, gate);
-    });
+    }, unless);
 }
 
 bool t1_reusable(const cadmm_ctx* c) { return c->t1_age >= 0 && c->t1_age < c->t1_refresh; }
@@ -552,6 +580,11 @@ CarryArgs carry_args(const cadmm_ctx* c, int l) {
     return k;
 }
 
+// A launch that returns where no community of layer l takes a Z step, see z_gate.
+Unless unless_gated(const cadmm_ctx* c, int l, int cls = P_OTHER, double bytes = 0.0) {
+    return Unless{c->gate_notes[l], 0, cls, bytes};
+}
+
 double carry_bytes(const cadmm_ctx* c, int l) {
     return 4.0 * ((double)c->hg.n_seg * c->C[l] + 2.0 * (double)c->hg.N * c->C[l]) + 8.0 * (double)c->hg.n_seg;
 }
@@ -560,7 +593,7 @@ double carry_bytes(const cadmm_ctx* c, int l) {
 void carry_T(cadmm_ctx* c, int l) {
     if (c->t1_refresh <= 0) return;
     timed(c, P_T_CARRY, carry_bytes(c, l), 0.0,
-          [&] { launch_t_carry(c->stream, c->T[l], carry_args(c, l), c->hg.N, c->C[l]); });
+          [&] { launch_t_carry(c->stream, c->T[l], carry_args(c, l), c->hg.N, c->C[l]); }, unless_gated(c, l - 1));
 }
 
 // The searches of later candidates: four (what a search that has moved usually needs), then sixteen, then the rest up to
@@ -611,6 +644,7 @@ void w_update(cadmm_ctx* c, int l) {
                                        fly ? c->Z[l] : nullptr, c->nu, c->W[l], c->partials);
           });
     timed(c, P_OTHER, 16.0 * n_norms, 0.0, [&] { launch_w_begin(s, c->partials, n_norms, unit, sp); });
+    const int skip = note_flag(c, &unit->skip);                                  // a step below resolution is not taken
     float* Q = c->G[l];                                                          // G_l is no longer needed
     const bool leave_g = !last && leaves_gradient(c, l);
     // T(W - g/tau) = T - Q/tau with Q = A~ Z_{l-1} gradW
@@ -630,7 +664,7 @@ void w_update(cadmm_ctx* c, int l) {
                   GemmEpilogue again;          // Q itself, only if the step was taken ahead and then rejected
                   again.unit = unit;
                   launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, again);
-              });
+              }, Unless{skip, 1, P_OTHER, leave_g ? 12.0 * (double)count : 0.0});
     } else {
         gemm_nn(c, c->H[l], c->gradW, Q, N, K, Cl);
     }
@@ -644,7 +678,8 @@ void w_update(cadmm_ctx* c, int l) {
         later_candidates(c, (double)count, 1, [&](int n) {
             launch_w_trial(s, c->T[l], Q, c->Z[l], count, n, sp, unit, c->partials, c->status, spec ? 1 : 0);
         });
-    });
+    }, Unless{skip, 1, P_OTHER, 0.0});
+    const double unmoved = last ? (c->schedule == 1 ? 4.0 : 5.0) : leave_g && !spec ? 3.0 : 0.0;       // G (and the last layer's old T) is left all the same
     timed(c, P_W_STEP, 4.0 * ((spec ? 0.0 : last ? 7.0 : leave_g ? 5.0 : 3.0) * (double)count + 3.0 * K * Cl), 0.0, [&] {
         // W^{k+1}; T_l = A~ Z^k W^{k+1}; last layer: G_L of that T_L for the Z step of layer L-1
         if (last)
@@ -652,7 +687,7 @@ void w_update(cadmm_ctx* c, int l) {
                                c->schedule == 1 ? nullptr : c->TLprev, c->rho);
         else
             launch_w_step(s, c->W[l], c->Wt[l], c->gradW, K, Cl, c->T[l], Q, count, unit, spec ? 1 : 0, leave_g ? c->Z[l] : nullptr, c->nu);
-    });
+    }, Unless{skip, 1, unmoved > 0.0 ? P_W_STEP : P_OTHER, 4.0 * unmoved * (double)count});
     if (last) c->gl_valid = true;
     else c->gh_valid = false;
 }
@@ -715,23 +750,25 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     a.gate = floor_first(c, l, sum_tiles) ? c->gates + l : nullptr;
     a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
     if (a.gate) timed(c, P_Z_TRIAL, 4.0 * 6.0 * sum_tiles * (double)N, 0.0, [&] { launch_z_floor(s, a); });
+    c->gate_notes[l] = note_flag(c, a.gate);
+    const Unless gated = unless_gated(c, l);
     if (!lowrank) {
         GemmEpilogue ge;
         ge.gate = a.gate;
-        gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn, ge);                // grad W_{l+1}
+        gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn, ge, gated);         // grad W_{l+1}
     }
-    aggregate_segments(c, c->tmpV, c->P, Cn, a.gate);                            // A~_{r,m} (grad W) per segment
+    aggregate_segments(c, c->tmpV, c->P, Cn, a.gate, gated);                            // A~_{r,m} (grad W) per segment
     // one pass reads Z_l, grad, T_l (or their sums) over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
     const double zt_bytes = 4.0 * ((a.gate ? 0.0 : sum_tiles ? 6.0 * sum_tiles * (double)N : 3.0 * (double)N * Cl) +
                                    (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;
     timed(c, P_Z_TRIAL, zt_bytes, 0.0, [&] {
         launch_z_first(s, a);
         if (!next_last) later_candidates(c, (double)c->hg.n_seg * Cn, 1, [&](int n) { launch_z_more(s, a, n); });
-    });
+    }, gated);
     timed(c, P_Z_STEP, 4.0 * (3.0 * (double)N * Cl + (double)N + (lowrank ? (double)N * Cn : 0.0)), 0.0, [&] {
         if (lowrank) launch_z_step_lowrank(s, c->Z[l], c->T[l], c->tmpA, Wt, c->nu, c->d_row_comm, N, Cl, Cn, units, M, a.gate);
         else launch_z_step(s, c->Z[l], c->tmpB, c->d_row_comm, N, Cl, units, M, a.gate);
-    });
+    }, gated);
 }
 
 // last layer Z_L (Eq. 5) and, for dual_form 0, the dual step (Eq. 2), both from Z_L^k, U^k and the T_L in memory
@@ -777,11 +814,12 @@ void last_layer_update(cadmm_ctx* c, bool carry) {
     }
     const bool with_carry = carry && c->t1_refresh > 0;
     const CarryArgs k = with_carry ? carry_args(c, L) : CarryArgs();
-    timed(c, P_LAST_LAYER, 4.0 * (5.0 * (double)N * c->C[L] + (double)N) + (with_carry ? carry_bytes(c, L) : 0.0), 0.0, [&] {
+    const double solve_bytes = 4.0 * (5.0 * (double)N * c->C[L] + (double)N);
+    timed(c, P_LAST_LAYER, solve_bytes + (with_carry ? carry_bytes(c, L) : 0.0), 0.0, [&] {
         launch_last_layer(c->stream, c->Z[L], c->U, c->T[L], c->d_labels, N, c->C[L], c->risk, c->rho, c->J,
                           c->dual_form == 0 ? 1 : 0, with_carry ? &k : nullptr,
                           c->dual_form == 0 ? c->G[L] : nullptr);
-    });
+    }, with_carry ? unless_gated(c, L - 1, P_LAST_LAYER, solve_bytes) : Unless());
     if (with_carry && c->dual_form == 0) c->gl_valid = true;
 }
 
@@ -1058,6 +1096,7 @@ void cadmm_destroy(cadmm_ctx* ctx) {
             if (ctx->stage_free[k]) (void)hipEventDestroy(ctx->stage_free[k]);
         }
         if (ctx->readout) (void)hipHostFree(ctx->readout);
+        for (int32_t* piece : ctx->prof_flags) (void)hipHostFree(piece);
         if (ctx->ev_own) (void)hipEventDestroy(ctx->ev_own);
         if (ctx->ev_op) (void)hipEventDestroy(ctx->ev_op);
     }
@@ -1138,6 +1177,7 @@ int cadmm_set_model(cadmm_ctx* c, const cadmm_model* m) {
     c->schedule = m->schedule;
     c->step_policy = m->step_policy;
     c->fista_mode = m->fista_mode;
+    c->gate_notes.assign(c->L + 1, -1);
     c->agg_first.assign(c->L + 1, 0);
     for (int l = 2; l <= c->L; ++l) c->agg_first[l] = (3 * c->C[l] < c->C[l - 1]) ? 1 : 0;
     c->has_model = true;
@@ -1516,6 +1556,7 @@ int cadmm_profile(cadmm_ctx* c, int enable) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         for (auto& r : c->prof_recs) { c->prof_pool.push_back(r.a); c->prof_pool.push_back(r.b); }
         c->prof_recs.clear();
+        c->prof_flags_used = 0;
         for (int i = 0; i < CADMM_PROFILE_CLASSES; ++i) {
             c->prof_ms[i] = 0; c->prof_launches[i] = 0; c->prof_bytes[i] = 0; c->prof_flops[i] = 0;
         }
@@ -1537,14 +1578,18 @@ int cadmm_get_profile(cadmm_ctx* c, double* ms, int64_t* records, double* bytes,
             (void)hipEventDestroy(r.b);
             continue;
         }
-        c->prof_ms[r.cls] += (double)t;
-        c->prof_launches[r.cls] += 1;
-        c->prof_bytes[r.cls] += r.bytes;
-        c->prof_flops[r.cls] += r.flops;
+        const int note = r.unless.flag;
+        const bool idle = note >= 0 && c->prof_flags[note / kProfFlags][note % kProfFlags] == r.unless.idle_value;
+        const int cls = idle ? r.unless.cls : r.cls;
+        c->prof_ms[cls] += (double)t;
+        c->prof_launches[cls] += 1;
+        c->prof_bytes[cls] += idle ? r.unless.bytes : r.bytes;
+        c->prof_flops[cls] += idle ? 0.0 : r.flops;
         c->prof_pool.push_back(r.a);
         c->prof_pool.push_back(r.b);
     }
     c->prof_recs.clear();
+    c->prof_flags_used = 0;
     for (int i = 0; i < CADMM_PROFILE_CLASSES; ++i) {
         if (ms) ms[i] = c->prof_ms[i];
         if (records) records[i] = c->prof_launches[i];

@@ -1282,6 +1282,8 @@ __global__ __launch_bounds__(256) void fista_finish_kernel(FistaArgs a, int ncan
     }
 }
 
+__global__ void note_flag_kernel(const int32_t* flag, int32_t* note) { *note = *flag; }
+
 __global__ void fill_units_kernel(Unit* units, int n, double step) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
@@ -1509,6 +1511,10 @@ void launch_fista_stage(hipStream_t s, const FistaArgs& a, int stage, int more, 
     else CADMM_FISTA(4);
 #undef CADMM_FISTA
     if (stage < a.J) hipLaunchKernelGGL(fista_finish_kernel, dim3(a.M), dim3(256), 0, s, a, nc * rounds, more ? 0 : 1, stage);
+}
+
+void launch_note_flag(hipStream_t s, const int32_t* flag, int32_t* note) {
+    hipLaunchKernelGGL(note_flag_kernel, dim3(1), dim3(1), 0, s, flag, note);
 }
 
 void launch_fill_units(hipStream_t s, Unit* units, int n, double step) {

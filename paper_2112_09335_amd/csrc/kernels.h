@@ -271,6 +271,8 @@ constexpr int kArgmaxBlocks = 512;
 void launch_argmax_rows(hipStream_t s, const float* T, int32_t* pred, const int32_t* perm, const int32_t* labels, int32_t* hits,
                         int64_t N, int C);
 void launch_fill_units(hipStream_t s, Unit* units, int n, double step);
+// *note (pinned host memory) = *flag, at this point of the stream
+void launch_note_flag(hipStream_t s, const int32_t* flag, int32_t* note);
 // gather / scatter rows between caller order and internal order: dst[r,:] = src[idx[r],:] or dst[idx[r],:] = src[r,:]
 void launch_permute_rows(hipStream_t s, const float* src, float* dst, const int32_t* idx, int64_t N, int C,
                          int scatter);

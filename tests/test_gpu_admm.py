@@ -200,6 +200,38 @@ def test_step_floor_tested_first_gives_the_same_iterates_bit_for_bit(name, more)
         assert np.array_equal(a, b)
 
 
+def test_the_profile_books_only_what_ran():
+    """From the forward pass on most layers take no step at first, and what only a step needs returns at once: neither its flops
+    nor its bytes are booked, and its records are no records of its kernel's class."""
+    from paper_2112_09335_amd import binding
+    w = synth.config(5, 0.002, M=4)
+    s = binding.Solver.from_workload(w, 0)
+    try:
+        s.tune("use_floor_first", 2)
+        nnz, seen = s.graph_sizes()[0], set()
+        for it in range(10):
+            s.profile(True)
+            s.run(1)
+            prof = s.get_profile()
+            s.profile(False)
+            trials = s.get_steps()[2]
+            moved_W = trials[:w.L] > 0
+            moved_Z = (trials[w.L:].reshape(w.L - 1, w.M) > 0).any(axis=1)           # layers 1 .. L-1
+            trial = next(p for name, p in prof.items() if name.endswith("+finish"))
+            hidden = [l for l in range(1, w.L) if moved_W[l - 1]]
+            assert trial["records"] == len(hidden)
+            assert trial["flops"] == sum(2.0 * w.N * w.dims[l - 1] * w.dims[l] for l in hidden)
+            seg, stepped = prof["spmm_rows_kernel[segments]"], [l for l in range(1, w.L) if moved_Z[l - 1]]
+            assert seg["records"] == len(stepped)
+            assert seg["flops"] == sum(2.0 * nnz * w.dims[l + 1] for l in stepped)
+            assert prof["z_step_kernel"]["records"] == len(stepped)
+            assert prof["t_carry_kernel"]["records"] == len([l for l in stepped if l + 1 < w.L])
+            seen |= set(moved_W[:-1]) | set(moved_Z)
+        assert seen == {True, False}                     # (both were met)
+    finally:
+        s.close()
+
+
 def test_the_column_tile_knob_reaches_captured_iterations():
     """The tile width decides the order of an aggregation's sums and who leaves the row sums of the Z search: iterations
     captured before the knob was turned must not be replayed after it."""
