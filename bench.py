@@ -124,22 +124,31 @@ def class_entries(prof):
 
 def mfma_leg(steps, warmup):
     """The wide products on the GEMM-heavy configuration (8 layers of 512 units, N = 500 000), both product paths:
-    achieved rate per kernel class against the matrix-core peak of the dtype it issues."""
+    achieved rate per kernel class against the matrix-core peak of the dtype it issues.  From the forward pass on an
+    iteration's steps reach one layer further back each time, and a layer without a step skips most of its products: both
+    paths start from the initial weights and are timed once every layer steps."""
     import torch
     from paper_2112_09335_amd import binding, synth
     w = synth.config(5)
+    warmup = max(warmup, w.L + 1)
     solver = binding.Solver.from_workload(w, 0)
     out = {"workload": f"configs[4] {w.name}", "N": w.N, "widths": w.dims, "steps": steps, "paths": {}}
     try:
         for split in (1, 0):
             solver.tune("gemm_split", split)
+            solver.init(w.W0)
             dt, prof, _ = timed_run(solver, steps, warmup)
+            trials = solver.get_steps()[2]
+            moving = int((trials[:w.L] > 0).sum()), int((trials[w.L:].reshape(w.L - 1, w.M) > 0).any(axis=1).sum())
             kernels = [{k: e[k] for k in ("kernel", "issued", "achieved", "peak", "unit", "frac", "avg_launch_ms", "launches",
                                           "share_of_step") if k in e}
                        | ({"fp32_product_TFLOPs": e["fp32_product_TFLOPs"]} if "fp32_product_TFLOPs" in e else {})
                        for e in class_entries(prof) if e["bound"] == "mfma"]
             out["paths"]["bf16_split" if split else "fp32"] = dict(gemm_split=split, iterations_per_s=steps / dt,
-                                                                  ms_per_step=1e3 * dt / steps, kernels=kernels)
+                                                                  ms_per_step=1e3 * dt / steps,
+                                                                  warmup=warmup,
+                                                                  layers_with_a_W_step=moving[0],
+                                                                  layers_with_a_Z_step=moving[1], kernels=kernels)
         # what the matrix cores issue from registers alone on this box: the ceiling the fractions above are read against
         out["calibration"] = {
             "fp32_mfma_TFLOPs": solver.op_calibrate("mfma", 20000, 3),
