@@ -1018,6 +1018,11 @@ int on_op_stream(cadmm_ctx* c, const char* what, F body) {
         c->own_busy = true;
         return check_launch(c, what);
     }
+    if (!c->op_stream) {
+        int current = c->device;
+        HIP_TRY(c, hipGetDevice(&current));
+        if (current != c->device) return fail(c, CADMM_EHIP, std::string(what) + ": the null stream is that of another device, which is current");
+    }
     for (hipEvent_t* e : {&c->ev_own, &c->ev_op})
         if (!*e) HIP_TRY(c, make_event(c, e));
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
