@@ -120,9 +120,9 @@ struct cadmm_ctx {
     // Kernel-level calls on a stream of the caller's (cadmm_op_stream): such a call is launched there, after what the context's
     // own stream holds (own_busy: something may still run on it) and after the kernel-level call before it; whatever uses
     // the own stream next waits for it (op_busy).  op_unrecorded: the last of them was on the null stream, and the event that
-    // stands for it is recorded when somebody has to wait.
+    // stands for it is recorded when somebody has to wait; op_streams: that has happened, and every call has its event.
     hipStream_t op_stream = nullptr;
-    bool op_stream_set = false, op_busy = false, op_unrecorded = false, own_busy = false;
+    bool op_stream_set = false, op_busy = false, op_unrecorded = false, op_streams = false, own_busy = false;
     hipEvent_t ev_own = nullptr, ev_op = nullptr;
     // pinned host memory, allocated when first needed and freed with the context: two pieces through which large transfers
     // are pipelined, and a page for readouts of a few values
@@ -981,7 +981,7 @@ hipError_t record_op(cadmm_ctx* c) {
         (void)hipThreadExchangeStreamCaptureMode(&mode);
     }
     if (current != c->device) (void)hipSetDevice(current);
-    if (e == hipSuccess) c->op_unrecorded = false;
+    if (e == hipSuccess) { c->op_unrecorded = false; c->op_streams = true; }
     return e;
 }
 
@@ -1008,8 +1008,10 @@ hipError_t own_stream(cadmm_ctx* c) {
 // a small product).  A stream that is being captured is the exception: work of the context's stream cannot be waited for
 // from inside a capture, so there the context's stream is drawn into the capture and back.
 // Calls on the null stream follow each other there, and it is never destroyed: one waits for another only where the stream
-// changes.  Without a workspace nothing else of the context can be waiting for them, and the event is not recorded with
-// every call (2000 x 256 x 64: 11.4 -> 8.8 us a call).
+// changes.  Without a workspace nothing else of the context can be waiting for them, and until a call goes to another stream
+// the event is not recorded with every call (2000 x 256 x 64: 11.4 -> 8.8 us a call).  The first call on another stream then waits
+// for whatever the null stream holds by that time; from it on each call has its event behind it, so that a call waits for
+// the one before it and not for what the program has put on the null stream since.
 template <class F>
 int on_op_stream(cadmm_ctx* c, const char* what, F body) {
     if (!c->op_stream_set || c->op_stream == c->stream) {
@@ -1053,7 +1055,7 @@ int on_op_stream(cadmm_ctx* c, const char* what, F body) {
     c->stream = c->op_stream;
     body();
     c->stream = own;
-    c->op_unrecorded = !c->op_stream && !c->has_ws;
+    c->op_unrecorded = !c->op_stream && !c->has_ws && !c->op_streams;
     if (!c->op_unrecorded) HIP_TRY(c, hipEventRecord(c->ev_op, c->op_stream));
     c->own_busy = false;             // what the own stream held comes before what this stream holds now
     c->op_busy = true;

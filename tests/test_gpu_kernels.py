@@ -445,7 +445,7 @@ def test_a_capture_of_the_own_stream_leaves_the_order_of_the_calls_around_it():
 @pytest.mark.parametrize("own", [False, True])
 def test_calls_on_the_null_stream_and_on_another_one_in_turn(own):
     """The calls share their scratch: one on another stream (a side stream, the context's own) waits for those on the null
-    stream before it, and they for it, although a call on the null stream leaves no event behind."""
+    stream before it, and they for it, although the calls before the first change of stream leave no event behind."""
     import torch
     from paper_2112_09335_amd import binding
     s = binding.Solver(0)
@@ -469,6 +469,40 @@ def test_calls_on_the_null_stream_and_on_another_one_in_turn(own):
         torch.cuda.synchronize()
         for i, o in enumerate(out):
             assert torch.equal(o, want[i % 2]), i
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("mode", ["global", "relaxed"])
+def test_the_first_change_of_stream_while_some_other_stream_is_captured(mode):
+    """The event behind calls on the null stream is recorded when the first call goes to another stream: also where the thread
+    is capturing a stream that has nothing to do with either.  The capture is whole and replays give the eager result."""
+    import torch
+    from paper_2112_09335_amd import binding
+    s = binding.Solver(0)
+    try:
+        A, G = torch.randn(20000, 256, device="cuda"), torch.randn(20000, 200, device="cuda")
+        x, y = torch.randn(1000, device="cuda"), torch.zeros(1000, device="cuda")
+        side, captured = torch.cuda.Stream(), torch.cuda.Stream()
+        out = [torch.empty(256, 200, device="cuda") for _ in range(2)]
+        want = A.double().t() @ G.double()
+        torch.cuda.synchronize()
+        for _ in range(20):
+            s.op_wgrad_noalloc(A, G, out[0])
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=captured, capture_error_mode=mode):
+            torch.add(x, 1.0, out=y)
+            with torch.cuda.stream(side):
+                s.op_wgrad_noalloc(A, G, out[1])
+            y.mul_(2.0)
+        torch.cuda.synchronize()
+        for o in out:
+            assert (o - want).norm() <= 1e-5 * want.norm()
+        for k in range(3):
+            x.add_(1.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(y, (x + 1.0) * 2.0), k
     finally:
         s.close()
 

@@ -68,3 +68,25 @@ assert not any(w == "record-elsewhere" for w, a, b in log), log
 assert rec.hipSetDevice(0) == 0
 assert call(None)[0] == 0
 """)
+
+
+def test_a_call_on_another_stream_waits_for_the_call_before_it_and_not_for_the_null_stream(recorder):
+    """Calls on the null stream alone enqueue their kernels and nothing else.  Once a call has gone to another stream, every call has
+    its event right behind its kernels: the next one on another stream waits for that event, and records nothing on the null
+    stream, where the program's own work may have been enqueued in between."""
+    recorder("""
+for _ in range(3):
+    rc, log = call(None)
+    assert rc == 0 and [w for w, _, _ in log] == ["launch"], log
+rc, log = call(A)                                    # the first change: the event is recorded now, whatever the thread captures
+assert [w for w, _, _ in log] == ["record-relaxed", "wait", "launch", "record"], log
+assert log[1] == ("wait", A, log[0][1]) and log[3] == ("record", log[0][1], A)
+ev = log[0][1]
+for other in (B, OWN, A, A):
+    for _ in range(2):
+        rc, log = call(None)
+        assert log[-2:] == [("launch", 0, 0), ("record", ev, 0)], log
+    rc, log = call(other)
+    assert log[:2] == [("wait", other, ev), ("launch", other, 0)], log
+    assert not any(w.startswith("record") and b == 0 for w, _, b in log), log
+""")
