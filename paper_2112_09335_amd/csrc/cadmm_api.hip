@@ -419,7 +419,8 @@ SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, co
     sc.rec = d.rec; sc.ent = d.ent;
     sc.n_long = rs.n_long(); sc.long_row = d.long_row; sc.long_part_ptr = d.long_ptr;
     sc.side = c->side;
-    sc.n_out = c->hg.N;
+    sc.n_out = &rs == &c->hg.seg_sched ? c->hg.n_seg : c->hg.N;
+    sc.n_cols = c->hg.N;
     sc.group_rows = c->hg.group_rows;
     for (int l = 0; l < 7; ++l) {
         sc.blocks[l] = d.blocks[l];

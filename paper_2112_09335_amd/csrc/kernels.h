@@ -39,6 +39,7 @@ struct SpmmSchedule {
     const int32_t* long_part_ptr = nullptr;
     float* side = nullptr;
     int64_t n_out = 0;             // output rows
+    int64_t n_cols = 0;            // rows of the gathered matrix
     double group_rows = 0.0;       // rows of the community an average gather goes to
     const int4* blocks[7] = {};
     int64_t n_blocks[7] = {};

@@ -416,7 +416,7 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
     const int64_t nb = g_xcd_remap ? 8 * longest : (sc.n_blocks[lpr_log2] + 7) / 8 * 8;       // (a multiple of 8 either way)
     if (nb > 0) {
         const dim3 grid((unsigned)nb, (unsigned)((width + tile - 1) / tile)), block(256);
-        const bool off32 = sc.n_out <= (1 << 24) && 4 * sc.n_out * (int64_t)width <= ((int64_t)1 << 32);
+        const bool off32 = sc.n_cols <= (1 << 24) && 4 * sc.n_cols * (int64_t)width <= ((int64_t)1 << 32);
 #define CADMM_ROWS(L_) do { if (off32) CADMM_ROWS_OFF(L_, 1); else CADMM_ROWS_OFF(L_, 0); } while (0)
 #define CADMM_ROWS_OFF(L_, O_) do { \
         if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \

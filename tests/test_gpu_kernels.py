@@ -132,13 +132,15 @@ def test_aggregate_in_whole_rows_even_tiles_and_tiles_of_a_line(one_community_ct
     assert rel_err(Y, g.A @ X.astype(np.float64)) < 2e-6
 
 
-@pytest.mark.parametrize("n", [1 << 24, (1 << 24) + 3])
-def test_aggregate_on_both_sides_of_the_32_bit_offsets(n):
-    """Up to 2^24 rows a gather's offset is formed in 32 bits, beyond in 64.  A few edges between far ends of the numbering;
-    a node without edges keeps its row.  Three terms at most per entry: within 1e-6 of their magnitudes."""
+@pytest.mark.parametrize("n,widths", [(1 << 24, (4, 5, 16, 32)), ((1 << 24) + 3, (4, 5, 16, 32)), (1 << 22, (256,)), ((1 << 22) + 3, (256,)),
+                                      (1 << 18, (4096,)), ((1 << 18) + 1, (4096, 4095))])
+def test_aggregate_on_both_sides_of_the_32_bit_offsets(n, widths):
+    """Up to 2^24 rows and 4 GiB a gather's offset is formed in 32 bits, beyond in 64: one to many lanes per gathered row, few rows
+    of many columns and the other way round.  A few edges between far ends of the numbering; a node without edges
+    keeps its row.  Three terms at most per entry: within 1e-6 of their magnitudes."""
     import torch
     from paper_2112_09335_amd import binding
-    say("row offsets", n)
+    say("row offsets", n, widths)
     rng = np.random.default_rng(9)
     nodes = np.unique(np.concatenate([[0, n - 1, n - 2], rng.integers(0, n, size=997)])).astype(np.int32)
     src, dst = nodes[:-1], nodes[1:]                       # a path through them
@@ -146,15 +148,16 @@ def test_aggregate_on_both_sides_of_the_32_bit_offsets(n):
     s = binding.Solver(0)
     try:
         s.build_graph(n, src, dst, 1, None)
-        s.set_model([5, 5, 3], **HYPER)
+        s.set_model([max(widths), 5, 3], **HYPER)
         s.set_workspace()
-        for width in (4, 5):
+        for width in widths:
             X = torch.randn(n, width, device="cuda")
             Y = s.op_aggregate(X)
             want = X.clone()
             x = X[torch.from_numpy(nodes).cuda().long()].double()          # every touched node has two neighbours: 1/3 each
             want[torch.from_numpy(nodes).cuda().long()] = ((x + x.roll(1, 0) + x.roll(-1, 0)) / 3.0).float()
-            assert (Y - want).abs().max().item() <= 1e-6 * X.abs().max().item()
+            assert want.sub_(Y).abs_().max().item() <= 1e-6 * X.abs().max().item()
+            del X, Y, want
     finally:
         s.close()
 
