@@ -559,17 +559,20 @@ void eval_scalars(cadmm_ctx* c) {
     c->scal_valid = true;
 }
 
-// Whether the Z search of layer l tests the step floor before grad W_{l+1} and the segment products are formed.  From the
+// How the Z search of hidden layer l goes about it: what its gradient and everything after that depends on.
+// gate: the step floor is tested before grad W_{l+1} and the segment products are formed (null: with the search).  From the
 // forward pass on an iteration's steps reach one layer further back each time; until then a layer's gradient is below
 // resolution, and without a step in any community nothing of what only a step needs is formed.  That costs two launches
 // (9 us in every iteration): 1 % and less of an iteration from 2^24 entries on (65536 x 256: 0.9 ms).
-bool floor_first(const cadmm_ctx* c, int l, int sum_tiles) {
-    return sum_tiles > 0 && (c->use_floor_first == 2 || (c->use_floor_first == 1 && c->hg.N * (int64_t)c->C[l] >= (int64_t)1 << 24));
-}
-const int32_t* z_gate(const cadmm_ctx* c, int l) {
-    int tiles = sum_tiles_of(c, l, grad_path(c, l));
-    if (tiles > c->row_sum_tiles) tiles = 0;
-    return floor_first(c, l, tiles) ? c->gates + l : nullptr;
+struct ZSearch { GradPath path; int sum_tiles; int32_t* gate; };
+ZSearch z_search(const cadmm_ctx* c, int l) {
+    ZSearch z;
+    z.path = grad_path(c, l);
+    z.sum_tiles = sum_tiles_of(c, l, z.path);
+    if (z.sum_tiles > c->row_sum_tiles) z.sum_tiles = 0;      // (the tiles' width was tuned since the workspace was laid out)
+    const bool large = c->hg.N * (int64_t)c->C[l] >= (int64_t)1 << 24;
+    z.gate = z.sum_tiles > 0 && (c->use_floor_first == 2 || (c->use_floor_first == 1 && large)) ? c->gates + l : nullptr;
+    return z;
 }
 
 CarryArgs carry_args(const cadmm_ctx* c, int l) {
@@ -577,11 +580,11 @@ CarryArgs carry_args(const cadmm_ctx* c, int l) {
     k.P = c->Pbuf[(l - 1) & 1];
     k.row_seg_ptr = c->d_row_seg_ptr; k.seg_comm = c->d_seg_comm; k.seg_pos = c->d_seg_pos;
     k.units = c->unitsZ + (size_t)(l - 2) * c->hg.M; k.M = c->hg.M;
-    k.gate = z_gate(c, l - 1);
+    k.gate = z_search(c, l - 1).gate;
     return k;
 }
 
-// A launch that returns where no community of layer l takes a Z step, see z_gate.
+// A launch that returns where no community of layer l takes a Z step, see ZSearch.
 Unless unless_gated(const cadmm_ctx* c, int l, int cls = P_OTHER, double bytes = 0.0) {
     return Unless{c->gate_notes[l], 0, cls, bytes};
 }
@@ -715,10 +718,10 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     // With a very narrow next layer the gradient is never stored: its consumers (the product with
     // W_{l+1}, the search, the step) rebuild it per element from Z_l, T_l and the N x C_{l+1} factor
     // A~ G_{l+1}, which removes a full write and two full reads of an N x C_l matrix.
-    const GradPath path = grad_path(c, l);
+    const ZSearch how = z_search(c, l);
+    const GradPath path = how.path;
     const bool lowrank = path == kGradLowRank;
-    int sum_tiles = sum_tiles_of(c, l, path);
-    if (sum_tiles > c->row_sum_tiles) sum_tiles = 0;          // (the tiles' width was tuned since the workspace was laid out)
+    const int sum_tiles = how.sum_tiles;
     double* const row_sums = sum_tiles ? c->row_sums : nullptr;
     if (lowrank) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
@@ -748,7 +751,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     a.Tn = c->T[l + 1]; a.Zn = c->Z[l + 1]; a.P = c->P; a.Cn = Cn;
     a.Gn = c->G[l + 1];
     a.next_is_last = next_last;
-    a.gate = floor_first(c, l, sum_tiles) ? c->gates + l : nullptr;
+    a.gate = how.gate;
     a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
     if (a.gate) timed(c, P_Z_TRIAL, 4.0 * 6.0 * sum_tiles * (double)N, 0.0, [&] { launch_z_floor(s, a); });
     c->gate_notes[l] = note_flag(c, a.gate);
