@@ -112,6 +112,56 @@ def test_many_rows_reach_the_128_column_products(dims):
     run_case(w, 6, "many-rows/" + "-".join(map(str, dims)))
 
 
+@pytest.mark.parametrize("policy", [0, 1])
+@pytest.mark.parametrize("dims,n", [([24, 133, 136, 5], 325), ([201, 480, 400, 5], 163)])
+def test_two_wide_layers_of_many_rows_take_every_branch_of_the_w_step(dims, n, policy):
+    """Layer 2 from 512 tiles of 128 x 128 on: the product that leaves G_2 beside its first trial, where the search takes no step,
+    accepts what was taken ahead, and (steps that may shrink) rejects it.  480 x 400: the gradient of W_2 in several tiles of
+    256 x 128, the last one partial in either direction."""
+    from paper_2112_09335_amd import binding
+    w = copies(synth.make_workload("many-rows", 41, 101, 3, dims, dims[-1], 4, graph="sbm", features="gaussian", avg_degree=8,
+                                   frac_intra=0.7), n)
+    w.hyper["step_policy"] = policy
+    tiles = lambda a, b, t: -(-a // t) * -(-b // 128)
+    assert tiles(w.N, dims[2], 128) >= 512
+    if dims[1] > 256:
+        K, C = dims[1:3]
+        assert 2 * -(-K // 256) == -(-K // 128)                            # the rows of W fill tiles of 256
+        assert min(1024 // tiles(K, C, 128), w.N * (K + C) // (2 * K * C)) * tiles(K, C, 128) >= 512      # and tiles of 128 would do
+        assert tiles(K, C, 256) > 4 and K % 256 and C % 128
+    say(f"[two-wide/{dims}/{policy}] N={w.N}")
+    solver, orc, trials = binding.Solver.from_workload(w, 0), make_oracle(w), []
+    try:
+        for k in range(6):
+            step_with_relu_ties(solver, orc, f"two-wide/{dims}/{policy} it{k + 1}")
+            trials.append(int(solver.get_steps()[2][1]))
+            say(f"it{k + 1} ok, candidates of the W search of layer 2: {trials[-1]}")
+    finally:
+        solver.close()
+    ahead = [after for before, after in zip(trials, trials[1:]) if before == 1]         # what followed an accepted first candidate
+    assert 0 in trials and (max(ahead) > 1 if policy else 1 in ahead), trials
+
+
+@pytest.mark.parametrize("start,candidates", [(40, 21 + 16), (52, 21 + 32)])
+@pytest.mark.parametrize("n", [20, 90])
+def test_the_last_candidates_of_a_search_come_in_rounds(n, start, candidates):
+    """tau_1 starts 2^start too small: the search accepts in the second round of sixteen candidates of its last pass or in a later
+    one.  2.7e5 entries, where all candidates are one pass, and 1.2e6, where it comes behind passes of four and sixteen."""
+    from paper_2112_09335_amd import binding
+    w = copies(synth.make_workload("late", 41, 101, 3, [24, 133, 5], 5, 4, graph="sbm", features="gaussian", avg_degree=8,
+                                   frac_intra=0.7), n)
+    w.hyper.update(tau0=1e-3 * 2.0 ** -start, max_backtrack=64)
+    say("late candidates", w.N, start)
+    solver, orc, trials = binding.Solver.from_workload(w, 0), make_oracle(w), []
+    try:
+        for k in range(4):
+            step_with_relu_ties(solver, orc, f"late{n}/{start} it{k + 1}")
+            trials.append(int(solver.get_steps()[2][0]))
+    finally:
+        solver.close()
+    assert max(trials) > candidates, trials
+
+
 def test_backtracking_cap_status_and_resume_are_consistent():
     from paper_2112_09335_amd import binding
     w = synth.config(1, 0.5)
