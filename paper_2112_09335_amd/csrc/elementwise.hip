@@ -384,7 +384,8 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
     if (unit->done) return;
     const double spec_inv = (speculated && unit->spec) ? 1.0 / unit->step0 : 0.0;      // T0 holds T0 - Q/step0: undo
     // round r's workgroups are their own: the rounds of a small matrix share the chip (2000 x 64, four rounds: 31 us in one
-    // after the other, 5 so), those of a large one follow each other
+    // after the other, 5 so); those of a large one fill it by themselves, and where its search is over, as it mostly is in this
+    // pass, 4 x 2048 workgroups have left after 4.4 us, as 2048 have
     const int r = blockIdx.y;
     double step = unit->step;
     for (int j = 0; j < r * NC; ++j) step *= (double)sp.eta;
@@ -416,8 +417,8 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
 }
 
 // D[q] = sum of partials[i * stride + q] over the blocks i0 <= i < i1 for q < count, by 256 threads (the caller synchronises).  A
-// wavefront takes four values at a time, their loads in flight together (five iterations on
-// 2000 nodes: 46 us in these kernels with one value at a time, 37 so).
+// wavefront takes four values at a time, their loads in flight together (five iterations on 2000 nodes: 46 us in these kernels
+// with one value at a time, 37 so).
 __device__ __forceinline__ void sum_candidates(const double* __restrict__ partials, int i0, int i1, int stride, int count, double* D) {
     const int lane = threadIdx.x & 63;
     for (int q0 = (threadIdx.x >> 6) * 4; q0 < count; q0 += 16) {
