@@ -1066,10 +1066,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 && P
 }
 
 // gemm_tn_split_kernel<1> in larger tiles, for matrices whose rows fill them.  With the prologue a thread holds three
-// operands' numbers in flight, which leaves the 128 x 128 kernel at three wavefronts per SIMD, two barriers per step and 2.3
-// elements to split per matrix instruction.  Here a workgroup forms 256 x 128, a wavefront 128 x 64 of it (128 accumulator
-// registers, two wavefronts per SIMD): half as much to split, three quarters as much to read from LDS, two buffers and one
-// barrier per step, and the next step's numbers are formed and split between the matrix instructions of this one.
+// operands' numbers in flight, which leaves the 128 x 128 kernel at three wavefronts per SIMD; per step it has two barriers and
+// 24 matrix instructions of a wavefront for 16 numbers to split per lane and 12 LDS reads of 16 bytes.  Here a workgroup forms
+// 256 x 128, a wavefront 128 x 64 of it (128 accumulator registers, two wavefronts per SIMD): 48 matrix instructions for 24 numbers
+// and 18 reads, three quarters as much of either, two buffers and one barrier per step, and the next step's numbers are formed and
+// split between the matrix instructions of this one.
 // 500000 x 512 x 512 1657 -> 1332 us, 200000 x 256 x 256 198 -> 162, 20000 x 700 x 512 128 -> 100, 30000 x 480 x 200 71 -> 58,
 // 13752 x 767 x 1000 174 -> 159.  The same tile without the prologue gains 0 to 6 % (the 128 x 128 kernel then fits four
 // wavefronts), and in out = A B it loses to its longer epilogue what it gains: not used there.
@@ -1396,9 +1397,9 @@ struct TnPlan {
 // least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.  The sums over a
 // chunk's rows are in fp32, their error grows with its length: whatever the tile and these limits ask for, there are no
 // fewer chunks than at the base (128-row tiles, 256 rows).  Longer chunks would be faster with the prologue, whose
-// registers let the chip hold 768 workgroups and not 1024, but not as accurate: 13752 x 767 x 1000 in 864 rows 157 us and
-// 4.6e-7 of the 64-bit product, in 640 rows 182 us and 3.9e-7; 16956 x 476 x 347 in 784 rows 83 us and 4.4e-7, in 256 rows
-// 76 us and 2.6e-7.  They fit the scratch of the shape (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
+// registers let the chip hold 768 workgroups and not 1024, but not as accurate: with 128 x 128 tiles 13752 x 767 x 1000 in
+// 864 rows 157 us and 4.6e-7 of the 64-bit product, in 640 rows 182 us and 3.9e-7; 16956 x 476 x 347 in 784 rows 83 us and 4.4e-7,
+// in 256 rows 76 us and 2.6e-7.  They fit the scratch of the shape (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
 constexpr int kTnBlocks = 1024;
 // prologue: the right operand is formed on the way.
 TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
