@@ -362,8 +362,8 @@ enum ProfClass {
     P_G_ONLY, P_W_TRIAL, P_Z_TRIAL, P_W_STEP, P_Z_STEP, P_LAST_LAYER, P_T_CARRY, P_GEMM_GRADZ, P_OTHER
 };
 const char* kProfNames[CADMM_PROFILE_CLASSES] = {
-    "spmm_rows_kernel[rows]", "spmm_rows_kernel[rows,gradz]", "spmm_rows_kernel[segments]", "gemm_nn_kernel<128,0>",
-    "gemm_nn_kernel<128,1>", "gemm_nn_kernel<128,2>+finish", "gemm_nn_kernel<32>", "gemm_tn_kernel<128>+reduce", "gemm_tn_kernel<32>+reduce",
+    "spmm_rows_kernel[rows]", "spmm_rows_kernel[rows,gradz]", "spmm_rows_kernel[segments]", "gemm_nn_kernel<128,0|3>",
+    "gemm_nn_kernel<128,1>", "gemm_nn_kernel<128,2|4>+finish", "gemm_nn_kernel<32>", "gemm_tn_kernel<128>+reduce", "gemm_tn_kernel<32>+reduce",
     "phi_G_kernel", "G_only_kernel",
     "w_trial_kernel", "z_trial_kernel", "w_step_kernel", "z_step_kernel", "last_layer_kernel", "t_carry_kernel",
     "gemm_nn_gradz_kernel", "other"};
@@ -1612,11 +1612,11 @@ int cadmm_get_profile(cadmm_ctx* c, double* ms, int64_t* records, double* bytes,
 
 const char* cadmm_profile_class_name(int32_t cls) {
     if (cls < 0 || cls >= CADMM_PROFILE_CLASSES) return "";
-    if (get_gemm_split()) {                      // the wide products run as the bf16-split kernel: name that symbol
-        if (cls == P_GEMM_NN_128) return "gemm_nn_split_kernel<0>";
+    if (get_gemm_split()) {                      // the wide products run as the bf16-split kernels: name those
+        if (cls == P_GEMM_NN_128) return "gemm_nn_split_kernel<0|3>";
         if (cls == P_GEMM_NN_128_GRADZ) return "gemm_nn_split_kernel<1>";
-        if (cls == P_GEMM_NN_128_TRIAL) return "gemm_nn_split_kernel<2>+finish";
-        if (cls == P_GEMM_TN) return "gemm_tn_split_kernel+reduce";
+        if (cls == P_GEMM_NN_128_TRIAL) return "gemm_nn_split_kernel<2|4>+finish";
+        if (cls == P_GEMM_TN) return "gemm_tn_split|wide_kernel+reduce";
     }
     return kProfNames[cls];
 }
