@@ -12,6 +12,7 @@
 // of them by two sums where the change is quadratic in 1/step), the finishing kernel picks the first that
 // passes the test  value(step) - value(0) <= -||grad||^2 / (2 step)  and marks the search done; later passes
 // see the flag and return at once.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -383,37 +384,36 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
     __shared__ double sm[NC * 4];
     if (unit->done) return;
     const double spec_inv = (speculated && unit->spec) ? 1.0 / unit->step0 : 0.0;      // T0 holds T0 - Q/step0: undo
-    // round r's workgroups are their own: the rounds of a small matrix share the chip (2000 x 64, four rounds: 31 us in one
-    // after the other, 5 so); those of a large one fill it by themselves, and where its search is over, as it mostly is in this
-    // pass, 4 x 2048 workgroups have left after 4.4 us, as 2048 have
-    const int r = blockIdx.y;
     double step = unit->step;
-    for (int j = 0; j < r * NC; ++j) step *= (double)sp.eta;
-    double inv[NC], D[NC];
+    for (int j = 0; j < (int)blockIdx.y * NC; ++j) step *= (double)sp.eta;
+    for (int r = blockIdx.y; r < rounds; r += gridDim.y) {          // (side by side or one after the other: launch_w_trial)
+        double inv[NC], D[NC];
 #pragma unroll
-    for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; D[j] = 0.0; }
-    for_quads(count, [&](int64_t i, auto w) {
-        const int64_t nv = count - i;
-        float t0v[4], qv[4], zv[4];
-        ldq(t0v, T0 + i, nv, w);
-        ldq(qv, Q + i, nv, w);
-        ldq(zv, Z + i, nv, w);
+        for (int j = 0; j < NC; ++j) { inv[j] = 1.0 / step; step *= (double)sp.eta; D[j] = 0.0; }
+        for_quads(count, [&](int64_t i, auto w) {
+            const int64_t nv = count - i;
+            float t0v[4], qv[4], zv[4];
+            ldq(t0v, T0 + i, nv, w);
+            ldq(qv, Q + i, nv, w);
+            ldq(zv, Z + i, nv, w);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const double q = (double)qv[v], z = (double)zv[v];
-            const double t0 = (double)t0v[v] + q * spec_inv;
-            const double e0 = fmax(t0, 0.0) - z;
+            for (int v = 0; v < 4; ++v) {
+                const double q = (double)qv[v], z = (double)zv[v];
+                const double t0 = (double)t0v[v] + q * spec_inv;
+                const double e0 = fmax(t0, 0.0) - z;
 #pragma unroll
-            for (int j = 0; j < NC; ++j) {
-                const double e1 = fmax(t0 - q * inv[j], 0.0) - z;
-                D[j] += (e1 - e0) * (e1 + e0);
+                for (int j = 0; j < NC; ++j) {
+                    const double e1 = fmax(t0 - q * inv[j], 0.0) - z;
+                    D[j] += (e1 - e0) * (e1 + e0);
+                }
             }
-        }
-    });
-    const double hnu = 0.5 * (double)sp.nu;
+        });
+        const double hnu = 0.5 * (double)sp.nu;
 #pragma unroll
-    for (int j = 0; j < NC; ++j) D[j] *= hnu;
-    block_sums_to<NC>(D, sm, partials + ((int64_t)blockIdx.x * rounds + r) * NC);
+        for (int j = 0; j < NC; ++j) D[j] *= hnu;
+        block_sums_to<NC>(D, sm, partials + ((int64_t)blockIdx.x * rounds + r) * NC);
+        for (int j = 0; j < ((int)gridDim.y - 1) * NC; ++j) step *= (double)sp.eta;
+    }
 }
 
 // D[q] = sum of partials[i * stride + q] over the blocks i0 <= i < i1 for q < count, by 256 threads (the caller synchronises).  A
@@ -1368,9 +1368,16 @@ void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float*
         hipLaunchKernelGGL((w_trial_kernel<1>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
     else if (ncand <= 4)
         hipLaunchKernelGGL((w_trial_kernel<4>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
-    else
-        hipLaunchKernelGGL((w_trial_kernel<kMaxCand>), dim3(nb, (ncand + kMaxCand - 1) / kMaxCand), dim3(256), 0, s, T0, Q, Z, count, sp,
-                           (ncand + kMaxCand - 1) / kMaxCand, unit, partials, speculated);
+    else {
+        // The rounds of a small matrix share the chip (2000 x 64, four rounds: 31 us in one after the other, 5 so), up to as many
+        // workgroups as a large one has in a single round.  Those of a large one follow each other: each round fills the chip by
+        // itself, and where the search is over, as it mostly is in this pass, 2048 workgroups that leave at once and the
+        // launch behind them take 3.1 us, 4 x 2048 4.4.
+        const int rounds = (ncand + kMaxCand - 1) / kMaxCand;
+        const int side_by_side = std::max(1, std::min(rounds, kReduceBlocks / nb));
+        hipLaunchKernelGGL((w_trial_kernel<kMaxCand>), dim3(nb, side_by_side), dim3(256), 0, s, T0, Q, Z, count, sp, rounds, unit,
+                           partials, speculated);
+    }
     const int nc = ncand == 1 ? 1 : ncand <= 4 ? 4 : (ncand + kMaxCand - 1) / kMaxCand * kMaxCand;
     hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, nc, sp, unit, status);
 }

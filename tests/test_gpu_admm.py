@@ -143,10 +143,11 @@ def test_two_wide_layers_of_many_rows_take_every_branch_of_the_w_step(dims, n, p
 
 
 @pytest.mark.parametrize("start,candidates", [(40, 21 + 16), (52, 21 + 32)])
-@pytest.mark.parametrize("n", [20, 90])
+@pytest.mark.parametrize("n", [20, 44, 60, 90])
 def test_the_last_candidates_of_a_search_come_in_rounds(n, start, candidates):
     """tau_1 starts 2^start too small: the search accepts in the second round of sixteen candidates of its last pass or in a later
-    one.  2.7e5 entries, where all candidates are one pass, and 1.2e6, where it comes behind passes of four and sixteen."""
+    one.  262 to 1181 workgroups a round: four, three or two rounds side by side, or one after the other; the smallest has all
+    candidates in one pass, the others come to it behind passes of four and sixteen."""
     from paper_2112_09335_amd import binding
     w = copies(synth.make_workload("late", 41, 101, 3, [24, 133, 5], 5, 4, graph="sbm", features="gaussian", avg_degree=8,
                                    frac_intra=0.7), n)
