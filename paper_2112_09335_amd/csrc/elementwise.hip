@@ -545,7 +545,10 @@ struct RowWalk {
 // the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidate's change, S2.  Bound by HBM traffic.
 // SM: kind of the width Cn.
 // With a gate the search comes in two parts, the rows (launch_z_floor) and, where any community takes a step, the segments:
-// for the rows alone two more launches, for the segments nothing that nobody needs.  `part` says which chunks a launch takes.
+// for the rows alone two more launches, for the segments nothing that nobody needs.  PART says which chunks a launch takes.
+// PART and GATED (here and below) are template parameters since a branch at a kernel's start, taken or not, keeps the other
+// arguments from being loaded beside what it looks at: with them and gemm_nn_narrow_kernel's the iterations of a small run that has no
+// gate take 191.0 us, without them 192.1 (20000 nodes, 500-128-3).
 constexpr int kFirstVals = 5;
 enum FirstPart { kBoth = 0, kRowsOnly = 1, kSegmentsOnly = 2 };
 template <int RM>
@@ -569,13 +572,13 @@ __device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int
     }
 }
 
-template <int HID, int SM>
-__global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a, int part) {
+template <int HID, int SM, int PART>
+__global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
     __shared__ double sm[kFirstVals * 4];
-    if (part == kRowsOnly && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
-    if (part == kSegmentsOnly && *a.gate == 0) return;
+    if (PART == kRowsOnly && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
+    if (PART == kSegmentsOnly && *a.gate == 0) return;
     const int4 ck = a.chunks[blockIdx.x];               // community, kind, first row / segment, one past the last
-    if ((part == kRowsOnly && ck.y != 0) || (part == kSegmentsOnly && ck.y == 0)) return;
+    if ((PART == kRowsOnly && ck.y != 0) || (PART == kSegmentsOnly && ck.y == 0)) return;
     double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
     if (ck.y == 0) {
         if (a.row_sums) {                               // the kernel that formed the gradient left the rows' sums
@@ -590,8 +593,8 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a, int part) {
     } else {
         const RowWalk w(a.Cn);
         const Unit* const u = a.units + ck.x;           // (launch_z_floor has started the search, or the finishing kernel will)
-        if (part == kSegmentsOnly && u->done) return;
-        const double inv = HID ? 1.0 / (part == kSegmentsOnly ? u->step0 : first_candidate(u, a.sp)) : 0.0;
+        if (PART == kSegmentsOnly && u->done) return;
+        const double inv = HID ? 1.0 / (PART == kSegmentsOnly ? u->step0 : first_candidate(u, a.sp)) : 0.0;
         for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
             const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
             for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
@@ -623,17 +626,17 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a, int part) {
 
 // One workgroup per community: adds its chunks' sums in order, applies the step floor and takes the decision (all of
 // them if the whole change is quadratic).
-template <int HID>
-__global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a, int part) {
+template <int HID, int PART>
+__global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
     __shared__ double sm[kFirstVals * 4];
     __shared__ double S[kFirstVals];
     const int unit = blockIdx.x;
     Unit* u = a.units + unit;
-    if (part == kSegmentsOnly && u->done) return;
+    if (PART == kSegmentsOnly && u->done) return;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
     double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
     for (int i = c0 + threadIdx.x; i < c1; i += 256) {
-        if (part != kBoth && (a.chunks[i].y == 0) != (part == kRowsOnly)) continue;
+        if (PART != kBoth && (a.chunks[i].y == 0) != (PART == kRowsOnly)) continue;
 #pragma unroll
         for (int q = 0; q < kFirstVals; ++q) s[q] += a.partials[(int64_t)i * kFirstVals + q];
     }
@@ -641,14 +644,14 @@ __global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a, int p
     __syncthreads();
     if (threadIdx.x == 0) {
         const double hnu = 0.5 * (double)a.sp.nu;
-        if (part != kSegmentsOnly) {
+        if (PART != kSegmentsOnly) {
             begin_search(u, a.sp);
             floor_test(u, S[1], S[2]);
             if (u->done) return;
             u->c1 = -2.0 * hnu * S[0];
             u->c2 = hnu * S[1];
         }
-        if (part == kRowsOnly) {
+        if (PART == kRowsOnly) {
             atomicOr(a.gate, 1);
         } else if (HID) {
             const double d = hnu * S[3];
@@ -739,12 +742,14 @@ __device__ __forceinline__ void load_inv(double* s_inv, const Unit* __restrict__
 }
 
 // Z_{l,m} <- Z_{l,m} - grad / theta_{l,m}; the loads of a row are issued before its community is known.
-template <bool LDSU, int RM>
+template <bool LDSU, int RM, bool GATED>
 __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, const float* __restrict__ gradZ,
                                                      const int32_t* __restrict__ row_comm, int64_t N, int Cl,
                                                      const Unit* __restrict__ units, int M, const int32_t* __restrict__ gate) {
     __shared__ double s_inv[LDSU ? kStepUnits : 1];
-    if (gate && *gate == 0) return;
+    if constexpr (GATED) {
+        if (*gate == 0) return;
+    }
     load_inv<LDSU>(s_inv, units, M);
     const RowWalk w(Cl);
     const int64_t r_step = (int64_t)gridDim.x * w.r_step;
@@ -768,7 +773,7 @@ __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, con
 // the order in which gemm_nn_gradz_kernel formed it for the search; a lane group handles two rows per trip with every load issued before the first use.  The rows of W_{l+1}^T
 // live in LDS, not in 64 registers per lane: the kernel is a plain in-place update of Z_l and needs the wavefronts in
 // flight that a small register footprint allows (5 TB/s against 4.4 with the rows in registers).
-template <bool LDSU>
+template <bool LDSU, bool GATED>
 __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__ Zl, const float* __restrict__ Tl,
                                                              const float* __restrict__ SG, const float* __restrict__ Wt,
                                                              float nu, const int32_t* __restrict__ row_comm, int64_t N,
@@ -776,7 +781,9 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
                                                              const int32_t* __restrict__ gate) {
     __shared__ double s_inv[LDSU ? kStepUnits : 1];
     extern __shared__ __align__(16) float s_wt[];        // [Cn][Cl]
-    if (gate && *gate == 0) return;
+    if constexpr (GATED) {
+        if (*gate == 0) return;
+    }
     if constexpr (LDSU) {
         for (int i = threadIdx.x; i < M; i += 256) s_inv[i] = unit_inv(units + i);
     }
@@ -886,10 +893,12 @@ __device__ __forceinline__ const double* carry_inv(double* s_inv, const CarryArg
     return s_inv;
 }
 
-template <int SM>
+template <int SM, bool GATED>
 __global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, CarryArgs k, int64_t N, int Cn) {
     __shared__ double s_buf[kStepUnits];
-    if (k.gate && *k.gate == 0) return;
+    if constexpr (GATED) {
+        if (*k.gate == 0) return;
+    }
     const double* const s_inv = carry_inv(s_buf, k);
     const RowWalk w(Cn);
     const int64_t r_step = (int64_t)gridDim.x * w.r_step;
@@ -914,14 +923,15 @@ __global__ __launch_bounds__(256) void t_carry_kernel(float* __restrict__ Tn, Ca
 // whose smooth part is the whole objective: x_j = y_j - grad(y_j)/Lip, Lip = rho + (1/2 | 1).
 // CARRY: T_L is then brought to the new Z_{L-1} (carry_sum) and, with G, the gradient G_L = -(U + rho (Z_L - T_L)) of the
 // next iteration is left, all while the row is in registers: one launch and no second pass over Z_L, U and T_L.
-template <int LPLOG, int CARRY, int SM>
+template <int LPLOG, int CARRY, int SM, bool GATED>
 __global__ __launch_bounds__(256) void last_layer_kernel(float* __restrict__ ZL, float* __restrict__ U, float* __restrict__ TL,
                                                          const int32_t* __restrict__ labels, int64_t N, int CL,
                                                          int risk, float rho, int J, int update_u, CarryArgs k,
                                                          float* __restrict__ G) {
     __shared__ double s_buf[CARRY ? kStepUnits : 1];
     const double* s_inv = nullptr;
-    const bool carries = CARRY && !(k.gate && *k.gate == 0);
+    bool carries = CARRY;
+    if constexpr (GATED) carries = *k.gate != 0;
     if constexpr (CARRY) {
         if (carries) s_inv = carry_inv(s_buf, k);
     }
@@ -1405,20 +1415,31 @@ static void with_mode(int width, F f) {
     else if (width >= 4) f(std::integral_constant<int, kTail>{});
     else f(std::integral_constant<int, kNarrow>{});
 }
-
-static void launch_first_part(hipStream_t s, const ZTrialArgs& a, int part) {
-    const dim3 grid(a.n_chunks), block(256);
-    if (a.n_chunks > 0)
-        with_mode(a.Cn, [&](auto sm) {
-            constexpr int SM = decltype(sm)::value;
-            if (a.next_is_last) hipLaunchKernelGGL((z_first_kernel<0, SM>), grid, block, 0, s, a, part);
-            else hipLaunchKernelGGL((z_first_kernel<1, SM>), grid, block, 0, s, a, part);
-        });
-    if (a.next_is_last) hipLaunchKernelGGL((z_first_finish_kernel<0>), dim3(a.M), dim3(256), 0, s, a, part);
-    else hipLaunchKernelGGL((z_first_finish_kernel<1>), dim3(a.M), dim3(256), 0, s, a, part);
+// calls f with a condition as an integral constant
+template <class F>
+static void with_flag(bool is, F f) {
+    if (is) f(std::true_type{});
+    else f(std::false_type{});
 }
-void launch_z_floor(hipStream_t s, const ZTrialArgs& a) { launch_first_part(s, a, kRowsOnly); }
-void launch_z_first(hipStream_t s, const ZTrialArgs& a) { launch_first_part(s, a, a.gate ? kSegmentsOnly : kBoth); }
+
+template <int PART>
+static void launch_first_part(hipStream_t s, const ZTrialArgs& a) {
+    const dim3 grid(a.n_chunks), block(256);
+    const auto go = [&](auto hid, auto sm) {
+        constexpr int HID = decltype(hid)::value, SM = decltype(sm)::value;
+        if (a.n_chunks > 0) hipLaunchKernelGGL((z_first_kernel<HID, SM, PART>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((z_first_finish_kernel<HID, PART>), dim3(a.M), block, 0, s, a);
+    };
+    const std::integral_constant<int, 0> last;
+    const std::integral_constant<int, 1> hidden;
+    if constexpr (PART == kRowsOnly) go(last, std::integral_constant<int, kFull>{});        // (the rows know nothing of the next layer)
+    else with_mode(a.Cn, [&](auto sm) { a.next_is_last ? go(last, sm) : go(hidden, sm); });
+}
+void launch_z_floor(hipStream_t s, const ZTrialArgs& a) { launch_first_part<kRowsOnly>(s, a); }
+void launch_z_first(hipStream_t s, const ZTrialArgs& a) {
+    if (a.gate) launch_first_part<kSegmentsOnly>(s, a);
+    else launch_first_part<kBoth>(s, a);
+}
 
 void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand) {
     // the pass of four is often needed and takes a grid that fills the chip, the others hardly ever
@@ -1439,8 +1460,11 @@ void launch_z_step(hipStream_t s, float* Zl, const float* gradZ, const int32_t* 
     const int nb = flat_grid(N * (int64_t)Cl);
     with_mode(Cl, [&](auto rm) {
         constexpr int RM = decltype(rm)::value;
-        if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M, gate);
-        else hipLaunchKernelGGL((z_step_kernel<false, RM>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M, gate);
+        with_flag(gate != nullptr, [&](auto gated) {
+            constexpr bool GATED = decltype(gated)::value;
+            if (M <= kStepUnits) hipLaunchKernelGGL((z_step_kernel<true, RM, GATED>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M, gate);
+            else hipLaunchKernelGGL((z_step_kernel<false, RM, GATED>), dim3(nb), dim3(256), 0, s, Zl, gradZ, row_comm, N, Cl, units, M, gate);
+        });
     });
 }
 
@@ -1450,16 +1474,21 @@ void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const floa
     int64_t nb = (N * (int64_t)Cl + 2047) / 2048;
     nb = nb < 1 ? 1 : (nb > 4 * kReduceBlocks ? 4 * kReduceBlocks : nb);
     const size_t lds = (size_t)Cn * Cl * sizeof(float);                 // at most 16 x 1024 floats (the low-rank limit)
-    if (M <= kStepUnits)
-        hipLaunchKernelGGL((z_step_lowrank_kernel<true>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
-    else
-        hipLaunchKernelGGL((z_step_lowrank_kernel<false>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
+    with_flag(gate != nullptr, [&](auto gated) {
+        constexpr bool GATED = decltype(gated)::value;
+        if (M <= kStepUnits)
+            hipLaunchKernelGGL((z_step_lowrank_kernel<true, GATED>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
+        else
+            hipLaunchKernelGGL((z_step_lowrank_kernel<false, GATED>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
+    });
 }
 
 void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int Cn) {
     const int nb = flat_grid(N * (int64_t)Cn * 4);
     with_mode(Cn, [&](auto sm) {
-        hipLaunchKernelGGL((t_carry_kernel<decltype(sm)::value>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
+        with_flag(k.gate != nullptr, [&](auto gated) {
+            hipLaunchKernelGGL((t_carry_kernel<decltype(sm)::value, decltype(gated)::value>), dim3(nb), dim3(256), 0, s, Tn, k, N, Cn);
+        });
     });
 }
 
@@ -1471,8 +1500,9 @@ void launch_last_layer(hipStream_t s, float* ZL, float* U, float* TL, const int3
         auto go = [&](auto lg) {
             constexpr int LG = decltype(lg)::value;
             const dim3 grid((unsigned)(((N << LG) + 255) / 256));
-            if (carry) hipLaunchKernelGGL((last_layer_kernel<LG, 1, SM>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G);
-            else hipLaunchKernelGGL((last_layer_kernel<LG, 0, SM>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, nullptr);
+            if (carry && k.gate) hipLaunchKernelGGL((last_layer_kernel<LG, 1, SM, true>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G);
+            else if (carry) hipLaunchKernelGGL((last_layer_kernel<LG, 1, SM, false>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, G);
+            else hipLaunchKernelGGL((last_layer_kernel<LG, 0, SM, false>), grid, dim3(256), 0, s, ZL, U, TL, labels, N, CL, risk, rho, J, update_u, k, nullptr);
         };
         if constexpr (SM == kNarrow) {
             go(std::integral_constant<int, 0>{});
