@@ -200,10 +200,12 @@ int  cadmm_set_state(cadmm_ctx* ctx, const float* const* W, const float* const* 
  *                        a change of Z_{l,m}, for every r in N_m or r = m)
  *   transform:           out = A B        A device n x K, B device K x C, out n x C
  *   wgrad:               out = A^T G      A device n x K, G device n x C, out K x C
- * They run on the context's stream, or on the one named by cadmm_op_stream (NULL = the default stream; that of the context's
- * device, so a call there while another device is current is CADMM_EHIP and runs nothing): there, in the order of the calls, after everything the context has enqueued before and before everything it enqueues later.  A call on a
- * stream that is being captured is ordered inside the captured graph; a replay of that graph is the caller's to order
- * against the context (aggregate, aggregate_segments and wgrad use scratch of the workspace, as the iterations do).
+ * They run on the context's stream, or on the one named by cadmm_op_stream: there, in the order of the calls, after everything
+ * the context has enqueued before and before everything it enqueues later.  NULL is the default stream of the context's device:
+ * while another device is current such a call is CADMM_EHIP and runs nothing (cadmm_op_wgrad_noalloc makes the context's
+ * device current itself).  A call on a stream that is being captured is ordered inside the captured graph; a replay of that
+ * graph is the caller's to order against the context (aggregate, aggregate_segments and wgrad use scratch of the workspace,
+ * as the iterations do).
  */
 int  cadmm_op_stream(cadmm_ctx* ctx, void* hip_stream);
 int  cadmm_op_aggregate(cadmm_ctx* ctx, const float* X, int32_t width, float* Y);

@@ -683,7 +683,8 @@ void w_update(cadmm_ctx* c, int l) {
             launch_w_trial(s, c->T[l], Q, c->Z[l], count, n, sp, unit, c->partials, c->status, spec ? 1 : 0);
         });
     }, Unless{skip, 1, P_OTHER, 0.0});
-    const double unmoved = last ? (c->schedule == 1 ? 4.0 : 5.0) : leave_g && !spec ? 3.0 : 0.0;       // G (and the last layer's old T) is left all the same
+    // G (and the last layer's old T) is left all the same
+    const double unmoved = last ? (c->schedule == 1 ? 4.0 : 5.0) : leave_g && !spec ? 3.0 : 0.0;
     timed(c, P_W_STEP, 4.0 * ((spec ? 0.0 : last ? 7.0 : leave_g ? 5.0 : 3.0) * (double)count + 3.0 * K * Cl), 0.0, [&] {
         // W^{k+1}; T_l = A~ Z^k W^{k+1}; last layer: G_L of that T_L for the Z step of layer L-1
         if (last)
@@ -761,7 +762,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
         ge.gate = a.gate;
         gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn, ge, gated);         // grad W_{l+1}
     }
-    aggregate_segments(c, c->tmpV, c->P, Cn, a.gate, gated);                            // A~_{r,m} (grad W) per segment
+    aggregate_segments(c, c->tmpV, c->P, Cn, a.gate, gated);                     // A~_{r,m} (grad W) per segment
     // one pass reads Z_l, grad, T_l (or their sums) over the rows and P with T_{l+1}, Z_{l+1} (or G_L alone) over the segments
     const double zt_bytes = 4.0 * ((a.gate ? 0.0 : sum_tiles ? 6.0 * sum_tiles * (double)N : 3.0 * (double)N * Cl) +
                                    (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;

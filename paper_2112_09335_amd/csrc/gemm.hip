@@ -1077,8 +1077,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 && P
 // and 18 reads, three quarters as much of either, two buffers and one barrier per step, and the next step's numbers are formed and
 // split between the matrix instructions of this one.
 // 500000 x 512 x 512 1657 -> 1332 us (in iterations in which eight such layers step 1850 -> 1510), 200000 x 256 x 256 198 -> 162,
-// 20000 x 700 x 512 128 -> 100, 30000 x 480 x 200 71 -> 58, 13752 x 767 x 1000 174 -> 159.  The same tile without the prologue gains 0 to 6 % (the 128 x 128 kernel then fits four
-// wavefronts), and in out = A B it loses to its longer epilogue what it gains: not used there.
+// 20000 x 700 x 512 128 -> 100, 30000 x 480 x 200 71 -> 58, 13752 x 767 x 1000 174 -> 159.  The same tile without the prologue
+// gains 0 to 6 % (the 128 x 128 kernel then fits four wavefronts), and in out = A B it loses to its longer epilogue what it
+// gains: not used there.
 constexpr int kWideM = 4, kWideN = 2;                        // 32 x 32 accumulators of a wavefront
 constexpr int kWideRows = 64 * kWideM, kWideCols = 64 * kWideN;
 constexpr int kWideA = kWideRows * BK, kWideB = kWideCols * BK;        // bf16 of one plane: the tile of A, then that of B
