@@ -281,9 +281,10 @@ const char* cadmm_profile_class_name(int32_t cls);
  * Process-wide: "spmm_tile_cols": feature columns handled per
  * aggregation launch (0 = all at once); "spmm_xcd_remap": 1 = each XCD walks one contiguous slice of the aggregation's
  * work list, whole communities one after the other (default), 0 = workgroups in plain order;
- * "gemm_split": 1 = products with more than 32 result columns run on the bf16 matrix
- * cores, both operands split exactly into three bf16 parts and the six largest cross products accumulated in fp32
- * (default), 0 = on the fp32 matrix cores. */
+ * "gemm_split": 1 = products with more than 32 result columns split both operands for the 16-bit matrix cores and accumulate
+ * in fp32 (default): exactly into three bf16 parts with the six largest cross products, or, large products inside the sweep,
+ * scaled by powers of two into two fp16 parts with the three largest; 2 = two fp16 parts inside the sweep at any size (for
+ * tests); 0 = on the fp32 matrix cores. */
 int  cadmm_tune(cadmm_ctx* ctx, const char* key, int32_t value);
 
 #ifdef __cplusplus

@@ -88,6 +88,15 @@ struct cadmm_ctx {
     double* partials = nullptr;
     double* row_sums = nullptr; // RowSums of the Z gradient being searched, for up to row_sum_tiles tiles
     int row_sum_tiles = 0;
+    // For products on pairs of fp16: RowMax of H_l (h_max_tiles: the tiles of the aggregation that left it, 0: it did not), of
+    // tmpA and of tmpB (their room in tiles), and the right operand in operand layout.
+    std::vector<float*> h_max;
+    std::vector<int> h_max_room, h_max_tiles;
+    float* a_max = nullptr;
+    float* b_max = nullptr;
+    int a_max_room = 0, b_max_room = 0;
+    unsigned short* planes = nullptr;
+    int* col_back = nullptr;
     Unit* unitsW = nullptr;     // [L]
     Unit* unitsZ = nullptr;     // [(L-1) * M]
     Unit* unitsF = nullptr;     // [M]: the L of the last-layer solve with backtracking (fista_mode 1)
@@ -204,11 +213,17 @@ GradPath grad_path(const cadmm_ctx* c, int l) {
 // Column tiles in which the last kernel of that path leaves the rows' sums for the search; 0: it does not, the search reads the
 // gradient (narrow layers, where that is little, and so many tiles that their sums would not be).
 constexpr int kMaxSumTiles = 16;
+int row_tiles(const cadmm_ctx* c, int width) { return spmm_tiles(schedule_of(c, c->d_rows, c->hg.row_sched), width); }
+// Whether the product that forms the gradient of layer l (kGradProduct) runs on pairs.
+bool grad_on_pairs(const cadmm_ctx* c, int l) {
+    const int Cl = c->C[l], Cn = c->C[l + 1];
+    return gemm_nn_pair(c->hg.N, Cn, Cl) && row_tiles(c, Cn) <= c->a_max_room;
+}
 int sum_tiles_of(const cadmm_ctx* c, int l, GradPath path) {
     const int Cl = c->C[l];
     int tiles = 0;
     if (path == kGradLowRank) tiles = 1;
-    else if (path == kGradProduct) tiles = Cl > 32 ? gemm_nn_tiles(c->hg.N, Cl) : 0;
+    else if (path == kGradProduct) tiles = Cl > 32 ? gemm_nn_tiles(c->hg.N, Cl, grad_on_pairs(c, l)) : 0;
     else if (Cl >= 4) tiles = spmm_tiles(schedule_of(c, c->d_rows, c->hg.row_sched), Cl);
     return tiles <= kMaxSumTiles ? tiles : 0;
 }
@@ -328,13 +343,37 @@ size_t layout(cadmm_ctx* c, char* base) {
     const size_t np2 = nch * kRestCand;
     np = np > np2 ? np : np2;
     for (int l = 1; l <= L; ++l) {               // block results of the products that also evaluate a candidate
-        const size_t np3 = (size_t)gemm_nn_blocks(N, c->C[l]);
+        const size_t np3 = (size_t)std::max(gemm_nn_blocks(N, c->C[l], false), gemm_nn_blocks(N, c->C[l], true));
         np = np > np3 ? np : np3;
     }
     c->partials = b.take<double>(np);
     c->row_sum_tiles = 0;
     for (int l = 1; l < L; ++l) c->row_sum_tiles = std::max(c->row_sum_tiles, sum_tiles_reserved(c, l));
     c->row_sums = b.take<double>((size_t)N * c->row_sum_tiles * 3);
+    // RowMax and operand planes by form alone, whatever the number of rows and the tuning make of it
+    const SpmmSchedule rows = schedule_of(c, c->d_rows, g.row_sched);
+    size_t planes = 0;
+    auto want = [&](int K, int C) {
+        if (!gemm_nn_pair_form(K, C)) return false;
+        planes = std::max(planes, gemm_nn_pair_planes(K, C));
+        return true;
+    };
+    c->h_max.assign(L + 1, nullptr);
+    c->h_max_room.assign(L + 1, 0);
+    c->h_max_tiles.assign(L + 1, 0);
+    c->a_max_room = c->b_max_room = 0;
+    for (int l = 1; l <= L; ++l) {
+        const int K = c->C[l - 1], Cl = c->C[l];
+        if (!c->agg_first[l] && want(K, Cl)) c->h_max_room[l] = spmm_default_tiles(rows, K);
+        c->h_max[l] = b.take<float>((size_t)N * c->h_max_room[l]);
+        if (l < 2) continue;
+        if (product_last(K, Cl) && want(Cl, K)) c->a_max_room = std::max(c->a_max_room, spmm_default_tiles(rows, Cl));
+        if (want(K, Cl)) c->b_max_room = std::max({c->b_max_room, spmm_default_tiles(rows, K), gemm_nn_pair_tiles(K)});
+    }
+    c->a_max = b.take<float>((size_t)N * c->a_max_room);
+    c->b_max = b.take<float>((size_t)N * c->b_max_room);
+    c->planes = b.take<unsigned short>(planes);
+    c->col_back = b.take<int>(planes ? max_of(c->C, 0, L) : 0);
     c->unitsW = b.take<Unit>(L);
     c->unitsZ = b.take<Unit>((size_t)(L - 1) * g.M);
     c->unitsF = b.take<Unit>((size_t)g.M);
@@ -461,6 +500,24 @@ void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpil
           });
 }
 
+// H_l = A~ X, with its RowMax where the products with H_l run on pairs.
+void aggregate_H(cadmm_ctx* c, const float* X, int l) {
+    SpmmEpilogue e;
+    const int K = c->C[l - 1], tiles = row_tiles(c, K);
+    const bool max = gemm_nn_pair(c->hg.N, K, c->C[l]) && tiles <= c->h_max_room[l];
+    if (max) e.row_max = c->h_max[l];
+    c->h_max_tiles[l] = max ? tiles : 0;
+    aggregate(c, X, c->H[l], K, e);
+}
+
+// For products with a left operand whose RowMax has that many tiles (0: there is none).
+PairOperands pair_operands(const cadmm_ctx* c, const float* row_max, int tiles) {
+    PairOperands p;
+    if (tiles > 0) { p.row_max = row_max; p.max_tiles = tiles; p.planes = c->planes; p.col_back = c->col_back; }
+    return p;
+}
+PairOperands pair_of_H(const cadmm_ctx* c, int l) { return pair_operands(c, c->h_max[l], c->h_max_tiles[l]); }
+
 // P_{(i,c)} = sum over the entries of row i in community c of A~_ij V_j, one output row per segment, in the
 // (community, row) order: the segments with several entries as a row list, those with one entry as scaled copies.
 void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width, const int32_t* gate = nullptr,
@@ -476,8 +533,9 @@ void aggregate_segments(cadmm_ctx* c, const float* V, float* P, int width, const
 
 bool t1_reusable(const cadmm_ctx* c) { return c->t1_age >= 0 && c->t1_age < c->t1_refresh; }
 
-GemmEpilogue relu_epilogue(float* relu_out) {
+GemmEpilogue forward_epilogue(const cadmm_ctx* c, int l, float* relu_out) {
     GemmEpilogue e;
+    e.pair = pair_of_H(c, l);
     if (relu_out) { e.kind = 3; e.Tio = relu_out; }
     return e;
 }
@@ -494,9 +552,9 @@ void compute_T(cadmm_ctx* c, int l, bool force = false, float* relu_out = nullpt
         aggregate(c, c->tmpV, c->T[l], c->C[l], SpmmEpilogue());
         if (relu_out) launch_relu(c->stream, c->T[l], relu_out, N * c->C[l], 1);
     } else {
-        if (l >= 2) aggregate(c, c->Z[l - 1], c->H[l], c->C[l - 1], SpmmEpilogue());   // the W step needs H_l itself
+        if (l >= 2) aggregate_H(c, c->Z[l - 1], l);                                    // the W step needs H_l itself
         if (carried) return;
-        gemm_nn(c, c->H[l], c->W[l], c->T[l], N, c->C[l - 1], c->C[l], relu_epilogue(relu_out));
+        gemm_nn(c, c->H[l], c->W[l], c->T[l], N, c->C[l - 1], c->C[l], forward_epilogue(c, l, relu_out));
     }
 }
 
@@ -661,16 +719,22 @@ void w_update(cadmm_ctx* c, int l) {
     } else if (spec) {
         GemmEpilogue ge;
         ge.kind = 2; ge.Zl = c->Z[l]; ge.nu = c->nu; ge.Tio = c->T[l]; ge.unit = unit; ge.partials = c->partials; ge.leave_g = leave_g;
+        ge.pair = pair_of_H(c, l);
+        const bool on_pairs = ge.pair.planes && gemm_nn_pair(N, K, Cl);
         timed(c, P_GEMM_NN_128_TRIAL, 4.0 * ((double)N * K + (double)K * Cl + (leave_g ? 4.0 : 3.0) * (double)count), 2.0 * (double)N * K * Cl,
               [&] {
                   launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, ge);
-                  launch_w_trial_finish(s, c->partials, (int)gemm_nn_blocks(N, Cl), sp, unit, c->status);
+                  launch_w_trial_finish(s, c->partials, (int)gemm_nn_blocks(N, Cl, on_pairs), sp, unit, c->status);
                   GemmEpilogue again;          // Q itself, only if the step was taken ahead and then rejected
                   again.unit = unit;
+                  again.pair = ge.pair;
+                  again.pair.ready = true;
                   launch_gemm_nn(s, c->H[l], c->gradW, Q, N, K, Cl, again);
               }, Unless{skip, 1, P_OTHER, leave_g ? 12.0 * (double)count : 0.0});
     } else {
-        gemm_nn(c, c->H[l], c->gradW, Q, N, K, Cl);
+        GemmEpilogue ge;
+        ge.pair = pair_of_H(c, l);
+        gemm_nn(c, c->H[l], c->gradW, Q, N, K, Cl, ge);
     }
     // one pass reads T0, Q, Z_l (and U for the last layer); passes after an accepted one return at once
     timed(c, P_W_TRIAL, spec ? 0.0 : 4.0 * (double)count * (last ? 4 : 3), 0.0, [&] {
@@ -724,6 +788,9 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     const bool lowrank = path == kGradLowRank;
     const int sum_tiles = how.sum_tiles;
     double* const row_sums = sum_tiles ? c->row_sums : nullptr;
+    // grad W_{l+1} runs on pairs if whatever forms the gradient can leave its RowMax
+    const bool want_max = !lowrank && gemm_nn_pair(N, Cl, Cn);
+    int max_tiles = 0;
     if (lowrank) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
         timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] { launch_lowrank_operand(s, c->W[l + 1], c->Bcat, Cl, Cn); });
@@ -731,14 +798,22 @@ void z_update_hidden(cadmm_ctx* c, int l) {
             launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->Bcat, Wt, c->tmpV, N, Cl, Cn, Cn, c->nu, row_sums);
         });
     } else if (path == kGradProduct) {
-        aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
+        const bool on_pairs = grad_on_pairs(c, l);
+        SpmmEpilogue epi;
+        if (on_pairs) epi.row_max = c->a_max;
+        aggregate(c, c->G[l + 1], c->tmpA, Cn, epi);                             // A~ G_{l+1}
         GemmEpilogue ge;
+        if (on_pairs) {
+            ge.pair = pair_operands(c, c->a_max, row_tiles(c, Cn));
+            if (want_max) { ge.out_max = c->b_max; max_tiles = gemm_nn_pair_tiles(Cl); }
+        }
         ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu; ge.row_sums = row_sums;
         gemm_nn(c, c->tmpA, Wt, c->tmpB, N, Cn, Cl, ge);
     } else {
         gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl);                         // G_{l+1} W_{l+1}^T
         SpmmEpilogue epi;
         epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu; epi.row_sums = row_sums;
+        if (want_max && row_tiles(c, Cl) <= c->b_max_room) { epi.row_max = c->b_max; max_tiles = row_tiles(c, Cl); }
         aggregate(c, c->tmpA, c->tmpB, Cl, epi);
     }
     ZTrialArgs a;
@@ -760,6 +835,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     if (!lowrank) {
         GemmEpilogue ge;
         ge.gate = a.gate;
+        ge.pair = pair_operands(c, c->b_max, max_tiles);
         gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn, ge, gated);         // grad W_{l+1}
     }
     aggregate_segments(c, c->tmpV, c->P, Cn, a.gate, gated);                     // A~_{r,m} (grad W) per segment
@@ -1296,7 +1372,7 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
     }
     c->t1_age = -1;
     for (int l = 2; l <= L; ++l) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
-    aggregate(c, c->Z[0], c->H[1], c->C[0], SpmmEpilogue());      // A~ Z_0 never changes
+    aggregate_H(c, c->Z[0], 1);                                   // A~ Z_0 never changes
     for (int l = 1; l <= L; ++l) {
         compute_T(c, l, false, l < L ? c->Z[l] : nullptr);
         if (l == L) launch_relu(s, c->T[l], c->Z[l], N * c->C[l], 0);
@@ -1411,9 +1487,9 @@ int cadmm_predict(cadmm_ctx* c, int32_t* pred, float* logits, double* accuracy) 
             gemm_nn(c, in, c->W[l], c->tmpV, N, c->C[l - 1], c->C[l]);
             aggregate(c, c->tmpV, c->T[l], c->C[l], SpmmEpilogue());
         } else {
-            if (l >= 2) aggregate(c, in, c->H[l], c->C[l - 1], SpmmEpilogue());
+            if (l >= 2) aggregate_H(c, in, l);
             // (of a hidden layer only the activation is needed)
-            gemm_nn(c, c->H[l], c->W[l], l < L ? nullptr : c->T[l], N, c->C[l - 1], c->C[l], relu_epilogue(l < L ? c->G[l] : nullptr));
+            gemm_nn(c, c->H[l], c->W[l], l < L ? nullptr : c->T[l], N, c->C[l - 1], c->C[l], forward_epilogue(c, l, l < L ? c->G[l] : nullptr));
         }
         if (l < L) {
             if (c->agg_first[l]) launch_relu(s, c->T[l], c->G[l], N * c->C[l], 1);

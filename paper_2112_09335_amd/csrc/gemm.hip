@@ -110,6 +110,78 @@ __device__ __forceinline__ void xcd_group(unsigned b, unsigned nb, unsigned inne
     }
 }
 
+// What an epilogue does with one quad of results (EPI as below): v the product's, z and t the rows of Zl and of Tl (Tio), o the
+// quad's place in the result matrix, nv how many of its columns exist there.
+struct EpilogueArgs {
+    float* out;
+    const float* Zl;
+    const float* tin;
+    float nu;
+    float* Tio;
+    double inv0;             // EPI 2, 4: 1 / first candidate
+    bool take, hold;         // EPI 2, 4: the step is taken ahead; EPI 4: no step at all
+};
+template <int EPI, int MODE>
+__device__ __forceinline__ void epilogue_quad(float (&v)[4], float4 z4, float4 t4, int64_t o, int nv, const EpilogueArgs& a,
+                                              double& dsum) {
+    float t[4] = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (EPI == 1 || EPI == 2 || EPI == 4) {
+        const float z[4] = {z4.x, z4.y, z4.z, z4.w};
+        t[0] = t4.x; t[1] = t4.y; t[2] = t4.z; t[3] = t4.w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            // (columns past C hold a copy of the last one; with z and t zero there a zero adds nothing)
+            if constexpr (MODE != kFull) v[e] = e < nv ? v[e] : 0.f;
+            if constexpr (EPI == 1) v[e] = a.nu * (z[e] - fmaxf(t[e], 0.f)) + v[e];
+            if constexpr (EPI == 2 || EPI == 4) {
+                const double t0 = (double)t[e], zd = (double)z[e];
+                const double t1 = t0 - (double)v[e] * a.inv0;
+                const double e0 = fmax(t0, 0.0) - zd, e1 = fmax(t1, 0.0) - zd;
+                dsum += (e1 - e0) * (e1 + e0);
+                t[e] = (float)t1;
+            }
+        }
+    }
+    if constexpr (EPI == 2) {
+        if (a.take) st4u(a.Tio + o, t, nv);
+        else st4u(a.out + o, v, nv);
+    } else if constexpr (EPI == 4) {
+        if (a.take) st4u(a.Tio + o, t, nv);
+        if (a.take || a.hold) {                                  // (as launch_G_only forms it)
+            const float z[4] = {z4.x, z4.y, z4.z, z4.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = t[e] > 0.f ? a.nu * (float)((double)t[e] - (double)z[e]) : 0.f;
+        }
+        st4u(a.out + o, v, nv);
+    } else if constexpr (EPI == 3) {
+        if (a.out) st4u(a.out + o, v, nv);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
+        st4u(a.Tio + o, v, nv);
+    } else {
+        st4u(a.out + o, v, nv);
+    }
+}
+// EPI 1: RowSums of a quad of columns c .. c + 3 (of C), over 16 or 32 neighbouring lanes (LANES); every one of them gets the sums.
+template <int LANES>
+__device__ __forceinline__ void quad_row_sums(double (&rs)[3], const float (&v)[4], float4 z4, float4 t4, int c, int C, float nu) {
+    const float z[4] = {z4.x, z4.y, z4.z, z4.w}, tt[4] = {t4.x, t4.y, t4.z, t4.w};
+    rs[0] = rs[1] = rs[2] = 0.0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const bool in = c + e < C;
+        const float g = nu * (z[e] - fmaxf(tt[e], 0.f)) + v[e];
+        const double zd = in ? (double)z[e] : 0.0, gd = in ? (double)g : 0.0;
+        rs[0] += (zd - fmax((double)tt[e], 0.0)) * gd;
+        rs[1] += gd * gd;
+        rs[2] += zd * zd;
+    }
+#pragma unroll
+    for (int o = 1; o < LANES; o <<= 1)
+#pragma unroll
+        for (int s = 0; s < 3; ++s) rs[s] += __shfl_xor(rs[s], o, 64);
+}
+
 // Epilogue of a result tile of 64 T x 64 T held as T x T accumulators per wavefront (2 x 2 wavefronts).
 // The accumulators hold 32 consecutive columns per row and lane group; passing each 32-row slab of the tile
 // through LDS (Cs: 32 x (64 T + 4) floats, the operand buffer reused) turns every global access of the epilogue into
@@ -120,9 +192,7 @@ __device__ __forceinline__ void xcd_group(unsigned b, unsigned nb, unsigned inne
 // (2M x 128 x 256: 1444 us without it, 1681 with).
 template <int EPI, int T, int MODE>
 __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
-                                                   float* __restrict__ out, const float* __restrict__ Zl,
-                                                   const float* tin, float nu, float* __restrict__ Tio, double inv0,
-                                                   bool take, bool hold, double& dsum, double* __restrict__ row_sums) {
+                                                   const EpilogueArgs& args, double& dsum, double* __restrict__ row_sums) {
     constexpr int BN = 64 * T;
     constexpr int LDC = BN + 4;
     constexpr int Q = BN / 4;                            // quads per row
@@ -132,18 +202,6 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
     const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lk = lane >> 5;
-    // one result element: returns what goes to out, updates t (EPI 2) and the candidate's sum
-    auto finish = [&](float v, float z, float& t) -> float {
-        if constexpr (EPI == 1) v = nu * (z - fmaxf(t, 0.f)) + v;
-        if constexpr (EPI == 2 || EPI == 4) {
-            const double t0 = (double)t, zd = (double)z;
-            const double t1 = t0 - (double)v * inv0;
-            const double e0 = fmax(t0, 0.0) - zd, e1 = fmax(t1, 0.0) - zd;
-            dsum += (e1 - e0) * (e1 + e0);
-            t = (float)t1;
-        }
-        return v;
-    };
 #pragma unroll
     for (int q = 0; q < 2 * T; ++q) {
         __syncthreads();
@@ -165,8 +223,8 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                     const int f = tid + 256 * (u0 + u);
                     const int64_t row = m0 + 32 * q + f / Q;
                     const int64_t ro = (row < n ? row : n - 1) * (int64_t)C;
-                    z4[u] = ld_quad<MODE>(Zl + ro, c0 + 4 * (f % Q), C);
-                    t4[u] = ld_quad<MODE>(tin + ro, c0 + 4 * (f % Q), C);
+                    z4[u] = ld_quad<MODE>(args.Zl + ro, c0 + 4 * (f % Q), C);
+                    t4[u] = ld_quad<MODE>(args.tin + ro, c0 + 4 * (f % Q), C);
                 }
             }
 #pragma unroll
@@ -176,59 +234,17 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
                 const int64_t row = m0 + 32 * q + rl;
                 const int c = c0 + 4 * cq;
                 const float4 v4 = *reinterpret_cast<const float4*>(Cs + rl * LDC + 4 * cq);
-                float v[4] = {v4.x, v4.y, v4.z, v4.w}, t[4] = {0.f, 0.f, 0.f, 0.f};
+                float v[4] = {v4.x, v4.y, v4.z, v4.w};
                 if constexpr (EPI == 1) {
                     if (row_sums) {                              // (uniform) the row's sums over this tile's columns
-                        const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w}, tt[4] = {t4[u].x, t4[u].y, t4[u].z, t4[u].w};
-                        double rs[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const bool in = c + e < C;
-                            const float g = nu * (z[e] - fmaxf(tt[e], 0.f)) + v[e];
-                            const double zd = in ? (double)z[e] : 0.0, gd = in ? (double)g : 0.0;
-                            rs[0] += (zd - fmax((double)tt[e], 0.0)) * gd;
-                            rs[1] += gd * gd;
-                            rs[2] += zd * zd;
-                        }
-#pragma unroll
-                        for (int o = 1; o < Q; o <<= 1)
-#pragma unroll
-                            for (int s = 0; s < 3; ++s) rs[s] += __shfl_xor(rs[s], o, 64);
+                        double rs[3];
+                        quad_row_sums<Q>(rs, v, z4[u], t4[u], c, C, args.nu);
                         if (cq < 3 && row < n) row_sums[((int64_t)(c0 / BN) * n + row) * 3 + cq] = cq == 0 ? rs[0] : cq == 1 ? rs[1] : rs[2];
                     }
                 }
                 if (row >= n || c >= C) continue;
-                const int64_t o = row * C + c;
-                const int nv = MODE == kFull ? 4 : C - c;       // columns of this lane (four, or the row's last few)
-                if constexpr (EPI == 1 || EPI == 2 || EPI == 4) {
-                    const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
-                    t[0] = t4[u].x; t[1] = t4[u].y; t[2] = t4[u].z; t[3] = t4[u].w;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        // (columns past C hold a copy of the last one; with z and t zero there a zero adds nothing)
-                        if constexpr (MODE != kFull) v[e] = e < nv ? v[e] : 0.f;
-                        v[e] = finish(v[e], z[e], t[e]);
-                    }
-                }
-                if constexpr (EPI == 2) {
-                    if (take) st4u(Tio + o, t, nv);
-                    else st4u(out + o, v, nv);
-                } else if constexpr (EPI == 4) {
-                    if (take) st4u(Tio + o, t, nv);
-                    if (take || hold) {                                  // (as launch_G_only forms it)
-                        const float z[4] = {z4[u].x, z4[u].y, z4[u].z, z4[u].w};
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) v[e] = t[e] > 0.f ? nu * (float)((double)t[e] - (double)z[e]) : 0.f;
-                    }
-                    st4u(out + o, v, nv);
-                } else if constexpr (EPI == 3) {
-                    if (out) st4u(out + o, v, nv);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
-                    st4u(Tio + o, v, nv);
-                } else {
-                    st4u(out + o, v, nv);
-                }
+                // columns of this lane: four, or the row's last few
+                epilogue_quad<EPI, MODE>(v, z4[u], t4[u], row * C + c, MODE == kFull ? 4 : C - c, args, dsum);
             }
         }
     }
@@ -248,9 +264,9 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, 
         inv0 = unit->skip ? 0.0 : 1.0 / unit->step0;
         take = unit->spec != 0 && !unit->skip;
     }
-    const float* tin = (EPI == 2 || EPI == 4) ? Tio : Tl;
-    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, dsum, row_sums);
-    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, out, Zl, tin, nu, Tio, inv0, take, hold, dsum, row_sums);   // (C > 32)
+    const EpilogueArgs args{out, Zl, (EPI == 2 || EPI == 4) ? Tio : Tl, nu, Tio, inv0, take, hold};
+    if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, args, dsum, row_sums);
+    else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, args, dsum, row_sums);   // (C > 32)
     if constexpr (EPI == 2 || EPI == 4) {
         __shared__ double red[4];
 #pragma unroll
@@ -674,6 +690,400 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
         }
     }
     tile_epilogue<EPI, T>(acc, reinterpret_cast<float*>(smem), m0, c0, n, C, out, Zl, Tl, nu, Tio, unit, partials);
+}
+
+// ------------------------------------------------------------------------------------------------ NN, pairs of fp16
+// The same product with half the matrix instructions: an operand scaled by a power of two so that its largest entry lies in
+// [2^14, 2^15) is the sum of two fp16 numbers, x = hi + lo, hi = fp16(x) and lo = fp16(x - hi) rounded to nearest, to 2^-23 of
+// itself (entries below 2^-16 of the largest: to 2^-39 of the largest), and hi*hi, hi*lo and lo*hi are accumulated in fp32;
+// lo*lo is below 2^-22 of |a||b|.  A row of A has a scale of its own (from RowMax, left by whatever formed A), so has a column
+// of B; results are scaled back by ldexp.  What bounds wide products is the power the matrix instructions take (the chip runs
+// them at 1.55 to 1.65 GHz, by GRBM_GUI_ACTIVE over time), and the fp32 roundings are half as many: against 64 bits the error of
+// 512-long sums is 2.6e-7 of the result where the three-way split of bf16 has 3.5e-7 (Gaussian operands; at 16 it would be 1.2
+// times, from 64 on it is 0.75 to 0.95 times that of the bf16 split, also for positive ones, for rows and columns scaled by 1e-8
+// to 1e8 and for entries spread over e^(4 N(0,1))).
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float float2v __attribute__((ext_vector_type(2)));
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+
+// two fp32 numbers times s -> their two fp16 parts, each pair packed into one dword (low half = first number)
+__device__ __forceinline__ void split2_pair(float x0, float x1, float s, unsigned& h, unsigned& l) {
+    const float2v y = {x0 * s, x1 * s};
+    const half2v hi = __builtin_convertvector(y, half2v);
+    const float2v r = {fmaf(x0, s, -(float)hi.x), fmaf(x1, s, -(float)hi.y)};             // exact
+    h = __builtin_bit_cast(unsigned, hi);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector(r, half2v));
+}
+// The scale of numbers of largest magnitude m is 2^(141 - e) with the exponent field e of m (15 and more, so that it is a number).
+__device__ __forceinline__ int pair_exponent(float m) {
+    const int e = (int)(__float_as_uint(m) >> 23) & 255;
+    return (e < 15 ? 15 : e) - 141;                              // what results are scaled back by
+}
+__device__ __forceinline__ float pair_scale(int back) { return __uint_as_float((unsigned)(127 - back) << 23); }
+
+constexpr int kPairK = 32;                                       // contraction per step
+constexpr int kPairTM = 4, kPairTN = 2;                          // 32 x 32 accumulators of a wavefront: 128 x 64
+constexpr int kPairWaves = 4;                                    // side by side
+constexpr int kPairRows = 32 * kPairTM, kPairCols = 32 * kPairTN * kPairWaves;
+constexpr int kPairLeast = 129;                                  // columns: half a tile and less go by other kernels
+constexpr int kPairSub = 2 * 2 * 512;                            // fp16 of 32 rows (columns of B) and one step: 16-k halves, parts, lanes of eight
+
+// B (K x C) in the matrix cores' own operand layout, [32 columns][step][16-k half][part][lane][8], zeros past K, and what the
+// columns' results are scaled back by.  A workgroup takes 32 columns; entries are read twice, the second time from the L2.
+__global__ __launch_bounds__(1024) void pair_weights_kernel(const float* __restrict__ B, int K, int C, unsigned short* __restrict__ planes,
+                                                            int* __restrict__ back, const int32_t* __restrict__ gate) {
+    __shared__ float s_max[32][32];
+    __shared__ int s_back[32];
+    if (gate && *gate == 0) return;
+    const int li = threadIdx.x & 31, g = threadIdx.x >> 5;
+    const int c = blockIdx.x * 32 + li;
+    const float* const col = B + (c < C ? c : C - 1);
+    auto load8 = [&](int k0, float (&x)[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float v = col[(int64_t)(k0 + e < K ? k0 + e : K - 1) * C];
+            x[e] = k0 + e < K ? v : 0.f;
+        }
+    };
+    float m = 0.f;
+    for (int k0 = 8 * g; k0 < K; k0 += 256) {
+        float x[8];
+        load8(k0, x);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(x[e]));
+    }
+    s_max[g][li] = m;
+    __syncthreads();
+    if (g == 0) {
+        for (int i = 1; i < 32; ++i) m = fmaxf(m, s_max[i][li]);
+        s_back[li] = pair_exponent(m);
+        if (c < C) back[c] = s_back[li];
+    }
+    __syncthreads();
+    const float s = pair_scale(s_back[li]);
+    const int steps = (K + kPairK - 1) / kPairK;
+    for (int k0 = 8 * g; k0 < steps * kPairK; k0 += 256) {
+        float x[8];
+        load8(k0, x);
+        uint4v h, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            unsigned a, b;
+            split2_pair(x[2 * e], x[2 * e + 1], s, a, b);
+            h[e] = a;
+            l[e] = b;
+        }
+        unsigned short* const o = planes + ((int64_t)blockIdx.x * steps + k0 / kPairK) * kPairSub + (k0 & 16 ? 1024 : 0) +
+                                  ((k0 & 8 ? 32 : 0) + li) * 8;
+        *reinterpret_cast<uint4v*>(o) = h;
+        *reinterpret_cast<uint4v*>(o + 512) = l;
+    }
+}
+
+// A wavefront's 128 x 64 results, 32 rows at a time through a slab of LDS of its own (no barrier) so that every global access
+// is a 16-byte piece of 256 consecutive bytes.  EPI as in tile_epilogue.  s_rs / s_rm: EPI 1, where this wavefront's share of its
+// rows' sums and its largest magnitudes go (null: nobody asks).
+constexpr int kPairLd = 64 + 4;
+template <int EPI, int MODE>
+__device__ __forceinline__ void pair_epilogue(floatx16 (&acc)[kPairTM][kPairTN], float* Cs, const int* s_back, const int (&cb)[kPairTN],
+                                              int64_t m0, int c0, int64_t n, int C, const EpilogueArgs& args, double& dsum,
+                                              double* s_rs, float* s_rm) {
+    const int lane = threadIdx.x & 63;
+    const int li = lane & 31, lk = lane >> 5;
+    const int c = c0 + 4 * (lane & 15);
+    constexpr int U = 4;                                 // pieces of a lane at a time, their loads before any is used
+#pragma unroll
+    for (int q = 0; q < kPairTM; ++q) {
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+            const int4 rb = *reinterpret_cast<const int4*>(s_back + 32 * q + 8 * r4 + 4 * lk);
+            const int b[4] = {rb.x, rb.y, rb.z, rb.w};
+#pragma unroll
+            for (int j = 0; j < kPairTN; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    Cs[(8 * r4 + 4 * lk + e) * kPairLd + j * 32 + li] = ldexpf(acc[q][j][4 * r4 + e], b[e] + cb[j]);
+        }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u0 = 0; u0 < 8; u0 += U) {
+            float4 z4[U], t4[U];
+            if constexpr (EPI == 1 || EPI == 2 || EPI == 4) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int64_t row = m0 + 32 * q + 4 * (u0 + u) + (lane >> 4);
+                    const int64_t ro = (row < n ? row : n - 1) * (int64_t)C;
+                    z4[u] = ld_quad<MODE>(args.Zl + ro, c, C);
+                    t4[u] = ld_quad<MODE>(args.tin + ro, c, C);
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int rl = 4 * (u0 + u) + (lane >> 4);
+                const int64_t row = m0 + 32 * q + rl;
+                const float4 v4 = *reinterpret_cast<const float4*>(Cs + rl * kPairLd + 4 * (lane & 15));
+                float v[4] = {v4.x, v4.y, v4.z, v4.w};
+                if constexpr (EPI == 1) {
+                    if (s_rs) {                          // (uniform)
+                        double rs[3];
+                        quad_row_sums<16>(rs, v, z4[u], t4[u], c, C, args.nu);
+                        const int p = lane & 15;
+                        if (p < 3) s_rs[(32 * q + rl) * 3 + p] = p == 0 ? rs[0] : p == 1 ? rs[1] : rs[2];
+                    }
+                }
+                const bool in = row < n && c < C;
+                if (in) epilogue_quad<EPI, MODE>(v, z4[u], t4[u], row * C + c, MODE == kFull ? 4 : C - c, args, dsum);
+                if constexpr (EPI == 1) {
+                    if (s_rm) {
+                        float m = in ? fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))) : 0.f;
+#pragma unroll
+                        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+                        if ((lane & 15) == 0) s_rm[32 * q + rl] = m;
+                    }
+                }
+            }
+        }
+    }
+}
+
+// A workgroup forms 128 rows by 256 columns.  A is split on its way to LDS (three buffers, so that a step's first
+// operands are read before the barrier that starts it); B comes from the L2 straight into registers, in operand layout
+// (pair_weights_kernel), a half step ahead: no wavefront reads what another does.  Two workgroups of four wavefronts share a
+// compute unit, one's epilogue beside the other's products.  Against one workgroup of 256 x 256, both operands in LDS, the large
+// product is as fast and the mid-sized one is not cut into three rounds and a bit: us for 500000 x 512 x 512 and 200000 x 256
+// x 256, bf16 split 1590 and 182, 256 x 256 946 and 195, 128 x 128 1090 and 186, this one 950 and 122.
+template <int EPI>
+__global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_nn_pair_kernel(
+    const float* __restrict__ A, const unsigned short* __restrict__ planes, const int* __restrict__ col_back,
+    const float* __restrict__ row_max, int max_tiles, float* __restrict__ out, int64_t n, int K, int C,
+    const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
+    double* __restrict__ partials, float* __restrict__ out_max, const int32_t* __restrict__ gate) {
+    if constexpr (EPI == 0) {
+        if (gate && *gate == 0) return;
+        // gated plain product, as in gemm_nn_kernel
+        if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
+    }
+    constexpr int WN = kPairWaves, NT = 64 * WN;
+    constexpr int AP = kPairRows * 4 / NT;               // pieces of eight k per thread and step
+    constexpr int BUF = kPairTM * kPairSub;
+    constexpr int kSlabs = WN * 32 * kPairLd * 4;        // bytes: the wavefronts' slabs, then (EPI 1) their rows' sums and maxima
+    constexpr int kSums = WN * kPairRows * 3 * 8, kMaxima = WN * kPairRows * 4;
+    static_assert(kSlabs + kSums + kMaxima <= 3 * BUF * 2, "the epilogue's share must fit the operand buffers");
+    __shared__ __align__(16) unsigned short smem[3 * BUF];
+    __shared__ __align__(16) int s_back[kPairRows];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 31, lk = lane >> 5;
+    const int ctiles = (C + kPairCols - 1) / kPairCols;
+    int64_t mtile;
+    int ctile;
+    xcd_group(blockIdx.x, gridDim.x, (unsigned)ctiles, mtile, ctile);
+    const int64_t m0 = mtile * kPairRows;
+    const int c0 = ctile * kPairCols + 64 * wave;          // this wavefront's columns
+    int steps = (K + kPairK - 1) / kPairK;
+    if constexpr (EPI == 2 || EPI == 4) {
+        if (unit->skip) {                                // as in gemm_nn_kernel
+            if (EPI == 2) return;
+            steps = 0;
+        }
+    }
+
+    // piece: eight k of a row, four pieces per row; rows past n repeat the last one, their results are never stored.  In LDS a
+    // piece is the 16 bytes of one lane in operand layout, lanes exchanged so that eight pieces written at once hit different banks.
+    const float* const At = A + m0 * K;
+    const int rows = (int)(n - m0 < kPairRows ? n - m0 : kPairRows);
+    int aoff[AP], aw[AP];
+    float scale[AP];
+#pragma unroll
+    for (int i = 0; i < AP; ++i) {
+        const int r = (tid + NT * i) >> 2, p = tid & 3, rr = r < rows ? r : rows - 1;
+        float m = 0.f;
+        for (int t0 = p; t0 < max_tiles; t0 += 16)               // (the four threads of a row share its tiles)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m = fmaxf(m, row_max[(int64_t)(t0 + 4 * u < max_tiles ? t0 + 4 * u : t0) * n + m0 + rr]);
+        m = fmaxf(m, __shfl_xor(m, 1, 64));
+        m = fmaxf(m, __shfl_xor(m, 2, 64));
+        const int back = pair_exponent(m);
+        scale[i] = pair_scale(back);
+        if (p == 0) s_back[r] = back;
+        aoff[i] = rr * K + 8 * p;
+        aw[i] = (r >> 5) * kPairSub + (p >> 1) * 1024 + ((p & 1) * 32 + ((r & 31) ^ (p << 2))) * 8;
+    }
+    const int nsub = (C + 31) / 32;
+    const half8* Bw[kPairTN];
+#pragma unroll
+    for (int j = 0; j < kPairTN; ++j) {
+        const int sub = c0 / 32 + j < nsub ? c0 / 32 + j : nsub - 1;         // (columns past C: never stored)
+        Bw[j] = reinterpret_cast<const half8*>(planes + (int64_t)sub * ((K + kPairK - 1) / kPairK) * kPairSub) + lane;
+    }
+
+    floatx16 acc[kPairTM][kPairTN];
+#pragma unroll
+    for (int i = 0; i < kPairTM; ++i)
+#pragma unroll
+        for (int j = 0; j < kPairTN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    float4u ra[AP][2];
+    auto fetch = [&](int kt, int i) {
+        const float* const p = At + kt * kPairK + aoff[i];
+        if (kt * kPairK + kPairK <= K) {
+            ra[i][0] = *reinterpret_cast<const float4u*>(p);
+            ra[i][1] = *reinterpret_cast<const float4u*>(p + 4);
+        } else {                                         // the last, partial step: zeros past K
+            const int left = K - kt * kPairK - 8 * (tid & 3);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float v = p[e < left ? e : left - 1];
+                ra[i][e >> 2][e & 3] = e < left ? v : 0.f;
+            }
+        }
+    };
+    auto stash = [&](unsigned short* D, int i) {
+        uint4v h, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            unsigned a, b;
+            split2_pair(ra[i][e >> 1][2 * (e & 1)], ra[i][e >> 1][2 * (e & 1) + 1], scale[i], a, b);
+            h[e] = a;
+            l[e] = b;
+        }
+        *reinterpret_cast<uint4v*>(D + aw[i]) = h;
+        *reinterpret_cast<uint4v*>(D + aw[i] + 512) = l;
+    };
+    half8 b[2][kPairTN][2], a[2][2];
+    auto load_b = [&](int half) {                        // both parts of this wavefront's columns, 16-k half `half` of the contraction
+        const int h = half < 2 * steps ? half : 2 * steps - 1;
+#pragma unroll
+        for (int j = 0; j < kPairTN; ++j)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) b[half & 1][j][p] = Bw[j][h * 128 + 64 * p];
+    };
+    // lane's operand of rows 32 i .., half kc: piece 2 kc + lk, lanes exchanged as they were written
+    const int ar0 = (lk * 32 + (li ^ (lk << 2))) * 8, ar1 = 1024 + (lk * 32 + (li ^ ((2 + lk) << 2))) * 8;
+    auto load_a = [&](int w, const unsigned short* S, int kc, int i) {
+        const unsigned short* const p = S + i * kPairSub + (kc ? ar1 : ar0);
+        a[w][0] = *reinterpret_cast<const half8*>(p);
+        a[w][1] = *reinterpret_cast<const half8*>(p + 512);
+    };
+    unsigned short *S0 = smem, *S1 = smem + BUF, *S2 = smem + 2 * BUF;       // this step's tile, the next one's, and where the one after goes
+    // STASH, FETCH: whether there are a step after the next and one after that
+    auto step = [&](int kt, auto STASH, auto FETCH) {
+        __syncthreads();
+        constexpr int SUBS = 2 * kPairTM;
+#pragma unroll
+        for (int st = 0; st < SUBS; ++st) {
+            const int kc = st / kPairTM, i = st % kPairTM, w = st & 1;
+            if (st + 1 < SUBS) load_a(w ^ 1, S0, (st + 1) / kPairTM, (st + 1) % kPairTM);
+            else load_a(w ^ 1, S1, 0, 0);                // (behind the last step: read and not used)
+            if (i == 0) load_b(2 * kt + kc + 1);
+#pragma unroll
+            for (int t = 0; t < 3; ++t)                  // smallest terms first
+#pragma unroll
+                for (int j = 0; j < kPairTN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[w][t == 0 ? 1 : 0], b[kc][j][t == 1 ? 1 : 0], acc[i][j], 0, 0, 0);
+            if constexpr (decltype(STASH)::value) {
+                if (st < AP) {
+                    stash(S2, st);
+                    if constexpr (decltype(FETCH)::value) fetch(kt + 3, st);
+                }
+            }
+            // the operands' reads first, then the split between the matrix instructions
+            __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+#pragma unroll
+            for (int u = 0; u < 3 * kPairTN; ++u) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 4, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        unsigned short* const t = S0;
+        S0 = S1;
+        S1 = S2;
+        S2 = t;
+    };
+    using yes = std::true_type;
+    using no = std::false_type;
+    if (steps > 0) {
+        load_b(0);
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            if (p >= steps) break;
+#pragma unroll
+            for (int i = 0; i < AP; ++i) fetch(p, i);
+            if (p < 2)
+#pragma unroll
+                for (int i = 0; i < AP; ++i) stash(smem + p * BUF, i);
+        }
+        __syncthreads();
+        load_a(0, S0, 0, 0);
+        int kt = 0;
+        for (; kt + 3 < steps; ++kt) step(kt, yes{}, yes{});
+        if (kt + 2 < steps) step(kt++, yes{}, no{});
+        for (; kt < steps; ++kt) step(kt, no{}, no{});
+    }
+    __syncthreads();                                     // every wavefront is through with the operands
+    float* const Cs = reinterpret_cast<float*>(smem) + wave * 32 * kPairLd;
+    double* const s_sums = reinterpret_cast<double*>(reinterpret_cast<char*>(smem) + kSlabs);
+    float* const s_maxima = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + kSlabs + kSums);
+    // (epilogue 1 has no partials: the argument then carries the row sums)
+    double* const row_sums = EPI == 1 ? partials : nullptr;
+    int cb[kPairTN];
+#pragma unroll
+    for (int j = 0; j < kPairTN; ++j) cb[j] = col_back[c0 + 32 * j + li < C ? c0 + 32 * j + li : C - 1];
+    EpilogueArgs args{out, Zl, (EPI == 2 || EPI == 4) ? Tio : Tl, nu, Tio, 0.0, false, false};
+    double dsum = 0.0;
+    if constexpr (EPI == 2 || EPI == 4) {
+        args.hold = EPI == 4 && unit->skip != 0;
+        args.inv0 = unit->skip ? 0.0 : 1.0 / unit->step0;
+        args.take = unit->spec != 0 && !unit->skip;
+    }
+    double* const s_rs = EPI == 1 && row_sums ? s_sums + wave * kPairRows * 3 : nullptr;
+    float* const s_rm = EPI == 1 && out_max ? s_maxima + wave * kPairRows : nullptr;
+    if (C % 4 == 0) pair_epilogue<EPI, kFull>(acc, Cs, s_back, cb, m0, c0, n, C, args, dsum, s_rs, s_rm);
+    else pair_epilogue<EPI, kTail>(acc, Cs, s_back, cb, m0, c0, n, C, args, dsum, s_rs, s_rm);
+    if constexpr (EPI == 1) {
+        if (row_sums || out_max) {
+            __syncthreads();
+            for (int r = tid; r < kPairRows; r += NT) {
+                const int64_t row = m0 + r;
+                if (row >= n) break;
+                const int64_t o = (int64_t)ctile * n + row;
+                if (row_sums) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        double s = 0.0;
+#pragma unroll
+                        for (int w = 0; w < WN; ++w) s += s_sums[(w * kPairRows + r) * 3 + q];
+                        row_sums[o * 3 + q] = s;
+                    }
+                }
+                if (out_max) {
+                    float m = 0.f;
+#pragma unroll
+                    for (int w = 0; w < WN; ++w) m = fmaxf(m, s_maxima[w * kPairRows + r]);
+                    out_max[o] = m;
+                }
+            }
+        }
+    }
+    if constexpr (EPI == 2 || EPI == 4) {
+        __shared__ double red[WN];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) dsum += __shfl_down(dsum, o, 64);
+        if (lane == 0) red[wave] = dsum;
+        __syncthreads();
+        if (tid == 0) {
+            double s = 0.0;
+#pragma unroll
+            for (int w = 0; w < WN; ++w) s += red[w];
+            partials[blockIdx.x] = 0.5 * (double)nu * s;
+        }
+    }
 }
 
 // out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 16.
@@ -1361,7 +1771,9 @@ __global__ __launch_bounds__(256) void stream_update_kernel(const float4* __rest
     }
 }
 
-int g_split = 1;      // 1: wide products run on the bf16 matrix cores with three-way split operands, 0: fp32 MFMA
+// 1: wide products run on the 16-bit matrix cores with split operands (pairs of fp16 or three bf16, by size), 0: fp32 MFMA,
+// 2: pairs of fp16 wherever gemm_nn_pair_form allows
+int g_split = 1;
 
 // Tiles per wavefront direction of the split product out[n x C]: 128 x 128 tiles where they give every compute unit two, else
 // 64 x 64 (see gemm_nn_split_kernel).
@@ -1372,6 +1784,21 @@ int nn_tile(int64_t n, int C, int split) {
 }
 
 }  // namespace
+
+// (below 64 long sums the pairs are the less accurate split)
+bool gemm_nn_pair_form(int K, int C) { return K >= 64 && C >= kPairLeast; }
+// A workgroup's tile is larger than the bf16 kernels' and B takes a launch of its own to be split (5 us): pairs pay from 128 long
+// sums and 150 tiles on, or fewer tiles of longer sums.  us with bf16 and with pairs, that launch with them: 20000 x 256 x 256 (157
+// tiles) 24.5 and 21.4, 12000 x 128 x 512 (188) 17.8 and 17.1, 8000 x 512 x 512 (126) 36 and 32, 8000 x 256 x 512 21.0 and
+// 21.4, 12000 x 256 x 256 (94) 17.3 and 20.2, 30000 x 64 x 300 (470) 15.6 and 18.2, 200000 x 256 x 256 163 and 124, 13752 x 767
+// x 1000 149 and 83.
+bool gemm_nn_pair(int64_t n, int K, int C) {
+    if (!gemm_nn_pair_form(K, C) || g_split == 0) return false;
+    const int64_t tiles = ((n + kPairRows - 1) / kPairRows) * gemm_nn_pair_tiles(C);
+    return g_split == 2 || (K >= 128 && (tiles >= 150 || tiles * K >= 60000));
+}
+int gemm_nn_pair_tiles(int C) { return (C + kPairCols - 1) / kPairCols; }
+size_t gemm_nn_pair_planes(int K, int C) { return (size_t)((K + kPairK - 1) / kPairK) * ((C + 31) / 32) * kPairSub; }
 
 // Scratch is asked for by shape alone, so that a workspace holds what its shapes need however the library is tuned later.
 // The base is that of chunks of at least 256 rows, about 1024 workgroups of 128-row tiles; callers are refused by it.  Small
@@ -1435,16 +1862,31 @@ TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
 
 }  // namespace
 
-void set_gemm_split(int on) { g_split = on ? 1 : 0; }
+void set_gemm_split(int mode) { g_split = mode == 0 || mode == 2 ? mode : 1; }
 int get_gemm_split() { return g_split; }
 
 void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, int64_t n, int K, int C,
                     const GemmEpilogue& epi) {
     if (n <= 0 || C <= 0) return;
     const dim3 block(256);
+    if (epi.pair.planes && gemm_nn_pair(n, K, C)) {
+        const PairOperands& p = epi.pair;
+        if (!p.ready) hipLaunchKernelGGL(pair_weights_kernel, dim3((unsigned)((C + 31) / 32)), dim3(1024), 0, s, B, K, C, p.planes, p.col_back, epi.gate);
+        const dim3 grid((unsigned)gemm_nn_blocks(n, C, true));
+#define CADMM_PAIR(E_, Tl_, unit_, partials_, out_max_, gate_) \
+        hipLaunchKernelGGL(gemm_nn_pair_kernel<E_>, grid, dim3(64 * kPairWaves), 0, s, A, p.planes, p.col_back, p.row_max, p.max_tiles, out, \
+                           n, K, C, epi.Zl, Tl_, epi.nu, epi.Tio, unit_, partials_, out_max_, gate_)
+        if (epi.kind == 3) CADMM_PAIR(3, nullptr, nullptr, nullptr, nullptr, nullptr);
+        else if (epi.kind == 2 && epi.leave_g) CADMM_PAIR(4, nullptr, epi.unit, epi.partials, nullptr, nullptr);
+        else if (epi.kind == 2) CADMM_PAIR(2, nullptr, epi.unit, epi.partials, nullptr, nullptr);
+        else if (epi.kind == 1) CADMM_PAIR(1, epi.Tl, nullptr, epi.row_sums, epi.out_max, nullptr);
+        else CADMM_PAIR(0, nullptr, epi.unit, nullptr, nullptr, epi.gate);
+#undef CADMM_PAIR
+        return;
+    }
     if (C > 32) {
         const int t = nn_tile(n, C, g_split);
-        const dim3 grid((unsigned)gemm_nn_blocks(n, C));
+        const dim3 grid((unsigned)gemm_nn_blocks(n, C, false));
 #define CADMM_NN(K4_, K3_, K2_, K1_, K0_) \
         if (epi.kind == 3) \
             hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, nullptr, nullptr); \
@@ -1489,7 +1931,8 @@ void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const
     hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, Bcat, Wt, out, n, K1, K2, C, nu, row_sums);
 }
 
-int gemm_nn_tiles(int64_t n, int C) {
+int gemm_nn_tiles(int64_t n, int C, bool pair) {
+    if (pair) return gemm_nn_pair_tiles(C);
     const int b = 64 * nn_tile(n, C, g_split);
     return (C + b - 1) / b;
 }
@@ -1498,7 +1941,8 @@ int gemm_nn_most_tiles(int64_t n, int C) {
     return (C + b - 1) / b;
 }
 
-int64_t gemm_nn_blocks(int64_t n, int C) {
+int64_t gemm_nn_blocks(int64_t n, int C, bool pair) {
+    if (pair) return ((n + kPairRows - 1) / kPairRows) * gemm_nn_pair_tiles(C);
     const int b = 64 * nn_tile(n, C, g_split);
     return ((n + b - 1) / b) * ((C + b - 1) / b);
 }

@@ -14,6 +14,8 @@ namespace cadmm {
 // sums over the tile's columns that the search for theta needs of the gradient g just formed: sum e g with
 // e = Zl - relu(Tl), sum g^2, sum Zl^2 (three doubles at row_sums + (tile * rows + row) * 3), so that the search does not
 // have to read the three N x C_l matrices again.
+// RowMax: with row_max (widths of four and more) the launch leaves, per column tile and row, the largest magnitude of the
+// result (one float at row_max + tile * rows + row), which a product that takes the result as its left operand scales by.
 // gate (epilogue 0; may be null): the launch does nothing where *gate is 0, see ZTrialArgs.
 struct SpmmEpilogue {
     int kind = 0;
@@ -22,6 +24,7 @@ struct SpmmEpilogue {
     const float* Tl = nullptr;
     float nu = 0.f;
     double* row_sums = nullptr;
+    float* row_max = nullptr;
 };
 // Device view of a row list laid out for the aggregation (RowSchedule on the host).  rec[i] = (first chunk, one past
 // the last chunk, output row, 0) of scheduled row i; a chunk is 8 (column, value) pairs of 8 bytes, padded with
@@ -77,8 +80,18 @@ struct Unit;
 // Where the search takes no step at all (unit->skip) nothing reads Q: the product is not formed, out gets G with leave_g.
 // epilogue 3 (forward pass): Tio = relu(A B), and out = A B unless out is null; a pass over the pre-activations of its own
 // would read them once more (200000 x 256: 76 us).
+// What a product needs to run on pairs of fp16 (gemm_nn_pair): RowMax of A, and scratch for B in operand layout; ready: the
+// scratch holds it already.
+struct PairOperands {
+    const float* row_max = nullptr;
+    int max_tiles = 0;
+    unsigned short* planes = nullptr;    // gemm_nn_pair_planes(K, C) of them
+    int* col_back = nullptr;             // C
+    bool ready = false;
+};
 struct GemmEpilogue {
     int kind = 0;
+    PairOperands pair;
     const float* Zl = nullptr;
     const float* Tl = nullptr;
     float nu = 0.f;
@@ -87,14 +100,21 @@ struct GemmEpilogue {
     const int32_t* gate = nullptr;   // epilogue 0: nothing is formed where *gate is 0, see ZTrialArgs
     bool leave_g = false;
     double* partials = nullptr;
-    double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C) column tiles
+    double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C, pair) column tiles
+    float* out_max = nullptr;      // epilogue 1 on pairs: RowMax of the result, per tile as row_sums
 };
-int gemm_nn_tiles(int64_t n, int C);           // column tiles of that launch (C > 32)
+// Whether a product with PairOperands runs on them: by form (for what is laid out), by form and size.
+bool gemm_nn_pair_form(int K, int C);
+bool gemm_nn_pair(int64_t n, int K, int C);
+int gemm_nn_pair_tiles(int C);
+size_t gemm_nn_pair_planes(int K, int C);
+int gemm_nn_tiles(int64_t n, int C, bool pair);        // column tiles of the launch (C > 32); pair: with PairOperands, gemm_nn_pair
 int gemm_nn_most_tiles(int64_t n, int C);      // most of them, whatever set_gemm_split says
 void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, int64_t n, int K, int C,
                     const GemmEpilogue& epi = GemmEpilogue());
-// 1: plain products wider than 32 columns use three-way bf16 splits of both operands on the bf16 matrix cores
-void set_gemm_split(int on);
+// 1: products wider than 32 columns split both operands for the 16-bit matrix cores (2: into pairs of fp16 wherever the form
+// allows, for tests), 0: fp32 MFMA
+void set_gemm_split(int mode);
 int get_gemm_split();
 // calibration kernels: chains of fp32 MFMAs on registers (returns the flops of the launch; out: blocks * 256 floats),
 // and a plain copy of count floats (count % 4 == 0)
@@ -104,7 +124,7 @@ double launch_mfma_bf16_chain(hipStream_t s, float* out, int blocks, int iters, 
 void launch_stream_copy(hipStream_t s, const float* src, float* dst, int64_t count);
 // dst = 0.999 dst + src in place (count % 4 == 0): two reads and one write-back per element
 void launch_stream_update(hipStream_t s, const float* src, float* dst, int64_t count);
-int64_t gemm_nn_blocks(int64_t n, int C);      // grid size of that launch (= block results of epilogue 2)
+int64_t gemm_nn_blocks(int64_t n, int C, bool pair);   // grid size of that launch (= block results of epilogue 2)
 // out[n x C] = [nu (Zl - relu(Tl)) | SG] * Bcat, Bcat = [W (K1 x C); S (K2 x C)], C <= 32, K1 % 4 == K2 % 4 == 0:
 // the product (grad_Z psi) W with grad = nu (Zl - relu(Tl)) + SG W^T, S = W^T W, the gradient never stored.
 // The rows' RowSums (one tile) are left on the way: the gradient is rebuilt per element with Wt = W^T (C x K1), the

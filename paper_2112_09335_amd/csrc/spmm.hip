@@ -74,6 +74,15 @@ __device__ __forceinline__ void reduce_row_sums(double (&s)[3], int lpr_log2) {
         for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], o, 64);
 }
 
+// Largest magnitude of a result row (RowMax): this lane's quad, over 2^lpr_log2 neighbouring lanes; every one of them gets it.
+__device__ __forceinline__ float quad_max(const float (&v)[4]) {
+    return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+}
+__device__ __forceinline__ float reduce_row_max(float m, int lpr_log2) {
+    for (int o = 1; o < (1 << lpr_log2); o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+    return m;
+}
+
 // Slice k of the workgroup table (the workgroups of XCD k) is [start[k], start[k+1]).
 struct XcdMap {
     long long start[9];
@@ -140,7 +149,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EP
     const int4* __restrict__ rec, int64_t nrows, const int2* __restrict__ ent, const float* __restrict__ X,
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
     XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu,
-    double* __restrict__ row_sums, int64_t n_out, const int32_t* __restrict__ gate) {
+    double* __restrict__ row_sums, float* __restrict__ row_max, int64_t n_out, const int32_t* __restrict__ gate) {
     if (EPI == 0 && gate && *gate == 0) return;
     // Workgroup b belongs to XCD b mod 8 and takes the (b / 8)-th entry of that XCD's slice of the table (or, without
     // the XCD-aware numbering, simply entry b).  Records from nrows on are the parts of split rows.
@@ -228,6 +237,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EP
                         for (int q = lpr; q < 3; ++q) o[q] = q == 1 ? rs[1] : rs[2];
                 }
             }
+        }
+    }
+    if constexpr (VEC == 4) {
+        if (row_max && !is_part) {                       // (every lane of the row's first group; off lanes hold its last columns)
+            const float m = reduce_row_max(quad_max(acc), lpr_log2);
+            if (sub == 0) row_max[(int64_t)blockIdx.y * n_out + r.z] = m;
         }
     }
     if (!on) return;
@@ -323,7 +338,7 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
                                                           float* __restrict__ Y, int width,
                                                           const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                           float nu, int lpr_log2, double* __restrict__ row_sums,
-                                                          int n_tiles, int64_t n_out, const int32_t* __restrict__ gate) {
+                                                          float* __restrict__ row_max, int n_tiles, int64_t n_out, const int32_t* __restrict__ gate) {
     const int64_t i = blockIdx.x;
     if (i >= n_long || (EPI == 0 && gate && *gate == 0)) return;
     const int64_t row = long_row[i];
@@ -331,6 +346,7 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
     const int lpr = 1 << lpr_log2, groups = 64 >> lpr_log2;
     const int sub = threadIdx.x & (lpr - 1), grp = threadIdx.x >> lpr_log2;
     double rs[3] = {0.0, 0.0, 0.0};
+    float most = 0.f;
     for (int cb = 0; cb < width; cb += lpr * VEC) {             // same trip count in every lane
         const bool ok = cb + sub * VEC < width;
         const int c = cb + sub * VEC + VEC <= width ? cb + sub * VEC : width - VEC;
@@ -359,7 +375,14 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
             for (int v = 0; v < VEC; ++v) acc[v] = nu * (z[v] - fmaxf(t[v], 0.f)) + acc[v];
             if constexpr (VEC == 4) add_row_sums(rs, acc, z, t, cb + sub * VEC - c);
         }
+        if constexpr (VEC == 4) most = fmaxf(most, quad_max(acc));
         store_vec<VEC>(Y + o, acc);
+    }
+    if constexpr (VEC == 4) {
+        if (row_max && grp == 0) {                              // likewise for the largest magnitude
+            most = reduce_row_max(most, lpr_log2);
+            for (int tile = sub; tile < n_tiles; tile += lpr) row_max[(int64_t)tile * n_out + row] = tile == 0 ? most : 0.f;
+        }
     }
     if constexpr (EPI == 1 && VEC == 4) {
         if (row_sums && grp == 0) {                             // the whole row's sums in the first tile's place
@@ -420,9 +443,9 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
 #define CADMM_ROWS(L_) do { if (off32) CADMM_ROWS_OFF(L_, 1); else CADMM_ROWS_OFF(L_, 0); } while (0)
 #define CADMM_ROWS_OFF(L_, O_) do { \
         if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
-                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, sc.n_out, nullptr); \
+                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, epi.row_max, sc.n_out, nullptr); \
         else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
-                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, 0, epi.gate); } while (0)
+                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, epi.row_max, sc.n_out, epi.gate); } while (0)
         if (lpr_log2 == 0) CADMM_ROWS(0);
         else if (lpr_log2 == 1) CADMM_ROWS(1);
         else if (lpr_log2 == 2) CADMM_ROWS(2);
@@ -437,10 +460,10 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         if (epi.kind == 1)
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
                                sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2, epi.row_sums,
-                               (width + tile - 1) / tile, sc.n_out, nullptr);
+                               epi.row_max, (width + tile - 1) / tile, sc.n_out, nullptr);
         else
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
-                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, 0, 0, epi.gate);
+                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, epi.row_max, (width + tile - 1) / tile, sc.n_out, epi.gate);
     }
 }
 

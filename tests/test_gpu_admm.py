@@ -432,6 +432,52 @@ def test_fp32_matrix_core_path_matches_the_oracle_too():
         probe.close()
 
 
+@pytest.fixture
+def pairs_everywhere():
+    """The products on pairs of fp16 wherever their form allows, not from a size on (process-wide)."""
+    from paper_2112_09335_amd import binding
+    probe = binding.Solver(device=-1)
+    probe.tune("gemm_split", 2)
+    yield
+    probe.tune("gemm_split", 1)
+    probe.close()
+
+
+# One column tile, and a part of a second; contractions of one step, of whole and of partial ones; the gradient
+# of Z by the product and by the aggregation; split rows, whose largest magnitude the combine kernel leaves
+@pytest.mark.parametrize("dims,more,hubs", [([101, 301, 90, 6], {}, 0), ([64, 97, 97, 256, 257, 7], {"step_policy": 1}, 0),
+                                            ([96, 256, 256, 10], {"schedule": 1}, 3), ([67, 449, 261, 65, 3], {"dual_form": 1}, 3)])
+def test_products_on_pairs_inside_the_sweep(pairs_everywhere, dims, more, hubs):
+    w = synth.make_workload("pairs", 31 + len(dims), 1501, 5, dims, dims[-1], 4, graph="sbm", features="gaussian",
+                            avg_degree=9, frac_intra=0.8, labelled_fraction=0.7)
+    if hubs:
+        w = synth.add_hubs(w, 5, hubs, 700, 0.5)
+    w.hyper.update(more)
+    run_case(w, 4, "pairs/" + "-".join(map(str, dims)))
+
+
+@pytest.mark.parametrize("N,K,C", [(1, 64, 129), (127, 65, 130), (128, 95, 192), (129, 96, 193), (1000, 97, 255), (300, 512, 256),
+                                   (257, 129, 257), (640, 1000, 513)])
+def test_product_on_pairs_of_scaled_rows_and_columns(pairs_everywhere, N, K, C):
+    """Without edges A~ is the identity and the forward pass leaves relu(X W_1): rows of X and columns of W_1 from 1e-12 to 1e12
+    (and zero rows) keep the accuracy of a 32-bit product, since each has a scale of its own."""
+    from paper_2112_09335_amd import binding
+    rng = np.random.default_rng(N + K + C)
+    X = rng.standard_normal((N, K)) * 10.0 ** rng.integers(-12, 13, (N, 1)) * (rng.random((N, 1)) < 0.95)
+    X, W1 = X.astype(np.float32), (rng.standard_normal((K, C)) * 10.0 ** rng.integers(-12, 13, (1, C))).astype(np.float32)
+    s = binding.Solver(0)
+    s.build_graph(N, np.zeros(0, np.int32), np.zeros(0, np.int32), 1, np.zeros(N, np.int32))
+    s.set_model([K, C, 3], **synth.DEFAULT_HYPER)
+    s.set_workspace()
+    s.set_data(X, np.zeros(N, np.int32))
+    s.init([W1, np.ones((C, 3), np.float32)])
+    got = s.get_Z(1)
+    s.close()
+    exact, mag = X.astype(np.float64) @ W1.astype(np.float64), np.abs(X).astype(np.float64) @ np.abs(W1).astype(np.float64)
+    # (the tolerance of the other split products: a few roundings of 32-bit sums)
+    assert np.all(np.abs(got - np.maximum(exact, 0.0)) <= 2e-6 * mag)
+
+
 def test_hub_rows_and_hub_segments_are_split_inside_the_sweep():
     """Rows and (row, community) segments above the aggregation's split threshold (384 entries), as the power-law graph
     has them at full size, inside whole iterations: the aggregation that carries the penalty term nu (Z_l - relu(T_l))
