@@ -103,12 +103,16 @@ struct cadmm_ctx {
     float* fistaX = nullptr;    // N x C_L each: x_j and y_j of that solve
     float* fistaY = nullptr;
     int32_t* gates = nullptr;          // [L]: whether any community of layer l = 1..L-1 takes a Z step (floor_first)
+    int32_t* run_w = nullptr;          // [L+1] each: whether layer l's W and Z steps are worth forming (launch_rest_w)
+    int32_t* run_z = nullptr;
     LayerScalars* scalars = nullptr;   // [L+1]
     int32_t* status = nullptr;
     // What the buffers hold at the moment.  base_valid: every H_l and T_l belongs to the current iterate.  gl_valid /
     // gh_valid: so does G_L / do the G_l of the hidden layers that need one.  scal_valid: so do the readout scalars.
     // stepped: an iteration has been run since the state was set from outside (there is a dual residual).
-    bool base_valid = false, gl_valid = false, gh_valid = false, scal_valid = false, stepped = false;
+    // rest_fresh: gates and unitsW tell what the last sweep moved, and since then nothing has been written but what a sweep
+    // writes; rest: the sweep being enqueued knows that.
+    bool base_valid = false, gl_valid = false, gh_valid = false, scal_valid = false, stepped = false, rest_fresh = false, rest = false;
     int iter = 0;
     // The pre-activations T_l = A~ Z_{l-1} W_l are carried from one iteration to the next instead of being
     // formed anew: the W step leaves T_l - Q/tau = A~ Z_{l-1}^k W_l^{k+1}, and the Z step of layer l-1 changes
@@ -124,8 +128,8 @@ struct cadmm_ctx {
     bool use_lowrank = true;
     bool use_speculative = true;
     int use_floor_first = 1;     // 0: never, 1: by size, 2: wherever the row sums allow it
-    struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false; };
-    GraphSlot graphs[32];
+    struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false, rest_after = false; };
+    GraphSlot graphs[64];
     // Kernel-level calls on a stream of the caller's (cadmm_op_stream): such a call is launched there, after what the context's
     // own stream holds (own_busy: something may still run on it) and after the kernel-level call before it; whatever uses
     // the own stream next waits for it (op_busy).  op_unrecorded: the last of them was on the null stream, and the event that
@@ -382,6 +386,8 @@ size_t layout(cadmm_ctx* c, char* base) {
         c->fistaY = b.take<float>(N * c->C[L]);
     }
     c->gates = b.take<int32_t>(L);
+    c->run_w = b.take<int32_t>(L + 1);
+    c->run_z = b.take<int32_t>(L + 1);
     c->scalars = b.take<LayerScalars>(L + 1);
     c->status = b.take<int32_t>(4);
     return (b.off + 255) & ~(size_t)255;
@@ -493,21 +499,22 @@ SearchParams search_params(const cadmm_ctx* c) {
     return sp;
 }
 
-void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpilogue& epi) {
+void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpilogue& epi, const Unless& unless = Unless()) {
     timed(c, epi.kind ? P_SPMM_GRADZ : P_SPMM, spmm_bytes(c, c->hg.N, width, epi.kind ? 2 : 0),
           2.0 * (double)c->hg.nnz * width, [&] {
               launch_spmm(c->stream, schedule_of(c, c->d_rows, c->hg.row_sched), X, Y, width, epi);
-          });
+          }, unless);
 }
 
-// H_l = A~ X, with its RowMax where the products with H_l run on pairs.
-void aggregate_H(cadmm_ctx* c, const float* X, int l) {
+// H_l = A~ X, with its RowMax where the products with H_l run on pairs.  gate (may be null): where *gate is 0 it is there already.
+void aggregate_H(cadmm_ctx* c, const float* X, int l, const int32_t* gate = nullptr) {
     SpmmEpilogue e;
+    e.gate = gate;
     const int K = c->C[l - 1], tiles = row_tiles(c, K);
     const bool max = gemm_nn_pair(c->hg.N, K, c->C[l]) && tiles <= c->h_max_room[l];
     if (max) e.row_max = c->h_max[l];
     c->h_max_tiles[l] = max ? tiles : 0;
-    aggregate(c, X, c->H[l], K, e);
+    aggregate(c, X, c->H[l], K, e, Unless{note_flag(c, gate), 0, P_OTHER, 0.0});
 }
 
 // For products with a left operand whose RowMax has that many tiles (0: there is none).
@@ -540,6 +547,29 @@ GemmEpilogue forward_epilogue(const cadmm_ctx* c, int l, float* relu_out) {
     return e;
 }
 
+// How the Z search of hidden layer l goes about it: what its gradient and everything after that depends on.
+// gate: the step floor is tested before grad W_{l+1} and the segment products are formed (null: with the search).  From the
+// forward pass on an iteration's steps reach one layer further back each time; until then a layer's gradient is below
+// resolution, and without a step in any community nothing of what only a step needs is formed.  That costs two launches
+// (9 us in every iteration): 1 % and less of an iteration from 2^24 entries on (65536 x 256: 0.9 ms).
+struct ZSearch { GradPath path; int sum_tiles; int32_t* gate; };
+ZSearch z_search(const cadmm_ctx* c, int l) {
+    ZSearch z;
+    z.path = grad_path(c, l);
+    z.sum_tiles = sum_tiles_of(c, l, z.path);
+    if (z.sum_tiles > c->row_sum_tiles) z.sum_tiles = 0;      // (the tiles' width was tuned since the workspace was laid out)
+    const bool large = c->hg.N * (int64_t)c->C[l] >= (int64_t)1 << 24;
+    z.gate = z.sum_tiles > 0 && (c->use_floor_first == 2 || (c->use_floor_first == 1 && large)) ? c->gates + l : nullptr;
+    return z;
+}
+
+// Whether a sweep keeps track of which layers rest: where any of them looks at the step floor first.
+bool tracks_rest(const cadmm_ctx* c) {
+    for (int l = 1; l < c->L && c->schedule == 0; ++l)
+        if (z_search(c, l).gate) return true;
+    return false;
+}
+
 // T_l = A~ Z_{l-1} W_l in the association chosen for the layer.  Used by the initial forward pass and
 // by every base evaluation, so that re-evaluating an unchanged point reproduces T_l bit for bit.
 // relu_out (may be null): also gets relu(T_l).
@@ -552,7 +582,8 @@ void compute_T(cadmm_ctx* c, int l, bool force = false, float* relu_out = nullpt
         aggregate(c, c->tmpV, c->T[l], c->C[l], SpmmEpilogue());
         if (relu_out) launch_relu(c->stream, c->T[l], relu_out, N * c->C[l], 1);
     } else {
-        if (l >= 2) aggregate_H(c, c->Z[l - 1], l);                                    // the W step needs H_l itself
+        // the W step needs H_l itself; where Z_{l-1} has not moved since it was formed it is as it was
+        if (l >= 2) aggregate_H(c, c->Z[l - 1], l, c->rest_fresh && !force ? z_search(c, l - 1).gate : nullptr);
         if (carried) return;
         gemm_nn(c, c->H[l], c->W[l], c->T[l], N, c->C[l - 1], c->C[l], forward_epilogue(c, l, relu_out));
     }
@@ -569,7 +600,7 @@ void form_T(cadmm_ctx* c) {
     for (int l = 1; l <= c->L; ++l) compute_T(c, l);
     if (!reuse) {                                // every T_l was just formed exactly
         c->t1_age = 0;
-        c->gl_valid = false;
+        c->gl_valid = c->rest_fresh = false;
     }
     c->base_valid = true;
 }
@@ -615,22 +646,6 @@ void eval_scalars(cadmm_ctx* c) {
     c->gl_valid = c->gh_valid = true;
     launch_risk(c->stream, c->Z[L], c->d_labels, N, c->C[L], c->risk, c->partials, c->scalars + L);
     c->scal_valid = true;
-}
-
-// How the Z search of hidden layer l goes about it: what its gradient and everything after that depends on.
-// gate: the step floor is tested before grad W_{l+1} and the segment products are formed (null: with the search).  From the
-// forward pass on an iteration's steps reach one layer further back each time; until then a layer's gradient is below
-// resolution, and without a step in any community nothing of what only a step needs is formed.  That costs two launches
-// (9 us in every iteration): 1 % and less of an iteration from 2^24 entries on (65536 x 256: 0.9 ms).
-struct ZSearch { GradPath path; int sum_tiles; int32_t* gate; };
-ZSearch z_search(const cadmm_ctx* c, int l) {
-    ZSearch z;
-    z.path = grad_path(c, l);
-    z.sum_tiles = sum_tiles_of(c, l, z.path);
-    if (z.sum_tiles > c->row_sum_tiles) z.sum_tiles = 0;      // (the tiles' width was tuned since the workspace was laid out)
-    const bool large = c->hg.N * (int64_t)c->C[l] >= (int64_t)1 << 24;
-    z.gate = z.sum_tiles > 0 && (c->use_floor_first == 2 || (c->use_floor_first == 1 && large)) ? c->gates + l : nullptr;
-    return z;
 }
 
 CarryArgs carry_args(const cadmm_ctx* c, int l) {
@@ -698,14 +713,17 @@ void w_update(cadmm_ctx* c, int l) {
         right = c->H[l];
     }
     const bool fly = gradient_on_the_fly(c, l);    // G_l = nu (relu(T_l) - Z_l) 1[T_l > 0] formed inside the product
+    // where the layer rests its search is left as it ended, with no step, and its G_l as it is
+    const int32_t* const run = c->rest && fly && z_search(c, l).gate ? c->run_w + l : nullptr;
+    const Unless resting{note_flag(c, run), 0, P_OTHER, 0.0};
     int n_norms = 0;
     timed(c, Cl > 32 ? P_GEMM_TN : P_GEMM_TN_32,
           4.0 * ((double)N * K + (double)N * Cl * (fly ? 2 : 1) + (double)K * Cl), 2.0 * (double)N * K * Cl,
           [&] {
               n_norms = launch_gemm_tn(s, left, fly ? c->T[l] : right, c->gradW, N, K, Cl, c->tn_partial,
-                                       fly ? c->Z[l] : nullptr, c->nu, c->W[l], c->partials);
-          });
-    timed(c, P_OTHER, 16.0 * n_norms, 0.0, [&] { launch_w_begin(s, c->partials, n_norms, unit, sp); });
+                                       fly ? c->Z[l] : nullptr, c->nu, c->W[l], c->partials, run);
+          }, resting);
+    timed(c, P_OTHER, 16.0 * n_norms, 0.0, [&] { launch_w_begin(s, c->partials, n_norms, unit, sp, run); }, resting);
     const int skip = note_flag(c, &unit->skip);                                  // a step below resolution is not taken
     float* Q = c->G[l];                                                          // G_l is no longer needed
     const bool leave_g = !last && leaves_gradient(c, l);
@@ -720,6 +738,7 @@ void w_update(cadmm_ctx* c, int l) {
         GemmEpilogue ge;
         ge.kind = 2; ge.Zl = c->Z[l]; ge.nu = c->nu; ge.Tio = c->T[l]; ge.unit = unit; ge.partials = c->partials; ge.leave_g = leave_g;
         ge.pair = pair_of_H(c, l);
+        ge.gate = run;
         const bool on_pairs = ge.pair.planes && gemm_nn_pair(N, K, Cl);
         timed(c, P_GEMM_NN_128_TRIAL, 4.0 * ((double)N * K + (double)K * Cl + (leave_g ? 4.0 : 3.0) * (double)count), 2.0 * (double)N * K * Cl,
               [&] {
@@ -791,6 +810,9 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     // grad W_{l+1} runs on pairs if whatever forms the gradient can leave its RowMax
     const bool want_max = !lowrank && gemm_nn_pair(N, Cl, Cn);
     int max_tiles = 0;
+    // where the layer rests the gradient is below resolution as it was
+    const int32_t* const run = c->rest && how.gate ? c->run_z + l : nullptr;
+    const Unless resting{note_flag(c, run), 0, P_OTHER, 0.0};
     if (lowrank) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
         timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] { launch_lowrank_operand(s, c->W[l + 1], c->Bcat, Cl, Cn); });
@@ -800,17 +822,21 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     } else if (path == kGradProduct) {
         const bool on_pairs = grad_on_pairs(c, l);
         SpmmEpilogue epi;
+        epi.gate = run;
         if (on_pairs) epi.row_max = c->a_max;
-        aggregate(c, c->G[l + 1], c->tmpA, Cn, epi);                             // A~ G_{l+1}
+        aggregate(c, c->G[l + 1], c->tmpA, Cn, epi, resting);                    // A~ G_{l+1}
         GemmEpilogue ge;
+        ge.gate = run;
         if (on_pairs) {
             ge.pair = pair_operands(c, c->a_max, row_tiles(c, Cn));
             if (want_max) { ge.out_max = c->b_max; max_tiles = gemm_nn_pair_tiles(Cl); }
         }
         ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu; ge.row_sums = row_sums;
-        gemm_nn(c, c->tmpA, Wt, c->tmpB, N, Cn, Cl, ge);
+        gemm_nn(c, c->tmpA, Wt, c->tmpB, N, Cn, Cl, ge, resting);
     } else {
-        gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl);                         // G_{l+1} W_{l+1}^T
+        GemmEpilogue ge;
+        ge.gate = run;
+        gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl, ge, resting);            // G_{l+1} W_{l+1}^T
         SpmmEpilogue epi;
         epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu; epi.row_sums = row_sums;
         if (want_max && row_tiles(c, Cl) <= c->b_max_room) { epi.row_max = c->b_max; max_tiles = row_tiles(c, Cl); }
@@ -828,8 +854,10 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     a.Gn = c->G[l + 1];
     a.next_is_last = next_last;
     a.gate = how.gate;
+    a.run = run;
+    a.moved = tracks_rest(c) ? c->gates + l : nullptr;
     a.sp = sp; a.units = units; a.partials = c->partials; a.status = c->status;
-    if (a.gate) timed(c, P_Z_TRIAL, 4.0 * 6.0 * sum_tiles * (double)N, 0.0, [&] { launch_z_floor(s, a); });
+    if (a.gate) timed(c, P_Z_TRIAL, 4.0 * 6.0 * sum_tiles * (double)N, 0.0, [&] { launch_z_floor(s, a); }, resting);
     c->gate_notes[l] = note_flag(c, a.gate);
     const Unless gated = unless_gated(c, l);
     if (!lowrank) {
@@ -933,7 +961,10 @@ void sweep(cadmm_ctx* c) {
     } else {
         const int L = c->L;
         base_eval(c);
+        c->rest = c->rest_fresh && tracks_rest(c);
+        if (c->rest) launch_rest_w(c->stream, L, c->unitsW, c->gates, c->run_w, c->run_z);
         for (int l = 1; l <= L; ++l) w_update(c, l);
+        if (c->rest) launch_rest_z(c->stream, L, c->unitsW, c->run_z);
         // Ascending l keeps the Z update Jacobi although Z_l is overwritten in place: layer l reads Z_{l+1}^k
         // (not yet touched) and T_l, T_{l+1}, which were formed from Z^k before any Z changed.
         for (int l = 1; l <= L - 1; ++l) {
@@ -944,6 +975,8 @@ void sweep(cadmm_ctx* c) {
         c->gl_valid = false;                         // G_L belongs to the old Z_L and U now
         last_layer_update(c, true);
     }
+    c->rest = false;
+    c->rest_fresh = c->t1_age >= 0 && tracks_rest(c);
     if (c->dual_form == 1) c->u_pending = true;      // applied by the next base evaluation, on the new iterates
     c->gh_valid = c->base_valid = c->scal_valid = false;
     c->stepped = true;
@@ -1371,6 +1404,7 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
                                   hipMemcpyHostToDevice, s));
     }
     c->t1_age = -1;
+    c->rest_fresh = false;
     for (int l = 2; l <= L; ++l) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
     aggregate_H(c, c->Z[0], 1);                                   // A~ Z_0 never changes
     for (int l = 1; l <= L; ++l) {
@@ -1404,15 +1438,16 @@ int cadmm_run(cadmm_ctx* c, int32_t k) {
         const bool reuse = !c->base_valid && t1_reusable(c);
         const bool gl = c->gl_valid && (c->base_valid || reuse);
         cadmm_ctx::GraphSlot& slot = c->graphs[(c->base_valid ? 1 : 0) | (reuse ? 2 : 0) | (gl ? 4 : 0) | (c->gh_valid ? 8 : 0) |
-                                               (c->u_pending ? 16 : 0)];
+                                               (c->u_pending ? 16 : 0) | (c->rest_fresh ? 32 : 0)];
         if (!slot.tried) {
             // capture this variant once; the capture enqueues nothing, sweep() only advances the host flags
             slot.tried = true;
-            const bool bv = c->base_valid, glv = c->gl_valid, ghv = c->gh_valid, scv = c->scal_valid, st = c->stepped, up = c->u_pending;
+            const bool bv = c->base_valid, glv = c->gl_valid, ghv = c->gh_valid, scv = c->scal_valid, st = c->stepped, up = c->u_pending, rf = c->rest_fresh;
             const int it = c->iter, age = c->t1_age;
             if (hipStreamBeginCapture(c->stream, hipStreamCaptureModeRelaxed) == hipSuccess) {
                 sweep(c);
                 slot.gl_after = c->gl_valid;
+                slot.rest_after = c->rest_fresh;
                 hipGraph_t graph = nullptr;
                 hipError_t e = hipStreamEndCapture(c->stream, &graph);
                 if (e == hipSuccess && graph) {
@@ -1420,6 +1455,7 @@ int cadmm_run(cadmm_ctx* c, int32_t k) {
                     (void)hipGraphDestroy(graph);
                 }
                 c->base_valid = bv; c->gl_valid = glv; c->gh_valid = ghv; c->scal_valid = scv; c->stepped = st; c->u_pending = up;
+                c->rest_fresh = rf;
                 c->iter = it; c->t1_age = age;
             }
             (void)hipGetLastError();
@@ -1429,6 +1465,7 @@ int cadmm_run(cadmm_ctx* c, int32_t k) {
             if (!c->base_valid && !reuse) c->t1_age = 0;
             if (c->t1_age >= 0) c->t1_age++;
             c->gl_valid = slot.gl_after;
+            c->rest_fresh = slot.rest_after;
             c->base_valid = c->gh_valid = c->scal_valid = false;
             c->stepped = true;
             c->u_pending = c->dual_form == 1;
@@ -1497,7 +1534,7 @@ int cadmm_predict(cadmm_ctx* c, int32_t* pred, float* logits, double* accuracy) 
         }
     }
     // the T and G buffers now hold the forward pass, not images of the state
-    c->base_valid = c->gl_valid = c->gh_valid = c->scal_valid = false;
+    c->base_valid = c->gl_valid = c->gh_valid = c->scal_valid = c->rest_fresh = false;
     c->t1_age = -1;
     // classes in the caller's node order, and per workgroup how many labelled nodes have their label
     static_assert(kArgmaxBlocks * sizeof(int32_t) <= kReadoutBytes, "the counts fit the readout page");
@@ -1602,6 +1639,7 @@ int cadmm_set_state(cadmm_ctx* c, const float* const* W, const float* const* Z, 
     HIP_TRY(c, own_stream(c));
     if (c->u_pending) base_eval(c);          // finish the pending dual step before anything is overwritten
     c->t1_age = -1;
+    c->rest_fresh = false;
     if (W)
         for (int l = 1; l <= L; ++l)
             if (W[l - 1])
@@ -1711,6 +1749,7 @@ int cadmm_tune(cadmm_ctx* c, const char* key, int32_t value) {
         else if (k_floor) c->use_floor_first = value;
         else if (k_refresh) { c->t1_refresh = value; c->t1_age = -1; }
         else set_gemm_split(value);                  // process-wide
+        c->rest_fresh = false;
         drop_graphs(c);
         return CADMM_OK;
     }

@@ -319,9 +319,13 @@ __global__ __launch_bounds__(256) void risk_finish_kernel(const double* __restri
 // ------------------------------------------------------------------------------------------ W search
 // Adds the block sums of ||gradW||^2 and ||W||^2 (left by the reduction of the W-gradient product) in order and starts
 // the search.
+template <bool GATED>
 __global__ __launch_bounds__(256) void w_begin_kernel(const double* __restrict__ partials, int nblocks, Unit* unit,
-                                                      SearchParams sp) {
+                                                      SearchParams sp, const int32_t* __restrict__ gate) {
     __shared__ double sm[4];
+    if constexpr (GATED) {
+        if (*gate == 0) return;
+    }
     double g = 0.0, b = 0.0;
     for (int i = threadIdx.x; i < nblocks; i += 256) { g += partials[2 * i]; b += partials[2 * i + 1]; }
     g = block_sum(g, sm);
@@ -330,6 +334,20 @@ __global__ __launch_bounds__(256) void w_begin_kernel(const double* __restrict__
         begin_search(unit, sp);
         floor_test(unit, g, b);
     }
+}
+
+// See launch_rest_w, launch_rest_z; thread l - 1 takes layer l (at most 64 of them).
+__global__ __launch_bounds__(64) void rest_w_kernel(int L, const Unit* __restrict__ unitsW, const int32_t* __restrict__ moved,
+                                                    int32_t* __restrict__ run_w, int32_t* __restrict__ run_z) {
+    const int l = (int)threadIdx.x + 1;
+    if (l > L) return;
+    const bool here = l == L || moved[l] != 0, before = l > 1 && moved[l - 1] != 0, after = l + 1 >= L || moved[l + 1] != 0;
+    run_w[l] = here || before || !unitsW[l - 1].skip;
+    run_z[l] = here || before || after;
+}
+__global__ __launch_bounds__(64) void rest_z_kernel(int L, const Unit* __restrict__ unitsW, int32_t* __restrict__ run_z) {
+    const int l = (int)threadIdx.x + 1;
+    if (l < L && (!unitsW[l - 1].skip || !unitsW[l].skip)) run_z[l] = 1;
 }
 
 // Last layer: under T -> T - Q/tau the penalty <U, Z - T> + rho/2 ||Z - T||^2 changes by
@@ -575,6 +593,7 @@ __device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int
 template <int HID, int SM, int PART>
 __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
     __shared__ double sm[kFirstVals * 4];
+    if (PART == kRowsOnly && a.run && *a.run == 0) return;
     if (PART == kRowsOnly && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
     if (PART == kSegmentsOnly && *a.gate == 0) return;
     const int4 ck = a.chunks[blockIdx.x];               // community, kind, first row / segment, one past the last
@@ -632,7 +651,9 @@ __global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
     __shared__ double S[kFirstVals];
     const int unit = blockIdx.x;
     Unit* u = a.units + unit;
+    if (PART == kRowsOnly && a.run && *a.run == 0) return;
     if (PART == kSegmentsOnly && u->done) return;
+    if (PART == kBoth && a.moved && unit == 0 && threadIdx.x == 0) *a.moved = 1;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
     double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
     for (int i = c0 + threadIdx.x; i < c1; i += 256) {
@@ -1355,8 +1376,17 @@ void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t 
     hipLaunchKernelGGL(risk_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
 }
 
-void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp) {
-    hipLaunchKernelGGL(w_begin_kernel, dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp);
+void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp, const int32_t* gate) {
+    if (gate) hipLaunchKernelGGL((w_begin_kernel<true>), dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp, gate);
+    else hipLaunchKernelGGL((w_begin_kernel<false>), dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp, gate);
+}
+
+void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* run_w, int32_t* run_z) {
+    hipLaunchKernelGGL(rest_w_kernel, dim3(1), dim3(64), 0, s, L, unitsW, moved, run_w, run_z);
+}
+
+void launch_rest_z(hipStream_t s, int L, const Unit* unitsW, int32_t* run_z) {
+    hipLaunchKernelGGL(rest_z_kernel, dim3(1), dim3(64), 0, s, L, unitsW, run_z);
 }
 
 void launch_w_trial_finish(hipStream_t s, double* partials, int n_partials, SearchParams sp, Unit* unit,

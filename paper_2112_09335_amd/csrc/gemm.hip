@@ -592,8 +592,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
     const float* __restrict__ A, const float* __restrict__ B, float* __restrict__ out, int64_t n, int K, int C,
     const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
     double* __restrict__ partials, const int32_t* __restrict__ gate) {
+    if ((EPI == 0 || (T == 2 && EPI != 3)) && gate && *gate == 0) return;
     if constexpr (EPI == 0) {
-        if (gate && *gate == 0) return;
         // gated plain product, as in gemm_nn_kernel
         if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
     }
@@ -860,8 +860,8 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
     const float* __restrict__ row_max, int max_tiles, float* __restrict__ out, int64_t n, int K, int C,
     const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
     double* __restrict__ partials, float* __restrict__ out_max, const int32_t* __restrict__ gate) {
+    if (EPI != 3 && gate && *gate == 0) return;
     if constexpr (EPI == 0) {
-        if (gate && *gate == 0) return;
         // gated plain product, as in gemm_nn_kernel
         if (unit != nullptr && (!unit->spec || unit->skip || (unit->done && unit->step == unit->step0))) return;
     }
@@ -1393,7 +1393,8 @@ template <int PRO, int T, int PF>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 && PRO == 0 ? 4 : 1, T == 2 && PRO == 0 ? 4 : 8))) void gemm_tn_split_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                             const float* __restrict__ Zl, float nu,
                                                             float* __restrict__ partial, int64_t n, int K, int C,
-                                                            int64_t rows_per_chunk) {
+                                                            int64_t rows_per_chunk, const int32_t* __restrict__ gate) {
+    if (PRO == 1 && T == 2 && gate && *gate == 0) return;
     constexpr int BT = 64 * T;
     constexpr int LDH = BK + 8;
     constexpr int PLANE = BT * LDH;
@@ -1526,7 +1527,8 @@ __device__ __forceinline__ void wide_step(floatx16 (&acc)[kWideM][kWideN], const
 __global__ __launch_bounds__(256, 2) void gemm_tn_wide_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                               const float* __restrict__ Zl, float nu,
                                                               float* __restrict__ partial, int64_t n, int K, int C,
-                                                              int64_t rows_per_chunk) {
+                                                              int64_t rows_per_chunk, const int32_t* __restrict__ gate) {
+    if (gate && *gate == 0) return;
     __shared__ __align__(16) unsigned short smem[2 * kWideBuf];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1625,10 +1627,13 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_wide_kernel(const float* __res
 // consecutive entries, 256 / X groups of lanes that take the chunks round-robin, four loads in flight each, and are
 // added up in LDS.  X = 16 for large results, 4 for small ones, whose few workgroups would walk many chunks one by one.
 // With W, the workgroup also leaves its share of ||out||^2 and ||W||^2 in norms (two doubles per workgroup).
-template <int X>
+template <int X, bool GATED>
 __global__ __launch_bounds__(256) void gemm_tn_reduce_kernel(const float* __restrict__ partial, float* __restrict__ out,
                                                              int64_t count, int nchunks, const float* __restrict__ W,
-                                                             double* __restrict__ norms) {
+                                                             double* __restrict__ norms, const int32_t* __restrict__ gate) {
+    if constexpr (GATED) {
+        if (*gate == 0) return;
+    }
     constexpr int G = 256 / X;
     __shared__ double sm[G][4 * X];
     const int x = threadIdx.x & (X - 1), y = threadIdx.x / X;
@@ -1877,9 +1882,9 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
         hipLaunchKernelGGL(gemm_nn_pair_kernel<E_>, grid, dim3(64 * kPairWaves), 0, s, A, p.planes, p.col_back, p.row_max, p.max_tiles, out, \
                            n, K, C, epi.Zl, Tl_, epi.nu, epi.Tio, unit_, partials_, out_max_, gate_)
         if (epi.kind == 3) CADMM_PAIR(3, nullptr, nullptr, nullptr, nullptr, nullptr);
-        else if (epi.kind == 2 && epi.leave_g) CADMM_PAIR(4, nullptr, epi.unit, epi.partials, nullptr, nullptr);
-        else if (epi.kind == 2) CADMM_PAIR(2, nullptr, epi.unit, epi.partials, nullptr, nullptr);
-        else if (epi.kind == 1) CADMM_PAIR(1, epi.Tl, nullptr, epi.row_sums, epi.out_max, nullptr);
+        else if (epi.kind == 2 && epi.leave_g) CADMM_PAIR(4, nullptr, epi.unit, epi.partials, nullptr, epi.gate);
+        else if (epi.kind == 2) CADMM_PAIR(2, nullptr, epi.unit, epi.partials, nullptr, epi.gate);
+        else if (epi.kind == 1) CADMM_PAIR(1, epi.Tl, nullptr, epi.row_sums, epi.out_max, epi.gate);
         else CADMM_PAIR(0, nullptr, epi.unit, nullptr, nullptr, epi.gate);
 #undef CADMM_PAIR
         return;
@@ -1892,13 +1897,13 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
             hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, nullptr, nullptr); \
         else if (epi.kind == 2 && epi.leave_g) \
             hipLaunchKernelGGL(K4_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
-                               epi.partials, nullptr); \
+                               epi.partials, epi.gate); \
         else if (epi.kind == 2) \
             hipLaunchKernelGGL(K2_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
-                               epi.partials, nullptr); \
+                               epi.partials, epi.gate); \
         else if (epi.kind == 1) \
             hipLaunchKernelGGL(K1_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, epi.Tl, epi.nu, nullptr, nullptr, \
-                               epi.row_sums, nullptr); \
+                               epi.row_sums, epi.gate); \
         else \
             hipLaunchKernelGGL(K0_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, nullptr, epi.unit, \
                                nullptr, epi.gate)
@@ -1948,19 +1953,19 @@ int64_t gemm_nn_blocks(int64_t n, int C, bool pair) {
 }
 
 int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
-                   float* partial, const float* Zl, float nu, const float* W, double* norms) {
+                   float* partial, const float* Zl, float nu, const float* W, double* norms, const int32_t* gate) {
     if (K <= 0 || C <= 0) return 0;
     TnPlan p = tn_plan(n, K, C, Zl != nullptr);
     const dim3 grid((unsigned)((int64_t)p.nchunks * p.tiles)), block(256);
-#define CADMM_TN(KERNEL_) hipLaunchKernelGGL(KERNEL_, grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk)
+#define CADMM_TN(KERNEL_, ...) hipLaunchKernelGGL(KERNEL_, grid, block, 0, s, A, G, Zl, nu, partial, n, K, C, p.rows_per_chunk, ##__VA_ARGS__)
     if (p.bn == 64) {
-        if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 1, 4>));
-        else CADMM_TN((gemm_tn_split_kernel<0, 1, 4>));
+        if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 1, 4>), gate);
+        else CADMM_TN((gemm_tn_split_kernel<0, 1, 4>), gate);
     } else if (p.wide) {
-        CADMM_TN(gemm_tn_wide_kernel);
+        CADMM_TN(gemm_tn_wide_kernel, gate);
     } else if (g_split && p.bn == 128) {
-        if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 2, 1>));
-        else CADMM_TN((gemm_tn_split_kernel<0, 2, 1>));
+        if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 2, 1>), gate);
+        else CADMM_TN((gemm_tn_split_kernel<0, 2, 1>), gate);
     } else if (p.bn == 128) {
         if (Zl) CADMM_TN((gemm_tn_kernel<128, 1, 0>));
         else CADMM_TN((gemm_tn_kernel<128, 0, 0>));
@@ -1975,8 +1980,10 @@ int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, in
     const bool large = count >= 16384;               // a workgroup of 64 entries on every compute unit
     const int64_t tiles = (count + (large ? 63 : 15)) / (large ? 64 : 16);
     const int nb = (int)(tiles < kReduceBlocks ? tiles : kReduceBlocks);
-    if (large) hipLaunchKernelGGL((gemm_tn_reduce_kernel<16>), dim3(nb), block, 0, s, partial, out, count, p.nchunks, W, norms);
-    else hipLaunchKernelGGL((gemm_tn_reduce_kernel<4>), dim3(nb), block, 0, s, partial, out, count, p.nchunks, W, norms);
+#define CADMM_REDUCE(X_, G_) hipLaunchKernelGGL((gemm_tn_reduce_kernel<X_, G_>), dim3(nb), block, 0, s, partial, out, count, p.nchunks, W, norms, gate)
+    if (large) { if (gate) CADMM_REDUCE(16, true); else CADMM_REDUCE(16, false); }
+    else { if (gate) CADMM_REDUCE(4, true); else CADMM_REDUCE(4, false); }
+#undef CADMM_REDUCE
     return nb;
 }
 

@@ -97,7 +97,9 @@ struct GemmEpilogue {
     float nu = 0.f;
     float* Tio = nullptr;
     const Unit* unit = nullptr;
-    const int32_t* gate = nullptr;   // epilogue 0: nothing is formed where *gate is 0, see ZTrialArgs
+    // where *gate is 0 the result is not wanted (ZTrialArgs, launch_rest): epilogue 0 forms nothing there, epilogues 1, 2 and 4
+    // form it all the same in the kernels of small products
+    const int32_t* gate = nullptr;
     bool leave_g = false;
     double* partials = nullptr;
     double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C, pair) column tiles
@@ -137,10 +139,10 @@ size_t gemm_tn_base_floats(int64_t n, int K, int C);            // what decides 
 size_t gemm_tn_reserve(size_t base);                            // ... and the scratch that serves every shape of that base
 // With Zl != nullptr, G holds the pre-activation T of a hidden layer and the right operand is
 // nu (relu(T) - Zl) 1[T > 0], formed on the fly.  With W (K x C), norms gets block sums of ||out||^2 and ||W||^2 (pairs);
-// returns how many (at most kReduceBlocks).
+// returns how many (at most kReduceBlocks).  gate (with Zl): where *gate is 0 the result is not wanted.
 int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, int64_t n, int K, int C,
                    float* partial, const float* Zl = nullptr, float nu = 0.f, const float* W = nullptr,
-                   double* norms = nullptr);
+                   double* norms = nullptr, const int32_t* gate = nullptr);
 // out[C x K] = in[K x C]^T (small)
 void launch_transpose(hipStream_t s, const float* in, float* out, int K, int C);
 
@@ -192,8 +194,17 @@ void launch_G_only(hipStream_t s, const float* T, const float* Z, float* U, floa
 // R(Z_L, Y) summed over labelled rows -> out->risk
 void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t N, int CL, int risk,
                  double* partials, LayerScalars* out);
+// Which layers rest in this iteration.  A W or Z step of a hidden layer that was found below resolution is below resolution
+// again, bit for bit, as long as nothing it depends on has changed, and nothing of it is formed anew.  moved[l], l = 1..L-1:
+// whether any community of layer l took a Z step in the last iteration (ZTrialArgs::moved).
+// launch_rest_w, before the W steps: run_w[l] = 0 where layer l did not step last time and neither Z_l nor Z_{l-1} (and with it T_l
+// and H_l) has moved since.  launch_rest_z, behind them: run_z[l] = 0 where Z_{l-1}, Z_l and Z_{l+1} have not moved and W_l
+// and W_{l+1} have not stepped now.  Both are 1 wherever that reaches the last layer, whose Z always moves.
+void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* run_w, int32_t* run_z);
+void launch_rest_z(hipStream_t s, int L, const Unit* unitsW, int32_t* run_z);
 // unit.g = ||gradW||^2, unit.bnorm = ||W||^2 from block sums (pairs), applies the step floor, starts the search.
-void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp);
+// gate (may be null): where *gate is 0 the unit stays as it is (launch_rest_w).
+void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp, const int32_t* gate);
 // The whole W search of the last layer (its objective is quadratic in T): one pass over memory and the decision.
 void launch_w_last_search(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U, int64_t count,
                           SearchParams sp, Unit* unit, double* partials, int32_t* status);
@@ -232,6 +243,8 @@ struct ZTrialArgs {
     // Floor first: the step floor is tested with the rows' sums alone, before anything that only a step needs is formed
     // (grad W_{l+1}, the segment products), and *gate says whether any community takes one.
     int32_t* gate = nullptr;
+    int32_t* moved = nullptr;            // without a gate: set to 1, as if one did (may be null)
+    const int32_t* run = nullptr;        // with a gate (may be null): where *run is 0, *gate and the searches stay as they are (launch_rest_z)
     Unit* units;           // [M]
     double* partials;      // [n_chunks * kRestCand]
     int32_t* status;

@@ -251,6 +251,50 @@ def test_step_floor_tested_first_gives_the_same_iterates_bit_for_bit(name, more)
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("dims,more,split", [([40, 64, 48, 64, 64, 5], {}, 1), ([40, 64, 48, 64, 64, 5], {"step_policy": 1}, 1),
+                                             ([70, 192, 130, 200, 160, 5], {"dual_form": 1}, 2), ([60, 400, 100, 33, 36, 4], {}, 1)])
+def test_layers_at_rest_are_left_as_they_are_bit_for_bit(dims, more, split):
+    """A layer whose steps were below resolution is not looked at again until something it depends on has changed
+    (launch_rest_w, launch_rest_z): the same iterates, step parameters and trial counts as without, whatever else is
+    called between the iterations and over two exact evaluations of the pre-activations."""
+    from paper_2112_09335_amd import binding
+    w = synth.make_workload("rest", 77, 1301, 4, dims, dims[-1], 4, graph="sbm", features="gaussian", avg_degree=8, frac_intra=0.8)
+    w.hyper.update(more)
+    got = []
+    try:
+        for mode in (0, 2):
+            s = binding.Solver.from_workload(w, 0)
+            s.tune("gemm_split", split)                  # (process-wide)
+            s.init(w.W0)
+            s.tune("use_floor_first", mode)
+            s.tune("t1_refresh", 4)
+            seen = []
+            for k in (1, 1, 1, 1, 2, 3, 1):
+                s.run(k)
+                seen += [*s.get_steps()]
+                if k == 2:
+                    s.predict()
+                if k == 3:
+                    seen += [s.eval()["objective"]]
+                    s.profile(True)                      # (the next iteration is not replayed)
+            s.profile(False)
+            Z = s.get_Z(1)
+            s.set_state(Z=[Z * np.float32(1.25)] + [None] * (w.L - 1))
+            s.run(2)
+            seen += [s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [s.get_U(), *s.get_steps()]
+            s.init(w.W0)                                 # and from the start again
+            s.run(3)
+            seen += [s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [*s.get_steps()]
+            got.append(seen)
+            s.close()
+    finally:
+        probe = binding.Solver(device=-1)
+        probe.tune("gemm_split", 1)
+        probe.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 def test_the_profile_books_only_what_ran():
     """From the forward pass on most layers take no step at first, and what only a step needs returns at once: neither its flops
     nor its bytes are booked, and its records are no records of its kernel's class."""
