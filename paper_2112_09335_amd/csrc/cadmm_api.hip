@@ -105,12 +105,13 @@ struct cadmm_ctx {
     int32_t* gates = nullptr;          // [L]: whether any community of layer l = 1..L-1 takes a Z step (floor_first)
     int32_t* run_w = nullptr;          // [L+1] each: whether layer l's W and Z steps are worth forming (launch_rest_w)
     int32_t* run_z = nullptr;
+    int32_t* forward_bad = nullptr;    // a hidden pre-activation of the forward pass is not finite
     LayerScalars* scalars = nullptr;   // [L+1]
     int32_t* status = nullptr;
     // What the buffers hold at the moment.  base_valid: every H_l and T_l belongs to the current iterate.  gl_valid /
     // gh_valid: so does G_L / do the G_l of the hidden layers that need one.  scal_valid: so do the readout scalars.
     // stepped: an iteration has been run since the state was set from outside (there is a dual residual).
-    // rest_fresh: gates and unitsW tell what the last sweep moved, and since then nothing has been written but what a sweep
+    // rest_fresh: gates and unitsW tell what the last sweep moved (behind the forward pass: nothing), and since then nothing has been written but what a sweep
     // writes; rest: the sweep being enqueued knows that.
     bool base_valid = false, gl_valid = false, gh_valid = false, scal_valid = false, stepped = false, rest_fresh = false, rest = false;
     int iter = 0;
@@ -388,6 +389,7 @@ size_t layout(cadmm_ctx* c, char* base) {
     c->gates = b.take<int32_t>(L);
     c->run_w = b.take<int32_t>(L + 1);
     c->run_z = b.take<int32_t>(L + 1);
+    c->forward_bad = b.take<int32_t>(1);
     c->scalars = b.take<LayerScalars>(L + 1);
     c->status = b.take<int32_t>(4);
     return (b.off + 255) & ~(size_t)255;
@@ -543,6 +545,7 @@ bool t1_reusable(const cadmm_ctx* c) { return c->t1_age >= 0 && c->t1_age < c->t
 GemmEpilogue forward_epilogue(const cadmm_ctx* c, int l, float* relu_out) {
     GemmEpilogue e;
     e.pair = pair_of_H(c, l);
+    e.bad = c->forward_bad;
     if (relu_out) { e.kind = 3; e.Tio = relu_out; }
     return e;
 }
@@ -1398,24 +1401,29 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
     const int64_t N = c->hg.N;
     hipStream_t s = c->stream;
     HIP_TRY(c, own_stream(c));
+    c->rest_fresh = false;
     for (int l = 1; l <= L; ++l) {
         if (!W0[l - 1]) return fail(c, CADMM_EINVAL, "null weight pointer");
         HIP_TRY(c, hipMemcpyAsync(c->W[l], W0[l - 1], (size_t)c->C[l - 1] * c->C[l] * sizeof(float),
                                   hipMemcpyHostToDevice, s));
     }
     c->t1_age = -1;
-    c->rest_fresh = false;
     for (int l = 2; l <= L; ++l) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
+    HIP_TRY(c, hipMemsetAsync(c->forward_bad, 0, sizeof(int32_t), s));
+    bool noted = tracks_rest(c);                                  // whether every hidden product tells of numbers that are not finite
     aggregate_H(c, c->Z[0], 1);                                   // A~ Z_0 never changes
     for (int l = 1; l <= L; ++l) {
         compute_T(c, l, false, l < L ? c->Z[l] : nullptr);
         if (l == L) launch_relu(s, c->T[l], c->Z[l], N * c->C[l], 0);
+        else noted = noted && !c->agg_first[l] && gemm_nn_notes_bad(c->C[l]);
     }
     HIP_TRY(c, hipMemsetAsync(c->U, 0, (size_t)N * c->C[L] * sizeof(float), s));
     HIP_TRY(c, hipMemsetAsync(c->status, 0, 4 * sizeof(int32_t), s));
     launch_fill_units(s, c->unitsW, L, (double)c->tau0);
     launch_fill_units(s, c->unitsZ, (L - 1) * c->hg.M, (double)c->theta0);
     launch_fill_units(s, c->unitsF, c->hg.M, (double)c->rho);
+    if (noted) launch_rest_start(s, L, c->hg.M, c->unitsW, c->unitsZ, c->gates, c->forward_bad);
+    c->rest_fresh = noted;
     HIP_TRY(c, hipStreamSynchronize(s));                           // W0 host buffers may be freed by the caller
     c->iter = 0;
     c->base_valid = true;                                          // the forward pass left every H_l and T_l

@@ -345,6 +345,15 @@ __global__ __launch_bounds__(64) void rest_w_kernel(int L, const Unit* __restric
     run_w[l] = here || before || !unitsW[l - 1].skip;
     run_z[l] = here || before || after;
 }
+__global__ __launch_bounds__(256) void rest_start_kernel(int L, int M, Unit* __restrict__ unitsW, Unit* __restrict__ unitsZ,
+                                                         int32_t* __restrict__ moved, const int32_t* __restrict__ bad) {
+    const int rest = *bad == 0;
+    for (int i = threadIdx.x; i < L - 1; i += 256) {
+        moved[i + 1] = !rest;
+        unitsW[i].done = unitsW[i].skip = rest;
+    }
+    for (int i = threadIdx.x; i < (L - 1) * M; i += 256) unitsZ[i].done = unitsZ[i].skip = rest;
+}
 __global__ __launch_bounds__(64) void rest_z_kernel(int L, const Unit* __restrict__ unitsW, int32_t* __restrict__ run_z) {
     const int l = (int)threadIdx.x + 1;
     if (l < L && (!unitsW[l - 1].skip || !unitsW[l].skip)) run_z[l] = 1;
@@ -1379,6 +1388,10 @@ void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t 
 void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit* unit, SearchParams sp, const int32_t* gate) {
     if (gate) hipLaunchKernelGGL((w_begin_kernel<true>), dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp, gate);
     else hipLaunchKernelGGL((w_begin_kernel<false>), dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp, gate);
+}
+
+void launch_rest_start(hipStream_t s, int L, int M, Unit* unitsW, Unit* unitsZ, int32_t* moved, const int32_t* bad) {
+    hipLaunchKernelGGL(rest_start_kernel, dim3(1), dim3(256), 0, s, L, M, unitsW, unitsZ, moved, bad);
 }
 
 void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* run_w, int32_t* run_z) {

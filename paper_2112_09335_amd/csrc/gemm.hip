@@ -154,6 +154,8 @@ __device__ __forceinline__ void epilogue_quad(float (&v)[4], float4 z4, float4 t
         }
         st4u(a.out + o, v, nv);
     } else if constexpr (EPI == 3) {
+        // (a finite number times zero is zero, any other is no number; entries past the row's end repeat finite ones or not)
+        dsum += (double)((v[0] * 0.f + v[1] * 0.f) + (v[2] * 0.f + v[3] * 0.f));
         if (a.out) st4u(a.out + o, v, nv);
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = fmaxf(v[e], 0.f);
@@ -250,6 +252,11 @@ __device__ __forceinline__ void tile_epilogue_mode(floatx16 (&acc)[T][T], float*
     }
 }
 
+// EPI 3: *bad = 1 if a result was not finite; s: what epilogue_quad has added up (bad: null if nobody asks).
+__device__ __forceinline__ void note_bad(double s, int32_t* bad) {
+    if (bad && __any(!(s == 0.0)) && (threadIdx.x & 63) == 0) atomicOr(bad, 1);
+}
+
 template <int EPI, int T>
 __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, int64_t m0, int c0, int64_t n, int C,
                                               float* __restrict__ out, const float* __restrict__ Zl,
@@ -267,6 +274,8 @@ __device__ __forceinline__ void tile_epilogue(floatx16 (&acc)[T][T], float* Cs, 
     const EpilogueArgs args{out, Zl, (EPI == 2 || EPI == 4) ? Tio : Tl, nu, Tio, inv0, take, hold};
     if (C % 4 == 0) tile_epilogue_mode<EPI, T, kFull>(acc, Cs, m0, c0, n, C, args, dsum, row_sums);
     else tile_epilogue_mode<EPI, T, kTail>(acc, Cs, m0, c0, n, C, args, dsum, row_sums);   // (C > 32)
+    // (nor has epilogue 3: it carries the flag)
+    if constexpr (EPI == 3) note_bad(dsum, reinterpret_cast<int32_t*>(partials));
     if constexpr (EPI == 2 || EPI == 4) {
         __shared__ double red[4];
 #pragma unroll
@@ -1046,6 +1055,7 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
     float* const s_rm = EPI == 1 && out_max ? s_maxima + wave * kPairRows : nullptr;
     if (C % 4 == 0) pair_epilogue<EPI, kFull>(acc, Cs, s_back, cb, m0, c0, n, C, args, dsum, s_rs, s_rm);
     else pair_epilogue<EPI, kTail>(acc, Cs, s_back, cb, m0, c0, n, C, args, dsum, s_rs, s_rm);
+    if constexpr (EPI == 3) note_bad(dsum, reinterpret_cast<int32_t*>(partials));
     if constexpr (EPI == 1) {
         if (row_sums || out_max) {
             __syncthreads();
@@ -1881,7 +1891,8 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
 #define CADMM_PAIR(E_, Tl_, unit_, partials_, out_max_, gate_) \
         hipLaunchKernelGGL(gemm_nn_pair_kernel<E_>, grid, dim3(64 * kPairWaves), 0, s, A, p.planes, p.col_back, p.row_max, p.max_tiles, out, \
                            n, K, C, epi.Zl, Tl_, epi.nu, epi.Tio, unit_, partials_, out_max_, gate_)
-        if (epi.kind == 3) CADMM_PAIR(3, nullptr, nullptr, nullptr, nullptr, nullptr);
+        double* const bad = reinterpret_cast<double*>(epi.bad);
+        if (epi.kind == 3) CADMM_PAIR(3, nullptr, nullptr, bad, nullptr, nullptr);
         else if (epi.kind == 2 && epi.leave_g) CADMM_PAIR(4, nullptr, epi.unit, epi.partials, nullptr, epi.gate);
         else if (epi.kind == 2) CADMM_PAIR(2, nullptr, epi.unit, epi.partials, nullptr, epi.gate);
         else if (epi.kind == 1) CADMM_PAIR(1, epi.Tl, nullptr, epi.row_sums, epi.out_max, epi.gate);
@@ -1894,7 +1905,8 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
         const dim3 grid((unsigned)gemm_nn_blocks(n, C, false));
 #define CADMM_NN(K4_, K3_, K2_, K1_, K0_) \
         if (epi.kind == 3) \
-            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, nullptr, nullptr); \
+            hipLaunchKernelGGL(K3_, grid, block, 0, s, A, B, out, n, K, C, nullptr, nullptr, 0.f, epi.Tio, nullptr, \
+                               reinterpret_cast<double*>(epi.bad), nullptr); \
         else if (epi.kind == 2 && epi.leave_g) \
             hipLaunchKernelGGL(K4_, grid, block, 0, s, A, B, out, n, K, C, epi.Zl, nullptr, epi.nu, epi.Tio, epi.unit, \
                                epi.partials, epi.gate); \
@@ -1945,6 +1957,8 @@ int gemm_nn_most_tiles(int64_t n, int C) {
     const int b = 64 * nn_tile(n, C, 1);
     return (C + b - 1) / b;
 }
+
+bool gemm_nn_notes_bad(int C) { return C > 32; }
 
 int64_t gemm_nn_blocks(int64_t n, int C, bool pair) {
     if (pair) return ((n + kPairRows - 1) / kPairRows) * gemm_nn_pair_tiles(C);

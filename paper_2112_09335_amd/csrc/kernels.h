@@ -102,6 +102,7 @@ struct GemmEpilogue {
     const int32_t* gate = nullptr;
     bool leave_g = false;
     double* partials = nullptr;
+    int32_t* bad = nullptr;        // epilogue 3: set to 1 if a result is not finite, where gemm_nn_notes_bad
     double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C, pair) column tiles
     float* out_max = nullptr;      // epilogue 1 on pairs: RowMax of the result, per tile as row_sums
 };
@@ -110,6 +111,7 @@ bool gemm_nn_pair_form(int K, int C);
 bool gemm_nn_pair(int64_t n, int K, int C);
 int gemm_nn_pair_tiles(int C);
 size_t gemm_nn_pair_planes(int K, int C);
+bool gemm_nn_notes_bad(int C);
 int gemm_nn_tiles(int64_t n, int C, bool pair);        // column tiles of the launch (C > 32); pair: with PairOperands, gemm_nn_pair
 int gemm_nn_most_tiles(int64_t n, int C);      // most of them, whatever set_gemm_split says
 void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, int64_t n, int K, int C,
@@ -200,6 +202,10 @@ void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t 
 // launch_rest_w, before the W steps: run_w[l] = 0 where layer l did not step last time and neither Z_l nor Z_{l-1} (and with it T_l
 // and H_l) has moved since.  launch_rest_z, behind them: run_z[l] = 0 where Z_{l-1}, Z_l and Z_{l+1} have not moved and W_l
 // and W_{l+1} have not stepped now.  Both are 1 wherever that reaches the last layer, whose Z always moves.
+// launch_rest_start, behind a forward pass: Z_l = relu(T_l) to the bit, so that the gradients of the hidden layers are exactly zero
+// and none of them would step; moved and the units are left as an iteration that finds that out leaves them.  Unless *bad:
+// the pre-activations of a hidden layer are not all finite (times zero they would be no numbers).
+void launch_rest_start(hipStream_t s, int L, int M, Unit* unitsW, Unit* unitsZ, int32_t* moved, const int32_t* bad);
 void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* run_w, int32_t* run_z);
 void launch_rest_z(hipStream_t s, int L, const Unit* unitsW, int32_t* run_z);
 // unit.g = ||gradW||^2, unit.bnorm = ||W||^2 from block sums (pairs), applies the step floor, starts the search.

@@ -295,6 +295,32 @@ def test_layers_at_rest_are_left_as_they_are_bit_for_bit(dims, more, split):
         assert np.array_equal(a, b)
 
 
+@pytest.mark.parametrize("entry", [np.inf, np.nan, 3e38])
+@pytest.mark.parametrize("split", [1, 2])
+def test_layers_do_not_rest_on_numbers_that_are_not_finite(entry, split):
+    """The gradients behind a forward pass are zero only where its pre-activations are finite (3e38 overflows in them)."""
+    from paper_2112_09335_amd import binding
+    w = synth.make_workload("rest-inf", 78, 700, 3, [70, 160, 140, 150, 5], 5, 4, graph="sbm", features="gaussian", avg_degree=8, frac_intra=0.8)
+    w.X = w.X.copy()
+    w.X[11, 3:9] = entry
+    got = []
+    probe = binding.Solver(device=-1)
+    try:
+        probe.tune("gemm_split", split)                  # (process-wide)
+        for mode in (0, 2):
+            s = binding.Solver.from_workload(w, 0)
+            s.tune("use_floor_first", mode)
+            s.run(3)
+            got.append([s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [*s.get_steps(), s.eval()["status"]])
+            s.close()
+    finally:
+        probe.tune("gemm_split", 1)
+        probe.close()
+    assert got[0][-1] != 0                               # (the first layer's search meets them)
+    for a, b in zip(*got):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
 def test_the_profile_books_only_what_ran():
     """From the forward pass on most layers take no step at first, and what only a step needs returns at once: neither its flops
     nor its bytes are booked, and its records are no records of its kernel's class."""
