@@ -1735,11 +1735,11 @@ int cadmm_get_profile(cadmm_ctx* c, double* ms, int64_t* records, double* bytes,
 
 const char* cadmm_profile_class_name(int32_t cls) {
     if (cls < 0 || cls >= CADMM_PROFILE_CLASSES) return "";
-    if (get_gemm_split()) {                      // the wide products run as the bf16-split kernels: name those
-        if (cls == P_GEMM_NN_128) return "gemm_nn_split_kernel<0|3>";
-        if (cls == P_GEMM_NN_128_GRADZ) return "gemm_nn_split_kernel<1>";
-        if (cls == P_GEMM_NN_128_TRIAL) return "gemm_nn_split_kernel<2|4>+finish";
-        if (cls == P_GEMM_TN) return "gemm_tn_split|wide_kernel+reduce";
+    if (get_gemm_split()) {                      // the wide products run as the 16-bit split kernels: name those
+        if (cls == P_GEMM_NN_128) return "gemm_nn_pair|split_kernel<0|3>";
+        if (cls == P_GEMM_NN_128_GRADZ) return "gemm_nn_pair|split_kernel<1>";
+        if (cls == P_GEMM_NN_128_TRIAL) return "gemm_nn_pair|split_kernel<2|4>+finish";
+        if (cls == P_GEMM_TN) return "gemm_tn_pair|split_kernel+reduce";
     }
     return kProfNames[cls];
 }

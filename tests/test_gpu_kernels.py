@@ -282,6 +282,34 @@ def test_an_infinity_in_the_last_row_stays_an_infinity_in_narrow_products(ctx, n
     assert torch.equal(s.op_wgrad_noalloc(A, G), want)
 
 
+# 129 columns of A are the fewest, with and without a last column tile that is full; chunks that end inside a step, and a last one of
+# fewer than sixteen rows (50003 = 196 * 255 + 23 in chunks of 208 rows and so on)
+@pytest.mark.parametrize("n,K,C", [(50003, 129, 33), (49161, 256, 128), (60001, 500, 129), (65537, 129, 300)])
+@pytest.mark.parametrize("kind", ["even", "growing", "late", "columns"])
+def test_wgrad_on_pairs_follows_its_columns_scales(ctx, n, K, C, kind):
+    """The W-gradient product splits a column scaled by its first rows: columns that grow by 2^80 from row to row, that start with
+    thousands of zeros, or that are 1e-20 to 1e20 of each other must come out as from 32-bit products."""
+    import torch
+    s, g, _ = ctx
+    say("wgrad on pairs", n, K, C, kind)
+    gen = torch.Generator(device="cuda").manual_seed(n + K)
+    A = torch.randn((n, K), generator=gen, device="cuda")
+    G = torch.randn((n, C), generator=gen, device="cuda") * 1e-3
+    if kind == "growing":
+        A *= torch.exp2(torch.arange(n, device="cuda") * (40.0 / n))[:, None]
+        G *= torch.exp2(torch.arange(n, device="cuda") * (80.0 / n) - 60.0)[:, None]
+    elif kind == "late":
+        A[: n // 3, ::2] = 0
+        G[: n // 2, 1::3] = 0
+    elif kind == "columns":
+        A *= 10.0 ** torch.randint(-20, 1, (1, K), generator=gen, device="cuda")
+        G *= 10.0 ** torch.randint(0, 20, (1, C), generator=gen, device="cuda")
+    got = s.op_wgrad_noalloc(A, G).double()
+    ref, mag = A.double().t() @ G.double(), A.double().abs().t() @ G.double().abs()
+    # (fp32 sums over chunks of at most a few hundred rows; the tolerance of the other products)
+    assert ((got - ref).abs() / mag).max().item() < 2e-6
+
+
 def base_chunk_rows(n, K, C):
     """Rows per chunk of the W-gradient product at its base: about 1024 workgroups of 128-row tiles, at least 256 rows."""
     tiles = -(-K // 128) * -(-C // (128 if C > 32 else 32))
