@@ -25,15 +25,18 @@ if ROOT not in sys.path:
 # published MI355X peaks
 HBM_PEAK_GBS = 8000.0
 MFMA_FP32_PEAK_TFLOPS = 157.3
-MFMA_BF16_PEAK_TFLOPS = 2500.0
-SPLIT_PRODUCTS = 6      # bf16 MFMA products issued per fp32 product in the split kernels
+MFMA_BF16_PEAK_TFLOPS = 2500.0      # (fp16 the same)
+# fp16 MFMA products issued per fp32 product by the pair kernels; the bf16-split ones of fewer rows or narrower operands, which
+# share their classes, issue six and are counted as three
+PAIR_PRODUCTS = 3
 
 # A kernel class is priced against the MFMA roofline if its arithmetic intensity (algorithmic flops per
 # algorithmic byte over the timed region) is above the machine balance, else against HBM bandwidth.
 MACHINE_BALANCE = MFMA_FP32_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBS * 1e9)      # flop per byte
 
-DTYPE = ("f32 state and accumulation; products wider than 32 columns issued as 6 bf16 MFMA terms of exactly split fp32 "
-         "operands (fp32 MFMA with gemm_split=0), narrower ones as fp32 MFMA; search decisions and reductions in f64")
+DTYPE = ("f32 state and accumulation; products wider than 32 columns issued as 3 fp16 MFMA terms of scaled fp32 operands split in "
+         "two, or as 6 bf16 terms of operands split in three (fp32 MFMA with gemm_split=0), narrower ones as fp32 MFMA; search "
+         "decisions and reductions in f64")
 
 # Bytes per launch group that crossed the L2 -> fabric boundary (FETCH_SIZE + WRITE_SIZE of rocprofv3 --pmc, each scaled
 # by what a plain copy of known size reads) are not measured here: traffic_table.py writes them from the counter runs
@@ -75,13 +78,13 @@ def roofline_entry(name, p):
     if sec <= 0 or p["records"] == 0:
         return None
     per_launch_ms = p["ms"] / p["records"]
-    if name.startswith(("gemm_nn_split", "gemm_tn_split")) and p["bytes"] > 0 and p["flops"] / p["bytes"] > MACHINE_BALANCE:
-        # fp32-exact product issued as six bf16 MFMA products: priced in issued bf16 flops against the bf16 peak
-        ach = SPLIT_PRODUCTS * p["flops"] / sec / 1e12
+    if name.startswith(("gemm_nn_pair", "gemm_tn_pair")) and p["bytes"] > 0 and p["flops"] / p["bytes"] > MACHINE_BALANCE:
+        # priced in issued 16-bit flops against their peak
+        ach = PAIR_PRODUCTS * p["flops"] / sec / 1e12
         return dict(kernel=name, bound="mfma", achieved=ach, peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=ach / MFMA_BF16_PEAK_TFLOPS, traffic=None, avg_launch_ms=per_launch_ms,
                     launches=p["records"], share_of_step=None, fp32_product_TFLOPs=p["flops"] / sec / 1e12,
-                    issued="bf16 x6")
+                    issued="fp16 x3")
     if name.startswith("gemm") and p["bytes"] > 0 and p["flops"] / p["bytes"] > MACHINE_BALANCE:
         ach = p["flops"] / sec / 1e12
         return dict(kernel=name, bound="mfma", achieved=ach, peak=MFMA_FP32_PEAK_TFLOPS, unit="TFLOP/s",
@@ -144,7 +147,7 @@ def mfma_leg(steps, warmup):
                                           "share_of_step") if k in e}
                        | ({"fp32_product_TFLOPs": e["fp32_product_TFLOPs"]} if "fp32_product_TFLOPs" in e else {})
                        for e in class_entries(prof) if e["bound"] == "mfma"]
-            out["paths"]["bf16_split" if split else "fp32"] = dict(gemm_split=split, iterations_per_s=steps / dt,
+            out["paths"]["split" if split else "fp32"] = dict(gemm_split=split, iterations_per_s=steps / dt,
                                                                   ms_per_step=1e3 * dt / steps,
                                                                   warmup=warmup,
                                                                   layers_with_a_W_step=moving[0],

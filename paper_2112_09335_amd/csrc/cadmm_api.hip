@@ -635,8 +635,9 @@ void base_eval(cadmm_ctx* c) {
 void eval_scalars(cadmm_ctx* c) {
     const int L = c->L;
     const int64_t N = c->hg.N;
-    form_T(c);
     if (c->scal_valid) return;
+    // carried pre-activations are at hand; what the next sweep needs beside them (H_l) is its own business
+    if (!t1_reusable(c)) form_T(c);
     for (int l = 1; l <= L; ++l) {
         const double cnt = (double)N * c->C[l];
         const bool fly = gradient_on_the_fly(c, l);
@@ -676,16 +677,16 @@ void carry_T(cadmm_ctx* c, int l) {
           [&] { launch_t_carry(c->stream, c->T[l], carry_args(c, l), c->hg.N, c->C[l]); }, unless_gated(c, l - 1));
 }
 
-// The searches of later candidates: four (what a search that has moved usually needs), then sixteen, then the rest up to
+// The searches of later candidates: four (what a search that has moved usually needs), then `second`, then the rest up to
 // max_backtrack + 1 in all; where a pass over the data is cheap against a launch, all of them at once.  At once against in
 // stages, ten iterations from the initial weights: 1.80 against 1.91 ms at 1.3e5 entries (2000 x 64), 2.30 against 2.27 at
 // 5.1e5 (8000 x 64), 3.42 against 3.13 at 2.0e6 (32000 x 64).  The first iterations, which move far, lose from 2.6e5 on, later
 // ones gain up to 1.0e6.
 template <class F>
-void later_candidates(const cadmm_ctx* c, double elements, int tried, F pass) {
+void later_candidates(const cadmm_ctx* c, double elements, int tried, int second, F pass) {
     int left = c->max_bt + 1 - tried;
     if (left > 0 && elements <= 524288.0) { pass(left); return; }
-    for (int n : {4, kMaxCand, kRestCand}) {
+    for (int n : {4, second, kRestCand}) {
         if (left <= 0) return;
         pass(n);
         left -= n;
@@ -765,7 +766,7 @@ void w_update(cadmm_ctx* c, int l) {
             return;
         }
         if (!spec) launch_w_trial(s, c->T[l], Q, c->Z[l], count, 1, sp, unit, c->partials, c->status);
-        later_candidates(c, (double)count, 1, [&](int n) {
+        later_candidates(c, (double)count, 1, kFreshCand, [&](int n) {
             launch_w_trial(s, c->T[l], Q, c->Z[l], count, n, sp, unit, c->partials, c->status, spec ? 1 : 0);
         });
     }, Unless{skip, 1, P_OTHER, 0.0});
@@ -875,7 +876,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
                                    (next_last ? 2.0 : 3.0) * (double)c->hg.n_seg * Cn) + 4.0 * (double)c->hg.n_seg;
     timed(c, P_Z_TRIAL, zt_bytes, 0.0, [&] {
         launch_z_first(s, a);
-        if (!next_last) later_candidates(c, (double)c->hg.n_seg * Cn, 1, [&](int n) { launch_z_more(s, a, n); });
+        if (!next_last) later_candidates(c, (double)c->hg.n_seg * Cn, 1, kMaxCand, [&](int n) { launch_z_more(s, a, n); });
     }, gated);
     timed(c, P_Z_STEP, 4.0 * (3.0 * (double)N * Cl + (double)N + (lowrank ? (double)N * Cn : 0.0)), 0.0, [&] {
         if (lowrank) launch_z_step_lowrank(s, c->Z[l], c->T[l], c->tmpA, Wt, c->nu, c->d_row_comm, N, Cl, Cn, units, M, a.gate);

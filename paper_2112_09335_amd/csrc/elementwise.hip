@@ -165,6 +165,7 @@ __device__ __forceinline__ double first_candidate(const Unit* u, SearchParams sp
 // Start of a search, before its first decision.
 __device__ __forceinline__ void begin_search(Unit* u, SearchParams sp) {
     u->spec = (u->ntrials == 1) ? 1 : 0;     // last search: first candidate accepted
+    u->fresh = (u->ntrials == 0) ? 1 : 0;
     u->ntrials = 0;
     u->keep = u->step;
     u->step = first_candidate(u, sp);
@@ -407,9 +408,9 @@ template <int NC>
 __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ T0, const float* __restrict__ Q,
                                                       const float* __restrict__ Z, int64_t count, SearchParams sp,
                                                       int rounds, const Unit* unit, double* __restrict__ partials,
-                                                      int speculated) {
+                                                      int speculated, int leave_fresh) {
     __shared__ double sm[NC * 4];
-    if (unit->done) return;
+    if (unit->done || (leave_fresh && unit->fresh)) return;
     const double spec_inv = (speculated && unit->spec) ? 1.0 / unit->step0 : 0.0;      // T0 holds T0 - Q/step0: undo
     double step = unit->step;
     for (int j = 0; j < (int)blockIdx.y * NC; ++j) step *= (double)sp.eta;
@@ -427,11 +428,11 @@ __global__ __launch_bounds__(256) void w_trial_kernel(const float* __restrict__ 
             for (int v = 0; v < 4; ++v) {
                 const double q = (double)qv[v], z = (double)zv[v];
                 const double t0 = (double)t0v[v] + q * spec_inv;
-                const double e0 = fmax(t0, 0.0) - z;
+                const double r0 = fmax(t0, 0.0), e2 = 2.0 * (r0 - z);
 #pragma unroll
-                for (int j = 0; j < NC; ++j) {
-                    const double e1 = fmax(t0 - q * inv[j], 0.0) - z;
-                    D[j] += (e1 - e0) * (e1 + e0);
+                for (int j = 0; j < NC; ++j) {           // (e1 - e0) (e1 + e0) with e = relu(t) - z
+                    const double d = fmax(t0 - q * inv[j], 0.0) - r0;
+                    D[j] += d * (d + e2);
                 }
             }
         });
@@ -464,10 +465,10 @@ __device__ __forceinline__ void sum_candidates(const double* __restrict__ partia
 
 // Sums the ncand block results (stride per block) of a pass and takes the decision.
 __global__ __launch_bounds__(256) void w_trial_finish_kernel(const double* __restrict__ partials, int nblocks, int ncand,
-                                                             SearchParams sp, Unit* unit, int32_t* status) {
+                                                             SearchParams sp, Unit* unit, int32_t* status, int leave_fresh) {
     __shared__ double sm[4];
     __shared__ double D[kRestCand];
-    if (unit->done) return;
+    if (unit->done || (leave_fresh && unit->fresh)) return;
     if (ncand == 1) {                                  // many blocks (a product's workgroups), one candidate
         double a = 0.0, b = 0.0, c = 0.0, d = 0.0;     // four independent loads in flight per thread
         int i = threadIdx.x;
@@ -568,15 +569,19 @@ struct RowWalk {
 //   segments (kind 1), next layer the last one: <U, Z_L - T> + rho/2 ||Z_L - T||^2 under T -> T - P/theta changes by
 //     -S1/theta + rho/2 S2/theta^2 with S1 = sum p G_L (G_L = -(u + rho (z - t)) is at hand) and S2 = sum p^2.
 //   segments, next layer hidden (HID): its ReLU makes the term piecewise quadratic; the first candidate is evaluated.
+//     Where the previous search did not accept its first candidate this one will hardly either (a layer's first search takes
+//     three or four): the first four are evaluated then, for a tenth more than for one and in place of a second pass
+//     (500000 rows, 512 columns: 1.32 ms for one, 1.49 for four).
 // So with a last next layer this one pass over memory is the whole search, and with a hidden one the later passes read
-// the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidate's change, S2.  Bound by HBM traffic.
+// the segments alone.  Per chunk: A, B, ||Z||^2, S1 or the candidates' changes, S2.  Bound by HBM traffic.
 // SM: kind of the width Cn.
 // With a gate the search comes in two parts, the rows (launch_z_floor) and, where any community takes a step, the segments:
 // for the rows alone two more launches, for the segments nothing that nobody needs.  PART says which chunks a launch takes.
 // PART and GATED (here and below) are template parameters since a branch at a kernel's start, taken or not, keeps the other
 // arguments from being loaded beside what it looks at: with them and gemm_nn_narrow_kernel's the iterations of a small run that has no
 // gate take 191.0 us, without them 192.1 (20000 nodes, 500-128-3).
-constexpr int kFirstVals = 5;
+constexpr int kFirstCand = 4;
+constexpr int kFirstVals = 3 + kFirstCand;
 enum FirstPart { kBoth = 0, kRowsOnly = 1, kSegmentsOnly = 2 };
 template <int RM>
 __device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int end, double (&s)[kFirstVals]) {
@@ -607,7 +612,7 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
     if (PART == kSegmentsOnly && *a.gate == 0) return;
     const int4 ck = a.chunks[blockIdx.x];               // community, kind, first row / segment, one past the last
     if ((PART == kRowsOnly && ck.y != 0) || (PART == kSegmentsOnly && ck.y == 0)) return;
-    double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    double s[kFirstVals] = {};
     if (ck.y == 0) {
         if (a.row_sums) {                               // the kernel that formed the gradient left the rows' sums
             const int64_t n = 3 * (int64_t)(ck.w - ck.z);
@@ -622,31 +627,52 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
         const RowWalk w(a.Cn);
         const Unit* const u = a.units + ck.x;           // (launch_z_floor has started the search, or the finishing kernel will)
         if (PART == kSegmentsOnly && u->done) return;
-        const double inv = HID ? 1.0 / (PART == kSegmentsOnly ? u->step0 : first_candidate(u, a.sp)) : 0.0;
-        for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
-            const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
-            for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
-                float pv[4], tv[4], zv[4];
-                ldr<SM>(pv, a.P + pbase, 4 * cv, a.Cn);
-                if constexpr (HID) {
-                    ldr<SM>(tv, a.Tn + base, 4 * cv, a.Cn);
-                    ldr<SM>(zv, a.Zn + base, 4 * cv, a.Cn);
-                } else {
-                    ldr<SM>(tv, a.Gn + base, 4 * cv, a.Cn);
-                }
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const double t = (double)tv[v], p = (double)pv[v];
+        // (f: what a quad of a segment's row adds)
+        auto walk = [&](auto f) {
+            for (int q = ck.z + w.r_first; q < ck.w; q += w.r_step) {
+                const int64_t base = (int64_t)a.segc_row[q] * a.Cn, pbase = (int64_t)q * a.Cn;
+                for (int cv = w.c_first; cv < w.wv; cv += 1 << w.shift) {
+                    float pv[4], tv[4], zv[4];
+                    ldr<SM>(pv, a.P + pbase, 4 * cv, a.Cn);
                     if constexpr (HID) {
-                        const double z = (double)zv[v];
-                        const double e0 = fmax(t, 0.0) - z, e1 = fmax(t - p * inv, 0.0) - z;
-                        s[3] += (e1 - e0) * (e1 + e0);
+                        ldr<SM>(tv, a.Tn + base, 4 * cv, a.Cn);
+                        ldr<SM>(zv, a.Zn + base, 4 * cv, a.Cn);
                     } else {
-                        s[3] += p * t;
-                        s[4] += p * p;
+                        ldr<SM>(tv, a.Gn + base, 4 * cv, a.Cn);
                     }
+                    f(pv, tv, zv);
                 }
             }
+        };
+        if constexpr (HID) {
+            // (r0 = relu(t), d its change: (e1 - e0) (e1 + e0) = d (d + 2 e0) with e = relu(t) - z)
+            auto candidates = [&](auto NC) {
+                constexpr int kC = decltype(NC)::value;
+                double inv[kC], step = PART == kSegmentsOnly ? u->step0 : first_candidate(u, a.sp);
+#pragma unroll
+                for (int j = 0; j < kC; ++j) { inv[j] = 1.0 / step; step *= (double)a.sp.eta; }
+                walk([&](const float (&pv)[4], const float (&tv)[4], const float (&zv)[4]) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const double t = (double)tv[v], p = (double)pv[v], r0 = fmax(t, 0.0), e2 = 2.0 * (r0 - (double)zv[v]);
+#pragma unroll
+                        for (int j = 0; j < kC; ++j) {
+                            const double d = fmax(t - p * inv[j], 0.0) - r0;
+                            s[3 + j] += d * (d + e2);
+                        }
+                    }
+                });
+            };
+            if (PART == kSegmentsOnly ? u->spec : u->ntrials == 1) candidates(std::integral_constant<int, 1>{});
+            else candidates(std::integral_constant<int, kFirstCand>{});
+        } else {
+            walk([&](const float (&pv)[4], const float (&tv)[4], const float (&)[4]) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    s[3] += (double)pv[v] * (double)tv[v];
+                    s[4] += (double)pv[v] * (double)pv[v];
+                }
+            });
         }
     }
     block_sums_to<kFirstVals>(s, sm, a.partials + (int64_t)blockIdx.x * kFirstVals);
@@ -664,7 +690,7 @@ __global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
     if (PART == kSegmentsOnly && u->done) return;
     if (PART == kBoth && a.moved && unit == 0 && threadIdx.x == 0) *a.moved = 1;
     const int c0 = a.unit_chunk_ptr[unit], c1 = a.unit_chunk_ptr[unit + 1];
-    double s[kFirstVals] = {0.0, 0.0, 0.0, 0.0, 0.0};
+    double s[kFirstVals] = {};
     for (int i = c0 + threadIdx.x; i < c1; i += 256) {
         if (PART != kBoth && (a.chunks[i].y == 0) != (PART == kRowsOnly)) continue;
 #pragma unroll
@@ -684,8 +710,9 @@ __global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
         if (PART == kRowsOnly) {
             atomicOr(a.gate, 1);
         } else if (HID) {
-            const double d = hnu * S[3];
-            decide(u, &d, 1, a.sp, a.status);
+            double D[kFirstCand];
+            for (int j = 0; j < kFirstCand; ++j) D[j] = hnu * S[3 + j];
+            decide(u, D, u->spec ? 1 : kFirstCand, a.sp, a.status);
         } else {
             u->c1 -= S[3];
             u->c2 += 0.5 * (double)a.sp.rho * S[4];
@@ -723,12 +750,11 @@ __global__ __launch_bounds__(256) void z_more_kernel(ZTrialArgs a, int rounds) {
                     ldr<SM>(zv, a.Zn + base, 4 * cv, a.Cn);
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        const double t = (double)tv[v], z = (double)zv[v], p = (double)pv[v];
-                        const double e0 = fmax(t, 0.0) - z;
+                        const double t = (double)tv[v], p = (double)pv[v], r0 = fmax(t, 0.0), e2 = 2.0 * (r0 - (double)zv[v]);
 #pragma unroll
                         for (int j = 0; j < NC; ++j) {
-                            const double e1 = fmax(t - p * inv[j], 0.0) - z;
-                            D[j] += (e1 - e0) * (e1 + e0);
+                            const double d = fmax(t - p * inv[j], 0.0) - r0;
+                            D[j] += d * (d + e2);
                         }
                     }
                 }
@@ -1330,7 +1356,7 @@ __global__ void fill_units_kernel(Unit* units, int n, double step) {
     if (i >= n) return;
     Unit u;
     u.step = step; u.step0 = step; u.keep = step; u.g = 0.0; u.bnorm = 0.0; u.done = 0; u.skip = 0; u.ntrials = 0;
-    u.spec = 0; u.total = 0; u.pad = 0; u.c1 = 0.0; u.c2 = 0.0;
+    u.spec = 0; u.total = 0; u.fresh = 0; u.c1 = 0.0; u.c2 = 0.0;
     units[i] = u;
 }
 
@@ -1404,7 +1430,7 @@ void launch_rest_z(hipStream_t s, int L, const Unit* unitsW, int32_t* run_z) {
 
 void launch_w_trial_finish(hipStream_t s, double* partials, int n_partials, SearchParams sp, Unit* unit,
                            int32_t* status) {
-    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, n_partials, 1, sp, unit, status);
+    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, n_partials, 1, sp, unit, status, 0);
 }
 
 void launch_w_last_search(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U, int64_t count,
@@ -1417,10 +1443,14 @@ void launch_w_last_search(hipStream_t s, const float* T0, const float* Q, const 
 void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float* Z, int64_t count, int ncand,
                     SearchParams sp, Unit* unit, double* partials, int32_t* status, int speculated) {
     int nb = flat_grid(count);
+    // a fresh search needs more than four candidates: the pass after this one starts it, if the passes then still hold them all
+    const int leave_fresh = ncand == 4 && (sp.max_backtrack > 4 + kFreshCand || (sp.max_backtrack > 4 && sp.max_backtrack <= kFreshCand));
     if (ncand == 1)
-        hipLaunchKernelGGL((w_trial_kernel<1>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
+        hipLaunchKernelGGL((w_trial_kernel<1>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated, 0);
     else if (ncand <= 4)
-        hipLaunchKernelGGL((w_trial_kernel<4>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated);
+        hipLaunchKernelGGL((w_trial_kernel<4>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated, leave_fresh);
+    else if (ncand == kFreshCand)
+        hipLaunchKernelGGL((w_trial_kernel<kFreshCand>), dim3(nb), dim3(256), 0, s, T0, Q, Z, count, sp, 1, unit, partials, speculated, 0);
     else {
         // The rounds of a small matrix share the chip (2000 x 64, four rounds: 31 us in one after the other, 5 so), up to as many
         // workgroups as a large one has in a single round.  Those of a large one follow each other: each round fills the chip by
@@ -1429,10 +1459,10 @@ void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float*
         const int rounds = (ncand + kMaxCand - 1) / kMaxCand;
         const int side_by_side = std::max(1, std::min(rounds, kReduceBlocks / nb));
         hipLaunchKernelGGL((w_trial_kernel<kMaxCand>), dim3(nb, side_by_side), dim3(256), 0, s, T0, Q, Z, count, sp, rounds, unit,
-                           partials, speculated);
+                           partials, speculated, 0);
     }
-    const int nc = ncand == 1 ? 1 : ncand <= 4 ? 4 : (ncand + kMaxCand - 1) / kMaxCand * kMaxCand;
-    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, nc, sp, unit, status);
+    const int nc = ncand == 1 ? 1 : ncand <= 4 ? 4 : ncand == kFreshCand ? kFreshCand : (ncand + kMaxCand - 1) / kMaxCand * kMaxCand;
+    hipLaunchKernelGGL(w_trial_finish_kernel, dim3(1), dim3(256), 0, s, partials, nb, nc, sp, unit, status, leave_fresh);
 }
 
 void launch_w_step(hipStream_t s, float* W, float* Wt, const float* gradW, int K, int C, float* T, float* Q,

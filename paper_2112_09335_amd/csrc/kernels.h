@@ -151,6 +151,10 @@ void launch_transpose(hipStream_t s, const float* in, float* out, int K, int C);
 // ---------------------------------------------------------------- fused elementwise + reductions (elementwise.hip)
 constexpr int kReduceBlocks = 2048;      // grid of the flat reducing kernels
 constexpr int kMaxCand = 16;             // step-size candidates evaluated at once in a later pass
+// Candidates of the second of the later passes: a unit's first search climbs from tau0 through 11 to 21 candidates, that is the
+// first one and these (ten workloads of 8 000 to 2 M nodes); so many in one pass instead of four and sixteen: 256 M entries 1.17 ms
+// for 0.57 and 1.03.
+constexpr int kFreshCand = 20;
 constexpr int kRestCand = 64;            // most candidates a pass evaluates (in rounds of kMaxCand)
 constexpr int kLowRankMax = 16;          // widest next layer for which the Z gradient is kept in low-rank form
 
@@ -166,7 +170,7 @@ struct Unit {
     int32_t ntrials;   // candidates tested this iteration
     int32_t spec;      // the previous search accepted its first candidate: a speculative step with step0 is safe
     int32_t total;     // candidates tested since the counter was cleared (the last-layer solve adds up its steps)
-    int32_t pad;
+    int32_t fresh;     // the previous search tested no candidate (there has been none, or its step was below resolution)
     double c1, c2;     // the part of the objective's change that is quadratic in 1/step: c1 / step + c2 / step^2
 };
 
@@ -214,7 +218,8 @@ void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit*
 // The whole W search of the last layer (its objective is quadratic in T): one pass over memory and the decision.
 void launch_w_last_search(hipStream_t s, const float* T0, const float* Q, const float* Z, const float* U, int64_t count,
                           SearchParams sp, Unit* unit, double* partials, int32_t* status);
-// One pass of the W search of a hidden layer: the next ncand candidates step*eta^j (1, 4, or rounds of kMaxCand) on
+// One pass of the W search of a hidden layer: the next ncand candidates step*eta^j (1, 4, kFreshCand, or rounds of kMaxCand; the
+// pass of four leaves a fresh search to the next one) on
 // phi_l(T0 - Q/step).  speculated != 0: T0 already holds the speculative step T0 - Q/step0; the pass rebuilds
 // T0 = T0 + Q/step0.
 void launch_w_trial(hipStream_t s, const float* T0, const float* Q, const float* Z, int64_t count, int ncand,
@@ -257,8 +262,8 @@ struct ZTrialArgs {
 };
 // Starts the searches of all communities and applies the step floor (with row_sums and gate).
 void launch_z_floor(hipStream_t s, const ZTrialArgs& a);
-// Starts the searches of all communities (unless launch_z_floor has) and judges the first candidate; with a last next
-// layer, all of them.
+// Starts the searches of all communities (unless launch_z_floor has) and judges the first candidate, or the first four where
+// the previous search did not accept its first; with a last next layer, all of them.
 void launch_z_first(hipStream_t s, const ZTrialArgs& a);
 // The next ncand candidates (4, or rounds of kMaxCand) where the next layer is hidden.
 void launch_z_more(hipStream_t s, const ZTrialArgs& a, int ncand);
