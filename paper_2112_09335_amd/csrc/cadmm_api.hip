@@ -26,6 +26,7 @@ static __device__ __align__(256) float scratch[kStaticScratchFloats];
 constexpr int kMaxDevices = 64;
 constexpr size_t kReadoutBytes = 16384;                            // pinned page for small readouts
 constexpr int kProfFlags = 4096;
+constexpr int kStageSlots = 8;                                     // pieces of a large readout in flight at most
 static float* g_scratch_ptr[kMaxDevices] = {};                     // device address of `scratch` on GPU d, once looked up
 static std::mutex g_scratch_mutex;
 
@@ -141,7 +142,7 @@ struct cadmm_ctx {
     // pinned host memory, allocated when first needed and freed with the context: two pieces through which large transfers
     // are pipelined, and a page for readouts of a few values
     char* stage[2] = {nullptr, nullptr};
-    hipEvent_t stage_free[2] = {nullptr, nullptr};
+    hipEvent_t stage_free[kStageSlots] = {};
     char* readout = nullptr;
     int64_t large_readouts = 0;
     // optional per-kernel-class timing with HIP events on the context's stream
@@ -1013,6 +1014,7 @@ hipError_t make_event(cadmm_ctx* c, hipEvent_t* e) {
 constexpr size_t kStageBytes = (size_t)8 << 20;
 constexpr size_t kStageMin = (size_t)4 << 20;
 constexpr size_t kStageGet = (size_t)16 << 20;
+constexpr size_t kStageLong = (size_t)64 << 20;
 constexpr int64_t kStageWork = 8 * 16384;        // HostPool work that asks for eight threads
 
 bool have_stage(cadmm_ctx* c, size_t bytes) {
@@ -1023,11 +1025,12 @@ bool have_stage(cadmm_ctx* c, size_t bytes) {
             (void)hipGetLastError();
             return false;
         }
-        if (!c->stage_free[k] && make_event(c, &c->stage_free[k]) != hipSuccess) {
+    }
+    for (hipEvent_t& e : c->stage_free)
+        if (!e && make_event(c, &e) != hipSuccess) {
             (void)hipGetLastError();
             return false;
         }
-    }
     return true;
 }
 
@@ -1042,18 +1045,24 @@ int copy_out(cadmm_ctx* c, void* dst, const void* src, size_t bytes) {
         HIP_TRY(c, hipStreamSynchronize(c->stream));
         return CADMM_OK;
     }
-    const size_t n = (bytes + kStageBytes - 1) / kStageBytes;
-    auto size_of = [&](size_t k) { return k + 1 < n ? kStageBytes : bytes - k * kStageBytes; };
+    // A readout of a few MB in pieces of 2 MB, so that its first bytes are copied out while the last are on their way, and so
+    // that all of them are on their way while the threads start (predict, 8 MB of logits: 1060 us in one piece and the threads
+    // first).  From kStageLong on a piece's fixed costs count for more.
+    const size_t piece = bytes < kStageLong ? kStageBytes / 4 : kStageBytes, slots = 2 * (kStageBytes / piece);
+    static_assert(2 * 4 <= kStageSlots, "an event per slot");
+    const size_t n = (bytes + piece - 1) / piece;
+    auto size_of = [&](size_t k) { return k + 1 < n ? piece : bytes - k * piece; };
+    auto slot_of = [&](size_t k) { return c->stage[k & 1] + (k % slots / 2) * piece; };
     auto issue = [&](size_t k) {
-        hipError_t e = hipMemcpyAsync(c->stage[k & 1], static_cast<const char*>(src) + k * kStageBytes, size_of(k), hipMemcpyDeviceToHost, c->stream);
-        return e != hipSuccess ? e : hipEventRecord(c->stage_free[k & 1], c->stream);
+        hipError_t e = hipMemcpyAsync(slot_of(k), static_cast<const char*>(src) + k * piece, size_of(k), hipMemcpyDeviceToHost, c->stream);
+        return e != hipSuccess ? e : hipEventRecord(c->stage_free[k % slots], c->stream);
     };
+    for (size_t k = 0; k < n && k < slots; ++k) HIP_TRY(c, issue(k));
     HostPool pool(kStageWork);
-    for (size_t k = 0; k < n && k < 2; ++k) HIP_TRY(c, issue(k));
     for (size_t k = 0; k < n; ++k) {
-        HIP_TRY(c, hipEventSynchronize(c->stage_free[k & 1]));
-        copy_with(pool, static_cast<char*>(dst) + k * kStageBytes, c->stage[k & 1], size_of(k));
-        if (k + 2 < n) HIP_TRY(c, issue(k + 2));
+        HIP_TRY(c, hipEventSynchronize(c->stage_free[k % slots]));
+        copy_with(pool, static_cast<char*>(dst) + k * piece, slot_of(k), size_of(k));
+        if (k + slots < n) HIP_TRY(c, issue(k + slots));
     }
     return CADMM_OK;
 }
@@ -1216,10 +1225,10 @@ void cadmm_destroy(cadmm_ctx* ctx) {
         for (auto& r : ctx->prof_recs) { (void)hipEventDestroy(r.a); (void)hipEventDestroy(r.b); }
         for (auto e : ctx->prof_pool) (void)hipEventDestroy(e);
         drop_graphs(ctx);
-        for (int k = 0; k < 2; ++k) {
+        for (int k = 0; k < 2; ++k)
             if (ctx->stage[k]) (void)hipHostFree(ctx->stage[k]);
-            if (ctx->stage_free[k]) (void)hipEventDestroy(ctx->stage_free[k]);
-        }
+        for (hipEvent_t e : ctx->stage_free)
+            if (e) (void)hipEventDestroy(e);
         if (ctx->readout) (void)hipHostFree(ctx->readout);
         for (int32_t* piece : ctx->prof_flags) (void)hipHostFree(piece);
         if (ctx->ev_own) (void)hipEventDestroy(ctx->ev_own);
@@ -1410,8 +1419,8 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
     }
     c->t1_age = -1;
     for (int l = 2; l <= L; ++l) launch_transpose(s, c->W[l], c->Wt[l], c->C[l - 1], c->C[l]);
-    HIP_TRY(c, hipMemsetAsync(c->forward_bad, 0, sizeof(int32_t), s));
     bool noted = tracks_rest(c);                                  // whether every hidden product tells of numbers that are not finite
+    if (noted) HIP_TRY(c, hipMemsetAsync(c->forward_bad, 0, sizeof(int32_t), s));
     aggregate_H(c, c->Z[0], 1);                                   // A~ Z_0 never changes
     for (int l = 1; l <= L; ++l) {
         compute_T(c, l, false, l < L ? c->Z[l] : nullptr);

@@ -581,10 +581,10 @@ struct RowWalk {
 // arguments from being loaded beside what it looks at: with them and gemm_nn_narrow_kernel's the iterations of a small run that has no
 // gate take 191.0 us, without them 192.1 (20000 nodes, 500-128-3).
 constexpr int kFirstCand = 4;
-constexpr int kFirstVals = 3 + kFirstCand;
+template <int HID> constexpr int kFirstValues = HID ? 3 + kFirstCand : 5;
 enum FirstPart { kBoth = 0, kRowsOnly = 1, kSegmentsOnly = 2 };
-template <int RM>
-__device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int end, double (&s)[kFirstVals]) {
+template <int RM, int V>
+__device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int end, double (&s)[V]) {
     const RowWalk w(a.Cl);
     for (int r = begin + w.r_first; r < end; r += w.r_step) {
         const int64_t base = (int64_t)r * a.Cl;
@@ -606,6 +606,7 @@ __device__ __forceinline__ void z_first_rows(const ZTrialArgs& a, int begin, int
 
 template <int HID, int SM, int PART>
 __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
+    constexpr int kFirstVals = kFirstValues<HID>;
     __shared__ double sm[kFirstVals * 4];
     if (PART == kRowsOnly && a.run && *a.run == 0) return;
     if (PART == kRowsOnly && blockIdx.x == 0 && threadIdx.x == 0) *a.gate = 0;
@@ -682,6 +683,7 @@ __global__ __launch_bounds__(256) void z_first_kernel(ZTrialArgs a) {
 // them if the whole change is quadratic).
 template <int HID, int PART>
 __global__ __launch_bounds__(256) void z_first_finish_kernel(ZTrialArgs a) {
+    constexpr int kFirstVals = kFirstValues<HID>;
     __shared__ double sm[kFirstVals * 4];
     __shared__ double S[kFirstVals];
     const int unit = blockIdx.x;
