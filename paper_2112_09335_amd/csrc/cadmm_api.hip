@@ -1014,7 +1014,7 @@ hipError_t make_event(cadmm_ctx* c, hipEvent_t* e) {
 constexpr size_t kStageBytes = (size_t)8 << 20;
 constexpr size_t kStageMin = (size_t)4 << 20;
 constexpr size_t kStageGet = (size_t)16 << 20;
-constexpr size_t kStageLong = (size_t)64 << 20;
+constexpr size_t kStageLong = (size_t)16 << 20;
 constexpr int64_t kStageWork = 8 * 16384;        // HostPool work that asks for eight threads
 
 bool have_stage(cadmm_ctx* c, size_t bytes) {
@@ -1047,7 +1047,7 @@ int copy_out(cadmm_ctx* c, void* dst, const void* src, size_t bytes) {
     }
     // A readout of a few MB in pieces of 2 MB, so that its first bytes are copied out while the last are on their way, and so
     // that all of them are on their way while the threads start (predict, 8 MB of logits: 1060 us in one piece and the threads
-    // first).  From kStageLong on a piece's fixed costs count for more.
+    // first, 995 so).  From kStageLong on a piece's fixed costs count for more (32 MB: 840 us in pieces of 8 MB, 920 of 2).
     const size_t piece = bytes < kStageLong ? kStageBytes / 4 : kStageBytes, slots = 2 * (kStageBytes / piece);
     static_assert(2 * 4 <= kStageSlots, "an event per slot");
     const size_t n = (bytes + piece - 1) / piece;
