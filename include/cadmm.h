@@ -269,8 +269,9 @@ const char* cadmm_profile_class_name(int32_t cls);
 
 /* Tuning knobs for experiments.  "use_graph" (per context): 1 = cadmm_run replays one iteration as a
  * captured HIP graph when the context's stream is not the default stream (default), 0 = plain launches.
- * "use_lowrank" (per context): 1 = with a next layer of at most 16 units the Z gradient is kept as
- * nu (Z_l - relu(T_l)) + (A~ G_{l+1}) W_{l+1}^T and rebuilt per element by its consumers (default), 0 = stored.
+ * "use_lowrank" (per context): with a next layer of at most 16 units the Z gradient is kept as
+ * nu (Z_l - relu(T_l)) + (A~ G_{l+1}) W_{l+1}^T and rebuilt per element by its consumers: 1 = from 32768 nodes on, from 8192 for up to 64 units
+ * (default), 2 = at any size, 0 = never, it is stored.
  * "use_speculative" (per context): 1 = in a wide hidden layer the product Q = A~ Z_{l-1} grad W also evaluates the
  * first candidate of the tau search and takes the step on the pre-activation speculatively (default), 0 = separate passes.
  * "use_floor_first" (per context): the Z search of a hidden layer tests the step floor before it forms what only a step

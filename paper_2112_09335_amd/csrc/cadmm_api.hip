@@ -83,7 +83,6 @@ struct cadmm_ctx {
     float* Pbuf[2] = {nullptr, nullptr};   // layers alternate: P of layer l stays until layer l+1 is done
     float* gradW = nullptr;
     std::vector<float*> Wt;     // transposes of W_2 .. W_L, kept by the W steps
-    float* Bcat = nullptr;      // [W_{l+1}; W_{l+1}^T W_{l+1}] for the low-rank form of the Z gradient
     float* tn_partial = nullptr;
     size_t tn_base_floats = 0;  // largest gemm_tn_base_floats that tn_partial serves
     double* partials = nullptr;
@@ -127,7 +126,7 @@ struct cadmm_ctx {
     // already at hand).  Replayed by cadmm_run when the stream is not the
     // default stream; launch-bound problem sizes gain most.
     bool use_graph = true;
-    bool use_lowrank = true;
+    int use_lowrank = 1;         // 0: never, 1: by size, 2: wherever the widths allow it
     bool use_speculative = true;
     int use_floor_first = 1;     // 0: never, 1: by size, 2: wherever the row sums allow it
     struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false, rest_after = false; };
@@ -207,13 +206,18 @@ SpmmSchedule schedule_of(const cadmm_ctx* c, const cadmm_ctx::DevSchedule& d, co
 // or two of the aggregation, there is no difference to be seen (five iterations, 200000 nodes: 64, 64 7.86 and 7.83 ms, 48, 48
 // 7.37 and 7.46; 20000 nodes 1.84 and 1.84, 1.78 and 1.79), and the aggregation stays last.
 enum GradPath { kGradLowRank, kGradProduct, kGradAggregate };
-bool low_rank_shape(const cadmm_ctx* c, int l) {
+bool low_rank_form(const cadmm_ctx* c, int l) {
     const int Cl = c->C[l], Cn = c->C[l + 1];
-    return Cn <= kLowRankMax && Cn < Cl && Cn % 4 == 0 && Cl % 4 == 0 && Cl <= 1024;
+    return Cn <= kLowRankMax && Cn < Cl && Cl % 4 == 0 && Cl <= 1024;
 }
+// The low-rank form saves a write and two reads of an N x C_l matrix; its product walks C_l in steps of 32 in workgroups of 128
+// rows, which few rows or wide layers make a long chain in few workgroups.  us per iteration with the gradient stored and not:
+// 20000 rows, widths 256, 16 199 and 211, 64, 8 147 and 142, 1000, 8 426 and 438; 50000 rows 320 and 309, 202 and 195, 845 and 818;
+// 100000 rows 579 and 566, 302 and 281, 1523 and 1434; 2000 rows 113 and 132, 103 and 103, 165 and 227.
+bool low_rank_shape(const cadmm_ctx* c, int l) { return low_rank_form(c, l) && c->hg.N >= (c->C[l] <= 64 ? 8192 : 32768); }
 bool product_last(int Cl, int Cn) { return Cn < Cl || (Cn == Cl && Cl > 64); }
 GradPath grad_path(const cadmm_ctx* c, int l) {
-    if (c->use_lowrank && low_rank_shape(c, l)) return kGradLowRank;
+    if (c->use_lowrank == 2 ? low_rank_form(c, l) : c->use_lowrank == 1 && low_rank_shape(c, l)) return kGradLowRank;
     return product_last(c->C[l], c->C[l + 1]) ? kGradProduct : kGradAggregate;
 }
 // Column tiles in which the last kernel of that path leaves the rows' sums for the search; 0: it does not, the search reads the
@@ -342,7 +346,6 @@ size_t layout(cadmm_ctx* c, char* base) {
     c->gradW = b.take<float>(wmax);
     c->Wt.assign(L + 1, nullptr);
     for (int l = 2; l <= L; ++l) c->Wt[l] = b.take<float>((size_t)c->C[l - 1] * c->C[l]);
-    c->Bcat = b.take<float>((size_t)(max_of(c->C, 0, L) + kLowRankMax) * kLowRankMax);
     c->tn_partial = b.take<float>(gemm_tn_reserve(tnbase));
     c->tn_base_floats = tnbase;
     size_t np = (size_t)kReduceBlocks * kRestCand;
@@ -820,9 +823,8 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     const Unless resting{note_flag(c, run), 0, P_OTHER, 0.0};
     if (lowrank) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
-        timed(c, P_OTHER, 8.0 * Cl * Cn, 0.0, [&] { launch_lowrank_operand(s, c->W[l + 1], c->Bcat, Cl, Cn); });
-        timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * (Cl + Cn) * Cn, [&] {
-            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->Bcat, Wt, c->tmpV, N, Cl, Cn, Cn, c->nu, row_sums);
+        timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * Cl * Cn, [&] {
+            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->W[l + 1], Wt, c->tmpV, N, Cl, Cn, c->nu, row_sums);
         });
     } else if (path == kGradProduct) {
         const bool on_pairs = grad_on_pairs(c, l);
@@ -1762,7 +1764,7 @@ int cadmm_tune(cadmm_ctx* c, const char* key, int32_t value) {
     const bool k_floor = std::strcmp(key, "use_floor_first") == 0;
     if (k_lowrank || k_spec || k_split || k_refresh || k_floor) {
         // each of these changes the launch sequence of an iteration: captured iterations of this context are dropped
-        if (k_lowrank) c->use_lowrank = value != 0;
+        if (k_lowrank) c->use_lowrank = value == 0 || value == 2 ? value : 1;
         else if (k_spec) c->use_speculative = value != 0;
         else if (k_floor) c->use_floor_first = value;
         else if (k_refresh) { c->t1_refresh = value; c->t1_age = -1; }

@@ -831,7 +831,8 @@ __global__ __launch_bounds__(256) void z_step_kernel(float* __restrict__ Zl, con
 // the order in which gemm_nn_gradz_kernel formed it for the search; a lane group handles two rows per trip with every load issued before the first use.  The rows of W_{l+1}^T
 // live in LDS, not in 64 registers per lane: the kernel is a plain in-place update of Z_l and needs the wavefronts in
 // flight that a small register footprint allows (5 TB/s against 4.4 with the rows in registers).
-template <bool LDSU, bool GATED>
+// SM: kind of the width Cn.
+template <bool LDSU, int SM, bool GATED>
 __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__ Zl, const float* __restrict__ Tl,
                                                              const float* __restrict__ SG, const float* __restrict__ Wt,
                                                              float nu, const int32_t* __restrict__ row_comm, int64_t N,
@@ -870,7 +871,7 @@ __global__ __launch_bounds__(256) void z_step_lowrank_kernel(float* __restrict__
 #pragma unroll
             for (int k4 = 0; k4 < kLowRankMax / 4; ++k4) {
                 float v[4] = {0.f, 0.f, 0.f, 0.f};
-                if (4 * k4 < Cn) ldv4(v, SG + rr * Cn + 4 * k4);
+                if (4 * k4 < Cn) ldr<SM>(v, SG + rr * Cn, 4 * k4, Cn);
                 sg[q][4 * k4] = v[0]; sg[q][4 * k4 + 1] = v[1]; sg[q][4 * k4 + 2] = v[2]; sg[q][4 * k4 + 3] = v[3];
             }
         }
@@ -1086,29 +1087,6 @@ __global__ __launch_bounds__(256) void relu_kernel(const float* __restrict__ T, 
         }
         stq(Z + i, t, nv, w);
     });
-}
-
-// What the low-rank form of the Z gradient needs of W_{l+1} (Cl x Cn, Cn <= kLowRankMax): Bcat = [W; W^T W].
-// One workgroup: W goes through LDS (64 KB at most), thread (i, j) forms its entry of W^T W in fp64.
-__global__ __launch_bounds__(256) void lowrank_operand_kernel(const float* __restrict__ W, float* __restrict__ Bcat, int Cl,
-                                                              int Cn) {
-    extern __shared__ __align__(16) float s_w[];
-    const int n = Cl * Cn;
-    for (int i = threadIdx.x; i < n; i += 256) {
-        const float w = W[i];
-        s_w[i] = w;
-        Bcat[i] = w;
-    }
-    __syncthreads();
-    const int i = threadIdx.x / Cn, j = threadIdx.x % Cn;
-    if (i >= Cn) return;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};            // four chains: the loop is bound by the latency of one
-    int k = 0;
-    for (; k + 3 < Cl; k += 4)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[q] += (double)s_w[(k + q) * Cn + i] * (double)s_w[(k + q) * Cn + j];
-    for (; k < Cl; ++k) acc[0] += (double)s_w[k * Cn + i] * (double)s_w[k * Cn + j];
-    Bcat[n + threadIdx.x] = (float)((acc[0] + acc[1]) + (acc[2] + acc[3]));
 }
 
 // class of every node, see launch_argmax_rows
@@ -1549,12 +1527,13 @@ void launch_z_step_lowrank(hipStream_t s, float* Zl, const float* Tl, const floa
     int64_t nb = (N * (int64_t)Cl + 2047) / 2048;
     nb = nb < 1 ? 1 : (nb > 4 * kReduceBlocks ? 4 * kReduceBlocks : nb);
     const size_t lds = (size_t)Cn * Cl * sizeof(float);                 // at most 16 x 1024 floats (the low-rank limit)
-    with_flag(gate != nullptr, [&](auto gated) {
-        constexpr bool GATED = decltype(gated)::value;
-        if (M <= kStepUnits)
-            hipLaunchKernelGGL((z_step_lowrank_kernel<true, GATED>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
-        else
-            hipLaunchKernelGGL((z_step_lowrank_kernel<false, GATED>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
+    with_mode(Cn, [&](auto sm) {
+        constexpr int SM = decltype(sm)::value;
+        with_flag(gate != nullptr, [&](auto gated) {
+            constexpr bool GATED = decltype(gated)::value;
+            if (M <= kStepUnits) hipLaunchKernelGGL((z_step_lowrank_kernel<true, SM, GATED>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
+            else hipLaunchKernelGGL((z_step_lowrank_kernel<false, SM, GATED>), dim3((unsigned)nb), dim3(256), lds, s, Zl, Tl, SG, Wt, nu, row_comm, N, Cl, Cn, units, M, gate);
+        });
     });
 }
 
@@ -1589,10 +1568,6 @@ void launch_last_layer(hipStream_t s, float* ZL, float* U, float* TL, const int3
             else go(std::integral_constant<int, 4>{});
         }
     });
-}
-
-void launch_lowrank_operand(hipStream_t s, const float* W, float* Bcat, int Cl, int Cn) {
-    hipLaunchKernelGGL(lowrank_operand_kernel, dim3(1), dim3(256), (size_t)Cl * Cn * sizeof(float), s, W, Bcat, Cl, Cn);
 }
 
 void launch_relu(hipStream_t s, const float* T, float* Z, int64_t count, int apply_relu) {

@@ -1096,17 +1096,15 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
     }
 }
 
-// out[n x C] = [ nu (Z - relu(T)) | SG ] * Bcat  with Bcat = [ W (K1 x C) ; S (K2 x C) ],  C <= 16.
-// This is (grad_Z psi) W for grad = nu (Z - relu(T)) + SG W^T and S = W^T W, without ever storing the gradient:
-// the left operand is formed while its tile is loaded.  K1 and K2 are multiples of four, K2 = C.
-// The kernel is bound by reading Z and T; beside that it rebuilds the gradient of every element (C fused multiply-adds, the
-// rows of W^T and the block's rows of SG from LDS) for the row sums of the search, which then reads neither matrix:
-// 0.82 ms for the product and 0.75 for the search's pass over the rows of 2M x 256, 1.0 ms together.
+// out[n x C] = g W with g = nu (Z - relu(T)) + SG W^T  (W: K1 x C, SG: n x C, C <= 16, K1 a multiple of four).
+// This is (grad_Z psi) W without ever storing the gradient: an element of it is formed while its tile is loaded (C fused
+// multiply-adds, the rows of W^T and the block's rows of SG from LDS), for the product and for the row sums of the search, which
+// then reads neither Z nor T.  The kernel is bound by reading those two.
 constexpr int kSgLd = kLowRankMax + 4;            // row stride of SG in LDS: the eight rows a wavefront reads at once hit different banks
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                            const float* __restrict__ SG, const float* __restrict__ Bcat,
+                                                            const float* __restrict__ SG, const float* __restrict__ W,
                                                             const float* __restrict__ Wt, float* __restrict__ out, int64_t n,
-                                                            int K1, int K2, int C, float nu, double* __restrict__ row_sums) {
+                                                            int K1, int C, float nu, double* __restrict__ row_sums) {
     constexpr int BN = 32;
     // 32 columns of Z_l and T_l per step: every row then gives a whole 128-byte line of each matrix to one step.
     // With half lines the second half had left the L2 before its step came (twice the traffic, measured).
@@ -1121,25 +1119,33 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     const int lane = tid & 63;
     const int wm = tid >> 6;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int K = K1 + K2;
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    // threads of the first two wavefronts: quad tid % 8 of row tid / 8 of the tile that starts at column k0
+    // threads of the first two wavefronts: quad tid % 8 of row tid / 8 of the tile that starts at column k0; rows past C are zero
     const bool has_w = tid < 8 * kLowRankMax;
     float4 rw = make_float4(0.f, 0.f, 0.f, 0.f);
     auto fetch_w = [&](int k0) {
-        const int q = tid >> 3 < K2 ? tid >> 3 : K2 - 1, k = k0 + 4 * (tid & 7) < K1 ? k0 + 4 * (tid & 7) : 0;
-        rw = *reinterpret_cast<const float4*>(Wt + (int64_t)q * K1 + k);
+        const int k = k0 + 4 * (tid & 7) < K1 ? k0 + 4 * (tid & 7) : 0;
+        if (tid >> 3 < C) rw = *reinterpret_cast<const float4*>(Wt + (int64_t)(tid >> 3) * K1 + k);
     };
     if (has_w) {
         fetch_w(0);
         *reinterpret_cast<float4*>(s_wt[0] + 4 * tid) = rw;
     }
-    for (int i = tid; i < BM * (K2 / 4); i += 256) {
-        const int r = i / (K2 / 4), q = i - r * (K2 / 4);
-        const int64_t gr = m0 + r < n ? m0 + r : n - 1;
-        *reinterpret_cast<float4*>(s_sg + r * kSgLd + 4 * q) = *reinterpret_cast<const float4*>(SG + gr * K2 + 4 * q);
+    if (C % 4 == 0) {
+        for (int i = tid; i < BM * (C / 4); i += 256) {
+            const int r = i / (C / 4), q = i - r * (C / 4);
+            const int64_t gr = m0 + r < n ? m0 + r : n - 1;
+            *reinterpret_cast<float4*>(s_sg + r * kSgLd + 4 * q) = *reinterpret_cast<const float4*>(SG + gr * C + 4 * q);
+        }
+    } else {
+        const int q = tid & 15;
+        for (int r = tid >> 4; r < BM; r += 16) {
+            const int64_t gr = m0 + r < n ? m0 + r : n - 1;
+            const float v = SG[gr * C + (q < C ? q : C - 1)];
+            s_sg[r * kSgLd + q] = q < C ? v : 0.f;
+        }
     }
     // thread: quad tid % 8 of rows tid / 8 + 32 i
     const int kq = tid & 7;
@@ -1153,6 +1159,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
 #pragma unroll
     for (int i = 0; i < 4; ++i) rs[i][0] = rs[i][1] = rs[i][2] = 0.0;
     float4 rz[4], rt[4], rb;
+    const int bmode = row_mode(C);
+    const int kr = tid / (BN / 4), cq = tid % (BN / 4);                  // W: 32 x 8 quads, one per thread
     auto fetch = [&](int k0) {
         const int k = k0 + 4 * kq < K1 ? k0 + 4 * kq : 0;                // (quads past K1 are not used)
 #pragma unroll
@@ -1160,33 +1168,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             rz[i] = *reinterpret_cast<const float4*>(Zl + grow[i] * K1 + k);
             rt[i] = *reinterpret_cast<const float4*>(Tl + grow[i] * K1 + k);
         }
-        const int kr = tid / (BN / 4), cq = tid % (BN / 4);              // 32 x 8 quads, one per thread
-        rb = ld_quad_raw<kFull>(Bcat + (int64_t)(k0 + kr < K ? k0 + kr : K - 1) * C, 4 * cq, C);
+        rb = ld_quad_raw(bmode, W + (int64_t)(k0 + kr < K1 ? k0 + kr : K1 - 1) * C, 4 * cq, C);
     };
-    auto stash = [&](int k0) {
-        const int k = k0 + 4 * kq;
-        const bool own = k < K1;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float z[4] = {rz[i].x, rz[i].y, rz[i].z, rz[i].w}, t[4] = {rt[i].x, rt[i].y, rt[i].z, rt[i].w};
-            float* const d = As + ((tid >> 3) + 32 * i) * LDA + 4 * kq;
-            float v[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = nu * (z[e] - fmaxf(t[e], 0.f));
-            if (!own) {                                                  // the columns of SG, then zeros
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = k < K ? s_sg[((tid >> 3) + 32 * i) * kSgLd + (k - K1) + e] : 0.f;
-            }
-            d[0] = v[0]; d[1] = v[1]; d[2] = v[2]; d[3] = v[3];
-        }
-        {
-            const int kr = tid / (BN / 4), cq = tid % (BN / 4);
-            *reinterpret_cast<float4*>(Bs + kr * LDB + 4 * cq) = fix_quad<kFull>(rb, 4 * cq, C);
-        }
-    };
-    // the gradient of the quads just stashed, and what the search needs of it
-    auto sums = [&](int k0, const float* wt) {
-        if (k0 + 4 * kq >= K1) return;
+    // the gradient of the quads that were fetched, into the tile, and what the search needs of it
+    auto stash = [&](int k0, const float* wt) {
+        const bool own = k0 + 4 * kq < K1;
         float g[4][4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1195,7 +1181,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             g[i][2] = nu * (rz[i].z - fmaxf(rt[i].z, 0.f));
             g[i][3] = nu * (rz[i].w - fmaxf(rt[i].w, 0.f));
         }
-        for (int q4 = 0; q4 < K2; q4 += 4) {
+        for (int q4 = 0; q4 < C; q4 += 4) {
             float4 sg[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) sg[i] = *reinterpret_cast<const float4*>(s_sg + ((tid >> 3) + 32 * i) * kSgLd + q4);
@@ -1214,6 +1200,16 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
+            float* const d = As + ((tid >> 3) + 32 * i) * LDA + 4 * kq;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) d[e] = own ? g[i][e] : 0.f;
+        }
+        float4 b = fix_quad(bmode, rb, 4 * cq, C);
+        if (k0 + kr >= K1) b = make_float4(0.f, 0.f, 0.f, 0.f);
+        *reinterpret_cast<float4*>(Bs + kr * LDB + 4 * cq) = b;
+        if (!own) return;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
             const float z[4] = {rz[i].x, rz[i].y, rz[i].z, rz[i].w}, t[4] = {rt[i].x, rt[i].y, rt[i].z, rt[i].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
@@ -1224,7 +1220,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             }
         }
     };
-    const int nk = (K + GBK - 1) / GBK;
+    const int nk = (K1 + GBK - 1) / GBK;
     const int li = lane & 31, lk = lane >> 5;
     fetch(0);
     if (has_w) fetch_w(GBK);
@@ -1232,8 +1228,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         __syncthreads();
         // the tile of W^T is stored a step before it is read: no third barrier
         if (has_w) *reinterpret_cast<float4*>(s_wt[(kt + 1) & 1] + 4 * tid) = rw;
-        stash(kt * GBK);
-        sums(kt * GBK, s_wt[kt & 1]);
+        stash(kt * GBK, s_wt[kt & 1]);
         __syncthreads();
         if (kt + 1 < nk) {
             fetch((kt + 1) * GBK);
@@ -2034,10 +2029,10 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
     }
 }
 
-void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Bcat,
-                          const float* Wt, float* out, int64_t n, int K1, int K2, int C, float nu, double* row_sums) {
+void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* W,
+                          const float* Wt, float* out, int64_t n, int K1, int C, float nu, double* row_sums) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, Bcat, Wt, out, n, K1, K2, C, nu, row_sums);
+    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, W, Wt, out, n, K1, C, nu, row_sums);
 }
 
 int gemm_nn_tiles(int64_t n, int C, bool pair) {

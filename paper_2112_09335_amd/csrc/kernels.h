@@ -129,12 +129,11 @@ void launch_stream_copy(hipStream_t s, const float* src, float* dst, int64_t cou
 // dst = 0.999 dst + src in place (count % 4 == 0): two reads and one write-back per element
 void launch_stream_update(hipStream_t s, const float* src, float* dst, int64_t count);
 int64_t gemm_nn_blocks(int64_t n, int C, bool pair);   // grid size of that launch (= block results of epilogue 2)
-// out[n x C] = [nu (Zl - relu(Tl)) | SG] * Bcat, Bcat = [W (K1 x C); S (K2 x C)], C <= 32, K1 % 4 == K2 % 4 == 0:
-// the product (grad_Z psi) W with grad = nu (Zl - relu(Tl)) + SG W^T, S = W^T W, the gradient never stored.
-// The rows' RowSums (one tile) are left on the way: the gradient is rebuilt per element with Wt = W^T (C x K1), the
-// operations and their order as in launch_z_step_lowrank.
-void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Bcat,
-                          const float* Wt, float* out, int64_t n, int K1, int K2, int C, float nu, double* row_sums);
+// out[n x C] = g W with g = nu (Zl - relu(Tl)) + SG Wt, the product (grad_Z psi) W with the gradient never stored (W: K1 x C,
+// Wt its transpose, SG: n x C; C <= kLowRankMax, K1 % 4 == 0).  The rows' RowSums (one tile) are left on the way.  The operations
+// that form an element of g and their order are those of launch_z_step_lowrank.
+void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* W,
+                          const float* Wt, float* out, int64_t n, int K1, int C, float nu, double* row_sums);
 // out[K x C] = A[n x K]^T * G[n x C]; partial: scratch of gemm_tn_scratch_floats(n,K,C) floats.
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C);
 size_t gemm_tn_base_floats(int64_t n, int K, int C);            // what decides whether a caller's scratch will do ...
@@ -288,8 +287,6 @@ void launch_t_carry(hipStream_t s, float* Tn, const CarryArgs& k, int64_t N, int
 // carry: T_L is then brought to the new Z_{L-1}, and G (if not null; needs update_u) gets -(U_new + rho (Z_L_new - T_L_new)).
 void launch_last_layer(hipStream_t s, float* ZL, float* U, float* TL, const int32_t* labels, int64_t N,
                        int CL, int risk, float rho, int J, int update_u, const CarryArgs* carry, float* G);
-// Bcat = [W; W^T W] for the low-rank form of the Z gradient (W is Cl x Cn)
-void launch_lowrank_operand(hipStream_t s, const float* W, float* Bcat, int Cl, int Cn);
 // Last layer by FISTA with backtracking on the block subproblem of Z_{L,m} (Appendix A, Eq. 5): one L per community
 // and step, found by the device-side search over the rows of the community (chunk tables of the graph, kind 0).
 // Stage `stage` of `J` steps: stage 0 evaluates 16 candidates L = rho eta^q at y_0 = Z_L; stage j = 1..J-1 takes step

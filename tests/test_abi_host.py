@@ -129,7 +129,7 @@ def test_workspace_size_depends_on_the_shapes_alone(dims):
     s.set_model(dims, **synth.DEFAULT_HYPER)
     sizes = {s.workspace_bytes()}
     try:
-        for key, values in (("gemm_split", (0, 2, 1)), ("use_lowrank", (0, 1)), ("spmm_tile_cols", (4, 32, 0))):
+        for key, values in (("gemm_split", (0, 2, 1)), ("use_lowrank", (0, 2, 1)), ("spmm_tile_cols", (4, 32, 0))):
             for v in values:
                 s.tune(key, v)
                 sizes.add(s.workspace_bytes())

@@ -502,6 +502,20 @@ def test_fp32_matrix_core_path_matches_the_oracle_too():
         probe.close()
 
 
+# three to sixteen units behind the last hidden layer, in whole quads and not; contractions of whole and partial steps; split rows
+@pytest.mark.parametrize("dims,hubs", [([30, 64, 3], 0), ([33, 100, 36, 5], 0), ([40, 132, 16], 2), ([24, 256, 13], 2), ([50, 68, 40, 10], 2)])
+def test_low_rank_gradient_behind_any_few_units(dims, hubs):
+    w = synth.make_workload("low-rank", 51 + dims[-1], 1301, 4, dims, dims[-1], 4, graph="sbm", features="gaussian", avg_degree=8,
+                            frac_intra=0.8, labelled_fraction=0.7)
+    if hubs:
+        w = synth.add_hubs(w, 5, hubs, 600, 0.5)
+    run_case(w, 5, "low-rank/" + "-".join(map(str, dims)), tune={"use_lowrank": 2})
+
+
+def test_low_rank_gradient_of_the_power_law_sample():
+    run_case(synth.config(4, 0.002), 6, "low-rank/config4", tune={"use_lowrank": 2})
+
+
 @pytest.fixture
 def pairs_everywhere():
     """The products on pairs of fp16 wherever their form allows, not from a size on (process-wide)."""
