@@ -1,6 +1,8 @@
 // Dense fp32 contractions of the sweep on the gfx950 matrix cores: v_mfma_f32_32x32x2_f32, or (default for results
 // wider than 32 columns, the *_split_kernel variants) v_mfma_f32_32x32x16_bf16 on operands split exactly into
-// three bf16 parts each, which gives the same accuracy at a fraction of the matrix-core time:
+// three bf16 parts each, or (large products inside the sweep, the *_pair_kernel variants) v_mfma_f32_32x32x16_f16 on
+// scaled operands of two fp16 parts each, half as many instructions again; both give the fp32 kernels' accuracy at a
+// fraction of the matrix-core time:
 //   gemm_nn : out[n x C] = A[n x K] B[K x C]     (T_l = H_l W_l, Q = H_l gradW, G W^T, gradZ W;
 //                                                 paper Section 3.1 and Appendix A)
 //   gemm_tn : out[K x C] = A[n x K]^T G[n x C]   (gradient of phi with respect to W_l: a sum over all
@@ -11,6 +13,7 @@
 // while the current one feeds the MFMAs.
 //   split products and fp32 products wider than 32 columns: 2 x 2 wavefronts, 128 x 128 results and 16 of the contraction
 //   per step; split products with few tiles 64 x 64 (kFewTiles);
+//   products on pairs: 128 x 256 results (nn) and 256 x 128 (tn), see there;
 //   results of at most 32 columns: a wavefront forms 32 rows by 32 columns, 32 of the contraction per step.
 // MFMA operand layout for 32x32x2 (64 lanes): lane holds A[i = lane%32][k = lane/32] and B[k = lane/32][j = lane%32];
 // accumulator register r of a lane is C[8*(r/4) + 4*(lane/32) + r%4][lane%32].
