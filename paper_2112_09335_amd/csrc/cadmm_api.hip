@@ -824,7 +824,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     if (lowrank) {
         aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
         timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * Cl * Cn, [&] {
-            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, c->W[l + 1], Wt, c->tmpV, N, Cl, Cn, c->nu, row_sums);
+            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, Wt, c->tmpV, N, Cl, Cn, c->nu, row_sums);
         });
     } else if (path == kGradProduct) {
         const bool on_pairs = grad_on_pairs(c, l);

@@ -29,6 +29,7 @@ namespace cadmm {
 namespace {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 128;
 constexpr int BK = 16;
@@ -1102,39 +1103,42 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
 // out[n x C] = g W with g = nu (Z - relu(T)) + SG W^T  (W: K1 x C, SG: n x C, C <= 16, K1 a multiple of four).
 // This is (grad_Z psi) W without ever storing the gradient: an element of it is formed while its tile is loaded (C fused
 // multiply-adds, the rows of W^T and the block's rows of SG from LDS), for the product and for the row sums of the search, which
-// then reads neither Z nor T.  The kernel is bound by reading those two.
+// then reads neither Z nor T.  The kernel is bound by reading those two, with the vector work and the products behind it: the
+// products take v_mfma_f32_16x16x4_f32 (C <= 16: a 32 x 32 instruction's second half would be zeros) and both operands from the tiles
+// that the gradient is formed with, W as the columns of W^T.  2000000 x 256 x 16: 1035 us with v_mfma_f32_32x32x2_f32 on a copy of W's
+// rows in LDS (five spilled registers), 833 so, 5.2 TB/s of Z, T, SG and out; the same
+// sums to the bit.
 constexpr int kSgLd = kLowRankMax + 4;            // row stride of SG in LDS: the eight rows a wavefront reads at once hit different banks
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
-                                                            const float* __restrict__ SG, const float* __restrict__ W,
+                                                            const float* __restrict__ SG,
                                                             const float* __restrict__ Wt, float* __restrict__ out, int64_t n,
                                                             int K1, int C, float nu, double* __restrict__ row_sums) {
-    constexpr int BN = 32;
     // 32 columns of Z_l and T_l per step: every row then gives a whole 128-byte line of each matrix to one step.
     // With half lines the second half had left the L2 before its step came (twice the traffic, measured).
     constexpr int GBK = 32;
-    constexpr int LDA = GBK + 1;
-    constexpr int LDB = BN + 4;
-    __shared__ __align__(16) float As[BM * LDA];
-    __shared__ __align__(16) float Bs[GBK * LDB];
+    constexpr int LD = GBK + 4;                      // 16 rows by 4 columns, a matrix instruction's operand, hit different banks
+    __shared__ __align__(16) float As[BM * LD];
     __shared__ __align__(16) float s_sg[BM * kSgLd];
-    __shared__ __align__(16) float s_wt[2][kLowRankMax * GBK];           // the step's 32 columns of W^T
+    __shared__ __align__(16) float s_wt[2][kLowRankMax * LD];            // the step's 32 columns of W^T, zeros past its rows and columns
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wm = tid >> 6;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
-    floatx16 acc;
+    floatx4 acc[2];                                  // rows 0 .. 15 and 16 .. 31 of the wavefront's 32
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    for (int r = 0; r < 4; ++r) acc[0][r] = acc[1][r] = 0.f;
     // threads of the first two wavefronts: quad tid % 8 of row tid / 8 of the tile that starts at column k0; rows past C are zero
     const bool has_w = tid < 8 * kLowRankMax;
     float4 rw = make_float4(0.f, 0.f, 0.f, 0.f);
     auto fetch_w = [&](int k0) {
-        const int k = k0 + 4 * (tid & 7) < K1 ? k0 + 4 * (tid & 7) : 0;
-        if (tid >> 3 < C) rw = *reinterpret_cast<const float4*>(Wt + (int64_t)(tid >> 3) * K1 + k);
+        const int k = k0 + 4 * (tid & 7);
+        rw = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (tid >> 3 < C && k < K1) rw = *reinterpret_cast<const float4*>(Wt + (int64_t)(tid >> 3) * K1 + k);
     };
+    const int wt_at = (tid >> 3) * LD + 4 * (tid & 7);
     if (has_w) {
         fetch_w(0);
-        *reinterpret_cast<float4*>(s_wt[0] + 4 * tid) = rw;
+        *reinterpret_cast<float4*>(s_wt[0] + wt_at) = rw;
     }
     if (C % 4 == 0) {
         for (int i = tid; i < BM * (C / 4); i += 256) {
@@ -1161,9 +1165,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
     double rs[4][3];
 #pragma unroll
     for (int i = 0; i < 4; ++i) rs[i][0] = rs[i][1] = rs[i][2] = 0.0;
-    float4 rz[4], rt[4], rb;
-    const int bmode = row_mode(C);
-    const int kr = tid / (BN / 4), cq = tid % (BN / 4);                  // W: 32 x 8 quads, one per thread
+    float4 rz[4], rt[4];
     auto fetch = [&](int k0) {
         const int k = k0 + 4 * kq < K1 ? k0 + 4 * kq : 0;                // (quads past K1 are not used)
 #pragma unroll
@@ -1171,7 +1173,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             rz[i] = *reinterpret_cast<const float4*>(Zl + grow[i] * K1 + k);
             rt[i] = *reinterpret_cast<const float4*>(Tl + grow[i] * K1 + k);
         }
-        rb = ld_quad_raw(bmode, W + (int64_t)(k0 + kr < K1 ? k0 + kr : K1 - 1) * C, 4 * cq, C);
     };
     // the gradient of the quads that were fetched, into the tile, and what the search needs of it
     auto stash = [&](int k0, const float* wt) {
@@ -1190,7 +1191,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             for (int i = 0; i < 4; ++i) sg[i] = *reinterpret_cast<const float4*>(s_sg + ((tid >> 3) + 32 * i) * kSgLd + q4);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const float4 w = *reinterpret_cast<const float4*>(wt + (q4 + q) * GBK + 4 * kq);
+                const float4 w = *reinterpret_cast<const float4*>(wt + (q4 + q) * LD + 4 * kq);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float f = q == 0 ? sg[i].x : q == 1 ? sg[i].y : q == 2 ? sg[i].z : sg[i].w;
@@ -1202,14 +1203,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             }
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float* const d = As + ((tid >> 3) + 32 * i) * LDA + 4 * kq;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) d[e] = own ? g[i][e] : 0.f;
-        }
-        float4 b = fix_quad(bmode, rb, 4 * cq, C);
-        if (k0 + kr >= K1) b = make_float4(0.f, 0.f, 0.f, 0.f);
-        *reinterpret_cast<float4*>(Bs + kr * LDB + 4 * cq) = b;
+        for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<float4*>(As + ((tid >> 3) + 32 * i) * LD + 4 * kq) =
+                own ? make_float4(g[i][0], g[i][1], g[i][2], g[i][3]) : make_float4(0.f, 0.f, 0.f, 0.f);
         if (!own) return;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
@@ -1224,13 +1220,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
         }
     };
     const int nk = (K1 + GBK - 1) / GBK;
-    const int li = lane & 31, lk = lane >> 5;
+    const int li = lane & 15, lk = lane >> 4;
     fetch(0);
     if (has_w) fetch_w(GBK);
     for (int kt = 0; kt < nk; ++kt) {
         __syncthreads();
         // the tile of W^T is stored a step before it is read: no third barrier
-        if (has_w) *reinterpret_cast<float4*>(s_wt[(kt + 1) & 1] + 4 * tid) = rw;
+        if (has_w) *reinterpret_cast<float4*>(s_wt[(kt + 1) & 1] + wt_at) = rw;
         stash(kt * GBK, s_wt[kt & 1]);
         __syncthreads();
         if (kt + 1 < nk) {
@@ -1238,17 +1234,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
             if (has_w) fetch_w((kt + 2) * GBK);
         }
 #pragma unroll
-        for (int kk = 0; kk < GBK; kk += 2) {
-            const float a = As[(wm * 32 + li) * LDA + kk + lk];
-            const float b = Bs[(kk + lk) * LDB + li];
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc, 0, 0, 0);
+        for (int kk = 0; kk < GBK; kk += 4) {
+            const float b = s_wt[kt & 1][li * LD + kk + lk];             // (results past C are not stored)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(As[(wm * 32 + 16 * t + li) * LD + kk + lk], b, acc[t], 0, 0, 0);
         }
     }
     if (li < C) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = m0 + wm * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-            if (row < n) out[row * C + li] = acc[r];
+        for (int r = 0; r < 8; ++r) {
+            const int64_t row = m0 + wm * 32 + 16 * (r >> 2) + 4 * lk + (r & 3);
+            if (row < n) out[row * C + li] = acc[r >> 2][r & 3];
         }
     }
 #pragma unroll
@@ -2032,10 +2029,10 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
     }
 }
 
-void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* W,
-                          const float* Wt, float* out, int64_t n, int K1, int C, float nu, double* row_sums) {
+void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Wt, float* out, int64_t n,
+                          int K1, int C, float nu, double* row_sums) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, W, Wt, out, n, K1, C, nu, row_sums);
+    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, Wt, out, n, K1, C, nu, row_sums);
 }
 
 int gemm_nn_tiles(int64_t n, int C, bool pair) {

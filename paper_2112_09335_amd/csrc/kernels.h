@@ -129,11 +129,11 @@ void launch_stream_copy(hipStream_t s, const float* src, float* dst, int64_t cou
 // dst = 0.999 dst + src in place (count % 4 == 0): two reads and one write-back per element
 void launch_stream_update(hipStream_t s, const float* src, float* dst, int64_t count);
 int64_t gemm_nn_blocks(int64_t n, int C, bool pair);   // grid size of that launch (= block results of epilogue 2)
-// out[n x C] = g W with g = nu (Zl - relu(Tl)) + SG Wt, the product (grad_Z psi) W with the gradient never stored (W: K1 x C,
-// Wt its transpose, SG: n x C; C <= kLowRankMax, K1 % 4 == 0).  The rows' RowSums (one tile) are left on the way.  The operations
+// out[n x C] = g W with g = nu (Zl - relu(Tl)) + SG Wt, the product (grad_Z psi) W with the gradient never stored (Wt: the
+// transpose of W, K1 x C; SG: n x C; C <= kLowRankMax, K1 % 4 == 0).  The rows' RowSums (one tile) are left on the way.  The operations
 // that form an element of g and their order are those of launch_z_step_lowrank.
-void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* W,
-                          const float* Wt, float* out, int64_t n, int K1, int C, float nu, double* row_sums);
+void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Wt,
+                          float* out, int64_t n, int K1, int C, float nu, double* row_sums);
 // out[K x C] = A[n x K]^T * G[n x C]; partial: scratch of gemm_tn_scratch_floats(n,K,C) floats.
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C);
 size_t gemm_tn_base_floats(int64_t n, int K, int C);            // what decides whether a caller's scratch will do ...
