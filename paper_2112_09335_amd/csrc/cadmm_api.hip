@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
 #include <mutex>
@@ -29,6 +30,7 @@ constexpr int kProfFlags = 4096;
 constexpr int kStageSlots = 8;                                     // pieces of a large readout in flight at most
 static float* g_scratch_ptr[kMaxDevices] = {};                     // device address of `scratch` on GPU d, once looked up
 static std::mutex g_scratch_mutex;
+static std::atomic<uint32_t> g_turns{0};                           // how often a process-wide knob has been turned (cadmm_tune)
 
 struct cadmm_ctx {
     int device = 0;
@@ -131,6 +133,7 @@ struct cadmm_ctx {
     int use_floor_first = 1;     // 0: never, 1: by size, 2: wherever the row sums allow it
     struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false, rest_after = false; };
     GraphSlot graphs[64];
+    uint32_t turns = g_turns;    // of the process-wide knobs that the graphs, rest_fresh and h_max_tiles know of (follow_tuning)
     // Kernel-level calls on a stream of the caller's (cadmm_op_stream): such a call is launched there, after what the context's
     // own stream holds (own_busy: something may still run on it) and after the kernel-level call before it; whatever uses
     // the own stream next waits for it (op_busy).  op_unrecorded: the last of them was on the null stream, and the event that
@@ -512,14 +515,16 @@ void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpil
           }, unless);
 }
 
-// H_l = A~ X, with its RowMax where the products with H_l run on pairs.  gate (may be null): where *gate is 0 it is there already.
+// H_l = A~ X, with its RowMax where the products with H_l run on pairs.  gate (may be null): where *gate is 0 it is there already,
+// and so is its RowMax if the launch that formed it has left just what this one would.
 void aggregate_H(cadmm_ctx* c, const float* X, int l, const int32_t* gate = nullptr) {
     SpmmEpilogue e;
-    e.gate = gate;
     const int K = c->C[l - 1], tiles = row_tiles(c, K);
-    const bool max = gemm_nn_pair(c->hg.N, K, c->C[l]) && tiles <= c->h_max_room[l];
+    const int max = gemm_nn_pair(c->hg.N, K, c->C[l]) && tiles <= c->h_max_room[l] ? tiles : 0;
+    if (max != c->h_max_tiles[l]) gate = nullptr;
+    e.gate = gate;
     if (max) e.row_max = c->h_max[l];
-    c->h_max_tiles[l] = max ? tiles : 0;
+    c->h_max_tiles[l] = max;
     aggregate(c, X, c->H[l], K, e, Unless{note_flag(c, gate), 0, P_OTHER, 0.0});
 }
 
@@ -1114,8 +1119,27 @@ hipError_t record_op(cadmm_ctx* c) {
     return e;
 }
 
+void drop_graphs(cadmm_ctx* c) {
+    for (auto& slot : c->graphs) {
+        if (slot.exec) (void)hipGraphExecDestroy(slot.exec);
+        slot.exec = nullptr;
+        slot.tried = false;
+    }
+}
+
+// What was enqueued under other settings of the process-wide knobs, by whichever context they were turned, is neither replayed
+// nor built upon: captured iterations are dropped, and nothing rests on what was left for launches of another shape.
+void follow_tuning(cadmm_ctx* c) {
+    const uint32_t turns = g_turns.load();
+    if (c->turns == turns) return;
+    c->turns = turns;
+    c->rest_fresh = false;
+    drop_graphs(c);
+}
+
 // Called by everything that enqueues on the context's own stream.
 hipError_t own_stream(cadmm_ctx* c) {
+    follow_tuning(c);
     if (!c->op_busy) return hipSuccess;
     // A capture cannot wait for work outside of it, and what runs next on the stream itself still has to.
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -1189,14 +1213,6 @@ int on_op_stream(cadmm_ctx* c, const char* what, F body) {
     c->own_busy = false;             // what the own stream held comes before what this stream holds now
     c->op_busy = true;
     return check_launch(c, what);
-}
-
-void drop_graphs(cadmm_ctx* c) {
-    for (auto& slot : c->graphs) {
-        if (slot.exec) (void)hipGraphExecDestroy(slot.exec);
-        slot.exec = nullptr;
-        slot.tried = false;
-    }
 }
 
 }  // namespace
@@ -1762,20 +1778,24 @@ int cadmm_tune(cadmm_ctx* c, const char* key, int32_t value) {
     const bool k_lowrank = std::strcmp(key, "use_lowrank") == 0, k_spec = std::strcmp(key, "use_speculative") == 0;
     const bool k_split = std::strcmp(key, "gemm_split") == 0, k_refresh = std::strcmp(key, "t1_refresh") == 0;
     const bool k_floor = std::strcmp(key, "use_floor_first") == 0;
-    if (k_lowrank || k_spec || k_split || k_refresh || k_floor) {
+    const bool k_tile = std::strcmp(key, "spmm_tile_cols") == 0, k_remap = std::strcmp(key, "spmm_xcd_remap") == 0;
+    if (k_split || k_tile || k_remap) {              // process-wide: every context follows with its next call
+        if (k_split) set_gemm_split(value);
+        else if (k_tile) set_spmm_tile_cols(value);
+        else set_spmm_xcd_remap(value);
+        ++g_turns;
+        return CADMM_OK;
+    }
+    if (k_lowrank || k_spec || k_refresh || k_floor) {
         // each of these changes the launch sequence of an iteration: captured iterations of this context are dropped
         if (k_lowrank) c->use_lowrank = value == 0 || value == 2 ? value : 1;
         else if (k_spec) c->use_speculative = value != 0;
         else if (k_floor) c->use_floor_first = value;
-        else if (k_refresh) { c->t1_refresh = value; c->t1_age = -1; }
-        else set_gemm_split(value);                  // process-wide
+        else { c->t1_refresh = value; c->t1_age = -1; }
         c->rest_fresh = false;
         drop_graphs(c);
         return CADMM_OK;
     }
-    // process-wide, and part of a captured launch as well
-    if (std::strcmp(key, "spmm_tile_cols") == 0) { set_spmm_tile_cols(value); drop_graphs(c); return CADMM_OK; }
-    if (std::strcmp(key, "spmm_xcd_remap") == 0) { set_spmm_xcd_remap(value); drop_graphs(c); return CADMM_OK; }
     return fail(c, CADMM_EINVAL, "unknown tuning key");
 }
 

@@ -295,6 +295,62 @@ def test_layers_at_rest_are_left_as_they_are_bit_for_bit(dims, more, split):
         assert np.array_equal(a, b)
 
 
+def solver_in_cleared_memory(w):
+    """As Solver.from_workload, in a workspace that starts as zeros (the block that was freed last is handed out again)."""
+    import torch
+    from paper_2112_09335_amd import binding
+    s = binding.Solver(0)
+    s.build_graph(w.N, w.src, w.dst, w.M, w.comm)
+    s.set_model(w.dims, **w.hyper)
+    torch.cuda.empty_cache()
+    zeros = torch.zeros(s.workspace_bytes() + 256, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    at = zeros.data_ptr()
+    del zeros
+    s.set_workspace()
+    assert s.workspace.data_ptr() == at
+    s.set_data(w.X, w.labels)
+    return s
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("who", ["this", "other"])
+@pytest.mark.parametrize("key,values", [("spmm_tile_cols", (4, 0)), ("spmm_tile_cols", (0, 4, 0)), ("gemm_split", (0, 2)), ("gemm_split", (2, 1, 2))])
+def test_process_wide_knobs_turned_during_a_run(key, values, who, graph):
+    """What an iteration leaves for the next one under one setting (largest magnitudes of rows, layers at rest, captured iterations)
+    is not taken for what another one would leave, whichever context turns the knob: the same iterates as from a run that keeps
+    nothing.  A second round from the initial weights meets the settings with everything captured already."""
+    from paper_2112_09335_amd import binding
+    w = synth.make_workload("knobs", 79, 1301, 4, [70, 192, 130, 200, 160, 5], 5, 4, graph="sbm", features="gaussian", avg_degree=8, frac_intra=0.8)
+    got = []
+    other = binding.Solver(device=-1)
+    try:
+        for keep in (0, 2):
+            other.tune("gemm_split", 2)
+            other.tune("spmm_tile_cols", 0)
+            s = solver_in_cleared_memory(w)
+            s.tune("use_floor_first", keep)
+            s.tune("use_graph", graph if keep else 0)
+            seen = []
+            for again in range(2):
+                for i, value in enumerate(values):
+                    (s if who == "this" else other).tune(key, value)
+                    if i == 0:
+                        s.init(w.W0)
+                    s.run(1)
+                s.run(2)
+                seen += [s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [s.get_U(), *s.get_steps()]
+            assert all(np.isfinite(x).all() for x in seen)
+            got.append(seen)
+            s.close()
+    finally:
+        other.tune("gemm_split", 1)
+        other.tune("spmm_tile_cols", 0)
+        other.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("entry", [np.inf, np.nan, 3e38])
 @pytest.mark.parametrize("split", [1, 2])
 def test_layers_do_not_rest_on_numbers_that_are_not_finite(entry, split):
