@@ -26,9 +26,9 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0
 MFMA_FP32_PEAK_TFLOPS = 157.3
 MFMA_BF16_PEAK_TFLOPS = 2500.0      # (fp16 the same)
-# fp16 MFMA products issued per fp32 product by the pair kernels; the bf16-split ones of fewer rows or narrower operands, which
-# share their classes, issue six and are counted as three
-PAIR_PRODUCTS = 3
+# 16-bit MFMA products issued per fp32 product: by class name, the number and how an entry calls it.  Both kinds share the classes of
+# the products over the rows; those on three bf16 parts (fewer rows, narrower operands) are counted there as if they issued three.
+ISSUED = {"gemm_nn_pair": (3, "fp16 x3 (bf16 x6 where not on pairs)"), "gemm_tn_split": (6, "bf16 x6")}
 
 # A kernel class is priced against the MFMA roofline if its arithmetic intensity (algorithmic flops per
 # algorithmic byte over the timed region) is above the machine balance, else against HBM bandwidth.
@@ -78,13 +78,14 @@ def roofline_entry(name, p):
     if sec <= 0 or p["records"] == 0:
         return None
     per_launch_ms = p["ms"] / p["records"]
-    if name.startswith(("gemm_nn_pair", "gemm_tn_pair")) and p["bytes"] > 0 and p["flops"] / p["bytes"] > MACHINE_BALANCE:
+    issued = ISSUED.get(name.split("|")[0])
+    if issued and p["bytes"] > 0 and p["flops"] / p["bytes"] > MACHINE_BALANCE:
         # priced in issued 16-bit flops against their peak
-        ach = PAIR_PRODUCTS * p["flops"] / sec / 1e12
+        ach = issued[0] * p["flops"] / sec / 1e12
         return dict(kernel=name, bound="mfma", achieved=ach, peak=MFMA_BF16_PEAK_TFLOPS, unit="TFLOP/s",
                     frac=ach / MFMA_BF16_PEAK_TFLOPS, traffic=None, avg_launch_ms=per_launch_ms,
                     launches=p["records"], share_of_step=None, fp32_product_TFLOPs=p["flops"] / sec / 1e12,
-                    issued="fp16 x3")
+                    issued=issued[1])
     if name.startswith("gemm") and p["bytes"] > 0 and p["flops"] / p["bytes"] > MACHINE_BALANCE:
         ach = p["flops"] / sec / 1e12
         return dict(kernel=name, bound="mfma", achieved=ach, peak=MFMA_FP32_PEAK_TFLOPS, unit="TFLOP/s",

@@ -1767,7 +1767,7 @@ const char* cadmm_profile_class_name(int32_t cls) {
         if (cls == P_GEMM_NN_128) return "gemm_nn_pair|split_kernel<0|3>";
         if (cls == P_GEMM_NN_128_GRADZ) return "gemm_nn_pair|split_kernel<1>";
         if (cls == P_GEMM_NN_128_TRIAL) return "gemm_nn_pair|split_kernel<2|4>+finish";
-        if (cls == P_GEMM_TN) return "gemm_tn_pair|split_kernel+reduce";
+        if (cls == P_GEMM_TN) return "gemm_tn_split|wide_kernel+reduce";
     }
     return kProfNames[cls];
 }

@@ -13,7 +13,7 @@
 // while the current one feeds the MFMAs.
 //   split products and fp32 products wider than 32 columns: 2 x 2 wavefronts, 128 x 128 results and 16 of the contraction
 //   per step; split products with few tiles 64 x 64 (kFewTiles);
-//   products on pairs: 128 x 256 results (nn) and 256 x 128 (tn), see there;
+//   products on pairs: 128 x 256 results; W gradients whose rows fill them: 256 x 128; see there;
 //   results of at most 32 columns: a wavefront forms 32 rows by 32 columns, 32 of the contraction per step.
 // MFMA operand layout for 32x32x2 (64 lanes): lane holds A[i = lane%32][k = lane/32] and B[k = lane/32][j = lane%32];
 // accumulator register r of a lane is C[8*(r/4) + 4*(lane/32) + r%4][lane%32].
@@ -1486,33 +1486,62 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 && P
         }
 }
 
-// ------------------------------------------------------------------------------------------------ TN, pairs of fp16
-// out = A^T G on pairs of fp16 (gemm_nn_pair_kernel) in tiles of 256 x 128, a wavefront 128 x 64: half the matrix instructions of
-// the bf16 split, and of the splitting and the LDS reads per matrix instruction what the larger tile leaves.  A column of A or
-// of G has a scale of its own, and the lanes that load the column keep it: from the first step's largest entry with kTnRoom
-// powers of two to spare; where a later entry would pass 2^15 the scale is lowered.  Every tile in LDS has its columns' ratios to
-// the tile before beside it (ones, nearly always), and whoever multiplies brings the accumulators to them first.
-// us with the prologue (bf16 split in tiles of 256 x 128 before) and without (128 x 128): 500000 x 512 x 512 1534 and 1064, 1442
-// and 964; 200000 x 256 x 256 194 and 154, 179 and 132; 13752 x 767 x 1000 179 and 130, 151 and 119.  Error against 64 bits
-// 0.68 to 0.9 times that of the bf16 split, with and without the prologue.
+// gemm_tn_split_kernel<1> in larger tiles, for matrices whose rows fill them.  With the prologue a thread holds three
+// operands' numbers in flight, which leaves the 128 x 128 kernel at three wavefronts per SIMD; per step it has two barriers and
+// 24 matrix instructions of a wavefront for 16 numbers to split per lane and 12 LDS reads of 16 bytes.  Here a workgroup forms
+// 256 x 128, a wavefront 128 x 64 of it (128 accumulator registers, two wavefronts per SIMD): 48 matrix instructions for 24 numbers
+// and 18 reads, three quarters as much of either, two buffers and one barrier per step, and the next step's numbers are formed and
+// split between the matrix instructions of this one.
+// 500000 x 512 x 512 1657 -> 1332 us (in iterations in which eight such layers step 1850 -> 1510), 200000 x 256 x 256 198 -> 162,
+// 20000 x 700 x 512 128 -> 100, 30000 x 480 x 200 71 -> 58, 13752 x 767 x 1000 174 -> 159.  The same tile without the prologue
+// gains 0 to 6 % (the 128 x 128 kernel then fits four wavefronts), and in out = A B it loses to its longer epilogue what it
+// gains: not used there.
+// Not on pairs of fp16, which would take half the matrix instructions (1534 -> 1064 us): the sum runs along the rows, whose sizes
+// in a column of A and of G have nothing to do with each other, and where the largest entry of a column meets zeros, or large rows of
+// the one meet small rows of the other, an entry held to a part of its column's largest is not held to enough of itself (features of
+// some nodes 1e7 times the others', those nodes' G zero: 4e-6 of |A||G|; rows of e^(4 N(0,1)) against their inverses: 1e-3).
 constexpr int kWideM = 4, kWideN = 2;                        // 32 x 32 accumulators of a wavefront
 constexpr int kWideRows = 64 * kWideM, kWideCols = 64 * kWideN;
-constexpr int kTnRoom = 5;
-constexpr int kTnPairA = kWideRows / 32 * 1024, kTnPairB = kWideCols / 32 * 1024;      // fp16 of 32 columns and one step: parts, lanes of eight
-constexpr int kTnPairBuf = kTnPairA + kTnPairB;
-template <int PRO>
-__global__ __launch_bounds__(256, 2) void gemm_tn_pair_kernel(const float* __restrict__ A, const float* __restrict__ G,
+constexpr int kWideA = kWideRows * BK, kWideB = kWideCols * BK;        // bf16 of one plane: the tile of A, then that of B
+constexpr int kWideBuf = 3 * (kWideA + kWideB);
+// A tile row's 16 k are two 16-byte halves, swapped in every other group of four rows: the eight lanes that read or write at
+// once hit different banks without padding.  Element of the half that holds k (0 or 8) of row r:
+__device__ __forceinline__ int wide_at(int r, int half) { return r * BK + ((half ^ ((r >> 2) & 1)) << 3); }
+// One step: the products of the tiles in S; after those of accumulator row i, between(i).
+template <class F>
+__device__ __forceinline__ void wide_step(floatx16 (&acc)[kWideM][kWideN], const unsigned short* S, int ao, int bo, F between) {
+    bf16x8 b[kWideN][3], a[2][3];
+    auto load_a = [&](bf16x8 (&x)[3], int i) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) x[p] = *reinterpret_cast<const bf16x8*>(S + ao + p * kWideA + i * 32 * BK);
+    };
+#pragma unroll
+    for (int j = 0; j < kWideN; ++j)
+#pragma unroll
+        for (int p = 0; p < 3; ++p) b[j][p] = *reinterpret_cast<const bf16x8*>(S + bo + p * kWideB + j * 32 * BK);
+    load_a(a[0], 0);
+#pragma unroll
+    for (int i = 0; i < kWideM; ++i) {
+        if (i + 1 < kWideM) load_a(a[(i + 1) & 1], i + 1);
+        constexpr int P[6] = {2, 0, 1, 1, 0, 0}, Q[6] = {0, 2, 1, 0, 1, 0};          // smallest terms first
+#pragma unroll
+        for (int t = 0; t < 6; ++t)
+#pragma unroll
+            for (int j = 0; j < kWideN; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i & 1][P[t]], b[j][Q[t]], acc[i][j], 0, 0, 0);
+        between(i);
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void gemm_tn_wide_kernel(const float* __restrict__ A, const float* __restrict__ G,
                                                               const float* __restrict__ Zl, float nu,
                                                               float* __restrict__ partial, int64_t n, int K, int C,
                                                               int64_t rows_per_chunk, const int32_t* __restrict__ gate) {
     if (gate && *gate == 0) return;
-    __shared__ __align__(16) unsigned short smem[3 * kTnPairBuf];
-    __shared__ __align__(16) float s_ratio[3][kWideRows + kWideCols];
-    __shared__ __align__(16) int s_changed[3][4];        // by wavefront
-    __shared__ __align__(16) int s_back[kWideRows + kWideCols];
+    __shared__ __align__(16) unsigned short smem[2 * kWideBuf];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int li = lane & 31, lk = lane >> 5;
     const int ktiles = (K + kWideRows - 1) / kWideRows;
@@ -1524,7 +1553,6 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_pair_kernel(const float* __res
     const int c0 = (tile % ctiles) * kWideCols;
     const int64_t r_begin = chunk * rows_per_chunk;
     const int64_t r_end = (r_begin + rows_per_chunk < n) ? (r_begin + rows_per_chunk) : n;
-    const int steps = r_begin < r_end ? (int)((r_end - r_begin + BK - 1) / BK) : 0;
 
     floatx16 acc[kWideM][kWideN];
 #pragma unroll
@@ -1534,184 +1562,74 @@ __global__ __launch_bounds__(256, 2) void gemm_tn_pair_kernel(const float* __res
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    // A: this thread's column, sixteen rows of a step.  G: the column of lane % 32 of the wavefront's 32, rows 8 (lane / 32) .. + 7.
-    // Columns past the edge repeat the last one: never stored.  The last step takes the chunk's last sixteen rows (of the
-    // chunk before too, if it has fewer): those that are not its own get a G of zero.  n >= 16.
-    const int gc = 32 * wave + li;
-    const int acol = k0 + tid < K ? k0 + tid : K - 1, goff = 8 * lk * C + (c0 + gc < C ? c0 + gc : C - 1);
-    float ra[16], rg[8], rz[PRO ? 8 : 1];
-    auto first_row = [&](int t) {
-        const int64_t r0 = r_begin + (int64_t)t * BK;
-        return r0 + BK <= r_end ? r0 : r_end - BK;
-    };
-    auto fetch_a = [&](int t) {
-        const float* const p = A + first_row(t) * K;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) ra[e] = (p + (int64_t)e * K)[acol];
-    };
-    auto fetch_g = [&](int t) {
-        const int64_t o = first_row(t) * C;
+    // columns past the edge repeat the last one: never stored; rows past the chunk: G is set to zero there
+    const int col = tid & (kWideCols - 1);
+    const int rg = __builtin_amdgcn_readfirstlane(tid / kWideCols);
+    const int acol = k0 + tid < K ? k0 + tid : K - 1, gcol = c0 + col < C ? c0 + col : C - 1;
+    float ra[2][8], rgv[8], rz[8];
+    auto fetch_a = [&](int64_t r0, int h) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            rg[e] = (G + o + (int64_t)e * C)[goff];
-            if constexpr (PRO == 1) rz[e] = (Zl + o + (int64_t)e * C)[goff];
+            const int64_t r = r0 + 8 * h + e;
+            ra[h][e] = (A + (r < r_end ? r : r_end - 1) * K)[acol];
         }
     };
-    int aback = 0, gback = 0;
-    float alim = -1.f, glim = -1.f;                      // (the first step sets the scale)
-    // the scale for entries of up to m: as it was, or a new one; returns the ratio (of the first one to nothing: one)
-    auto rescale = [&](float m, int& back, float& lim, bool& changed) {
-        const bool first = lim < 0.f;
-        const int b = m > lim ? pair_exponent(m) + kTnRoom : back;
-        const float ratio = ldexpf(1.f, first ? 0 : back - b);
-        changed = b != back && !first;
-        back = b;
-        lim = ldexpf(1.f, 15 + b);
-        return ratio;
-    };
-    auto stash8 = [&](unsigned short* D, const float (&x)[8], float s) {
-        uint4v h, l;
+    auto fetch_g = [&](int64_t r0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            unsigned a, b;
-            split2_pair(x[2 * e], x[2 * e + 1], s, a, b);
-            h[e] = a;
-            l[e] = b;
+        for (int e = 0; e < 8; ++e) {
+            const int64_t r = r0 + 8 * rg + e, rr = r < r_end ? r : r_end - 1;
+            rgv[e] = (G + rr * C)[gcol];
+            rz[e] = (Zl + rr * C)[gcol];
         }
-        *reinterpret_cast<uint4v*>(D) = h;
-        *reinterpret_cast<uint4v*>(D + 512) = l;
     };
-    const int aw = (tid >> 5) * 1024 + li * 8, gw = kTnPairA + wave * 1024 + lane * 8;
-    bool a_changed = false;
-    auto scale_a = [&](int q) {
-        float m = 0.f;
+    const int aw = wide_at(tid, 0), aw8 = wide_at(tid, 1), gw = 3 * kWideA + wide_at(col, rg);
+    auto stash_a = [&](unsigned short* D, int h) { stash_split<8>(D, kWideA, h ? aw8 : aw, ra[h]); };
+    auto stash_g = [&](unsigned short* D, int64_t r0) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) m = fmaxf(m, fabsf(ra[e]));
-        s_ratio[q][tid] = rescale(m, aback, alim, a_changed);
+        for (int e = 0; e < 8; ++e) rgv[e] = rgv[e] > 0.f ? nu * (rgv[e] - rz[e]) : 0.f;
+        if (r0 + BK > r_end)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) rgv[e] = r0 + 8 * rg + e < r_end ? rgv[e] : 0.f;
+        stash_split<8>(D, kWideB, gw, rgv);
     };
-    auto stash_a = [&](unsigned short* D, int h) {
-        float x[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = ra[8 * h + e];
-        stash8(D + aw + 256 * h, x, pair_scale(aback));
-    };
-    // LAST: the rows may not all be the step's own
-    auto stash_g = [&](unsigned short* D, int q, int t, auto LAST) {
-        if constexpr (PRO == 1)
-#pragma unroll
-            for (int e = 0; e < 8; ++e) rg[e] = rg[e] > 0.f ? nu * (rg[e] - rz[e]) : 0.f;
-        if constexpr (decltype(LAST)::value) {
-            const int own = (int)(r_begin + (int64_t)t * BK - first_row(t)) - 8 * lk;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) rg[e] = e >= own ? rg[e] : 0.f;
-        }
-        float m = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) m = fmaxf(m, fabsf(rg[e]));
-        m = fmaxf(m, __shfl_xor(m, 32, 64));             // (both lanes of a column decide the same)
-        bool changed;
-        s_ratio[q][kWideRows + gc] = rescale(m, gback, glim, changed);
-        s_changed[q][wave] = __any(changed || a_changed);
-        stash8(D + gw, rg, pair_scale(gback));
-    };
-    half8 a[2][2], b[kWideN][2];
-    const int ao = wm * kWideM * 1024 + lane * 8, bo = kTnPairA + wn * kWideN * 1024 + lane * 8;
-    auto load_a = [&](int w, const unsigned short* S, int i) {
-        a[w][0] = *reinterpret_cast<const half8*>(S + ao + i * 1024);
-        a[w][1] = *reinterpret_cast<const half8*>(S + ao + i * 1024 + 512);
-    };
-    auto load_b = [&](const unsigned short* S) {
-#pragma unroll
-        for (int j = 0; j < kWideN; ++j)
-#pragma unroll
-            for (int p = 0; p < 2; ++p) b[j][p] = *reinterpret_cast<const half8*>(S + bo + j * 1024 + 512 * p);
-    };
-    int q0 = 0, q1 = 1, q2 = 2;                          // slots of this step's tile, the next one's, and the one after
-    // STASH: whether there is a step after the next, whose tile is made meanwhile; LAST: it is the last one
-    auto step = [&](int t, auto STASH, auto LAST) {
-        __syncthreads();
-        const int4 changed = *reinterpret_cast<const int4*>(s_changed[q0]);
-        if (__builtin_amdgcn_readfirstlane(changed.x | changed.y | changed.z | changed.w)) {
-#pragma unroll
-            for (int i = 0; i < kWideM; ++i)
-#pragma unroll
-                for (int j = 0; j < kWideN; ++j) {
-                    const float rc = s_ratio[q0][kWideRows + wn * 32 * kWideN + j * 32 + li];
-#pragma unroll
-                    for (int r = 0; r < 16; ++r)
-                        acc[i][j][r] *= rc * s_ratio[q0][wm * 32 * kWideM + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3)];
-                }
-        }
-        const unsigned short* const S0 = smem + q0 * kTnPairBuf;
-        const unsigned short* const S1 = smem + q1 * kTnPairBuf;
-        unsigned short* const S2 = smem + q2 * kTnPairBuf;
-#pragma unroll
-        for (int i = 0; i < kWideM; ++i) {
-            if (i + 1 < kWideM) load_a((i + 1) & 1, S0, i + 1);
-            else load_a(0, S1, 0);                       // (behind the last step: read and not used)
-#pragma unroll
-            for (int p = 0; p < 3; ++p)                  // smallest terms first
-#pragma unroll
-                for (int j = 0; j < kWideN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[i & 1][p == 0 ? 1 : 0], b[j][p == 1 ? 1 : 0], acc[i][j], 0, 0, 0);
-            if (i + 1 == kWideM) load_b(S1);
-            if constexpr (decltype(STASH)::value) {
-                if (i == 0) { scale_a(q2); stash_a(S2, 0); }
-                if (i == 1) {
-                    stash_a(S2, 1);
-                    if constexpr (!decltype(LAST)::value) fetch_a(t + 3);
-                }
-                if (i == 2) {
-                    stash_g(S2, q2, t + 2, LAST);
-                    if constexpr (!decltype(LAST)::value) fetch_g(t + 3);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        const int q = q0;
-        q0 = q1;
-        q1 = q2;
-        q2 = q;
-    };
-    using yes = std::true_type;
-    using no = std::false_type;
+    const int ao = wide_at(wm * 32 * kWideM + li, lk), bo = 3 * kWideA + wide_at(wn * 32 * kWideN + li, lk);
+    const int steps = r_begin < r_end ? (int)((r_end - r_begin + BK - 1) / BK) : 0;
     if (steps > 0) {
-        for (int t = 0; t < 2 && t < steps; ++t) {
-            fetch_a(t);
-            fetch_g(t);
-            unsigned short* const D = smem + t * kTnPairBuf;
-            scale_a(t);
-            stash_a(D, 0);
-            stash_a(D, 1);
-            stash_g(D, t, t, yes{});
-        }
-        fetch_a(2);
-        fetch_g(2);
-        __syncthreads();
-        load_a(0, smem, 0);
-        load_b(smem);
-        int t = 0;
-        for (; t + 3 < steps; ++t) step(t, yes{}, no{});
-        if (t + 2 < steps) step(t++, yes{}, yes{});
-        for (; t < steps; ++t) step(t, no{}, no{});
+        fetch_a(r_begin, 0);
+        fetch_a(r_begin, 1);
+        fetch_g(r_begin);
+        stash_a(smem, 0);
+        stash_a(smem, 1);
+        stash_g(smem, r_begin);
+        const int64_t r1 = r_begin + BK;
+        fetch_a(r1, 0);                           // (past the chunk's end: its last row again, stored nowhere)
+        fetch_a(r1, 1);
+        fetch_g(r1);
     }
-    s_back[tid] = aback;
-    if (lk == 0) s_back[kWideRows + gc] = gback;
-    __syncthreads();
+    for (int t = 0; t < steps; ++t) {
+        unsigned short* const D = smem + ((t + 1) & 1) * kWideBuf;
+        const int64_t r1 = r_begin + (int64_t)(t + 1) * BK, r2 = r1 + BK;
+        __syncthreads();
+        // (behind the last step the buffer that nobody reads any more is filled once more)
+        wide_step(acc, smem + (t & 1) * kWideBuf, ao, bo, [&](int i) {
+            if (i == 0) { stash_a(D, 0); fetch_a(r2, 0); }
+            if (i == 1) { stash_a(D, 1); fetch_a(r2, 1); }
+            if (i == 2) { stash_g(D, r1); fetch_g(r2); }
+        });
+    }
     float* dst = partial + chunk * (int64_t)K * C;
 #pragma unroll
-    for (int j = 0; j < kWideN; ++j) {
-        const int cl = wn * 32 * kWideN + j * 32 + li, c = c0 + cl;
-        if (c >= C) continue;
-        const int cb = s_back[kWideRows + cl];
+    for (int i = 0; i < kWideM; ++i)
 #pragma unroll
-        for (int i = 0; i < kWideM; ++i)
+        for (int j = 0; j < kWideN; ++j) {
+            const int c = c0 + wn * 32 * kWideN + j * 32 + li;
+            if (c >= C) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int kl = wm * 32 * kWideM + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
-                if (k0 + kl < K) dst[(int64_t)(k0 + kl) * C + c] = ldexpf(acc[i][j][r], s_back[kl] + cb);
+                const int k = k0 + wm * 32 * kWideM + i * 32 + 8 * (r >> 2) + 4 * lk + (r & 3);
+                if (k < K) dst[(int64_t)k * C + c] = acc[i][j][r];
             }
-    }
+        }
 }
 
 // out = sum of the chunks' partial matrices, in fp64 and in a fixed order.  A workgroup takes 4 X entries: X lanes of four
@@ -1919,15 +1837,16 @@ struct TnPlan {
     int64_t rows_per_chunk;
     int bn;              // columns per tile: 128, 64 (split product with few workgroups) or 32
     int tiles;
-    bool pair;           // 256 rows of K per tile: gemm_tn_pair_kernel
+    bool wide;           // 256 rows of K per tile: gemm_tn_wide_kernel
 };
 
 // The rows are cut into chunks so that about 1024 workgroups share the product, four per compute unit.  A chunk has at
 // least 64 rows, and beyond 32 chunks the partial matrices stay below half the size of the operands.  The sums over a
 // chunk's rows are in fp32, their error grows with its length: whatever the tile and these limits ask for, there are no
-// fewer chunks than at the base (128-row tiles, 256 rows).  Longer chunks would be faster but not as accurate: with bf16 splits and the prologue in 128 x 128 tiles 13752 x 767 x 1000 in 864 rows 157 us and 4.6e-7 of the
-// 64-bit product, in 640 rows 182 us and 3.9e-7; 16956 x 476 x 347 in 784 rows 83 us and 4.4e-7, in 256 rows 76 us and 2.6e-7.
-// They fit the scratch of the shape (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
+// fewer chunks than at the base (128-row tiles, 256 rows).  Longer chunks would be faster with the prologue, whose
+// registers let the chip hold 768 workgroups and not 1024, but not as accurate: with 128 x 128 tiles 13752 x 767 x 1000 in
+// 864 rows 157 us and 4.6e-7 of the 64-bit product, in 640 rows 182 us and 3.9e-7; 16956 x 476 x 347 in 784 rows 83 us and 4.4e-7,
+// in 256 rows 76 us and 2.6e-7.  They fit the scratch of the shape (gemm_tn_scratch_floats) whatever tile and operand path is chosen.
 constexpr int kTnBlocks = 1024;
 // prologue: the right operand is formed on the way.
 TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
@@ -1935,7 +1854,7 @@ TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
     const int64_t base_chunks = (int64_t)gemm_tn_base_floats(n, K, C) / ((int64_t)K * C);
     auto plan = [&](int bm, int bn, int blocks = kTnBlocks) {
         p.bn = bn;
-        p.pair = bm == kWideRows;
+        p.wide = bm == kWideRows;
         p.tiles = ((K + bm - 1) / bm) * ((C + bn - 1) / bn);
         int64_t nch = (blocks + p.tiles - 1) / p.tiles;
         nch = std::min(nch, (n + 63) / 64);
@@ -1949,16 +1868,9 @@ TnPlan tn_plan(int64_t n, int K, int C, bool prologue) {
     };
     if (C <= 32) { plan(BM, 32); return p; }
     plan(BM, 128);
-    // Pairs of fp16 from 129 columns of A on.  With the prologue wherever the 128 x 128 tiles would be 256: us before and with
-    // them 20000 x 500 x 128 38.4 and 33.1, 10000 x 500 x 200 38.6 and 35.3, 2000 x 512 x 512 30.4 and 27.9, 100000 x 300 x 257 231
-    // and 188, 20000 x 300 x 60 29.3 and 29.7.  Without it the 128 x 128 kernel has twice the wavefronts per SIMD and is the better
-    // one where the tiles of 256 would be emptier (50000 x 600 x 128 63 and 69) or the chunks short (2000 x 512 x 512 27.2 and
-    // 28.9, 192 rows 40.2 and 38.8).
-    const int64_t blocks = (int64_t)p.nchunks * p.tiles;
-    const bool as_full = (K + kWideRows - 1) / kWideRows * 2 == (K + 127) / 128;
-    if (g_split && n >= 64 && K > 128 && (prologue ? 2 * blocks >= kFewTiles : as_full && blocks >= kFewTiles && p.rows_per_chunk >= 192)) {
-        plan(kWideRows, kWideCols, kTnBlocks / 2);
-    } else if (g_split && blocks < kFewTiles) plan(64, 64);
+    if (g_split && (int64_t)p.nchunks * p.tiles < kFewTiles) plan(64, 64);
+    // (where the last 256 rows would be half empty the tiles cost more than they gain: 384 x 256 138 -> 188 us)
+    else if (g_split && prologue && (K + kWideRows - 1) / kWideRows * 2 == (K + 127) / 128) plan(kWideRows, 128, kTnBlocks / 2);
     return p;
 }
 
@@ -2062,9 +1974,8 @@ int launch_gemm_tn(hipStream_t s, const float* A, const float* G, float* out, in
     if (p.bn == 64) {
         if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 1, 4>), gate);
         else CADMM_TN((gemm_tn_split_kernel<0, 1, 4>), gate);
-    } else if (p.pair) {
-        if (Zl) CADMM_TN((gemm_tn_pair_kernel<1>), gate);
-        else CADMM_TN((gemm_tn_pair_kernel<0>), gate);
+    } else if (p.wide) {
+        CADMM_TN(gemm_tn_wide_kernel, gate);
     } else if (g_split && p.bn == 128) {
         if (Zl) CADMM_TN((gemm_tn_split_kernel<1, 2, 1>), gate);
         else CADMM_TN((gemm_tn_split_kernel<0, 2, 1>), gate);

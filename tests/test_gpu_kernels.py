@@ -282,16 +282,17 @@ def test_an_infinity_in_the_last_row_stays_an_infinity_in_narrow_products(ctx, n
     assert torch.equal(s.op_wgrad_noalloc(A, G), want)
 
 
-# 129 columns of A are the fewest, with and without a last column tile that is full; chunks that end inside a step, and a last one of
-# fewer than sixteen rows (50003 = 196 * 255 + 23 in chunks of 208 rows and so on)
+# 128 x 128 tiles (two of A's columns, one and three of G's) and 64 x 64 ones (49161 rows); last chunks that end inside a step
 @pytest.mark.parametrize("n,K,C", [(50003, 129, 33), (49161, 256, 128), (60001, 500, 129), (65537, 129, 300)])
-@pytest.mark.parametrize("kind", ["even", "growing", "late", "columns"])
-def test_wgrad_on_pairs_follows_its_columns_scales(ctx, n, K, C, kind):
-    """The W-gradient product splits a column scaled by its first rows: columns that grow by 2^80 from row to row, that start with
-    thousands of zeros, or that are 1e-20 to 1e20 of each other must come out as from 32-bit products."""
+@pytest.mark.parametrize("kind", ["even", "growing", "late", "columns", "masked", "opposed"])
+def test_wgrad_of_rows_and_columns_of_unlike_size(ctx, n, K, C, kind):
+    """Columns that grow by 2^80 from row to row, that start with thousands of zeros, or that are 1e-20 to 1e20 of each other must
+    come out as from 32-bit products, also where the largest entries of a column meet zeros (a node whose features are 1e7 times the
+    others', all of its units inactive) or every row of A is as much larger as that of G is smaller: an operand is held in all
+    24 bits whatever the rest of its column is like."""
     import torch
     s, g, _ = ctx
-    say("wgrad on pairs", n, K, C, kind)
+    say("wgrad of unlike rows", n, K, C, kind)
     gen = torch.Generator(device="cuda").manual_seed(n + K)
     A = torch.randn((n, K), generator=gen, device="cuda")
     G = torch.randn((n, C), generator=gen, device="cuda") * 1e-3
@@ -304,6 +305,13 @@ def test_wgrad_on_pairs_follows_its_columns_scales(ctx, n, K, C, kind):
     elif kind == "columns":
         A *= 10.0 ** torch.randint(-20, 1, (1, K), generator=gen, device="cuda")
         G *= 10.0 ** torch.randint(0, 20, (1, C), generator=gen, device="cuda")
+    elif kind == "masked":
+        A[5::1000] *= 1e7
+        G[5::1000] = 0
+    elif kind == "opposed":
+        size = torch.exp(4.0 * torch.randn((n, 1), generator=gen, device="cuda"))
+        A *= size
+        G /= size
     got = s.op_wgrad_noalloc(A, G).double()
     ref, mag = A.double().t() @ G.double(), A.double().abs().t() @ G.double().abs()
     # (fp32 sums over chunks of at most a few hundred rows; the tolerance of the other products)

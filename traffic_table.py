@@ -29,7 +29,7 @@ CLASSES = {
     "spmm_rows_kernel[segments]": [("spmm_rows_kernel", "segments"), ("spmm_combine_kernel", "segments"), ("spmm_single_kernel", None)],
     "gemm_nn_pair|split_kernel<2|4>+finish": [(r"gemm_nn_(?:pair|split)_kernel<[24][,>]", None)],
     "gemm_nn_pair|split_kernel<0|3>": [(r"gemm_nn_(?:pair|split)_kernel<0[,>]", None)],       # (3 is the forward pass alone)
-    "gemm_tn_pair|split_kernel+reduce": [(r"gemm_tn_(pair|split)_kernel", None)],
+    "gemm_tn_split|wide_kernel+reduce": [(r"gemm_tn_(split|wide)_kernel", None)],
     "gemm_nn_kernel<32>": [(r"gemm_nn_narrow_kernel<[05],", None)],
     "gemm_tn_kernel<32>+reduce": [(r"gemm_tn_kernel<32", None)],
     "gemm_nn_gradz_kernel": [(r"gemm_nn_gradz_kernel", None)],
