@@ -283,9 +283,10 @@ const char* cadmm_profile_class_name(int32_t cls);
  * aggregation launch (0 = all at once); "spmm_xcd_remap": 1 = each XCD walks one contiguous slice of the aggregation's
  * work list, whole communities one after the other (default), 0 = workgroups in plain order;
  * "gemm_split": 1 = products with more than 32 result columns split both operands for the 16-bit matrix cores and accumulate
- * in fp32 (default): exactly into three bf16 parts with the six largest cross products, or, large products inside the sweep,
- * scaled by powers of two into two fp16 parts with the three largest; 2 = two fp16 parts inside the sweep at any size (for
- * tests); 0 = on the fp32 matrix cores. */
+ * in fp32 (default): exactly into three bf16 parts with the six largest cross products, or, in large products over the nodes inside
+ * the sweep, scaled by powers of two into two fp16 parts with the three largest, for those tiles of results whose operands are
+ * alike enough in size that all of them are certain to come out to 2^-20 of sum |a||b| (usually to 2^-23), the others in three; 2 = so
+ * inside the sweep at any size (for tests); 0 = on the fp32 matrix cores. */
 int  cadmm_tune(cadmm_ctx* ctx, const char* key, int32_t value);
 
 #ifdef __cplusplus

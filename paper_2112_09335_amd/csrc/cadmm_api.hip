@@ -90,15 +90,15 @@ struct cadmm_ctx {
     double* partials = nullptr;
     double* row_sums = nullptr; // RowSums of the Z gradient being searched, for up to row_sum_tiles tiles
     int row_sum_tiles = 0;
-    // For products on pairs of fp16: RowMax of H_l (h_max_tiles: the tiles of the aggregation that left it, 0: it did not), of
+    // For products on pairs of fp16: RowRange of H_l (h_range_tiles: the tiles of the aggregation that left it, 0: it did not), of
     // tmpA and of tmpB (their room in tiles), and the right operand in operand layout.
-    std::vector<float*> h_max;
-    std::vector<int> h_max_room, h_max_tiles;
-    float* a_max = nullptr;
-    float* b_max = nullptr;
-    int a_max_room = 0, b_max_room = 0;
+    std::vector<uint32_t*> h_range;
+    std::vector<int> h_range_room, h_range_tiles;
+    uint32_t* a_range = nullptr;
+    uint32_t* b_range = nullptr;
+    int a_range_room = 0, b_range_room = 0;
     unsigned short* planes = nullptr;
-    int* col_back = nullptr;
+    int* columns = nullptr;
     Unit* unitsW = nullptr;     // [L]
     Unit* unitsZ = nullptr;     // [(L-1) * M]
     Unit* unitsF = nullptr;     // [M]: the L of the last-layer solve with backtracking (fista_mode 1)
@@ -133,7 +133,7 @@ struct cadmm_ctx {
     int use_floor_first = 1;     // 0: never, 1: by size, 2: wherever the row sums allow it
     struct GraphSlot { hipGraphExec_t exec = nullptr; bool tried = false, gl_after = false, rest_after = false; };
     GraphSlot graphs[64];
-    uint32_t turns = g_turns;    // of the process-wide knobs that the graphs, rest_fresh and h_max_tiles know of (follow_tuning)
+    uint32_t turns = g_turns;    // of the process-wide knobs that the graphs, rest_fresh and h_range_tiles know of (follow_tuning)
     // Kernel-level calls on a stream of the caller's (cadmm_op_stream): such a call is launched there, after what the context's
     // own stream holds (own_busy: something may still run on it) and after the kernel-level call before it; whatever uses
     // the own stream next waits for it (op_busy).  op_unrecorded: the last of them was on the null stream, and the event that
@@ -230,7 +230,7 @@ int row_tiles(const cadmm_ctx* c, int width) { return spmm_tiles(schedule_of(c, 
 // Whether the product that forms the gradient of layer l (kGradProduct) runs on pairs.
 bool grad_on_pairs(const cadmm_ctx* c, int l) {
     const int Cl = c->C[l], Cn = c->C[l + 1];
-    return gemm_nn_pair(c->hg.N, Cn, Cl) && row_tiles(c, Cn) <= c->a_max_room;
+    return gemm_nn_pair(c->hg.N, Cn, Cl) && row_tiles(c, Cn) <= c->a_range_room;
 }
 int sum_tiles_of(const cadmm_ctx* c, int l, GradPath path) {
     const int Cl = c->C[l];
@@ -362,7 +362,7 @@ size_t layout(cadmm_ctx* c, char* base) {
     c->row_sum_tiles = 0;
     for (int l = 1; l < L; ++l) c->row_sum_tiles = std::max(c->row_sum_tiles, sum_tiles_reserved(c, l));
     c->row_sums = b.take<double>((size_t)N * c->row_sum_tiles * 3);
-    // RowMax and operand planes by form alone, whatever the number of rows and the tuning make of it
+    // RowRange and operand planes by form alone, whatever the number of rows and the tuning make of it
     const SpmmSchedule rows = schedule_of(c, c->d_rows, g.row_sched);
     size_t planes = 0;
     auto want = [&](int K, int C) {
@@ -370,22 +370,22 @@ size_t layout(cadmm_ctx* c, char* base) {
         planes = std::max(planes, gemm_nn_pair_planes(K, C));
         return true;
     };
-    c->h_max.assign(L + 1, nullptr);
-    c->h_max_room.assign(L + 1, 0);
-    c->h_max_tiles.assign(L + 1, 0);
-    c->a_max_room = c->b_max_room = 0;
+    c->h_range.assign(L + 1, nullptr);
+    c->h_range_room.assign(L + 1, 0);
+    c->h_range_tiles.assign(L + 1, 0);
+    c->a_range_room = c->b_range_room = 0;
     for (int l = 1; l <= L; ++l) {
         const int K = c->C[l - 1], Cl = c->C[l];
-        if (!c->agg_first[l] && want(K, Cl)) c->h_max_room[l] = spmm_default_tiles(rows, K);
-        c->h_max[l] = b.take<float>((size_t)N * c->h_max_room[l]);
+        if (!c->agg_first[l] && want(K, Cl)) c->h_range_room[l] = spmm_default_tiles(rows, K);
+        c->h_range[l] = b.take<uint32_t>((size_t)N * c->h_range_room[l]);
         if (l < 2) continue;
-        if (product_last(K, Cl) && want(Cl, K)) c->a_max_room = std::max(c->a_max_room, spmm_default_tiles(rows, Cl));
-        if (want(K, Cl)) c->b_max_room = std::max({c->b_max_room, spmm_default_tiles(rows, K), gemm_nn_pair_tiles(K)});
+        if (product_last(K, Cl) && want(Cl, K)) c->a_range_room = std::max(c->a_range_room, spmm_default_tiles(rows, Cl));
+        if (want(K, Cl)) c->b_range_room = std::max({c->b_range_room, spmm_default_tiles(rows, K), gemm_nn_pair_tiles(K)});
     }
-    c->a_max = b.take<float>((size_t)N * c->a_max_room);
-    c->b_max = b.take<float>((size_t)N * c->b_max_room);
+    c->a_range = b.take<uint32_t>((size_t)N * c->a_range_room);
+    c->b_range = b.take<uint32_t>((size_t)N * c->b_range_room);
     c->planes = b.take<unsigned short>(planes);
-    c->col_back = b.take<int>(planes ? max_of(c->C, 0, L) : 0);
+    c->columns = b.take<int>(planes ? 2 * (size_t)max_of(c->C, 0, L) : 0);
     c->unitsW = b.take<Unit>(L);
     c->unitsZ = b.take<Unit>((size_t)(L - 1) * g.M);
     c->unitsF = b.take<Unit>((size_t)g.M);
@@ -515,26 +515,26 @@ void aggregate(cadmm_ctx* c, const float* X, float* Y, int width, const SpmmEpil
           }, unless);
 }
 
-// H_l = A~ X, with its RowMax where the products with H_l run on pairs.  gate (may be null): where *gate is 0 it is there already,
-// and so is its RowMax if the launch that formed it has left just what this one would.
+// H_l = A~ X, with its RowRange where the products with H_l run on pairs.  gate (may be null): where *gate is 0 it is there already,
+// and so is its RowRange if the launch that formed it has left just what this one would.
 void aggregate_H(cadmm_ctx* c, const float* X, int l, const int32_t* gate = nullptr) {
     SpmmEpilogue e;
     const int K = c->C[l - 1], tiles = row_tiles(c, K);
-    const int max = gemm_nn_pair(c->hg.N, K, c->C[l]) && tiles <= c->h_max_room[l] ? tiles : 0;
-    if (max != c->h_max_tiles[l]) gate = nullptr;
+    const int left = gemm_nn_pair(c->hg.N, K, c->C[l]) && tiles <= c->h_range_room[l] ? tiles : 0;
+    if (left != c->h_range_tiles[l]) gate = nullptr;
     e.gate = gate;
-    if (max) e.row_max = c->h_max[l];
-    c->h_max_tiles[l] = max;
+    if (left) e.row_range = c->h_range[l];
+    c->h_range_tiles[l] = left;
     aggregate(c, X, c->H[l], K, e, Unless{note_flag(c, gate), 0, P_OTHER, 0.0});
 }
 
-// For products with a left operand whose RowMax has that many tiles (0: there is none).
-PairOperands pair_operands(const cadmm_ctx* c, const float* row_max, int tiles) {
+// For products with a left operand whose RowRange has that many tiles (0: there is none).
+PairOperands pair_operands(const cadmm_ctx* c, const uint32_t* row_range, int tiles) {
     PairOperands p;
-    if (tiles > 0) { p.row_max = row_max; p.max_tiles = tiles; p.planes = c->planes; p.col_back = c->col_back; }
+    if (tiles > 0) { p.row_range = row_range; p.range_tiles = tiles; p.planes = c->planes; p.columns = c->columns; }
     return p;
 }
-PairOperands pair_of_H(const cadmm_ctx* c, int l) { return pair_operands(c, c->h_max[l], c->h_max_tiles[l]); }
+PairOperands pair_of_H(const cadmm_ctx* c, int l) { return pair_operands(c, c->h_range[l], c->h_range_tiles[l]); }
 
 // P_{(i,c)} = sum over the entries of row i in community c of A~_ij V_j, one output row per segment, in the
 // (community, row) order: the segments with several entries as a row list, those with one entry as scaled copies.
@@ -820,9 +820,9 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     const bool lowrank = path == kGradLowRank;
     const int sum_tiles = how.sum_tiles;
     double* const row_sums = sum_tiles ? c->row_sums : nullptr;
-    // grad W_{l+1} runs on pairs if whatever forms the gradient can leave its RowMax
-    const bool want_max = !lowrank && gemm_nn_pair(N, Cl, Cn);
-    int max_tiles = 0;
+    // grad W_{l+1} runs on pairs if whatever forms the gradient can leave its RowRange
+    const bool want_range = !lowrank && gemm_nn_pair(N, Cl, Cn);
+    int range_tiles = 0;
     // where the layer rests the gradient is below resolution as it was
     const int32_t* const run = c->rest && how.gate ? c->run_z + l : nullptr;
     const Unless resting{note_flag(c, run), 0, P_OTHER, 0.0};
@@ -835,13 +835,13 @@ void z_update_hidden(cadmm_ctx* c, int l) {
         const bool on_pairs = grad_on_pairs(c, l);
         SpmmEpilogue epi;
         epi.gate = run;
-        if (on_pairs) epi.row_max = c->a_max;
+        if (on_pairs) epi.row_range = c->a_range;
         aggregate(c, c->G[l + 1], c->tmpA, Cn, epi, resting);                    // A~ G_{l+1}
         GemmEpilogue ge;
         ge.gate = run;
         if (on_pairs) {
-            ge.pair = pair_operands(c, c->a_max, row_tiles(c, Cn));
-            if (want_max) { ge.out_max = c->b_max; max_tiles = gemm_nn_pair_tiles(Cl); }
+            ge.pair = pair_operands(c, c->a_range, row_tiles(c, Cn));
+            if (want_range) { ge.out_range = c->b_range; range_tiles = gemm_nn_pair_tiles(Cl); }
         }
         ge.kind = 1; ge.Zl = c->Z[l]; ge.Tl = c->T[l]; ge.nu = c->nu; ge.row_sums = row_sums;
         gemm_nn(c, c->tmpA, Wt, c->tmpB, N, Cn, Cl, ge, resting);
@@ -851,7 +851,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
         gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl, ge, resting);            // G_{l+1} W_{l+1}^T
         SpmmEpilogue epi;
         epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu; epi.row_sums = row_sums;
-        if (want_max && row_tiles(c, Cl) <= c->b_max_room) { epi.row_max = c->b_max; max_tiles = row_tiles(c, Cl); }
+        if (want_range && row_tiles(c, Cl) <= c->b_range_room) { epi.row_range = c->b_range; range_tiles = row_tiles(c, Cl); }
         aggregate(c, c->tmpA, c->tmpB, Cl, epi);
     }
     ZTrialArgs a;
@@ -875,7 +875,7 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     if (!lowrank) {
         GemmEpilogue ge;
         ge.gate = a.gate;
-        ge.pair = pair_operands(c, c->b_max, max_tiles);
+        ge.pair = pair_operands(c, c->b_range, range_tiles);
         gemm_nn(c, c->tmpB, c->W[l + 1], c->tmpV, N, Cl, Cn, ge, gated);         // grad W_{l+1}
     }
     aggregate_segments(c, c->tmpV, c->P, Cn, a.gate, gated);                     // A~_{r,m} (grad W) per segment

@@ -1,8 +1,8 @@
 // Dense fp32 contractions of the sweep on the gfx950 matrix cores: v_mfma_f32_32x32x2_f32, or (default for results
 // wider than 32 columns, the *_split_kernel variants) v_mfma_f32_32x32x16_bf16 on operands split exactly into
 // three bf16 parts each, or (large products inside the sweep, the *_pair_kernel variants) v_mfma_f32_32x32x16_f16 on
-// scaled operands of two fp16 parts each, half as many instructions again; both give the fp32 kernels' accuracy at a
-// fraction of the matrix-core time:
+// scaled operands of two fp16 parts each, half as many instructions again, where that gives the fp32 kernels' accuracy too,
+// at a fraction of the matrix-core time:
 //   gemm_nn : out[n x C] = A[n x K] B[K x C]     (T_l = H_l W_l, Q = H_l gradW, G W^T, gradZ W;
 //                                                 paper Section 3.1 and Appendix A)
 //   gemm_tn : out[K x C] = A[n x K]^T G[n x C]   (gradient of phi with respect to W_l: a sum over all
@@ -707,14 +707,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(T == 2 ? 4 
 
 // ------------------------------------------------------------------------------------------------ NN, pairs of fp16
 // The same product with half the matrix instructions: an operand scaled by a power of two so that its largest entry lies in
-// [2^14, 2^15) is the sum of two fp16 numbers, x = hi + lo, hi = fp16(x) and lo = fp16(x - hi) rounded to nearest, to 2^-23 of
-// itself (entries below 2^-16 of the largest: to 2^-39 of the largest), and hi*hi, hi*lo and lo*hi are accumulated in fp32;
-// lo*lo is below 2^-22 of |a||b|.  A row of A has a scale of its own (from RowMax, left by whatever formed A), so has a column
-// of B; results are scaled back by ldexp.  What bounds wide products is the power the matrix instructions take (the chip runs
-// them at 1.55 to 1.65 GHz, by GRBM_GUI_ACTIVE over time), and the fp32 roundings are half as many: against 64 bits the error of
-// 512-long sums is 2.6e-7 of the result where the three-way split of bf16 has 3.5e-7 (Gaussian operands; at 16 it would be 1.2
-// times, from 64 on it is 0.75 to 0.95 times that of the bf16 split, also for positive ones, for rows and columns scaled by 1e-8
-// to 1e8 and for entries spread over e^(4 N(0,1))).
+// [2^14, 2^15) is the sum of two fp16 numbers, x = hi + lo, hi = fp16(x) and lo = fp16(x - hi) rounded to nearest, to 2^-24 of
+// itself or 2^-25, whichever is more, and hi*hi, hi*lo and lo*hi are accumulated in fp32; lo*lo is below 2^-24 of |a||b|.  A row of A
+// has a scale of its own (from RowRange, left by whatever formed A), so has a column of B; results are scaled back by ldexp.
+// Entries far below the largest of their row or column are not held to 24 bits of themselves.  That is of no account where enough
+// of a row's largest entries meet large ones of the column, and a tile of results is formed on pairs only if that is certain for
+// each of them, by counting alone: if of the n entries of a row that are not zero l are near the largest, and of a column s are not
+// near its largest (zeros among them), at least l - s products have two near factors.  Near: at least 2^-6 (2^-7 in a column) of the
+// power of two in the largest, scaled 2^8 and 2^7.  With l - s >= n / 16 the sum |a||b| is at least n / 16 * 2^15, what the 2^-25
+// add up to at most 2 n 2^15 2^-25, and a result is within 3 * 2^-24 + 2^-20 of |a||b|, usually a tenth of that and less.  A tile for
+// which the counts do not say so (features of some columns 1e6 times the others', one-hot weights, rows with few entries) is formed
+// from bf16 triples like the products of gemm_nn_split_kernel, to the bit.
+// What bounds wide products is the power the matrix instructions take (the chip runs them at 1.55 to 1.65 GHz, by GRBM_GUI_ACTIVE over
+// time), and the fp32 roundings are half as many: against 64 bits the error of 512-long sums is 2.6e-7 of the result where the
+// three-way split of bf16 has 3.5e-7 (Gaussian operands; at 16 it would be 1.2 times, from 64 on it is 0.75 to 0.95 times that of the
+// bf16 split, also for positive ones and for rows and columns scaled by 1e-8 to 1e8).
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float float2v __attribute__((ext_vector_type(2)));
@@ -741,13 +748,20 @@ constexpr int kPairWaves = 4;                                    // side by side
 constexpr int kPairRows = 32 * kPairTM, kPairCols = 32 * kPairTN * kPairWaves;
 constexpr int kPairLeast = 129;                                  // columns: half a tile and less go by other kernels
 constexpr int kPairSub = 2 * 2 * 512;                            // fp16 of 32 rows (columns of B) and one step: 16-k halves, parts, lanes of eight
+constexpr int kTripleSub = 2 * 3 * 512;                          // bf16 likewise
+// Near entries (range_word): of a column; of a wavefront's 64 columns of a result row, which are parts of a tile's, as tiles are of
+// the row's.  In all a row's are within 3 + 1 + 2 binades, as those of an aggregation's tile are within 4 + 2.
+constexpr int kNearColumn = 7, kNearSlab = 3, kSlabBinades = 1, kTileBinades = 2;
+constexpr int kUnlike = -(1 << 30);                              // reach of a row that is not for pairs
 
 // B (K x C) in the matrix cores' own operand layout, [32 columns][step][16-k half][part][lane][8], zeros past K, and what the
-// columns' results are scaled back by.  A workgroup takes 32 columns; entries are read twice, the second time from the L2.
+// columns' results are scaled back by; behind the C of them, how many entries of a column are not near its largest.  A workgroup
+// takes 32 columns; entries are read twice, the second time from the L2.
 __global__ __launch_bounds__(1024) void pair_weights_kernel(const float* __restrict__ B, int K, int C, unsigned short* __restrict__ planes,
-                                                            int* __restrict__ back, const int32_t* __restrict__ gate) {
+                                                            int* __restrict__ columns, const int32_t* __restrict__ gate) {
     __shared__ float s_max[32][32];
-    __shared__ int s_back[32];
+    __shared__ int s_small[32][32];
+    __shared__ float s_top[32];
     if (gate && *gate == 0) return;
     const int li = threadIdx.x & 31, g = threadIdx.x >> 5;
     const int c = blockIdx.x * 32 + li;
@@ -770,16 +784,20 @@ __global__ __launch_bounds__(1024) void pair_weights_kernel(const float* __restr
     __syncthreads();
     if (g == 0) {
         for (int i = 1; i < 32; ++i) m = fmaxf(m, s_max[i][li]);
-        s_back[li] = pair_exponent(m);
-        if (c < C) back[c] = s_back[li];
+        s_top[li] = m;
+        if (c < C) columns[c] = pair_exponent(m);
     }
     __syncthreads();
-    const float s = pair_scale(s_back[li]);
+    m = s_top[li];
+    const float s = pair_scale(pair_exponent(m)), near = range_near(m, kNearColumn);
+    int small = 0;
     const int steps = (K + kPairK - 1) / kPairK;
     for (int k0 = 8 * g; k0 < steps * kPairK; k0 += 256) {
         float x[8];
         load8(k0, x);
         uint4v h, l;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) small += k0 + e < K && fabsf(x[e]) < near ? 1 : 0;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             unsigned a, b;
@@ -792,16 +810,24 @@ __global__ __launch_bounds__(1024) void pair_weights_kernel(const float* __restr
         *reinterpret_cast<uint4v*>(o) = h;
         *reinterpret_cast<uint4v*>(o + 512) = l;
     }
+    s_small[g][li] = small;
+    __syncthreads();
+    if (g == 0 && c < C) {
+        for (int i = 1; i < 32; ++i) small += s_small[i][li];
+        // nothing but zeros asks for nothing; a largest entry that cannot be scaled to 2^14 (or is no number) for more than there is
+        const uint32_t e = magnitude_exponent(m);
+        columns[C + c] = m == 0.f ? kUnlike : e < 15 || e == 255 ? K + 1 : small;
+    }
 }
 
 // A wavefront's 128 x 64 results, 32 rows at a time through a slab of LDS of its own (no barrier) so that every global access
 // is a 16-byte piece of 256 consecutive bytes.  EPI as in tile_epilogue.  s_rs / s_rm: EPI 1, where this wavefront's share of its
-// rows' sums and its largest magnitudes go (null: nobody asks).
+// rows' sums and its RowRange words go (null: nobody asks).
 constexpr int kPairLd = 64 + 4;
 template <int EPI, int MODE>
 __device__ __forceinline__ void pair_epilogue(floatx16 (&acc)[kPairTM][kPairTN], float* Cs, const int* s_back, const int (&cb)[kPairTN],
                                               int64_t m0, int c0, int64_t n, int C, const EpilogueArgs& args, double& dsum,
-                                              double* s_rs, float* s_rm) {
+                                              double* s_rs, uint32_t* s_rm) {
     const int lane = threadIdx.x & 63;
     const int li = lane & 31, lk = lane >> 5;
     const int c = c0 + 4 * (lane & 15);
@@ -851,9 +877,13 @@ __device__ __forceinline__ void pair_epilogue(floatx16 (&acc)[kPairTM][kPairTN],
                 if constexpr (EPI == 1) {
                     if (s_rm) {
                         float m = in ? fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3]))) : 0.f;
+                        m = __int_as_float(over_lanes<16>(__float_as_int(m), [](int a, int b) { return max(a, b); }));       // (as whole numbers)
+                        const float t = range_near(m, kNearSlab);
+                        int n = 0;
 #pragma unroll
-                        for (int o = 1; o < 16; o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-                        if ((lane & 15) == 0) s_rm[32 * q + rl] = m;
+                        for (int e = 0; e < 4; ++e) n += in && c + e < C ? (fabsf(v[e]) >= t ? 1 : 0) + (v[e] != 0.f ? 1 << 16 : 0) : 0;
+                        n = over_lanes<16>(n, [](int a, int b) { return a + b; });
+                        if ((lane & 15) == 0) s_rm[32 * q + rl] = range_word_of(m, n);
                     }
                 }
             }
@@ -866,13 +896,15 @@ __device__ __forceinline__ void pair_epilogue(floatx16 (&acc)[kPairTM][kPairTN],
 // (pair_weights_kernel), a half step ahead: no wavefront reads what another does.  Two workgroups of four wavefronts share a
 // compute unit, one's epilogue beside the other's products.  Against one workgroup of 256 x 256, both operands in LDS, the large
 // product is as fast and the mid-sized one is not cut into three rounds and a bit: us for 500000 x 512 x 512 and 200000 x 256
-// x 256, bf16 split 1590 and 182, 256 x 256 946 and 195, 128 x 128 1090 and 186, this one 950 and 122.
+// x 256, bf16 split 1590 and 182, 256 x 256 946 and 195, 128 x 128 1090 and 186, this one 950 and 122.  The counts of RowRange cost
+// them 1 % (its words read, a barrier that is there anyway), 5 % where the result's are left too; a tile on triples takes 1.6 times as
+// long (of 500000 x 512 x 512 with epilogue 4, all of them: 1940 us, on pairs 1210).
 template <int EPI>
 __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_nn_pair_kernel(
-    const float* __restrict__ A, const unsigned short* __restrict__ planes, const int* __restrict__ col_back,
-    const float* __restrict__ row_max, int max_tiles, float* __restrict__ out, int64_t n, int K, int C,
+    const float* __restrict__ A, const float* __restrict__ B, const unsigned short* __restrict__ planes, const int* __restrict__ columns,
+    const uint32_t* __restrict__ row_range, int range_tiles, float* __restrict__ out, int64_t n, int K, int C,
     const float* __restrict__ Zl, const float* __restrict__ Tl, float nu, float* __restrict__ Tio, const Unit* unit,
-    double* __restrict__ partials, float* __restrict__ out_max, const int32_t* __restrict__ gate) {
+    double* __restrict__ partials, uint32_t* __restrict__ out_range, const int32_t* __restrict__ gate) {
     if (EPI != 3 && gate && *gate == 0) return;
     if constexpr (EPI == 0) {
         // gated plain product, as in gemm_nn_kernel
@@ -881,11 +913,12 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
     constexpr int WN = kPairWaves, NT = 64 * WN;
     constexpr int AP = kPairRows * 4 / NT;               // pieces of eight k per thread and step
     constexpr int BUF = kPairTM * kPairSub;
-    constexpr int kSlabs = WN * 32 * kPairLd * 4;        // bytes: the wavefronts' slabs, then (EPI 1) their rows' sums and maxima
-    constexpr int kSums = WN * kPairRows * 3 * 8, kMaxima = WN * kPairRows * 4;
-    static_assert(kSlabs + kSums + kMaxima <= 3 * BUF * 2, "the epilogue's share must fit the operand buffers");
+    constexpr int kSlabs = WN * 32 * kPairLd * 4;        // bytes: the wavefronts' slabs, then (EPI 1) their rows' sums and words
+    constexpr int kSums = WN * kPairRows * 3 * 8, kWords = WN * kPairRows * 4;
+    static_assert(kSlabs + kSums + kWords <= 3 * BUF * 2, "the epilogue's share must fit the operand buffers");
     __shared__ __align__(16) unsigned short smem[3 * BUF];
     __shared__ __align__(16) int s_back[kPairRows];
+    __shared__ __align__(16) int s_reach[NT / 16], s_small[NT / 16];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -910,20 +943,44 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
     const int rows = (int)(n - m0 < kPairRows ? n - m0 : kPairRows);
     int aoff[AP], aw[AP];
     float scale[AP];
+    int reach = -kUnlike;                                // the least of the tile's rows, as far as this thread knows
 #pragma unroll
     for (int i = 0; i < AP; ++i) {
         const int r = (tid + NT * i) >> 2, p = tid & 3, rr = r < rows ? r : rows - 1;
-        float m = 0.f;
-        for (int t0 = p; t0 < max_tiles; t0 += 16)               // (the four threads of a row share its tiles)
+        // the four threads of a row share its tiles; sixteen of them and less are read once
+        const uint32_t* const words = row_range + m0 + rr;
+        uint32_t word[4];
+        int top = 0, near = 0;
+        auto load = [&](int t0) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) m = fmaxf(m, row_max[(int64_t)(t0 + 4 * u < max_tiles ? t0 + 4 * u : t0) * n + m0 + rr]);
-        m = fmaxf(m, __shfl_xor(m, 1, 64));
-        m = fmaxf(m, __shfl_xor(m, 2, 64));
-        const int back = pair_exponent(m);
+            for (int u = 0; u < 4; ++u) word[u] = t0 + 4 * u < range_tiles ? words[(int64_t)(t0 + 4 * u) * n] : 0u;
+        };
+        for (int t0 = p; t0 < range_tiles + p; t0 += 16) {
+            load(t0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) top = max(top, (int)range_exponent(word[u]));
+        }
+        top = over_lanes<4>(top, [](int a, int b) { return max(a, b); });
+        for (int t0 = p; t0 < range_tiles + p; t0 += 16) {
+            if (range_tiles > 16) load(t0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) near += range_share(word[u], (uint32_t)top, kTileBinades, 16);
+        }
+        near = over_lanes<4>(near, [](int a, int b) { return a + b; });
+        if (top != 0) reach = min(reach, top < 15 || top == 255 ? kUnlike + 1 : near);
+        const int back = max(top, 15) - 141;
         scale[i] = pair_scale(back);
         if (p == 0) s_back[r] = back;
         aoff[i] = rr * K + 8 * p;
         aw[i] = (r >> 5) * kPairSub + (p >> 1) * 1024 + ((p & 1) * 32 + ((r & 31) ^ (p << 2))) * 8;
+    }
+    int small = ctile * kPairCols + tid < C ? columns[C + ctile * kPairCols + tid] : kUnlike;        // the most of the tile's columns
+    static_assert(NT == kPairCols, "a thread per column");
+    reach = over_lanes<16>(reach, [](int a, int b) { return min(a, b); });
+    small = over_lanes<16>(small, [](int a, int b) { return max(a, b); });
+    if ((lane & 15) == 0) {
+        s_reach[tid >> 4] = reach;
+        s_small[tid >> 4] = small;
     }
     const int nsub = (C + 31) / 32;
     const half8* Bw[kPairTN];
@@ -1021,6 +1078,86 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
     };
     using yes = std::true_type;
     using no = std::false_type;
+    // The tile from bf16 triples: two buffers of A, one barrier per step, B straight from the matrix.  (Nobody reads the pairs that the
+    // buffers hold.)
+    auto triples = [&] {
+        int boff[kPairTN];
+#pragma unroll
+        for (int j = 0; j < kPairTN; ++j) boff[j] = 8 * lk * C + (c0 + 32 * j + li < C ? c0 + 32 * j + li : C - 1);
+        auto stash3 = [&](unsigned short* D, int i) {
+            const int r = (tid + NT * i) >> 2, p = tid & 3;
+            float x[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = ra[i][e >> 2][e & 3];
+            stash_split<8>(D, 512, (r >> 5) * kTripleSub + (p >> 1) * 1536 + ((p & 1) * 32 + ((r & 31) ^ (p << 2))) * 8, x);
+        };
+        float rb[kPairTN][8];
+        auto fetch_b = [&](int half) {
+            const float* const p = B + (int64_t)half * 16 * C;
+            if (half * 16 + 16 <= K) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int j = 0; j < kPairTN; ++j) rb[j][e] = (p + (int64_t)e * C)[boff[j]];
+            } else {                                     // past K: the last row again, A is zero there
+                const int left = K - half * 16 - 8 * lk;
+                for (int e = 0; e < 8; ++e)
+#pragma unroll
+                    for (int j = 0; j < kPairTN; ++j) rb[j][e] = p[boff[j] + (int64_t)(e < left ? e : left - 1) * C];
+            }
+        };
+        if (tid < kPairRows) s_back[tid] = 0;
+#pragma unroll
+        for (int i = 0; i < AP; ++i) fetch(0, i);
+#pragma unroll
+        for (int i = 0; i < AP; ++i) stash3(smem, i);
+        if (steps > 1)
+#pragma unroll
+            for (int i = 0; i < AP; ++i) fetch(1, i);
+#pragma unroll 1
+        for (int kt = 0; kt < steps; ++kt) {
+            const unsigned short* const S = smem + (kt & 1) * kPairTM * kTripleSub;
+            unsigned short* const D = smem + (~kt & 1) * kPairTM * kTripleSub;
+            __syncthreads();
+            if (kt + 1 < steps) {
+#pragma unroll
+                for (int i = 0; i < AP; ++i) stash3(D, i);
+                if (kt + 2 < steps)
+#pragma unroll
+                    for (int i = 0; i < AP; ++i) fetch(kt + 2, i);
+            }
+#pragma unroll 1
+            for (int kc = 0; kc < 2; ++kc) {
+                fetch_b(2 * kt + kc);
+                intx4 b[kPairTN][3];
+#pragma unroll
+                for (int j = 0; j < kPairTN; ++j)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        unsigned h, m, l;
+                        split3_pair(rb[j][2 * e], rb[j][2 * e + 1], h, m, l);
+                        b[j][0][e] = (int)h;
+                        b[j][1][e] = (int)m;
+                        b[j][2][e] = (int)l;
+                    }
+#pragma unroll
+                for (int i = 0; i < kPairTM; ++i) {
+                    const unsigned short* const p = S + i * kTripleSub + kc * 1536 + (lk * 32 + (li ^ ((2 * kc + lk) << 2))) * 8;
+                    bf16x8 a3[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) a3[q] = *reinterpret_cast<const bf16x8*>(p + 512 * q);
+                    constexpr int P[6] = {2, 0, 1, 1, 0, 0}, Q[6] = {0, 2, 1, 0, 1, 0};          // smallest terms first
+#pragma unroll
+                    for (int t = 0; t < 6; ++t)
+#pragma unroll
+                        for (int j = 0; j < kPairTN; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3[P[t]], __builtin_bit_cast(bf16x8, b[j][Q[t]]), acc[i][j], 0, 0, 0);
+                }
+            }
+        }
+    };
+    bool on_pairs = true;
+    static_assert(2 * kPairTM * kTripleSub <= 3 * BUF, "two buffers of triples in the three of pairs");
     if (steps > 0) {
         load_b(0);
 #pragma unroll
@@ -1033,21 +1170,28 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
                 for (int i = 0; i < AP; ++i) stash(smem + p * BUF, i);
         }
         __syncthreads();
-        load_a(0, S0, 0, 0);
-        int kt = 0;
-        for (; kt + 3 < steps; ++kt) step(kt, yes{}, yes{});
-        if (kt + 2 < steps) step(kt++, yes{}, no{});
-        for (; kt < steps; ++kt) step(kt, no{}, no{});
+        static_assert(NT == 256, "a lane per sixteen threads");
+        on_pairs = __builtin_amdgcn_readfirstlane(over_lanes<16>(s_reach[lane & 15], [](int a, int b) { return min(a, b); }) >=
+                                                  over_lanes<16>(s_small[lane & 15], [](int a, int b) { return max(a, b); }));
+        if (on_pairs) {
+            load_a(0, S0, 0, 0);
+            int kt = 0;
+            for (; kt + 3 < steps; ++kt) step(kt, yes{}, yes{});
+            if (kt + 2 < steps) step(kt++, yes{}, no{});
+            for (; kt < steps; ++kt) step(kt, no{}, no{});
+        } else {
+            triples();
+        }
     }
     __syncthreads();                                     // every wavefront is through with the operands
     float* const Cs = reinterpret_cast<float*>(smem) + wave * 32 * kPairLd;
     double* const s_sums = reinterpret_cast<double*>(reinterpret_cast<char*>(smem) + kSlabs);
-    float* const s_maxima = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + kSlabs + kSums);
+    uint32_t* const s_words = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(smem) + kSlabs + kSums);
     // (epilogue 1 has no partials: the argument then carries the row sums)
     double* const row_sums = EPI == 1 ? partials : nullptr;
     int cb[kPairTN];
 #pragma unroll
-    for (int j = 0; j < kPairTN; ++j) cb[j] = col_back[c0 + 32 * j + li < C ? c0 + 32 * j + li : C - 1];
+    for (int j = 0; j < kPairTN; ++j) cb[j] = on_pairs ? columns[c0 + 32 * j + li < C ? c0 + 32 * j + li : C - 1] : 0;
     EpilogueArgs args{out, Zl, (EPI == 2 || EPI == 4) ? Tio : Tl, nu, Tio, 0.0, false, false};
     double dsum = 0.0;
     if constexpr (EPI == 2 || EPI == 4) {
@@ -1056,12 +1200,12 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
         args.take = unit->spec != 0 && !unit->skip;
     }
     double* const s_rs = EPI == 1 && row_sums ? s_sums + wave * kPairRows * 3 : nullptr;
-    float* const s_rm = EPI == 1 && out_max ? s_maxima + wave * kPairRows : nullptr;
+    uint32_t* const s_rm = EPI == 1 && out_range ? s_words + wave * kPairRows : nullptr;
     if (C % 4 == 0) pair_epilogue<EPI, kFull>(acc, Cs, s_back, cb, m0, c0, n, C, args, dsum, s_rs, s_rm);
     else pair_epilogue<EPI, kTail>(acc, Cs, s_back, cb, m0, c0, n, C, args, dsum, s_rs, s_rm);
     if constexpr (EPI == 3) note_bad(dsum, reinterpret_cast<int32_t*>(partials));
     if constexpr (EPI == 1) {
-        if (row_sums || out_max) {
+        if (row_sums || out_range) {
             __syncthreads();
             for (int r = tid; r < kPairRows; r += NT) {
                 const int64_t row = m0 + r;
@@ -1076,11 +1220,14 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
                         row_sums[o * 3 + q] = s;
                     }
                 }
-                if (out_max) {
-                    float m = 0.f;
+                if (out_range) {
+                    uint32_t top = 0;
+                    int near = 0;
 #pragma unroll
-                    for (int w = 0; w < WN; ++w) m = fmaxf(m, s_maxima[w * kPairRows + r]);
-                    out_max[o] = m;
+                    for (int w = 0; w < WN; ++w) top = max(top, range_exponent(s_words[w * kPairRows + r]));
+#pragma unroll
+                    for (int w = 0; w < WN; ++w) near += range_share(s_words[w * kPairRows + r], top, kSlabBinades, 4);
+                    out_range[o] = top ? range_word(top, near) : 0u;
                 }
             }
         }
@@ -1885,16 +2032,16 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
     const dim3 block(256);
     if (epi.pair.planes && gemm_nn_pair(n, K, C)) {
         const PairOperands& p = epi.pair;
-        if (!p.ready) hipLaunchKernelGGL(pair_weights_kernel, dim3((unsigned)((C + 31) / 32)), dim3(1024), 0, s, B, K, C, p.planes, p.col_back, epi.gate);
+        if (!p.ready) hipLaunchKernelGGL(pair_weights_kernel, dim3((unsigned)((C + 31) / 32)), dim3(1024), 0, s, B, K, C, p.planes, p.columns, epi.gate);
         const dim3 grid((unsigned)gemm_nn_blocks(n, C, true));
 #define CADMM_PAIR(E_, Tl_, unit_, partials_, out_max_, gate_) \
-        hipLaunchKernelGGL(gemm_nn_pair_kernel<E_>, grid, dim3(64 * kPairWaves), 0, s, A, p.planes, p.col_back, p.row_max, p.max_tiles, out, \
+        hipLaunchKernelGGL(gemm_nn_pair_kernel<E_>, grid, dim3(64 * kPairWaves), 0, s, A, B, p.planes, p.columns, p.row_range, p.range_tiles, out, \
                            n, K, C, epi.Zl, Tl_, epi.nu, epi.Tio, unit_, partials_, out_max_, gate_)
         double* const bad = reinterpret_cast<double*>(epi.bad);
         if (epi.kind == 3) CADMM_PAIR(3, nullptr, nullptr, bad, nullptr, nullptr);
         else if (epi.kind == 2 && epi.leave_g) CADMM_PAIR(4, nullptr, epi.unit, epi.partials, nullptr, epi.gate);
         else if (epi.kind == 2) CADMM_PAIR(2, nullptr, epi.unit, epi.partials, nullptr, epi.gate);
-        else if (epi.kind == 1) CADMM_PAIR(1, epi.Tl, nullptr, epi.row_sums, epi.out_max, epi.gate);
+        else if (epi.kind == 1) CADMM_PAIR(1, epi.Tl, nullptr, epi.row_sums, epi.out_range, epi.gate);
         else CADMM_PAIR(0, nullptr, epi.unit, nullptr, nullptr, epi.gate);
 #undef CADMM_PAIR
         return;

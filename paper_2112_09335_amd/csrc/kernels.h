@@ -7,6 +7,44 @@
 
 namespace cadmm {
 
+// A word of RowRange: the exponent field of the largest magnitude m of some entries, and the number of those that are near it, that
+// is at least 2^-binades of the power of two in m, less a sixteenth of the number that are not zero (rounded up).  0: all are zero.
+constexpr int kRangeBias = 1 << 20;
+__device__ __forceinline__ uint32_t range_exponent(uint32_t word) { return word >> 23; }
+__device__ __forceinline__ int range_reach(uint32_t word) { return (int)(word & 0x7fffffu) - kRangeBias; }
+__device__ __forceinline__ uint32_t range_word(uint32_t exponent, int reach) { return exponent << 23 | (uint32_t)(reach + kRangeBias); }
+__device__ __forceinline__ uint32_t magnitude_exponent(float m) { return __float_as_uint(m) >> 23 & 255; }
+// From where on an entry counts as near (m: no negative number).
+__device__ __forceinline__ float range_near(float m, int binades) {
+    const int e = (int)magnitude_exponent(m) - binades;
+    return __uint_as_float((uint32_t)(e > 0 ? e : 1) << 23);
+}
+// counts: near entries, and 2^16 times those that are not zero
+__device__ __forceinline__ uint32_t range_word_of(float m, int counts) {
+    return m > 0.f ? range_word(magnitude_exponent(m), (counts & 0xffff) - ((counts >> 16) + 15) / 16) : 0u;
+}
+// The value of a neighbour that has not been seen yet when steps 1, 2, 4 and 8 follow each other, in 2, 4, 8 and 16 lanes: within a
+// quad by exchange, then from the mirrored place of the other quad or half (any lane of it will do).  Vector instructions, where a
+// shuffle is an access to LDS.
+template <int STEP>
+__device__ __forceinline__ int neighbour(int v) {
+    constexpr int ctrl = STEP == 1 ? 0xB1 : STEP == 2 ? 0x4E : STEP == 4 ? 0x141 : 0x140;
+    return __builtin_amdgcn_update_dpp(v, v, ctrl, 0xf, 0xf, false);
+}
+template <int LANES, class F>
+__device__ __forceinline__ int over_lanes(int v, F f) {              // f over 2 .. 16 neighbouring lanes; every one of them gets it
+    v = f(v, neighbour<1>(v));
+    if constexpr (LANES > 2) v = f(v, neighbour<2>(v));
+    if constexpr (LANES > 4) v = f(v, neighbour<4>(v));
+    if constexpr (LANES > 8) v = f(v, neighbour<8>(v));
+    return v;
+}
+// What a part adds to the whole: entries that are near the largest of a part whose exponent is up to `binades` below the whole's
+// stay near enough; of any other part (of at most 16 * few entries) none counts.
+__device__ __forceinline__ int range_share(uint32_t word, uint32_t exponent, int binades, int few) {
+    return word == 0 ? 0 : range_exponent(word) + binades >= exponent ? range_reach(word) : -few;
+}
+
 // ---------------------------------------------------------------- sparse aggregation (spmm.hip)
 // Y[r,:] = sum_{p in [lo[r], hi[r])} val[p] * X[col[p],:]   for r < nrows.
 // epilogue 0: store;  1: Y = nu * (Zl - relu(Tl)) + sum  (gradient of the Z subproblem).
@@ -14,8 +52,9 @@ namespace cadmm {
 // sums over the tile's columns that the search for theta needs of the gradient g just formed: sum e g with
 // e = Zl - relu(Tl), sum g^2, sum Zl^2 (three doubles at row_sums + (tile * rows + row) * 3), so that the search does not
 // have to read the three N x C_l matrices again.
-// RowMax: with row_max (widths of four and more) the launch leaves, per column tile and row, the largest magnitude of the
-// result (one float at row_max + tile * rows + row), which a product that takes the result as its left operand scales by.
+// RowRange: with row_range (widths of four and more) the launch leaves, per column tile and row, a word (at row_range + tile *
+// rows + row) that says how large the largest entries of the result are and how many come near them, for a product that takes the
+// result as its left operand (gemm_nn_pair_kernel): see range_word.
 // gate (epilogue 0; may be null): the launch does nothing where *gate is 0, see ZTrialArgs.
 struct SpmmEpilogue {
     int kind = 0;
@@ -24,7 +63,7 @@ struct SpmmEpilogue {
     const float* Tl = nullptr;
     float nu = 0.f;
     double* row_sums = nullptr;
-    float* row_max = nullptr;
+    uint32_t* row_range = nullptr;
 };
 // Device view of a row list laid out for the aggregation (RowSchedule on the host).  rec[i] = (first chunk, one past
 // the last chunk, output row, 0) of scheduled row i; a chunk is 8 (column, value) pairs of 8 bytes, padded with
@@ -80,13 +119,13 @@ struct Unit;
 // Where the search takes no step at all (unit->skip) nothing reads Q: the product is not formed, out gets G with leave_g.
 // epilogue 3 (forward pass): Tio = relu(A B), and out = A B unless out is null; a pass over the pre-activations of its own
 // would read them once more (200000 x 256: 76 us).
-// What a product needs to run on pairs of fp16 (gemm_nn_pair): RowMax of A, and scratch for B in operand layout; ready: the
+// What a product needs to run on pairs of fp16 (gemm_nn_pair): RowRange of A, and scratch for B in operand layout; ready: the
 // scratch holds it already.
 struct PairOperands {
-    const float* row_max = nullptr;
-    int max_tiles = 0;
+    const uint32_t* row_range = nullptr;
+    int range_tiles = 0;
     unsigned short* planes = nullptr;    // gemm_nn_pair_planes(K, C) of them
-    int* col_back = nullptr;             // C
+    int* columns = nullptr;              // 2 C
     bool ready = false;
 };
 struct GemmEpilogue {
@@ -104,7 +143,7 @@ struct GemmEpilogue {
     double* partials = nullptr;
     int32_t* bad = nullptr;        // epilogue 3: set to 1 if a result is not finite, where gemm_nn_notes_bad
     double* row_sums = nullptr;    // epilogue 1, C > 32: RowSums per tile of gemm_nn_tiles(n, C, pair) column tiles
-    float* out_max = nullptr;      // epilogue 1 on pairs: RowMax of the result, per tile as row_sums
+    uint32_t* out_range = nullptr;      // epilogue 1 on pairs: RowRange of the result, per tile as row_sums
 };
 // Whether a product with PairOperands runs on them: by form (for what is laid out), by form and size.
 bool gemm_nn_pair_form(int K, int C);

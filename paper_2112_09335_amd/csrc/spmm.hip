@@ -74,13 +74,35 @@ __device__ __forceinline__ void reduce_row_sums(double (&s)[3], int lpr_log2) {
         for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], o, 64);
 }
 
-// Largest magnitude of a result row (RowMax): this lane's quad, over 2^lpr_log2 neighbouring lanes; every one of them gets it.
+// Largest magnitude of a result row: this lane's quad, over 2^lpr_log2 neighbouring lanes; every one of them gets it.
 __device__ __forceinline__ float quad_max(const float (&v)[4]) {
     return fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
 }
+template <class F>
+__device__ __forceinline__ int reduce_row(int v, int lpr_log2, F f) {
+    if (lpr_log2 < 3) {
+        for (int o = 1; o < (1 << lpr_log2); o <<= 1) v = f(v, __shfl_xor(v, o, 64));
+        return v;
+    }
+    v = over_lanes<8>(v, f);
+    for (int o = 8; o < (1 << lpr_log2); o <<= 1) v = f(v, __shfl_xor(v, o, 64));
+    return v;
+}
+// (the bits of numbers that are not negative are in the order of the numbers)
 __device__ __forceinline__ float reduce_row_max(float m, int lpr_log2) {
-    for (int o = 1; o < (1 << lpr_log2); o <<= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
-    return m;
+    return __int_as_float(reduce_row(__float_as_int(m), lpr_log2, [](int a, int b) { return a > b ? a : b; }));
+}
+// RowRange (range_word_of): this lane's quad from entry `skip` on, against the row's largest magnitude m.
+constexpr int kNearBinades = 4;
+__device__ __forceinline__ int quad_counts(const float (&v)[4], float m, int skip) {
+    const float t = range_near(m, kNearBinades);
+    int n = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n += e < skip ? 0 : (fabsf(v[e]) >= t ? 1 : 0) + (v[e] != 0.f ? 1 << 16 : 0);
+    return n;
+}
+__device__ __forceinline__ int reduce_row_counts(int n, int lpr_log2) {
+    return reduce_row(n, lpr_log2, [](int a, int b) { return a + b; });
 }
 
 // Slice k of the workgroup table (the workgroups of XCD k) is [start[k], start[k+1]).
@@ -144,12 +166,13 @@ __device__ __forceinline__ void load_chunk(const int2* __restrict__ ent, int64_t
 // of six (they are asked for where a row takes eight lanes and more: 63 registers, not 71).  Over the rows, us before and
 // after: 200000 x 256 249 and 233, x 128 120 and 109, x 33 69 and 60; 500000 x 512 1398 and 1268; 2M power law x 128 2715 and
 // 2465, x 16 456 and 446.
-template <int VEC, int EPI, int LPRL, int OFF32>
+// RANGE: leaves RowRange (a template parameter: its registers cost the other launches 3 %).
+template <int VEC, int EPI, int LPRL, int OFF32, int RANGE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EPI == 0 && LPRL == 3 ? 8 : 1, 8))) void spmm_rows_kernel(
     const int4* __restrict__ rec, int64_t nrows, const int2* __restrict__ ent, const float* __restrict__ X,
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
     XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu,
-    double* __restrict__ row_sums, float* __restrict__ row_max, int64_t n_out, const int32_t* __restrict__ gate) {
+    double* __restrict__ row_sums, uint32_t* __restrict__ row_range, int64_t n_out, const int32_t* __restrict__ gate) {
     if (EPI == 0 && gate && *gate == 0) return;
     // Workgroup b belongs to XCD b mod 8 and takes the (b / 8)-th entry of that XCD's slice of the table (or, without
     // the XCD-aware numbering, simply entry b).  Records from nrows on are the parts of split rows.
@@ -239,10 +262,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EP
             }
         }
     }
-    if constexpr (VEC == 4) {
-        if (row_max && !is_part) {                       // (every lane of the row's first group; off lanes hold its last columns)
+    if constexpr (RANGE) {
+        if (!is_part) {                                   // (every lane of the row's first group; off lanes hold its last columns)
             const float m = reduce_row_max(quad_max(acc), lpr_log2);
-            if (sub == 0) row_max[(int64_t)blockIdx.y * n_out + r.z] = m;
+            const int n = reduce_row_counts(quad_counts(acc, m, on ? col0 + sub * 4 - cc : 4), lpr_log2);
+            if (sub == 0) row_range[(int64_t)blockIdx.y * n_out + r.z] = range_word_of(m, n);
         }
     }
     if (!on) return;
@@ -338,7 +362,7 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
                                                           float* __restrict__ Y, int width,
                                                           const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                           float nu, int lpr_log2, double* __restrict__ row_sums,
-                                                          float* __restrict__ row_max, int n_tiles, int64_t n_out, const int32_t* __restrict__ gate) {
+                                                          uint32_t* __restrict__ row_range, int n_tiles, int64_t n_out, const int32_t* __restrict__ gate) {
     const int64_t i = blockIdx.x;
     if (i >= n_long || (EPI == 0 && gate && *gate == 0)) return;
     const int64_t row = long_row[i];
@@ -379,9 +403,17 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
         store_vec<VEC>(Y + o, acc);
     }
     if constexpr (VEC == 4) {
-        if (row_max && grp == 0) {                              // likewise for the largest magnitude
+        if (row_range && grp == 0) {                            // the whole row's in the first tile's place
             most = reduce_row_max(most, lpr_log2);
-            for (int tile = sub; tile < n_tiles; tile += lpr) row_max[(int64_t)tile * n_out + row] = tile == 0 ? most : 0.f;
+            int n = 0;
+            for (int cb = 0; cb + sub * VEC < width; cb += lpr * VEC) {              // (each lane reads what it has stored)
+                const int c = cb + sub * VEC + VEC <= width ? cb + sub * VEC : width - VEC;
+                float v[4];
+                load_vec<VEC>(v, Y + row * (int64_t)width + c);
+                n += quad_counts(v, most, cb + sub * VEC - c);
+            }
+            n = reduce_row_counts(n, lpr_log2);
+            for (int tile = sub; tile < n_tiles; tile += lpr) row_range[(int64_t)tile * n_out + row] = tile == 0 ? range_word_of(most, n) : 0u;
         }
     }
     if constexpr (EPI == 1 && VEC == 4) {
@@ -441,17 +473,19 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         const dim3 grid((unsigned)nb, (unsigned)((width + tile - 1) / tile)), block(256);
         const bool off32 = sc.n_cols <= (1 << 24) && 4 * sc.n_cols * (int64_t)width <= ((int64_t)1 << 32);
 #define CADMM_ROWS(L_) do { if (off32) CADMM_ROWS_OFF(L_, 1); else CADMM_ROWS_OFF(L_, 0); } while (0)
-#define CADMM_ROWS_OFF(L_, O_) do { \
-        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
-                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, epi.row_max, sc.n_out, nullptr); \
-        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_, O_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
-                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, epi.row_max, sc.n_out, epi.gate); } while (0)
+#define CADMM_ROWS_OFF(L_, O_) do { if (VEC == 4 && epi.row_range) CADMM_ROWS_EPI(L_, O_, (VEC == 4)); else CADMM_ROWS_EPI(L_, O_, 0); } while (0)
+#define CADMM_ROWS_EPI(L_, O_, R_) do { \
+        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_, O_, R_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
+                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, epi.row_range, sc.n_out, nullptr); \
+        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_, O_, R_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
+                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, epi.row_range, sc.n_out, epi.gate); } while (0)
         if (lpr_log2 == 0) CADMM_ROWS(0);
         else if (lpr_log2 == 1) CADMM_ROWS(1);
         else if (lpr_log2 == 2) CADMM_ROWS(2);
         else CADMM_ROWS(3);
 #undef CADMM_ROWS
 #undef CADMM_ROWS_OFF
+#undef CADMM_ROWS_EPI
     }
     if (sc.n_long > 0) {
         const dim3 grid((unsigned)sc.n_long), block(64);
@@ -460,10 +494,10 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         if (epi.kind == 1)
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
                                sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2, epi.row_sums,
-                               epi.row_max, (width + tile - 1) / tile, sc.n_out, nullptr);
+                               epi.row_range, (width + tile - 1) / tile, sc.n_out, nullptr);
         else
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
-                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, epi.row_max, (width + tile - 1) / tile, sc.n_out, epi.gate);
+                               sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, epi.row_range, (width + tile - 1) / tile, sc.n_out, epi.gate);
     }
 }
 

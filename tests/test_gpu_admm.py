@@ -596,15 +596,10 @@ def test_products_on_pairs_inside_the_sweep(pairs_everywhere, dims, more, hubs):
     run_case(w, 4, "pairs/" + "-".join(map(str, dims)))
 
 
-@pytest.mark.parametrize("N,K,C", [(1, 64, 129), (127, 65, 130), (128, 95, 192), (129, 96, 193), (1000, 97, 255), (300, 512, 256),
-                                   (257, 129, 257), (640, 1000, 513)])
-def test_product_on_pairs_of_scaled_rows_and_columns(pairs_everywhere, N, K, C):
-    """Without edges A~ is the identity and the forward pass leaves relu(X W_1): rows of X and columns of W_1 from 1e-12 to 1e12
-    (and zero rows) keep the accuracy of a 32-bit product, since each has a scale of its own."""
+def first_layer(X, W1):
+    """relu(X W_1): without edges A~ is the identity, and this is what the forward pass leaves as Z_1."""
     from paper_2112_09335_amd import binding
-    rng = np.random.default_rng(N + K + C)
-    X = rng.standard_normal((N, K)) * 10.0 ** rng.integers(-12, 13, (N, 1)) * (rng.random((N, 1)) < 0.95)
-    X, W1 = X.astype(np.float32), (rng.standard_normal((K, C)) * 10.0 ** rng.integers(-12, 13, (1, C))).astype(np.float32)
+    N, (K, C) = X.shape[0], W1.shape
     s = binding.Solver(0)
     s.build_graph(N, np.zeros(0, np.int32), np.zeros(0, np.int32), 1, np.zeros(N, np.int32))
     s.set_model([K, C, 3], **synth.DEFAULT_HYPER)
@@ -613,9 +608,86 @@ def test_product_on_pairs_of_scaled_rows_and_columns(pairs_everywhere, N, K, C):
     s.init([W1, np.ones((C, 3), np.float32)])
     got = s.get_Z(1)
     s.close()
+    return got
+
+
+@pytest.mark.parametrize("N,K,C", [(1, 64, 129), (127, 65, 130), (128, 95, 192), (129, 96, 193), (1000, 97, 255), (300, 512, 256),
+                                   (257, 129, 257), (640, 1000, 513)])
+def test_product_on_pairs_of_scaled_rows_and_columns(pairs_everywhere, N, K, C):
+    """Rows of X and columns of W_1 from 1e-12 to 1e12 (and zero rows) keep the accuracy of a 32-bit product, since each has a scale
+    of its own."""
+    rng = np.random.default_rng(N + K + C)
+    X = rng.standard_normal((N, K)) * 10.0 ** rng.integers(-12, 13, (N, 1)) * (rng.random((N, 1)) < 0.95)
+    X, W1 = X.astype(np.float32), (rng.standard_normal((K, C)) * 10.0 ** rng.integers(-12, 13, (1, C))).astype(np.float32)
+    got = first_layer(X, W1)
     exact, mag = X.astype(np.float64) @ W1.astype(np.float64), np.abs(X).astype(np.float64) @ np.abs(W1).astype(np.float64)
     # (the tolerance of the other split products: a few roundings of 32-bit sums)
     assert np.all(np.abs(got - np.maximum(exact, 0.0)) <= 2e-6 * mag)
+
+
+@pytest.mark.parametrize("N,K,C", [(128, 95, 192), (300, 512, 256), (257, 129, 257), (640, 1000, 513)])
+@pytest.mark.parametrize("kind", ["even", "outlier", "opposed", "one-hot", "tiny columns", "few", "one row", "one column"])
+def test_product_on_pairs_of_unlike_columns_and_rows(pairs_everywhere, kind, N, K, C):
+    """Where the largest entries of a row meet zeros of a column, or small ones (a feature 1e8 times the others that has no weight,
+    features as much larger as their weights are smaller, weights that pick one feature), parts of a row's largest entry are not
+    parts of what a result is made of.  Such tiles of 128 x 256 results come from operands in all 24 bits, to the bit as below the sizes
+    from which products run on pairs; the others stay on pairs."""
+    rng = np.random.default_rng(N + K + C)
+    X, W1 = rng.standard_normal((N, K)), rng.standard_normal((K, C))
+    rows, cols = slice(0, N), slice(0, C)                # of the results that are not for pairs
+    if kind == "even":
+        rows = slice(0, 0)
+    elif kind == "outlier":
+        X[:, 3] *= 1e8
+        W1[3] = 0.0
+    elif kind == "opposed":
+        size = np.exp(4.0 * rng.standard_normal(K))
+        X, W1 = X * size, W1 / size[:, None]
+    elif kind == "one-hot":
+        X *= 10.0 ** rng.integers(-9, 4, K)
+        W1 = np.where(np.arange(K)[:, None] == np.arange(C) % K, W1, 0.0)
+    elif kind == "tiny columns":                         # a few features far below the rest, and weights that ask for nothing else
+        X[:, 7:12] *= 1e-13
+        W1 = np.where((np.arange(K) >= 7)[:, None] & (np.arange(K) < 12)[:, None], W1, 0.0)
+    elif kind == "few":                                  # three entries in a row, weights of all sizes
+        X[rng.random((N, K)) > 3.0 / K] = 0.0
+        W1 *= np.exp(4.0 * rng.standard_normal((K, C)))
+    elif kind == "one row":                              # of the last tile
+        X[N - 1, 5] = 1e9
+        rows = slice((N - 1) // 128 * 128, N)
+    elif kind == "one column":
+        W1[5, 0] = 1e9
+        cols = slice(0, min(C, 256))
+    X, W1 = X.astype(np.float32), W1.astype(np.float32)
+    from paper_2112_09335_amd import binding
+    got = first_layer(X, W1)
+    probe = binding.Solver(device=-1)
+    probe.tune("gemm_split", 1)                          # (process-wide; pairs_everywhere sets it back)
+    probe.close()
+    triples = first_layer(X, W1)
+    exact, mag = X.astype(np.float64) @ W1.astype(np.float64), np.abs(X).astype(np.float64) @ np.abs(W1).astype(np.float64)
+    assert np.all(np.abs(got - np.maximum(exact, 0.0)) <= 2e-6 * mag)
+    assert np.array_equal(got[rows, cols], triples[rows, cols])
+    on_pairs = np.ones((N, C), bool)
+    on_pairs[rows, cols] = False
+    assert not on_pairs.any() or (got != triples)[on_pairs].mean() > 0.1
+
+
+@pytest.mark.parametrize("more,hubs", [({}, 0), ({"schedule": 1}, 2), ({"dual_form": 1}, 0)])
+def test_tiles_that_are_not_for_pairs_inside_the_sweep(pairs_everywhere, more, hubs):
+    """A feature far larger than the others with weights as much smaller, weights whose rows differ by powers of ten, and as they are in
+    some of the layers: both ways of forming a tile in every product of the sweep."""
+    w = synth.make_workload("unlike", 41, 1501, 5, [96, 256, 200, 256, 10], 10, 4, graph="sbm", features="gaussian", avg_degree=9,
+                            frac_intra=0.8, labelled_fraction=0.7)
+    if hubs:
+        w = synth.add_hubs(w, 5, hubs, 700, 0.5)
+    w.X, w.W0 = w.X.copy(), [W.copy() for W in w.W0]
+    w.X[:, 0] *= 256.0
+    w.W0[0][0] /= 256.0
+    w.W0[1] *= np.float32(2.0) ** -np.random.default_rng(5).integers(0, 40, (256, 1)).astype(np.float32)
+    w.W0[1] *= 4.0
+    w.hyper.update(more)
+    run_case(w, 4, "pairs/unlike/" + ("+".join(more) or "default"))
 
 
 def test_hub_rows_and_hub_segments_are_split_inside_the_sweep():
