@@ -827,10 +827,12 @@ void z_update_hidden(cadmm_ctx* c, int l) {
     const int32_t* const run = c->rest && how.gate ? c->run_z + l : nullptr;
     const Unless resting{note_flag(c, run), 0, P_OTHER, 0.0};
     if (lowrank) {
-        aggregate(c, c->G[l + 1], c->tmpA, Cn, SpmmEpilogue());                  // A~ G_{l+1}
+        SpmmEpilogue epi;
+        epi.gate = run;
+        aggregate(c, c->G[l + 1], c->tmpA, Cn, epi, resting);                    // A~ G_{l+1}
         timed(c, P_GEMM_GRADZ, 4.0 * (2.0 * (double)N * Cl + 2.0 * (double)N * Cn), 2.0 * (double)N * Cl * Cn, [&] {
-            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, Wt, c->tmpV, N, Cl, Cn, c->nu, row_sums);
-        });
+            launch_gemm_nn_gradz(s, c->Z[l], c->T[l], c->tmpA, Wt, c->tmpV, N, Cl, Cn, c->nu, row_sums, run);
+        }, resting);
     } else if (path == kGradProduct) {
         const bool on_pairs = grad_on_pairs(c, l);
         SpmmEpilogue epi;
@@ -851,8 +853,9 @@ void z_update_hidden(cadmm_ctx* c, int l) {
         gemm_nn(c, c->G[l + 1], Wt, c->tmpA, N, Cn, Cl, ge, resting);            // G_{l+1} W_{l+1}^T
         SpmmEpilogue epi;
         epi.kind = 1; epi.Zl = c->Z[l]; epi.Tl = c->T[l]; epi.nu = c->nu; epi.row_sums = row_sums;
+        epi.gate = run;
         if (want_range && row_tiles(c, Cl) <= c->b_range_room) { epi.row_range = c->b_range; range_tiles = row_tiles(c, Cl); }
-        aggregate(c, c->tmpA, c->tmpB, Cl, epi);
+        aggregate(c, c->tmpA, c->tmpB, Cl, epi, resting);
     }
     ZTrialArgs a;
     const cadmm_ctx::DevChunks& ct = c->d_chunks[l];

@@ -1256,10 +1256,15 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
 // rows in LDS (five spilled registers), 833 so, 5.2 TB/s of Z, T, SG and out; the same
 // sums to the bit.
 constexpr int kSgLd = kLowRankMax + 4;            // row stride of SG in LDS: the eight rows a wavefront reads at once hit different banks
+template <bool GATED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
                                                             const float* __restrict__ SG,
                                                             const float* __restrict__ Wt, float* __restrict__ out, int64_t n,
-                                                            int K1, int C, float nu, double* __restrict__ row_sums) {
+                                                            int K1, int C, float nu, double* __restrict__ row_sums,
+                                                            const int32_t* __restrict__ gate) {
+    if constexpr (GATED) {
+        if (*gate == 0) return;
+    }
     // 32 columns of Z_l and T_l per step: every row then gives a whole 128-byte line of each matrix to one step.
     // With half lines the second half had left the L2 before its step came (twice the traffic, measured).
     constexpr int GBK = 32;
@@ -2089,9 +2094,11 @@ void launch_gemm_nn(hipStream_t s, const float* A, const float* B, float* out, i
 }
 
 void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Wt, float* out, int64_t n,
-                          int K1, int C, float nu, double* row_sums) {
+                          int K1, int C, float nu, double* row_sums, const int32_t* gate) {
     if (n <= 0) return;
-    hipLaunchKernelGGL(gemm_nn_gradz_kernel, dim3((unsigned)((n + BM - 1) / BM)), dim3(256), 0, s, Zl, Tl, SG, Wt, out, n, K1, C, nu, row_sums);
+    const dim3 grid((unsigned)((n + BM - 1) / BM));
+    if (gate) hipLaunchKernelGGL((gemm_nn_gradz_kernel<true>), grid, dim3(256), 0, s, Zl, Tl, SG, Wt, out, n, K1, C, nu, row_sums, gate);
+    else hipLaunchKernelGGL((gemm_nn_gradz_kernel<false>), grid, dim3(256), 0, s, Zl, Tl, SG, Wt, out, n, K1, C, nu, row_sums, gate);
 }
 
 int gemm_nn_tiles(int64_t n, int C, bool pair) {

@@ -55,7 +55,7 @@ __device__ __forceinline__ int range_share(uint32_t word, uint32_t exponent, int
 // RowRange: with row_range (widths of four and more) the launch leaves, per column tile and row, a word (at row_range + tile *
 // rows + row) that says how large the largest entries of the result are and how many come near them, for a product that takes the
 // result as its left operand (gemm_nn_pair_kernel): see range_word.
-// gate (epilogue 0; may be null): the launch does nothing where *gate is 0, see ZTrialArgs.
+// gate (may be null): the launch does nothing where *gate is 0, see ZTrialArgs.
 struct SpmmEpilogue {
     int kind = 0;
     const int32_t* gate = nullptr;
@@ -170,9 +170,9 @@ void launch_stream_update(hipStream_t s, const float* src, float* dst, int64_t c
 int64_t gemm_nn_blocks(int64_t n, int C, bool pair);   // grid size of that launch (= block results of epilogue 2)
 // out[n x C] = g W with g = nu (Zl - relu(Tl)) + SG Wt, the product (grad_Z psi) W with the gradient never stored (Wt: the
 // transpose of W, K1 x C; SG: n x C; C <= kLowRankMax, K1 % 4 == 0).  The rows' RowSums (one tile) are left on the way.  The operations
-// that form an element of g and their order are those of launch_z_step_lowrank.
+// that form an element of g and their order are those of launch_z_step_lowrank.  gate (may be null): nothing is formed where *gate is 0.
 void launch_gemm_nn_gradz(hipStream_t s, const float* Zl, const float* Tl, const float* SG, const float* Wt,
-                          float* out, int64_t n, int K1, int C, float nu, double* row_sums);
+                          float* out, int64_t n, int K1, int C, float nu, double* row_sums, const int32_t* gate);
 // out[K x C] = A[n x K]^T * G[n x C]; partial: scratch of gemm_tn_scratch_floats(n,K,C) floats.
 size_t gemm_tn_scratch_floats(int64_t n, int K, int C);
 size_t gemm_tn_base_floats(int64_t n, int K, int C);            // what decides whether a caller's scratch will do ...

@@ -166,6 +166,7 @@ __device__ __forceinline__ void load_chunk(const int2* __restrict__ ent, int64_t
 // of six (they are asked for where a row takes eight lanes and more: 63 registers, not 71).  Over the rows, us before and
 // after: 200000 x 256 249 and 233, x 128 120 and 109, x 33 69 and 60; 500000 x 512 1398 and 1268; 2M power law x 128 2715 and
 // 2465, x 16 456 and 446.
+// EPI 2: epilogue 1 with a gate (an instance of its own, as the look at it keeps the other arguments from being loaded beside it).
 // RANGE: leaves RowRange (a template parameter: its registers cost the other launches 3 %).
 template <int VEC, int EPI, int LPRL, int OFF32, int RANGE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EPI == 0 && LPRL == 3 ? 8 : 1, 8))) void spmm_rows_kernel(
@@ -173,6 +174,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EP
     float* __restrict__ Y, float* __restrict__ side, int width, int lpr_log2_arg, const int4* __restrict__ blocks,
     XcdMap xm, int tile_cols, int xcd_remap, const float* __restrict__ Zl, const float* __restrict__ Tl, float nu,
     double* __restrict__ row_sums, uint32_t* __restrict__ row_range, int64_t n_out, const int32_t* __restrict__ gate) {
+    if constexpr (EPI == 2) {
+        if (*gate == 0) return;
+    }
     if (EPI == 0 && gate && *gate == 0) return;
     // Workgroup b belongs to XCD b mod 8 and takes the (b / 8)-th entry of that XCD's slice of the table (or, without
     // the XCD-aware numbering, simply entry b).  Records from nrows on are the parts of split rows.
@@ -213,7 +217,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EP
     // the epilogue's operands (rows of Z_l and T_l at the output row) are asked for before the gathers, so that their
     // latency is not added at the end of every row
     float ez[VEC], et[VEC];
-    if constexpr (EPI == 1) {
+    if constexpr (EPI >= 1) {
         if (!is_part && grp == 0) {
             const int64_t o = (int64_t)r.z * (int64_t)width + cc;
             load_vec<VEC>(ez, Zl + o);
@@ -245,7 +249,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OFF32 && EP
         for (int v = 0; v < VEC; ++v) acc[v] += __shfl_xor(acc[v], off, 64);
     }
     if (grp != 0) return;
-    if constexpr (EPI == 1) {
+    if constexpr (EPI >= 1) {
         if (!is_part) {
 #pragma unroll
             for (int v = 0; v < VEC; ++v) acc[v] = nu * (ez[v] - fmaxf(et[v], 0.f)) + acc[v];
@@ -364,7 +368,7 @@ __global__ __launch_bounds__(64) void spmm_combine_kernel(const float* __restric
                                                           float nu, int lpr_log2, double* __restrict__ row_sums,
                                                           uint32_t* __restrict__ row_range, int n_tiles, int64_t n_out, const int32_t* __restrict__ gate) {
     const int64_t i = blockIdx.x;
-    if (i >= n_long || (EPI == 0 && gate && *gate == 0)) return;
+    if (i >= n_long || (gate && *gate == 0)) return;
     const int64_t row = long_row[i];
     const int p0 = long_part_ptr[i], p1 = long_part_ptr[i + 1];
     const int lpr = 1 << lpr_log2, groups = 64 >> lpr_log2;
@@ -475,10 +479,12 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
 #define CADMM_ROWS(L_) do { if (off32) CADMM_ROWS_OFF(L_, 1); else CADMM_ROWS_OFF(L_, 0); } while (0)
 #define CADMM_ROWS_OFF(L_, O_) do { if (VEC == 4 && epi.row_range) CADMM_ROWS_EPI(L_, O_, (VEC == 4)); else CADMM_ROWS_EPI(L_, O_, 0); } while (0)
 #define CADMM_ROWS_EPI(L_, O_, R_) do { \
-        if (epi.kind == 1) hipLaunchKernelGGL((spmm_rows_kernel<VEC, 1, L_, O_, R_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, \
-                                              sc.side, width, lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, epi.row_range, sc.n_out, nullptr); \
-        else hipLaunchKernelGGL((spmm_rows_kernel<VEC, 0, L_, O_, R_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, \
-                                lpr_log2, sc.blocks[lpr_log2], xm, tile, g_xcd_remap, nullptr, nullptr, 0.f, nullptr, epi.row_range, sc.n_out, epi.gate); } while (0)
+        if (epi.kind == 1 && epi.gate) CADMM_ROWS_KERNEL(2, L_, O_, R_); \
+        else if (epi.kind == 1) CADMM_ROWS_KERNEL(1, L_, O_, R_); \
+        else CADMM_ROWS_KERNEL(0, L_, O_, R_); } while (0)
+#define CADMM_ROWS_KERNEL(E_, L_, O_, R_) \
+        hipLaunchKernelGGL((spmm_rows_kernel<VEC, E_, L_, O_, R_>), grid, block, 0, s, sc.rec, sc.n_rows, sc.ent, X, Y, sc.side, width, lpr_log2, \
+                           sc.blocks[lpr_log2], xm, tile, g_xcd_remap, epi.Zl, epi.Tl, epi.nu, epi.row_sums, epi.row_range, sc.n_out, epi.gate)
         if (lpr_log2 == 0) CADMM_ROWS(0);
         else if (lpr_log2 == 1) CADMM_ROWS(1);
         else if (lpr_log2 == 2) CADMM_ROWS(2);
@@ -486,6 +492,7 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
 #undef CADMM_ROWS
 #undef CADMM_ROWS_OFF
 #undef CADMM_ROWS_EPI
+#undef CADMM_ROWS_KERNEL
     }
     if (sc.n_long > 0) {
         const dim3 grid((unsigned)sc.n_long), block(64);
@@ -494,7 +501,7 @@ void launch_vec(hipStream_t s, const SpmmSchedule& sc, const float* X, float* Y,
         if (epi.kind == 1)
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 1>), grid, block, 0, s, sc.side, sc.long_row,
                                sc.long_part_ptr, sc.n_long, Y, width, epi.Zl, epi.Tl, epi.nu, clog2, epi.row_sums,
-                               epi.row_range, (width + tile - 1) / tile, sc.n_out, nullptr);
+                               epi.row_range, (width + tile - 1) / tile, sc.n_out, epi.gate);
         else
             hipLaunchKernelGGL((spmm_combine_kernel<VEC, 0>), grid, block, 0, s, sc.side, sc.long_row,
                                sc.long_part_ptr, sc.n_long, Y, width, nullptr, nullptr, 0.f, clog2, nullptr, epi.row_range, (width + tile - 1) / tile, sc.n_out, epi.gate);

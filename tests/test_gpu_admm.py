@@ -252,7 +252,8 @@ def test_step_floor_tested_first_gives_the_same_iterates_bit_for_bit(name, more)
 
 
 @pytest.mark.parametrize("dims,more,split", [([40, 64, 48, 64, 64, 5], {}, 1), ([40, 64, 48, 64, 64, 5], {"step_policy": 1}, 1),
-                                             ([70, 192, 130, 200, 160, 5], {"dual_form": 1}, 2), ([60, 400, 100, 33, 36, 4], {}, 1)])
+                                             ([70, 192, 130, 200, 160, 5], {"dual_form": 1}, 2), ([60, 400, 100, 33, 36, 4], {}, 1),
+                                             ([48, 24, 40, 20, 64, 90, 5], {}, 1), ([40, 96, 12, 64, 16, 48, 6], {}, 1)])
 def test_layers_at_rest_are_left_as_they_are_bit_for_bit(dims, more, split):
     """A layer whose steps were below resolution is not looked at again until something it depends on has changed
     (launch_rest_w, launch_rest_z): the same iterates, step parameters and trial counts as without, whatever else is
@@ -267,6 +268,7 @@ def test_layers_at_rest_are_left_as_they_are_bit_for_bit(dims, more, split):
             s.tune("gemm_split", split)                  # (process-wide)
             s.init(w.W0)
             s.tune("use_floor_first", mode)
+            s.tune("use_lowrank", 2)
             s.tune("t1_refresh", 4)
             seen = []
             for k in (1, 1, 1, 1, 2, 3, 1):
@@ -405,6 +407,43 @@ def test_the_profile_books_only_what_ran():
             assert prof["t_carry_kernel"]["records"] == len([l for l in stepped if l + 1 < w.L])
             seen |= set(moved_W[:-1]) | set(moved_Z)
         assert seen == {True, False}                     # (both were met)
+    finally:
+        s.close()
+
+
+@pytest.mark.parametrize("dims", [[40, 64, 96, 128, 132, 5], [48, 64, 12, 72, 16, 96, 5], [40, 200, 160, 132, 92, 5]])
+def test_a_layer_at_rest_forms_no_gradient(dims):
+    """Whichever way the gradient of Z_l is formed (the aggregation last, in front of a wider layer; the product last; low rank, in front
+    of a narrow one), none of its launches does anything where the layer rests: the profile books those of the other layers alone."""
+    from paper_2112_09335_amd import binding
+    w = synth.make_workload("rest", 83, 1501, 4, dims, dims[-1], 4, graph="sbm", features="gaussian", avg_degree=8, frac_intra=0.8)
+    s = binding.Solver.from_workload(w, 0)
+    L, met = w.L, set()
+    # the class of a layer's last launch that forms the gradient, as the widths decide it
+    kind = {l: "gemm_nn_gradz_kernel" if dims[l + 1] <= 16 else "split_kernel<1>" if dims[l + 1] < dims[l] else "[rows,gradz]"
+            for l in range(1, L)}
+    try:
+        s.tune("use_floor_first", 2)
+        s.tune("use_lowrank", 2)
+        s.run(1)                                         # (behind the forward pass layers of at most 32 units do not rest yet)
+        moved_Z = [False] * (L + 1)
+        for it in range(1, 2 * L):
+            before, moved_W = moved_Z, [False] * (L + 2)
+            s.profile(it >= 2)
+            s.run(1)
+            prof = s.get_profile() if it >= 2 else None
+            s.profile(False)
+            trials = s.get_steps()[2]
+            moved_W = [False] + list(trials[:L] > 0)
+            moved_Z = [False] + list((trials[L:].reshape(L - 1, w.M) > 0).any(axis=1)) + [True]
+            if it < 2:
+                continue
+            runs = [l for l in range(1, L) if l + 1 == L or before[l - 1] or before[l] or before[l + 1] or moved_W[l] or moved_W[l + 1]]
+            for name in set(kind.values()):
+                booked = sum(p["records"] for full, p in prof.items() if full.endswith(name))
+                assert booked == sum(kind[l] == name for l in runs), (it, name, runs)
+            met |= {(kind[l], l in runs) for l in range(1, L)}
+        assert {(k, True) for k in kind.values()} <= met and any(not runs for _, runs in met)
     finally:
         s.close()
 
