@@ -12,6 +12,15 @@ from parity import compare_iterate, expected_ties, record_case, say, step_with_r
 pytestmark = pytest.mark.gpu
 
 
+def low_rank_launches(solver):
+    """How many gradients one more iteration keeps in low-rank form."""
+    solver.profile(True)
+    solver.run(1)
+    n = solver.get_profile()["gemm_nn_gradz_kernel"]["records"]
+    solver.profile(False)
+    return n
+
+
 def run_case(w, iters, tag, max_ties=None, tune=None):
     """Per-iteration parity of one workload.  A hidden pre-activation within fp32 rounding of zero (a ReLU tie, see
     step_with_relu_ties) is accepted only entry by entry, and in at most max_ties iterations of the case: the number
@@ -33,6 +42,8 @@ def run_case(w, iters, tag, max_ties=None, tune=None):
                 ties.append(dict(iter=k, entries=flipped))
             done = k
             say(f"[{tag}] it{k} ok, worst rel err so far {worst:.2e}")
+        if "use_lowrank" in (tune or {}):                # (the case says which path it is for)
+            assert (low_rank_launches(solver) > 0) == (tune["use_lowrank"] == 2)
         assert len(ties) <= max_ties, f"{len(ties)} iterations with ReLU ties in {iters} iterations"
     finally:
         solver.close()
@@ -243,6 +254,8 @@ def test_step_floor_tested_first_gives_the_same_iterates_bit_for_bit(name, more)
     for mode in (0, 2):
         s = binding.Solver.from_workload(w, 0)
         s.tune("use_floor_first", mode)
+        if name == "lowrank":
+            s.tune("use_lowrank", 2)
         s.run(5)
         tau, theta, trials, _ = s.get_steps()
         got.append([s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [s.get_U(), tau, theta, trials])
@@ -529,17 +542,18 @@ def test_dual_ascent_on_new_iterates_variant():
 
 
 def test_low_rank_gradient_path_and_its_stored_twin():
-    """Narrow next layers (multiples of four up to 16 units) keep the Z gradient in low-rank form; both that
-    path and the stored-gradient path must match the oracle, three layers so that both hidden layers use it."""
+    """Narrow next layers (up to 16 units) keep the Z gradient in low-rank form (at this size if asked to); both that path and the
+    stored-gradient path must match the oracle, three layers so that both hidden layers use it."""
     from paper_2112_09335_amd import binding
     w = synth.make_workload("lowrank", 21, 1500, 6, [36, 48, 12, 4], 4, 6, graph="sbm", features="gaussian",
                             avg_degree=9, frac_intra=0.8)
-    run_case(w, 6, "low-rank")
+    run_case(w, 6, "low-rank", tune={"use_lowrank": 2})
     # the gradient kernel takes 32 columns at a time: a last step of four own columns, the factor's and zeros
     run_case(synth.make_workload("lowrank", 22, 1500, 6, [36, 100, 12, 4], 4, 5, graph="sbm", features="gaussian",
-                                 avg_degree=9, frac_intra=0.8), 5, "low-rank/partial-step")
+                                 avg_degree=9, frac_intra=0.8), 5, "low-rank/partial-step", tune={"use_lowrank": 2})
     a = binding.Solver.from_workload(w, 0)
     b = binding.Solver.from_workload(w, 0)
+    a.tune("use_lowrank", 2)
     b.tune("use_lowrank", 0)
     a.run(5)
     b.run(5)
@@ -548,6 +562,7 @@ def test_low_rank_gradient_path_and_its_stored_twin():
         assert np.abs(za - zb).max() <= 1e-5 * np.abs(zb).max()
     ta, tb = a.get_steps(), b.get_steps()
     assert np.array_equal(ta[0], tb[0]) and np.array_equal(ta[1], tb[1]) and np.array_equal(ta[2], tb[2])
+    assert low_rank_launches(a) == 2 and low_rank_launches(b) == 0
     a.close()
     b.close()
 
@@ -563,7 +578,7 @@ def test_layer_by_layer_schedule_matches_the_oracle():
     w = synth.config(4, 0.002)                      # narrow-side association, low-rank gradient, hub rows
     w.hyper["schedule"] = 1
     w.hyper["dual_form"] = 1
-    run_case(w, 6, "layer-by-layer/config4/dual-form-1")
+    run_case(w, 6, "layer-by-layer/config4/dual-form-1", tune={"use_lowrank": 2})
     w = synth.make_workload("serial", 14, 900, 1, [24, 40, 12, 5], 5, 5, graph="sbm", features="gaussian",
                             avg_degree=8, frac_intra=1.0)
     w.hyper["schedule"] = 1                         # the paper's serial run: one community
@@ -740,7 +755,7 @@ def test_hub_rows_and_hub_segments_are_split_inside_the_sweep():
     deg = np.bincount(w.src, minlength=w.N) + np.bincount(w.dst, minlength=w.N)
     assert np.sort(deg)[-3] > 500
     # layer 1: C_2 >= C_1, so G_2 W_2^T is aggregated at width 32 with the penalty epilogue; layer 2: low-rank form
-    run_case(w, 6, "hubs/epilogue-aggregation+low-rank")
+    run_case(w, 6, "hubs/epilogue-aggregation+low-rank", tune={"use_lowrank": 2})
     # widths that are no multiple of four (one column per lane) through the same path
     base = synth.make_workload("hub", 33, 2000, 4, [20, 30, 30, 5], 5, 6, graph="sbm", features="gaussian",
                                avg_degree=8, frac_intra=0.8)
@@ -754,7 +769,7 @@ def test_hub_rows_and_hub_segments_are_split_inside_the_sweep():
     base = synth.make_workload("hub", 35, 2400, 6, [24, 40, 8], 8, 6, graph="dcsbm", features="gaussian",
                                avg_degree=10, frac_intra=0.8, exponent=2.5)
     w = synth.add_hubs(base, 36, 3, 650, 0.7)
-    run_case(w, 6, "hubs/low-rank-two-layers")
+    run_case(w, 6, "hubs/low-rank-two-layers", tune={"use_lowrank": 2})
     run_case(w, 5, "hubs/stored-gradient-two-layers", tune=dict(use_lowrank=0))
 
 
@@ -815,7 +830,7 @@ def test_more_communities_than_a_workgroup_keeps_step_parameters_for():
     """The Z-step and carry kernels keep 1/theta of up to 1024 communities in LDS and look the parameters up in memory
     beyond that: 1100 communities of a few nodes each, on the low-rank path (two layers) and on the stored-gradient
     path (three layers)."""
-    run_case(synth.config(4, 0.002, M=1100), 3, "many-communities/config4")       # N = 4000
+    run_case(synth.config(4, 0.002, M=1100), 3, "many-communities/config4", tune={"use_lowrank": 2})       # N = 4000
     run_case(synth.config(3, 0.008, M=1100), 3, "many-communities/config3")       # N = 1600, three layers
 
 
