@@ -485,6 +485,24 @@ def test_the_column_tile_knob_reaches_captured_iterations():
         b.close()
 
 
+# below the staged sizes, one piece of 8 MB that is not full, full, two with the second one row, three
+@pytest.mark.parametrize("N", [65535, 65536, 98305, 131072, 131073, 262145])
+def test_large_readouts_come_out_whole(N):
+    """64 bytes a row: what is read is what was set, through whichever pieces of pinned memory it leaves (from the second on)."""
+    from paper_2112_09335_amd import binding
+    s = binding.Solver(0)
+    s.build_graph(N, np.zeros(0, np.int32), np.zeros(0, np.int32), 1, np.zeros(N, np.int32))
+    s.set_model([2, 16, 3], **synth.DEFAULT_HYPER)
+    s.set_workspace()
+    s.set_data(np.ones((N, 2), np.float32), np.zeros(N, np.int32))
+    s.init([np.ones((2, 16), np.float32), np.ones((16, 3), np.float32)])
+    Z = np.random.default_rng(N).standard_normal((N, 16)).astype(np.float32)
+    s.set_state(Z=[Z, None])
+    for _ in range(3):
+        assert np.array_equal(s.get_Z(1), Z)
+    s.close()
+
+
 def test_inference_matches_the_oracle_between_iterations():
     from paper_2112_09335_amd import binding
     w = synth.config(3, 0.01)
