@@ -106,6 +106,7 @@ struct cadmm_ctx {
     int32_t* gates = nullptr;          // [L]: whether any community of layer l = 1..L-1 takes a Z step (floor_first)
     int32_t* run_w = nullptr;          // [L+1] each: whether layer l's W and Z steps are worth forming (launch_rest_w)
     int32_t* run_z = nullptr;
+    int32_t* left_g = nullptr;         // [L+1]: whether G_l has been left since the forward pass behind which the layers rest
     int32_t* forward_bad = nullptr;    // a hidden pre-activation of the forward pass is not finite
     LayerScalars* scalars = nullptr;   // [L+1]
     int32_t* status = nullptr;
@@ -395,6 +396,7 @@ size_t layout(cadmm_ctx* c, char* base) {
     c->gates = b.take<int32_t>(L);
     c->run_w = b.take<int32_t>(L + 1);
     c->run_z = b.take<int32_t>(L + 1);
+    c->left_g = b.take<int32_t>(L + 1);
     c->forward_bad = b.take<int32_t>(1);
     c->scalars = b.take<LayerScalars>(L + 1);
     c->status = b.take<int32_t>(4);
@@ -976,7 +978,7 @@ void sweep(cadmm_ctx* c) {
         const int L = c->L;
         base_eval(c);
         c->rest = c->rest_fresh && tracks_rest(c);
-        if (c->rest) launch_rest_w(c->stream, L, c->unitsW, c->gates, c->run_w, c->run_z);
+        if (c->rest) launch_rest_w(c->stream, L, c->unitsW, c->gates, c->left_g, c->run_w, c->run_z);
         for (int l = 1; l <= L; ++l) w_update(c, l);
         if (c->rest) launch_rest_z(c->stream, L, c->unitsW, c->run_z);
         // Ascending l keeps the Z update Jacobi although Z_l is overwritten in place: layer l reads Z_{l+1}^k
@@ -1446,7 +1448,9 @@ int cadmm_init(cadmm_ctx* c, const float* const* W0) {
     launch_fill_units(s, c->unitsW, L, (double)c->tau0);
     launch_fill_units(s, c->unitsZ, (L - 1) * c->hg.M, (double)c->theta0);
     launch_fill_units(s, c->unitsF, c->hg.M, (double)c->rho);
-    if (noted) launch_rest_start(s, L, c->hg.M, c->unitsW, c->unitsZ, c->gates, c->forward_bad);
+    uint64_t ungated = 0;
+    for (int l = 1; l < L; ++l) ungated |= (uint64_t)(z_search(c, l).gate == nullptr) << l;
+    if (noted) launch_rest_start(s, L, c->hg.M, c->unitsW, c->unitsZ, c->gates, ungated, c->left_g, c->forward_bad);
     c->rest_fresh = noted;
     HIP_TRY(c, hipStreamSynchronize(s));                           // W0 host buffers may be freed by the caller
     c->iter = 0;

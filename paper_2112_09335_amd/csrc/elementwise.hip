@@ -339,18 +339,24 @@ __global__ __launch_bounds__(256) void w_begin_kernel(const double* __restrict__
 
 // See launch_rest_w, launch_rest_z; thread l - 1 takes layer l (at most 64 of them).
 __global__ __launch_bounds__(64) void rest_w_kernel(int L, const Unit* __restrict__ unitsW, const int32_t* __restrict__ moved,
-                                                    int32_t* __restrict__ run_w, int32_t* __restrict__ run_z) {
+                                                    int32_t* __restrict__ left_g, int32_t* __restrict__ run_w, int32_t* __restrict__ run_z) {
     const int l = (int)threadIdx.x + 1;
     if (l > L) return;
     const bool here = l == L || moved[l] != 0, before = l > 1 && moved[l - 1] != 0, after = l + 1 >= L || moved[l + 1] != 0;
-    run_w[l] = here || before || !unitsW[l - 1].skip;
+    // G_l is not there yet, and layer l - 1 may form its gradient
+    const bool wanted = l > 1 && !left_g[l] && ((l > 2 && moved[l - 2] != 0) || !unitsW[l - 2].skip);
+    const bool run = here || before || !unitsW[l - 1].skip || wanted;
+    run_w[l] = run;
+    if (run) left_g[l] = 1;
     run_z[l] = here || before || after;
 }
 __global__ __launch_bounds__(256) void rest_start_kernel(int L, int M, Unit* __restrict__ unitsW, Unit* __restrict__ unitsZ,
-                                                         int32_t* __restrict__ moved, const int32_t* __restrict__ bad) {
+                                                         int32_t* __restrict__ moved, uint64_t ungated, int32_t* __restrict__ left_g,
+                                                         const int32_t* __restrict__ bad) {
     const int rest = *bad == 0;
     for (int i = threadIdx.x; i < L - 1; i += 256) {
-        moved[i + 1] = !rest;
+        moved[i + 1] = !rest || (ungated >> (i + 1) & 1) != 0;
+        left_g[i + 1] = 0;
         unitsW[i].done = unitsW[i].skip = rest;
     }
     for (int i = threadIdx.x; i < (L - 1) * M; i += 256) unitsZ[i].done = unitsZ[i].skip = rest;
@@ -1396,12 +1402,13 @@ void launch_w_begin(hipStream_t s, const double* partials, int n_partials, Unit*
     else hipLaunchKernelGGL((w_begin_kernel<false>), dim3(1), dim3(256), 0, s, partials, n_partials, unit, sp, gate);
 }
 
-void launch_rest_start(hipStream_t s, int L, int M, Unit* unitsW, Unit* unitsZ, int32_t* moved, const int32_t* bad) {
-    hipLaunchKernelGGL(rest_start_kernel, dim3(1), dim3(256), 0, s, L, M, unitsW, unitsZ, moved, bad);
+void launch_rest_start(hipStream_t s, int L, int M, Unit* unitsW, Unit* unitsZ, int32_t* moved, uint64_t ungated, int32_t* left_g,
+                       const int32_t* bad) {
+    hipLaunchKernelGGL(rest_start_kernel, dim3(1), dim3(256), 0, s, L, M, unitsW, unitsZ, moved, ungated, left_g, bad);
 }
 
-void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* run_w, int32_t* run_z) {
-    hipLaunchKernelGGL(rest_w_kernel, dim3(1), dim3(64), 0, s, L, unitsW, moved, run_w, run_z);
+void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* left_g, int32_t* run_w, int32_t* run_z) {
+    hipLaunchKernelGGL(rest_w_kernel, dim3(1), dim3(64), 0, s, L, unitsW, moved, left_g, run_w, run_z);
 }
 
 void launch_rest_z(hipStream_t s, int L, const Unit* unitsW, int32_t* run_z) {

@@ -242,13 +242,15 @@ void launch_risk(hipStream_t s, const float* ZL, const int32_t* labels, int64_t 
 // again, bit for bit, as long as nothing it depends on has changed, and nothing of it is formed anew.  moved[l], l = 1..L-1:
 // whether any community of layer l took a Z step in the last iteration (ZTrialArgs::moved).
 // launch_rest_w, before the W steps: run_w[l] = 0 where layer l did not step last time and neither Z_l nor Z_{l-1} (and with it T_l
-// and H_l) has moved since.  launch_rest_z, behind them: run_z[l] = 0 where Z_{l-1}, Z_l and Z_{l+1} have not moved and W_l
+// and H_l) has moved since, unless layer l - 1 may need G_l and it has not been left since the forward pass (left_g).  launch_rest_z, behind them: run_z[l] = 0 where Z_{l-1}, Z_l and Z_{l+1} have not moved and W_l
 // and W_{l+1} have not stepped now.  Both are 1 wherever that reaches the last layer, whose Z always moves.
 // launch_rest_start, behind a forward pass: Z_l = relu(T_l) to the bit, so that the gradients of the hidden layers are exactly zero
-// and none of them would step; moved and the units are left as an iteration that finds that out leaves them.  Unless *bad:
+// and none of them would step; moved and the units are left as an iteration that finds that out leaves them (ungated: bit l for a
+// layer that has no gate and says that it moved whether it did or not), but no G_l is.  Unless *bad:
 // the pre-activations of a hidden layer are not all finite (times zero they would be no numbers).
-void launch_rest_start(hipStream_t s, int L, int M, Unit* unitsW, Unit* unitsZ, int32_t* moved, const int32_t* bad);
-void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* run_w, int32_t* run_z);
+void launch_rest_start(hipStream_t s, int L, int M, Unit* unitsW, Unit* unitsZ, int32_t* moved, uint64_t ungated, int32_t* left_g,
+                       const int32_t* bad);
+void launch_rest_w(hipStream_t s, int L, const Unit* unitsW, const int32_t* moved, int32_t* left_g, int32_t* run_w, int32_t* run_z);
 void launch_rest_z(hipStream_t s, int L, const Unit* unitsW, int32_t* run_z);
 // unit.g = ||gradW||^2, unit.bnorm = ||W||^2 from block sums (pairs), applies the step floor, starts the search.
 // gate (may be null): where *gate is 0 the unit stays as it is (launch_rest_w).

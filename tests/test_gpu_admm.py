@@ -366,6 +366,29 @@ def test_process_wide_knobs_turned_during_a_run(key, values, who, graph):
         assert np.array_equal(a, b)
 
 
+# layers of fewer than 2^24 entries look at the step floor with the search, larger ones before it: in front of, between, and two
+# layers before one that rests
+@pytest.mark.parametrize("dims", [[8, 40, 424, 5], [8, 40, 424, 420, 5], [8, 424, 40, 424, 5], [8, 424, 36, 40, 424, 5]])
+@pytest.mark.parametrize("M", [1, 3])
+def test_a_run_owes_nothing_to_the_run_before_it(M, dims):
+    """A layer that rests from the forward pass on leaves no gradient for the layer in front of it: that one must not take what an
+    earlier run from other weights has left for one."""
+    from paper_2112_09335_amd import binding
+    w = synth.make_workload("again", 87, 40000, M, dims, dims[-1], 3, graph="sbm", features="gaussian", avg_degree=4, frac_intra=0.8 if M > 1 else 1.0)
+    got = []
+    for mode in (0, 1):
+        s = binding.Solver.from_workload(w, 0)
+        s.tune("use_floor_first", mode)
+        for first in (True, False):
+            s.init([W * np.float32(3.0) for W in w.W0] if first else w.W0)
+            s.run(4)
+        got.append([s.get_W(l) for l in range(1, w.L + 1)] + [s.get_Z(l) for l in range(1, w.L + 1)] + [s.get_U(), *s.get_steps()])
+        assert s.eval()["status"] == 0
+        s.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+
+
 @pytest.mark.parametrize("entry", [np.inf, np.nan, 3e38])
 @pytest.mark.parametrize("split", [1, 2])
 def test_layers_do_not_rest_on_numbers_that_are_not_finite(entry, split):
