@@ -897,8 +897,8 @@ __device__ __forceinline__ void pair_epilogue(floatx16 (&acc)[kPairTM][kPairTN],
 // compute unit, one's epilogue beside the other's products.  Against one workgroup of 256 x 256, both operands in LDS, the large
 // product is as fast and the mid-sized one is not cut into three rounds and a bit: us for 500000 x 512 x 512 and 200000 x 256
 // x 256, bf16 split 1590 and 182, 256 x 256 946 and 195, 128 x 128 1090 and 186, this one 950 and 122.  The counts of RowRange cost
-// them 1 % (its words read, a barrier that is there anyway), 5 % where the result's are left too; a tile on triples takes 1.6 times as
-// long (of 500000 x 512 x 512 with epilogue 4, all of them: 1940 us, on pairs 1210).
+// them 1 % (its words read, a barrier that is there anyway), 4 % where the result's are left too; tiles on triples take as long as
+// those of the bf16 kernel (500000 x 512 x 512 with epilogue 4, all of them 1830 us, the bf16 kernel 1795, on pairs 1210).
 template <int EPI>
 __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_nn_pair_kernel(
     const float* __restrict__ A, const float* __restrict__ B, const unsigned short* __restrict__ planes, const int* __restrict__ columns,
@@ -1092,23 +1092,22 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
             stash_split<8>(D, 512, (r >> 5) * kTripleSub + (p >> 1) * 1536 + ((p & 1) * 32 + ((r & 31) ^ (p << 2))) * 8, x);
         };
         float rb[kPairTN][8];
-        auto fetch_b = [&](int half) {
+        auto fetch_b = [&](int half, int j) {
             const float* const p = B + (int64_t)half * 16 * C;
             if (half * 16 + 16 <= K) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e)
-#pragma unroll
-                    for (int j = 0; j < kPairTN; ++j) rb[j][e] = (p + (int64_t)e * C)[boff[j]];
+                for (int e = 0; e < 8; ++e) rb[j][e] = (p + (int64_t)e * C)[boff[j]];
             } else {                                     // past K: the last row again, A is zero there
                 const int left = K - half * 16 - 8 * lk;
-                for (int e = 0; e < 8; ++e)
 #pragma unroll
-                    for (int j = 0; j < kPairTN; ++j) rb[j][e] = p[boff[j] + (int64_t)(e < left ? e : left - 1) * C];
+                for (int e = 0; e < 8; ++e) rb[j][e] = p[boff[j] + (int64_t)(e < left ? e : left - 1) * C];
             }
         };
         if (tid < kPairRows) s_back[tid] = 0;
 #pragma unroll
         for (int i = 0; i < AP; ++i) fetch(0, i);
+#pragma unroll
+        for (int j = 0; j < kPairTN; ++j) fetch_b(0, j);
 #pragma unroll
         for (int i = 0; i < AP; ++i) stash3(smem, i);
         if (steps > 1)
@@ -1128,30 +1127,34 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
             }
 #pragma unroll 1
             for (int kc = 0; kc < 2; ++kc) {
-                fetch_b(2 * kt + kc);
-                intx4 b[kPairTN][3];
+                const unsigned short* const p0 = S + kc * 1536 + (lk * 32 + (li ^ ((2 * kc + lk) << 2))) * 8;
 #pragma unroll
-                for (int j = 0; j < kPairTN; ++j)
+                for (int j = 0; j < kPairTN; ++j) {      // (a column tile's parts at a time, A's read once for each: nothing spills)
+                    intx4 b[3];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         unsigned h, m, l;
                         split3_pair(rb[j][2 * e], rb[j][2 * e + 1], h, m, l);
-                        b[j][0][e] = (int)h;
-                        b[j][1][e] = (int)m;
-                        b[j][2][e] = (int)l;
+                        b[0][e] = (int)h;
+                        b[1][e] = (int)m;
+                        b[2][e] = (int)l;
                     }
+                    fetch_b(2 * kt + kc + 1, j);
+                    asm volatile("" ::: "memory");     // (A's parts are not kept from one column tile to the next)
 #pragma unroll
-                for (int i = 0; i < kPairTM; ++i) {
-                    const unsigned short* const p = S + i * kTripleSub + kc * 1536 + (lk * 32 + (li ^ ((2 * kc + lk) << 2))) * 8;
-                    bf16x8 a3[3];
+                    for (int i0 = 0; i0 < kPairTM; i0 += 2) {
+                        bf16x8 a3[2][3];
 #pragma unroll
-                    for (int q = 0; q < 3; ++q) a3[q] = *reinterpret_cast<const bf16x8*>(p + 512 * q);
-                    constexpr int P[6] = {2, 0, 1, 1, 0, 0}, Q[6] = {0, 2, 1, 0, 1, 0};          // smallest terms first
+                        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                    for (int t = 0; t < 6; ++t)
+                            for (int q = 0; q < 3; ++q) a3[i][q] = *reinterpret_cast<const bf16x8*>(p0 + (i0 + i) * kTripleSub + 512 * q);
+                        constexpr int P[6] = {2, 0, 1, 1, 0, 0}, Q[6] = {0, 2, 1, 0, 1, 0};          // smallest terms first
 #pragma unroll
-                        for (int j = 0; j < kPairTN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3[P[t]], __builtin_bit_cast(bf16x8, b[j][Q[t]]), acc[i][j], 0, 0, 0);
+                        for (int t = 0; t < 6; ++t)
+#pragma unroll
+                            for (int i = 0; i < 2; ++i)
+                                acc[i0 + i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a3[i][P[t]], __builtin_bit_cast(bf16x8, b[Q[t]]), acc[i0 + i][j], 0, 0, 0);
+                    }
                 }
             }
         }
@@ -1252,9 +1255,8 @@ __global__ __launch_bounds__(64 * kPairWaves) __attribute__((amdgpu_waves_per_eu
 // multiply-adds, the rows of W^T and the block's rows of SG from LDS), for the product and for the row sums of the search, which
 // then reads neither Z nor T.  The kernel is bound by reading those two, with the vector work and the products behind it: the
 // products take v_mfma_f32_16x16x4_f32 (C <= 16: a 32 x 32 instruction's second half would be zeros) and both operands from the tiles
-// that the gradient is formed with, W as the columns of W^T.  2000000 x 256 x 16: 1035 us with v_mfma_f32_32x32x2_f32 on a copy of W's
-// rows in LDS (five spilled registers), 833 so, 5.2 TB/s of Z, T, SG and out; the same
-// sums to the bit.
+// that the gradient is formed with, W as the columns of W^T.  2000000 x 256 x 16: 985 us with v_mfma_f32_32x32x2_f32 on [W; W^T W],
+// which a launch of its own made, 833 so, 5.2 TB/s of Z, T, SG and out.
 constexpr int kSgLd = kLowRankMax + 4;            // row stride of SG in LDS: the eight rows a wavefront reads at once hit different banks
 template <bool GATED>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void gemm_nn_gradz_kernel(const float* __restrict__ Zl, const float* __restrict__ Tl,
@@ -1957,7 +1959,7 @@ bool gemm_nn_pair_form(int K, int C) { return K >= 64 && C >= kPairLeast; }
 // sums and 150 tiles on, or fewer tiles of longer sums.  us with bf16 and with pairs, that launch with them: 20000 x 256 x 256 (157
 // tiles) 24.5 and 21.4, 12000 x 128 x 512 (188) 17.8 and 17.1, 8000 x 512 x 512 (126) 36 and 32, 8000 x 256 x 512 21.0 and
 // 21.4, 12000 x 256 x 256 (94) 17.3 and 20.2, 30000 x 64 x 300 (470) 15.6 and 18.2, 200000 x 256 x 256 163 and 124, 13752 x 767
-// x 1000 149 and 83.
+// x 1000 149 and 83.  (Every tile on pairs.  One on triples is as fast as the bf16 kernel's to a tenth.)
 bool gemm_nn_pair(int64_t n, int K, int C) {
     if (!gemm_nn_pair_form(K, C) || g_split == 0) return false;
     const int64_t tiles = ((n + kPairRows - 1) / kPairRows) * gemm_nn_pair_tiles(C);
