@@ -1118,7 +1118,13 @@ hipError_t record_op(cadmm_ctx* c) {
 }
 
 void drop_graphs(cadmm_ctx* c) {
+    bool waited = false;
     for (auto& slot : c->graphs) {
+        if (slot.exec && !waited) {                  // the last iterations may still be on their way
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            if (hipStreamIsCapturing(c->stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone) (void)hipStreamSynchronize(c->stream);
+            waited = true;
+        }
         if (slot.exec) (void)hipGraphExecDestroy(slot.exec);
         slot.exec = nullptr;
         slot.tried = false;
