@@ -720,13 +720,15 @@ def test_product_on_pairs_of_scaled_rows_and_columns(pairs_everywhere, N, K, C):
     assert np.all(np.abs(got - np.maximum(exact, 0.0)) <= 2e-6 * mag)
 
 
-@pytest.mark.parametrize("N,K,C", [(128, 95, 192), (300, 512, 256), (257, 129, 257), (640, 1000, 513)])
-@pytest.mark.parametrize("kind", ["even", "outlier", "opposed", "one-hot", "tiny columns", "few", "one row", "one column"])
+# (the aggregation of 40000 rows in one community goes in tiles of 32 columns: nineteen words a row)
+@pytest.mark.parametrize("kind,N,K,C", [(kind, *shape) for kind in ("even", "outlier", "opposed", "one-hot", "tiny columns", "few", "one row", "one column")
+                                        for shape in ((128, 95, 192), (300, 512, 256), (257, 129, 257), (640, 1000, 513))] +
+                         [(kind, 40000, 608, 130) for kind in ("even", "opposed", "one row")])
 def test_product_on_pairs_of_unlike_columns_and_rows(pairs_everywhere, kind, N, K, C):
     """Where the largest entries of a row meet zeros of a column, or small ones (a feature 1e8 times the others that has no weight,
     features as much larger as their weights are smaller, weights that pick one feature), parts of a row's largest entry are not
-    parts of what a result is made of.  Such tiles of 128 x 256 results come from operands in all 24 bits, to the bit as below the sizes
-    from which products run on pairs; the others stay on pairs."""
+    parts of what a result is made of.  Such tiles of 128 x 256 results come from operands in all 24 bits, to the bit as the kernel-level
+    product; the others stay on pairs."""
     rng = np.random.default_rng(N + K + C)
     X, W1 = rng.standard_normal((N, K)), rng.standard_normal((K, C))
     rows, cols = slice(0, N), slice(0, C)                # of the results that are not for pairs
@@ -754,12 +756,12 @@ def test_product_on_pairs_of_unlike_columns_and_rows(pairs_everywhere, kind, N, 
         W1[5, 0] = 1e9
         cols = slice(0, min(C, 256))
     X, W1 = X.astype(np.float32), W1.astype(np.float32)
+    import torch
     from paper_2112_09335_amd import binding
     got = first_layer(X, W1)
-    probe = binding.Solver(device=-1)
-    probe.tune("gemm_split", 1)                          # (process-wide; pairs_everywhere sets it back)
-    probe.close()
-    triples = first_layer(X, W1)
+    s = binding.Solver(0)
+    triples = np.maximum(s.op_transform(torch.from_numpy(X).cuda(), torch.from_numpy(W1).cuda()).cpu().numpy(), 0.0)       # (has no counts)
+    s.close()
     exact, mag = X.astype(np.float64) @ W1.astype(np.float64), np.abs(X).astype(np.float64) @ np.abs(W1).astype(np.float64)
     assert np.all(np.abs(got - np.maximum(exact, 0.0)) <= 2e-6 * mag)
     assert np.array_equal(got[rows, cols], triples[rows, cols])
