@@ -279,7 +279,7 @@ const char* cadmm_profile_class_name(int32_t cls);
  * "t1_refresh" (per context): the pre-activations A~ Z_{l-1} W_l are carried from one iteration to the
  * next (through the W step, and through the segment products of the Z step) and formed anew every
  * this many iterations (default 16; 0 = always form them anew).
- * Process-wide: "spmm_tile_cols": feature columns handled per
+ * Process-wide (every context follows with its next call): "spmm_tile_cols": feature columns handled per
  * aggregation launch (0 = all at once); "spmm_xcd_remap": 1 = each XCD walks one contiguous slice of the aggregation's
  * work list, whole communities one after the other (default), 0 = workgroups in plain order;
  * "gemm_split": 1 = products with more than 32 result columns split both operands for the 16-bit matrix cores and accumulate
