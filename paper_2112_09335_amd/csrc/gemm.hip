@@ -1955,15 +1955,18 @@ int nn_tile(int64_t n, int C, int split) {
 
 // (below 64 long sums the pairs are the less accurate split)
 bool gemm_nn_pair_form(int K, int C) { return K >= 64 && C >= kPairLeast; }
-// A workgroup's tile is larger than the bf16 kernels' and B takes a launch of its own to be split (5 us): pairs pay from 128 long
-// sums and 150 tiles on, or fewer tiles of longer sums.  us with bf16 and with pairs, that launch with them: 20000 x 256 x 256 (157
-// tiles) 24.5 and 21.4, 12000 x 128 x 512 (188) 17.8 and 17.1, 8000 x 512 x 512 (126) 36 and 32, 8000 x 256 x 512 21.0 and
-// 21.4, 12000 x 256 x 256 (94) 17.3 and 20.2, 30000 x 64 x 300 (470) 15.6 and 18.2, 200000 x 256 x 256 163 and 124, 13752 x 767
-// x 1000 149 and 83.  (Every tile on pairs.  One on triples is as fast as the bf16 kernel's to a tenth.)
+// A workgroup's tile is larger than the bf16 kernels' (columns past C cost as much as others), B takes a launch of its own to be split
+// (5 us), and both weigh the more the shorter the sums: pairs pay from 3.3e6 results and, for sums shorter than 512, 3.2e11 / K^2 on.  us with
+// bf16 and with pairs, that launch with them (forward product): 10000 x 512 x 512 48.9 and 40.7, 24000 x 256 x 256 34.5 and 29.5,
+// 20000 x 256 x 256 24.5 and 21.4, 80000 x 128 x 512 90 and 82, 160000 x 256 x 256 148 and 115, 13752 x 767 x 1000 149 and 84; below the line
+// 10000 x 449 x 289 31 and 40, 10000 x 800 x 129 38 and 56, 10000 x 128 x 512 19.6 and 24.5, 40000 x 128 x 289 36 and 46, 12000 x 256 x 256
+// 17.3 and 20.2.  Of 252 shapes (6000 to 160000 rows, 128 to 800 long sums, 129 to 1000 columns) it sends 140 to pairs, at 0.55 to 1.07 of
+// bf16's time, and keeps four from them that would gain a tenth.  (Every tile on pairs; with none of them, 1.1 to 1.7 of bf16's time, the least in
+// the largest.)
 bool gemm_nn_pair(int64_t n, int K, int C) {
     if (!gemm_nn_pair_form(K, C) || g_split == 0) return false;
-    const int64_t tiles = ((n + kPairRows - 1) / kPairRows) * gemm_nn_pair_tiles(C);
-    return g_split == 2 || (K >= 128 && (tiles >= 150 || tiles * K >= 60000));
+    const double results = (double)n * C;
+    return g_split == 2 || (K >= 128 && results >= 3.3e6 && results * K * K >= 3.2e11);
 }
 int gemm_nn_pair_tiles(int C) { return (C + kPairCols - 1) / kPairCols; }
 size_t gemm_nn_pair_planes(int K, int C) { return (size_t)((K + kPairK - 1) / kPairK) * ((C + 31) / 32) * kPairSub; }
